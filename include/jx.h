@@ -138,9 +138,11 @@ typedef struct {
      * caller's stream around the stage's launches (summed over query slices) */
     float rotate_ms, prep_ms, beam_ms, rerank_ms;
     /* the beamSearch kernel instance the call launched, as a profiler prints it:
-     * "beam_search_kernel<KIND,T,CPL,NREG,QB>" -- distance provider (0 uint8, 1 float32, 2 4-bit codes, 3 1-bit
+     * "beam_search_kernel<KIND,T,CPL,NREG,QB,MODE>" -- distance provider (0 uint8, 1 float32, 2 4-bit codes, 3 1-bit
      * codes, 4 binary16), lanes per record, 16-byte chunks per lane, frontier registers per lane (64 entries
-     * each), query bits; "beam_search_pair_kernel<...>" = two expansions per round */
+     * each), query bits, form (0 general, 1 tag table and R <= 64, 2 the same with more records in flight for small
+     * batches); "beam_search_pair_kernel<...>" = two expansions per round; "beam_search_ahead_kernel<...>" = a team of
+     * wavefronts per query (small batches, long records) */
     char beam_kernel[96];
 } jx_stats;
 

@@ -78,6 +78,13 @@ constexpr int mirror_entries() {
 // registers and none of the lower ones, so only register r's lanes have to compare against it: the candidates are
 // broadcast one by one per register, which makes the step cost O(inserted) instead of O(inserted x registers).
 // One LDS scatter / gather applies the permutation; the tail beyond L is dropped.
+// That chain of dependent LDS reads is about 1,300 cycles.  Up to MERGE_FEW candidates (an expansion inserts 4 to 7 on
+// average) go in one by one without LDS instead, about 150 cycles each; broadcasting and ranking them with ballots but
+// moving the frontier through LDS once took 1,400.  With three and more registers per lane an insertion moves them all,
+// and the chain is the shorter way (L = 256, 10,000 queries, ten one by one: 1256 -> 1341 us).
+template <int NREG>
+constexpr int MERGE_FEW = NREG == 1 ? 10 : (NREG == 2 ? 8 : 0);  // frontier_merge: candidates inserted one by one
+
 template <int NREG>
 __device__ __forceinline__ void frontier_merge(uint64_t (&fk)[NREG], uint64_t* fr, int& count, uint64_t& worst, const int L,
                                                const uint64_t ck, const int n, const int lane) {
@@ -87,7 +94,45 @@ __device__ __forceinline__ void frontier_merge(uint64_t (&fk)[NREG], uint64_t* f
     // worst = entry L - 1 of the frontier with the flag bit set (all ones while the frontier is not full): kept in
     // a register from merge to merge, so that the usual expansion, which inserts nothing, reads no LDS here
     bool beats = lane < n && ckm < worst;
-    if (ballot(beats) == 0ull) return;  // nothing enters the frontier (the common case late in a search)
+    uint64_t todo = ballot(beats);
+    if (todo == 0ull) return;  // nothing enters the frontier (the common case late in a search)
+    if (__builtin_popcountll(todo) <= MERGE_FEW<NREG>) {
+        // few candidates (the usual case): one after the other, ranked with a ballot per frontier register and moved
+        // in with a one-lane shift; the mirror is written and not waited for
+        int n_ins = 0;
+        while (todo) {
+            const int j = __builtin_ctzll(todo);
+            todo &= todo - 1ull;
+            const uint64_t s = readlane64(ckm, j);
+            int rank = 0;
+            uint64_t same = 0;
+#pragma unroll
+            for (int r = 0; r < NREG; r++) {
+                rank += __builtin_popcountll(ballot((fk[r] | 1ull) < s));
+                same |= ballot((fk[r] | 1ull) == s);
+            }
+            if (same) continue;  // in the frontier already (the visited table forgot it)
+            n_ins++;
+#pragma unroll
+            for (int r = NREG - 1; r >= 0; r--) {
+                const uint64_t in = r ? readlane64(fk[r ? r - 1 : 0], 63) : 0ull;
+                const uint64_t up = wave_shift_up(fk[r], in);
+                const int p = r * 64 + lane;
+                fk[r] = p < rank ? fk[r] : (p == rank ? s - 1ull : up);
+            }
+        }
+        if (n_ins == 0) return;
+#pragma unroll
+        for (int r = 0; r < NREG; r++) {
+            if (r * 64 + lane >= L) fk[r] = JX_EMPTY_KEY;  // truncate to the beam width
+            fr[r * 64 + lane] = fk[r];
+            if (r == (L - 1) >> 6) worst = readlane64(fk[r], (L - 1) & 63) | 1ull;
+        }
+        wave_sync();
+        count = count + n_ins < L ? count + n_ins : L;
+        return;
+    }
+    // many (the first expansions of a search): all ranks at once by binary search in the mirror
     uint32_t pos = 0;
 #pragma unroll
     for (int step = MIR / 2; step >= 1; step >>= 1)
@@ -134,7 +179,9 @@ __device__ __forceinline__ void frontier_merge(uint64_t (&fk)[NREG], uint64_t* f
     }
     wave_sync();
     count = count + n_ins < L ? count + n_ins : L;
-    worst = fr[L - 1] | 1ull;
+#pragma unroll
+    for (int r = 0; r < NREG; r++)
+        if (r == (L - 1) >> 6) worst = readlane64(fk[r], (L - 1) & 63) | 1ull;
 }
 
 // The expansion list of one query (Alg. 1's set V; what Alg. 4 hands to robustPrune), kept in LDS in expansion order:
@@ -187,14 +234,34 @@ __device__ __forceinline__ void write_visited(const BeamArgs& a, const int64_t q
     }
 }
 
+// Records in flight per lane group of the wide instances, for batches of at most two wavefronts per SIMD: 48 records at
+// once (a row has about 36 new neighbours), in at most 160 registers
+template <int T, int CPL>
+constexpr int wide_u() {
+    constexpr int G = 64 / T;
+    constexpr int want = (48 + G - 1) / G, fit = 160 / (4 * CPL);
+    return want < fit ? want : fit;
+}
+
+// Not where the usual form covers a row already (four lanes per record)
+template <int T, int CPL>
+constexpr bool has_wide() {
+    return 64 / T * wide_u<T, CPL>() > 64 / T * (8 / CPL > 0 ? 8 / CPL : 1) && T > 4;
+}
+// Beyond 1,536 queries the registers of the wide instances cost more residency than the loads in flight gain.  L = 128,
+// 1,000 queries: d = 128 float32 343 -> 270 us, d = 960 2220 -> 1930, its 4-bit codes 679 -> 599; as insertion search
+// (expansion lists) d = 960, 1,060 points 1233 -> 940 us, 1,325 points 1405 -> 1240, 1,656 points 1785 -> 1815.
+static constexpr long long WIDE_MAX_QUERIES = 1536;
+
 // One query per wavefront, WPB wavefronts (queries) per workgroup; TILED selects the element-strided loads of the
 // load ablation (jx_distance.h); VIS returns the expansion list instead of the frontier (BeamArgs::vis_cap).
-template <int KIND, int T, int CPL, int NREG, int QB, int WPB, bool TILED, bool VIS = false>
+template <int KIND, int T, int CPL, int NREG, int QB, int WPB, bool TILED, bool VIS = false, int MODE = 0>
 __device__ __forceinline__ void beam_search_body(const BeamArgs& a) {
     constexpr int G = 64 / T;
     constexpr int UMAX = (KIND == K_RQ1) ? JX_UMAX_RQ1 : ((KIND == K_U8) ? JX_UMAX_EXACT : ((KIND == K_RQ4) ? JX_UMAX_RQ4 : 8));  // 16-byte loads in flight per lane (the 1-bit path keeps its bit planes in registers)
     constexpr int U0 = (UMAX / CPL) > 0 ? (UMAX / CPL) : 1;
-    constexpr int U = U0 < (64 / G) ? U0 : (64 / G);  // records in flight per lane group
+    constexpr bool FAST = MODE != 0;
+    constexpr int U = MODE == 2 ? wide_u<T, CPL>() : (U0 < (64 / G) ? U0 : (64 / G));  // records in flight per lane group
     constexpr int FCAP = mirror_entries<NREG>();  // entries of the LDS mirror of the frontier
     extern __shared__ __align__(16) unsigned char smem[];
     const int wave = threadIdx.x >> 6;
@@ -251,6 +318,77 @@ __device__ __forceinline__ void beam_search_body(const BeamArgs& a) {
     count = 1;
     evals = 1;
 
+    if constexpr (FAST) {
+        // tag table, rows of one 64-entry block: the same loop without the general form's branches (a lone wavefront
+        // issues an instruction every four to five cycles, so they are latency), and with the row of the second closest
+        // unexpanded entry read ahead, behind the gathers of this expansion: it is the next one to be expanded unless a
+        // new candidate overtakes it.  Cycles of an expansion, 128-byte vectors, L = 32, 1,000 queries: select and row
+        // 480, filter 330, gather and distances 1,250, merge 1,220.  With the one-by-one merge (frontier_merge), before
+        // -> after: N = 1M, L = 16, one query 37.6 -> 33.0 us, 1,000 queries 92 -> 80, 10,000 177 -> 168
+        const uint32_t* my_adj = a.adj + (lane < a.R ? lane : 0);
+        uint32_t row_u = a.entry, row_v = my_adj[(size_t)a.entry * (uint32_t)a.R];
+        for (;;) {
+            // ---- 1. the two closest unexpanded entries
+            uint64_t ukey = 0;
+            uint32_t u2 = 0;
+            int sel_r = -1, sel_lane = 0;
+            bool have2 = false;
+#pragma unroll
+            for (int r = 0; r < NREG; r++) {
+                uint64_t m = ballot((fk[r] & 1ull) == 0ull);
+                if (sel_r < 0 && m != 0ull) {
+                    sel_r = r;
+                    sel_lane = __builtin_ctzll(m);
+                    ukey = readlane64(fk[r], sel_lane);
+                    m &= m - 1ull;
+                }
+                if (!have2 && m != 0ull) {
+                    have2 = true;
+                    u2 = readlane32((uint32_t)fk[r], __builtin_ctzll(m)) >> 1;
+                }
+            }
+            if (sel_r < 0) break;
+            const uint32_t u = key_id(ukey);
+#pragma unroll
+            for (int r = 0; r < NREG; r++) fk[r] |= (r == sel_r && lane == sel_lane) ? 1ull : 0ull;
+            if constexpr (VIS) {
+                if (lane == 0 && hops < (uint32_t)a.vis_cap) vis[hops] = ukey | 1ull;
+            }
+            hops++;
+            // ---- 2. adjacency row
+            if (row_u != u) row_v = my_adj[(size_t)u * (uint32_t)a.R];
+            const uint32_t v = lane < a.R ? row_v : JX_NONE_ID;
+            // ---- 3. visited filter (see the general form); padding finds its own tag in no set and is masked
+            const uint32_t h = (v * 0x9E3779B1u) & id_mask;
+            const uint32_t tag = h & ((1u << tag_bits) - 1u);
+            const uint32_t w = tab[h >> tag_bits];
+            row_u = have2 ? u2 : u;
+            row_v = my_adj[(size_t)row_u * (uint32_t)a.R];
+            const bool is_new = v != JX_NONE_ID && (w & 0xFFFFu) != tag && (w >> 16) != tag;
+            const uint64_t nm = ballot(is_new);
+            if (nm == 0ull) continue;
+            const int n_new = __builtin_popcountll(nm);
+            if (is_new) {
+                tab[h >> tag_bits] = (w << 16) | tag;
+                cand_id[prefix_count(nm)] = v;
+            }
+            wave_sync();
+            // ---- 4./5. gather + distances
+            if (full) {
+                for (int s0 = 0; s0 < n_new; s0 += G * U)
+                    eval_batch<KIND, T, CPL, QB, U, true, TILED>(q, a.ds, s0, n_new, cand_id, cand_key, g, lig);
+            } else {
+                for (int s0 = 0; s0 < n_new; s0 += G * U)
+                    eval_batch<KIND, T, CPL, QB, U, false, TILED>(q, a.ds, s0, n_new, cand_id, cand_key, g, lig);
+            }
+            evals += n_new;
+            wave_sync();
+            const uint64_t ck = lane < n_new ? cand_key[lane] : JX_EMPTY_KEY;
+            wave_sync();
+            // ---- 6. merge into the sorted frontier
+            frontier_merge<NREG>(fk, fr, count, worst, L, ck, n_new, lane);
+        }
+    } else
     for (;;) {
         // ---- 1. closest unexpanded entry
         int sel_r = -1, sel_lane = 0;
@@ -338,10 +476,11 @@ __device__ __forceinline__ void beam_search_body(const BeamArgs& a) {
     }
 }
 
-template <int KIND, int T, int CPL, int NREG, int QB>
-__global__ void __launch_bounds__(JX_BEAM_WPB * 64) __attribute__((amdgpu_waves_per_eu(((KIND <= K_F32 || KIND == K_F16) && NREG <= 2 && CPL <= 2) ? JX_WPE_EXACT : ((query_in_lds<KIND, CPL, QB>() && NREG <= 4) ? JX_WPE_RQ1 : 1), 8)))
+// MODE 1: tag table and R <= 64; 2: the same with more records in flight (see beam_search_body)
+template <int KIND, int T, int CPL, int NREG, int QB, int MODE>
+__global__ void __launch_bounds__(JX_BEAM_WPB * 64) __attribute__((amdgpu_waves_per_eu(MODE == 2 ? 1 : ((KIND <= K_F32 || KIND == K_F16) && NREG <= 2 && CPL <= 2) ? JX_WPE_EXACT : ((query_in_lds<KIND, CPL, QB>() && NREG <= 4) ? JX_WPE_RQ1 : 1), 8)))
 beam_search_kernel(BeamArgs a) {
-    beam_search_body<KIND, T, CPL, NREG, QB, JX_BEAM_WPB, false>(a);
+    beam_search_body<KIND, T, CPL, NREG, QB, JX_BEAM_WPB, false, false, MODE>(a);
 }
 
 // Ablation instances (exact distances): WPB queries per workgroup, element-strided ("tiled") loads.
@@ -352,9 +491,9 @@ beam_search_variant_kernel(BeamArgs a) {
 }
 
 // Insertion with the expansion list as candidate set (exact distances; see BeamArgs::vis_cap)
-template <int KIND, int T, int CPL, int NREG>
+template <int KIND, int T, int CPL, int NREG, int MODE>
 __global__ void __launch_bounds__(64) beam_search_visited_kernel(BeamArgs a) {
-    beam_search_body<KIND, T, CPL, NREG, 0, 1, false, true>(a);
+    beam_search_body<KIND, T, CPL, NREG, 0, 1, false, true, MODE>(a);
 }
 
 // ------------------------------------------------------------------ two expansions per round

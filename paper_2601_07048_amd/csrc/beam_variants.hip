@@ -184,11 +184,16 @@ template <int KIND, int T, int CPL>
 static hipError_t launch_visited_shape(const BeamArgs& a, hipStream_t st, char* name) {
     const int nreg = (a.L + 63) / 64;
     const size_t tail = 64 * 8 + 64 * 4 + (size_t)a.hash_slots * (a.tag_bits ? 2 : 4) + (size_t)a.vis_cap * 8;
-    if (name) snprintf(name, 96, "beam_search_visited_kernel<%d,%d,%d,%d>", KIND, T, CPL, nreg <= 1 ? 1 : 2);
-    if (nreg <= 1)
-        hipLaunchKernelGGL((beam_search_visited_kernel<KIND, T, CPL, 1>), dim3((unsigned)a.nq), dim3(64), mirror_entries<1>() * 8 + tail, st, a);
-    else
-        hipLaunchKernelGGL((beam_search_visited_kernel<KIND, T, CPL, 2>), dim3((unsigned)a.nq), dim3(64), mirror_entries<2>() * 8 + tail, st, a);
+    const int mode = a.tag_bits > 0 && a.R <= 64 ? (a.nq <= WIDE_MAX_QUERIES && has_wide<T, CPL>() ? 2 : 1) : 0;
+    if (name) snprintf(name, 96, "beam_search_visited_kernel<%d,%d,%d,%d,%d>", KIND, T, CPL, nreg <= 1 ? 1 : 2, mode);
+#define JX_LAUNCH(NR)                                                                                                         \
+    {                                                                                                                         \
+        auto kern = mode == 2 ? beam_search_visited_kernel<KIND, T, CPL, NR, has_wide<T, CPL>() ? 2 : 1>                      \
+                              : (mode ? beam_search_visited_kernel<KIND, T, CPL, NR, 1> : beam_search_visited_kernel<KIND, T, CPL, NR, 0>); \
+        hipLaunchKernelGGL(kern, dim3((unsigned)a.nq), dim3(64), mirror_entries<NR>() * 8 + tail, st, a);                     \
+    }
+    if (nreg <= 1) JX_LAUNCH(1) else JX_LAUNCH(2)
+#undef JX_LAUNCH
     return hipGetLastError();
 }
 

@@ -49,6 +49,10 @@ struct BeamArgs {
 };
 // kernel_name (may be NULL): receives the name of the instance that was launched, at most 96 bytes
 hipError_t launch_beam_search(int kind, int qbits, const BeamArgs& a, hipStream_t st, char* kernel_name = nullptr);
+// batches that leave the machine mostly idle: a team of wavefronts per query; *done = whether the batch is one and
+// has been launched
+hipError_t launch_beam_ahead(int kind, int qbits, const BeamArgs& a, hipStream_t st, char* kernel_name, bool* done);
+hipError_t launch_beam_codes(int kind, int qbits, const BeamArgs& a, hipStream_t st, char* kernel_name);
 // ablation instances (JX_FLAG_TILED_LOADS, JX_FLAG_QPW_*, JX_FLAG_WAVES_*); hipErrorInvalidValue where none exists
 hipError_t launch_beam_variant(int kind, const BeamArgs& a, hipStream_t st, char* kernel_name);
 // beamSearch that returns the expansion list (BeamArgs::vis_cap); instances: see visited_list_offered()

@@ -1,0 +1,76 @@
+"""Small batches run on kernels of their own (more records in flight, a team of wavefronts per query that reads ahead),
+larger ones on one wavefront per query.  All of them are the same search: ids, distances (to the last bit) and expansion
+counts equal those of the general kernel, which a full-id visited table selects, on both sides of every size limit."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import dev, jx_dtype, random_data
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def jx():
+    from paper_2601_07048_amd import jx as m
+    return m
+
+
+def _compare(jx, g, q, L, **kw):
+    g.set_flags(0)
+    ids, dist, st = g.search(q, min(10, L), L, stats=True, **kw)
+    g.set_flags(jx.FLAG_VISITED_IDS | jx.FLAG_NO_PAIR)
+    ids0, dist0, st0 = g.search(q, min(10, L), L, stats=True, **kw)
+    g.set_flags(0)
+    assert st0["beam_kernel"].startswith("beam_search_kernel<") and st0["beam_kernel"].endswith(",0>"), st0["beam_kernel"]
+    assert torch.equal(ids, ids0), st["beam_kernel"]
+    assert torch.equal(dist, dist0), st["beam_kernel"]
+    assert st["hops"] == st0["hops"], st["beam_kernel"]
+    return st["beam_kernel"].split("<")[0]
+
+
+@pytest.mark.parametrize("dtype,d,R", [("uint8", 128, 64), ("uint8", 96, 33), ("uint8", 256, 64), ("uint8", 128, 80),
+                                       ("float32", 128, 64), ("float32", 100, 17), ("float32", 200, 64), ("float32", 960, 64),
+                                       ("float32", 1536, 40), ("float16", 128, 64), ("float16", 960, 64)])
+def test_small_batches_equal_the_general_kernel(jx, dtype, d, R):
+    n = 3000
+    x = random_data(n, d, np.uint8 if dtype == "uint8" else np.float32, 5).astype(dtype)
+    q = random_data(2100, d, np.uint8 if dtype == "uint8" else np.float32, 6).astype(dtype)
+    g = jx.Index(d, jx_dtype(jx, x), R, 64, 1.2, capacity=n, max_batch=4096)
+    g.insert(dev(x))
+    names = set()
+    for L in (1, 16, 64, 65, 128, 200):
+        for nq in (1, 3, 256, 257, 513, 2049):
+            if nq > 513 and L not in (16, 65):
+                continue
+            names.add(_compare(jx, g, dev(q[:nq]), L))
+    assert ("beam_search_ahead_kernel" in names) == (d >= 200 and dtype != "uint8" and R <= 64), names
+
+
+@pytest.mark.parametrize("d,bits,qbits", [(960, 4, 8), (960, 4, 4), (960, 8, 8), (1536, 1, 4), (1536, 2, 4), (960, 1, 8), (128, 4, 8)])
+def test_small_batches_of_code_searches(jx, d, bits, qbits):
+    n = 2000
+    x = random_data(n, d, np.float32, 7)
+    q = random_data(600, d, np.float32, 8)
+    g = jx.Index(d, jx.F32, 48, 64, 1.2, capacity=n, max_batch=4096, quant_bits=bits)
+    g.insert(dev(x))
+    rot = np.linalg.qr(np.random.default_rng(9).standard_normal((d, d)))[0].astype(np.float32)
+    g.quantize(bits, dev(rot), query_bits=qbits, rule=jx.RULE_MAXABS)
+    names = set()
+    for L in (16, 100, 192):
+        for nq in (1, 255, 600):
+            names.add(_compare(jx, g, dev(q[:nq]), L, mode=jx.RABITQ))
+    assert ("beam_search_ahead_kernel" in names) == (d >= 960), names
+
+
+@pytest.mark.parametrize("d", [128, 960])
+def test_expansion_list_builds_equal_the_general_kernel(jx, d):
+    """The candidate search of insertion that returns the expansion list: a graph built from small internal batches (team
+    and wide instances) is the graph of the general kernel."""
+    x = random_data(2500, d, np.float32, 11)
+    adj = []
+    for flags in (0, jx.FLAG_VISITED_IDS):
+        g = jx.Index(d, jx.F32, 64, 96, 1.2, capacity=2500, max_batch=4096, cand_mode=jx.CAND_VISITED, flags=flags)
+        g.insert(dev(x))
+        adj.append(g.export_graph()[0])
+    assert torch.equal(adj[0], adj[1])
