@@ -1,4 +1,5 @@
-// Exhaustive k-nearest-neighbour search: the recall ground truth (Sec. 6.1).
+// Exhaustive k-nearest-neighbour search: the recall ground truth (Sec. 6.1).  The tiled form, for small searches, rows off
+// 16-byte boundaries, lists that only just fit the scratch, and the queries knn_tile.hip hands back; the rest runs there.
 //
 // A 256-thread workgroup owns a tile of 64 queries and streams a slice of the
 // base set through LDS in tiles of 64 vectors.  Each thread accumulates a 4x4
@@ -29,6 +30,10 @@ __global__ void __launch_bounds__(256) bruteforce_tile_kernel(BfArgs a) {
     const int tx = tid & 15, ty = tid >> 4;
     const int k = a.k;
     const long long q0 = (long long)blockIdx.x * BF_TQ;
+    if (a.redo) {  // whole workgroups leave, before the first barrier
+        const long long qf = q0 + lane;
+        if (ballot(qf < a.nq && a.redo[qf] != 0u) == 0ull) return;
+    }
     const int dw = (DT == JX_U8) ? a.d / 4 : (DT == JX_F16 ? a.d / 2 : a.d);  // dwords per vector
     const long long per = (a.n + a.nsplit - 1) / a.nsplit;
     const long long b_begin = (long long)blockIdx.y * per;
@@ -168,6 +173,10 @@ __global__ void __launch_bounds__(64) bruteforce_merge_kernel(BfArgs a) {
     uint64_t* keys = reinterpret_cast<uint64_t*>(dyn);
     const long long qi = blockIdx.x;
     const int lane = threadIdx.x;
+    if (a.redo) {
+        const long long qf = qi / BF_TQ * BF_TQ + lane;
+        if (ballot(qf < a.nq && a.redo[qf] != 0u) == 0ull) return;
+    }
     const int m = a.nsplit * a.k;
     const uint64_t* src = a.partial + (size_t)qi * m;
     for (int i = lane; i < m; i += 64) keys[i] = src[i];

@@ -574,14 +574,8 @@ int jx_bruteforce(jx_index* idx, const void* d_queries, int64_t nq, int32_t k, u
     if (idx->n == 0) return fail(JX_ESTATE, "index is empty");
     if (nq <= 0) return JX_OK;
     hipStream_t st = as_stream(stream);
-    // split the base set, and slice the queries so that the per-slice partial lists fit the workspace
-    const int64_t nsplit = bruteforce_nsplit(idx->n, nq);
-    int64_t per_q = nsplit * k * 8;
-    int64_t slice = idx->work_bytes / per_q;
-    slice = (slice / 64) * 64;
-    if (slice < 64) return fail(JX_ECAPACITY, "workspace too small for brute force");
-    for (int64_t q0 = 0; q0 < nq; q0 += slice) {
-        int64_t m = nq - q0 < slice ? nq - q0 : slice;
+    for (int64_t q0 = 0; q0 < nq;) {
+        int64_t m = nq - q0 < 16384 ? nq - q0 : 16384;
         jx::BfArgs a;
         memset(&a, 0, sizeof a);
         a.base = idx->d_vecs;
@@ -591,11 +585,23 @@ int jx_bruteforce(jx_index* idx, const void* d_queries, int64_t nq, int32_t k, u
         a.n = idx->n;
         a.nq = m;
         a.k = k;
-        a.nsplit = (int)nsplit;
-        a.partial = (uint64_t*)idx->d_work;
         a.out_ids = d_out_ids + (size_t)q0 * k;
         a.out_dist = d_out_dist + (size_t)q0 * k;
-        JX_HIP(jx::launch_bruteforce(a, st));
+        bool done = false;
+        JX_HIP(jx::launch_knn_tile(a, idx->d_work, idx->work_bytes, st, &done));
+        if (!done) {
+            // split the base set, and slice the queries so that the per-slice partial lists fit the workspace
+            const int64_t nsplit = bruteforce_nsplit(idx->n, m);
+            int64_t slice = idx->work_bytes / (nsplit * k * 8);
+            slice = (slice / 64) * 64;
+            if (slice < 64) return fail(JX_ECAPACITY, "workspace too small for brute force");
+            if (m > slice) m = slice;
+            a.nq = m;
+            a.nsplit = (int)nsplit;
+            a.partial = (uint64_t*)idx->d_work;
+            JX_HIP(jx::launch_bruteforce(a, st));
+        }
+        q0 += m;
     }
     return JX_OK;
 }
@@ -631,7 +637,9 @@ int jx_bruteforce_static(const void* d_base, int64_t n, int32_t dim, int32_t dty
     a.partial = (uint64_t*)sc;  // every list the merge reads is written by the tile kernel first: nothing to clear
     a.out_ids = d_out_ids;
     a.out_dist = d_out_dist;
-    JX_HIP(jx::launch_bruteforce(a, as_stream(stream)));
+    bool done = false;
+    JX_HIP(jx::launch_knn_tile(a, sc, JX_STATIC_SCRATCH_BYTES, as_stream(stream), &done));
+    if (!done) JX_HIP(jx::launch_bruteforce(a, as_stream(stream)));
     return JX_OK;
 }
 

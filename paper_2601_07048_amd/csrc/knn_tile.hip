@@ -1,0 +1,692 @@
+// Exhaustive k-nearest-neighbour search on the matrix cores.
+//
+// A 256-thread workgroup owns 128 queries and streams a slice of the base set in steps of 128 vectors.  Each of its
+// four wavefronts computes a 64 x 64 block of <q, b> (32x32 MFMA tiles, operands staged through LDS in slabs of 128
+// bytes a row, the next slab on its way in registers), and d = |q|^2 + |b|^2 - 2 <q, b> is compared with the query's
+// threshold, one add and one compare per pair.  What passes is appended to a 32-entry buffer of the query in LDS; a
+// buffer that is half full is merged into the query's sorted list of this slice (global memory, L2) by one wavefront,
+// which also renews the threshold.  With m slices the largest of their r-th distances, r = ceil(k / m), bounds the k-th
+// of all: every slice publishes its r-th, so a slice accepts little that the whole set would not accept (the k-th of its
+// own m-th part of the base set would let m times as much pass: 1,562 vectors and k = 128 made 450 entries a query).
+//
+//   uint8            v_mfma_i32_32x32x32_i8 on the values shifted by -128 (distances do not change): exact integers, so
+//                    the lists hold the result.
+//   float32/binary16 v_mfma_f32_32x32x2_f32 / 32x32x16_f16: these distances only choose KNN_SLACK more candidates
+//                    than asked for.  The merge kernel evaluates them with the arithmetic of bruteforce_tile_kernel,
+//                    operation by operation, orders them, and proves that nothing left out can be among the first
+//                    k: the first distance left out, less the error bound of both forms, has to exceed the k-th one.
+//                    Queries for which it does not (ties, infinities, NaN) are flagged, and their tiles are done again
+//                    by bruteforce_tile_kernel.  So the result is that kernel's, bit for bit.
+//
+// Bound: matrix cores for float32 (1.8 of 2.5 ms below, 107 TFLOP/s), vector instructions and barriers for uint8 (2.9 of
+// 4.4 ms without a single candidate).  Against bruteforce_tile_kernel: 10,000 x 1M uint8 d = 128, k = 10 27.0 -> 4.4 ms;
+// 1,000 x 100,003 float32 d = 960, k = 100 12.9 -> 2.7 ms; 1,000 x 100,000 binary16 d = 960, k = 10 3.97 -> 0.84 ms;
+// 2 x 234,001 float32 d = 128, k = 1 1.12 -> 0.17 ms.  Without the seeds the lists fill with what comes first: 5.6 and 5.3 ms.
+#include "jx_distance.h"
+
+namespace jx {
+
+typedef float kf32x16 __attribute__((ext_vector_type(16)));
+typedef int ki32x16 __attribute__((ext_vector_type(16)));
+typedef int ki32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 kf16x8 __attribute__((ext_vector_type(8)));
+
+#define KT 128        // queries per workgroup, base vectors per step
+#define KROW 144      // bytes of a staged row: 128 and 16 of padding
+#define KCAP 32       // buffer entries per query
+#define KFLUSH 16     // a buffer with this many entries is merged
+#define KINF 0x50000000  // uint8: above every distance (6,144 x 255^2 < 2^29), far from overflow
+
+template <int DT> struct KAcc { typedef kf32x16 type; typedef float elem; };
+template <> struct KAcc<JX_U8> { typedef ki32x16 type; typedef int elem; };
+
+struct KnnLds {
+    uint4 a[KT * KROW / 16], b[KT * KROW / 16];
+    uint64_t buf[KT][KCAP];
+    uint32_t cnt[KT];   // entries appended to buf (may exceed KCAP: the rest is offered again)
+    uint32_t fill[KT];  // entries of the query's list
+    uint32_t lim[KT];   // threshold: int / float bits, exclusive
+    uint32_t t[KT];     // lim - |q|^2
+    uint32_t qn[KT], bn[KT];
+    uint32_t again;
+};
+
+// A chunk on its way to LDS: outside the rows or the vector the load has read another one (no branch holds it up), and
+// zero takes its place; uint8 values are shifted by -128.
+template <int DT>
+__device__ __forceinline__ uint4 knn_stage(uint4 v, const bool in) {
+    if (DT == JX_U8) {
+        v.x ^= 0x80808080u;
+        v.y ^= 0x80808080u;
+        v.z ^= 0x80808080u;
+        v.w ^= 0x80808080u;
+    }
+    return make_uint4(in ? v.x : 0u, in ? v.y : 0u, in ? v.z : 0u, in ? v.w : 0u);
+}
+
+template <int DT>
+__device__ __forceinline__ typename KAcc<DT>::elem knn_sq(uint4 v, typename KAcc<DT>::elem s) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        if constexpr (DT == JX_U8)
+            s = __builtin_amdgcn_sdot4((int)w[i], (int)w[i], s, false);
+        else if constexpr (DT == JX_F16)
+            s = hdot2(w[i], w[i], s);
+        else
+            s = fmaf(__uint_as_float(w[i]), __uint_as_float(w[i]), s);
+    }
+    return s;
+}
+
+template <int DT>
+__device__ __forceinline__ uint32_t knn_bits(typename KAcc<DT>::elem v) {
+    if constexpr (DT == JX_U8)
+        return (uint32_t)v;
+    else
+        return __float_as_uint(v);
+}
+template <int DT>
+__device__ __forceinline__ typename KAcc<DT>::elem knn_val(uint32_t b) {
+    if constexpr (DT == JX_U8)
+        return (int)b;
+    else
+        return __uint_as_float(b);
+}
+
+// One wavefront merges the buffer of query row q into its list (sorted keys, kp at most) and renews the threshold.
+// NL: list entries per lane.
+template <int DT, int NL>
+__device__ __forceinline__ void knn_flush(KnnLds& S, const int q, uint64_t* list, const int kp, uint32_t* published, const int nsplit,
+                                          const int split, const int r_th, const int lane) {
+    const int n_old = (int)S.fill[q];
+    const int m = (int)S.cnt[q] < KCAP ? (int)S.cnt[q] : KCAP;
+    uint64_t old[NL];
+    uint32_t to[NL];
+#pragma unroll
+    for (int r = 0; r < NL; r++) {
+        const int p = r * 64 + lane;
+        old[r] = p < n_old ? list[p] : JX_EMPTY_KEY;
+        to[r] = (uint32_t)p;
+    }
+    const uint64_t mine = lane < m ? S.buf[q][lane] : JX_EMPTY_KEY;
+    uint32_t at = 0;
+    for (int i = 0; i < m; i++) {
+        const uint64_t s = readlane64(mine, i);
+        uint32_t rank = 0;
+#pragma unroll
+        for (int r = 0; r < NL; r++) {
+            rank += (uint32_t)__builtin_popcountll(ballot(old[r] < s));
+            to[r] += s < old[r] ? 1u : 0u;
+        }
+        at += (lane == i ? rank : 0u) + (s < mine ? 1u : 0u);
+    }
+    const int n_new = n_old + m < kp ? n_old + m : kp;
+    uint32_t last = 0, rth = 0;  // distances of entries kp - 1 and r_th - 1
+    bool has = false, has_r = false;
+#pragma unroll
+    for (int r = 0; r < NL; r++) {
+        if (r * 64 + lane < n_old && to[r] < (uint32_t)kp) {
+            list[to[r]] = old[r];
+            if (to[r] == (uint32_t)kp - 1u) {
+                last = (uint32_t)(old[r] >> 32);
+                has = true;
+            }
+            if (to[r] == (uint32_t)r_th - 1u) {
+                rth = (uint32_t)(old[r] >> 32);
+                has_r = true;
+            }
+        }
+    }
+    if (lane < m && at < (uint32_t)kp) {
+        list[at] = mine;
+        if (at == (uint32_t)kp - 1u) {
+            last = (uint32_t)(mine >> 32);
+            has = true;
+        }
+        if (at == (uint32_t)r_th - 1u) {
+            rth = (uint32_t)(mine >> 32);
+            has_r = true;
+        }
+    }
+    __threadfence_block();  // the next merge of this list reads it with other lanes
+    const uint64_t who = ballot(has);
+    uint32_t lim = S.lim[q];
+    if (who) {
+        const uint32_t own = readlane32(last, __builtin_ctzll(who));
+        if (own < lim) lim = own;  // ids of later steps are larger: a distance equal to the last one's is out
+    }
+    if (published) {
+        if (has_r) __hip_atomic_store(published + split, rth, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t most = 0;
+        for (int s = lane; s < nsplit; s += 64) {
+            uint32_t v = __hip_atomic_load(published + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (s == split) v = 0;  // this slice's own is below its threshold anyway
+            most = v > most ? v : most;
+        }
+#pragma unroll
+        for (int x = 1; x < 64; x <<= 1) {
+            const uint32_t o = shfl_xor(most, x);
+            most = o > most ? o : most;
+        }
+        const uint64_t wr = ballot(has_r);
+        const uint32_t mine_r = wr ? readlane32(rth, __builtin_ctzll(wr)) : 0xFFFFFFFEu;  // fewer than r_th entries yet
+        most = mine_r > most ? mine_r : most;
+        if (most + 1u < lim) lim = most + 1u;  // equal distances stay in (their ids may be smaller)
+    }
+    if (lane == 0) {
+        S.lim[q] = lim;
+        if constexpr (DT == JX_U8)
+            S.t[q] = (uint32_t)((int)lim - (int)S.qn[q]);
+        else
+            S.t[q] = __float_as_uint(__uint_as_float(lim) - __uint_as_float(S.qn[q]));
+        S.fill[q] = (uint32_t)n_new;
+        S.cnt[q] = 0;
+    }
+    wave_sync();
+}
+
+// Largest value of the wavefront, in every lane
+template <typename E>
+__device__ __forceinline__ E knn_wave_max(E v) {
+    auto bits = [](E x) { return __builtin_bit_cast(uint32_t, x); };
+    auto val = [](uint32_t x) { return __builtin_bit_cast(E, x); };
+    auto top = [](E x, E y) { return x > y ? x : y; };
+    v = top(v, val(dpp_u32<0xB1>(bits(v))));
+    v = top(v, val(dpp_u32<0x4E>(bits(v))));
+    v = top(v, val(dpp_u32<0x141>(bits(v))));
+    v = top(v, val(dpp_u32<0x140>(bits(v))));
+    return top(top(val(readlane32(bits(v), 0)), val(readlane32(bits(v), 16))), top(val(readlane32(bits(v), 32)), val(readlane32(bits(v), 48))));
+}
+
+// ONE: vectors of one slab; the queries stay in LDS.
+// SEED: only the slice's first a.seed_steps steps, to publish a first r_th distance before the search begins: the
+// smallest distance of each of the 128 columns over the steps, then the r_th smallest of these.  It is no smaller than
+// the r_th of all that was seen.
+template <int DT, int NL, bool ONE, bool SEED>
+__global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
+    typedef typename KAcc<DT>::type acc_t;
+    typedef typename KAcc<DT>::elem elem_t;
+    __shared__ KnnLds S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
+    const long long q0 = (long long)blockIdx.x * KT;
+    const int split = blockIdx.y;
+    const long long steps = (a.n + KT - 1) / KT;  // every slice has as many, or one more
+    const long long b_begin = split * steps / a.nsplit * KT;
+    long long b_end = (split + 1) * steps / a.nsplit * KT;
+    if (b_end > a.n) b_end = a.n;
+    if (SEED && b_end > b_begin + (long long)a.seed_steps * KT) b_end = b_begin + (long long)a.seed_steps * KT;
+    const uint8_t* Q = reinterpret_cast<const uint8_t*>(a.queries);
+    const uint8_t* B = reinterpret_cast<const uint8_t*>(a.base);
+    const int nslab = ONE ? 1 : (a.nch + 7) / 8;
+    const int srow = tid >> 3, sch = tid & 7;  // staging: 8 threads per row, rows srow + 32 t
+
+    for (int i = tid; i < KT; i += 256) {
+        S.cnt[i] = 0;
+        S.fill[i] = 0;
+        uint32_t lim = DT == JX_U8 ? (uint32_t)KINF : 0x7F800000u;
+        if (!SEED && a.seed_steps && q0 + i < a.nq) {
+            uint32_t most = 0;
+            for (int s = 0; s < a.nsplit; s++) {
+                const uint32_t v = a.published[(size_t)(q0 + i) * a.nsplit + s];
+                most = v > most ? v : most;
+            }
+            if (most + 1u < lim) lim = most + 1u;
+        }
+        S.lim[i] = lim;
+    }
+    if (tid == 0) S.again = 0;
+    __syncthreads();
+    elem_t best[SEED ? 64 : 1];  // largest 2 <q, b> - |b|^2 of each element
+    if constexpr (SEED) {
+#pragma unroll
+        for (int e = 0; e < 64; e++) best[e] = DT == JX_U8 ? (elem_t)-0x7FFFFFFF : (elem_t)-__builtin_inff();
+    }
+    uint32_t bmax = 0;
+
+    uint4 pa[4], pb[4];
+    const size_t row_bytes = (size_t)(a.nch * 16);
+    auto at = [&](const uint8_t* base, const long long row, const long long rows, const int ch) {
+        return load16(base + (size_t)(row < rows ? row : rows - 1) * row_bytes + (size_t)((ch < a.nch ? ch : a.nch - 1) * 16));
+    };
+    auto fetch = [&](const long long b0, const int slab, const bool queries) {
+#pragma unroll
+        for (int t = 0; t < 4; t++) pb[t] = at(B, b0 + srow + 32 * t, b_end, slab * 8 + sch);
+        if (queries) {
+#pragma unroll
+            for (int t = 0; t < 4; t++) pa[t] = at(Q, q0 + srow + 32 * t, a.nq, slab * 8 + sch);
+        }
+    };
+    if (b_begin < b_end) fetch(b_begin, 0, true);
+
+    for (long long b0 = b_begin; b0 < b_end; b0 += KT) {
+        const bool first = b0 == b_begin;
+        acc_t acc[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[i][j][e] = 0;
+        elem_t nb[4] = {0, 0, 0, 0}, nq[4] = {0, 0, 0, 0};
+        for (int slab = 0; slab < nslab; slab++) {
+            const bool queries = first || !ONE;
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const bool chunk = slab * 8 + sch < a.nch;
+                if (queries) {
+                    const uint4 v = knn_stage<DT>(pa[t], chunk && q0 + srow + 32 * t < a.nq);
+                    S.a[(srow + 32 * t) * (KROW / 16) + sch] = v;
+                    if (first) nq[t] = knn_sq<DT>(v, nq[t]);
+                }
+                const uint4 v = knn_stage<DT>(pb[t], chunk && b0 + srow + 32 * t < b_end);
+                S.b[(srow + 32 * t) * (KROW / 16) + sch] = v;
+                nb[t] = knn_sq<DT>(v, nb[t]);
+            }
+            if (slab == nslab - 1) {  // norms: the 8 threads of a row
+#pragma unroll
+                for (int t = 0; t < 4; t++) {
+                    const int row = srow + 32 * t;
+                    const elem_t x = group_sum<8>(nb[t]);
+                    const bool in = b0 + row < b_end;
+                    if (sch == 0) S.bn[row] = in ? knn_bits<DT>(x) : (DT == JX_U8 ? 0x7FFFFFFFu : 0x7F800000u);
+                    if (in && knn_bits<DT>(x) > bmax) bmax = knn_bits<DT>(x);
+                    if (first) {
+                        const elem_t y = group_sum<8>(nq[t]);
+                        if (sch == 0) {
+                            S.qn[row] = knn_bits<DT>(y);
+                            // rows beyond the last query accept nothing
+                            if (DT == JX_U8)
+                                S.t[row] = q0 + row < a.nq ? (uint32_t)((int)S.lim[row] - (int)y) : 0xB0000000u;
+                            else if (S.lim[row] < 0x7F800000u)
+                                S.t[row] = q0 + row < a.nq ? __float_as_uint(__uint_as_float(S.lim[row]) - (float)y) : 0xFF800000u;
+                            else
+                                S.t[row] = q0 + row < a.nq ? 0x7F800000u : 0xFF800000u;
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+            if (!ONE && slab + 1 < nslab)
+                fetch(b0, slab + 1, true);
+            else if (b0 + KT < b_end)
+                fetch(b0 + KT, 0, !ONE);
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                uint4 fa[2], fb[2];
+#pragma unroll
+                for (int i = 0; i < 2; i++) {
+                    fa[i] = S.a[(wm * 64 + i * 32 + col) * (KROW / 16) + s * 2 + half];
+                    fb[i] = S.b[(wn * 64 + i * 32 + col) * (KROW / 16) + s * 2 + half];
+                }
+#pragma unroll
+                for (int i = 0; i < 2; i++)
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+                        if constexpr (DT == JX_U8) {
+                            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(ki32x4, fa[i]), __builtin_bit_cast(ki32x4, fb[j]), acc[i][j], 0, 0, 0);
+                        } else if constexpr (DT == JX_F16) {
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(kf16x8, fa[i]), __builtin_bit_cast(kf16x8, fb[j]), acc[i][j], 0, 0, 0);
+                        } else {
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[i].x), __uint_as_float(fb[j].x), acc[i][j], 0, 0, 0);
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[i].y), __uint_as_float(fb[j].y), acc[i][j], 0, 0, 0);
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[i].z), __uint_as_float(fb[j].z), acc[i][j], 0, 0, 0);
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[i].w), __uint_as_float(fb[j].w), acc[i][j], 0, 0, 0);
+                        }
+                    }
+            }
+            if (slab + 1 < nslab) __syncthreads();  // else the barrier behind the appends stands before the next write
+        }
+        elem_t nbv[2];
+#pragma unroll
+        for (int j = 0; j < 2; j++) nbv[j] = knn_val<DT>(S.bn[wn * 64 + j * 32 + col]);
+        if constexpr (SEED) {
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+#pragma unroll
+                for (int j = 0; j < 2; j++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++) {
+                        const elem_t v = DT == JX_U8 ? (elem_t)(acc[i][j][e] * 2 - nbv[j]) : (elem_t)(acc[i][j][e] * 2 - nbv[j]);
+                        elem_t& m = best[(i * 2 + j) * 16 + e];
+                        m = v > m ? v : m;
+                    }
+            __syncthreads();
+            continue;
+        }
+        // ---- compare and append; what found a full buffer is offered again after the merges
+        uint64_t stored = 0;  // elements of this lane's 64 that are in a buffer already
+        for (int round = 0;; round++) {
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                uint4 tv[4];
+#pragma unroll
+                for (int h = 0; h < 4; h++) tv[h] = *reinterpret_cast<const uint4*>(&S.t[wm * 64 + i * 32 + 8 * h + 4 * half]);
+#pragma unroll
+                for (int h = 0; h < 4; h++) {
+                    int r0 = wm * 64 + i * 32 + 8 * h + 4 * half;
+                    asm volatile("" : "+v"(r0));  // not known outside: addresses of all 64 elements would not fit the registers
+                    const uint32_t tt[4] = {tv[h].x, tv[h].y, tv[h].z, tv[h].w};
+                    // d < limit as 2 <q, b> + t > |b|^2, t = limit - |q|^2: the largest of four rows first
+                    elem_t v[2][4];
+                    bool any = false;
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+#pragma unroll
+                        for (int c = 0; c < 4; c++) {
+                            const elem_t x = acc[i][j][h * 4 + c], t = knn_val<DT>(tt[c]);
+                            if constexpr (DT == JX_U8)
+                                v[j][c] = (x << 1) + t;
+                            else
+                                v[j][c] = fmaf(2.f, x, t);
+                        }
+                        elem_t most;
+                        if constexpr (DT == JX_U8)
+                            most = max(max(max(v[j][0], v[j][1]), v[j][2]), v[j][3]);
+                        else
+                            most = fmaxf(fmaxf(fmaxf(v[j][0], v[j][1]), v[j][2]), v[j][3]);
+                        any = any || most >= nbv[j];
+                    }
+                    if (ballot(any) == 0ull) continue;
+#pragma unroll
+                    for (int c = 0; c < 4; c++)
+#pragma unroll
+                        for (int j = 0; j < 2; j++) {
+                            const int bit = ((i * 4 + h) * 4 + c) * 2 + j;
+                            const uint32_t id = (uint32_t)b0 + (uint32_t)(wn * 64 + j * 32 + col);
+                            if ((round == 0 ? v[j][c] > nbv[j] : v[j][c] >= nbv[j]) && !((stored >> bit) & 1ull) && id < (uint32_t)b_end) {
+                                const uint32_t pos = atomicAdd(&S.cnt[r0 + c], 1u);
+                                if (pos < KCAP) {
+                                    uint32_t code;
+                                    const elem_t x = acc[i][j][h * 4 + c], qn = knn_val<DT>(S.qn[r0 + c]);
+                                    if constexpr (DT == JX_U8)
+                                        code = (uint32_t)(qn + nbv[j] - 2 * x);
+                                    else
+                                        code = __float_as_uint(fmaxf((qn + nbv[j]) - 2.f * x, 0.f));
+                                    S.buf[r0 + c][pos] = ((uint64_t)code << 32) | (uint64_t)id;
+                                    stored |= 1ull << bit;
+                                } else {
+                                    S.again = 1;
+                                }
+                            }
+                        }
+                }
+            }
+            __syncthreads();
+            const uint32_t again = S.again;
+            // wavefront w merges the buffers of rows 32 w .. 32 w + 31
+            uint64_t need = ballot(lane < 32 && S.cnt[wave * 32 + (lane & 31)] >= KFLUSH);
+            while (need) {
+                const int q = wave * 32 + __builtin_ctzll(need);
+                need &= need - 1ull;
+                knn_flush<DT, NL>(S, q, a.lists + ((size_t)(q0 + q) * a.nsplit + split) * a.kp, a.kp,
+                                   a.published ? a.published + (size_t)(q0 + q) * a.nsplit : nullptr, a.nsplit, split, a.r_th, lane);
+            }
+            if (!again) break;  // the next step's first barrier stands between these merges and its appends
+            __syncthreads();
+            if (tid == 0) S.again = 0;
+            __syncthreads();
+        }
+    }
+    if constexpr (SEED) {
+        elem_t* cols = reinterpret_cast<elem_t*>(&S.buf[0][0]);  // [64][128]
+        static_assert(sizeof(S.buf) >= 64 * 128 * 4, "columns of 64 queries");
+        for (int h = 0; h < 2; h++) {  // 64 queries at a time
+            if (wm == h) {
+#pragma unroll
+                for (int i = 0; i < 2; i++)
+#pragma unroll
+                    for (int j = 0; j < 2; j++)
+#pragma unroll
+                        for (int e = 0; e < 16; e++)
+                            cols[(i * 32 + 8 * (e >> 2) + 4 * half + (e & 3)) * 128 + wn * 64 + j * 32 + col] = best[(i * 2 + j) * 16 + e];
+            }
+            __syncthreads();
+            for (int r = wave; r < 64; r += 4) {
+                const long long qi = q0 + h * 64 + r;
+                if (qi >= a.nq) break;
+                elem_t x = cols[r * 128 + lane], y = cols[r * 128 + 64 + lane], m = 0;
+                const elem_t none = DT == JX_U8 ? (elem_t)-0x7FFFFFFF : (elem_t)-__builtin_inff();
+                for (int k = 0; k < a.r_th; k++) {
+                    m = knn_wave_max<elem_t>(x > y ? x : y);
+                    const uint64_t hx = ballot(x == m), hy = ballot(y == m);
+                    if (hx) {
+                        if (lane == __builtin_ctzll(hx)) x = none;
+                    } else if (hy) {
+                        if (lane == __builtin_ctzll(hy)) y = none;
+                    }
+                }
+                uint32_t code = 0x7F800000u;
+                const elem_t qn = knn_val<DT>(S.qn[h * 64 + r]);
+                if constexpr (DT == JX_U8) {
+                    if (m > -0x40000000) code = (uint32_t)(qn - m);
+                } else {
+                    const float d = fmaxf(qn - m, 0.f);
+                    if (d < __builtin_inff() && m > -__builtin_inff()) code = __float_as_uint(d);
+                }
+                if (lane == 0) a.published[(size_t)qi * a.nsplit + split] = code;
+            }
+            __syncthreads();
+        }
+        return;
+    }
+    // ---- what is left in the buffers, and the padding of short lists
+    __syncthreads();
+    for (int i = 0; i < 32; i++) {
+        const int q = wave * 32 + i;
+        if (q0 + q >= a.nq) break;
+        uint64_t* list = a.lists + ((size_t)(q0 + q) * a.nsplit + split) * a.kp;
+        if (S.cnt[q]) knn_flush<DT, NL>(S, q, list, a.kp, nullptr, 0, 0, a.kp, lane);
+        for (int e = (int)S.fill[q] + lane; e < a.kp; e += 64) list[e] = JX_EMPTY_KEY;
+    }
+    if (DT != JX_U8 && blockIdx.x == 0) {  // largest |b|^2 of the slice (NaN and infinity come out on top)
+        __syncthreads();
+        if (tid == 0) S.again = 0;
+        __syncthreads();
+        atomicMax(&S.again, bmax);
+        __syncthreads();
+        if (tid == 0) a.bmax[split] = S.again;
+    }
+}
+
+// One wavefront per query: the kp smallest keys of its lists, then (float types) the exact distances.
+template <int DT, int NL>
+__global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
+    __shared__ uint64_t ex[192];
+    const long long qi = blockIdx.x;
+    const int lane = threadIdx.x;
+    const int kp = a.kp;
+    uint64_t top[NL];
+#pragma unroll
+    for (int r = 0; r < NL; r++) top[r] = JX_EMPTY_KEY;
+    uint64_t worst = JX_EMPTY_KEY;  // entry kp - 1
+    const uint64_t* src = a.lists + (size_t)qi * a.nsplit * kp;
+    for (int s0 = 0; s0 < a.nsplit; s0 += 64) {  // a list per lane, entry by entry
+        for (int c = 0; c < kp; c++) {
+            const uint64_t key = s0 + lane < a.nsplit ? src[(size_t)(s0 + lane) * kp + c] : JX_EMPTY_KEY;
+            uint64_t todo = ballot(key < worst);
+            if (todo == 0ull) break;  // the lists are sorted: what follows is no smaller
+            while (todo) {
+                const uint64_t x = readlane64(key, __builtin_ctzll(todo));
+                todo &= todo - 1ull;
+                int rank = 0;
+#pragma unroll
+                for (int r = 0; r < NL; r++) rank += __builtin_popcountll(ballot(top[r] < x));
+#pragma unroll
+                for (int r = NL - 1; r >= 0; r--) {
+                    const uint64_t in = r ? readlane64(top[r ? r - 1 : 0], 63) : 0ull;
+                    const uint64_t up = wave_shift_up(top[r], in);
+                    const int p = r * 64 + lane;
+                    top[r] = p < rank ? top[r] : (p == rank ? x : up);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < NL; r++) {
+                if (r * 64 + lane >= kp) top[r] = JX_EMPTY_KEY;
+                if (r == (kp - 1) >> 6) worst = readlane64(top[r], (kp - 1) & 63);
+            }
+        }
+    }
+    if constexpr (DT == JX_U8) {
+#pragma unroll
+        for (int r = 0; r < NL; r++) {
+            const int p = r * 64 + lane;
+            if (p < a.k) {
+                const bool valid = top[r] != JX_EMPTY_KEY;
+                a.out_ids[qi * a.k + p] = valid ? (uint32_t)top[r] : JX_NONE_ID;
+                a.out_dist[qi * a.k + p] = valid ? (float)(uint32_t)(top[r] >> 32) : __builtin_inff();
+            }
+        }
+        return;
+    }
+    // ---- the distances of bruteforce_tile_kernel: one candidate per lane, the same operations in the same order
+    const uint4* q4 = reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(a.queries) + (size_t)qi * (size_t)(a.nch * 16));
+    float qq = 0.f;  // |q|^2: binary16 in that kernel's order, float32 only for the bound
+    for (int ch = 0; ch < a.nch; ch++) qq = knn_sq<DT>(q4[ch], qq);
+    int n_valid = 0;
+    for (int r = 0; r < NL; r++) {
+        uint64_t cur = JX_EMPTY_KEY;
+#pragma unroll
+        for (int x = 0; x < NL; x++)
+            if (x == r) cur = top[x];
+        const bool valid = cur != JX_EMPTY_KEY;
+        n_valid += __builtin_popcountll(ballot(valid));
+        if (ballot(valid) == 0ull) {
+            ex[r * 64 + lane] = JX_EMPTY_KEY;
+            continue;
+        }
+        const uint32_t id = valid ? (uint32_t)cur : 0u;
+        const uint4* b4 = reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(a.base) + (size_t)id * (size_t)(a.nch * 16));
+        float acc = 0.f, bb = 0.f;
+#pragma unroll 8
+        for (int ch = 0; ch < a.nch; ch++) {
+            const uint4 x = q4[ch], y = b4[ch];
+            if constexpr (DT == JX_F16) {
+                acc = hdot2(x.x, y.x, acc);
+                acc = hdot2(x.y, y.y, acc);
+                acc = hdot2(x.z, y.z, acc);
+                acc = hdot2(x.w, y.w, acc);
+                bb = knn_sq<DT>(y, bb);
+            } else {
+                float d;
+                d = __uint_as_float(x.x) - __uint_as_float(y.x);
+                acc = fmaf(d, d, acc);
+                d = __uint_as_float(x.y) - __uint_as_float(y.y);
+                acc = fmaf(d, d, acc);
+                d = __uint_as_float(x.z) - __uint_as_float(y.z);
+                acc = fmaf(d, d, acc);
+                d = __uint_as_float(x.w) - __uint_as_float(y.w);
+                acc = fmaf(d, d, acc);
+            }
+        }
+        const float dist = DT == JX_F16 ? fmaxf(qq + bb - 2.f * acc, 0.f) : acc;
+        ex[r * 64 + lane] = valid ? (((uint64_t)f32_to_ordered(dist) << 32) | id) : JX_EMPTY_KEY;
+    }
+    wave_sync();
+    float kth = -1.f;
+    for (int r = 0; r < NL; r++) {
+        const uint64_t mine = ex[r * 64 + lane];
+        int rank = 0;
+        for (int t = 0; t < n_valid; t++) rank += ex[t] < mine ? 1 : 0;
+        if (mine != JX_EMPTY_KEY && rank < a.k) {
+            const float dist = ordered_to_f32((uint32_t)(mine >> 32));
+            a.out_ids[qi * a.k + rank] = (uint32_t)mine;
+            a.out_dist[qi * a.k + rank] = dist;
+            if (rank == a.k - 1) kth = dist;
+        }
+    }
+    for (int p = n_valid + lane; p < a.k; p += 64) {
+        a.out_ids[qi * a.k + p] = JX_NONE_ID;
+        a.out_dist[qi * a.k + p] = __builtin_inff();
+    }
+    // ---- proof.  Both forms are sums of d terms in float32: each is off by at most (d + 8) 2^-24 (|q| + |b|)^2, the
+    // comparison with the rounded threshold included.  Comparisons with NaN leave the result unproven
+    uint32_t bm = 0;
+    for (int s = lane; s < a.nsplit; s += 64) bm = a.bmax[s] > bm ? a.bmax[s] : bm;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const uint32_t o = shfl_xor(bm, m);
+        bm = o > bm ? o : bm;
+    }
+    const uint64_t who = ballot(kth >= 0.f);
+    bool proven = n_valid == a.n;
+    if (!proven && n_valid == kp && who && bm < 0x7F800000u) {
+        const float e_k = __uint_as_float(readlane32(__float_as_uint(kth), __builtin_ctzll(who)));
+        const float len = sqrtf(qq) + sqrtf(__uint_as_float(bm));
+        const float eps = (float)(a.d + 16) * 1.2e-7f * (len * len);
+        proven = __uint_as_float((uint32_t)(worst >> 32)) - eps > e_k;
+    }
+    if (lane == 0) a.redo[qi] = proven ? 0u : 1u;
+}
+
+// ------------------------------------------------------------------ launch
+
+template <int DT, int NL>
+static hipError_t launch_knn(const KnnArgs& a, hipStream_t st) {
+    constexpr bool U8 = DT == JX_U8;
+    dim3 grid((unsigned)((a.nq + KT - 1) / KT), (unsigned)a.nsplit), block(256);
+    const bool one = U8 && a.nch <= 8;
+    if (a.seed_steps) hipLaunchKernelGGL((one ? knn_tile_kernel<DT, 1, U8, true> : knn_tile_kernel<DT, 1, false, true>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((one ? knn_tile_kernel<DT, NL, U8, false> : knn_tile_kernel<DT, NL, false, false>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((knn_merge_kernel<DT, NL>), dim3((unsigned)a.nq), dim3(64), 0, st, a);
+    return hipGetLastError();
+}
+template <int DT>
+static hipError_t launch_knn_lists(const KnnArgs& a, hipStream_t st) {
+    return a.kp <= 64 ? launch_knn<DT, 1>(a, st) : launch_knn<DT, 3>(a, st);
+}
+
+// Takes the search over where it is the faster one and its lists fit scratch_bytes; *done says so.
+hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_bytes, hipStream_t st, bool* done) {
+    *done = false;
+    const bool exact = b.dtype == JX_U8;
+    const long long row = (long long)b.d * (exact ? 1 : (b.dtype == JX_F16 ? 2 : 4));
+    if (((uintptr_t)b.base | (uintptr_t)b.queries) & 15) return hipSuccess;  // rows are read 16 bytes at a time
+    KnnArgs a;
+    a.base = b.base;
+    a.queries = b.queries;
+    a.n = b.n;
+    a.nq = b.nq;
+    a.d = b.d;
+    a.nch = (int)(row / 16);
+    a.k = b.k;
+    a.kp = exact ? b.k : b.k + KNN_SLACK;
+    a.out_ids = b.out_ids;
+    a.out_dist = b.out_dist;
+    const long long qt = (b.nq + KT - 1) / KT, steps = (b.n + KT - 1) / KT;
+    // as many slices as keep every CU at its two workgroups; one workgroup more would be a round of its own
+    long long nsplit = KNN_BLOCKS / qt > 1 ? KNN_BLOCKS / qt : 1;
+    if (nsplit > 512) nsplit = 512;
+    if (nsplit > steps / 2) nsplit = steps / 2;  // two steps at least
+    const long long aux = ((b.nq * 4 + 255) & ~255LL) + 4096 + 256;
+    const long long fit = (scratch_bytes - aux) / (b.nq * (a.kp * 8 + 4));
+    if (nsplit > fit) nsplit = fit;
+    // small searches end in one wave of the tiled kernel's smaller tiles (10 x 2,672 uint8, k = 50: 266 us there)
+    if (nsplit < 1 || qt * nsplit < 64) return hipSuccess;
+    a.nsplit = (int)nsplit;
+    a.r_th = (int)((a.kp + nsplit - 1) / nsplit);
+    uint8_t* p = (uint8_t*)scratch + scratch_bytes - aux;  // behind the lists and the published distances
+    p -= (uintptr_t)p & 255;
+    a.lists = (uint64_t*)scratch;
+    a.published = nsplit > 1 ? (uint32_t*)(a.lists + (size_t)b.nq * nsplit * a.kp) : nullptr;
+    a.redo = (uint32_t*)p;
+    a.bmax = (uint32_t*)(p + ((b.nq * 4 + 255) & ~255LL));
+    hipError_t e = hipSuccess;
+    // a first threshold from a sixteenth of every slice, where that is little against the rest
+    const long long each = steps / nsplit;
+    a.seed_steps = a.published && each >= 8 && a.r_th <= 32 ? (int)((each + 15) / 16) : 0;
+    if (a.published && !a.seed_steps) e = launch_fill_u32(a.published, b.nq * nsplit, 0x7F800000u, st);
+    if (e != hipSuccess) return e;
+    *done = true;
+    if (exact) return launch_knn_lists<JX_U8>(a, st);
+    e = b.dtype == JX_F16 ? launch_knn_lists<JX_F16>(a, st) : launch_knn_lists<JX_F32>(a, st);
+    if (e != hipSuccess) return e;
+    BfArgs again = b;  // tiles with a flagged query, over the lists (at least as long)
+    again.nsplit = a.nsplit < 64 ? a.nsplit : 64;
+    again.partial = (uint64_t*)scratch;
+    again.redo = a.redo;
+    return launch_bruteforce(again, st);
+}
+
+}  // namespace jx
