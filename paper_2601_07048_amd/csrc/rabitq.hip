@@ -196,10 +196,14 @@ __global__ void __launch_bounds__(256) encode_kernel(EncodeArgs a) {
 //     <xbar,|r|> = l1/2 + sum_j PrefA[cnt_j(t)],   ||xbar||^2 = d/4 + sum_j 2j cnt_j(t),
 // where cnt_j(t) counts the level-j breakpoints <= t and PrefA are prefix sums of the magnitudes in descending
 // order.  So only the d magnitudes are sorted (bitonic network in LDS); the level-j breakpoints j/|r|_(p) are then
-// already ascending in p, their quotients are tabulated once in double (comparisons are on the very values the
-// definition compares), and every breakpoint evaluates its cosine with one binary search per level: the state at
-// the end of its group of equal t.  The largest cosine wins, the smallest t among equals, and t -> 0+ competes.  The
-// level of a coordinate is then the number of its own breakpoints that are <= t.
+// already ascending in p.  Breakpoints are compared as products, j |r|_(p') against j' |r|_(p), which are exact in double
+// (two different quotients of integers below 8 and float32 numbers differ by 2^-27 of their size, so the rounded quotients
+// compare alike).  A thread takes consecutive breakpoints of one level and moves its counts along: the state at the end of
+// each group of equal t.  The largest cosine wins, the smallest t among equals, and t -> 0+ competes.  The level of a
+// coordinate is then the number of its own breakpoints that are <= t.
+// Bound: vector instructions.  A table of the quotients and a binary search per breakpoint and level took ten times the LDS
+// reads, and its 54 KB held a CU to two workgroups: 50,000 vectors of d = 960, 4 bits 16.7 -> 7.8 ms.  Bounding the cosine
+// on a grid of 256 values of t first left most breakpoints in and took 15.7 ms.
 #define MC_CAP 8192   // breakpoints per vector
 #define MC_DMAX 4096  // dimensions
 
@@ -219,18 +223,21 @@ __device__ __forceinline__ double block_scan_incl(double v, double* ws, int tid)
     return v + off;
 }
 
+// NL = 2^(bits-1) - 1 levels
+template <int NL>
 __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
     extern __shared__ __align__(16) unsigned char dyn[];
-    const int half = 1 << (a.bits - 1), nl = half - 1;
+    constexpr int half = NL + 1;
     int dpad = 256;
     while (dpad < a.d) dpad <<= 1;
     float* sa = reinterpret_cast<float*>(dyn);                          // [dpad] magnitudes, descending
     double* pref = reinterpret_cast<double*>(dyn + (size_t)dpad * 4);   // [dpad + 1] prefix sums of sa
-    double* Q = pref + dpad + 2;                                        // [nl][d] quotients j / sa[p]
     __shared__ double ws[8];
     __shared__ double red_c[256], red_t[256];
+    __shared__ float red_a[256];  // the breakpoint's magnitude; its level is red_t * red_a
+    __shared__ int red_j[256];
     __shared__ int s_npos;
-    __shared__ double s_l1, s_l2, s_ip, s_best_t;
+    __shared__ double s_l1, s_l2, s_ip;
     const int tid = threadIdx.x;
     const long long v = blockIdx.x;
     const float* r = a.rot + (size_t)v * a.d;
@@ -287,39 +294,62 @@ __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
             pref[e + 1] = run;
         }
     }
-    for (int e = tid; e < nl * npos; e += 256) {
-        const int j = e / npos + 1, p = e - (j - 1) * npos;
-        Q[(size_t)(j - 1) * a.d + p] = (double)j / (double)sa[p];
-    }
     __syncthreads();
     // ---- every breakpoint evaluates the cosine at the end of its group of equal t
     const double ip0 = 0.5 * s_l1, nn0 = 0.25 * (double)a.d;
     double best = -1.0, best_t = __builtin_inf();
-    for (int e = tid; e < nl * npos; e += 256) {
-        const int j = e / npos, p = e - j * npos;
-        const double t = Q[(size_t)j * a.d + p];
-        double ip = ip0, nn = nn0;
-        for (int jj = 0; jj < nl; jj++) {
-            const double* q = Q + (size_t)jj * a.d;
-            int lo = 0, hi = npos;  // number of level-(jj+1) breakpoints <= t
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (q[mid] <= t)
-                    lo = mid + 1;
-                else
-                    hi = mid;
+    float best_a = 1.f;
+    int best_j = 0;
+    constexpr int SEGS = 256 / NL;  // threads per level
+    const int lev = tid / SEGS, run = (npos + SEGS - 1) / SEGS;
+    const int p0 = (tid - lev * SEGS) * run, p1 = lev < NL ? (p0 + run < npos ? p0 + run : npos) : 0;
+    if (p0 < p1) {
+        const double J = (double)(lev + 1);
+        int cnt[NL];  // level-(jj+1) breakpoints <= t
+        {
+            const double A = (double)sa[p0];
+#pragma unroll
+            for (int jj = 0; jj < NL; jj++) {
+                const double lim = (double)(jj + 1) * A;
+                int lo = 0, hi = npos;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (lim <= J * (double)sa[mid])
+                        lo = mid + 1;
+                    else
+                        hi = mid;
+                }
+                cnt[jj] = lo;
             }
-            ip += pref[lo];
-            nn += 2.0 * (double)(jj + 1) * (double)lo;
         }
-        const double c = ip / sqrt(nn);
-        if (c > best || (c == best && t < best_t)) {
-            best = c;
-            best_t = t;
+        for (int p = p0; p < p1; p++) {
+            const float Af = sa[p];
+            const double A = (double)Af;
+            double ip = ip0, nn = nn0;
+#pragma unroll
+            for (int jj = 0; jj < NL; jj++) {
+                const double lim = (double)(jj + 1) * A;
+                int lo = cnt[jj];
+                while (lo < npos && lim <= J * (double)sa[lo]) lo++;
+                cnt[jj] = lo;
+                ip += pref[lo];
+                nn += 2.0 * (double)(jj + 1) * (double)lo;
+            }
+            // most breakpoints are behind the best so far by more than this estimate is off
+            if ((float)ip * __builtin_amdgcn_rsqf((float)nn) < (float)best * 0.999995f) continue;
+            const double c = ip / sqrt(nn);
+            if (c > best) {  // t grows within a thread: the first of equals stays
+                best = c;
+                best_t = J / A;
+                best_a = Af;
+                best_j = lev + 1;
+            }
         }
     }
     red_c[tid] = best;
     red_t[tid] = best_t;
+    red_a[tid] = best_a;
+    red_j[tid] = best_j;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
         if (tid < s) {
@@ -327,6 +357,8 @@ __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
             if (oc > red_c[tid] || (oc == red_c[tid] && ot < red_t[tid])) {
                 red_c[tid] = oc;
                 red_t[tid] = ot;
+                red_a[tid] = red_a[tid + s];
+                red_j[tid] = red_j[tid + s];
             }
         }
         __syncthreads();
@@ -334,10 +366,11 @@ __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
     if (tid == 0) {
         // the all-zero-level grid (t -> 0+) competes too; a later cosine must be strictly larger
         const double c0 = ip0 / sqrt(nn0);
-        s_best_t = (npos > 0 && nl > 0 && red_c[0] > c0) ? red_t[0] : 0.0;
+        if (!(npos > 0 && red_c[0] > c0)) red_j[0] = 0;
     }
     __syncthreads();
-    const double bt = s_best_t;
+    // level lv + 1 is reached where (lv + 1) / |r_i| <= j / a
+    const double bj = (double)red_j[0], ba = (double)red_a[0];
     // ---- codes: 32 / bits consecutive coordinates per thread -> one dword
     const double cb = ((double)(1 << a.bits) - 1.0) * 0.5;
     const int per = 32 / a.bits;
@@ -349,7 +382,7 @@ __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
             const double ax = fabs((double)x);
             int lv = 0;
             if (ax > 0.0)
-                while (lv + 1 < half && (double)(lv + 1) / ax <= bt) lv++;
+                while (lv + 1 < half && (double)(lv + 1) * ba <= bj * ax) lv++;
             const int u = x >= 0.0f ? half + lv : half - 1 - lv;
             w |= (uint32_t)u << (a.bits * j);
             ip += ((double)u - cb) * (double)x;
@@ -375,10 +408,9 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t st) {
         if ((a.bits != 4 && a.bits != 2) || a.d * nl > MC_CAP || a.d > MC_DMAX) return hipErrorInvalidValue;
         int dpad = 256;
         while (dpad < a.d) dpad <<= 1;
-        const size_t sh = (size_t)dpad * 4 + (size_t)(dpad + 2) * 8 + (size_t)nl * a.d * 8;
-        hipError_t e = hipFuncSetAttribute((const void*)encode_maxcos_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(encode_maxcos_kernel, dim3((unsigned)a.n), dim3(256), sh, st, a);
+        const size_t sh = (size_t)dpad * 4 + (size_t)(dpad + 2) * 8;
+        auto kern = a.bits == 4 ? encode_maxcos_kernel<7> : encode_maxcos_kernel<1>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)a.n), dim3(256), sh, st, a);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(encode_kernel, dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, st, a);
