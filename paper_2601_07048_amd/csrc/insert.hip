@@ -1297,6 +1297,109 @@ __global__ void __launch_bounds__(256) radix_scatter8_kernel(const uint64_t* key
     }
 }
 
+// ---- small edge buffers: bitonic chunks in LDS, then merge passes
+//
+// A pass of the radix sort is three launches of 4 to 14 us however few the keys are, and a sort is six or eight passes:
+// most of an insertion of a few points.  Up to SORT_ONE pairs are sorted by one workgroup in LDS, which lists the segments
+// as well; up to SORT_MERGE pairs by a workgroup per SORT_CHUNK pairs and a launch per doubling of the runs, every pair
+// finding its place by binary search in the neighbouring run.  The order is (key, value): what the stable radix sort
+// gives, because equal keys are emitted in ascending order of their values.
+// 16 insert calls of 32 points (2,048 pairs each) 6.65 -> 5.12 ms, a build of 200,000 points 43.4 -> 36.9 ms.
+#define SORT_ONE 8192
+#define SORT_CHUNK 4096
+#define SORT_MERGE (1 << 20)
+
+// one workgroup per `cap` pairs (a power of two); heads / counters: NULL, or the segment list of a single chunk
+__global__ void __launch_bounds__(1024) sort_chunk_kernel(const uint64_t* keys, const uint32_t* vals, uint64_t* keys_out, uint32_t* vals_out,
+                                                         long long n, int cap, uint32_t* heads, uint32_t* counters) {
+    extern __shared__ __align__(16) unsigned char dyn[];
+    uint64_t* sk = reinterpret_cast<uint64_t*>(dyn);        // [cap]
+    uint32_t* sv = reinterpret_cast<uint32_t*>(sk + cap);   // [cap]
+    __shared__ uint32_t wsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const long long base = (long long)blockIdx.x * cap;
+    const int m = (int)(n - base < cap ? n - base : cap);
+    for (int i = tid; i < cap; i += 1024) {
+        sk[i] = i < m ? keys[base + i] : JX_EMPTY_KEY;
+        sv[i] = i < m ? vals[base + i] : JX_NONE_ID;
+    }
+    __syncthreads();
+    for (int k = 2; k <= cap; k <<= 1) {
+        for (int j = k >> 1; j >= 1; j >>= 1) {
+            for (int p = tid; p < cap / 2; p += 1024) {
+                const int lo = ((p & ~(j - 1)) << 1) | (p & (j - 1)), hi = lo | j;
+                const uint64_t a = sk[lo], b = sk[hi];
+                const uint32_t x = sv[lo], y = sv[hi];
+                const bool after = a > b || (a == b && x > y);
+                if (after == ((lo & k) == 0)) {
+                    sk[lo] = b;
+                    sk[hi] = a;
+                    sv[lo] = y;
+                    sv[hi] = x;
+                }
+            }
+            // the 64 pairs of a wavefront lie in 128 neighbouring places while j <= 64: only before and after wider
+            // strides do the wavefronts wait for each other
+            if (j > 64 || (j == 1 && k > 64))
+                __syncthreads();
+            else
+                wave_sync();
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < m; i += 1024) {
+        keys_out[base + i] = sk[i];
+        vals_out[base + i] = sv[i];
+    }
+    if (!heads) return;
+    uint32_t done = 0;  // heads of the pairs before this round's
+    for (int i0 = 0; i0 < m; i0 += 1024) {
+        const int i = i0 + tid;
+        const uint32_t t = i < m ? (uint32_t)(sk[i] >> 32) : JX_NONE_ID;
+        const bool head = t != JX_NONE_ID && (i == 0 || (uint32_t)(sk[i - 1] >> 32) != t);
+        const uint64_t hm = ballot(head);
+        if (lane == 0) wsum[wave] = (uint32_t)__builtin_popcountll(hm);
+        __syncthreads();
+        uint32_t before = done, all = 0;
+        for (int w = 0; w < 16; w++) {
+            before += w < wave ? wsum[w] : 0u;
+            all += wsum[w];
+        }
+        if (head) heads[before + (uint32_t)prefix_count(hm)] = (uint32_t)i;
+        done += all;
+        __syncthreads();
+    }
+    if (tid < 16) counters[tid] = tid == 0 ? done : 0u;
+}
+
+// sorted runs of `run` pairs -> runs of twice as many
+__global__ void __launch_bounds__(256) merge_runs_kernel(const uint64_t* keys, const uint32_t* vals, uint64_t* keys_out, uint32_t* vals_out,
+                                                        long long n, long long run) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint64_t k = keys[i];
+    const uint32_t v = vals[i];
+    const long long r = i / run, pair = (r >> 1) * 2 * run;
+    const bool right = r & 1;
+    const long long o0 = right ? pair : pair + run;  // the neighbouring run
+    const long long o1 = o0 + run < n ? o0 + run : n;
+    long long lo = o0 < n ? o0 : n, hi = o1;
+    if (hi < lo) hi = lo;
+    const long long first = lo;
+    while (lo < hi) {  // its pairs that come before this one; of equal pairs (padding) the left run's come first
+        const long long mid = (lo + hi) >> 1;
+        const uint64_t ko = keys[mid];
+        const bool before = ko < k || (ko == k && (vals[mid] < v || (right && vals[mid] == v)));
+        if (before)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    const long long at = pair + (i - r * run) + (lo - first);
+    keys_out[at] = k;
+    vals_out[at] = v;
+}
+
 __global__ void __launch_bounds__(1024) segment_heads_kernel(const uint64_t* keys, long long n, uint32_t* heads, uint32_t* nseg) {
     __shared__ uint32_t woff[17];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
@@ -1485,6 +1588,47 @@ hipError_t launch_radix_sort(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_
         uint32_t* tv = vi; vi = vo; vo = tv;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_sort_edges(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b, long long n, int nbits,
+                             uint32_t* table, uint32_t* heads, uint32_t* counters, hipStream_t st) {
+    if (n > SORT_MERGE || n <= 0) {
+        hipError_t e = launch_radix_sort(keys_a, vals_a, keys_b, vals_b, n, nbits, table, st);
+        if (e != hipSuccess) return e;
+    } else {
+        int cap = SORT_CHUNK, passes = 0;
+        if (n <= SORT_ONE) {
+            cap = 64;
+            while (cap < n) cap *= 2;
+        } else {
+            for (long long run = SORT_CHUNK; run < n; run *= 2) passes++;
+        }
+        // the last pass writes to keys_a
+        uint64_t *ki = keys_a, *ko = passes & 1 ? keys_b : keys_a;
+        uint32_t *vi = vals_a, *vo = passes & 1 ? vals_b : vals_a;
+        const size_t sh = (size_t)cap * 12;
+        if (sh > 48 * 1024) {
+            hipError_t e = hipFuncSetAttribute((const void*)sort_chunk_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+            if (e != hipSuccess) return e;
+        }
+        const bool list = passes == 0 && heads;
+        hipLaunchKernelGGL(sort_chunk_kernel, dim3((unsigned)((n + cap - 1) / cap)), dim3(1024), sh, st, ki, vi, ko, vo, n, cap,
+                           list ? heads : nullptr, list ? counters : nullptr);
+        if (list) return hipGetLastError();
+        for (long long run = SORT_CHUNK; passes > 0; passes--, run *= 2) {
+            ki = ko;
+            vi = vo;
+            ko = ki == keys_a ? keys_b : keys_a;
+            vo = vi == vals_a ? vals_b : vals_a;
+            hipLaunchKernelGGL(merge_runs_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, ki, vi, ko, vo, n, run);
+        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (!heads) return hipSuccess;
+    hipError_t e = launch_fill_u32(counters, 16, 0u, st);
+    if (e != hipSuccess) return e;
+    return launch_segment_heads(keys_a, n, heads, counters, st);
 }
 
 hipError_t launch_scan_u32(uint32_t* data, long long n, hipStream_t st) {

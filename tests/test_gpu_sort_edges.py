@@ -1,0 +1,46 @@
+"""The sorts behind insertion and consolidation at the sizes where they change form: up to 8,192 edges in one workgroup, up
+to 2^20 by merge passes, the radix sort beyond.  The same points inserted with batches of other sizes go through other
+forms; every graph equals the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_common import dev, random_data, u32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def jx():
+    from paper_2601_07048_amd import jx as m
+    return m
+
+
+# edges of the last internal batch = points x R: one workgroup (full and not), one merge, several, runs that end early
+@pytest.mark.parametrize("n0,batch,R", [(1500, 1, 16), (1500, 33, 31), (2100, 512, 16), (2100, 513, 16), (3000, 700, 24), (6000, 1400, 48)])
+def test_insert_batches_equal_the_oracle(jx, n0, batch, R):
+    x = random_data(n0 + batch, 32, np.uint8, 31)
+    x[100:200] = x[0]  # equal distances
+    g = jx.Index(32, jx.U8, R, 24, 1.2, capacity=n0 + batch, max_batch=4096)
+    g.insert(dev(x[:n0]))
+    full = oracle.Index(32, np.uint8, R, 24, 1.2, n0 + batch)
+    full.insert(x[:n0])
+    full.insert(x[n0:])
+    g.insert(dev(x[n0:]))
+    assert np.array_equal(u32(g.export_graph()[0]), full.graph()[0])
+
+
+@pytest.mark.parametrize("drop", [3, 40, 700])
+def test_consolidation_equals_the_oracle(jx, drop):
+    n, R = 4000, 24
+    x = random_data(n, 32, np.uint8, 32)
+    ref = oracle.Index(32, np.uint8, R, 32, 1.2, n)
+    ref.insert(x)
+    g = jx.Index(32, jx.U8, R, 32, 1.2, capacity=n, max_batch=4096)
+    g.insert(dev(x))
+    ids = np.random.default_rng(4).choice(n, drop, replace=False).astype(np.uint32)
+    ref.delete(ids)
+    ref.consolidate()
+    g.delete(dev(ids))
+    g.consolidate()
+    assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0])
