@@ -662,8 +662,13 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     const long long aux = ((b.nq * 4 + 255) & ~255LL) + 4096 + 256;
     const long long fit = (scratch_bytes - aux) / (b.nq * (a.kp * 8 + 4));
     if (nsplit > fit) nsplit = fit;
-    // small searches end in one wave of the tiled kernel's smaller tiles (10 x 2,672 uint8, k = 50: 266 us there)
+    // Where the tiled kernel stays, tiled / this in us: few vectors (1,000 x 2,000 float32 d = 96, k = 10 181 / 210, 300 x
+    // 8,000, k = 1 125 / 155; uint8 300 x 8,000 108 / 111, k = 10 213 / 112); hardly any workgroups; and one neighbour or
+    // a few, whose lists cost it little, of more than 64 queries among fewer than 100,000 short vectors (130 x 50,000 uint8,
+    // k = 1 176 / 214, but 8,118 x 56,268 1450 / 535, 1,000 x 200,000 615 / 364 and d = 960 1,000 x 20,000 1145 / 669)
     if (nsplit < 1 || qt * nsplit < 64) return hipSuccess;
+    if (b.n < (exact ? 6000 : 16384)) return hipSuccess;
+    if (b.k < 8 && row < 1024 && b.nq > 64 && b.n < 100000 && b.nq * b.n < 60000000) return hipSuccess;
     a.nsplit = (int)nsplit;
     a.r_th = (int)((a.kp + nsplit - 1) / nsplit);
     uint8_t* p = (uint8_t*)scratch + scratch_bytes - aux;  // behind the lists and the published distances
@@ -673,9 +678,10 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     a.redo = (uint32_t*)p;
     a.bmax = (uint32_t*)(p + ((b.nq * 4 + 255) & ~255LL));
     hipError_t e = hipSuccess;
-    // a first threshold from a sixteenth of every slice, where that is little against the rest
+    // a first threshold from a sixteenth of every slice, one step at least: without it the first step of every slice is
+    // merged whole, 200 us and more
     const long long each = steps / nsplit;
-    a.seed_steps = a.published && each >= 8 && a.r_th <= 32 ? (int)((each + 15) / 16) : 0;
+    a.seed_steps = a.published && a.r_th <= 32 ? (int)((each + 15) / 16) : 0;
     if (a.published && !a.seed_steps) e = launch_fill_u32(a.published, b.nq * nsplit, 0x7F800000u, st);
     if (e != hipSuccess) return e;
     *done = true;
