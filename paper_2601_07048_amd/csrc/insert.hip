@@ -1567,20 +1567,24 @@ hipError_t launch_reverse_merge(int dtype, const InsertArgs& a, hipStream_t st) 
 
 // Sorts n (key, value) pairs on key bits [0, nbits), stable.  The result is in
 // keys_a/vals_a again (an even number of passes is always run).
-hipError_t launch_radix_sort(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b, long long n, int nbits,
-                             uint32_t* table, hipStream_t st) {
+static hipError_t launch_radix_sort(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b, long long n, int nbits,
+                                    int low_bits, uint32_t* table, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     const int ntiles = (int)((n + RS_TILE - 1) / RS_TILE);
-    // an even number of 8-bit passes (the result has to end in keys_a / vals_a; a pass over bits beyond nbits only
-    // copies).  With 4-bit digits the same sort took 14 passes of 162 us at 6.4M keys; these take 80 us each: the
-    // tile leaves LDS sorted, so the global writes are runs
-    int passes = (nbits + 7) / 8;
-    if (passes & 1) passes++;
-    if (passes > 8) passes = 8;
+    // an even number of 8-bit passes (the result has to end in keys_a / vals_a).  With 4-bit digits the same sort took 14
+    // passes of 162 us at 6.4M keys; these take 80 us each: the tile leaves LDS sorted, so the global writes are runs.
+    // Bits low_bits..31 are zero: no pass over them (the (vertex, candidate) pairs of a consolidation: six passes for eight)
+    int shifts[9], passes = 0;
+    for (int b = 0; b < (low_bits < 32 ? low_bits : 32) && b < nbits; b += 8) shifts[passes++] = b;
+    for (int b = 32; b < nbits; b += 8) shifts[passes++] = b;
+    if (passes & 1) {
+        shifts[passes] = shifts[passes - 1];  // the same digit again moves nothing
+        passes++;
+    }
     uint64_t *ki = keys_a, *ko = keys_b;
     uint32_t *vi = vals_a, *vo = vals_b;
     for (int p = 0; p < passes; p++) {
-        const int shift = 8 * p;
+        const int shift = shifts[p];
         hipLaunchKernelGGL(radix_hist8_kernel, dim3(ntiles), dim3(256), 0, st, ki, n, shift, table, ntiles);
         hipLaunchKernelGGL(radix_rowscan8_kernel, dim3(256), dim3(1024), 0, st, table, ntiles);
         hipLaunchKernelGGL(radix_scatter8_kernel, dim3(ntiles), dim3(256), 0, st, ki, vi, ko, vo, n, shift, table, ntiles);
@@ -1591,9 +1595,9 @@ hipError_t launch_radix_sort(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_
 }
 
 hipError_t launch_sort_edges(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b, long long n, int nbits,
-                             uint32_t* table, uint32_t* heads, uint32_t* counters, hipStream_t st) {
+                             int low_bits, uint32_t* table, uint32_t* heads, uint32_t* counters, hipStream_t st) {
     if (n > SORT_MERGE || n <= 0) {
-        hipError_t e = launch_radix_sort(keys_a, vals_a, keys_b, vals_b, n, nbits, table, st);
+        hipError_t e = launch_radix_sort(keys_a, vals_a, keys_b, vals_b, n, nbits, low_bits, table, st);
         if (e != hipSuccess) return e;
     } else {
         int cap = SORT_CHUNK, passes = 0;

@@ -707,7 +707,7 @@ static int run_subbatch(jx_index* idx, const InsertWork& w, int64_t pos0, int64_
     while (((int64_t)1 << tbits) <= n_after) tbits++;
     const int64_t E = B * p.R;
     JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys0), (uint32_t*)(W + w.vals0), (uint64_t*)(W + w.keys1),
-                                 (uint32_t*)(W + w.vals1), E, 32 + tbits, (uint32_t*)(W + w.table), (uint32_t*)(W + w.heads),
+                                 (uint32_t*)(W + w.vals1), E, 32 + tbits, 32, (uint32_t*)(W + w.table), (uint32_t*)(W + w.heads),
                                  (uint32_t*)(W + w.counters), st));
     // 4. per target: append or robustPrune
     // LDS room per wavefront for the vectors of a full row plus up to 32 new edges (96 x 128 bytes);
@@ -999,11 +999,11 @@ int jx_consolidate(jx_index* idx, void* stream) {
             JX_HIP(jx::launch_consol_emit(c, st));
             // (v, candidate) order brings repeated candidates together
             JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys0), (uint32_t*)(W + w.vals0), (uint64_t*)(W + w.keys1),
-                                         (uint32_t*)(W + w.vals1), E, 32 + tbits, (uint32_t*)(W + w.table), nullptr, nullptr, st));
+                                         (uint32_t*)(W + w.vals1), E, 32 + tbits, tbits, (uint32_t*)(W + w.table), nullptr, nullptr, st));
             JX_HIP(jx::launch_consol_dist(p.dtype, c, (uint64_t*)(W + w.keys1), (uint32_t*)(W + w.vals1), st));
             // (v, distance) order; the sort is stable, so equal distances stay in id order
             JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys1), (uint32_t*)(W + w.vals1), (uint64_t*)(W + w.keys0),
-                                         (uint32_t*)(W + w.vals0), E, 32 + tbits, (uint32_t*)(W + w.table), (uint32_t*)(W + w.heads),
+                                         (uint32_t*)(W + w.vals0), E, 32 + tbits, 32, (uint32_t*)(W + w.table), (uint32_t*)(W + w.heads),
                                          (uint32_t*)(W + w.counters), st));
             a.E = E;
             a.B = (E + p.R - 1) / p.R;
