@@ -210,7 +210,8 @@ __global__ void __launch_bounds__(256) encode_kernel(EncodeArgs a) {
 // each group of equal t.  The largest cosine wins, the smallest t among equals, and t -> 0+ competes.  The level of a
 // coordinate is then the number of its own breakpoints that are <= t.
 // Bound: vector instructions.  A table of the quotients and a binary search per breakpoint and level took ten times the LDS
-// reads, and its 54 KB held a CU to two workgroups: 50,000 vectors of d = 960, 4 bits 16.7 -> 7.8 ms.  Bounding the cosine
+// reads, and its 54 KB held a CU to two workgroups: 50,000 vectors of d = 960, 4 bits 16.7 -> 7.8 ms,
+// with the runs that cannot reach the best cosine ended early 7.1 ms.  Bounding the cosine
 // on a grid of 256 values of t first left most breakpoints in and took 15.7 ms.
 #define MC_CAP 8192   // breakpoints per vector
 #define MC_DMAX 4096  // dimensions
@@ -244,7 +245,9 @@ __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
     __shared__ double red_c[256], red_t[256];
     __shared__ float red_a[256];  // the breakpoint's magnitude; its level is red_t * red_a
     __shared__ int red_j[256];
+    __shared__ uint32_t s_low;
     __shared__ int s_npos;
+    if (threadIdx.x == 0) s_low = 0u;  // barriers follow before it is used
     __shared__ double s_l1, s_l2, s_ip;
     const int tid = threadIdx.x;
     const long long v = blockIdx.x;
@@ -306,30 +309,41 @@ __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
     // ---- every breakpoint evaluates the cosine at the end of its group of equal t
     const double ip0 = 0.5 * s_l1, nn0 = 0.25 * (double)a.d;
     double best = -1.0, best_t = __builtin_inf();
-    float best_a = 1.f;
+    float best_a = 1.f, best_est = -1.f;
     int best_j = 0;
+    // float32 estimates of the cosine, in units of the sum of the magnitudes: any float32 vector stays in range
+    const double unit = 1.0 / s_l1;
     constexpr int SEGS = 256 / NL;  // threads per level
     const int lev = tid / SEGS, run = (npos + SEGS - 1) / SEGS;
     const int p0 = (tid - lev * SEGS) * run, p1 = lev < NL ? (p0 + run < npos ? p0 + run : npos) : 0;
+    const double J = (double)(lev + 1);
+    int cnt[NL];  // level-(jj+1) breakpoints <= t
     if (p0 < p1) {
-        const double J = (double)(lev + 1);
-        int cnt[NL];  // level-(jj+1) breakpoints <= t
-        {
-            const double A = (double)sa[p0];
+        const double A = (double)sa[p0];
+        double ip = ip0, nn = nn0;
 #pragma unroll
-            for (int jj = 0; jj < NL; jj++) {
-                const double lim = (double)(jj + 1) * A;
-                int lo = 0, hi = npos;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (lim <= J * (double)sa[mid])
-                        lo = mid + 1;
-                    else
-                        hi = mid;
-                }
-                cnt[jj] = lo;
+        for (int jj = 0; jj < NL; jj++) {
+            const double lim = (double)(jj + 1) * A;
+            int lo = 0, hi = npos;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (lim <= J * (double)sa[mid])
+                    lo = mid + 1;
+                else
+                    hi = mid;
             }
+            cnt[jj] = lo;
+            ip += pref[lo];
+            nn += 2.0 * (double)(jj + 1) * (double)lo;
         }
+        atomicMax(&s_low, __float_as_uint((float)(ip * unit) * __builtin_amdgcn_rsqf((float)nn)));
+    }
+    __syncthreads();
+    if (p0 < p1) {
+        // the largest cosine among the first breakpoints of all runs has to be reached; from t on no cosine exceeds the
+        // largest <xbar,|r|> there is over ||xbar|| at t: beyond the maximum, where the counts move fastest, runs end early
+        const float low = __uint_as_float(s_low) * 0.99999f;
+        const float ip_all = (float)((ip0 + (double)NL * pref[npos]) * unit);
         for (int p = p0; p < p1; p++) {
             const float Af = sa[p];
             const double A = (double)Af;
@@ -343,11 +357,15 @@ __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
                 ip += pref[lo];
                 nn += 2.0 * (double)(jj + 1) * (double)lo;
             }
+            const float inv = __builtin_amdgcn_rsqf((float)nn);
+            if (ip_all * inv < low) break;
             // most breakpoints are behind the best so far by more than this estimate is off
-            if ((float)ip * __builtin_amdgcn_rsqf((float)nn) < (float)best * 0.999995f) continue;
+            const float est = (float)(ip * unit) * inv;
+            if (est < best_est * 0.999995f || est < low) continue;
             const double c = ip / sqrt(nn);
             if (c > best) {  // t grows within a thread: the first of equals stays
                 best = c;
+                best_est = est;
                 best_t = J / A;
                 best_a = Af;
                 best_j = lev + 1;
