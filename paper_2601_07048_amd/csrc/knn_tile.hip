@@ -35,7 +35,10 @@ typedef _Float16 kf16x8 __attribute__((ext_vector_type(8)));
 #define KROW 144      // bytes of a staged row: 128 and 16 of padding
 #define KCAP 32       // buffer entries per query
 #define KFLUSH 16     // a buffer with this many entries is merged
-#define KINF 0x50000000  // uint8: above every distance (6,144 x 255^2 < 2^29), far from overflow
+#define KU8_ROW 16384    // uint8: longest row, see KINF
+// uint8: above every distance (16,384 x 255^2 is just under 2^30), and no sum overflows: 2 <q, b> of the shifted values is at most
+// 2^29, |q|^2 at most 2^28, so 2 <q, b> + KINF - |q|^2 stays below 2^31 and 2 <q, b> - |b|^2 above -2^30
+#define KINF 0x50000000
 
 template <int DT> struct KAcc { typedef kf32x16 type; typedef float elem; };
 template <> struct KAcc<JX_U8> { typedef ki32x16 type; typedef int elem; };
@@ -643,6 +646,7 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     const bool exact = b.dtype == JX_U8;
     const long long row = (long long)b.d * (exact ? 1 : (b.dtype == JX_F16 ? 2 : 4));
     if (((uintptr_t)b.base | (uintptr_t)b.queries) & 15) return hipSuccess;  // rows are read 16 bytes at a time
+    if (exact && row > KU8_ROW) return hipSuccess;
     KnnArgs a;
     a.base = b.base;
     a.queries = b.queries;

@@ -1,0 +1,30 @@
+"""The exhaustive search on the matrix cores at the ends of what it takes: rows so long that uint8 distances leave its
+integer range.  Every result is compared with the tiled kernel's, which rows on 4-byte boundaries take."""
+import pytest
+import torch
+
+from test_gpu_knn import check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def jx():
+    from paper_2601_07048_amd import jx as m
+    return m
+
+
+@pytest.mark.parametrize("d", [16_384, 16_400, 20_640, 20_656, 43_696, 50_176])
+def test_uint8_rows_of_any_length(jx, d):
+    """Rows of nothing but 0 and nothing but 255 lie d x 255^2 apart: 2^30.3 at 20,656 dimensions, 2^31.6 at 50,176."""
+    b = torch.zeros((16_400, d), dtype=torch.uint8, device="cuda")
+    b[9_000:] = 255
+    b[100, 0] = 3
+    q = torch.zeros((4, d), dtype=torch.uint8, device="cuda")
+    q[1:] = 255
+    q[2, ::2] = 0
+    ids, dist = check(jx, b, q, 10)
+    assert ids[0].tolist() == list(range(10)) and ids[1].tolist() == list(range(9_000, 9_010))
+    assert not dist[:2].any()
+    _, dist = check(jx, b[:9_000].repeat(2, 1), q, 10)  # no base vector near; 100 and 9,100 a little nearer
+    assert dist[1, 2:].eq(float(d * 255 ** 2)).all()
