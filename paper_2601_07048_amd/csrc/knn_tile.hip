@@ -604,7 +604,8 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
         a.out_dist[qi * a.k + p] = __builtin_inff();
     }
     // ---- proof.  Both forms are sums of d terms in float32: each is off by at most (d + 8) 2^-24 (|q| + |b|)^2, the
-    // comparison with the rounded threshold included.  Comparisons with NaN leave the result unproven
+    // comparison with the rounded threshold included, and where squares are subnormal by half of 2^-149 for each of at
+    // most 4 d operations of the two.  Comparisons with NaN leave the result unproven
     uint32_t bm = 0;
     for (int s = lane; s < a.nsplit; s += 64) bm = a.bmax[s] > bm ? a.bmax[s] : bm;
 #pragma unroll
@@ -617,7 +618,7 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
     if (!proven && n_valid == kp && who && bm < 0x7F800000u) {
         const float e_k = __uint_as_float(readlane32(__float_as_uint(kth), __builtin_ctzll(who)));
         const float len = sqrtf(qq) + sqrtf(__uint_as_float(bm));
-        const float eps = (float)(a.d + 16) * 1.2e-7f * (len * len);
+        const float eps = (float)(a.d + 16) * 1.2e-7f * (len * len) + (float)(a.d + 16) * 0x1p-147f;
         proven = __uint_as_float((uint32_t)(worst >> 32)) - eps > e_k;
     }
     if (lane == 0) a.redo[qi] = proven ? 0u : 1u;

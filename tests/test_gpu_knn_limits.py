@@ -1,5 +1,5 @@
 """The exhaustive search on the matrix cores at the ends of what it takes: rows so long that uint8 distances leave its
-integer range.  Every result is compared with the tiled kernel's, which rows on 4-byte boundaries take."""
+integer range, floats so small that squares are subnormal.  Every result is compared with the tiled kernel's, which rows on 4-byte boundaries take."""
 import pytest
 import torch
 
@@ -28,3 +28,12 @@ def test_uint8_rows_of_any_length(jx, d):
     assert not dist[:2].any()
     _, dist = check(jx, b[:9_000].repeat(2, 1), q, 10)  # no base vector near; 100 and 9,100 a little nearer
     assert dist[1, 2:].eq(float(d * 255 ** 2)).all()
+
+
+@pytest.mark.parametrize("scale", [1e-18, 1e-20, 1e-22, 7e-23, 5e-23, 2e-23])
+def test_tiny_floats(jx, scale):
+    """Where squares are subnormal an operation is off by up to half of 2^-149 however small its result."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    for _ in range(4):
+        b, q = (torch.randn((n, 32), device="cuda", generator=g) * scale for n in (20_000, 400))
+        check(jx, b, q, 10)
