@@ -23,6 +23,7 @@
 // 1,000 x 100,003 float32 d = 960, k = 100 12.9 -> 2.7 ms; 1,000 x 100,000 binary16 d = 960, k = 10 3.97 -> 0.84 ms;
 // 2 x 234,001 float32 d = 128, k = 1 1.12 -> 0.17 ms.  Without the seeds the lists fill with what comes first: 5.6 and 5.3 ms.
 #include "jx_distance.h"
+#include "knn_bound.h"
 
 namespace jx {
 
@@ -49,7 +50,7 @@ struct KnnLds {
     uint32_t cnt[KT];   // entries appended to buf (may exceed KCAP: the rest is offered again)
     uint32_t fill[KT];  // entries of the query's list
     uint32_t lim[KT];   // threshold: int / float bits, exclusive
-    uint32_t t[KT];     // lim - |q|^2
+    uint32_t t[KT];     // lim - |q|^2 (floats: knn_threshold)
     uint32_t qn[KT], bn[KT];
     uint32_t again;
 };
@@ -182,7 +183,7 @@ __device__ __forceinline__ void knn_flush(KnnLds& S, const int q, uint64_t* list
         if constexpr (DT == JX_U8)
             S.t[q] = (uint32_t)((int)lim - (int)S.qn[q]);
         else
-            S.t[q] = __float_as_uint(__uint_as_float(lim) - __uint_as_float(S.qn[q]));
+            S.t[q] = __float_as_uint(knn_threshold(__uint_as_float(lim), __uint_as_float(S.qn[q])));
         S.fill[q] = (uint32_t)n_new;
         S.cnt[q] = 0;
     }
@@ -303,7 +304,7 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                             if (DT == JX_U8)
                                 S.t[row] = q0 + row < a.nq ? (uint32_t)((int)S.lim[row] - (int)y) : 0xB0000000u;
                             else if (S.lim[row] < 0x7F800000u)
-                                S.t[row] = q0 + row < a.nq ? __float_as_uint(__uint_as_float(S.lim[row]) - (float)y) : 0xFF800000u;
+                                S.t[row] = q0 + row < a.nq ? __float_as_uint(knn_threshold(__uint_as_float(S.lim[row]), (float)y)) : 0xFF800000u;
                             else
                                 S.t[row] = q0 + row < a.nq ? 0x7F800000u : 0xFF800000u;
                         }
