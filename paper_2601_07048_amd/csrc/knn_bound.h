@@ -1,6 +1,7 @@
 // Rounding rules of the exhaustive search on the matrix cores (knn_tile.hip): plain float arithmetic, so that the test of
 // these rules can compile them for the CPU.
 #pragma once
+#include <math.h>
 
 #ifdef __HIPCC__
 #define JX_HD __host__ __device__ __forceinline__
@@ -16,5 +17,19 @@ namespace jx {
 // u (|q|^2 + lim) + u lim, the sum here rounds up past |b|^2 <= 2 (|q|^2 + lim) within 4 u (|q|^2 + lim), and the
 // operations below lose 3 u (|q|^2 + lim): 9 u in all, and 16 u are added
 JX_HD float knn_threshold(float lim, float qq) { return (lim - qq) + (lim + qq) * 0x1p-20f; }
+
+// How far the two forms of a vector's distance (the norm form that chooses candidates, the form of the result) can be apart
+// if the result's form is at most e: both are sums of d terms, each off by at most (d + 8) 2^-24 (|q| + |b|)^2, the
+// comparison with a rounded threshold included, and where squares are subnormal by half of 2^-149 for each of at most 4 d
+// operations of the two.  |b| is at most the longest vector's (bb_max = |b|^2, infinity: unknown), and at most |q| + sqrt(e)
+// by the triangle inequality, the rounding of e included by the last factor.  Holds up to KNN_FLOAT_D dimensions
+#define KNN_FLOAT_D 65536
+JX_HD float knn_eps(int d, float qq, float e, float bb_max) {
+    const float c = (float)(d + 16) * 1.2e-7f;
+    float len = (2.f * sqrtf(qq) + sqrtf(e)) * (1.f + sqrtf(c));
+    const float all = sqrtf(qq) + sqrtf(bb_max);
+    if (all < len) len = all;
+    return c * (len * len) + (float)(d + 16) * 0x1p-147f;  // infinity where a norm of that length could overflow
+}
 
 }  // namespace jx

@@ -604,9 +604,9 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
         a.out_ids[qi * a.k + p] = JX_NONE_ID;
         a.out_dist[qi * a.k + p] = __builtin_inff();
     }
-    // ---- proof.  Both forms are sums of d terms in float32: each is off by at most (d + 8) 2^-24 (|q| + |b|)^2, the
-    // comparison with the rounded threshold included, and where squares are subnormal by half of 2^-149 for each of at
-    // most 4 d operations of the two.  Comparisons with NaN leave the result unproven
+    // ---- proof: what was left out is no nearer than the last entry kept, less what the forms can differ by (knn_eps), and
+    // that has to exceed the k-th distance.  A float32 vector with an infinity is infinitely far away; a binary16 one and any
+    // with a NaN leave every result unproven, as do comparisons with NaN
     uint32_t bm = 0;
     for (int s = lane; s < a.nsplit; s += 64) bm = a.bmax[s] > bm ? a.bmax[s] : bm;
 #pragma unroll
@@ -616,11 +616,9 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
     }
     const uint64_t who = ballot(kth >= 0.f);
     bool proven = n_valid == a.n;
-    if (!proven && n_valid == kp && who && bm < 0x7F800000u) {
+    if (!proven && n_valid == kp && who && bm < (DT == JX_F16 ? 0x7F800000u : 0x7F800001u)) {
         const float e_k = __uint_as_float(readlane32(__float_as_uint(kth), __builtin_ctzll(who)));
-        const float len = sqrtf(qq) + sqrtf(__uint_as_float(bm));
-        const float eps = (float)(a.d + 16) * 1.2e-7f * (len * len) + (float)(a.d + 16) * 0x1p-147f;
-        proven = __uint_as_float((uint32_t)(worst >> 32)) - eps > e_k;
+        proven = __uint_as_float((uint32_t)(worst >> 32)) - knn_eps(a.d, qq, e_k, __uint_as_float(bm)) > e_k;
     }
     if (lane == 0) a.redo[qi] = proven ? 0u : 1u;
 }
@@ -648,7 +646,7 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     const bool exact = b.dtype == JX_U8;
     const long long row = (long long)b.d * (exact ? 1 : (b.dtype == JX_F16 ? 2 : 4));
     if (((uintptr_t)b.base | (uintptr_t)b.queries) & 15) return hipSuccess;  // rows are read 16 bytes at a time
-    if (exact && row > KU8_ROW) return hipSuccess;
+    if (exact ? row > KU8_ROW : b.d > KNN_FLOAT_D) return hipSuccess;
     KnnArgs a;
     a.base = b.base;
     a.queries = b.queries;

@@ -1,5 +1,5 @@
 """The rounding rules of the float form of the exhaustive search (knn_bound.h), compiled for the CPU: what its first
-thresholds count is admitted."""
+thresholds count is admitted, and the two forms of a distance are no further apart than its bound says."""
 import ctypes as C
 import os
 import subprocess
@@ -13,6 +13,9 @@ SOURCE = """
 #include "knn_bound.h"
 extern "C" void thresholds(const float* lim, const float* qq, float* out, long n) {
     for (long i = 0; i < n; i++) out[i] = jx::knn_threshold(lim[i], qq[i]);
+}
+extern "C" void bounds(int d, const float* qq, const float* e, const float* bb_max, float* out, long n) {
+    for (long i = 0; i < n; i++) out[i] = jx::knn_eps(d, qq[i], e[i], bb_max[i]);
 }
 """
 
@@ -47,3 +50,42 @@ def test_counted_vectors_are_admitted(lib, offset, scale):
     t = np.empty(n, f)
     lib.thresholds(_ptr(lim), _ptr(qq), _ptr(t), C.c_long(n))
     assert ((2.0 * x.astype(np.float64) + t).astype(f) > bb).all()
+
+
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")
+@pytest.mark.parametrize("d", [4, 128, 1536])
+@pytest.mark.parametrize("offset", [0.0, 3.0, 1000.0])
+@pytest.mark.parametrize("scale", [3e-23, 1e-19, 1.0, 1e15])
+def test_bound_covers_both_forms(lib, d, offset, scale):
+    """|norm form - form of the result| <= knn_eps, for a longest vector of known and of unknown length.  Where
+    norms overflow the bound is not finite, and nothing is proven."""
+    rng = np.random.default_rng(8)
+    n, f = 2_000, np.float32
+    q = ((rng.standard_normal((n, d)) + offset) * scale).astype(f)
+    b = (q + rng.standard_normal((n, d)) * scale * 10.0 ** rng.uniform(-3, 1, (n, 1))).astype(f)
+    qq, bb, x, e = (np.zeros(n, f) for _ in range(4))
+    for j in range(d):
+        qq = (qq + q[:, j].astype(np.float64) * q[:, j]).astype(f)
+        bb = (bb + b[:, j].astype(np.float64) * b[:, j]).astype(f)
+        x = (x + q[:, j].astype(np.float64) * b[:, j]).astype(f)
+        t = (q[:, j] - b[:, j]).astype(np.float64)
+        e = (e + t * t).astype(f)
+    apart = np.abs((qq + bb - f(2) * x).astype(np.float64) - e)
+    for longest in (np.inf, max(1e38, bb.max()), bb.max()):
+        eps = np.empty(n, f)
+        lib.bounds(C.c_int(d), _ptr(qq), _ptr(e), _ptr(np.full(n, longest, f)), _ptr(eps), C.c_long(n))
+        assert (~(eps < np.inf) | (apart <= eps)).all()
+
+
+def test_one_long_vector_does_not_widen_the_bound(lib):
+    qq, e = np.array([1.0], np.float32), np.array([0.5], np.float32)
+    out = []
+    for longest in (2.0, 1e6, 3e38, np.inf):
+        eps = np.empty(1, np.float32)
+        lib.bounds(C.c_int(960), _ptr(qq), _ptr(e), _ptr(np.array([longest], np.float32)), _ptr(eps), C.c_long(1))
+        out.append(eps[0])
+    assert out[0] < out[1] == out[2] == out[3] < 1.5 * out[0]
+    for bad in (np.nan, np.inf):  # a query that cannot be proven
+        eps = np.empty(1, np.float32)
+        lib.bounds(C.c_int(960), _ptr(np.array([bad], np.float32)), _ptr(e), _ptr(np.array([2.0], np.float32)), _ptr(eps), C.c_long(1))
+        assert not eps[0] < np.inf
