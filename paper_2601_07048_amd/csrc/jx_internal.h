@@ -195,24 +195,6 @@ struct BfArgs {
 hipError_t launch_bruteforce(const BfArgs& a, hipStream_t st);
 
 // the same on the matrix cores (knn_tile.hip)
-#define KNN_SLACK 28  // float types: candidates kept beyond k
-#define KNN_BLOCKS 512
-struct KnnArgs {
-    const void* base;
-    const void* queries;
-    long long n, nq;
-    int d, nch;         // dimensions, 16-byte chunks per vector
-    int k, kp;          // neighbours asked for, kept per list
-    int nsplit;
-    uint64_t* lists;    // [nq][nsplit][kp] keys (distance, id)
-    uint32_t* published;  // [nq][nsplit] r_th-th distance of each slice, or NULL
-    int r_th;           // ceil(kp / nsplit)
-    int seed_steps;     // > 0: the slices' first thresholds come from their first seed_steps steps
-    uint32_t* redo;     // [nq] float types: 1 = the merge could not prove the result
-    uint32_t* bmax;     // [nsplit] float types: largest |b|^2 of the slice
-    uint32_t* out_ids;
-    float* out_dist;
-};
 hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_bytes, hipStream_t st, bool* done);
 
 // ---- small utilities ----------------------------------------------------------

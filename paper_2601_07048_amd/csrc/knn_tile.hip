@@ -15,8 +15,8 @@
 //                    than asked for.  The merge kernel evaluates them with the arithmetic of bruteforce_tile_kernel,
 //                    operation by operation, orders them, and proves that nothing left out can be among the first
 //                    k: the first distance left out, less the error bound of both forms, has to exceed the k-th one.
-//                    Queries for which it does not (ties, infinities, NaN) are flagged, and their tiles are done again
-//                    by bruteforce_tile_kernel.  So the result is that kernel's, bit for bit.
+//                    Queries for which it does not (ties, sets far from the origin) are flagged, and their tiles are done
+//                    again by bruteforce_tile_kernel.  So the result is that kernel's, bit for bit.
 //
 // Bound: matrix cores for float32 (1.8 of 2.5 ms below, 107 TFLOP/s), vector instructions and barriers for uint8 (2.9 of
 // 4.4 ms without a single candidate).  Against bruteforce_tile_kernel: 10,000 x 1M uint8 d = 128, k = 10 27.0 -> 4.4 ms;
@@ -40,6 +40,35 @@ typedef _Float16 kf16x8 __attribute__((ext_vector_type(8)));
 // uint8: above every distance (16,384 x 255^2 is just under 2^30), and no sum overflows: 2 <q, b> of the shifted values is at most
 // 2^29, |q|^2 at most 2^28, so 2 <q, b> + KINF - |q|^2 stays below 2^31 and 2 <q, b> - |b|^2 above -2^30
 #define KINF 0x50000000
+
+#define KNN_SLACK 28  // float types: candidates kept beyond k
+#define KNN_BLOCKS 512
+#define KNN_ODD 30  // rows that are listed for the merge of a query tile, see KnnOdd
+
+// Rows of the base set that no threshold can judge: float32 with a NaN, binary16 with a NaN or an infinity.  They are kept
+// out of the lists, and the merge evaluates them for every query; more than KNN_ODD of them leave its results unproven.
+struct KnnOdd {
+    uint32_t count;
+    uint32_t bb_max;  // largest |b|^2 of the other rows (float bits)
+    uint32_t id[KNN_ODD];
+};
+
+struct KnnArgs {
+    const void* base;
+    const void* queries;
+    long long n, nq;
+    int d, nch;         // dimensions, 16-byte chunks per vector
+    int k, kp;          // neighbours asked for, kept per list
+    int nsplit;
+    uint64_t* lists;    // [nq][nsplit][kp] keys (distance, id)
+    uint32_t* published;  // [nq][nsplit] r_th-th distance of each slice, or NULL
+    int r_th;           // ceil(kp / nsplit)
+    int seed_steps;     // > 0: the slices' first thresholds come from their first seed_steps steps
+    uint32_t* redo;     // [nq] float types: 1 = the merge could not prove the result
+    KnnOdd* odd;        // [tiles of KT queries] float types
+    uint32_t* out_ids;
+    float* out_dist;
+};
 
 template <int DT> struct KAcc { typedef kf32x16 type; typedef float elem; };
 template <> struct KAcc<JX_U8> { typedef ki32x16 type; typedef int elem; };
@@ -241,6 +270,7 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
         S.lim[i] = lim;
     }
     if (tid == 0) S.again = 0;
+    if (SEED && DT != JX_U8 && split == 0 && tid < 2) (&a.odd[blockIdx.x].count)[tid] = 0u;  // count and bb_max
     __syncthreads();
     elem_t best[SEED ? 64 : 1];  // largest 2 <q, b> - |b|^2 of each element
     if constexpr (SEED) {
@@ -294,8 +324,13 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                     const int row = srow + 32 * t;
                     const elem_t x = group_sum<8>(nb[t]);
                     const bool in = b0 + row < b_end;
-                    if (sch == 0) S.bn[row] = in ? knn_bits<DT>(x) : (DT == JX_U8 ? 0x7FFFFFFFu : 0x7F800000u);
-                    if (in && knn_bits<DT>(x) > bmax) bmax = knn_bits<DT>(x);
+                    const bool odd = DT != JX_U8 && in && knn_bits<DT>(x) >= (DT == JX_F16 ? 0x7F800000u : 0x7F800001u);
+                    if (sch == 0) S.bn[row] = odd ? 0x7FC00000u : (in ? knn_bits<DT>(x) : (DT == JX_U8 ? 0x7FFFFFFFu : 0x7F800000u));
+                    if (in && !odd && knn_bits<DT>(x) > bmax) bmax = knn_bits<DT>(x);
+                    if (!SEED && odd && sch == 0) {
+                        const uint32_t at = atomicAdd(&a.odd[blockIdx.x].count, 1u);
+                        if (at < KNN_ODD) a.odd[blockIdx.x].id[at] = (uint32_t)(b0 + row);
+                    }
                     if (first) {
                         const elem_t y = group_sum<8>(nq[t]);
                         if (sch == 0) {
@@ -484,20 +519,20 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
         if (S.cnt[q]) knn_flush<DT, NL>(S, q, list, a.kp, nullptr, 0, 0, a.kp, lane);
         for (int e = (int)S.fill[q] + lane; e < a.kp; e += 64) list[e] = JX_EMPTY_KEY;
     }
-    if (DT != JX_U8 && blockIdx.x == 0) {  // largest |b|^2 of the slice (NaN and infinity come out on top)
+    if (DT != JX_U8) {
         __syncthreads();
         if (tid == 0) S.again = 0;
         __syncthreads();
         atomicMax(&S.again, bmax);
         __syncthreads();
-        if (tid == 0) a.bmax[split] = S.again;
+        if (tid == 0) atomicMax(&a.odd[blockIdx.x].bb_max, S.again);
     }
 }
 
 // One wavefront per query: the kp smallest keys of its lists, then (float types) the exact distances.
 template <int DT, int NL>
 __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
-    __shared__ uint64_t ex[192];
+    __shared__ uint64_t ex[(NL + 1) * 64];
     const long long qi = blockIdx.x;
     const int lane = threadIdx.x;
     const int kp = a.kp;
@@ -548,18 +583,20 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
     const uint4* q4 = reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(a.queries) + (size_t)qi * (size_t)(a.nch * 16));
     float qq = 0.f;  // |q|^2: binary16 in that kernel's order, float32 only for the bound
     for (int ch = 0; ch < a.nch; ch++) qq = knn_sq<DT>(q4[ch], qq);
+    const KnnOdd& odd = a.odd[qi / KT];
+    const int n_odd = odd.count < KNN_ODD ? (int)odd.count : KNN_ODD;
     int n_valid = 0;
-    for (int r = 0; r < NL; r++) {
-        uint64_t cur = JX_EMPTY_KEY;
+#pragma unroll
+    for (int r = 0; r <= NL; r++) ex[r * 64 + lane] = JX_EMPTY_KEY;
+    wave_sync();
+    for (int r = 0; r <= NL; r++) {  // the list's candidates, then the rows that are in no list
+        uint64_t cur = r == NL && lane < n_odd ? (uint64_t)odd.id[lane < KNN_ODD ? lane : 0] : JX_EMPTY_KEY;
 #pragma unroll
         for (int x = 0; x < NL; x++)
             if (x == r) cur = top[x];
         const bool valid = cur != JX_EMPTY_KEY;
-        n_valid += __builtin_popcountll(ballot(valid));
-        if (ballot(valid) == 0ull) {
-            ex[r * 64 + lane] = JX_EMPTY_KEY;
-            continue;
-        }
+        const uint64_t vm = ballot(valid);
+        if (vm == 0ull) continue;
         const uint32_t id = valid ? (uint32_t)cur : 0u;
         const uint4* b4 = reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(a.base) + (size_t)id * (size_t)(a.nch * 16));
         float acc = 0.f, bb = 0.f;
@@ -585,11 +622,12 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
             }
         }
         const float dist = DT == JX_F16 ? fmaxf(qq + bb - 2.f * acc, 0.f) : acc;
-        ex[r * 64 + lane] = valid ? (((uint64_t)f32_to_ordered(dist) << 32) | id) : JX_EMPTY_KEY;
+        if (valid) ex[n_valid + lane] = ((uint64_t)f32_to_ordered(dist) << 32) | id;
+        n_valid += __builtin_popcountll(vm);
     }
     wave_sync();
     float kth = -1.f;
-    for (int r = 0; r < NL; r++) {
+    for (int r = 0; r <= NL; r++) {
         const uint64_t mine = ex[r * 64 + lane];
         int rank = 0;
         for (int t = 0; t < n_valid; t++) rank += ex[t] < mine ? 1 : 0;
@@ -605,20 +643,12 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
         a.out_dist[qi * a.k + p] = __builtin_inff();
     }
     // ---- proof: what was left out is no nearer than the last entry kept, less what the forms can differ by (knn_eps), and
-    // that has to exceed the k-th distance.  A float32 vector with an infinity is infinitely far away; a binary16 one and any
-    // with a NaN leave every result unproven, as do comparisons with NaN
-    uint32_t bm = 0;
-    for (int s = lane; s < a.nsplit; s += 64) bm = a.bmax[s] > bm ? a.bmax[s] : bm;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const uint32_t o = shfl_xor(bm, m);
-        bm = o > bm ? o : bm;
-    }
+    // that has to exceed the k-th distance.  Comparisons with NaN leave the result unproven
     const uint64_t who = ballot(kth >= 0.f);
     bool proven = n_valid == a.n;
-    if (!proven && n_valid == kp && who && bm < (DT == JX_F16 ? 0x7F800000u : 0x7F800001u)) {
+    if (!proven && n_valid == kp + n_odd && odd.count <= KNN_ODD && who) {
         const float e_k = __uint_as_float(readlane32(__float_as_uint(kth), __builtin_ctzll(who)));
-        proven = __uint_as_float((uint32_t)(worst >> 32)) - knn_eps(a.d, qq, e_k, __uint_as_float(bm)) > e_k;
+        proven = __uint_as_float((uint32_t)(worst >> 32)) - knn_eps(a.d, qq, e_k, __uint_as_float(odd.bb_max)) > e_k;
     }
     if (lane == 0) a.redo[qi] = proven ? 0u : 1u;
 }
@@ -663,7 +693,8 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     long long nsplit = KNN_BLOCKS / qt > 1 ? KNN_BLOCKS / qt : 1;
     if (nsplit > 512) nsplit = 512;
     if (nsplit > steps / 2) nsplit = steps / 2;  // two steps at least
-    const long long aux = ((b.nq * 4 + 255) & ~255LL) + 4096 + 256;
+    const long long redo_bytes = (b.nq * 4 + 255) & ~255LL;
+    const long long aux = redo_bytes + ((qt * (long long)sizeof(KnnOdd) + 255) & ~255LL) + 256;
     const long long fit = (scratch_bytes - aux) / (b.nq * (a.kp * 8 + 4));
     if (nsplit > fit) nsplit = fit;
     // Where the tiled kernel stays, tiled / this in us: few vectors (1,000 x 2,000 float32 d = 96, k = 10 181 / 210, 300 x
@@ -680,13 +711,15 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     a.lists = (uint64_t*)scratch;
     a.published = nsplit > 1 ? (uint32_t*)(a.lists + (size_t)b.nq * nsplit * a.kp) : nullptr;
     a.redo = (uint32_t*)p;
-    a.bmax = (uint32_t*)(p + ((b.nq * 4 + 255) & ~255LL));
+    a.odd = (KnnOdd*)(p + redo_bytes);
     hipError_t e = hipSuccess;
     // a first threshold from a sixteenth of every slice, one step at least: without it the first step of every slice is
     // merged whole, 200 us and more
     const long long each = steps / nsplit;
     a.seed_steps = a.published && a.r_th <= 32 ? (int)((each + 15) / 16) : 0;
     if (a.published && !a.seed_steps) e = launch_fill_u32(a.published, b.nq * nsplit, 0x7F800000u, st);
+    if (e != hipSuccess) return e;
+    if (!exact && !a.seed_steps) e = launch_fill_u32((uint32_t*)a.odd, qt * (long long)(sizeof(KnnOdd) / 4), 0u, st);
     if (e != hipSuccess) return e;
     *done = true;
     if (exact) return launch_knn_lists<JX_U8>(a, st);

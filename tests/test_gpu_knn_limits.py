@@ -1,5 +1,5 @@
 """The exhaustive search on the matrix cores at the ends of what it takes: rows so long that uint8 distances leave its
-integer range, floats so small that squares are subnormal.  Every result is compared with the tiled kernel's, which rows on 4-byte boundaries take."""
+integer range, floats so small that squares are subnormal, rows that no threshold can judge.  Every result is compared with the tiled kernel's, which rows on 4-byte boundaries take."""
 import pytest
 import torch
 
@@ -37,3 +37,23 @@ def test_tiny_floats(jx, scale):
     for _ in range(4):
         b, q = (torch.randn((n, 32), device="cuda", generator=g) * scale for n in (20_000, 400))
         check(jx, b, q, 10)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("rows", [1, 30, 31, 2_000])
+def test_rows_with_nan_and_infinities(jx, dtype, rows):
+    """Up to 30 rows that no threshold can judge are evaluated for every query; beyond that the tiled kernel runs."""
+    g = torch.Generator(device="cuda").manual_seed(2)
+    b, q = (torch.randn((n, 64), device="cuda", generator=g).to(dtype) for n in (20_000, 250))
+    at = torch.randperm(20_000, device="cuda", generator=g)[:rows]
+    for value in (float("nan"), -float("nan"), float("inf"), -float("inf")):
+        x = b.clone()
+        x[at, 5] = value
+        for k in (1, 30, 50, 128):
+            check(jx, x, q, k)
+    x = b.clone()
+    x[at[::2], 5], x[at[1::2], 6] = float("nan"), float("inf")
+    y = q.clone()
+    y[::50, 7] = float("nan")
+    y[1::50, 7] = float("inf")
+    check(jx, x, y, 10)
