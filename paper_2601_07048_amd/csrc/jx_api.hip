@@ -585,6 +585,7 @@ int jx_bruteforce(jx_index* idx, const void* d_queries, int64_t nq, int32_t k, u
         a.n = idx->n;
         a.nq = m;
         a.k = k;
+        a.nsplit = (int)bruteforce_nsplit(idx->n, m);
         a.out_ids = d_out_ids + (size_t)q0 * k;
         a.out_dist = d_out_dist + (size_t)q0 * k;
         bool done = false;

@@ -53,6 +53,9 @@ struct KnnOdd {
     uint32_t id[KNN_ODD];
 };
 
+template <int DT>
+constexpr uint32_t KNN_JUDGED = DT == JX_F16 ? 0x7F800000u : 0x7F800001u;  // bits of |b|^2 from which a row is one of those
+
 struct KnnArgs {
     const void* base;
     const void* queries;
@@ -66,6 +69,7 @@ struct KnnArgs {
     int seed_steps;     // > 0: the slices' first thresholds come from their first seed_steps steps
     uint32_t* redo;     // [nq] float types: 1 = the merge could not prove the result
     KnnOdd* odd;        // [tiles of KT queries] float types
+    uint4* hopeless;    // [tiles][nsplit] float types: a bit per query that can hardly be proven, as far as the slice can tell
     uint32_t* out_ids;
     float* out_dist;
 };
@@ -232,10 +236,39 @@ __device__ __forceinline__ E knn_wave_max(E v) {
     return top(top(val(readlane32(bits(v), 0)), val(readlane32(bits(v), 16))), top(val(readlane32(bits(v), 32)), val(readlane32(bits(v), 48))));
 }
 
+// Whether the tiled kernel takes its tiles of 64 queries, first (.x) and second (.y) of this tile, whatever is found here:
+// one query is hopeless on the word of all slices.  By a whole wavefront
+__device__ __forceinline__ uint2 knn_hopeless(const KnnArgs& a, const long long tile, const int lane) {
+    uint32_t w[4] = {~0u, ~0u, ~0u, ~0u};
+    for (int s = lane; s < a.nsplit; s += 64) {
+        const uint4 v = a.hopeless[tile * a.nsplit + s];
+        w[0] &= v.x;
+        w[1] &= v.y;
+        w[2] &= v.z;
+        w[3] &= v.w;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        w[i] &= dpp_u32<0xB1>(w[i]);
+        w[i] &= dpp_u32<0x4E>(w[i]);
+        w[i] &= dpp_u32<0x141>(w[i]);
+        w[i] &= dpp_u32<0x140>(w[i]);
+        w[i] = readlane32(w[i], 0) & readlane32(w[i], 16) & readlane32(w[i], 32) & readlane32(w[i], 48);
+    }
+    return make_uint2(w[0] | w[1], w[2] | w[3]);
+}
+
 // ONE: vectors of one slab; the queries stay in LDS.
 // SEED: only the slice's first a.seed_steps steps, to publish a first r_th distance before the search begins: the
 // smallest distance of each of the 128 columns over the steps, then the r_th smallest of these.  It is no smaller than
-// the r_th of all that was seen.
+// the r_th of all that was seen.  Float types: a query whose distances can be off by more than a share of that first
+// distance (a set far from the origin, squares that are subnormal) will hardly be proven: the KNN_SLACK candidates behind the
+// k-th would have to reach as far beyond it.  Where each half of a tile holds such a query the tiled kernel runs for all of
+// it anyway, and this one stops here.  The share is a quarter of the slack's part of the list, 0.24 at k = 1, 0.18 at 10 and
+// 0.05 at 100; a set of 16 intrinsic dimensions has 0.34, 0.15 and 0.03 between the k-th and the last.
+// 1,000 from the origin, k = 10, with the stop / without / the tiled kernel alone: 256 x 100,003 float32 d = 960 4,330 / 5,190
+// / 4,216 us, 1,000 x 200,000 float32 d = 128 1,893 / 3,270 / 1,822, 256 x 100,000 binary16 d = 960 1,891 / 2,298 / 1,817.
+// What only the finished lists show is paid twice: 29 or more copies of every vector 5,103 / 4,216 and 2,971 / 1,860
 template <int DT, int NL, bool ONE, bool SEED>
 __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
     typedef typename KAcc<DT>::type acc_t;
@@ -268,6 +301,12 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
             if (most + 1u < lim) lim = most + 1u;
         }
         S.lim[i] = lim;
+    }
+    if constexpr (DT != JX_U8 && !SEED) {
+        if (a.seed_steps) {
+            const uint2 w = knn_hopeless(a, blockIdx.x, lane);
+            if (w.x && (w.y || q0 + 64 >= a.nq)) return;  // the whole workgroup
+        }
     }
     if (tid == 0) S.again = 0;
     if (SEED && DT != JX_U8 && split == 0 && tid < 2) (&a.odd[blockIdx.x].count)[tid] = 0u;  // count and bb_max
@@ -319,18 +358,15 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                 nb[t] = knn_sq<DT>(v, nb[t]);
             }
             if (slab == nslab - 1) {  // norms: the 8 threads of a row
+                uint32_t norm[4];
 #pragma unroll
                 for (int t = 0; t < 4; t++) {
                     const int row = srow + 32 * t;
                     const elem_t x = group_sum<8>(nb[t]);
                     const bool in = b0 + row < b_end;
-                    const bool odd = DT != JX_U8 && in && knn_bits<DT>(x) >= (DT == JX_F16 ? 0x7F800000u : 0x7F800001u);
-                    if (sch == 0) S.bn[row] = odd ? 0x7FC00000u : (in ? knn_bits<DT>(x) : (DT == JX_U8 ? 0x7FFFFFFFu : 0x7F800000u));
-                    if (in && !odd && knn_bits<DT>(x) > bmax) bmax = knn_bits<DT>(x);
-                    if (!SEED && odd && sch == 0) {
-                        const uint32_t at = atomicAdd(&a.odd[blockIdx.x].count, 1u);
-                        if (at < KNN_ODD) a.odd[blockIdx.x].id[at] = (uint32_t)(b0 + row);
-                    }
+                    norm[t] = in ? knn_bits<DT>(x) : 0u;
+                    // binary16: what is listed as odd takes no other way into the result
+                    if (sch == 0) S.bn[row] = DT == JX_F16 && norm[t] == 0x7F800000u ? 0x7FC00000u : (in ? norm[t] : (DT == JX_U8 ? 0x7FFFFFFFu : 0x7F800000u));
                     if (first) {
                         const elem_t y = group_sum<8>(nq[t]);
                         if (sch == 0) {
@@ -342,6 +378,22 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                                 S.t[row] = q0 + row < a.nq ? __float_as_uint(knn_threshold(__uint_as_float(S.lim[row]), (float)y)) : 0xFF800000u;
                             else
                                 S.t[row] = q0 + row < a.nq ? 0x7F800000u : 0xFF800000u;
+                        }
+                    }
+                }
+                if constexpr (DT != JX_U8 && !SEED) {
+                    const uint32_t lo = max(norm[0], norm[1]), hi = max(norm[2], norm[3]), most = max(lo, hi);
+                    if (most < KNN_JUDGED<DT>) {
+                        bmax = max(bmax, most);
+                    } else if (sch == 0) {
+#pragma unroll
+                        for (int t = 0; t < 4; t++) {
+                            if (norm[t] < KNN_JUDGED<DT>) {
+                                bmax = max(bmax, norm[t]);
+                            } else {
+                                const uint32_t to = atomicAdd(&a.odd[blockIdx.x].count, 1u);
+                                if (to < KNN_ODD) a.odd[blockIdx.x].id[to] = (uint32_t)(b0 + srow + 32 * t);
+                            }
                         }
                     }
                 }
@@ -504,9 +556,20 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                     const float d = fmaxf(qn - m, 0.f);
                     if (d < __builtin_inff() && m > -__builtin_inff()) code = __float_as_uint(d);
                 }
-                if (lane == 0) a.published[(size_t)qi * a.nsplit + split] = code;
+                if (lane == 0) {
+                    a.published[(size_t)qi * a.nsplit + split] = code;
+                    S.lim[h * 64 + r] = code;
+                }
             }
             __syncthreads();
+        }
+        if constexpr (DT != JX_U8) {
+            if (tid < KT) {
+                const float first = __uint_as_float(S.lim[tid]);
+                const bool hope = first < __builtin_inff() && knn_eps(a.d, __uint_as_float(S.qn[tid]), first, __builtin_inff()) * (float)a.kp <= first * (float)(KNN_SLACK / 4);
+                const uint64_t bits = ballot(q0 + tid < a.nq && !hope);
+                if (lane == 0) reinterpret_cast<uint64_t*>(a.hopeless + (size_t)blockIdx.x * a.nsplit + split)[wave] = bits;
+            }
         }
         return;
     }
@@ -536,6 +599,15 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
     const long long qi = blockIdx.x;
     const int lane = threadIdx.x;
     const int kp = a.kp;
+    if constexpr (DT != JX_U8) {
+        if (a.seed_steps) {
+            const uint2 w = knn_hopeless(a, qi / KT, lane);
+            if (qi % KT < 64 ? w.x : w.y) {  // there may be no lists
+                if (lane == 0) a.redo[qi] = 1u;
+                return;
+            }
+        }
+    }
     uint64_t top[NL];
 #pragma unroll
     for (int r = 0; r < NL; r++) top[r] = JX_EMPTY_KEY;
@@ -670,7 +742,8 @@ static hipError_t launch_knn_lists(const KnnArgs& a, hipStream_t st) {
     return a.kp <= 64 ? launch_knn<DT, 1>(a, st) : launch_knn<DT, 3>(a, st);
 }
 
-// Takes the search over where it is the faster one and its lists fit scratch_bytes; *done says so.
+// Takes the search over where it is the faster one and its lists fit scratch_bytes; *done says so.  b.nsplit: the split the
+// tiled kernel would run with.
 hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_bytes, hipStream_t st, bool* done) {
     *done = false;
     const bool exact = b.dtype == JX_U8;
@@ -694,7 +767,8 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     if (nsplit > 512) nsplit = 512;
     if (nsplit > steps / 2) nsplit = steps / 2;  // two steps at least
     const long long redo_bytes = (b.nq * 4 + 255) & ~255LL;
-    const long long aux = redo_bytes + ((qt * (long long)sizeof(KnnOdd) + 255) & ~255LL) + 256;
+    const long long odd_bytes = (qt * (long long)sizeof(KnnOdd) + 255) & ~255LL;
+    const long long aux = redo_bytes + odd_bytes + (qt > KNN_BLOCKS ? qt : KNN_BLOCKS) * 16 + 256;
     const long long fit = (scratch_bytes - aux) / (b.nq * (a.kp * 8 + 4));
     if (nsplit > fit) nsplit = fit;
     // Where the tiled kernel stays, tiled / this in us: few vectors (1,000 x 2,000 float32 d = 96, k = 10 181 / 210, 300 x
@@ -712,6 +786,7 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     a.published = nsplit > 1 ? (uint32_t*)(a.lists + (size_t)b.nq * nsplit * a.kp) : nullptr;
     a.redo = (uint32_t*)p;
     a.odd = (KnnOdd*)(p + redo_bytes);
+    a.hopeless = (uint4*)(p + redo_bytes + odd_bytes);  // qt * nsplit <= max(qt, KNN_BLOCKS)
     hipError_t e = hipSuccess;
     // a first threshold from a sixteenth of every slice, one step at least: without it the first step of every slice is
     // merged whole, 200 us and more
@@ -725,8 +800,9 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     if (exact) return launch_knn_lists<JX_U8>(a, st);
     e = b.dtype == JX_F16 ? launch_knn_lists<JX_F16>(a, st) : launch_knn_lists<JX_F32>(a, st);
     if (e != hipSuccess) return e;
-    BfArgs again = b;  // tiles with a flagged query, over the lists (at least as long)
-    again.nsplit = a.nsplit < 64 ? a.nsplit : 64;
+    BfArgs again = b;  // tiles with a flagged query, over the lists and the published distances; the caller's split where it fits
+    const long long room = (scratch_bytes - aux) / (b.nq * b.k * 8);
+    if (again.nsplit > room) again.nsplit = (int)room;
     again.partial = (uint64_t*)scratch;
     again.redo = a.redo;
     return launch_bruteforce(again, st);

@@ -1,5 +1,6 @@
 """The exhaustive search on the matrix cores at the ends of what it takes: rows so long that uint8 distances leave its
-integer range, floats so small that squares are subnormal, rows that no threshold can judge.  Every result is compared with the tiled kernel's, which rows on 4-byte boundaries take."""
+integer range, floats so small that squares are subnormal, rows that no threshold can judge, sets far from the
+origin.  Every result is compared with the tiled kernel's, which rows on 4-byte boundaries take."""
 import pytest
 import torch
 
@@ -57,3 +58,21 @@ def test_rows_with_nan_and_infinities(jx, dtype, rows):
     y[::50, 7] = float("nan")
     y[1::50, 7] = float("inf")
     check(jx, x, y, 10)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("far", ["all", "every other query", "one tile of queries", "the base set's end"])
+def test_sets_far_from_the_origin(jx, dtype, far):
+    """Distances small against the norms cannot be proven.  Tiles of such queries alone leave early; others hold some."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    b, q = (torch.randn((n, 64), device="cuda", generator=g) for n in (20_000, 400))
+    if far == "all":
+        b, q = b + 500, q + 500
+    else:
+        b[10_000:] += 500
+    if far == "every other query":
+        q[::2] += 500
+    if far == "one tile of queries":
+        q[128:256] += 500
+    for k in (1, 10, 60):
+        check(jx, b.to(dtype), q.to(dtype), k)
