@@ -236,6 +236,13 @@ int jx_beam_frontier(jx_index* idx, const void* d_queries, int64_t nq, int32_t L
 int jx_bruteforce(jx_index* idx, const void* d_queries, int64_t nq, int32_t k, uint32_t* d_out_ids,
                   float* d_out_dist, void* stream);
 
+/* The kernel that the calling thread's last jx_bruteforce or
+ * jx_bruteforce_static launched for its (last slice of) queries and how it
+ * split the work: "knn_tile_kernel<DT,NL,ONE> nsplit=.. r_th=.. seed_steps=.."
+ * or "bruteforce_tile_kernel<DT> nsplit=..", DT = JX_U8 | JX_F32 | JX_F16; ""
+ * before the first.  The same kind of record as jx_stats.beam_kernel. */
+const char* jx_bruteforce_kernel(void);
+
 /*
  * jx_bruteforce for callers that cannot allocate device memory and have no
  * arena either: code under HIP graph capture, tight serving loops, harnesses

@@ -19,6 +19,7 @@ static __device__ __align__(256) unsigned char scratch[JX_STATIC_SCRATCH_BYTES];
 namespace {
 
 thread_local char g_err[512] = "";
+thread_local char g_bf_kernel[96] = "";  // see jx_bruteforce_kernel
 
 int fail(int code, const char* fmt, ...) {
     va_list ap;
@@ -194,6 +195,11 @@ int gram_mode(const jx_index* idx) {
 // next prune of the row skip the pairs among them
 bool incremental_prune(const jx_index* idx) { return !(idx->flags & JX_FLAG_NO_INCR_PRUNE); }
 
+hipError_t launch_tiled(const jx::BfArgs& a, hipStream_t st) {
+    snprintf(g_bf_kernel, sizeof g_bf_kernel, "bruteforce_tile_kernel<%d> nsplit=%d", a.dtype, a.nsplit);
+    return jx::launch_bruteforce(a, st);
+}
+
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 // split of the base set used by the brute-force kernels: at least ~2048 workgroups, at most 64 partial lists per query
@@ -278,6 +284,7 @@ const char* jx_strerror(int code) {
 }
 
 const char* jx_last_error(void) { return g_err; }
+const char* jx_bruteforce_kernel(void) { return g_bf_kernel; }
 
 int64_t jx_arena_bytes(const jx_params* p) {
     int rc = check_params(p);
@@ -590,7 +597,7 @@ int jx_bruteforce(jx_index* idx, const void* d_queries, int64_t nq, int32_t k, u
         a.out_ids = d_out_ids + (size_t)q0 * k;
         a.out_dist = d_out_dist + (size_t)q0 * k;
         bool done = false;
-        if (!nsplit) JX_HIP(jx::launch_knn_tile(a, idx->d_work, idx->work_bytes, st, &done));
+        if (!nsplit) JX_HIP(jx::launch_knn_tile(a, idx->d_work, idx->work_bytes, st, g_bf_kernel, &done));
         if (!done) {
             // split the base set, and slice what is left of the queries so that the per-slice partial lists fit the workspace:
             // in slices of 16,384, split for as many, 150,000 x 5,000 at k = 100 took 72 ms for 19, 1M x 1,000 28 for 8
@@ -602,7 +609,7 @@ int jx_bruteforce(jx_index* idx, const void* d_queries, int64_t nq, int32_t k, u
             a.nq = m;
             a.nsplit = (int)nsplit;
             a.partial = (uint64_t*)idx->d_work;
-            JX_HIP(jx::launch_bruteforce(a, st));
+            JX_HIP(launch_tiled(a, st));
         }
         q0 += m;
     }
@@ -641,8 +648,8 @@ int jx_bruteforce_static(const void* d_base, int64_t n, int32_t dim, int32_t dty
     a.out_ids = d_out_ids;
     a.out_dist = d_out_dist;
     bool done = false;
-    JX_HIP(jx::launch_knn_tile(a, sc, JX_STATIC_SCRATCH_BYTES, as_stream(stream), &done));
-    if (!done) JX_HIP(jx::launch_bruteforce(a, as_stream(stream)));
+    JX_HIP(jx::launch_knn_tile(a, sc, JX_STATIC_SCRATCH_BYTES, as_stream(stream), g_bf_kernel, &done));
+    if (!done) JX_HIP(launch_tiled(a, as_stream(stream)));
     return JX_OK;
 }
 

@@ -194,8 +194,8 @@ struct BfArgs {
 };
 hipError_t launch_bruteforce(const BfArgs& a, hipStream_t st);
 
-// the same on the matrix cores (knn_tile.hip)
-hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_bytes, hipStream_t st, bool* done);
+// the same on the matrix cores (knn_tile.hip); name: receives the kernel and its split where it ran, at most 96 bytes
+hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_bytes, hipStream_t st, char* name, bool* done);
 
 // ---- small utilities ----------------------------------------------------------
 hipError_t launch_fill_u32(uint32_t* p, long long n, uint32_t v, hipStream_t st);

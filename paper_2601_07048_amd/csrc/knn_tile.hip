@@ -22,6 +22,7 @@
 // 4.4 ms without a single candidate).  Against bruteforce_tile_kernel: 10,000 x 1M uint8 d = 128, k = 10 27.0 -> 4.4 ms;
 // 1,000 x 100,003 float32 d = 960, k = 100 12.9 -> 2.7 ms; 1,000 x 100,000 binary16 d = 960, k = 10 3.97 -> 0.84 ms;
 // 2 x 234,001 float32 d = 128, k = 1 1.12 -> 0.17 ms.  Without the seeds the lists fill with what comes first: 5.6 and 5.3 ms.
+#include <stdio.h>
 #include "jx_distance.h"
 #include "knn_bound.h"
 
@@ -439,7 +440,7 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                 for (int j = 0; j < 2; j++)
 #pragma unroll
                     for (int e = 0; e < 16; e++) {
-                        const elem_t v = DT == JX_U8 ? (elem_t)(acc[i][j][e] * 2 - nbv[j]) : (elem_t)(acc[i][j][e] * 2 - nbv[j]);
+                        const elem_t v = acc[i][j][e] * 2 - nbv[j];
                         elem_t& m = best[(i * 2 + j) * 16 + e];
                         m = v > m ? v : m;
                     }
@@ -727,11 +728,14 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
 
 // ------------------------------------------------------------------ launch
 
+static int knn_list_regs(int kp) { return kp <= 64 ? 1 : 3; }  // list entries per lane
+static bool knn_one_slab(int dtype, int nch) { return dtype == JX_U8 && nch <= 8; }
+
 template <int DT, int NL>
 static hipError_t launch_knn(const KnnArgs& a, hipStream_t st) {
     constexpr bool U8 = DT == JX_U8;
     dim3 grid((unsigned)((a.nq + KT - 1) / KT), (unsigned)a.nsplit), block(256);
-    const bool one = U8 && a.nch <= 8;
+    const bool one = knn_one_slab(DT, a.nch);
     if (a.seed_steps) hipLaunchKernelGGL((one ? knn_tile_kernel<DT, 1, U8, true> : knn_tile_kernel<DT, 1, false, true>), grid, block, 0, st, a);
     hipLaunchKernelGGL((one ? knn_tile_kernel<DT, NL, U8, false> : knn_tile_kernel<DT, NL, false, false>), grid, block, 0, st, a);
     hipLaunchKernelGGL((knn_merge_kernel<DT, NL>), dim3((unsigned)a.nq), dim3(64), 0, st, a);
@@ -739,12 +743,12 @@ static hipError_t launch_knn(const KnnArgs& a, hipStream_t st) {
 }
 template <int DT>
 static hipError_t launch_knn_lists(const KnnArgs& a, hipStream_t st) {
-    return a.kp <= 64 ? launch_knn<DT, 1>(a, st) : launch_knn<DT, 3>(a, st);
+    return knn_list_regs(a.kp) == 1 ? launch_knn<DT, 1>(a, st) : launch_knn<DT, 3>(a, st);
 }
 
 // Takes the search over where it is the faster one and its lists fit scratch_bytes; *done says so.  b.nsplit: the split the
 // tiled kernel would run with.
-hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_bytes, hipStream_t st, bool* done) {
+hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_bytes, hipStream_t st, char* name, bool* done) {
     *done = false;
     const bool exact = b.dtype == JX_U8;
     const long long row = (long long)b.d * (exact ? 1 : (b.dtype == JX_F16 ? 2 : 4));
@@ -764,7 +768,6 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     const long long qt = (b.nq + KT - 1) / KT, steps = (b.n + KT - 1) / KT;
     // as many slices as keep every CU at its two workgroups; one workgroup more would be a round of its own
     long long nsplit = KNN_BLOCKS / qt > 1 ? KNN_BLOCKS / qt : 1;
-    if (nsplit > 512) nsplit = 512;
     if (nsplit > steps / 2) nsplit = steps / 2;  // two steps at least
     const long long redo_bytes = (b.nq * 4 + 255) & ~255LL;
     const long long odd_bytes = (qt * (long long)sizeof(KnnOdd) + 255) & ~255LL;
@@ -797,6 +800,7 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     if (!exact && !a.seed_steps) e = launch_fill_u32((uint32_t*)a.odd, qt * (long long)(sizeof(KnnOdd) / 4), 0u, st);
     if (e != hipSuccess) return e;
     *done = true;
+    snprintf(name, 96, "knn_tile_kernel<%d,%d,%d> nsplit=%d r_th=%d seed_steps=%d", b.dtype, knn_list_regs(a.kp), knn_one_slab(b.dtype, a.nch) ? 1 : 0, a.nsplit, a.r_th, a.seed_steps);
     if (exact) return launch_knn_lists<JX_U8>(a, st);
     e = b.dtype == JX_F16 ? launch_knn_lists<JX_F16>(a, st) : launch_knn_lists<JX_F32>(a, st);
     if (e != hipSuccess) return e;

@@ -32,7 +32,7 @@ EXPORTS = [
     "jx_arena_bytes", "jx_create", "jx_destroy", "jx_insert", "jx_quantize", "jx_search", "jx_beam_frontier",
     "jx_bruteforce", "jx_size", "jx_export_graph", "jx_import_graph", "jx_export_codes", "jx_import_codes", "jx_rotate",
     "jx_encode_rotated", "jx_delete", "jx_consolidate", "jx_compact", "jx_deleted_count", "jx_probe_gather", "jx_mips_augment", "jx_strerror", "jx_last_error",
-    "jx_bruteforce_static", "jx_set_flags",
+    "jx_bruteforce_static", "jx_bruteforce_kernel", "jx_set_flags",
 ]
 
 
@@ -69,6 +69,7 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
     lib.jx_arena_bytes.restype = C.c_int64
     lib.jx_strerror.restype = C.c_char_p
     lib.jx_last_error.restype = C.c_char_p
+    lib.jx_bruteforce_kernel.restype = C.c_char_p
     for name in EXPORTS:
         getattr(lib, name)  # fail loudly on a missing symbol
     return lib
@@ -276,6 +277,11 @@ def bruteforce_static(base: torch.Tensor, queries: torch.Tensor, k: int, out=Non
         _check(_lib.jx_bruteforce_static(_ptr(base), C.c_int64(base.shape[0]), C.c_int32(base.shape[1]), C.c_int32(dtype),
                                          _ptr(queries), C.c_int64(nq), C.c_int32(k), _ptr(ids), _ptr(dist), _stream()))
     return ids, dist
+
+
+def bruteforce_kernel() -> str:
+    """jx_bruteforce_kernel: what the calling thread's last exhaustive search launched."""
+    return _lib.jx_bruteforce_kernel().decode()
 
 
 def mips_augment(x: torch.Tensor, max_norm: float = 0.0, is_query: bool = False, dim_out: int = 0, want_norms: bool = False):

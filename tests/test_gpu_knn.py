@@ -26,9 +26,11 @@ def off4(t):
     return out
 
 
-def check(jx, b, q, k):
+def check(jx, b, q, k, kernel="knn_tile_kernel"):
     ids, dist = jx.bruteforce_static(b, q, k)
+    assert jx.bruteforce_kernel().startswith(kernel + "<"), jx.bruteforce_kernel()
     ids0, dist0 = jx.bruteforce_static(off4(b), off4(q), k)
+    assert jx.bruteforce_kernel().startswith("bruteforce_tile_kernel<")
     assert torch.equal(ids, ids0)
     assert torch.equal(dist.view(torch.int32), dist0.view(torch.int32))
     return ids, dist
@@ -83,6 +85,7 @@ def test_index_search_slices_queries(jx):
     g = jx.Index(32, jx.U8, 8, 8, 1.2, capacity=10_000, max_batch=1024)
     g.import_graph(dev(b), torch.full((10_000, 8), -1, dtype=torch.int32, device="cuda"), 0)
     ids, dist = g.bruteforce(dev(q), 64)
+    assert jx.bruteforce_kernel().startswith("knn_tile_kernel<")
     for at in (0, 75_000, 149_872):
         i0, d0 = jx.bruteforce_static(dev(b), dev(q[at:at + 128]), 64)
         assert torch.equal(ids[at:at + 128], i0) and torch.equal(dist[at:at + 128], d0)

@@ -4,7 +4,7 @@ origin.  Every result is compared with the tiled kernel's, which rows on 4-byte 
 import pytest
 import torch
 
-from test_gpu_knn import check
+from test_gpu_knn import check, off4
 
 pytestmark = pytest.mark.gpu
 
@@ -24,10 +24,11 @@ def test_uint8_rows_of_any_length(jx, d):
     q = torch.zeros((4, d), dtype=torch.uint8, device="cuda")
     q[1:] = 255
     q[2, ::2] = 0
-    ids, dist = check(jx, b, q, 10)
+    kernel = "knn_tile_kernel" if d <= 16_384 else "bruteforce_tile_kernel"
+    ids, dist = check(jx, b, q, 10, kernel)
     assert ids[0].tolist() == list(range(10)) and ids[1].tolist() == list(range(9_000, 9_010))
     assert not dist[:2].any()
-    _, dist = check(jx, b[:9_000].repeat(2, 1), q, 10)  # no base vector near; 100 and 9,100 a little nearer
+    _, dist = check(jx, b[:9_000].repeat(2, 1), q, 10, kernel)  # no base vector near; 100 and 9,100 a little nearer
     assert dist[1, 2:].eq(float(d * 255 ** 2)).all()
 
 
@@ -50,7 +51,7 @@ def test_rows_with_nan_and_infinities(jx, dtype, rows):
     for value in (float("nan"), -float("nan"), float("inf"), -float("inf")):
         x = b.clone()
         x[at, 5] = value
-        for k in (1, 30, 50, 128):
+        for k in (8, 30, 50, 128):
             check(jx, x, q, k)
     x = b.clone()
     x[at[::2], 5], x[at[1::2], 6] = float("nan"), float("inf")
@@ -74,5 +75,53 @@ def test_sets_far_from_the_origin(jx, dtype, far):
         q[::2] += 500
     if far == "one tile of queries":
         q[128:256] += 500
-    for k in (1, 10, 60):
+    for k in (8, 10, 60):
         check(jx, b.to(dtype), q.to(dtype), k)
+
+
+def rows(dtype, n, d, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn((n, d), device="cuda", generator=g)
+    return (x * 40 + 128).clamp_(0, 255).to(torch.uint8) if dtype == torch.uint8 else x.to(dtype)
+
+
+@pytest.mark.parametrize("dtype,nq,k", [(torch.uint8, 65_536, 10), (torch.float32, 40_000, 1), (torch.float16, 40_000, 4)])
+def test_one_slice(jx, dtype, nq, k):
+    """So many queries that one workgroup takes the whole base set for its own: no distances are published."""
+    check(jx, rows(dtype, 16_500, 16, 4), rows(dtype, nq, 16, 5), k)
+    jx.bruteforce_static(rows(dtype, 16_500, 16, 4), rows(dtype, nq, 16, 5), k)
+    assert " nsplit=1 " in jx.bruteforce_kernel() and jx.bruteforce_kernel().endswith(" seed_steps=0"), jx.bruteforce_kernel()
+
+
+def index(jx, x, max_batch=1024):
+    kind = {torch.uint8: jx.U8, torch.float32: jx.F32, torch.float16: jx.F16}[x.dtype]
+    g = jx.Index(x.shape[1], kind, 8, 8, 1.2, capacity=x.shape[0], max_batch=max_batch)
+    g.import_graph(x, torch.full((x.shape[0], 8), -1, dtype=torch.int32, device="cuda"), 0)
+    return g
+
+
+def check_samples(jx, x, q, k, ids, dist, at):
+    for i in at:
+        i0, d0 = jx.bruteforce_static(off4(x), off4(q[i:i + 128]), k)
+        assert torch.equal(ids[i:i + 128], i0)
+        assert torch.equal(dist[i:i + 128].view(torch.int32), d0.view(torch.int32))
+
+
+@pytest.mark.parametrize("dtype", [torch.uint8, torch.float32, torch.float16])
+def test_lists_too_long_for_a_first_threshold(jx, dtype):
+    """More than 32 entries of every slice count: thresholds begin at infinity and are published as lists fill."""
+    x, q = rows(dtype, 16_500, 16, 6), rows(dtype, 16_384, 16, 7)
+    if dtype != torch.uint8:
+        x[[3, 11_000], 4] = float("nan")
+    ids, dist = index(jx, x).bruteforce(q, 128)
+    name = jx.bruteforce_kernel()
+    assert name.startswith("knn_tile_kernel<") and " nsplit=1 " not in name and name.endswith(" seed_steps=0"), name
+    check_samples(jx, x, q, 128, ids, dist, (0, 7_000, 16_256))
+
+
+def test_batches_that_the_tiled_kernel_keeps(jx):
+    """Few vectors: one split for all queries, in slices that fit the workspace (83,840 queries of 100 neighbours)."""
+    x, q = rows(torch.uint8, 2_000, 32, 8), rows(torch.uint8, 150_000, 32, 9)
+    ids, dist = index(jx, x).bruteforce(q, 100)
+    assert jx.bruteforce_kernel() == "bruteforce_tile_kernel<0> nsplit=1"
+    check_samples(jx, x, q, 100, ids, dist, (0, 83_776, 83_840, 149_872))
