@@ -65,8 +65,8 @@ def test_small_batches_of_code_searches(jx, d, bits, qbits):
 
 @pytest.mark.parametrize("d", [128, 960])
 def test_expansion_list_builds_equal_the_general_kernel(jx, d):
-    """The candidate search of insertion that returns the expansion list: a graph built from small internal batches (team
-    and wide instances) is the graph of the general kernel."""
+    """The candidate search of insertion that returns the expansion list, one wavefront per point: a graph built from small
+    internal batches (wide instances among them) is the graph of the general kernel."""
     x = random_data(2500, d, np.float32, 11)
     adj = []
     for flags in (0, jx.FLAG_VISITED_IDS):
@@ -74,3 +74,27 @@ def test_expansion_list_builds_equal_the_general_kernel(jx, d):
         g.insert(dev(x))
         adj.append(g.export_graph()[0])
     assert torch.equal(adj[0], adj[1])
+
+
+@pytest.mark.parametrize("d,n,bits", [(200, 40_000, 0), (960, 20_000, 0), (960, 30_000, 4)])
+def test_teams_evaluate_what_the_table_forgot(jx, d, n, bits):
+    """On enough vertices sets of the visited table overflow: neighbours it held when a team read their row ahead and has
+    forgotten by the expansion (d = 200, 64 queries: 265 of them at L = 64, 1,618 at 256) are evaluated there.  The
+    one-wavefront kernel with the same table (a switch that concerns other records leaves the teams out) does the same."""
+    x, q = random_data(n, d, np.float32, 5), random_data(64, d, np.float32, 6)
+    g = jx.Index(d, jx.F32, 64, 64, 1.2, capacity=n, max_batch=n, quant_bits=bits)
+    g.insert(dev(x))
+    kw = {}
+    if bits:
+        rot = np.linalg.qr(np.random.default_rng(9).standard_normal((d, d)))[0].astype(np.float32)
+        g.quantize(bits, dev(rot), query_bits=8, rule=jx.RULE_MAXABS)
+        kw["mode"] = jx.RABITQ
+    for L in (64, 128, 256):
+        got = []
+        for flags, kernel in ((0, "beam_search_ahead_kernel<"), (jx.FLAG_NO_PAIR, "beam_search_kernel<")):
+            g.set_flags(flags)
+            ids, dist, st = g.search(dev(q), 10, L, stats=True, **kw)
+            assert st["beam_kernel"].startswith(kernel), st["beam_kernel"]
+            got.append((ids, dist, st["hops"], st["dist_evals"]))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+        assert got[0][2:] == got[1][2:]
