@@ -6,11 +6,12 @@
 // float32: 8,000 cycles an expansion).  Here wavefront 0 owns frontier, visited table and merge, as in
 // beam_search_kernel.  When the entry it has to expand next has not been fetched, it asks for the S closest unexpanded
 // entries at once; all wavefronts then read those rows, evaluate the neighbours that the visited table does not hold
-// and leave ids and keys in S slots of LDS.  Wavefront 0 goes on expanding from the slots, in the order Alg. 1 prescribes, until the next entry is missing
-// again.  An entry fetched early keeps its slot while it is among the S closest, so nearly all of what is fetched is
-// used.  Distances do not depend on when they are taken, and the filter is applied at the expansion (which evaluates
-// what the table held when the row was read and has forgotten since), so frontier sequence, results and counters are those of beam_search_kernel, float sums to the last bit (the same record-to-lane
-// mapping); what is fetched beyond them costs bandwidth, which such a batch does not use.
+// and leave ids and keys in S slots of LDS.  Wavefront 0 goes on expanding from the slots, in the order Alg. 1
+// prescribes, until the next entry is missing again.  An entry fetched early keeps its slot while it is among the S
+// closest, so nearly all of what is fetched is used.  Distances do not depend on when they are taken, and the filter is
+// applied at the expansion (which evaluates what the table held when the row was read and has forgotten since), so
+// frontier sequence, results and counters are those of beam_search_kernel, float sums to the last bit (the same
+// record-to-lane mapping); what is fetched beyond them costs bandwidth, which such a batch does not use.
 #include <stdio.h>
 #include "beam_kernels.h"
 
@@ -264,10 +265,11 @@ __global__ void __launch_bounds__(NW * 64) beam_search_ahead_kernel(BeamArgs a) 
 
 // Batches whose teams are resident at once, four wavefronts per SIMD.  Against the one-wavefront kernels, L = 16 / 64 /
 // 128, 64 queries: float32 d = 960 355 / 895 / 1463 -> 138 / 292 / 602 us, 200 115 / 227 / 422 -> 71 / 161 / 291;
-// binary16 d = 960 294 / 627 / 1178 -> 108 / 224 / 406; 4-bit codes of d = 960 237 / 377 / 539 -> 220 / 328 / 462; 1-bit
-// codes of d = 1536 326 / 449 / 600 -> 323 / 445 / 566.  Beyond the limit a second round of teams costs more than the
-// team gains (without the filter at the fetch: d = 960 float32, 512 queries, L = 128 1637 -> 1803 us; 4-bit codes, 1,024
-// queries 591 -> 804).
+// binary16 d = 960 294 / 627 / 1178 -> 108 / 224 / 406; 4-bit codes of d = 960 237 / 377 / 539 -> 220 / 328 / 462.  Whole
+// searches on codes of d = 1536, L = 16 / 64 / 128 / 200: 1 bit, B_q = 4 215 / 322 / 512 / 832 -> 211 / 308 / 467 / 692, B_q
+// = 8 266 / 435 / 683 / 1034 -> 239 / 356 / 550 / 818; 2 bits, B_q = 4 302 / 523 / 832 / 1234 -> 231 / 354 / 540 / 790.  Beyond
+// the limit a second round of teams costs more than the team gains (without the filter at the fetch: d = 960 float32, 512
+// queries, L = 128 1637 -> 1803 us; 4-bit codes, 1,024 queries 591 -> 804).
 #define JX_AHEAD_WAVES 4096
 #define JX_AHEAD_QUERIES 512
 

@@ -250,8 +250,28 @@ constexpr bool has_wide() {
 }
 // Beyond 1,536 queries the registers of the wide instances cost more residency than the loads in flight gain.  L = 128,
 // 1,000 queries: d = 128 float32 343 -> 270 us, d = 960 2220 -> 1930, its 4-bit codes 679 -> 599; as insertion search
-// (expansion lists) d = 960, 1,060 points 1233 -> 940 us, 1,325 points 1405 -> 1240, 1,656 points 1785 -> 1815.
+// (expansion lists) d = 960, 1,060 points 1233 -> 940 us.
 static constexpr long long WIDE_MAX_QUERIES = 1536;
+
+// Whether two wavefronts of a wide instance fit a SIMD: at most 256 registers each, as compiled (160 of loads in flight leave
+// room for the fewest frontier registers only)
+template <int KIND, int T, int CPL, int NREG, int QB>
+constexpr bool wide_two_resident() {
+    if (4 * CPL * wide_u<T, CPL>() < 160) return true;
+    return CPL > 1 && NREG <= (QB == 8 ? 1 : 2);
+}
+
+// Largest batch of a wide instance.  One wavefront per SIMD ends at 1,024 queries: the next waits for a whole search (binary16
+// d = 960 and float32 d = 200 at L = 200, 8-bit codes at L = 128 from 1,060 to 1,536 queries 1.3 to 1.5 times as long).
+// Records of 64 lanes x 4 or 6 chunks are bound by bandwidth earlier: float32 d = 960 at L = 64 / 128, gain at 1,152 / 1,280 /
+// 1,536 queries 1.00 / 1.00 / 0.97, d = 1,536 0.94 / 0.91 / 0.92, but at L = 24 1.11 / 1.07 / 1.03 and 1.08 / 1.07 / 1.03;
+// insert calls of 1,280 and 1,536 points, expansion lists of d = 1,536, 7.81 and 8.67 ms with them, 7.58 and 8.56 without
+template <int KIND, int T, int CPL, int NREG, int QB>
+inline long long wide_max_queries(int L) {
+    if (!wide_two_resident<KIND, T, CPL, NREG, QB>()) return 1024;
+    if (CPL >= 4 && T == 64 && L > 32) return CPL == 4 ? 1280 : 1024;
+    return WIDE_MAX_QUERIES;
+}
 
 // One query per wavefront, WPB wavefronts (queries) per workgroup; TILED selects the element-strided loads of the
 // load ablation (jx_distance.h); VIS returns the expansion list instead of the frontier (BeamArgs::vis_cap).

@@ -98,3 +98,18 @@ def test_teams_evaluate_what_the_table_forgot(jx, d, n, bits):
             got.append((ids, dist, st["hops"], st["dist_evals"]))
         assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
         assert got[0][2:] == got[1][2:]
+
+
+@pytest.mark.parametrize("dtype,d,L,most", [("float32", 200, 128, 1536), ("float32", 200, 200, 1024), ("float16", 960, 200, 1024),
+                                            ("float32", 960, 128, 1280), ("float32", 960, 32, 1536), ("float32", 1536, 33, 1024)])
+def test_wide_instances_end_where_they_lose(jx, dtype, d, L, most):
+    """The instance with more records in flight runs up to the batch that its registers and the bandwidth allow, the usual
+    one from there on; both return the same."""
+    x = random_data(2000, d, np.float32, 15).astype(dtype)
+    q = dev(random_data(most + 1, d, np.float32, 16).astype(dtype))
+    g = jx.Index(d, jx_dtype(jx, x), 32, 48, 1.2, capacity=2000, max_batch=2048)
+    g.insert(dev(x))
+    ids, dist, st = g.search(q[:most], 10, L, stats=True)
+    ids1, dist1, st1 = g.search(q, 10, L, stats=True)
+    assert st["beam_kernel"].endswith(",2>") and st1["beam_kernel"].endswith(",1>"), (st["beam_kernel"], st1["beam_kernel"])
+    assert torch.equal(ids, ids1[:most]) and torch.equal(dist, dist1[:most])
