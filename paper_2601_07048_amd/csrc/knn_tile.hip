@@ -600,13 +600,11 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
     const long long qi = blockIdx.x;
     const int lane = threadIdx.x;
     const int kp = a.kp;
+    int nlists = a.nsplit;
     if constexpr (DT != JX_U8) {
         if (a.seed_steps) {
             const uint2 w = knn_hopeless(a, qi / KT, lane);
-            if (qi % KT < 64 ? w.x : w.y) {  // there may be no lists
-                if (lane == 0) a.redo[qi] = 1u;
-                return;
-            }
+            if (qi % KT < 64 ? w.x : w.y) nlists = 0;  // there may be none; the result stays unproven
         }
     }
     uint64_t top[NL];
@@ -614,9 +612,9 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
     for (int r = 0; r < NL; r++) top[r] = JX_EMPTY_KEY;
     uint64_t worst = JX_EMPTY_KEY;  // entry kp - 1
     const uint64_t* src = a.lists + (size_t)qi * a.nsplit * kp;
-    for (int s0 = 0; s0 < a.nsplit; s0 += 64) {  // a list per lane, entry by entry
+    for (int s0 = 0; s0 < nlists; s0 += 64) {  // a list per lane, entry by entry
         for (int c = 0; c < kp; c++) {
-            const uint64_t key = s0 + lane < a.nsplit ? src[(size_t)(s0 + lane) * kp + c] : JX_EMPTY_KEY;
+            const uint64_t key = s0 + lane < nlists ? src[(size_t)(s0 + lane) * kp + c] : JX_EMPTY_KEY;
             uint64_t todo = ballot(key < worst);
             if (todo == 0ull) break;  // the lists are sorted: what follows is no smaller
             while (todo) {
@@ -652,17 +650,17 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
         }
         return;
     }
-    // ---- the distances of bruteforce_tile_kernel: one candidate per lane, the same operations in the same order
+    // ---- the distances of bruteforce_tile_kernel: one candidate per lane, the same operations in the same order.  Nothing is
+    // stored to global memory on any path before: the query's loads would no longer be scalar ones (1,000 queries of d = 960,
+    // 128 candidates 136 -> 187 us)
     const uint4* q4 = reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(a.queries) + (size_t)qi * (size_t)(a.nch * 16));
     float qq = 0.f;  // |q|^2: binary16 in that kernel's order, float32 only for the bound
     for (int ch = 0; ch < a.nch; ch++) qq = knn_sq<DT>(q4[ch], qq);
     const KnnOdd& odd = a.odd[qi / KT];
     const int n_odd = odd.count < KNN_ODD ? (int)odd.count : KNN_ODD;
     int n_valid = 0;
-#pragma unroll
-    for (int r = 0; r <= NL; r++) ex[r * 64 + lane] = JX_EMPTY_KEY;
-    wave_sync();
-    for (int r = 0; r <= NL; r++) {  // the list's candidates, then the rows that are in no list
+    // the list's candidates, then the rows that are in no list
+    for (int r = 0; r <= NL; r++) {
         uint64_t cur = r == NL && lane < n_odd ? (uint64_t)odd.id[lane < KNN_ODD ? lane : 0] : JX_EMPTY_KEY;
 #pragma unroll
         for (int x = 0; x < NL; x++)
@@ -698,9 +696,10 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
         if (valid) ex[n_valid + lane] = ((uint64_t)f32_to_ordered(dist) << 32) | id;
         n_valid += __builtin_popcountll(vm);
     }
+    for (int p = n_valid + lane; p < (NL + 1) * 64; p += 64) ex[p] = JX_EMPTY_KEY;
     wave_sync();
     float kth = -1.f;
-    for (int r = 0; r <= NL; r++) {
+    for (int r = 0; r * 64 < n_valid; r++) {
         const uint64_t mine = ex[r * 64 + lane];
         int rank = 0;
         for (int t = 0; t < n_valid; t++) rank += ex[t] < mine ? 1 : 0;
