@@ -17,7 +17,8 @@ namespace jx {
 #define BF_TB 64
 #define BF_KS 16  // dwords of the vector dimension per slab
 
-template <int DT>
+// REDO: only tiles with a flagged query (BfArgs::redo)
+template <int DT, bool REDO>
 __global__ void __launch_bounds__(256) bruteforce_tile_kernel(BfArgs a) {
     __shared__ uint32_t Qs[BF_KS][BF_TQ + 1];
     __shared__ uint32_t Bs[BF_KS][BF_TB + 1];
@@ -30,7 +31,7 @@ __global__ void __launch_bounds__(256) bruteforce_tile_kernel(BfArgs a) {
     const int tx = tid & 15, ty = tid >> 4;
     const int k = a.k;
     const long long q0 = (long long)blockIdx.x * BF_TQ;
-    if (a.redo) {  // whole workgroups leave, before the first barrier
+    if constexpr (REDO) {  // whole workgroups leave, before the first barrier
         const long long qf = q0 + lane;
         if (ballot(qf < a.nq && a.redo[qf] != 0u) == 0ull) return;
     }
@@ -167,13 +168,13 @@ __global__ void __launch_bounds__(256) bruteforce_tile_kernel(BfArgs a) {
 }
 
 // One wavefront per query: k rounds of "take the smallest remaining key".
-template <int DT>
+template <int DT, bool REDO>
 __global__ void __launch_bounds__(64) bruteforce_merge_kernel(BfArgs a) {
     extern __shared__ __align__(16) unsigned char dyn[];
     uint64_t* keys = reinterpret_cast<uint64_t*>(dyn);
     const long long qi = blockIdx.x;
     const int lane = threadIdx.x;
-    if (a.redo) {
+    if constexpr (REDO) {
         const long long qf = qi / BF_TQ * BF_TQ + lane;
         if (ballot(qf < a.nq && a.redo[qf] != 0u) == 0ull) return;
     }
@@ -209,34 +210,22 @@ __global__ void __launch_bounds__(64) bruteforce_merge_kernel(BfArgs a) {
     }
 }
 
+template <int DT, bool REDO>
+static hipError_t launch_tile_kernels(const BfArgs& a, hipStream_t st) {
+    auto kt = bruteforce_tile_kernel<DT, REDO>;
+    (void)hipFuncSetAttribute((const void*)kt, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+    hipLaunchKernelGGL(kt, dim3((unsigned)((a.nq + BF_TQ - 1) / BF_TQ), (unsigned)a.nsplit), dim3(256), (size_t)BF_TQ * a.k * 8, st, a);
+    auto km = bruteforce_merge_kernel<DT, REDO>;
+    (void)hipFuncSetAttribute((const void*)km, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+    hipLaunchKernelGGL(km, dim3((unsigned)a.nq), dim3(64), (size_t)a.nsplit * a.k * 8, st, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_bruteforce(const BfArgs& a, hipStream_t st) {
     if (a.nq <= 0) return hipSuccess;
-    dim3 grid((unsigned)((a.nq + BF_TQ - 1) / BF_TQ), (unsigned)a.nsplit);
-    size_t sh = (size_t)BF_TQ * a.k * 8;
-    size_t shm = (size_t)a.nsplit * a.k * 8;
-    if (a.dtype == JX_U8) {
-        auto kt = bruteforce_tile_kernel<JX_U8>;
-        (void)hipFuncSetAttribute((const void*)kt, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        hipLaunchKernelGGL(kt, grid, dim3(256), sh, st, a);
-        auto km = bruteforce_merge_kernel<JX_U8>;
-        (void)hipFuncSetAttribute((const void*)km, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        hipLaunchKernelGGL(km, dim3((unsigned)a.nq), dim3(64), shm, st, a);
-    } else if (a.dtype == JX_F16) {
-        auto kt = bruteforce_tile_kernel<JX_F16>;
-        (void)hipFuncSetAttribute((const void*)kt, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        hipLaunchKernelGGL(kt, grid, dim3(256), sh, st, a);
-        auto km = bruteforce_merge_kernel<JX_F16>;
-        (void)hipFuncSetAttribute((const void*)km, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        hipLaunchKernelGGL(km, dim3((unsigned)a.nq), dim3(64), shm, st, a);
-    } else {
-        auto kt = bruteforce_tile_kernel<JX_F32>;
-        (void)hipFuncSetAttribute((const void*)kt, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        hipLaunchKernelGGL(kt, grid, dim3(256), sh, st, a);
-        auto km = bruteforce_merge_kernel<JX_F32>;
-        (void)hipFuncSetAttribute((const void*)km, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        hipLaunchKernelGGL(km, dim3((unsigned)a.nq), dim3(64), shm, st, a);
-    }
-    return hipGetLastError();
+    if (a.dtype == JX_U8) return launch_tile_kernels<JX_U8, false>(a, st);  // exact lists: nothing is handed back
+    if (a.dtype == JX_F16) return a.redo ? launch_tile_kernels<JX_F16, true>(a, st) : launch_tile_kernels<JX_F16, false>(a, st);
+    return a.redo ? launch_tile_kernels<JX_F32, true>(a, st) : launch_tile_kernels<JX_F32, false>(a, st);
 }
 
 // ------------------------------------------------------------------ utilities

@@ -745,6 +745,36 @@ static hipError_t launch_knn_lists(const KnnArgs& a, hipStream_t st) {
     return knn_list_regs(a.kp) == 1 ? launch_knn<DT, 1>(a, st) : launch_knn<DT, 3>(a, st);
 }
 
+// A few neighbours among vectors of few coordinates: the tiled kernel has as little to do as the vectors are short, this one
+// keeps k + KNN_SLACK candidates of float types, a few steps' worth of lists and five launches.  The number of vectors (for
+// float types of coordinates) from which this one is at least even; tiled / this in us, d = 16 and k = 1 unless said.
+//   float32   1 x 20,000 28.7 / 53.6, 1 x 80,000 55 / 67, 1 x 130,000 93 / 92; 64 x 120,000 252 / 323; 1,000 x 80,000 268 / 463,
+//             400 x 160,000 348 / 522, k = 2 1,000 x 640,000 0.93 times as fast; k = 4 1,000 x 260,000 664 / 795, but 100 x
+//             160,000 1.13 times as fast; 15,000 x 20,000 0.75, 5,000 x 80,000 even
+//   binary16  d = 64 1 x 20,000 36 / 49; 64 x 120,000 287 / 322, 457 x 120,000 350 / 439, 400 x 320,000 1.17 times as fast; k = 4
+//             457 x 120,000 355 / 431; from 1,000 queries on ahead
+//   uint8     d = 64 1 x 20,000 28.0 / 32.7; 130 x 120,000 249 / 274; 1,000 x 60,000 235 / 258, x 80,000 even
+static long long knn_fewest(const BfArgs& b, const long long row) {
+    if (b.dtype == JX_U8) {
+        if (row >= 96) return 0;
+        if (b.nq == 1) return b.k < 4 ? 25000 : 0;
+        return b.k > 1 || b.nq <= 48 || b.nq >= 1200 ? 0 : (b.nq < 600 ? 130000 : 70000);
+    }
+    const bool half = b.dtype == JX_F16;
+    long long coords = 0;
+    if (b.nq <= 4)
+        coords = b.nq * b.k <= (half ? 2 : 0) ? 2000000 : (b.nq * b.k <= 4 ? 1300000 : (b.nq * b.k <= 8 ? 650000 : 0));
+    else if (b.nq <= 32)
+        coords = 0;
+    else if (b.nq <= 64)
+        coords = b.k > 1 || row > 128 ? 0 : (half ? 8000000 : 2200000);
+    else if (b.nq < (half ? 600 : 2000))
+        coords = row > 128 || b.k > 5 ? 0 : (b.k < 4 ? (half ? 10500000 : 5200000) : (half ? 3900000 : (b.nq < 200 ? 1300000 : 4200000)));
+    else
+        coords = b.k < (half ? 2 : 4) ? 1000000 : 0;
+    return coords / b.d;
+}
+
 // Takes the search over where it is the faster one and its lists fit scratch_bytes; *done says so.  b.nsplit: the split the
 // tiled kernel would run with.
 hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_bytes, hipStream_t st, char* name, bool* done) {
@@ -780,6 +810,7 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     if (nsplit < 1 || qt * nsplit < 64) return hipSuccess;
     if (b.n < (exact ? 6000 : 16384)) return hipSuccess;
     if (b.k < 8 && row < 1024 && b.nq > 64 && b.n < 100000 && b.nq * b.n < 60000000) return hipSuccess;
+    if (b.n < knn_fewest(b, row)) return hipSuccess;
     a.nsplit = (int)nsplit;
     a.r_th = (int)((a.kp + nsplit - 1) / nsplit);
     uint8_t* p = (uint8_t*)scratch + scratch_bytes - aux;  // behind the lists and the published distances

@@ -85,7 +85,7 @@ def rows(dtype, n, d, seed):
     return (x * 40 + 128).clamp_(0, 255).to(torch.uint8) if dtype == torch.uint8 else x.to(dtype)
 
 
-@pytest.mark.parametrize("dtype,nq,k", [(torch.uint8, 65_536, 10), (torch.float32, 40_000, 1), (torch.float16, 40_000, 4)])
+@pytest.mark.parametrize("dtype,nq,k", [(torch.uint8, 65_536, 10), (torch.float32, 40_000, 4), (torch.float16, 40_000, 4)])
 def test_one_slice(jx, dtype, nq, k):
     """So many queries that one workgroup takes the whole base set for its own: no distances are published."""
     check(jx, rows(dtype, 16_500, 16, 4), rows(dtype, nq, 16, 5), k)
@@ -125,3 +125,16 @@ def test_batches_that_the_tiled_kernel_keeps(jx):
     ids, dist = index(jx, x).bruteforce(q, 100)
     assert jx.bruteforce_kernel() == "bruteforce_tile_kernel<0> nsplit=1"
     check_samples(jx, x, q, 100, ids, dist, (0, 83_776, 83_840, 149_872))
+
+
+@pytest.mark.parametrize("dtype,d,nq,k,fewest", [
+    (torch.uint8, 64, 1, 3, 25_000), (torch.uint8, 64, 300, 1, 130_000), (torch.uint8, 64, 700, 1, 85_715), (torch.float32, 16, 1, 1, 81_250),
+    (torch.float32, 16, 4, 2, 40_625), (torch.float16, 64, 2, 1, 31_250), (torch.float32, 16, 40, 1, 137_500), (torch.float16, 64, 64, 1, 125_000),
+    (torch.float32, 32, 400, 3, 162_500), (torch.float32, 16, 1_000, 5, 262_500), (torch.float32, 36, 200, 1, 100_000), (torch.float32, 16, 2_000, 3, 62_500),
+    (torch.float16, 32, 400, 2, 328_125), (torch.float16, 16, 601, 4, 99_834), (torch.float32, 16, 33, 2, 16_384)])
+def test_few_neighbours_of_short_vectors(jx, dtype, d, nq, k, fewest):
+    """The tiled kernel keeps what it does faster: on both sides of the number of vectors from which it does not."""
+    x, q = rows(dtype, fewest, d, 10), rows(dtype, nq, d, 11)
+    check(jx, x, q, k)
+    jx.bruteforce_static(x[:fewest - 1], q, k)
+    assert jx.bruteforce_kernel().startswith("bruteforce_tile_kernel<")
