@@ -212,7 +212,9 @@ __global__ void __launch_bounds__(256) encode_kernel(EncodeArgs a) {
 // Bound: vector instructions.  A table of the quotients and a binary search per breakpoint and level took ten times the LDS
 // reads, and its 54 KB held a CU to two workgroups: 50,000 vectors of d = 960, 4 bits 16.7 -> 7.8 ms,
 // with the runs that cannot reach the best cosine ended early 7.1 ms.  Bounding the cosine
-// on a grid of 256 values of t first left most breakpoints in and took 15.7 ms.
+// on a grid of 256 values of t first left most breakpoints in and took 15.7 ms.  Vectors of few dimensions have little to
+// move: with the table / now 53,353 x 96 1,105 / 1,111 us, 53,353 x 128 1,315 / 1,320, 30,000 x 256 1,222 / 1,270, 20,000 x
+// 512 2,170 / 1,612 (the searches for a run's first counts one after the other: 1,146, 1,418, 1,347 and 1,667)
 #define MC_CAP 8192   // breakpoints per vector
 #define MC_DMAX 4096  // dimensions
 
@@ -318,31 +320,44 @@ __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
     const int p0 = (tid - lev * SEGS) * run, p1 = lev < NL ? (p0 + run < npos ? p0 + run : npos) : 0;
     const double J = (double)(lev + 1);
     int cnt[NL];  // level-(jj+1) breakpoints <= t
+    // whether runs are long enough for an early end (never: 128 dimensions 1,320 -> 1,405 us, 256 1,270 -> 1,410)
+    const bool ends = run > 3;
+    uint32_t first = 0;         // estimate of the cosine at the run's first breakpoint
     if (p0 < p1) {
         const double A = (double)sa[p0];
-        double ip = ip0, nn = nn0;
+        // binary searches of all levels side by side, a chain of LDS reads for one (behind npos stand zeros, which are below
+        // every limit)
 #pragma unroll
-        for (int jj = 0; jj < NL; jj++) {
-            const double lim = (double)(jj + 1) * A;
-            int lo = 0, hi = npos;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (lim <= J * (double)sa[mid])
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            cnt[jj] = lo;
-            ip += pref[lo];
-            nn += 2.0 * (double)(jj + 1) * (double)lo;
+        for (int jj = 0; jj < NL; jj++) cnt[jj] = 0;
+        for (int step = dpad >> 1, last = 0; !last; step = step > 1 ? step >> 1 : 0) {
+            last = step == 0;  // dpad entries have dpad + 1 places: one more step of one
+            const int by = last ? 1 : step;
+#pragma unroll
+            for (int jj = 0; jj < NL; jj++)
+                if ((double)(jj + 1) * A <= J * (double)sa[cnt[jj] + by - 1]) cnt[jj] += by;
         }
-        atomicMax(&s_low, __float_as_uint((float)(ip * unit) * __builtin_amdgcn_rsqf((float)nn)));
+        if (ends) {
+            double ip = ip0, nn = nn0;
+#pragma unroll
+            for (int jj = 0; jj < NL; jj++) {
+                ip += pref[cnt[jj]];
+                nn += 2.0 * (double)(jj + 1) * (double)cnt[jj];
+            }
+            first = __float_as_uint((float)(ip * unit) * __builtin_amdgcn_rsqf((float)nn));
+        }
     }
-    __syncthreads();
+    if (ends) {
+        first = max(first, dpp_u32<0xB1>(first));
+        first = max(first, dpp_u32<0x4E>(first));
+        first = max(first, dpp_u32<0x141>(first));
+        first = max(first, dpp_u32<0x140>(first));
+        if ((tid & 15) == 0) atomicMax(&s_low, first);
+        __syncthreads();
+    }
     if (p0 < p1) {
         // the largest cosine among the first breakpoints of all runs has to be reached; from t on no cosine exceeds the
         // largest <xbar,|r|> there is over ||xbar|| at t: beyond the maximum, where the counts move fastest, runs end early
-        const float low = __uint_as_float(s_low) * 0.99999f;
+        const float low = ends ? __uint_as_float(s_low) * 0.99999f : 0.f;
         const float ip_all = (float)((ip0 + (double)NL * pref[npos]) * unit);
         for (int p = p0; p < p1; p++) {
             const float Af = sa[p];
