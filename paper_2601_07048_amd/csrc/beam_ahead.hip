@@ -336,6 +336,14 @@ hipError_t launch_beam_ahead(int kind, int qbits, const BeamArgs& a, hipStream_t
     // not for expansion lists (insertion): early in a build nearly every neighbour has been seen, and a link is the merge
     // (d = 960 float32, 24 points 122 -> 170 us, 142 points 294 -> 309)
     if (a.R > 64 || a.L > 256 || a.vis_cap || (a.flags & ~prune_flags)) return hipSuccess;
+    // nor for rows so short that handing over costs more than their gather and arithmetic (one query, R = 16 / 32 / 64: 4-bit
+    // codes of d = 960 at L = 200 0.86 / 0.98 / 1.29 times as fast, 1-bit codes of d = 1536 0.88 / 0.94 / 1.10, at L = 100 0.95
+    // / 1.02 / 1.06; float32 d = 200 at L = 256 0.94 / 1.4 / 2.0, d = 960 1.4 and more)
+    if (kind == K_RQ4 || kind == K_RQ1) {
+        if (a.R <= 16 || (a.R <= 32 && a.L > 128)) return hipSuccess;
+    } else if (a.R <= 16 && a.L > 128 && a.ds.nch <= 64) {
+        return hipSuccess;
+    }
     switch (kind) {
         case K_F32: return launch_ahead_kind<K_F32, 0>(a, st, name, done);
         case K_F16: return launch_ahead_kind<K_F16, 0>(a, st, name, done);

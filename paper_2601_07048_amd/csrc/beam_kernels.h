@@ -96,7 +96,7 @@ __device__ __forceinline__ void frontier_merge(uint64_t (&fk)[NREG], uint64_t* f
     bool beats = lane < n && ckm < worst;
     uint64_t todo = ballot(beats);
     if (todo == 0ull) return;  // nothing enters the frontier (the common case late in a search)
-    if (__builtin_popcountll(todo) <= MERGE_FEW<NREG>) {
+    if (MERGE_FEW<NREG> > 0 && __builtin_popcountll(todo) <= MERGE_FEW<NREG>) {  // (a constant: no such code at all where 0)
         // few candidates (the usual case): one after the other, ranked with a ballot per frontier register and moved
         // in with a one-lane shift; the mirror is written and not waited for
         int n_ins = 0;
@@ -271,6 +271,33 @@ inline long long wide_max_queries(int L) {
     if (!wide_two_resident<KIND, T, CPL, NREG, QB>()) return 1024;
     if (CPL >= 4 && T == 64 && L > 32) return CPL == 4 ? 1280 : 1024;
     return WIDE_MAX_QUERIES;
+}
+
+// Whether the instances of a shape with NREG frontier registers exist (MODE of beam_search_body)
+template <int KIND, int T, int CPL, int NREG>
+constexpr bool has_mode(int mode) {
+    return mode == 0 || (mode == 1 && NREG < 6) || (mode == 2 && has_wide<T, CPL>() && (NREG < 6 || KIND != K_RQ1));
+}
+
+// The form of a batch.  Figures: as many times as fast as the general form.
+//   2  wide: where a row may hold more neighbours than the usual form keeps in flight, and more than 16 unless a record takes
+//      four chunks of every lane (R = 16, one query, L = 200: float32 d = 96 0.95, d = 200 0.92, d = 960 1.4).  With six
+//      and eight frontier registers the merge is the longest part: not for bit planes (0.88 to 1.00), and others only where
+//      rows are long or records are (L = 300, R = 16 / 64: float32 d = 96 0.90 / 1.06, d = 960 1.13 / 1.24)
+//   1  the tag table's own loop.  It costs six or eight wavefronts' worth of registers the seventh or the fifth, and with six
+//      and eight frontier registers it gains nothing (0.93 to 1.01).  Short records with three or four frontier registers
+//      pay for the lost wavefront beyond 4,096 queries (256-byte uint8 and binary16, L = 200, 4,500 queries 0.78, 10,000
+//      0.89, 2,500 1.03); longer ones wait for memory (0.98 to 1.10)
+template <int KIND, int T, int CPL, int NREG, int QB>
+inline int beam_mode(const BeamArgs& a) {
+    if (a.tag_bits == 0 || a.R > 64) return 0;
+    constexpr int usual = 64 / T * (8 / CPL > 0 ? 8 / CPL : 1);  // records in flight
+    constexpr int rows = CPL >= 4 || usual > 16 ? usual : 16;
+    if (has_mode<KIND, T, CPL, NREG>(2) && a.R > rows && a.nq <= wide_max_queries<KIND, T, CPL, NREG, QB>(a.L) &&
+        (NREG < 6 || a.R > 32 || a.ds.nch > 64))
+        return 2;
+    if (NREG >= 6 || (NREG >= 3 && a.ds.rec_stride <= 256 && a.nq > 4096)) return 0;
+    return 1;
 }
 
 // One query per wavefront, WPB wavefronts (queries) per workgroup; TILED selects the element-strided loads of the

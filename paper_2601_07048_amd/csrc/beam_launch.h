@@ -39,9 +39,10 @@ static hipError_t launch_nreg(const BeamArgs& a, hipStream_t st, char* name) {
 #define JX_LAUNCH(NR)                                                                                   \
     {                                                                                                   \
         size_t sh = ((size_t)query_lds_bytes<KIND, T, CPL, QB>() + (size_t)mirror_entries<NR>() * 8 + 64 * 8 + 64 * 4 + (size_t)H * (a.tag_bits ? 2 : 4)) * JX_BEAM_WPB; \
-        const int mode = a.tag_bits > 0 && a.R <= 64 ? (has_wide<T, CPL>() && a.nq <= wide_max_queries<KIND, T, CPL, NR, QB>(a.L) ? 2 : 1) : 0; \
-        auto kern = mode == 2 ? beam_search_kernel<KIND, T, CPL, NR, QB, has_wide<T, CPL>() ? 2 : 1>    \
-                              : (mode ? beam_search_kernel<KIND, T, CPL, NR, QB, 1> : beam_search_kernel<KIND, T, CPL, NR, QB, 0>); \
+        const int mode = beam_mode<KIND, T, CPL, NR, QB>(a);                                            \
+        auto kern = mode == 2 ? beam_search_kernel<KIND, T, CPL, NR, QB, has_mode<KIND, T, CPL, NR>(2) ? 2 : 0> \
+                              : (mode ? beam_search_kernel<KIND, T, CPL, NR, QB, has_mode<KIND, T, CPL, NR>(1) ? 1 : 0> \
+                                      : beam_search_kernel<KIND, T, CPL, NR, QB, 0>);                   \
         if (sh > 48 * 1024) {                                                                           \
             hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh); \
             if (e != hipSuccess) return e;                                                              \

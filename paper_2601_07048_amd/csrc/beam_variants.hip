@@ -184,7 +184,7 @@ template <int KIND, int T, int CPL>
 static hipError_t launch_visited_shape(const BeamArgs& a, hipStream_t st, char* name) {
     const int nreg = (a.L + 63) / 64;
     const size_t tail = 64 * 8 + 64 * 4 + (size_t)a.hash_slots * (a.tag_bits ? 2 : 4) + (size_t)a.vis_cap * 8;
-    const int mode = a.tag_bits > 0 && a.R <= 64 ? (has_wide<T, CPL>() && a.nq <= wide_max_queries<KIND, T, CPL, 2, 0>(a.L) ? 2 : 1) : 0;
+    const int mode = beam_mode<KIND, T, CPL, 2, 0>(a);
     if (name) snprintf(name, 96, "beam_search_visited_kernel<%d,%d,%d,%d,%d>", KIND, T, CPL, nreg <= 1 ? 1 : 2, mode);
 #define JX_LAUNCH(NR)                                                                                                         \
     {                                                                                                                         \

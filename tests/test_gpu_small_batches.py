@@ -113,3 +113,36 @@ def test_wide_instances_end_where_they_lose(jx, dtype, d, L, most):
     ids1, dist1, st1 = g.search(q, 10, L, stats=True)
     assert st["beam_kernel"].endswith(",2>") and st1["beam_kernel"].endswith(",1>"), (st["beam_kernel"], st1["beam_kernel"])
     assert torch.equal(ids, ids1[:most]) and torch.equal(dist, dist1[:most])
+
+
+@pytest.mark.parametrize("dtype,d,R,L,form", [
+    ("float16", 128, 64, 200, {1000: 2, 4096: 1, 4097: 0}), ("uint8", 256, 16, 150, {1000: 1, 4097: 0}), ("float32", 200, 64, 200, {4097: 1}),
+    ("float32", 96, 16, 200, {1000: 1}), ("float32", 96, 17, 200, {1000: 2}), ("float32", 96, 32, 300, {1000: 0}), ("float32", 96, 33, 300, {1000: 2, 1025: 2, 1537: 0}),
+    ("float32", 960, 16, 300, {1000: 2, 1025: 0}), ("float32", 960, 16, 64, {1000: 2})])
+def test_forms_end_where_they_lose(jx, dtype, d, R, L, form):
+    """Rows that the usual form covers, frontiers of six registers and more, short records beyond four wavefronts per SIMD:
+    each batch runs in the form that is the fastest there, and all return the same."""
+    n = 1500
+    x = random_data(n, d, np.uint8 if dtype == "uint8" else np.float32, 17).astype(dtype)
+    q = dev(random_data(4097, d, np.uint8 if dtype == "uint8" else np.float32, 18).astype(dtype))
+    g = jx.Index(d, jx_dtype(jx, x), R, 48, 1.2, capacity=n, max_batch=4097)
+    g.insert(dev(x))
+    g.set_flags(jx.FLAG_VISITED_IDS)
+    ids0, dist0, st0 = g.search(q, 10, L, stats=True)
+    assert st0["beam_kernel"].endswith(",0>")
+    g.set_flags(0)
+    for nq, mode in form.items():
+        ids, dist, st = g.search(q[:nq], 10, L, stats=True)
+        assert st["beam_kernel"].startswith("beam_search_kernel<") and st["beam_kernel"].endswith(f",{mode}>"), (nq, st["beam_kernel"])
+        assert torch.equal(ids, ids0[:nq]) and torch.equal(dist, dist0[:nq])
+
+
+@pytest.mark.parametrize("R,L,team", [(64, 200, True), (33, 200, True), (32, 200, False), (32, 128, True), (16, 64, False)])
+def test_teams_need_rows_to_read_ahead(jx, R, L, team):
+    n, d = 1500, 960
+    x, q = random_data(n, d, np.float32, 19), random_data(64, d, np.float32, 20)
+    g = jx.Index(d, jx.F32, R, 48, 1.2, capacity=n, max_batch=4096, quant_bits=4)
+    g.insert(dev(x))
+    rot = np.linalg.qr(np.random.default_rng(9).standard_normal((d, d)))[0].astype(np.float32)
+    g.quantize(4, dev(rot), query_bits=8, rule=jx.RULE_MAXABS)
+    assert _compare(jx, g, dev(q), L, mode=jx.RABITQ) == ("beam_search_ahead_kernel" if team else "beam_search_kernel")
