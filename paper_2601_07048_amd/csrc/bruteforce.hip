@@ -1,5 +1,6 @@
-// Exhaustive k-nearest-neighbour search: the recall ground truth (Sec. 6.1).  The tiled form, for small searches, rows off
-// 16-byte boundaries, lists that only just fit the scratch, and the queries knn_tile.hip hands back; the rest runs there.
+// Exhaustive k-nearest-neighbour search: the recall ground truth (Sec. 6.1).  The tiled form, for small searches, a few
+// neighbours of short vectors, very long rows, rows off 16-byte boundaries, lists that only just fit the scratch, and the
+// queries knn_tile.hip hands back; the rest runs there.
 //
 // A 256-thread workgroup owns a tile of 64 queries and streams a slice of the
 // base set through LDS in tiles of 64 vectors.  Each thread accumulates a 4x4

@@ -14,13 +14,14 @@
 //   float32/binary16 v_mfma_f32_32x32x2_f32 / 32x32x16_f16: these distances only choose KNN_SLACK more candidates
 //                    than asked for.  The merge kernel evaluates them with the arithmetic of bruteforce_tile_kernel,
 //                    operation by operation, orders them, and proves that nothing left out can be among the first
-//                    k: the first distance left out, less the error bound of both forms, has to exceed the k-th one.
+//                    k: the first distance left out, less the error bound of both forms (knn_bound.h), has to exceed
+//                    the k-th one.
 //                    Queries for which it does not (ties, sets far from the origin) are flagged, and their tiles are done
 //                    again by bruteforce_tile_kernel.  So the result is that kernel's, bit for bit.
 //
 // Bound: matrix cores for float32 (1.8 of 2.5 ms below, 107 TFLOP/s), vector instructions and barriers for uint8 (2.9 of
-// 4.4 ms without a single candidate).  Against bruteforce_tile_kernel: 10,000 x 1M uint8 d = 128, k = 10 27.0 -> 4.4 ms;
-// 1,000 x 100,003 float32 d = 960, k = 100 12.9 -> 2.7 ms; 1,000 x 100,000 binary16 d = 960, k = 10 3.97 -> 0.84 ms;
+// 4.3 ms without a single candidate).  Against bruteforce_tile_kernel: 10,000 x 1M uint8 d = 128, k = 10 27.2 -> 4.31 ms;
+// 1,000 x 100,003 float32 d = 960, k = 100 13.0 -> 2.55 ms; 1,000 x 100,000 binary16 d = 960, k = 10 3.97 -> 0.84 ms;
 // 2 x 234,001 float32 d = 128, k = 1 1.12 -> 0.17 ms.  Without the seeds the lists fill with what comes first: 5.6 and 5.3 ms.
 #include <stdio.h>
 #include "jx_distance.h"
