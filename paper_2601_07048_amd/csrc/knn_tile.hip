@@ -47,7 +47,7 @@ typedef _Float16 kf16x8 __attribute__((ext_vector_type(8)));
 #define KNN_BLOCKS 512
 #define KNN_ODD 30  // rows that are listed for the merge of a query tile, see KnnOdd
 
-// Rows of the base set that no threshold can judge: float32 with a NaN, binary16 with a NaN or an infinity.  They are kept
+// Rows of the base set that no threshold can decide on: float32 with a NaN, binary16 with a NaN or an infinity.  They are kept
 // out of the lists, and the merge evaluates them for every query; more than KNN_ODD of them leave its results unproven.
 struct KnnOdd {
     uint32_t count;
@@ -56,7 +56,7 @@ struct KnnOdd {
 };
 
 template <int DT>
-constexpr uint32_t KNN_JUDGED = DT == JX_F16 ? 0x7F800000u : 0x7F800001u;  // bits of |b|^2 from which a row is one of those
+constexpr uint32_t KNN_DECIDABLE = DT == JX_F16 ? 0x7F800000u : 0x7F800001u;  // bits of |b|^2 from which a row is one of those
 
 struct KnnArgs {
     const void* base;
@@ -385,12 +385,12 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                 }
                 if constexpr (DT != JX_U8 && !SEED) {
                     const uint32_t lo = max(norm[0], norm[1]), hi = max(norm[2], norm[3]), most = max(lo, hi);
-                    if (most < KNN_JUDGED<DT>) {
+                    if (most < KNN_DECIDABLE<DT>) {
                         bmax = max(bmax, most);
                     } else if (sch == 0) {
 #pragma unroll
                         for (int t = 0; t < 4; t++) {
-                            if (norm[t] < KNN_JUDGED<DT>) {
+                            if (norm[t] < KNN_DECIDABLE<DT>) {
                                 bmax = max(bmax, norm[t]);
                             } else {
                                 const uint32_t to = atomicAdd(&a.odd[blockIdx.x].count, 1u);

@@ -1,5 +1,5 @@
 """The exhaustive search on the matrix cores at the ends of what it takes: rows so long that uint8 distances leave its
-integer range, floats so small that squares are subnormal, rows that no threshold can judge, sets far from the
+integer range, floats so small that squares are subnormal, rows that no threshold can decide on, sets far from the
 origin.  Every result is compared with the tiled kernel's, which rows on 4-byte boundaries take."""
 import pytest
 import torch
@@ -44,7 +44,7 @@ def test_tiny_floats(jx, scale):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("rows", [1, 30, 31, 2_000])
 def test_rows_with_nan_and_infinities(jx, dtype, rows):
-    """Up to 30 rows that no threshold can judge are evaluated for every query; beyond that the tiled kernel runs."""
+    """Up to 30 rows that no threshold can decide on are evaluated for every query; beyond that the tiled kernel runs."""
     g = torch.Generator(device="cuda").manual_seed(2)
     b, q = (torch.randn((n, 64), device="cuda", generator=g).to(dtype) for n in (20_000, 250))
     at = torch.randperm(20_000, device="cuda", generator=g)[:rows]
