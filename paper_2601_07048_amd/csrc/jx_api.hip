@@ -706,6 +706,7 @@ static int run_subbatch(jx_index* idx, const InsertWork& w, int64_t pos0, int64_
     a.vals = (uint32_t*)(W + w.vals0);
     a.heads = (const uint32_t*)(W + w.heads);
     a.nseg = (const uint32_t*)(W + w.counters);
+    a.lists = (uint64_t*)(W + w.keys1);  // free once the edges are sorted
     a.clean = incremental_prune(idx) ? idx->d_clean : nullptr;
     // forward prune: no LDS vector cache.  A whole frontier (128 x 128 bytes per wavefront) would leave room for
     // one workgroup per CU only, and the Gram-matrix form then measured slower (47 ms against 32 ms per 1M inserts)
@@ -987,6 +988,7 @@ int jx_consolidate(jx_index* idx, void* stream) {
     a.vals = (uint32_t*)(W + w.vals1);
     a.heads = (const uint32_t*)(W + w.heads);
     a.nseg = (const uint32_t*)(W + w.counters);
+    a.lists = (uint64_t*)(W + w.keys0);
     a.force_prune = 1;
     a.clean = incremental_prune(idx) ? idx->d_clean : nullptr;
     a.gram = gram_mode(idx);

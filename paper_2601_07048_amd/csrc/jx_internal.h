@@ -80,7 +80,8 @@ struct InsertArgs {
     uint64_t* keys;             // [B*R] edge keys
     uint32_t* vals;             // [B*R] edge sources
     const uint32_t* heads;      // segment starts (reverse merge); bit 31 is set by a kernel that has merged the segment
-    const uint32_t* nseg;       // number of segments (device)
+    const uint32_t* nseg;       // number of segments (device); [1], [2]: lengths of the lists below, cleared by the sort
+    uint64_t* lists;            // Gram-matrix kernels: room for an entry per edge, segments by size
     long long E;                // reverse merge: number of sorted edges (0 = B * R)
     int force_prune;            // consolidation: ignore the existing row, always prune the candidate segment
     int gram;                   // float data: 1 (float32) / 2 (binary16) = prunes of at most 128 candidates go to the Gram-matrix kernels

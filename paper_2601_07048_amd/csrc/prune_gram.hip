@@ -1,44 +1,48 @@
-// robustPrune (Alg. 3) for float32 / binary16 vectors as a dense contraction.
+// robustPrune (Alg. 3) as a dense contraction, one workgroup per prune.
 //
-// Whether candidate i discards candidate j (alpha * d(i,j) <= d(p,j)) does not
-// depend on the order in which Alg. 3 selects, so all pair distances of one
-// prune are computed at once from the Gram matrix of its candidate vectors,
+// Whether candidate i discards candidate j (alpha * d(i,j) <= d(p,j), i before j) does not depend on what Alg. 3 has
+// selected, so all pair distances of one prune are computed at once from the Gram matrix of its candidate vectors,
 //     d(i,j) = G_ii + G_jj - 2 G_ij,   G = X X^T,
-// on the matrix cores, and every candidate vector is read exactly once (the
-// selection-centric form reads the surviving candidates again for every
-// selected neighbour: 20-30 times the bytes for 2-6 KB vectors).
+// on the matrix cores, and every candidate vector is read exactly once.
+//   float32 : rows centred at the pruned vertex p (x_j - x_p: distances are translation invariant and the cancellation
+//             in G_ii + G_jj - 2 G_ij then involves local magnitudes only); G_jj is d(p,j) itself.  A centred value is
+//             the exact sum of three bfloat16 values (8 + 8 + 8 bits of its significand), and the six products of weight
+//             2^-16 and above go through v_mfma_f32_32x32x16_bf16: 192 cycles for 16 coordinates where
+//             v_mfma_f32_32x32x2f32 takes 512.  What is left out is below 2^-25 of a product.  Every 32 coordinates have a
+//             sum of their own, added to the total by the vector unit, so the result is nearer to the exact one than that
+//             of the float32 instruction: relative error of d(i,j) against 64 bits, root mean square / largest,
+//             d = 128 1.1e-7 / 4.7e-7 (float32 instruction 2.9e-7 / 1.5e-6), d = 960 1.4e-7 / 5.5e-7 (7.1e-7 / 2.9e-6).
+//   binary16: v_mfma_f32_32x32x16_f16 on the stored values (products exact, float32 accumulation).
+//   uint8   : v_mfma_i32_32x32x32_i8 on the values shifted by -128, exact.
 //
-// One wavefront per prune, up to 128 candidates = 4 blocks of 32 rows.  Operand
-// fragments go straight from global memory into the MFMA operand registers: a
-// lane (row r = lane % 32, half h = lane / 32) loads the 64 contiguous bytes
-// h*64 .. h*64+63 of each 128-byte piece of its row, and the k-th 16-byte
-// load is the operand of the k-th MFMA step for the A side (row block bi) and
-// the B side (row block bj) alike; since both sides use the same assignment of
-// vector coordinates to MFMA k-slots, any such assignment sums every
-// coordinate exactly once.
-//   float32 : v_mfma_f32_32x32x2f32 on rows centred at the pruned vertex p
-//             (x_j - x_p: distances are translation invariant and the
-//             cancellation in G_ii + G_jj - 2 G_ij then involves local
-//             magnitudes only); G_jj is d(p,j) itself.
-//   binary16: v_mfma_f32_32x32x16_f16 on the stored values (products exact,
-//             float32 accumulation, as in the binary16 distance provider);
-//             where d(p,.) is not known beforehand p joins as one more row.
-// The upper triangle of tiles is enough for candidates in any order: element
-// (i,j), i in an earlier block than j, yields both "i discards j" and "j
-// discards i" (two ballots per accumulator register = two 32-column stripes of
-// bit masks).  Alg. 3 itself is then a walk over the candidates in (distance,
-// id) order on 128-bit masks.
+// The rows are cut into NB blocks of 32, a wavefront each.  Per slab of 128 bytes of every row a wavefront loads, centres
+// and splits its own block once and puts it into LDS as MFMA operands; block b then takes the tiles (b, b), (b, b+1), ..
+// (b, b + nb/2) modulo nb, which covers every pair of blocks once and gives each wavefront the same number of tiles.  The
+// next slab is on its way while one is multiplied.  NB = 4 holds 128 candidates, NB = 8 holds 256.
+//
+// What bounds it: the matrix cores where vectors are long (d = 960, float32), the relation and the fixpoint where they are
+// short.  One wavefront per prune took 450 us for 256 candidates of d = 960, the length of a launch however small its
+// batch; a workgroup takes 60.  Build of 20,000 x 960 float32: prunes 62 -> 15 ms of 96 -> 49; 60,000 x 128 float32
+// 40.6 -> 21.6 ms, binary16 23.9 -> 12.5.
+//
+// The relation is kept as bit masks by victim, and only with discarders that come before it in (distance, id) order:
+// element (i, j) of a tile gives "i discards j" (bits gathered in the lane of j) or "j discards i" (a ballot per row).
+// Alg. 3 is then a fixpoint: a candidate with a selected discarder is dead; one whose discarders are all dead is
+// selected.  The first undecided candidate in order is always decided, so a round makes progress, and a handful of rounds
+// of 40 to 130 instructions replace a walk of up to 256 dependent LDS reads.  Candidates beyond the R-th selected one are
+// cut off afterwards: they cannot influence earlier ones.
 #include "jx_distance.h"
 
 namespace jx {
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef int gi32x16_t __attribute__((ext_vector_type(16)));
 typedef int gi32x4_t __attribute__((ext_vector_type(4)));
 
-// accumulator of a tile: float32, or int32 for uint8 vectors (v_mfma_i32_32x32x32_i8 on the values shifted by -128:
-// distances are translation invariant and everything stays an exact integer)
 template <int DT> struct GAcc { typedef f32x16_t type; };
 template <> struct GAcc<JX_U8> { typedef gi32x16_t type; };
 
@@ -49,7 +53,7 @@ __device__ __forceinline__ uint4 shift128(uint4 x) {
     x.w ^= 0x80808080u;
     return x;
 }
-// d(i,j) from G_ii, G_jj (held as raw bits in the float arrays) and G_ij, as the float the alpha test uses
+// d(i,j) from G_ii, G_jj (raw bits in the float arrays for uint8) and G_ij, as the float the alpha test uses
 template <int DT, typename A>
 __device__ __forceinline__ float gram_dist(float ni, float nj, A gij) {
     if constexpr (DT == JX_U8)
@@ -57,662 +61,392 @@ __device__ __forceinline__ float gram_dist(float ni, float nj, A gij) {
     else
         return fmaxf((ni + nj) - 2.f * (float)gij, 0.f);
 }
-template <int DT, typename A>
-__device__ __forceinline__ float gram_store(A g) {
-    if constexpr (DT == JX_U8)
-        return __int_as_float((int)g);
-    else
-        return (float)g;
+
+// two floats -> two bfloat16 (round to nearest even) in one register, and what is left of the floats (exact)
+__device__ __forceinline__ uint32_t take_bf16(float& a, float& b) {
+    const f32x2_t x = {a, b};
+    const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));
+    a -= __uint_as_float(h << 16);
+    b -= __uint_as_float(h & 0xFFFF0000u);
+    return h;
 }
 
-#ifndef GP_WPB
-#define GP_WPB 1  // wavefronts per workgroup (independent of each other)
-#endif
-#define GP_MAX 128
+// wavefronts per SIMD that the registers are held to: float32 needs 160 (NB = 4) and 224 of them
+#define GT_WAVES(DT, NB) ((DT) != JX_F32 ? 4 : (NB) == 4 ? 3 : 2)
+#define GT_SMALL 128
+#define GT_BIG 256
+#define GT_PIECE 576  // bytes of 32 rows x 16 operand bytes, padded: 64 bytes further on in the banks from piece to piece
 
-struct GramLds {
-    uint64_t key[GP_MAX];
-    uint32_t id[GP_MAX];
-    float dp[GP_MAX];   // d(p, j)
-    float nrm[GP_MAX];  // G_jj
-    float gv[GP_MAX];   // G_jp (binary16, p as extra row)
-    uint32_t kill[GP_MAX * 4];  // row i: mask over j of "i discards j", words of column blocks >= block(i)
-    uint32_t kb[GP_MAX * 4];    // row i: mask over j of "j discards i", words of column blocks > block(i)
-    uint32_t sel_id[GP_MAX];
-    uint32_t sel_dist[GP_MAX];
-    uint8_t order[GP_MAX];      // rank in (distance, id) order -> candidate slot
+template <int DT, int NB>
+struct TeamLds {
+    static constexpr int M = 32 * NB;
+    static constexpr int PIECES = DT == JX_F32 ? 12 : 8;  // operand pieces of a block and slab: [step][part][half]
+    union {
+        uint8_t slab[NB * PIECES * GT_PIECE];
+        struct {
+            uint32_t kb[NB * M];   // [w][victim]: which candidates of block w discard the victim
+            uint64_t key[M];
+            uint32_t by_rank[M];   // slot of the selected candidate of this rank, or JX_NONE_ID
+            uint32_t sel_id[M];
+            uint32_t sel_dist[M];  // float bits of d(p, selected), selection order
+        };
+    };
+    uint32_t id[M];
+    float dp[M];        // d(p, j); -1 beyond the last candidate: nothing discards it
+    float nrm[M];       // G_jj
+    uint32_t rank[M];   // place in (distance, id) order
+    int nsel;
 };
 
-__host__ __device__ constexpr int gp_tile(int nt, int bi, int bj) { return bi * nt - bi * (bi - 1) / 2 + (bj - bi); }
-
-// Preconditions: L->id[0..M) holds the candidates; with have_dp also L->dp[0..M), the candidates being in
-// (distance, id) order.  M + (binary16 && !have_dp ? 1 : 0) <= 32 * NT.  Returns the number selected
-// (L->sel_id / L->sel_dist, distance bits as float32).
-template <int DT, int NT>
-__device__ __forceinline__ int gram_prune_wave(const uint8_t* recs, size_t stride, int vec_bytes, GramLds* L, int M, uint32_t p,
-                                               bool have_dp, int R, float alpha) {
-    constexpr int NTILE = NT * (NT + 1) / 2;
-    const int lane = lane_id(), col = lane & 31, half = lane >> 5;
-    const bool extra = (DT != JX_F32) && !have_dp;
-    const int Mx = M + (extra ? 1 : 0);
-    const uint8_t* rp[NT];
-    bool rv[NT];
-    const uint8_t* pp = recs + (size_t)p * stride;
-#pragma unroll
-    for (int b = 0; b < NT; b++) {
-        const int i = b * 32 + col;
-        rv[b] = i < Mx;
-        const uint32_t id = i < M ? L->id[i] : p;
-        rp[b] = recs + (size_t)id * stride;
+// L->id[0..m): n_fixed candidates of unknown distance to p, then candidates in ascending (distance, id) order with their
+// distances in L->dp.  truncated: further candidates, none before the last one here, exist beyond the pool.  All threads
+// of the workgroup call; the arrays are visible (a barrier after they were filled).  Returns the number selected
+// (L->sel_id / L->sel_dist, visible to all), or -1 if the pool did not suffice.
+template <int DT, int NB>
+__device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, int vec_bytes, TeamLds<DT, NB>* L, int m, int n_fixed,
+                                          uint32_t p, int R, float alpha, bool truncated) {
+    using Lds = TeamLds<DT, NB>;
+    constexpr int TILES = NB / 2 + 1;
+    constexpr int BLOCK = Lds::PIECES * GT_PIECE;
+    const int tid = threadIdx.x;
+    int lane = lane_id();
+    asm volatile("" : "+v"(lane));  // what follows from it is worked out here and not kept across a caller's loop: no registers for that
+    const int col = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nb = (m + 31) >> 5;
+    const bool mine = wave < nb;
+    if (tid < 32 * nb) {
+        L->rank[tid] = tid < m ? (uint32_t)tid : 0xFFFFu;
+        if (tid >= m) L->dp[tid] = -1.f;
     }
-    typename GAcc<DT>::type acc[NTILE];
+    typename GAcc<DT>::type acc[TILES];
 #pragma unroll
-    for (int t = 0; t < NTILE; t++)
+    for (int t = 0; t < TILES; t++)
 #pragma unroll
         for (int e = 0; e < 16; e++) acc[t][e] = 0;
-
-    for (int p0 = 0; p0 < vec_bytes; p0 += 128) {
-        const int off = p0 + half * 64;
-        if constexpr (DT == JX_U8) {
-            uint4 f[NT][4];
+    // staging: a load covers 8 rows x 128 bytes
+    const int piece = lane & 7, r8 = lane >> 3;
+    const uint8_t* rp[4];
+    const uint8_t* pp = recs + (size_t)p * stride + piece * 16;
 #pragma unroll
-            for (int b = 0; b < NT; b++)
-#pragma unroll
-                for (int s = 0; s < 4; s++) {
-                    const int o = off + s * 16;
-                    f[b][s] = make_uint4(0, 0, 0, 0);  // rows and bytes beyond the data: zero after the shift
-                    if (rv[b] && o < vec_bytes) f[b][s] = shift128(load16(rp[b] + o));
-                }
-#pragma unroll
-            for (int s = 0; s < 4; s++)
-#pragma unroll
-                for (int bi = 0; bi < NT; bi++)
-#pragma unroll
-                    for (int bj = bi; bj < NT; bj++)
-                        acc[gp_tile(NT, bi, bj)] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                            __builtin_bit_cast(gi32x4_t, f[bi][s]), __builtin_bit_cast(gi32x4_t, f[bj][s]),
-                            acc[gp_tile(NT, bi, bj)], 0, 0, 0);
-        } else if constexpr (DT == JX_F32) {
-            float f[NT][16];
-            float c[16];
-#pragma unroll
-            for (int s = 0; s < 4; s++) {
-                const int o = off + s * 16;
-                uint4 x = make_uint4(0, 0, 0, 0);
-                if (o < vec_bytes) x = load16(pp + o);
-                c[4 * s + 0] = __uint_as_float(x.x);
-                c[4 * s + 1] = __uint_as_float(x.y);
-                c[4 * s + 2] = __uint_as_float(x.z);
-                c[4 * s + 3] = __uint_as_float(x.w);
-            }
-#pragma unroll
-            for (int b = 0; b < NT; b++)
-#pragma unroll
-                for (int s = 0; s < 4; s++) {
-                    const int o = off + s * 16;
-                    uint4 x = make_uint4(0, 0, 0, 0);
-                    if (o < vec_bytes) x = load16(rp[b] + o);  // rows beyond the last candidate point at p: they centre to zero
-                    f[b][4 * s + 0] = __uint_as_float(x.x) - c[4 * s + 0];
-                    f[b][4 * s + 1] = __uint_as_float(x.y) - c[4 * s + 1];
-                    f[b][4 * s + 2] = __uint_as_float(x.z) - c[4 * s + 2];
-                    f[b][4 * s + 3] = __uint_as_float(x.w) - c[4 * s + 3];
-                }
-#pragma unroll
-            for (int e = 0; e < 16; e++)
-#pragma unroll
-                for (int bi = 0; bi < NT; bi++)
-#pragma unroll
-                    for (int bj = bi; bj < NT; bj++)
-                        acc[gp_tile(NT, bi, bj)] =
-                            __builtin_amdgcn_mfma_f32_32x32x2f32(f[bi][e], f[bj][e], acc[gp_tile(NT, bi, bj)], 0, 0, 0);
-        } else {
-            uint4 f[NT][4];
-#pragma unroll
-            for (int b = 0; b < NT; b++)
-#pragma unroll
-                for (int s = 0; s < 4; s++) {
-                    const int o = off + s * 16;
-                    f[b][s] = make_uint4(0, 0, 0, 0);
-                    if (rv[b] && o < vec_bytes) f[b][s] = load16(rp[b] + o);
-                }
-#pragma unroll
-            for (int s = 0; s < 4; s++)
-#pragma unroll
-                for (int bi = 0; bi < NT; bi++)
-#pragma unroll
-                    for (int bj = bi; bj < NT; bj++)
-                        acc[gp_tile(NT, bi, bj)] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                            __builtin_bit_cast(f16x8_t, f[bi][s]), __builtin_bit_cast(f16x8_t, f[bj][s]),
-                            acc[gp_tile(NT, bi, bj)], 0, 0, 0);
-        }
+    for (int s = 0; s < 4; s++) {
+        const int slot = wave * 32 + s * 8 + r8;
+        rp[s] = recs + (size_t)(slot < m ? L->id[slot] : p) * stride + piece * 16;
     }
-
-    // Accumulator layout of the 32x32 tiles: register e of lane (col, half) holds row 8*(e/4) + 4*half + e%4, column col.
-    // ---- G_jj from the diagonal tiles
-    {
-        const int hcol = (col >> 2) & 1, ecol = ((col >> 3) << 2) | (col & 3);
+    float fnn[4] = {0.f, 0.f, 0.f, 0.f}, fnp[4] = {0.f, 0.f, 0.f, 0.f}, fpp = 0.f;
+    int inn[4] = {0, 0, 0, 0}, inp[4] = {0, 0, 0, 0}, ipp = 0;
+    const bool want_dp = DT != JX_F32 && mine && wave * 32 < n_fixed;
+    uint8_t* own = L->slab + (size_t)wave * BLOCK;
+    uint4 x[4], c;
+    auto fetch = [&](int p0) {
+        if (p0 + 128 <= vec_bytes) {  // uniform: no lane's load waits for a branch
+            c = load16(pp + p0);
 #pragma unroll
-        for (int b = 0; b < NT; b++) {
-            float dv = 0.f;
-#pragma unroll
-            for (int e = 0; e < 16; e++)
-                if (e == ecol) dv = gram_store<DT>(acc[gp_tile(NT, b, b)][e]);
-            if (half == hcol) L->nrm[b * 32 + col] = dv;
-        }
-    }
-    // ---- binary16 without known distances: column of the extra row p (slot M)
-    if (extra) {
-        const int bv = M >> 5, cv = M & 31;
-#pragma unroll
-        for (int bi = 0; bi < NT; bi++)
-#pragma unroll
-            for (int bj = bi; bj < NT; bj++)
-                if (bj == bv && col == cv) {
-#pragma unroll
-                    for (int e = 0; e < 16; e++)
-                        L->gv[bi * 32 + 8 * (e >> 2) + 4 * half + (e & 3)] = gram_store<DT>(acc[gp_tile(NT, bi, bj)][e]);
-                }
-    }
-    wave_sync();
-    if (!have_dp) {
-        for (int j = lane; j < M; j += 64) {
-            float d;
-            if constexpr (DT == JX_F32)
-                d = L->nrm[j];
-            else if constexpr (DT == JX_U8)
-                d = gram_dist<DT>(L->nrm[M], L->nrm[j], __float_as_int(L->gv[j]));
-            else
-                d = gram_dist<DT>(L->nrm[M], L->nrm[j], L->gv[j]);
-            L->dp[j] = d;
-            L->key[j] = ((uint64_t)__float_as_uint(d) << 32) | L->id[j];
-        }
-        wave_sync();
-        for (int j = lane; j < M; j += 64) {
-            const uint64_t k = L->key[j];
-            int rank = 0;
-            for (int t = 0; t < M; t++) {
-                const uint64_t o = L->key[t];
-                rank += (o < k || (o == k && t < j)) ? 1 : 0;
-            }
-            L->order[rank] = (uint8_t)j;
-        }
-    } else {
-        for (int j = lane; j < M; j += 64) L->order[j] = (uint8_t)j;
-    }
-    wave_sync();
-    // ---- the discard relation, tile by tile
-#pragma unroll
-    for (int bi = 0; bi < NT; bi++)
-#pragma unroll
-        for (int bj = bi; bj < NT; bj++) {
-            const int j = bj * 32 + col;
-            const float nj = L->nrm[j];
-            const float dpj = L->dp[j < M ? j : 0];
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int r0 = bi * 32 + 8 * (e >> 2) + (e & 3);
-                const int i = r0 + 4 * half;
-                const float ni = L->nrm[i];
-                const float dpi = L->dp[i < M ? i : 0];
-                const float dij = gram_dist<DT>(ni, nj, acc[gp_tile(NT, bi, bj)][e]);
-                const float ad = __fmul_rn(alpha, dij);
-                const bool ok = i < M && j < M && i != j;
-                const uint64_t m1 = ballot(ok && ad <= dpj);
-                if (lane == 0) {
-                    L->kill[r0 * 4 + bj] = (uint32_t)m1;
-                    L->kill[(r0 + 4) * 4 + bj] = (uint32_t)(m1 >> 32);
-                }
-                if (bi != bj) {
-                    const uint64_t m2 = ballot(ok && ad <= dpi);
-                    if (lane == 0) {
-                        L->kb[r0 * 4 + bj] = (uint32_t)m2;
-                        L->kb[(r0 + 4) * 4 + bj] = (uint32_t)(m2 >> 32);
-                    }
-                }
-            }
-        }
-    wave_sync();
-    // ---- Alg. 3: candidates in (distance, id) order; a candidate is gone if a selected one discards it
-    uint32_t A[4], S[4];
-#pragma unroll
-    for (int t = 0; t < 4; t++) {
-        const int rem = M - 32 * t;
-        A[t] = rem >= 32 ? 0xFFFFFFFFu : (rem <= 0 ? 0u : ((1u << rem) - 1u));
-        S[t] = 0u;
-    }
-    int nsel = 0;
-    for (int r = 0; r < M && nsel < R; r++) {
-        const int c = L->order[r];
-        const int w = c >> 5;
-        const uint32_t bit = 1u << (c & 31);
-        uint32_t aw = 0u;
-#pragma unroll
-        for (int t = 0; t < 4; t++)
-            if (t == w) aw = A[t];
-        if (!(aw & bit)) continue;
-        const uint32_t cid = L->id[c];
-        if (cid == p) continue;
-        bool gone = false;
-#pragma unroll
-        for (int t = 1; t < NT; t++)
-            if (t > w) gone = gone || (L->kb[c * 4 + t] & S[t]) != 0u;
-        if (gone) continue;
-        if (lane == 0) {
-            L->sel_id[nsel] = cid;
-            L->sel_dist[nsel] = __float_as_uint(L->dp[c]);
-        }
-        nsel++;
-#pragma unroll
-        for (int t = 0; t < NT; t++) {
-            if (t == w) S[t] |= bit;
-            if (t >= w) A[t] &= ~L->kill[c * 4 + t];
-        }
-    }
-    wave_sync();
-    return nsel;
-}
-
-// ---- forward prune of the final frontier of each new point (Alg. 4 step 2)
-template <int DT, int NT>
-__global__ void __launch_bounds__(GP_WPB * 64) forward_prune_gram_kernel(InsertArgs a) {
-    __shared__ GramLds lds[GP_WPB];
-    const int wave = threadIdx.x >> 6, lane = lane_id();
-    const long long i = (long long)blockIdx.x * GP_WPB + wave;
-    if (i >= a.B) return;
-    GramLds* L = &lds[wave];
-    long long xid = a.id_base + i;
-    if (xid >= a.id_skip) xid++;
-    const uint32_t* ids = a.cand_ids + (size_t)i * a.L;
-    const uint32_t* dbits = a.cand_dist + (size_t)i * a.L;
-    int nB = 0;
-    for (int c0 = 0; c0 < a.L; c0 += 64) {
-        const int j = c0 + lane;
-        const bool valid = j < a.L && ids[j] != JX_NONE_ID;  // the frontier is filled from the left
-        nB += __builtin_popcountll(ballot(valid));
-    }
-    if (nB > GP_MAX) return;  // left to the list-based kernel
-    const int nt = nB <= 64 ? 2 : (nB + 31) >> 5;
-    if (nt != NT) return;  // another instantiation's share
-    for (int j = lane; j < nB; j += 64) {
-        L->id[j] = ids[j];
-        L->dp[j] = __uint_as_float(dbits[j]);
-    }
-    wave_sync();
-    const int nsel = gram_prune_wave<DT, NT>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, nB, (uint32_t)xid, true, a.R, a.alpha);
-    uint32_t* row = a.adj + (size_t)xid * a.R;
-    for (int j = lane; j < a.R; j += 64) {
-        const bool on = j < nsel;
-        const uint32_t v = on ? L->sel_id[j] : JX_NONE_ID;
-        row[j] = v;
-        a.keys[(size_t)i * a.R + j] = on ? (((uint64_t)v << 32) | L->sel_dist[j]) : JX_EMPTY_KEY;
-        a.vals[(size_t)i * a.R + j] = on ? (uint32_t)xid : JX_NONE_ID;
-    }
-    if (a.clean && lane == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
-}
-
-// ---- reverse-edge merge (Alg. 4 step 3): the targets whose row overflows and whose candidates fit 128 slots
-template <int DT, int NT>
-__global__ void __launch_bounds__(GP_WPB * 64) reverse_merge_gram_kernel(InsertArgs a) {
-    __shared__ GramLds lds[GP_WPB];
-    const int wave = threadIdx.x >> 6, lane = lane_id();
-    GramLds* L = &lds[wave];
-    const long long nseg = *a.nseg;
-    const long long total = a.E ? a.E : a.B * a.R;
-    for (long long s = (long long)blockIdx.x * GP_WPB + wave; s < nseg; s += (long long)gridDim.x * GP_WPB) {
-        const uint32_t head = a.heads[s];
-        if (head & 0x80000000u) continue;  // already merged by another instantiation
-        const long long lo = head;
-        const uint32_t v = (uint32_t)(a.keys[lo] >> 32);
-        if (v == JX_NONE_ID) continue;
-        int m = 0;
-        for (long long c0 = lo; c0 < total; c0 += 64) {
-            const long long j = c0 + lane;
-            const bool same = j < total && (uint32_t)(a.keys[j] >> 32) == v;
-            const uint64_t sm = ballot(same);
-            m += __builtin_popcountll(sm);
-            if (sm != ~0ull) break;
-        }
-        uint32_t* row = a.adj + (size_t)v * a.R;
-        int deg = 0;
-        for (int rb = 0; rb < a.R; rb += 64) {
-            const bool on = rb + lane < a.R && row[rb + lane] != JX_NONE_ID;
-            deg += __builtin_popcountll(ballot(on));
-        }
-        if (a.force_prune) deg = 0;
-        if (!a.force_prune && deg + m <= a.R) continue;  // appended by the list-based kernel
-        const int M = deg + m;
-        const int Mx = M + (DT != JX_F32 ? 1 : 0);
-        if (Mx > GP_MAX) continue;  // left to the list-based kernel
-        const int nt = Mx <= 64 ? 2 : (Mx + 31) >> 5;
-        if (nt != NT) continue;
-        for (int j = lane; j < deg; j += 64) L->id[j] = row[j];
-        for (int j = lane; j < m; j += 64) L->id[deg + j] = a.vals[lo + j];
-        wave_sync();
-        const int nsel = gram_prune_wave<DT, NT>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, M, v, false, a.R, a.alpha);
-        for (int j = lane; j < a.R; j += 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
-        if (a.clean && lane == 0) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
-        // the row has changed, so degree and overflow can no longer be derived from it: mark the segment as done
-        if (lane == 0) const_cast<uint32_t*>(a.heads)[s] = head | 0x80000000u;
-        wave_sync();
-    }
-}
-
-
-// ---- more than 128 candidates: the same contraction, one block row of tiles at a time --------------------------
-// Eight 32-row blocks make 36 upper-triangle tiles, too many accumulators for one pass, and only the bit masks of
-// the relation have to survive a tile.  So the wavefront walks the block rows: for block row bi it accumulates the
-// tiles (bi, bi .. nb-1) over the whole vector length, turns them into mask words, and moves on; a block is read
-// (nb - bi) + 1 times instead of once, still far less than the list-based form reads.  G_jj (and G_jp for
-// binary16) are needed for columns of later blocks, so a first pass over the vectors computes them with plain
-// fused multiply-adds.
-// Beyond 256 candidates only a prefix is taken: Alg. 3 visits candidates in (distance, id) order and stops at R
-// selections, and what happens to a candidate depends on earlier ones only.  The pool is the existing neighbours
-// plus the closest new candidates (the new list arrives sorted) up to 256 rows; if the walk selects R neighbours
-// before it meets a pool member beyond the last included new candidate, the excluded ones could not have mattered
-// and the result is exact.  Otherwise the segment is left to the list-based kernel.
-#define GB_MAX 256
-#define GB_NB 8
-
-struct GramBigLds {
-    uint64_t key[GB_MAX];
-    uint32_t id[GB_MAX];
-    float dp[GB_MAX];
-    float nrm[GB_MAX];
-    uint32_t kill[GB_MAX * GB_NB];
-    uint32_t kb[GB_MAX * GB_NB];
-    uint32_t sel_id[GB_MAX];
-    uint32_t sel_dist[GB_MAX];  // float bits of d(p, selected), selection order
-    uint16_t order[GB_MAX];
-};
-
-// L->id[0..M): n_fixed existing neighbours, then new candidates, ascending, whose distances to p are the low words of
-// new_keys[0..M-n_fixed) (edge keys) or, if new_keys is null, new_dbits[0..M-n_fixed) (float bits).  truncated: further
-// new candidates exist beyond the pool.  Returns the number selected, or -1 if the pool did not suffice.
-template <int DT>
-__device__ __forceinline__ int gram_prune_big(const uint8_t* recs, size_t stride, int vec_bytes, GramBigLds* L, int M, uint32_t p,
-                                              int R, float alpha, int n_fixed, const uint64_t* new_keys, bool truncated,
-                                              const uint32_t* new_dbits = nullptr) {
-    const int lane = lane_id(), col = lane & 31, half = lane >> 5;
-    const int nb = (M + 31) >> 5;
-    const uint8_t* pp = recs + (size_t)p * stride;
-    // ---- pass 1: d(p, j) and G_jj.  float32: rows centred at p, so both are the same number
-    float npp = 0.f;
-    int ipp = 0;
-    if constexpr (DT != JX_F32) {
-        for (int p0 = half * 64; p0 < vec_bytes; p0 += 128)
-#pragma unroll
-            for (int s = 0; s < 4; s++) {
-                const int o = p0 + s * 16;
-                if (o < vec_bytes) {
-                    if constexpr (DT == JX_F16) {
-                        const uint4 x = load16(pp + o);
-                        npp = hdot2(x.x, x.x, npp);
-                        npp = hdot2(x.y, x.y, npp);
-                        npp = hdot2(x.z, x.z, npp);
-                        npp = hdot2(x.w, x.w, npp);
-                    } else {
-                        const uint4 x = shift128(load16(pp + o));
-                        ipp = __builtin_amdgcn_sdot4((int)x.x, (int)x.x, ipp, false);
-                        ipp = __builtin_amdgcn_sdot4((int)x.y, (int)x.y, ipp, false);
-                        ipp = __builtin_amdgcn_sdot4((int)x.z, (int)x.z, ipp, false);
-                        ipp = __builtin_amdgcn_sdot4((int)x.w, (int)x.w, ipp, false);
-                    }
-                }
-            }
-        npp += shfl_xor(npp, 32);
-        ipp += shfl_xor(ipp, 32);
-    }
-    for (int b = 0; b < nb; b++) {
-        const int i = b * 32 + col;
-        const uint8_t* rp = recs + (size_t)(i < M ? L->id[i] : p) * stride;
-        float nn = 0.f, np = 0.f;
-        int inn = 0, inp = 0;
-        for (int p0 = half * 64; p0 < vec_bytes; p0 += 128)
-#pragma unroll
-            for (int s = 0; s < 4; s++) {
-                const int o = p0 + s * 16;
-                if (o < vec_bytes) {
-                    uint4 x = load16(rp + o), c = load16(pp + o);
-                    if constexpr (DT == JX_F32) {
-                        const float d0 = __uint_as_float(x.x) - __uint_as_float(c.x), d1 = __uint_as_float(x.y) - __uint_as_float(c.y);
-                        const float d2 = __uint_as_float(x.z) - __uint_as_float(c.z), d3 = __uint_as_float(x.w) - __uint_as_float(c.w);
-                        nn = fmaf(d0, d0, nn);
-                        nn = fmaf(d1, d1, nn);
-                        nn = fmaf(d2, d2, nn);
-                        nn = fmaf(d3, d3, nn);
-                    } else if constexpr (DT == JX_F16) {
-                        nn = hdot2(x.x, x.x, nn);
-                        nn = hdot2(x.y, x.y, nn);
-                        nn = hdot2(x.z, x.z, nn);
-                        nn = hdot2(x.w, x.w, nn);
-                        np = hdot2(x.x, c.x, np);
-                        np = hdot2(x.y, c.y, np);
-                        np = hdot2(x.z, c.z, np);
-                        np = hdot2(x.w, c.w, np);
-                    } else {
-                        x = shift128(x);
-                        c = shift128(c);
-                        inn = __builtin_amdgcn_sdot4((int)x.x, (int)x.x, inn, false);
-                        inn = __builtin_amdgcn_sdot4((int)x.y, (int)x.y, inn, false);
-                        inn = __builtin_amdgcn_sdot4((int)x.z, (int)x.z, inn, false);
-                        inn = __builtin_amdgcn_sdot4((int)x.w, (int)x.w, inn, false);
-                        inp = __builtin_amdgcn_sdot4((int)x.x, (int)c.x, inp, false);
-                        inp = __builtin_amdgcn_sdot4((int)x.y, (int)c.y, inp, false);
-                        inp = __builtin_amdgcn_sdot4((int)x.z, (int)c.z, inp, false);
-                        inp = __builtin_amdgcn_sdot4((int)x.w, (int)c.w, inp, false);
-                    }
-                }
-            }
-        nn += shfl_xor(nn, 32);
-        np += shfl_xor(np, 32);
-        inn += shfl_xor(inn, 32);
-        inp += shfl_xor(inp, 32);
-        if (half == 0) {
-            float d = nn, nstore = nn;
-            if constexpr (DT == JX_F16) d = fmaxf(npp + nn - 2.f * np, 0.f);
+            for (int s = 0; s < 4; s++) x[s] = load16(rp[s] + p0);
             if constexpr (DT == JX_U8) {
-                d = (float)(uint32_t)(ipp + inn - 2 * inp);
-                nstore = __int_as_float(inn);
+                c = shift128(c);
+#pragma unroll
+                for (int s = 0; s < 4; s++) x[s] = shift128(x[s]);
             }
-            L->nrm[i] = i < M ? nstore : 0.f;
-            // a new candidate keeps the distance it was sorted by
-            if (i >= n_fixed && i < M)
-                d = __uint_as_float(new_keys ? (uint32_t)(new_keys[i - n_fixed] & 0xFFFFFFFFull) : new_dbits[i - n_fixed]);
-            L->dp[i] = d;
-            if (i < M) L->key[i] = ((uint64_t)__float_as_uint(d) << 32) | L->id[i];
-        }
-    }
-    wave_sync();
-    for (int j = lane; j < M; j += 64) {
-        const uint64_t k = L->key[j];
-        int rank = 0;
-        for (int t = 0; t < M; t++) {
-            const uint64_t o = L->key[t];
-            rank += (o < k || (o == k && t < j)) ? 1 : 0;
-        }
-        L->order[rank] = (uint16_t)j;
-    }
-    // ---- pass 2: block rows of the Gram matrix -> mask words
-    for (int bi = 0; bi < nb; bi++) {
-        typename GAcc<DT>::type acc[GB_NB];
+        } else {  // the last piece of a row: zeros (after the shift) beyond the data
+            const bool in = p0 + piece * 16 < vec_bytes;
+            const uint4 zero = make_uint4(0, 0, 0, 0);
+            c = in ? load16(pp + p0) : zero;
 #pragma unroll
-        for (int t = 0; t < GB_NB; t++)
+            for (int s = 0; s < 4; s++) x[s] = in ? load16(rp[s] + p0) : zero;
+            if (DT == JX_U8 && in) {
+                c = shift128(c);
 #pragma unroll
-            for (int e = 0; e < 16; e++) acc[t][e] = 0;
-        const uint8_t* rp[GB_NB];
-        bool rv[GB_NB];
-#pragma unroll
-        for (int t = 0; t < GB_NB; t++) {
-            const int i = (bi + t) * 32 + col;
-            rv[t] = i < M;
-            rp[t] = recs + (size_t)(i < M ? L->id[i] : p) * stride;
+                for (int s = 0; s < 4; s++) x[s] = shift128(x[s]);
+            }
         }
-        for (int p0 = 0; p0 < vec_bytes; p0 += 128) {
-            const int off = p0 + half * 64;
+    };
+    if (mine) fetch(0);
+    for (int p0 = 0; p0 < vec_bytes; p0 += 128) {
+        if (mine) {
             if constexpr (DT == JX_F32) {
-                float c[16], fa[16];
+                uint8_t* at = own + (((piece >> 2) * 6 + ((piece >> 1) & 1)) * GT_PIECE) + (piece & 1) * 8 + r8 * 16;
 #pragma unroll
                 for (int s = 0; s < 4; s++) {
-                    const int o = off + s * 16;
-                    uint4 x = make_uint4(0, 0, 0, 0), y = x;
-                    if (o < vec_bytes) {
-                        x = load16(pp + o);
-                        y = load16(rp[0] + o);
+                    float v0 = __uint_as_float(x[s].x) - __uint_as_float(c.x), v1 = __uint_as_float(x[s].y) - __uint_as_float(c.y);
+                    float v2 = __uint_as_float(x[s].z) - __uint_as_float(c.z), v3 = __uint_as_float(x[s].w) - __uint_as_float(c.w);
+#pragma unroll
+                    for (int part = 0; part < 3; part++) {
+                        uint2 h;
+                        h.x = take_bf16(v0, v1);
+                        h.y = take_bf16(v2, v3);
+                        *reinterpret_cast<uint2*>(at + part * 2 * GT_PIECE + s * 128) = h;
                     }
-                    c[4 * s + 0] = __uint_as_float(x.x);
-                    c[4 * s + 1] = __uint_as_float(x.y);
-                    c[4 * s + 2] = __uint_as_float(x.z);
-                    c[4 * s + 3] = __uint_as_float(x.w);
-                    fa[4 * s + 0] = __uint_as_float(y.x) - c[4 * s + 0];
-                    fa[4 * s + 1] = __uint_as_float(y.y) - c[4 * s + 1];
-                    fa[4 * s + 2] = __uint_as_float(y.z) - c[4 * s + 2];
-                    fa[4 * s + 3] = __uint_as_float(y.w) - c[4 * s + 3];
-                }
-#pragma unroll
-                for (int t = 0; t < GB_NB; t++) {
-                    if (bi + t >= nb) break;  // uniform
-                    float fb[16];
-                    if (t == 0) {
-#pragma unroll
-                        for (int e = 0; e < 16; e++) fb[e] = fa[e];
-                    } else {
-#pragma unroll
-                        for (int s = 0; s < 4; s++) {
-                            const int o = off + s * 16;
-                            uint4 y = make_uint4(0, 0, 0, 0);
-                            if (o < vec_bytes) y = load16(rp[t] + o);  // rows beyond M point at p and centre to zero
-                            fb[4 * s + 0] = __uint_as_float(y.x) - c[4 * s + 0];
-                            fb[4 * s + 1] = __uint_as_float(y.y) - c[4 * s + 1];
-                            fb[4 * s + 2] = __uint_as_float(y.z) - c[4 * s + 2];
-                            fb[4 * s + 3] = __uint_as_float(y.w) - c[4 * s + 3];
-                        }
-                    }
-#pragma unroll
-                    for (int e = 0; e < 16; e++) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[e], fb[e], acc[t], 0, 0, 0);
                 }
             } else {
-                uint4 fa[4];
 #pragma unroll
-                for (int s = 0; s < 4; s++) {
-                    const int o = off + s * 16;
-                    fa[s] = make_uint4(0, 0, 0, 0);
-                    if (rv[0] && o < vec_bytes) fa[s] = DT == JX_U8 ? shift128(load16(rp[0] + o)) : load16(rp[0] + o);
-                }
+                for (int s = 0; s < 4; s++) *reinterpret_cast<uint4*>(own + piece * GT_PIECE + (s * 8 + r8) * 16) = x[s];
+                if (want_dp) {
+                    if constexpr (DT == JX_F16) {
+                        fpp = hdot2(c.w, c.w, hdot2(c.z, c.z, hdot2(c.y, c.y, hdot2(c.x, c.x, fpp))));
 #pragma unroll
-                for (int t = 0; t < GB_NB; t++) {
-                    if (bi + t >= nb) break;  // uniform
-                    uint4 fb[4];
+                        for (int s = 0; s < 4; s++) {
+                            fnn[s] = hdot2(x[s].w, x[s].w, hdot2(x[s].z, x[s].z, hdot2(x[s].y, x[s].y, hdot2(x[s].x, x[s].x, fnn[s]))));
+                            fnp[s] = hdot2(x[s].w, c.w, hdot2(x[s].z, c.z, hdot2(x[s].y, c.y, hdot2(x[s].x, c.x, fnp[s]))));
+                        }
+                    } else {
+                        auto dot = [](const uint4& a, const uint4& b, int t) {
+                            t = __builtin_amdgcn_sdot4((int)a.x, (int)b.x, t, false);
+                            t = __builtin_amdgcn_sdot4((int)a.y, (int)b.y, t, false);
+                            t = __builtin_amdgcn_sdot4((int)a.z, (int)b.z, t, false);
+                            return __builtin_amdgcn_sdot4((int)a.w, (int)b.w, t, false);
+                        };
+                        ipp = dot(c, c, ipp);
 #pragma unroll
-                    for (int s = 0; s < 4; s++) {
-                        const int o = off + s * 16;
-                        fb[s] = fa[s];
-                        if (t > 0) {
-                            fb[s] = make_uint4(0, 0, 0, 0);
-                            if (rv[t] && o < vec_bytes) fb[s] = DT == JX_U8 ? shift128(load16(rp[t] + o)) : load16(rp[t] + o);
+                        for (int s = 0; s < 4; s++) {
+                            inn[s] = dot(x[s], x[s], inn[s]);
+                            inp[s] = dot(x[s], c, inp[s]);
                         }
                     }
+                }
+            }
+            if (p0 + 128 < vec_bytes) fetch(p0 + 128);
+        }
+        __syncthreads();
+        if (mine) {
+            const uint8_t* opnd = L->slab + half * GT_PIECE + col * 16;
+            if constexpr (DT == JX_F32) {
+                bf16x8_t a[2][3];
 #pragma unroll
-                    for (int s = 0; s < 4; s++) {
-                        if constexpr (DT == JX_U8)
-                            acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(gi32x4_t, fa[s]),
-                                                                           __builtin_bit_cast(gi32x4_t, fb[s]), acc[t], 0, 0, 0);
-                        else
-                            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, fa[s]),
-                                                                            __builtin_bit_cast(f16x8_t, fb[s]), acc[t], 0, 0, 0);
+                for (int q = 0; q < 6; q++)
+                    a[q / 3][q % 3] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)wave * BLOCK + q * 2 * GT_PIECE);
+#pragma unroll
+                for (int t = 0; t < TILES; t++) {
+                    if (2 * t < nb || t == 0 || (2 * t == nb && wave < t)) {  // uniform
+                        const int bj = wave + t < nb ? wave + t : wave + t - nb;
+                        // a sum of its own for the 32 coordinates of the slab, the smallest products first
+                        f32x16_t part;
+#pragma unroll
+                        for (int e = 0; e < 16; e++) part[e] = 0.f;
+#pragma unroll
+                        for (int ks = 0; ks < 2; ks++) {
+                            bf16x8_t b[3];
+#pragma unroll
+                            for (int q = 0; q < 3; q++)
+                                b[q] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)bj * BLOCK + (ks * 3 + q) * 2 * GT_PIECE);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][2], b[0], part, 0, 0, 0);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[2], part, 0, 0, 0);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[1], part, 0, 0, 0);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[0], part, 0, 0, 0);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[1], part, 0, 0, 0);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[0], part, 0, 0, 0);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 16; e++) acc[t][e] += part[e];
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < 4; ks++) {
+                    const uint4 a = *reinterpret_cast<const uint4*>(opnd + (size_t)wave * BLOCK + ks * 2 * GT_PIECE);
+#pragma unroll
+                    for (int t = 0; t < TILES; t++) {
+                        if (2 * t < nb || t == 0 || (2 * t == nb && wave < t)) {  // uniform
+                            const int bj = wave + t < nb ? wave + t : wave + t - nb;
+                            const uint4 b = *reinterpret_cast<const uint4*>(opnd + (size_t)bj * BLOCK + ks * 2 * GT_PIECE);
+                            if constexpr (DT == JX_U8)
+                                acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(gi32x4_t, a), __builtin_bit_cast(gi32x4_t, b),
+                                                                               acc[t], 0, 0, 0);
+                            else
+                                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b),
+                                                                                acc[t], 0, 0, 0);
+                        }
                     }
                 }
             }
         }
-        // masks of this block row
+        __syncthreads();
+    }
+    // Accumulator layout of the 32x32 tiles: register e of lane (col, half) holds row 8*(e/4) + 4*half + e%4, column col.
+    // ---- G_jj from the diagonal tiles, d(p, j) of the candidates that came without
+    if (mine) {
+        const int hcol = (col >> 2) & 1, ecol = ((col >> 3) << 2) | (col & 3);
+        float dv = 0.f;
 #pragma unroll
-        for (int t = 0; t < GB_NB; t++) {
-            if (bi + t >= nb) break;
-            const int bj = bi + t;
-            const int j = bj * 32 + col;
-            const float nj = L->nrm[j], dpj = L->dp[j];
+        for (int e = 0; e < 16; e++)
+            if (e == ecol) {
+                if constexpr (DT == JX_U8)
+                    dv = __int_as_float(acc[0][e]);
+                else
+                    dv = acc[0][e];
+            }
+        if (half == hcol) {
+            L->nrm[wave * 32 + col] = dv;
+            if (DT == JX_F32 && wave * 32 + col < n_fixed) L->dp[wave * 32 + col] = dv;
+        }
+        if (want_dp) {
+            if constexpr (DT == JX_F16) fpp = group_sum<8>(fpp);
+            if constexpr (DT == JX_U8) ipp = group_sum<8>(ipp);
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int r0 = bi * 32 + 8 * (e >> 2) + (e & 3);
-                const int i = r0 + 4 * half;
-                const float ni = L->nrm[i], dpi = L->dp[i];
-                const float dij = gram_dist<DT>(ni, nj, acc[t][e]);
-                const float ad = __fmul_rn(alpha, dij);
-                const bool ok = i < M && j < M && i != j;
-                const uint64_t m1 = ballot(ok && ad <= dpj);
-                if (lane == 0) {
-                    L->kill[r0 * GB_NB + bj] = (uint32_t)m1;
-                    L->kill[(r0 + 4) * GB_NB + bj] = (uint32_t)(m1 >> 32);
+            for (int s = 0; s < 4; s++) {
+                float d = 0.f;
+                if constexpr (DT == JX_F16) d = fmaxf((fpp + group_sum<8>(fnn[s])) - 2.f * group_sum<8>(fnp[s]), 0.f);
+                if constexpr (DT == JX_U8) d = (float)(uint32_t)(ipp + group_sum<8>(inn[s]) - 2 * group_sum<8>(inp[s]));
+                const int slot = wave * 32 + s * 8 + r8;
+                if (piece == 0 && slot < n_fixed) L->dp[slot] = d;
+            }
+        }
+    }
+    __syncthreads();
+    if (n_fixed > 0) {
+        // ranks: the candidates of known distance are in order already
+        uint64_t k = 0;
+        if (tid < m) {
+            k = ((uint64_t)__float_as_uint(L->dp[tid]) << 32) | L->id[tid];
+            L->key[tid] = k;
+        }
+        __syncthreads();
+        if (tid < m) {
+            int rank = tid < n_fixed ? 0 : tid - n_fixed;
+            for (int t = 0; t < n_fixed; t++) {
+                const uint64_t o = L->key[t];
+                rank += (o < k || (o == k && t < tid)) ? 1 : 0;
+            }
+            if (tid < n_fixed) {
+                int lo = n_fixed, hi = m;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (L->key[mid] < k) lo = mid + 1;
+                    else hi = mid;
                 }
-                if (t > 0) {
-                    const uint64_t m2 = ballot(ok && ad <= dpi);
-                    if (lane == 0) {
-                        L->kb[r0 * GB_NB + bj] = (uint32_t)m2;
-                        L->kb[(r0 + 4) * GB_NB + bj] = (uint32_t)(m2 >> 32);
+                rank += lo - n_fixed;
+            }
+            L->rank[tid] = (uint32_t)rank;
+        }
+        __syncthreads();
+    }
+    // ---- the discard relation, tile by tile.  Candidates that came in order (n_fixed = 0) are discarded by those of their own
+    // block and of blocks before it only: half of it
+    const bool sorted = n_fixed == 0;
+    if (mine) {
+#pragma unroll
+        for (int t = 0; t < TILES; t++) {
+            if (2 * t < nb || t == 0 || (2 * t == nb && wave < t)) {  // uniform
+                const int bj = wave + t < nb ? wave + t : wave + t - nb;
+                const int j = bj * 32 + col;
+                const float nj = L->nrm[j], dpj = L->dp[j];
+                const uint32_t rj = L->rank[j];
+                const bool fwd = !sorted || wave <= bj, back = t > 0 && (!sorted || bj < wave);
+                uint32_t victim_j = 0, victim_i = 0;
+                if (fwd) {
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        const int i0 = wave * 32 + 8 * g + 4 * half;
+                        const float4 n4 = *reinterpret_cast<const float4*>(&L->nrm[i0]);
+                        const uint4 r4 = *reinterpret_cast<const uint4*>(&L->rank[i0]);
+                        const float ni[4] = {n4.x, n4.y, n4.z, n4.w};
+                        const uint32_t ri[4] = {r4.x, r4.y, r4.z, r4.w};
+#pragma unroll
+                        for (int f = 0; f < 4; f++) {
+                            const float ad = __fmul_rn(alpha, gram_dist<DT>(ni[f], nj, acc[t][4 * g + f]));
+                            if (ri[f] < rj && ad <= dpj) victim_j |= 1u << (8 * g + f);
+                        }
                     }
+                    victim_j <<= 4 * half;
+                    victim_j |= shfl_xor(victim_j, 32);
+                    if (half == 0) L->kb[wave * Lds::M + j] = victim_j;
+                }
+                if (back) {
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        const int i0 = wave * 32 + 8 * g + 4 * half;
+                        const float4 n4 = *reinterpret_cast<const float4*>(&L->nrm[i0]);
+                        const float4 d4 = *reinterpret_cast<const float4*>(&L->dp[i0]);
+                        const uint4 r4 = *reinterpret_cast<const uint4*>(&L->rank[i0]);
+                        const float ni[4] = {n4.x, n4.y, n4.z, n4.w}, di[4] = {d4.x, d4.y, d4.z, d4.w};
+                        const uint32_t ri[4] = {r4.x, r4.y, r4.z, r4.w};
+#pragma unroll
+                        for (int f = 0; f < 4; f++) {
+                            const float ad = __fmul_rn(alpha, gram_dist<DT>(ni[f], nj, acc[t][4 * g + f]));
+                            const uint64_t mi = ballot(rj < ri[f] && ad <= di[f]);
+                            const uint32_t row = (col & 4) ? (uint32_t)(mi >> 32) : (uint32_t)mi;  // of the lane's own row, if it is among these two
+                            if (4 * g + f == (((col >> 3) << 2) | (col & 3))) victim_i = row;
+                        }
+                    }
+                    if (half == 0) L->kb[bj * Lds::M + wave * 32 + col] = victim_i;
                 }
             }
         }
     }
-    wave_sync();
-    // ---- Alg. 3 on 256-bit masks
-    const uint64_t tau = truncated ? L->key[M - 1] : JX_EMPTY_KEY;  // the last new candidate of the pool
-    uint32_t A[GB_NB], S[GB_NB];
+    __syncthreads();
+    // ---- Alg. 3
+    if (wave == 0) {
+        constexpr int H = NB / 2;
+        uint32_t kw[H][NB];
+        uint64_t U[H], S[H];
 #pragma unroll
-    for (int t = 0; t < GB_NB; t++) {
-        const int rem = M - 32 * t;
-        A[t] = rem >= 32 ? 0xFFFFFFFFu : (rem <= 0 ? 0u : ((1u << rem) - 1u));
-        S[t] = 0u;
+        for (int h = 0; h < H; h++) {
+            const int slot = h * 64 + lane;
+            const bool on = slot < m;
+#pragma unroll
+            for (int w = 0; w < NB; w++) kw[h][w] = on && w < nb && (!sorted || w <= slot >> 5) ? L->kb[w * Lds::M + slot] : 0u;
+            U[h] = ballot(on && L->id[on ? slot : 0] != p);
+            S[h] = 0;
+            L->by_rank[slot] = JX_NONE_ID;
+        }
+        for (;;) {
+            uint64_t any = 0, ns[H], nd[H];
+#pragma unroll
+            for (int h = 0; h < H; h++) any |= U[h];
+            if (!any) break;
+#pragma unroll
+            for (int h = 0; h < H; h++) {
+                uint32_t dead = 0, wait = 0;
+#pragma unroll
+                for (int w = 0; w < NB; w++) {
+                    dead |= kw[h][w] & (uint32_t)(S[w >> 1] >> (32 * (w & 1)));
+                    wait |= kw[h][w] & (uint32_t)(U[w >> 1] >> (32 * (w & 1)));
+                }
+                ns[h] = ballot(dead == 0 && wait == 0) & U[h];
+                nd[h] = ballot(dead != 0) & U[h];
+            }
+#pragma unroll
+            for (int h = 0; h < H; h++) {
+                U[h] &= ~(ns[h] | nd[h]);
+                S[h] |= ns[h];
+            }
+        }
+        wave_sync();
+#pragma unroll
+        for (int h = 0; h < H; h++)
+            if ((S[h] >> lane) & 1ull) L->by_rank[L->rank[h * 64 + lane]] = (uint32_t)(h * 64 + lane);
+        wave_sync();
+        const int tau = (int)L->rank[m > 0 ? m - 1 : 0];
+        int nsel = 0, inside = 0;
+#pragma unroll
+        for (int h = 0; h < H; h++) {
+            const uint32_t slot = L->by_rank[h * 64 + lane];
+            const uint64_t on = ballot(slot != JX_NONE_ID);
+            const int pos = nsel + prefix_count(on);
+            if (slot != JX_NONE_ID && pos < R) {
+                L->sel_id[pos] = L->id[slot];
+                L->sel_dist[pos] = __float_as_uint(L->dp[slot]);
+            }
+            nsel += __builtin_popcountll(on);
+            inside += __builtin_popcountll(ballot(slot != JX_NONE_ID && h * 64 + lane <= tau));
+        }
+        // beyond the last candidate of known distance an excluded one could come first
+        if (lane == 0) L->nsel = truncated && inside < R ? -1 : (nsel < R ? nsel : R);
     }
-    int nsel = 0;
-    bool short_pool = truncated;  // cleared when R neighbours are found inside the prefix
-    for (int r = 0; r < M; r++) {
-        if (nsel >= R) {
-            short_pool = false;
-            break;
-        }
-        const int c = L->order[r];
-        if (truncated && L->key[c] > tau) break;  // beyond the prefix with room left: excluded candidates would matter
-        const int w = c >> 5;
-        const uint32_t bit = 1u << (c & 31);
-        uint32_t aw = 0u;
-#pragma unroll
-        for (int t = 0; t < GB_NB; t++)
-            if (t == w) aw = A[t];
-        if (!(aw & bit)) continue;
-        const uint32_t cid = L->id[c];
-        if (cid == p) continue;
-        bool gone = false;
-#pragma unroll
-        for (int t = 1; t < GB_NB; t++)
-            if (t > w && t < nb) gone = gone || (L->kb[c * GB_NB + t] & S[t]) != 0u;
-        if (gone) continue;
-        if (lane == 0) {
-            L->sel_id[nsel] = cid;
-            L->sel_dist[nsel] = __float_as_uint(L->dp[c]);
-        }
-        nsel++;
-#pragma unroll
-        for (int t = 0; t < GB_NB; t++) {
-            if (t == w) S[t] |= bit;
-            if (t >= w && t < nb) A[t] &= ~L->kill[c * GB_NB + t];
-        }
-    }
-    wave_sync();
-    if (nsel >= R) short_pool = false;
-    return short_pool ? -1 : nsel;
+    __syncthreads();
+    return L->nsel;
 }
 
-// ---- forward prune of candidate lists of 129 .. 256 entries, or of the closest 256 of a longer list (expansion
-// lists as candidate sets hold 150 - 200 vertices).  Every point of the batch gets a mark in a.dead[i * a.L]: 0xFF =
-// row and reverse edges written here, 0 = left to the list-based kernel (which also owns lists of at most 128, the
-// one-pass kernels' share).
-template <int DT>
-__global__ void __launch_bounds__(GP_WPB * 64) forward_prune_gram_big_kernel(InsertArgs a) {
-    extern __shared__ __align__(16) unsigned char gb_dyn[];
-    const int wave = threadIdx.x >> 6, lane = lane_id();
-    GramBigLds* L = reinterpret_cast<GramBigLds*>(gb_dyn) + wave;
-    const long long i = (long long)blockIdx.x * GP_WPB + wave;
-    if (i >= a.B) return;
+// ---- forward prune of the candidate list of each new point (Alg. 4 step 2): lists of at most 128 (NB = 4), or of 129 to
+// 256 and the closest 256 of a longer one (NB = 8; exact if Alg. 3 finds R neighbours in them).  NB = 8 marks every point
+// of the batch in a.dead[i * a.L]: 0xFF = row and reverse edges written here, 0 = left to the list-based kernel (which
+// leaves lists of at most 128 alone).
+template <int DT, int NB>
+__global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) forward_prune_gram_kernel(InsertArgs a) {
+    __shared__ TeamLds<DT, NB> lds;
+    TeamLds<DT, NB>* L = &lds;
+    const int tid = threadIdx.x, lane = lane_id();
+    const long long i = blockIdx.x;
     long long xid = a.id_base + i;
     if (xid >= a.id_skip) xid++;
     const uint32_t* ids = a.cand_ids + (size_t)i * a.L;
@@ -723,101 +457,140 @@ __global__ void __launch_bounds__(GP_WPB * 64) forward_prune_gram_big_kernel(Ins
         const bool valid = j < a.L && ids[j] != JX_NONE_ID;  // the list is filled from the left
         nB += __builtin_popcountll(ballot(valid));
     }
-    if (lane == 0) a.dead[(size_t)i * a.L] = 0;
-    if (nB <= GP_MAX) return;
-    const int M = nB < GB_MAX ? nB : GB_MAX;
-    for (int j = lane; j < M; j += 64) L->id[j] = ids[j];
-    wave_sync();
-    const int nsel = gram_prune_big<DT>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, M, (uint32_t)xid, a.R, a.alpha, 0, nullptr,
-                                        M < nB, dbits);
-    if (nsel < 0) return;  // the closest 256 did not yield R neighbours
+    if (NB == 8 && nB <= GT_SMALL && tid == 0) a.dead[(size_t)i * a.L] = 0;
+    if ((NB == 8) != (nB > GT_SMALL)) return;
+    const int m = nB < 32 * NB ? nB : 32 * NB;
+    for (int j = tid; j < m; j += NB * 64) {
+        L->id[j] = ids[j];
+        L->dp[j] = __uint_as_float(dbits[j]);
+    }
+    __syncthreads();
+    const int nsel = team_prune<DT, NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, m, 0, (uint32_t)xid, a.R, a.alpha, m < nB);
+    if (NB == 8 && tid == 0) a.dead[(size_t)i * a.L] = nsel < 0 ? 0 : 0xFF;
+    if (nsel < 0) return;
     uint32_t* row = a.adj + (size_t)xid * a.R;
-    for (int j = lane; j < a.R; j += 64) {
+    for (int j = tid; j < a.R; j += NB * 64) {
         const bool on = j < nsel;
         const uint32_t v = on ? L->sel_id[j] : JX_NONE_ID;
         row[j] = v;
         a.keys[(size_t)i * a.R + j] = on ? (((uint64_t)v << 32) | L->sel_dist[j]) : JX_EMPTY_KEY;
         a.vals[(size_t)i * a.R + j] = on ? (uint32_t)xid : JX_NONE_ID;
     }
-    if (a.clean && lane == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
-    if (lane == 0) a.dead[(size_t)i * a.L] = 0xFF;
+    if (a.clean && tid == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
 }
 
-template <int DT>
-__global__ void __launch_bounds__(GP_WPB * 64) reverse_merge_gram_big_kernel(InsertArgs a) {
-    extern __shared__ __align__(16) unsigned char gb_dyn[];
-    const int wave = threadIdx.x >> 6, lane = lane_id();
-    GramBigLds* L = reinterpret_cast<GramBigLds*>(gb_dyn) + wave;
+// ---- reverse-edge merge (Alg. 4 step 3)
+// A thread per segment: appends where the row still fits, and lists the others by size, so that no workgroup of the
+// kernels below spends a chain of dependent loads on a segment that is not its own.  An entry holds the segment, the
+// degree of its row and the number of new edges (at most 1,023 are told apart); lists[0..) is the list of the small
+// ones, lists[.. E - 1] downwards that of the large ones.
+__global__ void __launch_bounds__(256) reverse_class_kernel(InsertArgs a) {
+    const int lane = lane_id();
     const long long nseg = *a.nseg;
     const long long total = a.E ? a.E : a.B * a.R;
-    for (long long s = (long long)blockIdx.x * GP_WPB + wave; s < nseg; s += (long long)gridDim.x * GP_WPB) {
-        const uint32_t head = a.heads[s];
-        if (head & 0x80000000u) continue;
-        const long long lo = head;
+    for (long long s0 = (long long)blockIdx.x * 256; s0 < nseg; s0 += (long long)gridDim.x * 256) {
+        const long long s = s0 + threadIdx.x;
+        int cls = 0;
+        uint64_t entry = 0;
+        if (s < nseg) {
+            const long long lo = a.heads[s];
+            const uint32_t v = (uint32_t)(a.keys[lo] >> 32);
+            long long known = 1, step = 1;  // keys[lo .. lo + known) belong to v
+            while (lo + known + step - 1 < total && (uint32_t)(a.keys[lo + known + step - 1] >> 32) == v) {
+                known += step;
+                step *= 2;
+            }
+            long long end = known + step - 1 < total - lo ? known + step - 1 : total - lo;
+            while (known < end) {
+                const long long mid = (known + end) >> 1;
+                if ((uint32_t)(a.keys[lo + mid] >> 32) == v) known = mid + 1;
+                else end = mid;
+            }
+            const long long m = known;
+            uint32_t* row = a.adj + (size_t)v * a.R;
+            int deg = 0;
+            if (!a.force_prune) {
+                int hi = a.R;
+                while (deg < hi) {  // the row is filled from the left
+                    const int mid = (deg + hi) >> 1;
+                    if (row[mid] != JX_NONE_ID) deg = mid + 1;
+                    else hi = mid;
+                }
+            }
+            if (!a.force_prune && deg + m <= a.R) {
+                for (int j = 0; j < (int)m; j++) row[deg + j] = a.vals[lo + j];
+                const_cast<uint32_t*>(a.heads)[s] = (uint32_t)lo | 0x80000000u;
+            } else {
+                cls = deg + m <= GT_SMALL ? 1 : (deg <= GT_BIG - 64 ? 2 : 0);  // too little room for new ones: list-based kernel
+                entry = (uint64_t)s | ((uint64_t)((uint32_t)deg << 10 | (uint32_t)(m < 1023 ? m : 1023)) << 32);
+            }
+        }
+#pragma unroll
+        for (int k = 1; k <= 2; k++) {
+            const uint64_t on = ballot(cls == k);
+            if (!on) continue;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(const_cast<uint32_t*>(a.nseg) + k, (uint32_t)__builtin_popcountll(on));
+            at = readlane32(at, 0) + (uint32_t)prefix_count(on);
+            if (cls == k) a.lists[k == 1 ? (long long)at : total - 1 - at] = entry;
+        }
+    }
+}
+
+// NB = 4: at most 128 candidates.  NB = 8: up to 256, or the existing neighbours and the closest new edges up to 256 (the
+// new edges arrive sorted); a pool that does not yield R neighbours no farther than its last new edge is left to the
+// list-based kernel.  A segment that is done is marked (bit 31 of its head): its rewritten row no longer tells.
+template <int DT, int NB>
+__global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) reverse_merge_gram_kernel(InsertArgs a) {
+    __shared__ TeamLds<DT, NB> lds;
+    TeamLds<DT, NB>* L = &lds;
+    const int tid = threadIdx.x;
+    const uint32_t n = a.nseg[NB == 4 ? 1 : 2];
+    const long long total = a.E ? a.E : a.B * a.R;
+    for (uint32_t at = blockIdx.x; at < n; at += gridDim.x) {
+        const uint64_t entry = a.lists[NB == 4 ? (long long)at : total - 1 - at];
+        const uint32_t s = (uint32_t)entry;
+        const int deg = (int)(entry >> 42), m = (int)(entry >> 32) & 1023;
+        const long long lo = a.heads[s];
         const uint32_t v = (uint32_t)(a.keys[lo] >> 32);
-        if (v == JX_NONE_ID) continue;
-        int m = 0;
-        for (long long c0 = lo; c0 < total; c0 += 64) {
-            const long long j = c0 + lane;
-            const bool same = j < total && (uint32_t)(a.keys[j] >> 32) == v;
-            const uint64_t sm = ballot(same);
-            m += __builtin_popcountll(sm);
-            if (sm != ~0ull) break;
-        }
         uint32_t* row = a.adj + (size_t)v * a.R;
-        int deg = 0;
-        for (int rb = 0; rb < a.R; rb += 64) {
-            const bool on = rb + lane < a.R && row[rb + lane] != JX_NONE_ID;
-            deg += __builtin_popcountll(ballot(on));
+        const int mp = m < 32 * NB - deg ? m : 32 * NB - deg;
+        for (int j = tid; j < deg; j += NB * 64) L->id[j] = row[j];
+        for (int j = tid; j < mp; j += NB * 64) {
+            L->id[deg + j] = a.vals[lo + j];
+            L->dp[deg + j] = __uint_as_float((uint32_t)a.keys[lo + j]);
         }
-        if (a.force_prune) deg = 0;
-        if (!a.force_prune && deg + m <= a.R) continue;
-        if (deg + m + (DT != JX_F32 ? 1 : 0) <= GP_MAX) continue;  // the one-pass kernels' share
-        if (deg > GB_MAX - 64) continue;                             // too little room for new candidates: list-based kernel
-        const int mp = m < GB_MAX - deg ? m : GB_MAX - deg;          // new candidates in the pool (the closest ones)
-        const int M = deg + mp;
-        for (int j = lane; j < deg; j += 64) L->id[j] = row[j];
-        for (int j = lane; j < mp; j += 64) L->id[deg + j] = a.vals[lo + j];
-        wave_sync();
-        const int nsel = gram_prune_big<DT>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, M, v, a.R, a.alpha, deg, a.keys + lo,
-                                            mp < m);
-        if (nsel < 0) continue;  // the prefix did not yield R neighbours: left to the list-based kernel
-        for (int j = lane; j < a.R; j += 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
-        if (a.clean && lane == 0) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
-        if (lane == 0) const_cast<uint32_t*>(a.heads)[s] = head | 0x80000000u;
-        wave_sync();
+        __syncthreads();
+        const int nsel = team_prune<DT, NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, deg + mp, deg, v, a.R, a.alpha, mp < m);
+        if (nsel >= 0) {
+            for (int j = tid; j < a.R; j += NB * 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
+            if (tid == 0) {
+                if (a.clean) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
+                const_cast<uint32_t*>(a.heads)[s] = (uint32_t)lo | 0x80000000u;
+            }
+        }
+        __syncthreads();
     }
 }
 
 template <int DT>
 static hipError_t launch_forward_gram_dt(const InsertArgs& a, hipStream_t st) {
-    dim3 grid((unsigned)((a.B + GP_WPB - 1) / GP_WPB)), block(GP_WPB * 64);
-    hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 2>), grid, block, 0, st, a);
-    if (a.L > 64) hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 3>), grid, block, 0, st, a);
-    if (a.L > 96) hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 4>), grid, block, 0, st, a);
-    if (a.L > GP_MAX) {  // longer lists (expansion lists): block-row form on the closest 256
-        const size_t sh = sizeof(GramBigLds) * GP_WPB;
-        hipError_t e = hipFuncSetAttribute((const void*)forward_prune_gram_big_kernel<DT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((forward_prune_gram_big_kernel<DT>), grid, block, sh, st, a);
-    }
+    hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 4>), dim3((unsigned)a.B), dim3(256), 0, st, a);
+    if (a.L > GT_SMALL) hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 8>), dim3((unsigned)a.B), dim3(512), 0, st, a);
     return hipGetLastError();
 }
 
 template <int DT>
 static hipError_t launch_reverse_gram_dt(const InsertArgs& a, hipStream_t st) {
-    long long want = ((a.E ? a.E : a.B * a.R) + GP_WPB - 1) / GP_WPB;
-    const long long cap = 8192 / GP_WPB;  // persistent wavefronts, segments dealt round-robin
-    dim3 grid((unsigned)(want < cap ? (want < 1 ? 1 : want) : cap)), block(GP_WPB * 64);
-    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 2>), grid, block, 0, st, a);
-    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 3>), grid, block, 0, st, a);
-    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 4>), grid, block, 0, st, a);
-    {   // 129 .. 256 candidates: few and long, 27 KB of LDS per wavefront
-        const size_t sh = sizeof(GramBigLds) * GP_WPB;
-        hipError_t e = hipFuncSetAttribute((const void*)reverse_merge_gram_big_kernel<DT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((reverse_merge_gram_big_kernel<DT>), dim3(grid.x < 4096 / GP_WPB ? grid.x : 4096 / GP_WPB), block, sh, st, a);
-    }
+    const long long most = a.E ? a.E : a.B * a.R;  // segments there can be
+    auto grid = [&](long long per, long long cap) {
+        const long long want = (most + per - 1) / per;
+        return dim3((unsigned)(want < cap ? (want < 1 ? 1 : want) : cap));
+    };
+    hipLaunchKernelGGL(reverse_class_kernel, grid(256, 1024), dim3(256), 0, st, a);
+    // persistent workgroups: as many as the card holds, twice over
+    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 4>), grid(1, 2048), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 8>), grid(1, 1024), dim3(512), 0, st, a);
     return hipGetLastError();
 }
 
