@@ -74,10 +74,9 @@ extern "C" {
  * variable.
  */
 #define JX_FLAG_NO_PAIR (1u << 0)       /* beamSearch: never take two expansions per round */
-#define JX_FLAG_NO_INCR_PRUNE (1u << 1) /* uint8 reverse merge: always prune a whole row, never only the pairs that
-                                           involve entries added since the row's last prune */
-#define JX_FLAG_NO_GRAM (1u << 2)       /* float data: robustPrune by the list-based kernels, not the Gram-matrix (MFMA) ones */
-#define JX_FLAG_GRAM_U8 (1u << 3)       /* uint8 data: robustPrune by the Gram-matrix kernels as well */
+#define JX_FLAG_NO_INCR_PRUNE (1u << 1) /* no effect: every overflowing row is pruned as a whole */
+#define JX_FLAG_NO_GRAM (1u << 2)       /* robustPrune by the list-based kernels, not the matrix-core (MFMA) ones */
+#define JX_FLAG_GRAM_U8 (1u << 3)       /* uint8 data: robustPrune by the Gram-matrix kernels, as for floats */
 #define JX_FLAG_VISITED_IDS (1u << 4)   /* beamSearch visited filter: direct-mapped table of full 32-bit ids (ParlayANN's
                                            table, Sec. 4.2) instead of two-way sets of 16-bit tags */
 #define JX_FLAG_VISITED_NONE (1u << 5)  /* beamSearch visited filter: none -- Alg. 2 as printed: every neighbour is

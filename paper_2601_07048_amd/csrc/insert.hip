@@ -112,13 +112,8 @@ __global__ void __launch_bounds__(1024) argmin_kernel(const double* dist, long l
 
 struct PruneLds {
     uint64_t a_key[INS_RA];   // existing neighbours sorted by (distance, id); key = distance bits << 32 | id
-    union {
-        struct {
-            uint64_t a_tmp[INS_RA];
-            uint64_t cand_key[64];
-        };
-        uint32_t gram_scratch[128 + 128 * 4];  // MFMA path: squared norms, then the discard relation
-    };
+    uint64_t a_tmp[INS_RA];
+    uint64_t cand_key[64];
     uint32_t cand_id[64];
     uint32_t cand_src[64];
     uint32_t sel_id[INS_RA];
@@ -240,204 +235,6 @@ __device__ __forceinline__ int robust_prune_wave(const DistSrc& ds, PruneLds* L,
     return nsel;
 }
 
-
-// robustPrune for the common small case on uint8 vectors of exactly 128 bytes:
-// up to 128 candidates, already merged and sorted in L->a_key, their vectors
-// cached in LDS (slot i = position i, the cache covers whole tiles of 32 slots).
-//
-// The discard relation "i discards j" (alpha * d(i,j) <= d(p,j), i before j)
-// does not depend on the order of selection, so it is computed for all pairs at
-// once: d(i,j) = ||x_i||^2 + ||x_j||^2 - 2 <x_i,x_j> and the Gram matrix is a
-// dense contraction done on the matrix cores (int8 MFMA 32x32x16 on the
-// vectors shifted by -128, which leaves distances unchanged and exact).  Each
-// accumulator element gives one ballot = one 32-column stripe of the relation
-// for two rows.  The sequential part of Alg. 3 is then a scalar walk over
-// bit masks: take the first live candidate, clear everything it discards.
-typedef int i32x16_t __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ int prune_cached_u8_mfma(PruneLds* L, const unsigned char* vc, int M, int R, float alpha) {
-    const int lane = lane_id();
-    const int col = lane & 31, half = lane >> 5;
-    const int nt = (M + 31) >> 5;  // tiles of 32 slots
-    uint32_t* nrm = L->gram_scratch;         // [128] squared norms of the shifted vectors
-    uint32_t* kmat = L->gram_scratch + 128;  // [128][4] discard relation, row i = mask over j
-    // ---- norms: 4 lanes per slot (32 bytes each), 16 slots per step
-    {
-        const int sb = lane & 15, part = lane >> 4;
-        for (int s0 = 0; s0 < nt * 32; s0 += 16) {
-            const unsigned char* cv = vc + (size_t)(s0 + sb) * 128 + part * 32;
-            uint4 c0 = *reinterpret_cast<const uint4*>(cv), c1 = *reinterpret_cast<const uint4*>(cv + 16);
-            c0.x ^= 0x80808080u; c0.y ^= 0x80808080u; c0.z ^= 0x80808080u; c0.w ^= 0x80808080u;
-            c1.x ^= 0x80808080u; c1.y ^= 0x80808080u; c1.z ^= 0x80808080u; c1.w ^= 0x80808080u;
-            int32_t nn = 0;
-            nn = __builtin_amdgcn_sdot4((int)c0.x, (int)c0.x, nn, false);
-            nn = __builtin_amdgcn_sdot4((int)c0.y, (int)c0.y, nn, false);
-            nn = __builtin_amdgcn_sdot4((int)c0.z, (int)c0.z, nn, false);
-            nn = __builtin_amdgcn_sdot4((int)c0.w, (int)c0.w, nn, false);
-            nn = __builtin_amdgcn_sdot4((int)c1.x, (int)c1.x, nn, false);
-            nn = __builtin_amdgcn_sdot4((int)c1.y, (int)c1.y, nn, false);
-            nn = __builtin_amdgcn_sdot4((int)c1.z, (int)c1.z, nn, false);
-            nn = __builtin_amdgcn_sdot4((int)c1.w, (int)c1.w, nn, false);
-            nn += shfl_xor(nn, 16);
-            nn += shfl_xor(nn, 32);
-            if (part == 0) nrm[s0 + sb] = (uint32_t)nn;
-        }
-    }
-    wave_sync();
-    // ---- discard relation, tile by tile (rows ti <= columns tj)
-    for (int ti = 0; ti < nt; ti++) {
-        long af[8];
-#pragma unroll
-        for (int ks = 0; ks < 8; ks++)
-            af[ks] = *reinterpret_cast<const long*>(vc + (size_t)(ti * 32 + col) * 128 + ks * 16 + half * 8) ^ (long)0x8080808080808080ULL;
-        for (int tj = ti; tj < nt; tj++) {
-            i32x16_t acc;
-#pragma unroll
-            for (int e = 0; e < 16; e++) acc[e] = 0;
-#pragma unroll
-            for (int ks = 0; ks < 8; ks++) {
-                const long bf = *reinterpret_cast<const long*>(vc + (size_t)(tj * 32 + col) * 128 + ks * 16 + half * 8) ^ (long)0x8080808080808080ULL;
-                acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(af[ks], bf, acc, 0, 0, 0);
-            }
-            const int j = tj * 32 + col;
-            const uint32_t nj = nrm[j];
-            const float d2 = j < M ? __uint_as_float((uint32_t)(L->a_key[j] >> 32)) : 0.f;
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int i = ti * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-                const uint32_t dij = nrm[i] + nj - 2u * (uint32_t)acc[e];
-                const bool kill = j < M && (__fmul_rn(alpha, (float)dij) <= d2);
-                const uint64_t km = ballot(kill);
-                if (lane == 0) {
-                    const int r0 = ti * 32 + 8 * (e >> 2) + (e & 3);
-                    kmat[r0 * 4 + tj] = (uint32_t)km;
-                    kmat[(r0 + 4) * 4 + tj] = (uint32_t)(km >> 32);
-                }
-            }
-        }
-    }
-    wave_sync();
-    // ---- Alg. 3 on bit masks
-    uint64_t alive0 = M >= 64 ? ~0ull : ((1ull << M) - 1ull);
-    uint64_t alive1 = M <= 64 ? 0ull : (M >= 128 ? ~0ull : ((1ull << (M - 64)) - 1ull));
-    int nsel = 0;
-    while (nsel < R) {
-        int i;
-        if (alive0) {
-            i = __builtin_ctzll(alive0);
-            alive0 &= alive0 - 1;
-        } else if (alive1) {
-            i = 64 + __builtin_ctzll(alive1);
-            alive1 &= alive1 - 1;
-        } else {
-            break;
-        }
-        const uint64_t kp = L->a_key[i];
-        if (lane == 0) {
-            L->sel_id[nsel] = (uint32_t)kp;
-            L->sel_dist[nsel] = (uint32_t)(kp >> 32);
-        }
-        nsel++;
-        // words of columns left of the row's own tile were never written and are
-        // not needed: every slot before i is already selected or discarded
-        const int ti = i >> 5;
-        uint32_t w[4];
-#pragma unroll
-        for (int t = 0; t < 4; t++) w[t] = (t >= ti && t < nt) ? kmat[i * 4 + t] : 0u;
-        alive0 &= ~(((uint64_t)w[1] << 32) | w[0]);
-        alive1 &= ~(((uint64_t)w[3] << 32) | w[2]);
-    }
-    wave_sync();
-    return nsel;
-}
-
-// robustPrune of a row that is mostly the output of an earlier robustPrune call
-// (uint8 vectors of 128 bytes, all M <= 128 candidates merged and sorted in
-// L->a_key, their vectors cached in LDS, L->a_dead[i] = 1 marks the entries that
-// were NOT selected together by that call: appended since, or new).
-//
-// Two entries that one call selected, i before j, satisfy "i does not discard j":
-// otherwise j would not have been selected.  Distances on uint8 data are exact
-// integers and alpha is fixed, so the same test gives the same answer now, and
-// only pairs with a marked entry have to be evaluated.  Marked entries are taken
-// in sorted order; when one is reached every earlier entry has its final state,
-// because only marked entries before it could have discarded anything.  An entry
-// beyond the R-th selected one is never output, so neither what it discards nor
-// whether it is discarded matters.
-template <int T, int CPL>
-__device__ __forceinline__ int prune_cached_u8_incremental(const DistSrc& cds, PruneLds* L, int M, int R, float alpha) {
-    constexpr int G = 64 / T;
-    constexpr int U0 = (8 / CPL) > 0 ? (8 / CPL) : 1;
-    constexpr int U = U0 < (64 / G) ? U0 : (64 / G);
-    const int lane = lane_id();
-    const int g = lane / T, lig = lane % T;
-    uint64_t dm[2], alive[2];
-    dm[0] = ballot(lane < M && L->a_dead[lane] != 0);
-    dm[1] = ballot(lane + 64 < M && L->a_dead[lane + 64] != 0);
-    alive[0] = M >= 64 ? ~0ull : ((1ull << M) - 1ull);
-    alive[1] = M <= 64 ? 0ull : (M >= 128 ? ~0ull : ((1ull << (M - 64)) - 1ull));
-    QueryRegs<K_U8, CPL, 0> q;
-    while (dm[0] | dm[1]) {
-        int t;
-        if (dm[0]) {
-            t = __builtin_ctzll(dm[0]);
-            dm[0] &= dm[0] - 1ull;
-        } else {
-            t = 64 + __builtin_ctzll(dm[1]);
-            dm[1] &= dm[1] - 1ull;
-        }
-        if (((alive[t >> 6] >> (t & 63)) & 1ull) == 0ull) continue;  // discarded by an earlier marked entry
-        const float dvt = __uint_as_float((uint32_t)(L->a_key[t] >> 32));
-        load_query<K_U8, T, CPL, 0>(q, cds, (int64_t)t, lig);
-        uint64_t rk[2] = {0ull, 0ull}, ck[2] = {0ull, 0ull};
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int c0 = h * 64;
-            if (c0 >= M) break;
-            const int nn = M - c0 < 64 ? M - c0 : 64;
-            if (lane < nn) L->cand_id[lane] = (uint32_t)(c0 + lane);
-            wave_sync();
-            for (int s0 = 0; s0 < nn; s0 += G * U)
-                eval_batch<K_U8, T, CPL, 0, U>(q, cds, s0, nn, L->cand_id, L->cand_key, g, lig);
-            wave_sync();
-            const int j = c0 + lane;
-            bool rkill = false, ckill = false;
-            if (lane < nn) {
-                const float d1 = (float)key_dist(L->cand_key[lane]);
-                const float dvj = __uint_as_float((uint32_t)(L->a_key[j] >> 32));
-                rkill = j > t && __fmul_rn(alpha, d1) <= dvj;  // t discards j
-                ckill = j < t && __fmul_rn(alpha, d1) <= dvt;  // j, if selected, discards t
-            }
-            rk[h] = ballot(rkill);
-            ck[h] = ballot(ckill);
-            wave_sync();
-        }
-        if ((ck[0] & alive[0]) | (ck[1] & alive[1])) {
-            alive[t >> 6] &= ~(1ull << (t & 63));
-        } else {
-            alive[0] &= ~rk[0];
-            alive[1] &= ~rk[1];
-        }
-    }
-    const int n0 = __builtin_popcountll(alive[0]);
-#pragma unroll
-    for (int h = 0; h < 2; h++) {
-        const int j = h * 64 + lane;
-        if (j < M && ((alive[h] >> lane) & 1ull)) {
-            const int pos = (h ? n0 : 0) + __builtin_popcountll(alive[h] & ((1ull << lane) - 1ull));
-            if (pos < R) {
-                const uint64_t k = L->a_key[j];
-                L->sel_id[pos] = (uint32_t)k;
-                L->sel_dist[pos] = (uint32_t)(k >> 32);
-            }
-        }
-    }
-    wave_sync();
-    const int total = n0 + __builtin_popcountll(alive[1]);
-    return total < R ? total : R;
-}
-
-
 template <int KIND, int T, int CPL>
 __global__ void __launch_bounds__(INS_WPB * 64) forward_prune_kernel(InsertArgs a) {
     __shared__ PruneLds lds[INS_WPB];
@@ -467,23 +264,7 @@ __global__ void __launch_bounds__(INS_WPB * 64) forward_prune_kernel(InsertArgs 
     if (a.gram && nB <= 128) return;  // served by the Gram-matrix kernel
     __threadfence_block();
     wave_sync();
-    int nsel;
-    if (KIND == K_U8 && a.ds.rec_stride == 128 && nB <= 128 && (long long)((nB + 31) & ~31) * 128 <= a.vec_cache_bytes) {
-        // the frontier is already sorted: cache its vectors in LDS and use the Gram-matrix form
-        extern __shared__ __align__(16) unsigned char vcache[];
-        unsigned char* vc = vcache + (size_t)wave * a.vec_cache_bytes;
-        for (int j = lane; j < nB; j += 64) L->a_key[j] = ((uint64_t)B.dbits[j] << 32) | B.ids[j];
-        for (int c = lane; c < nB * 8; c += 64) {
-            const int sl = c >> 3, ch = c & 7;
-            *reinterpret_cast<uint4*>(vc + (size_t)sl * 128 + ch * 16) =
-                load16(a.ds.recs + (size_t)B.ids[sl] * 128 + (size_t)ch * 16);
-        }
-        __threadfence_block();
-        wave_sync();
-        nsel = prune_cached_u8_mfma(L, vc, nB, a.R, a.alpha);
-    } else {
-        nsel = robust_prune_wave<KIND, T, CPL>(a.ds, L, 0, B, a.R, a.alpha);
-    }
+    const int nsel = robust_prune_wave<KIND, T, CPL>(a.ds, L, 0, B, a.R, a.alpha);
     uint32_t* row = a.adj + (size_t)xid * a.R;
     for (int j = lane; j < a.R; j += 64) {
         const bool on = j < nsel;
@@ -492,7 +273,6 @@ __global__ void __launch_bounds__(INS_WPB * 64) forward_prune_kernel(InsertArgs 
         a.keys[(size_t)i * a.R + j] = on ? (((uint64_t)v << 32) | L->sel_dist[j]) : JX_EMPTY_KEY;
         a.vals[(size_t)i * a.R + j] = on ? (uint32_t)xid : JX_NONE_ID;
     }
-    if (a.clean && lane == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
 }
 
 template <int KIND, int T, int CPL>
@@ -529,8 +309,6 @@ __global__ void __launch_bounds__(INS_WPB * 64) reverse_merge_kernel(InsertArgs 
             deg += __builtin_popcountll(ballot(on));
         }
         if (a.force_prune) deg = 0;  // consolidation: the segment holds the whole candidate set
-        int nclean = (a.clean && !a.force_prune) ? (int)a.clean[v] : 0;
-        if (nclean > deg) nclean = deg;
         if (!a.force_prune && deg + m <= a.R) {
             for (int j = lane; j < m; j += 64) row[deg + j] = a.vals[lo + j];
             continue;
@@ -563,17 +341,12 @@ __global__ void __launch_bounds__(INS_WPB * 64) reverse_merge_kernel(InsertArgs 
             wave_sync();
         }
         const int nsort = cached ? M : deg;
-        // few entries besides those one earlier call selected together: only their pairs need evaluating
-        const bool incremental = KIND == K_U8 && cached && a.ds.rec_stride == 128 && M <= 128 && M - nclean <= 12 && nclean > 0;
         for (int j = lane; j < nsort; j += 64) {
             const uint64_t k = L->a_tmp[j];
             int rank = 0;
             for (int t = 0; t < nsort; t++) rank += (L->a_tmp[t] < k) ? 1 : 0;
             L->a_key[rank] = k;
-            if (incremental)
-                L->a_dead[rank] = j >= nclean ? 1 : 0;
-            else
-                L->a_dead[j] = 0;
+            L->a_dead[j] = 0;
         }
         int nsel;
         if (cached) {
@@ -597,15 +370,7 @@ __global__ void __launch_bounds__(INS_WPB * 64) reverse_merge_kernel(InsertArgs 
             none.dead = nullptr;
             __threadfence_block();
             wave_sync();
-            if constexpr (KIND == K_U8) {
-                if (incremental)
-                    nsel = prune_cached_u8_incremental<T, CPL>(cds, L, M, a.R, a.alpha);
-                else if (a.ds.rec_stride == 128 && M <= 128 && (long long)((M + 31) & ~31) * 128 <= a.vec_cache_bytes)
-                    nsel = prune_cached_u8_mfma(L, vc, M, a.R, a.alpha);
-                else
-                    nsel = robust_prune_wave<KIND, T, CPL, true>(cds, L, M, none, a.R, a.alpha);
-            } else
-                nsel = robust_prune_wave<KIND, T, CPL, true>(cds, L, M, none, a.R, a.alpha);
+            nsel = robust_prune_wave<KIND, T, CPL, true>(cds, L, M, none, a.R, a.alpha);
         } else {
             BList B;
             B.ids = a.vals + lo;
@@ -633,487 +398,7 @@ __global__ void __launch_bounds__(INS_WPB * 64) reverse_merge_kernel(InsertArgs 
             }
         }
         for (int j = lane; j < a.R; j += 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
-        if (a.clean && lane == 0) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
         wave_sync();
-    }
-}
-
-// Reverse-edge merge, lean form for the case that dominates streaming inserts into uint8 indices of 128-byte
-// vectors: the row overflows, all but a few (LEAN_ND) of its candidates were selected together by the row's previous
-// robustPrune call (see prune_cached_u8_incremental for why their pairs need no test), and everything fits 128
-// slots.  One pass over the candidates' vectors in global memory yields d(v,c) and d(x,c) for every entry x that
-// is appended or new (v and those entries sit in registers); ranks come from merging them into the sorted prefix;
-// Alg. 3 is the same walk over the marked entries.  No vector cache in LDS, so five times as many wavefronts are
-// resident as in the general kernel, which then finds these segments marked as done (bit 31 of the head).
-#define LEAN_ND 12  // marked entries per row the lean kernel accepts (taken four at a time)
-struct LeanLds {
-    uint64_t key[128];      // (float bits of d(v,c), id), candidate order: the row, then the new edges
-    uint64_t skey[128];     // the same, sorted
-    uint32_t id[128];
-    uint32_t dd[LEAN_ND][128];  // d(marked entry k, candidate j), candidate order
-    uint8_t orig[128];      // candidate index of sorted position p
-    uint8_t flag[128];      // sorted position p: 0 = selected by the previous call, else 1 + index of the marked entry
-};
-
-__global__ void __launch_bounds__(64) reverse_merge_u8_lean_kernel(InsertArgs a) {
-    __shared__ LeanLds lds;
-    LeanLds* F = &lds;
-    const int lane = lane_id();
-    const int g = lane >> 2, lig = lane & 3;
-    const long long nseg = *a.nseg;
-    const long long total = a.E ? a.E : a.B * a.R;
-    const uint8_t* recs = a.ds.recs;
-    for (long long s = blockIdx.x; s < nseg; s += gridDim.x) {
-        const uint32_t head = a.heads[s];
-        if (head & 0x80000000u) continue;
-        const long long lo = head;
-        const uint32_t v = (uint32_t)(a.keys[lo] >> 32);
-        if (v == JX_NONE_ID) continue;
-        int m = 0;
-        for (long long c0 = lo; c0 < total; c0 += 64) {
-            const long long j = c0 + lane;
-            const bool same = j < total && (uint32_t)(a.keys[j] >> 32) == v;
-            const uint64_t sm = ballot(same);
-            m += __builtin_popcountll(sm);
-            if (sm != ~0ull) break;
-        }
-        uint32_t* row = a.adj + (size_t)v * a.R;
-        int deg = 0;
-        for (int rb = 0; rb < a.R; rb += 64) {
-            const bool on = rb + lane < a.R && row[rb + lane] != JX_NONE_ID;
-            deg += __builtin_popcountll(ballot(on));
-        }
-        if (deg + m <= a.R) {  // the row still fits: append in (distance, source) order
-            for (int j = lane; j < m; j += 64) row[deg + j] = a.vals[lo + j];
-            if (lane == 0) const_cast<uint32_t*>(a.heads)[s] = head | 0x80000000u;
-            continue;
-        }
-        int nclean = (int)a.clean[v];
-        if (nclean > deg) nclean = deg;
-        const int M = deg + m, nd = M - nclean;
-        if (nclean == 0 || M > 128 || nd > LEAN_ND) continue;
-        wave_sync();  // the previous segment's reads of the LDS arrays are done
-        for (int j = lane; j < M; j += 64) F->id[j] = j < deg ? row[j] : a.vals[lo + (j - deg)];
-        wave_sync();
-        auto sq = [](const uint4 (&x)[2]) {
-            uint32_t t = 0;
-            t = __builtin_amdgcn_udot4(x[0].x, x[0].x, t, false);
-            t = __builtin_amdgcn_udot4(x[0].y, x[0].y, t, false);
-            t = __builtin_amdgcn_udot4(x[0].z, x[0].z, t, false);
-            t = __builtin_amdgcn_udot4(x[0].w, x[0].w, t, false);
-            t = __builtin_amdgcn_udot4(x[1].x, x[1].x, t, false);
-            t = __builtin_amdgcn_udot4(x[1].y, x[1].y, t, false);
-            t = __builtin_amdgcn_udot4(x[1].z, x[1].z, t, false);
-            t = __builtin_amdgcn_udot4(x[1].w, x[1].w, t, false);
-            return t;
-        };
-        auto dot = [](const uint4 (&x)[2], const uint4 (&y)[2]) {
-            uint32_t t = 0;
-            t = __builtin_amdgcn_udot4(x[0].x, y[0].x, t, false);
-            t = __builtin_amdgcn_udot4(x[0].y, y[0].y, t, false);
-            t = __builtin_amdgcn_udot4(x[0].z, y[0].z, t, false);
-            t = __builtin_amdgcn_udot4(x[0].w, y[0].w, t, false);
-            t = __builtin_amdgcn_udot4(x[1].x, y[1].x, t, false);
-            t = __builtin_amdgcn_udot4(x[1].y, y[1].y, t, false);
-            t = __builtin_amdgcn_udot4(x[1].z, y[1].z, t, false);
-            t = __builtin_amdgcn_udot4(x[1].w, y[1].w, t, false);
-            return t;
-        };
-        // v and four marked entries at a time sit in registers, 32 bytes per lane of each 4-lane group; every group
-        // of four takes one pass over the candidates (16 per step, two steps in flight)
-        uint4 qv[2];
-        {
-            const uint8_t* pv = recs + (size_t)v * 128 + lig * 32;
-            qv[0] = load16(pv);
-            qv[1] = load16(pv + 16);
-        }
-        const uint32_t qqv = group_sum<4>(sq(qv));
-        for (int kb = 0; kb < nd; kb += 4) {
-            const int nk = nd - kb < 4 ? nd - kb : 4;
-            uint4 qd[4][2];
-            uint32_t qqd[4];
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const uint32_t idk = F->id[nclean + kb + (k < nk ? k : 0)];
-                const uint8_t* pk = recs + (size_t)idk * 128 + lig * 32;
-                qd[k][0] = load16(pk);
-                qd[k][1] = load16(pk + 16);
-            }
-#pragma unroll
-            for (int k = 0; k < 4; k++) qqd[k] = group_sum<4>(sq(qd[k]));
-            for (int c0 = 0; c0 < M; c0 += 32) {
-                uint4 x[2][2];
-                int jj[2];
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    jj[u] = c0 + 16 * u + g;
-                    const uint32_t id = F->id[jj[u] < M ? jj[u] : M - 1];
-                    const uint8_t* px = recs + (size_t)id * 128 + lig * 32;
-                    x[u][0] = load16(px);
-                    x[u][1] = load16(px + 16);
-                }
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    if (c0 + 16 * u >= M) break;  // wave-uniform
-                    const uint32_t aa = dot(x[u], x[u]);
-                    uint32_t dv = 0;
-                    if (kb == 0) dv = (uint32_t)group_sum<4>((int32_t)aa - 2 * (int32_t)dot(x[u], qv)) + qqv;
-                    uint32_t dk[4];
-#pragma unroll
-                    for (int k = 0; k < 4; k++) {
-                        dk[k] = 0;
-                        if (k < nk) dk[k] = (uint32_t)group_sum<4>((int32_t)aa - 2 * (int32_t)dot(x[u], qd[k])) + qqd[k];
-                    }
-                    if (lig == 0 && jj[u] < M) {
-                        if (kb == 0) F->key[jj[u]] = ((uint64_t)__float_as_uint((float)dv) << 32) | (uint64_t)F->id[jj[u]];
-#pragma unroll
-                        for (int k = 0; k < 4; k++)
-                            if (k < nk) F->dd[kb + k][jj[u]] = dk[k];
-                    }
-                }
-            }
-        }
-        wave_sync();
-        // ranks: the prefix is sorted already and every marked entry is merged into it.  Prefix entry: own index +
-        // marked entries below it; marked entry: prefix entries below it + marked entries below it
-        uint64_t kj[2];
-        int rank[2];
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int j = h * 64 + lane;
-            kj[h] = j < M ? F->key[j] : JX_EMPTY_KEY;
-            rank[h] = j < nclean ? j : 0;
-        }
-        for (int k = 0; k < nd; k++) {
-            const uint64_t kt = F->key[nclean + k];
-            const int below = __builtin_popcountll(ballot(lane < nclean && kj[0] < kt)) +
-                              __builtin_popcountll(ballot(64 + lane < nclean && kj[1] < kt));
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const int j = h * 64 + lane;
-                rank[h] += (kt < kj[h]) ? 1 : 0;
-                if (j == nclean + k) rank[h] += below;
-            }
-        }
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int j = h * 64 + lane;
-            if (j < M) {
-                F->skey[rank[h]] = kj[h];
-                F->orig[rank[h]] = (uint8_t)j;
-                F->flag[rank[h]] = j >= nclean ? (uint8_t)(1 + j - nclean) : (uint8_t)0;
-            }
-        }
-        wave_sync();
-        // Alg. 3 over the marked entries, sorted space
-        uint64_t sk[2], dm[2], alive[2];
-        float dvp[2];
-        int og[2];
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int p = h * 64 + lane;
-            sk[h] = p < M ? F->skey[p] : JX_EMPTY_KEY;
-            dvp[h] = __uint_as_float((uint32_t)(sk[h] >> 32));
-            og[h] = p < M ? (int)F->orig[p] : 0;
-            dm[h] = ballot(p < M && F->flag[p] != 0);
-        }
-        alive[0] = M >= 64 ? ~0ull : ((1ull << M) - 1ull);
-        alive[1] = M <= 64 ? 0ull : (M >= 128 ? ~0ull : ((1ull << (M - 64)) - 1ull));
-        while (dm[0] | dm[1]) {
-            int t;
-            if (dm[0]) {
-                t = __builtin_ctzll(dm[0]);
-                dm[0] &= dm[0] - 1ull;
-            } else {
-                t = 64 + __builtin_ctzll(dm[1]);
-                dm[1] &= dm[1] - 1ull;
-            }
-            if (((alive[t >> 6] >> (t & 63)) & 1ull) == 0ull) continue;
-            const int k = (int)F->flag[t] - 1;
-            const float dvt = __uint_as_float((uint32_t)(F->skey[t] >> 32));
-            uint64_t rk[2], ck[2];
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const int p = h * 64 + lane;
-                const float d1 = (float)F->dd[k][og[h]];
-                const float ad = __fmul_rn(a.alpha, d1);
-                rk[h] = ballot(p < M && p > t && ad <= dvp[h]);
-                ck[h] = ballot(p < M && p < t && ad <= dvt);
-            }
-            if ((ck[0] & alive[0]) | (ck[1] & alive[1])) {
-                alive[t >> 6] &= ~(1ull << (t & 63));
-            } else {
-                alive[0] &= ~rk[0];
-                alive[1] &= ~rk[1];
-            }
-        }
-        const int n0 = __builtin_popcountll(alive[0]);
-        const int tot = n0 + __builtin_popcountll(alive[1]);
-        const int nsel = tot < a.R ? tot : a.R;
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int p = h * 64 + lane;
-            if (p < M && ((alive[h] >> lane) & 1ull)) {
-                const int pos = (h ? n0 : 0) + __builtin_popcountll(alive[h] & ((1ull << lane) - 1ull));
-                if (pos < a.R) row[pos] = (uint32_t)sk[h];
-            }
-        }
-        for (int j = nsel + lane; j < a.R; j += 64) row[j] = JX_NONE_ID;
-        if (lane == 0) {
-            a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
-            const_cast<uint32_t*>(a.heads)[s] = head | 0x80000000u;
-        }
-    }
-}
-
-// Forward robustPrune, lean form for uint8 vectors of 128 bytes and frontiers of at most 128 entries.  The
-// selection loop of Alg. 3 has one dependent memory round trip per selected neighbour; here up to four pivots --
-// the next live candidates in order -- are taken per round: one pass over the live candidates behind the first
-// pivot loads every vector once and tests it against all four (the pivots sit in registers), then the pivots are
-// resolved in order: a pivot that is still live is selected and discards what it discards, one that an earlier
-// pivot discarded is skipped (its tests were wasted).  Every test is the pairwise test of Alg. 3 on exact
-// integers, so the result is the sequential algorithm's.
-template <int MAXC>
-struct FwdLds {
-    uint32_t id[MAXC];
-    float dx[MAXC];        // d(x, candidate)
-    uint32_t sel_id[MAXC];
-    uint32_t sel_dist[MAXC];
-    uint16_t cand[MAXC];   // live candidates behind the first pivot, compacted
-    uint8_t kb[MAXC];      // bit i: pivot i discards this candidate
-};
-
-// The rounds described above on the candidates F->id / F->dx (sorted by (distance, id); alive = one bit per
-// candidate).  Returns the number of selected neighbours, F->sel_id / F->sel_dist in selection order.
-template <int MAXC>
-__device__ __forceinline__ int multi_pivot_prune_u8(FwdLds<MAXC>* F, const uint8_t* recs, uint64_t (&alive)[MAXC / 64], const int R,
-                                                    const float alpha) {
-    constexpr int NW = MAXC / 64;
-    const int lane = lane_id();
-    const int g = lane >> 2, lig = lane & 3;
-    auto dot = [](const uint4 (&x)[2], const uint4 (&y)[2]) {
-        uint32_t t = 0;
-        t = __builtin_amdgcn_udot4(x[0].x, y[0].x, t, false);
-        t = __builtin_amdgcn_udot4(x[0].y, y[0].y, t, false);
-        t = __builtin_amdgcn_udot4(x[0].z, y[0].z, t, false);
-        t = __builtin_amdgcn_udot4(x[0].w, y[0].w, t, false);
-        t = __builtin_amdgcn_udot4(x[1].x, y[1].x, t, false);
-        t = __builtin_amdgcn_udot4(x[1].y, y[1].y, t, false);
-        t = __builtin_amdgcn_udot4(x[1].z, y[1].z, t, false);
-        t = __builtin_amdgcn_udot4(x[1].w, y[1].w, t, false);
-        return t;
-    };
-    auto any_alive = [&]() {
-        uint64_t m = 0;
-#pragma unroll
-        for (int w = 0; w < NW; w++) m |= alive[w];
-        return m != 0ull;
-    };
-    int nsel = 0;
-    while (nsel < R && any_alive()) {
-        // ---- pivots: the next live candidates, as many as may still be selected, at most four
-        int t[4], np = 0;
-        {
-            uint64_t m[NW];
-#pragma unroll
-            for (int w = 0; w < NW; w++) m[w] = alive[w];
-            const int room = R - nsel < 4 ? R - nsel : 4;
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                t[k] = 0;
-                if (k < room) {
-                    bool found = false;
-#pragma unroll
-                    for (int w = 0; w < NW; w++) {
-                        if (!found && m[w]) {
-                            t[k] = 64 * w + __builtin_ctzll(m[w]);
-                            m[w] &= m[w] - 1ull;
-                            np = k + 1;
-                            found = true;
-                        }
-                    }
-                }
-            }
-        }
-        // ---- live candidates behind the first pivot
-        int n_alive = 0;
-#pragma unroll
-        for (int h = 0; h < NW; h++) {
-            const int j = h * 64 + lane;
-            const bool on = ((alive[h] >> lane) & 1ull) && j > t[0];
-            const uint64_t m = ballot(on);
-            if (on) F->cand[n_alive + prefix_count(m)] = (uint16_t)j;
-            n_alive += __builtin_popcountll(m);
-        }
-        if (n_alive == 0 || nsel + 1 >= R) {
-            // the last neighbour there is, or the last one there is room for: nothing left to discard
-            if (lane == 0) {
-                F->sel_id[nsel] = F->id[t[0]];
-                F->sel_dist[nsel] = __float_as_uint(F->dx[t[0]]);
-            }
-            nsel++;
-            break;
-        }
-        wave_sync();
-        uint4 qd[4][2];
-        uint32_t qqd[4];
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const uint32_t idk = F->id[t[k < np ? k : 0]];
-            const uint8_t* pk = recs + (size_t)idk * 128 + lig * 32;
-            qd[k][0] = load16(pk);
-            qd[k][1] = load16(pk + 16);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; k++) qqd[k] = group_sum<4>(dot(qd[k], qd[k]));
-        for (int c0 = 0; c0 < n_alive; c0 += 32) {
-            uint4 x[2][2];
-            int jj[2], jc[2];
-#pragma unroll
-            for (int u = 0; u < 2; u++) {
-                jj[u] = c0 + 16 * u + g;
-                jc[u] = (int)F->cand[jj[u] < n_alive ? jj[u] : n_alive - 1];
-                const uint8_t* px = recs + (size_t)F->id[jc[u]] * 128 + lig * 32;
-                x[u][0] = load16(px);
-                x[u][1] = load16(px + 16);
-            }
-#pragma unroll
-            for (int u = 0; u < 2; u++) {
-                if (c0 + 16 * u >= n_alive) break;  // wave-uniform
-                const uint32_t aa = dot(x[u], x[u]);
-                uint32_t bits = 0;
-                const float dxc = F->dx[jc[u]];
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    if (k < np) {
-                        const uint32_t dk = (uint32_t)group_sum<4>((int32_t)aa - 2 * (int32_t)dot(x[u], qd[k])) + qqd[k];
-                        if (jc[u] > t[k] && __fmul_rn(alpha, (float)dk) <= dxc) bits |= 1u << k;
-                    }
-                }
-                if (lig == 0 && jj[u] < n_alive) F->kb[jc[u]] = (uint8_t)bits;
-            }
-        }
-        wave_sync();
-        uint64_t K[4][NW];
-#pragma unroll
-        for (int h = 0; h < NW; h++) {
-            const int j = h * 64 + lane;
-            const bool on = ((alive[h] >> lane) & 1ull) && j > t[0];
-            const uint32_t b = on ? (uint32_t)F->kb[j] : 0u;
-#pragma unroll
-            for (int k = 0; k < 4; k++) K[k][h] = ballot((b >> k) & 1u);
-        }
-        // ---- resolve the pivots in order
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            if (k < np && nsel < R) {
-                const int tk = t[k];
-                bool live = false;
-#pragma unroll
-                for (int w = 0; w < NW; w++)
-                    if (w == (tk >> 6)) live = (alive[w] >> (tk & 63)) & 1ull;
-                if (live) {
-                    if (lane == 0) {
-                        F->sel_id[nsel] = F->id[tk];
-                        F->sel_dist[nsel] = __float_as_uint(F->dx[tk]);
-                    }
-                    nsel++;
-#pragma unroll
-                    for (int w = 0; w < NW; w++) {
-                        if (w == (tk >> 6)) alive[w] &= ~(1ull << (tk & 63));
-                        alive[w] &= ~K[k][w];
-                    }
-                }
-            }
-        }
-        wave_sync();
-    }
-    wave_sync();
-    return nsel;
-}
-
-// N = 128 (final frontiers of L_build <= 128) or 512 (expansion lists)
-template <int N>
-__global__ void __launch_bounds__(64) forward_prune_u8_lean_kernel(InsertArgs a) {
-    __shared__ FwdLds<N> lds;
-    FwdLds<N>* F = &lds;
-    const int lane = lane_id();
-    const long long i = blockIdx.x;
-    if (i >= a.B) return;
-    long long xid = a.id_base + i;
-    if (xid >= a.id_skip) xid++;
-    const uint32_t* ids = a.cand_ids + (size_t)i * a.L;
-    const uint32_t* dbits = a.cand_dist + (size_t)i * a.L;
-    uint64_t alive[N / 64];
-#pragma unroll
-    for (int h = 0; h < N / 64; h++) {
-        const int j = h * 64 + lane;
-        uint32_t id = JX_NONE_ID;
-        if (j < a.L) id = ids[j];
-        const bool valid = id != JX_NONE_ID;
-        if (valid) {
-            F->id[j] = id;
-            F->dx[j] = __uint_as_float(dbits[j]);
-        }
-        alive[h] = ballot(valid);  // the frontier is filled from the left
-    }
-    wave_sync();
-    const int nsel = multi_pivot_prune_u8<N>(F, a.ds.recs, alive, a.R, a.alpha);
-    uint32_t* row = a.adj + (size_t)xid * a.R;
-    for (int j = lane; j < a.R; j += 64) {
-        const bool on = j < nsel;
-        const uint32_t v = on ? F->sel_id[j] : JX_NONE_ID;
-        row[j] = v;
-        a.keys[(size_t)i * a.R + j] = on ? (((uint64_t)v << 32) | F->sel_dist[j]) : JX_EMPTY_KEY;
-        a.vals[(size_t)i * a.R + j] = on ? (uint32_t)xid : JX_NONE_ID;
-    }
-    if (a.clean && lane == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
-}
-
-// The same rounds for consolidation after deletions (Sec. 4.6): the segment holds the whole candidate set of its
-// vertex, sorted by (distance, id); sets of at most 512 are pruned here and marked, larger ones are left to the
-// general kernel.
-__global__ void __launch_bounds__(64) consol_prune_u8_lean_kernel(InsertArgs a) {
-    __shared__ FwdLds<512> lds;
-    FwdLds<512>* F = &lds;
-    const int lane = lane_id();
-    const long long nseg = *a.nseg;
-    const long long total = a.E ? a.E : a.B * a.R;
-    for (long long s = blockIdx.x; s < nseg; s += gridDim.x) {
-        const uint32_t head = a.heads[s];
-        if (head & 0x80000000u) continue;
-        const long long lo = head;
-        const uint32_t v = (uint32_t)(a.keys[lo] >> 32);
-        if (v == JX_NONE_ID) continue;
-        int m = 0;
-        for (long long c0 = lo; c0 < total; c0 += 64) {
-            const long long j = c0 + lane;
-            const bool same = j < total && (uint32_t)(a.keys[j] >> 32) == v;
-            const uint64_t sm = ballot(same);
-            m += __builtin_popcountll(sm);
-            if (sm != ~0ull) break;
-        }
-        if (m > 512) continue;
-        wave_sync();  // the previous segment's reads of the LDS arrays are done
-        uint64_t alive[8];
-#pragma unroll
-        for (int h = 0; h < 8; h++) {
-            const int j = h * 64 + lane;
-            const bool valid = j < m;
-            if (valid) {
-                F->id[j] = a.vals[lo + j];
-                F->dx[j] = __uint_as_float((uint32_t)a.keys[lo + j]);
-            }
-            alive[h] = ballot(valid);
-        }
-        wave_sync();
-        const int nsel = multi_pivot_prune_u8<512>(F, a.ds.recs, alive, a.R, a.alpha);
-        uint32_t* row = a.adj + (size_t)v * a.R;
-        for (int j = lane; j < a.R; j += 64) row[j] = j < nsel ? F->sel_id[j] : JX_NONE_ID;
-        if (lane == 0) {
-            if (a.clean) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
-            const_cast<uint32_t*>(a.heads)[s] = head | 0x80000000u;
-        }
     }
 }
 
@@ -1523,16 +808,10 @@ static hipError_t launch_prune_shape(bool forward, const InsertArgs& a, hipStrea
 }
 
 hipError_t launch_forward_prune(int dtype, const InsertArgs& a, hipStream_t st) {
+    if (a.gram == 4) return launch_forward_prune_u8(a, st);
     if (a.gram) {
         hipError_t e = launch_forward_prune_gram(dtype, a, st);
         if (e != hipSuccess || a.L <= 128) return e;  // wider frontiers: the list-based kernel takes the rest
-    }
-    if (dtype == JX_U8 && !a.gram && a.ds.rec_stride == 128 && a.ds.nch == 8 && a.L <= 512) {
-        if (a.L <= 128)
-            hipLaunchKernelGGL(forward_prune_u8_lean_kernel<128>, dim3((unsigned)a.B), dim3(64), 0, st, a);
-        else
-            hipLaunchKernelGGL(forward_prune_u8_lean_kernel<512>, dim3((unsigned)a.B), dim3(64), 0, st, a);
-        return hipGetLastError();
     }
     if (dtype == JX_U8) return launch_prune_shape<K_U8>(true, a, st);
     if (dtype == JX_F16) return launch_prune_shape<K_F16>(true, a, st);
@@ -1540,24 +819,8 @@ hipError_t launch_forward_prune(int dtype, const InsertArgs& a, hipStream_t st) 
 }
 
 hipError_t launch_reverse_merge(int dtype, const InsertArgs& a, hipStream_t st) {
-    if (a.gram) {
-        hipError_t e = launch_reverse_merge_gram(dtype, a, st);
-        if (e != hipSuccess) return e;
-    }
-    if (dtype == JX_U8 && a.force_prune && a.ds.rec_stride == 128 && a.ds.nch == 8) {
-        // consolidation: candidate sets of at most 512 take the multi-pivot form
-        const long long want = a.E ? a.E : a.B * a.R;
-        const unsigned grid = (unsigned)(want < 8192 ? (want < 1 ? 1 : want) : 8192);
-        hipLaunchKernelGGL(consol_prune_u8_lean_kernel, dim3(grid), dim3(64), 0, st, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (dtype == JX_U8 && a.clean && !a.force_prune && a.ds.rec_stride == 128 && a.ds.nch == 8) {
-        // overflowing rows that are almost entirely their previous prune's output: lean kernel first
-        const long long want = a.E ? a.E : a.B * a.R;
-        const unsigned grid = (unsigned)(want < 8192 ? (want < 1 ? 1 : want) : 8192);
-        hipLaunchKernelGGL(reverse_merge_u8_lean_kernel, dim3(grid), dim3(64), 0, st, a);
-        hipError_t e = hipGetLastError();
+    if (a.gram) {  // then the list-based kernel: what these leave
+        hipError_t e = a.gram == 4 ? launch_reverse_merge_u8(a, st) : launch_reverse_merge_gram(dtype, a, st);
         if (e != hipSuccess) return e;
     }
     if (dtype == JX_U8) return launch_prune_shape<K_U8>(false, a, st);

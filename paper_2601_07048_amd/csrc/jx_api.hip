@@ -38,7 +38,7 @@ int fail(int code, const char* fmt, ...) {
 inline int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
 struct Layout {
-    int64_t vecs, adj, codes, P, centroid, stats, stripes, deleted, clean, work, work_bytes, total;
+    int64_t vecs, adj, codes, P, centroid, stats, stripes, deleted, work, work_bytes, total;
     int vec_bytes, code_bytes, meta_chunk, code_stride, plane_chunks, plane_shift;
 };
 
@@ -157,8 +157,6 @@ void layout(const jx_params* p, Layout* L) {
     off += 64 * 16 * 8;
     L->deleted = off;
     off += align256((int64_t)p->capacity + 4);
-    L->clean = off;
-    off += align256((int64_t)p->capacity + 4);
     // workspace: the larger of the insert phase and the query phase, at least 64 MiB
     const int64_t B = p->max_batch;
     InsertWork iw;
@@ -183,17 +181,15 @@ int64_t batch_cap(const jx_params& p, int64_t linked) {
     return c < 1 ? 1 : c;
 }
 
-// How robustPrune is computed: 0 = list-based kernels, 1 / 2 = Gram-matrix kernels for float32 / binary16 data (the
-// default for float data), 3 = Gram-matrix kernels for uint8 data (JX_FLAG_GRAM_U8)
+// How robustPrune is computed: 0 = list-based kernels (JX_FLAG_NO_GRAM), 1 / 2 / 3 = a workgroup and a Gram matrix per
+// prune for float32 / binary16 / uint8 data, 4 = a wavefront and 32 pivots per round, for uint8 vectors of at most 256
+// bytes: their matrix products cost next to nothing, and it looks only at what is still live (50,000 lists of 200, 128
+// bytes: 0.14 ms, the Gram matrix 0.8)
 int gram_mode(const jx_index* idx) {
     if (idx->flags & JX_FLAG_NO_GRAM) return 0;
-    if (idx->p.dtype == JX_U8) return (idx->flags & JX_FLAG_GRAM_U8) ? 3 : 0;
+    if (idx->p.dtype == JX_U8) return (idx->flags & JX_FLAG_GRAM_U8) || idx->vec_bytes > 256 ? 3 : 4;
     return idx->p.dtype == JX_F16 ? 2 : 1;
 }
-
-// Rows of uint8 indices remember how many leading entries one robustPrune call selected together, which lets the
-// next prune of the row skip the pairs among them
-bool incremental_prune(const jx_index* idx) { return !(idx->flags & JX_FLAG_NO_INCR_PRUNE); }
 
 hipError_t launch_tiled(const jx::BfArgs& a, hipStream_t st) {
     snprintf(g_bf_kernel, sizeof g_bf_kernel, "bruteforce_tile_kernel<%d> nsplit=%d", a.dtype, a.nsplit);
@@ -319,7 +315,6 @@ int jx_create(const jx_params* p, void* d_arena, int64_t arena_bytes, void* stre
     x->d_stats = (unsigned long long*)(x->d_arena + L.stats);
     x->d_stripes = (unsigned long long*)(x->d_arena + L.stripes);
     x->d_deleted = x->d_arena + L.deleted;
-    x->d_clean = x->d_arena + L.clean;
     x->d_work = x->d_arena + L.work;
     x->work_bytes = L.work_bytes;
     x->code_bytes = L.code_bytes;
@@ -331,7 +326,6 @@ int jx_create(const jx_params* p, void* d_arena, int64_t arena_bytes, void* stre
     hipError_t e = jx::launch_fill_u32(x->d_adj, (long long)p->capacity * p->R, JX_NONE, as_stream(stream));
     if (e == hipSuccess) e = jx::launch_fill_u32((uint32_t*)x->d_stats, 64, 0u, as_stream(stream));
     if (e == hipSuccess) e = jx::launch_fill_u32((uint32_t*)x->d_deleted, (p->capacity + 3) / 4, 0u, as_stream(stream));
-    if (e == hipSuccess) e = jx::launch_fill_u32((uint32_t*)x->d_clean, (p->capacity + 3) / 4, 0u, as_stream(stream));
     if (e != hipSuccess) {
         delete x;
         return fail(JX_EHIP, "arena initialisation: %s", hipGetErrorString(e));
@@ -378,7 +372,6 @@ int jx_import_graph(jx_index* idx, const void* d_vecs, int64_t n, const uint32_t
     JX_HIP(hipMemcpyAsync(idx->d_vecs, d_vecs, (size_t)n * idx->vec_bytes, hipMemcpyDeviceToDevice, st));
     JX_HIP(hipMemcpyAsync(idx->d_adj, d_adj, (size_t)n * idx->p.R * 4, hipMemcpyDeviceToDevice, st));
     if (n < idx->n) JX_HIP(jx::launch_fill_u32(idx->d_adj + (size_t)n * idx->p.R, (idx->n - n) * idx->p.R, JX_NONE, st));
-    JX_HIP(jx::launch_fill_u32((uint32_t*)idx->d_clean, (idx->p.capacity + 3) / 4, 0u, st));  // nothing is known about foreign rows
     if (idx->any_delete) {
         JX_HIP(jx::launch_fill_u32((uint32_t*)idx->d_deleted, (idx->p.capacity + 3) / 4, 0u, st));
         JX_HIP(jx::launch_fill_u32((uint32_t*)(idx->d_stats + 8), 2, 0u, st));
@@ -707,9 +700,6 @@ static int run_subbatch(jx_index* idx, const InsertWork& w, int64_t pos0, int64_
     a.heads = (const uint32_t*)(W + w.heads);
     a.nseg = (const uint32_t*)(W + w.counters);
     a.lists = (uint64_t*)(W + w.keys1);  // free once the edges are sorted
-    a.clean = incremental_prune(idx) ? idx->d_clean : nullptr;
-    // forward prune: no LDS vector cache.  A whole frontier (128 x 128 bytes per wavefront) would leave room for
-    // one workgroup per CU only, and the Gram-matrix form then measured slower (47 ms against 32 ms per 1M inserts)
     a.vec_cache_bytes = 0;
     a.gram = gram_mode(idx);
     JX_HIP(jx::launch_forward_prune(p.dtype, a, st));
@@ -990,7 +980,6 @@ int jx_consolidate(jx_index* idx, void* stream) {
     a.nseg = (const uint32_t*)(W + w.counters);
     a.lists = (uint64_t*)(W + w.keys0);
     a.force_prune = 1;
-    a.clean = incremental_prune(idx) ? idx->d_clean : nullptr;
     a.gram = gram_mode(idx);
     a.vec_cache_bytes = 12288;
     // 2. slices of consecutive vertices whose candidate lists fit the edge buffers; every new row is
@@ -1080,7 +1069,6 @@ int jx_compact(jx_index* idx, uint32_t* d_old_to_new, void* stream) {
     if (live > (uint64_t)n) return fail(JX_EHIP, "compaction counted %u live vertices of %lld", live, (long long)n);
     if (live < (uint64_t)n) JX_HIP(jx::launch_fill_u32(idx->d_adj + (size_t)live * p.R, (n - live) * p.R, JX_NONE, st));
     JX_HIP(jx::launch_fill_u32((uint32_t*)idx->d_deleted, (n + 3) / 4, 0u, st));
-    JX_HIP(jx::launch_fill_u32((uint32_t*)idx->d_clean, (n + 3) / 4, 0u, st));  // rows moved: start again from "nothing known"
     JX_HIP(jx::launch_fill_u32((uint32_t*)(idx->d_stats + 8), 2, 0u, st));
     idx->n = live;
     idx->entry = live ? new_entry : JX_NONE;

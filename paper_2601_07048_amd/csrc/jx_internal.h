@@ -84,16 +84,20 @@ struct InsertArgs {
     uint64_t* lists;            // Gram-matrix kernels: room for an entry per edge, segments by size
     long long E;                // reverse merge: number of sorted edges (0 = B * R)
     int force_prune;            // consolidation: ignore the existing row, always prune the candidate segment
-    int gram;                   // float data: 1 (float32) / 2 (binary16) = prunes of at most 128 candidates go to the Gram-matrix kernels
+    int gram;                   // 0 = list-based kernels only, 1 / 2 / 3 = Gram-matrix kernels (float32 / binary16 / uint8), 4 = pivot kernels (uint8)
     int vec_cache_bytes;        // reverse merge: LDS bytes per wavefront for candidate vectors (0 = never cache)
-    uint8_t* clean;             // [N] leading entries of each row that one robustPrune call selected together
-                                // (saturated at 255; 0 = nothing known), or NULL
 };
 
 hipError_t launch_entry_point(const void* vecs, int dtype, long long n, int d, double* partial, float* mean, double* dist,
                               uint32_t* out_id, hipStream_t st);
 hipError_t launch_forward_prune(int dtype, const InsertArgs& a, hipStream_t st);
 hipError_t launch_reverse_merge(int dtype, const InsertArgs& a, hipStream_t st);
+// splits the segments into lists[] by size and appends where the row still fits (prune_gram.hip); an entry of lists
+hipError_t launch_reverse_class(const InsertArgs& a, int small_max, int deg_max, hipStream_t st);
+__host__ __device__ inline int seg_deg(uint64_t entry) { return (int)(entry >> 44); }
+__host__ __device__ inline int seg_new(uint64_t entry) { return (int)(entry >> 32) & 4095; }
+hipError_t launch_forward_prune_u8(const InsertArgs& a, hipStream_t st);  // prune_u8.hip: vectors of at most 256 bytes
+hipError_t launch_reverse_merge_u8(const InsertArgs& a, hipStream_t st);
 hipError_t launch_forward_prune_gram(int dtype, const InsertArgs& a, hipStream_t st);
 hipError_t launch_reverse_merge_gram(int dtype, const InsertArgs& a, hipStream_t st);
 // Sorts n (key, value) pairs by key, then value (equal keys come in ascending order of their values) into keys_a / vals_a;
@@ -228,7 +232,6 @@ struct jx_index {
     unsigned long long* d_stats;  // [8] = vertices marked deleted so far, [10] scratch of jx_import_graph
     unsigned long long* d_stripes;  // [64][16] search counters (BeamArgs::stats)
     uint8_t* d_deleted;  // [capacity] 1 = logically deleted
-    uint8_t* d_clean;    // [capacity] see InsertArgs::clean
     int any_delete;      // a delete call has been made since the graph was created / imported
     uint32_t flags;      // JX_FLAG_* switches (jx_params.flags, jx_set_flags)
     // RaBitQ state

@@ -476,15 +476,15 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) forward_prune_gram_
         a.keys[(size_t)i * a.R + j] = on ? (((uint64_t)v << 32) | L->sel_dist[j]) : JX_EMPTY_KEY;
         a.vals[(size_t)i * a.R + j] = on ? (uint32_t)xid : JX_NONE_ID;
     }
-    if (a.clean && tid == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
 }
 
 // ---- reverse-edge merge (Alg. 4 step 3)
 // A thread per segment: appends where the row still fits, and lists the others by size, so that no workgroup of the
 // kernels below spends a chain of dependent loads on a segment that is not its own.  An entry holds the segment, the
-// degree of its row and the number of new edges (at most 1,023 are told apart); lists[0..) is the list of the small
-// ones, lists[.. E - 1] downwards that of the large ones.
-__global__ void __launch_bounds__(256) reverse_class_kernel(InsertArgs a) {
+// degree of its row and the number of new edges (at most 4,095 are told apart); lists[0..) is the list of the small
+// ones (at most small_max candidates), lists[.. E - 1] downwards that of the large ones; rows of more than deg_max
+// neighbours leave a large one too little room for new edges.
+__global__ void __launch_bounds__(256) reverse_class_kernel(InsertArgs a, int small_max, int deg_max) {
     const int lane = lane_id();
     const long long nseg = *a.nseg;
     const long long total = a.E ? a.E : a.B * a.R;
@@ -492,8 +492,9 @@ __global__ void __launch_bounds__(256) reverse_class_kernel(InsertArgs a) {
         const long long s = s0 + threadIdx.x;
         int cls = 0;
         uint64_t entry = 0;
-        if (s < nseg) {
-            const long long lo = a.heads[s];
+        const uint32_t head = s < nseg ? a.heads[s] : 0x80000000u;
+        if (!(head & 0x80000000u)) {  // not done by a kernel before
+            const long long lo = head;
             const uint32_t v = (uint32_t)(a.keys[lo] >> 32);
             long long known = 1, step = 1;  // keys[lo .. lo + known) belong to v
             while (lo + known + step - 1 < total && (uint32_t)(a.keys[lo + known + step - 1] >> 32) == v) {
@@ -521,8 +522,8 @@ __global__ void __launch_bounds__(256) reverse_class_kernel(InsertArgs a) {
                 for (int j = 0; j < (int)m; j++) row[deg + j] = a.vals[lo + j];
                 const_cast<uint32_t*>(a.heads)[s] = (uint32_t)lo | 0x80000000u;
             } else {
-                cls = deg + m <= GT_SMALL ? 1 : (deg <= GT_BIG - 64 ? 2 : 0);  // too little room for new ones: list-based kernel
-                entry = (uint64_t)s | ((uint64_t)((uint32_t)deg << 10 | (uint32_t)(m < 1023 ? m : 1023)) << 32);
+                cls = deg + m <= small_max ? 1 : (deg <= deg_max ? 2 : 0);
+                entry = (uint64_t)s | ((uint64_t)((uint32_t)deg << 12 | (uint32_t)(m < 4095 ? m : 4095)) << 32);
             }
         }
 #pragma unroll
@@ -550,7 +551,7 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) reverse_merge_gram_
     for (uint32_t at = blockIdx.x; at < n; at += gridDim.x) {
         const uint64_t entry = a.lists[NB == 4 ? (long long)at : total - 1 - at];
         const uint32_t s = (uint32_t)entry;
-        const int deg = (int)(entry >> 42), m = (int)(entry >> 32) & 1023;
+        const int deg = seg_deg(entry), m = seg_new(entry);
         const long long lo = a.heads[s];
         const uint32_t v = (uint32_t)(a.keys[lo] >> 32);
         uint32_t* row = a.adj + (size_t)v * a.R;
@@ -564,13 +565,16 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) reverse_merge_gram_
         const int nsel = team_prune<DT, NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, deg + mp, deg, v, a.R, a.alpha, mp < m);
         if (nsel >= 0) {
             for (int j = tid; j < a.R; j += NB * 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
-            if (tid == 0) {
-                if (a.clean) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
-                const_cast<uint32_t*>(a.heads)[s] = (uint32_t)lo | 0x80000000u;
-            }
+            if (tid == 0) const_cast<uint32_t*>(a.heads)[s] = (uint32_t)lo | 0x80000000u;
         }
         __syncthreads();
     }
+}
+
+hipError_t launch_reverse_class(const InsertArgs& a, int small_max, int deg_max, hipStream_t st) {
+    const long long want = ((a.E ? a.E : a.B * a.R) + 255) / 256;
+    hipLaunchKernelGGL(reverse_class_kernel, dim3((unsigned)(want < 1024 ? (want < 1 ? 1 : want) : 1024)), dim3(256), 0, st, a, small_max, deg_max);
+    return hipGetLastError();
 }
 
 template <int DT>
@@ -583,14 +587,12 @@ static hipError_t launch_forward_gram_dt(const InsertArgs& a, hipStream_t st) {
 template <int DT>
 static hipError_t launch_reverse_gram_dt(const InsertArgs& a, hipStream_t st) {
     const long long most = a.E ? a.E : a.B * a.R;  // segments there can be
-    auto grid = [&](long long per, long long cap) {
-        const long long want = (most + per - 1) / per;
-        return dim3((unsigned)(want < cap ? (want < 1 ? 1 : want) : cap));
-    };
-    hipLaunchKernelGGL(reverse_class_kernel, grid(256, 1024), dim3(256), 0, st, a);
+    auto grid = [&](long long cap) { return dim3((unsigned)(most < cap ? (most < 1 ? 1 : most) : cap)); };
+    hipError_t e = launch_reverse_class(a, GT_SMALL, GT_BIG - 64, st);
+    if (e != hipSuccess) return e;
     // persistent workgroups: as many as the card holds, twice over
-    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 4>), grid(1, 2048), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 8>), grid(1, 1024), dim3(512), 0, st, a);
+    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 4>), grid(2048), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 8>), grid(1024), dim3(512), 0, st, a);
     return hipGetLastError();
 }
 

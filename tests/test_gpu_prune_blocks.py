@@ -1,6 +1,7 @@
-"""robustPrune as one Gram matrix per workgroup: candidate lists around the edges of its 32-row blocks and of its two
+"""robustPrune on the matrix cores.  As one Gram matrix per workgroup: candidate lists around the edges of its 32-row blocks and of its two
 sizes (128, 256), with rows that end inside a 128-byte piece.  The data lie on a dyadic grid, where every partial sum is
-exact in float32 (and in the three bfloat16 parts of a value), so the adjacency table is the oracle's, bit for bit."""
+exact in float32 (and in the three bfloat16 parts of a value), so the adjacency table is the oracle's, bit for bit.
+In rounds of 32 pivots (uint8): the same edges, rows of one and of two 128-byte pieces, and hubs."""
 import numpy as np
 import pytest
 
@@ -61,3 +62,54 @@ def test_rows_that_are_not_finite(jx):
     g.insert(dev(x[300:]))
     adj = u32(g.export_graph()[0])
     assert np.all((adj < n) | (adj == 0xFFFFFFFF))
+
+
+@pytest.mark.parametrize("d", [16, 96, 128, 144, 256, 272])
+@pytest.mark.parametrize("R,L", [(8, 31), (12, 33), (31, 64), (33, 65), (64, 96), (63, 128), (100, 200), (256, 300)])
+def test_pivot_rounds_u8(jx, d, R, L):
+    """Frontiers of 31 to 300 entries, rows of 8 to 256; 272 bytes take the Gram matrix again."""
+    n = 700
+    x = random_data(n, d, np.uint8, seed=d + L)
+    ref = oracle.Index(d, np.uint8, R, L, 1.2, n, batch_growth=1.0)
+    gs = [jx.Index(d, jx.U8, R, L, 1.2, capacity=n, max_batch=n, batch_growth=1.0, flags=f) for f in (0, jx.FLAG_NO_GRAM)]
+    gone = np.random.default_rng(L).choice(n, n // 5, replace=False).astype(np.uint32)
+    ref.insert(x[:300]); ref.insert(x[300:])
+    before = ref.graph()[0].copy()
+    ref.delete(gone); ref.consolidate()
+    for g in gs:
+        g.insert(dev(x[:300])); g.insert(dev(x[300:]))
+        assert np.array_equal(u32(g.export_graph()[0]), before)
+        g.delete(dev(gone)); g.consolidate()
+        assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), "consolidated"
+
+
+@pytest.mark.parametrize("alpha", [1.0, 1.05, 1.9, 16.0, 1e30])
+def test_discard_limit_u8(jx, alpha):
+    """The largest distance at which a candidate is discarded is an integer found from d / alpha: extreme vectors, whose
+    distances reach 128 * 255^2, many equal distances, and factors that round either way."""
+    rng = np.random.default_rng(3)
+    x = rng.choice(np.array([0, 1, 254, 255], np.uint8), (600, 128))
+    x[::7] = rng.integers(0, 2, (len(x[::7]), 128), dtype=np.uint8)
+    ref = oracle.Index(128, np.uint8, 24, 100, alpha, 600)
+    g = jx.Index(128, jx.U8, 24, 100, alpha, capacity=600, max_batch=600)
+    ref.insert(x)
+    g.insert(dev(x))
+    assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0])
+
+
+@pytest.mark.parametrize("copies", [0, 900, 4000])
+def test_hub_u8(jx, copies):
+    """A centre that every point links to: more reverse edges than the first pool (512) and the second (2,048) hold.  With
+    copies of three points next to it the closest 512 or 2,048 yield fewer than R neighbours, and the next kernel goes on."""
+    rng = np.random.default_rng(8)
+    d, R = 128, 16
+    shell = np.clip(np.rint(128 + rng.normal(0, 25, (1500, d))), 0, 255).astype(np.uint8)
+    near = 128 + 4 * np.eye(d, dtype=np.int64)[rng.integers(0, 3, copies)]
+    x = np.concatenate([np.full((1, d), 128, np.uint8), near.astype(np.uint8), shell])
+    n = len(x)
+    ref = oracle.Index(d, np.uint8, R, 24, 1.2, n, batch_growth=1.0)
+    g = jx.Index(d, jx.U8, R, 24, 1.2, capacity=n, max_batch=n, batch_growth=1.0)
+    ref.insert(x[:1]); g.insert(dev(x[:1]))
+    for lo in range(1, n, 2700):  # the first of these batches is as large as max_batch lets it be
+        ref.insert(x[lo:lo + 2700]); g.insert(dev(x[lo:lo + 2700]))
+        assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), lo
