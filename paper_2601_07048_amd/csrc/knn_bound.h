@@ -24,8 +24,14 @@ JX_HD float knn_threshold(float lim, float qq) { return (lim - qq) + (lim + qq) 
 // operations of the two.  |b| is at most the longest vector's (bb_max = |b|^2, infinity: unknown), and at most |q| + sqrt(e)
 // by the triangle inequality, the rounding of e included by the last factor.  Holds up to KNN_FLOAT_D dimensions
 #define KNN_FLOAT_D 65536
-JX_HD float knn_eps(int d, float qq, float e, float bb_max) {
-    const float c = (float)(d + 16) * 1.2e-7f;
+// parts: what the values of the norm form lack, as a share of (|q| + |b|)^2.  float32 values go to the matrix cores as two
+// bfloat16 parts, x = h + l + r with |l| <= 2^-9 |x| and |r| <= 2^-18 |x|, and h h' + h l' + l h' leaves out l l', h r' and r h':
+// at most 3.02 2^-18 |q| |b|, twice that in 2 <q, b>, and |q| |b| is at most a quarter of (|q| + |b|)^2.  An instruction takes
+// 16 coordinates and is off by at most 8 2^-24 of its largest term, subnormals are kept (measured): 3 d / 16 of them in a row
+// by 1.5 d 2^-24 |q| |b|, which the first bound covers
+#define KNN_BF16_PARTS 6e-6f
+JX_HD float knn_eps(int d, float qq, float e, float bb_max, float parts = 0.f) {
+    const float c = (float)(d + 16) * 1.2e-7f + parts;
     float len = (2.f * sqrtf(qq) + sqrtf(e)) * (1.f + sqrtf(c));
     const float all = sqrtf(qq) + sqrtf(bb_max);
     if (all < len) len = all;

@@ -4,14 +4,14 @@
 // four wavefronts computes a 64 x 64 block of <q, b> (32x32 MFMA tiles, operands staged through LDS in slabs of 128
 // bytes a row, the next slab on its way in registers), and d = |q|^2 + |b|^2 - 2 <q, b> is compared with the query's
 // threshold, one add and one compare per pair.  What passes is appended to a 32-entry buffer of the query in LDS; a
-// buffer that is half full is merged into the query's sorted list of this slice (global memory, L2) by one wavefront,
-// which also renews the threshold.  With m slices the largest of their r-th distances, r = ceil(k / m), bounds the k-th
-// of all: every slice publishes its r-th, so a slice accepts little that the whole set would not accept (the k-th of its
-// own m-th part of the base set would let m times as much pass: 1,562 vectors and k = 128 made 450 entries a query).
+// buffer that is nearly full is merged into the query's sorted list of this slice (global memory, L2) by one wavefront,
+// which also renews the threshold: every slice publishes a few of its smallest distances, and enough of all slices'
+// published ones bound the k-th of all (knn_limit), so a slice accepts little that the whole set would not accept.
 //
 //   uint8            v_mfma_i32_32x32x32_i8 on the values shifted by -128 (distances do not change): exact integers, so
 //                    the lists hold the result.
-//   float32/binary16 v_mfma_f32_32x32x2_f32 / 32x32x16_f16: these distances only choose KNN_SLACK more candidates
+//   float32/binary16 v_mfma_f32_32x32x16_bf16 on two bfloat16 parts of each value (three products: 96 cycles for 16
+//                    coordinates, 512 by 32x32x2_f32) / 32x32x16_f16: these distances only choose KNN_SLACK more candidates
 //                    than asked for.  The merge kernel evaluates them with the arithmetic of bruteforce_tile_kernel,
 //                    operation by operation, orders them, and proves that nothing left out can be among the first
 //                    k: the first distance left out, less the error bound of both forms (knn_bound.h), has to exceed
@@ -19,10 +19,11 @@
 //                    Queries for which it does not (ties, sets far from the origin) are flagged, and their tiles are done
 //                    again by bruteforce_tile_kernel.  So the result is that kernel's, bit for bit.
 //
-// Bound: matrix cores for float32 (1.8 of 2.5 ms below, 107 TFLOP/s), vector instructions and barriers for uint8 (2.9 of
-// 4.3 ms without a single candidate).  Against bruteforce_tile_kernel: 10,000 x 1M uint8 d = 128, k = 10 27.2 -> 4.31 ms;
-// 1,000 x 100,003 float32 d = 960, k = 100 13.0 -> 2.55 ms; 1,000 x 100,000 binary16 d = 960, k = 10 3.97 -> 0.84 ms;
-// 2 x 234,001 float32 d = 128, k = 1 1.12 -> 0.17 ms.  Without the seeds the lists fill with what comes first: 5.6 and 5.3 ms.
+// Bound: float32 staging and barriers, a slab in 1.85 us where its products take 0.64 (0.68 of the 1.1 ms below; 1.8 ms on the
+// float32 instruction), uint8 likewise (2.0 of 2.75 ms), then appends and merges.  Against bruteforce_tile_kernel:
+// 10,000 x 1M uint8 d = 128, k = 10 27.2 -> 2.72 ms; 1,000 x 100,003 float32 d = 960, k = 100 13.0 -> 1.16 ms; 1,000 x 100,000
+// binary16 d = 960, k = 10 3.97 -> 0.58 ms; 100 x 1M uint8 d = 128, k = 10 0.076 ms.  Without the seeds the lists fill with
+// what comes first: 5.6 and 5.3 ms before these forms.
 #include <stdio.h>
 #include "jx_distance.h"
 #include "knn_bound.h"
@@ -33,18 +34,23 @@ typedef float kf32x16 __attribute__((ext_vector_type(16)));
 typedef int ki32x16 __attribute__((ext_vector_type(16)));
 typedef int ki32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 kf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 kbf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 kbf16x2 __attribute__((ext_vector_type(2)));
+typedef float kf32x2 __attribute__((ext_vector_type(2)));
 
 #define KT 128        // queries per workgroup, base vectors per step
 #define KROW 144      // bytes of a staged row: 128 and 16 of padding
 #define KCAP 32       // buffer entries per query
-#define KFLUSH 16     // a buffer with this many entries is merged
+#define KFLUSH 28     // a buffer with this many entries is merged: with 16, 24, 28 1,000 x 300,000 uint8 d = 96, k = 100 1,153, 966, 852 us
 #define KU8_ROW 16384    // uint8: longest row, see KINF
 // uint8: above every distance (16,384 x 255^2 is just under 2^30), and no sum overflows: 2 <q, b> of the shifted values is at most
 // 2^29, |q|^2 at most 2^28, so 2 <q, b> + KINF - |q|^2 stays below 2^31 and 2 <q, b> - |b|^2 above -2^30
 #define KINF 0x50000000
 
 #define KNN_SLACK 28  // float types: candidates kept beyond k
-#define KNN_BLOCKS 512
+#define KNN_BLOCKS 512   // and so the largest number of slices
+#define KNN_ENTRIES 512  // published distances of a query, all slices
+#define KNN_PUB 8        // ... of one slice
 #define KNN_ODD 30  // rows that are listed for the merge of a query tile, see KnnOdd
 
 // Rows of the base set that no threshold can decide on: float32 with a NaN, binary16 with a NaN or an infinity.  They are kept
@@ -58,6 +64,9 @@ struct KnnOdd {
 template <int DT>
 constexpr uint32_t KNN_DECIDABLE = DT == JX_F16 ? 0x7F800000u : 0x7F800001u;  // bits of |b|^2 from which a row is one of those
 
+template <int DT>
+constexpr float KNN_SPLIT = DT == JX_F32 ? KNN_BF16_PARTS : 0.f;
+
 struct KnnArgs {
     const void* base;
     const void* queries;
@@ -66,10 +75,11 @@ struct KnnArgs {
     int k, kp;          // neighbours asked for, kept per list
     int nsplit;
     uint64_t* lists;    // [nq][nsplit][kp] keys (distance, id)
-    uint32_t* published;  // [nq][nsplit] r_th-th distance of each slice, or NULL
+    uint32_t* published;  // [nq][nsplit][pub] distances of each slice's entries 2^pub_shift - 1, 2 2^pub_shift - 1, .., or NULL
     int r_th;           // ceil(kp / nsplit)
+    int pub, pub_shift;
     int seed_steps;     // > 0: the slices' first thresholds come from their first seed_steps steps
-    uint32_t* redo;     // [nq] float types: 1 = the merge could not prove the result
+    uint32_t* redo;     // [nq] the first limits, then (float types) 1 = the merge could not prove the result
     KnnOdd* odd;        // [tiles of KT queries] float types
     uint4* hopeless;    // [tiles][nsplit] float types: a bit per query that can hardly be proven, as far as the slice can tell
     uint32_t* out_ids;
@@ -86,8 +96,9 @@ struct KnnLds {
     uint32_t fill[KT];  // entries of the query's list
     uint32_t lim[KT];   // threshold: int / float bits, exclusive
     uint32_t t[KT];     // lim - |q|^2 (floats: knn_threshold)
-    uint32_t qn[KT], bn[KT];
+    uint32_t qn[KT], bn[2 * KT];
     uint32_t again;
+    uint32_t flag[3];   // of a step modulo 3: it has filled a buffer, nearly at least
 };
 
 // A chunk on its way to LDS: outside the rows or the vector the load has read another one (no branch holds it up), and
@@ -101,6 +112,26 @@ __device__ __forceinline__ uint4 knn_stage(uint4 v, const bool in) {
         v.w ^= 0x80808080u;
     }
     return make_uint4(in ? v.x : 0u, in ? v.y : 0u, in ? v.z : 0u, in ? v.w : 0u);
+}
+
+// Four float32 values on their way to LDS as bfloat16: rounded, and what that leaves, rounded again
+__device__ __forceinline__ void knn_split(uint4* row, const int sch, const uint4 v) {
+    float x[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+    uint2 part[2];
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+        uint32_t h[2];
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const kf32x2 two = {x[2 * i], x[2 * i + 1]};
+            h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, kbf16x2));
+            x[2 * i] -= __uint_as_float(h[i] << 16);
+            x[2 * i + 1] -= __uint_as_float(h[i] & 0xFFFF0000u);
+        }
+        part[p] = make_uint2(h[0], h[1]);
+    }
+    reinterpret_cast<uint2*>(row)[sch] = part[0];
+    reinterpret_cast<uint2*>(row)[8 + sch] = part[1];
 }
 
 template <int DT>
@@ -133,13 +164,66 @@ __device__ __forceinline__ typename KAcc<DT>::elem knn_val(uint32_t b) {
         return __uint_as_float(b);
 }
 
+// A bound on the kp-th distance from what the slices have published for a query, plus one; 0x7F800000 if that is too little.
+// Value r of a slice says that (r + 1) 2^pub_shift of its vectors are no farther, at any time (values only fall, in whatever
+// order they are seen), so 2^pub_shift times the values <= t is at most the number of vectors within t: the need-th smallest
+// value, need = ceil(kp / 2^pub_shift).  It is found by halving the range, 16 times at most: what is left above it, 2^-16 of
+// the range, lets next to nothing in.  The largest r_th-th distance of the slices, which needs one value per slice, let in
+// two to seven times as much: search launch of 1,000 x 100,003 float32 d = 960, k = 100 1,220 -> 1,136 us, of 10,000 x 1M
+// uint8, k = 10 4,374 -> 3,998
+struct KnnPublished {
+    uint32_t v[KNN_ENTRIES / 64];
+    // before other work: what takes its time is the way to memory that all XCDs see
+    __device__ __forceinline__ void load(const uint32_t* published, const int entries, const int lane) {
+#pragma unroll
+        for (int r = 0; r < KNN_ENTRIES / 64; r++) {
+            v[r] = 0x7F800000u;
+            if (r * 64 < entries && r * 64 + lane < entries) v[r] = __hip_atomic_load(published + r * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+};
+__device__ __forceinline__ uint32_t knn_limit(const KnnPublished& p, const int entries, const int need) {
+    uint32_t lo = 0x7F800000u, hi = 0;
+    int have = 0;
+#pragma unroll
+    for (int r = 0; r < KNN_ENTRIES / 64; r++) {
+        if (r * 64 < entries) {  // uniform
+            const bool on = p.v[r] < 0x7F800000u;
+            have += __builtin_popcountll(ballot(on));
+            lo = p.v[r] < lo ? p.v[r] : lo;
+            hi = on && p.v[r] > hi ? p.v[r] : hi;
+        }
+    }
+    if (have < need) return 0x7F800000u;
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+        const uint32_t l = shfl_xor(lo, x), h = shfl_xor(hi, x);
+        lo = l < lo ? l : lo;
+        hi = h > hi ? h : hi;
+    }
+    lo = readlane32(lo, 0);
+    hi = readlane32(hi, 0);
+    for (int step = 0; step < 16 && lo < hi; step++) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        int c = 0;
+#pragma unroll
+        for (int r = 0; r < KNN_ENTRIES / 64; r++)
+            if (r * 64 < entries) c += __builtin_popcountll(ballot(p.v[r] <= mid));
+        if (c >= need) hi = mid;
+        else lo = mid + 1;
+    }
+    return hi + 1u;  // equal distances stay in (their ids may be smaller)
+}
+
 // One wavefront merges the buffer of query row q into its list (sorted keys, kp at most) and renews the threshold.
 // NL: list entries per lane.
 template <int DT, int NL>
 __device__ __forceinline__ void knn_flush(KnnLds& S, const int q, uint64_t* list, const int kp, uint32_t* published, const int nsplit,
-                                          const int split, const int r_th, const int lane) {
+                                          const int split, const int pub, const int shift, const int lane) {
     const int n_old = (int)S.fill[q];
     const int m = (int)S.cnt[q] < KCAP ? (int)S.cnt[q] : KCAP;
+    KnnPublished others;
+    if (published) others.load(published, nsplit * pub, lane);
     uint64_t old[NL];
     uint32_t to[NL];
 #pragma unroll
@@ -161,33 +245,22 @@ __device__ __forceinline__ void knn_flush(KnnLds& S, const int q, uint64_t* list
         at += (lane == i ? rank : 0u) + (s < mine ? 1u : 0u);
     }
     const int n_new = n_old + m < kp ? n_old + m : kp;
-    uint32_t last = 0, rth = 0;  // distances of entries kp - 1 and r_th - 1
-    bool has = false, has_r = false;
-#pragma unroll
-    for (int r = 0; r < NL; r++) {
-        if (r * 64 + lane < n_old && to[r] < (uint32_t)kp) {
-            list[to[r]] = old[r];
-            if (to[r] == (uint32_t)kp - 1u) {
-                last = (uint32_t)(old[r] >> 32);
-                has = true;
-            }
-            if (to[r] == (uint32_t)r_th - 1u) {
-                rth = (uint32_t)(old[r] >> 32);
-                has_r = true;
-            }
-        }
-    }
-    if (lane < m && at < (uint32_t)kp) {
-        list[at] = mine;
-        if (at == (uint32_t)kp - 1u) {
-            last = (uint32_t)(mine >> 32);
+    uint32_t last = 0;  // distance of entry kp - 1
+    bool has = false;
+    auto place = [&](const uint64_t key, const uint32_t p) {
+        const uint32_t dist = (uint32_t)(key >> 32);
+        list[p] = key;
+        if (p == (uint32_t)kp - 1u) {
+            last = dist;
             has = true;
         }
-        if (at == (uint32_t)r_th - 1u) {
-            rth = (uint32_t)(mine >> 32);
-            has_r = true;
-        }
-    }
+        if (published && p < (uint32_t)(pub << shift) && ((p + 1) & ((1u << shift) - 1u)) == 0u)
+            __hip_atomic_store(published + split * pub + (p >> shift), dist, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+#pragma unroll
+    for (int r = 0; r < NL; r++)
+        if (r * 64 + lane < n_old && to[r] < (uint32_t)kp) place(old[r], to[r]);
+    if (lane < m && at < (uint32_t)kp) place(mine, at);
     __threadfence_block();  // the next merge of this list reads it with other lanes
     const uint64_t who = ballot(has);
     uint32_t lim = S.lim[q];
@@ -196,22 +269,8 @@ __device__ __forceinline__ void knn_flush(KnnLds& S, const int q, uint64_t* list
         if (own < lim) lim = own;  // ids of later steps are larger: a distance equal to the last one's is out
     }
     if (published) {
-        if (has_r) __hip_atomic_store(published + split, rth, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t most = 0;
-        for (int s = lane; s < nsplit; s += 64) {
-            uint32_t v = __hip_atomic_load(published + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (s == split) v = 0;  // this slice's own is below its threshold anyway
-            most = v > most ? v : most;
-        }
-#pragma unroll
-        for (int x = 1; x < 64; x <<= 1) {
-            const uint32_t o = shfl_xor(most, x);
-            most = o > most ? o : most;
-        }
-        const uint64_t wr = ballot(has_r);
-        const uint32_t mine_r = wr ? readlane32(rth, __builtin_ctzll(wr)) : 0xFFFFFFFEu;  // fewer than r_th entries yet
-        most = mine_r > most ? mine_r : most;
-        if (most + 1u < lim) lim = most + 1u;  // equal distances stay in (their ids may be smaller)
+        const uint32_t all = knn_limit(others, nsplit * pub, (kp + (1 << shift) - 1) >> shift);
+        if (all < lim) lim = all;
     }
     if (lane == 0) {
         S.lim[q] = lim;
@@ -223,6 +282,16 @@ __device__ __forceinline__ void knn_flush(KnnLds& S, const int q, uint64_t* list
         S.cnt[q] = 0;
     }
     wave_sync();
+}
+
+// The first limits, a wavefront per query
+__global__ void __launch_bounds__(64) knn_limit_kernel(KnnArgs a) {
+    const long long qi = blockIdx.x;
+    const int lane = threadIdx.x;
+    KnnPublished p;
+    p.load(a.published + (size_t)qi * a.nsplit * a.pub, a.nsplit * a.pub, lane);
+    const uint32_t lim = knn_limit(p, a.nsplit * a.pub, (a.kp + (1 << a.pub_shift) - 1) >> a.pub_shift);
+    if (lane == 0) a.redo[qi] = lim;
 }
 
 // Largest value of the wavefront, in every lane
@@ -260,7 +329,57 @@ __device__ __forceinline__ uint2 knn_hopeless(const KnnArgs& a, const long long 
     return make_uint2(w[0] | w[1], w[2] | w[3]);
 }
 
-// ONE: vectors of one slab; the queries stay in LDS.
+// What a seed launch publishes: best = largest 2 <q, b> - |b|^2 of each of the thread's 64 elements, 128 columns of a query in
+// all; of the columns the first pub 2^pub_shift
+template <int DT>
+__device__ __forceinline__ void knn_publish(KnnLds& S, const KnnArgs& a, const typename KAcc<DT>::elem (&best)[64], const long long q0, const int split) {
+    typedef typename KAcc<DT>::elem elem_t;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
+    elem_t* cols = reinterpret_cast<elem_t*>(&S.buf[0][0]);  // [64][128]
+    static_assert(sizeof(S.buf) >= 64 * 128 * 4, "columns of 64 queries");
+    for (int h = 0; h < 2; h++) {  // 64 queries at a time
+        if (wm == h) {
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+#pragma unroll
+                for (int j = 0; j < 2; j++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++)
+                        cols[(i * 32 + 8 * (e >> 2) + 4 * half + (e & 3)) * 128 + wn * 64 + j * 32 + col] = best[(i * 2 + j) * 16 + e];
+        }
+        __syncthreads();
+        for (int r = wave; r < 64; r += 4) {
+            const long long qi = q0 + h * 64 + r;
+            if (qi >= a.nq) break;
+            elem_t x = cols[r * 128 + lane], y = cols[r * 128 + 64 + lane];
+            const elem_t none = DT == JX_U8 ? (elem_t)-0x7FFFFFFF : (elem_t)-__builtin_inff();
+            const elem_t qn = knn_val<DT>(S.qn[h * 64 + r]);
+            for (int k = 0; k < a.pub << a.pub_shift; k++) {
+                const elem_t m = knn_wave_max<elem_t>(x > y ? x : y);
+                const uint64_t hx = ballot(x == m), hy = ballot(y == m);
+                if (hx) {
+                    if (lane == __builtin_ctzll(hx)) x = none;
+                } else if (hy) {
+                    if (lane == __builtin_ctzll(hy)) y = none;
+                }
+                uint32_t code = 0x7F800000u;
+                if constexpr (DT == JX_U8) {
+                    if (m > -0x40000000) code = (uint32_t)(qn - m);
+                } else {
+                    const float d = fmaxf(qn - m, 0.f);
+                    if (d < __builtin_inff() && m > -__builtin_inff()) code = __float_as_uint(d);
+                }
+                if (lane == 0) {
+                    if (((k + 1) & ((1 << a.pub_shift) - 1)) == 0) a.published[((size_t)qi * a.nsplit + split) * a.pub + (k >> a.pub_shift)] = code;
+                    if (k == a.r_th - 1) S.lim[h * 64 + r] = code;
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // SEED: only the slice's first a.seed_steps steps, to publish a first r_th distance before the search begins: the
 // smallest distance of each of the 128 columns over the steps, then the r_th smallest of these.  It is no smaller than
 // the r_th of all that was seen.  Float types: a query whose distances can be off by more than a share of that first
@@ -271,15 +390,15 @@ __device__ __forceinline__ uint2 knn_hopeless(const KnnArgs& a, const long long 
 // 1,000 from the origin, k = 10, with the stop / without / the tiled kernel alone: 256 x 100,003 float32 d = 960 4,330 / 5,190
 // / 4,216 us, 1,000 x 200,000 float32 d = 128 1,893 / 3,270 / 1,822, 256 x 100,000 binary16 d = 960 1,891 / 2,298 / 1,817.
 // What only the finished lists show is paid twice: 29 or more copies of every vector 5,103 / 4,216 and 2,971 / 1,860
-template <int DT, int NL, bool ONE, bool SEED>
+template <int DT, int NL, bool SEED>
 __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
     typedef typename KAcc<DT>::type acc_t;
     typedef typename KAcc<DT>::elem elem_t;
     __shared__ KnnLds S;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
-    const long long q0 = (long long)blockIdx.x * KT;
-    const int split = blockIdx.y;
+    const int tile = blockIdx.x, split = blockIdx.y;
+    const long long q0 = (long long)tile * KT;
     const long long steps = (a.n + KT - 1) / KT;  // every slice has as many, or one more
     const long long b_begin = split * steps / a.nsplit * KT;
     long long b_end = (split + 1) * steps / a.nsplit * KT;
@@ -287,7 +406,7 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
     if (SEED && b_end > b_begin + (long long)a.seed_steps * KT) b_end = b_begin + (long long)a.seed_steps * KT;
     const uint8_t* Q = reinterpret_cast<const uint8_t*>(a.queries);
     const uint8_t* B = reinterpret_cast<const uint8_t*>(a.base);
-    const int nslab = ONE ? 1 : (a.nch + 7) / 8;
+    const int nslab = (a.nch + 7) / 8;
     const int srow = tid >> 3, sch = tid & 7;  // staging: 8 threads per row, rows srow + 32 t
 
     for (int i = tid; i < KT; i += 256) {
@@ -295,23 +414,19 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
         S.fill[i] = 0;
         uint32_t lim = DT == JX_U8 ? (uint32_t)KINF : 0x7F800000u;
         if (!SEED && a.seed_steps && q0 + i < a.nq) {
-            uint32_t most = 0;
-            for (int s = 0; s < a.nsplit; s++) {
-                const uint32_t v = a.published[(size_t)(q0 + i) * a.nsplit + s];
-                most = v > most ? v : most;
-            }
-            if (most + 1u < lim) lim = most + 1u;
+            const uint32_t first = a.redo[q0 + i];
+            if (first < lim) lim = first;
         }
         S.lim[i] = lim;
     }
     if constexpr (DT != JX_U8 && !SEED) {
         if (a.seed_steps) {
-            const uint2 w = knn_hopeless(a, blockIdx.x, lane);
+            const uint2 w = knn_hopeless(a, tile, lane);
             if (w.x && (w.y || q0 + 64 >= a.nq)) return;  // the whole workgroup
         }
     }
     if (tid == 0) S.again = 0;
-    if (SEED && DT != JX_U8 && split == 0 && tid < 2) (&a.odd[blockIdx.x].count)[tid] = 0u;  // count and bb_max
+    if (SEED && DT != JX_U8 && split == 0 && tid < 2) (&a.odd[tile].count)[tid] = 0u;  // count and bb_max
     __syncthreads();
     elem_t best[SEED ? 64 : 1];  // largest 2 <q, b> - |b|^2 of each element
     if constexpr (SEED) {
@@ -325,15 +440,13 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
     auto at = [&](const uint8_t* base, const long long row, const long long rows, const int ch) {
         return load16(base + (size_t)(row < rows ? row : rows - 1) * row_bytes + (size_t)((ch < a.nch ? ch : a.nch - 1) * 16));
     };
-    auto fetch = [&](const long long b0, const int slab, const bool queries) {
+    auto fetch = [&](const long long b0, const int slab) {
 #pragma unroll
         for (int t = 0; t < 4; t++) pb[t] = at(B, b0 + srow + 32 * t, b_end, slab * 8 + sch);
-        if (queries) {
 #pragma unroll
-            for (int t = 0; t < 4; t++) pa[t] = at(Q, q0 + srow + 32 * t, a.nq, slab * 8 + sch);
-        }
+        for (int t = 0; t < 4; t++) pa[t] = at(Q, q0 + srow + 32 * t, a.nq, slab * 8 + sch);
     };
-    if (b_begin < b_end) fetch(b_begin, 0, true);
+    if (b_begin < b_end) fetch(b_begin, 0);
 
     for (long long b0 = b_begin; b0 < b_end; b0 += KT) {
         const bool first = b0 == b_begin;
@@ -346,17 +459,22 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                 for (int e = 0; e < 16; e++) acc[i][j][e] = 0;
         elem_t nb[4] = {0, 0, 0, 0}, nq[4] = {0, 0, 0, 0};
         for (int slab = 0; slab < nslab; slab++) {
-            const bool queries = first || !ONE;
 #pragma unroll
             for (int t = 0; t < 4; t++) {
                 const bool chunk = slab * 8 + sch < a.nch;
-                if (queries) {
+                {
                     const uint4 v = knn_stage<DT>(pa[t], chunk && q0 + srow + 32 * t < a.nq);
-                    S.a[(srow + 32 * t) * (KROW / 16) + sch] = v;
+                    if constexpr (DT == JX_F32)
+                        knn_split(S.a + (srow + 32 * t) * (KROW / 16), sch, v);
+                    else
+                        S.a[(srow + 32 * t) * (KROW / 16) + sch] = v;
                     if (first) nq[t] = knn_sq<DT>(v, nq[t]);
                 }
                 const uint4 v = knn_stage<DT>(pb[t], chunk && b0 + srow + 32 * t < b_end);
-                S.b[(srow + 32 * t) * (KROW / 16) + sch] = v;
+                if constexpr (DT == JX_F32)
+                    knn_split(S.b + (srow + 32 * t) * (KROW / 16), sch, v);
+                else
+                    S.b[(srow + 32 * t) * (KROW / 16) + sch] = v;
                 nb[t] = knn_sq<DT>(v, nb[t]);
             }
             if (slab == nslab - 1) {  // norms: the 8 threads of a row
@@ -393,41 +511,57 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                             if (norm[t] < KNN_DECIDABLE<DT>) {
                                 bmax = max(bmax, norm[t]);
                             } else {
-                                const uint32_t to = atomicAdd(&a.odd[blockIdx.x].count, 1u);
-                                if (to < KNN_ODD) a.odd[blockIdx.x].id[to] = (uint32_t)(b0 + srow + 32 * t);
+                                const uint32_t to = atomicAdd(&a.odd[tile].count, 1u);
+                                if (to < KNN_ODD) a.odd[tile].id[to] = (uint32_t)(b0 + srow + 32 * t);
                             }
                         }
                     }
                 }
             }
             __syncthreads();
-            if (!ONE && slab + 1 < nslab)
-                fetch(b0, slab + 1, true);
+            if (slab + 1 < nslab)
+                fetch(b0, slab + 1);
             else if (b0 + KT < b_end)
-                fetch(b0 + KT, 0, !ONE);
+                fetch(b0 + KT, 0);
+            if constexpr (DT == JX_F32) {
 #pragma unroll
-            for (int s = 0; s < 4; s++) {
-                uint4 fa[2], fb[2];
+                for (int s = 0; s < 2; s++) {
+                    kbf16x8 fa[2][2], fb[2][2];  // [tile][part]
 #pragma unroll
-                for (int i = 0; i < 2; i++) {
-                    fa[i] = S.a[(wm * 64 + i * 32 + col) * (KROW / 16) + s * 2 + half];
-                    fb[i] = S.b[(wn * 64 + i * 32 + col) * (KROW / 16) + s * 2 + half];
-                }
+                    for (int i = 0; i < 2; i++)
 #pragma unroll
-                for (int i = 0; i < 2; i++)
-#pragma unroll
-                    for (int j = 0; j < 2; j++) {
-                        if constexpr (DT == JX_U8) {
-                            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(ki32x4, fa[i]), __builtin_bit_cast(ki32x4, fb[j]), acc[i][j], 0, 0, 0);
-                        } else if constexpr (DT == JX_F16) {
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(kf16x8, fa[i]), __builtin_bit_cast(kf16x8, fb[j]), acc[i][j], 0, 0, 0);
-                        } else {
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[i].x), __uint_as_float(fb[j].x), acc[i][j], 0, 0, 0);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[i].y), __uint_as_float(fb[j].y), acc[i][j], 0, 0, 0);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[i].z), __uint_as_float(fb[j].z), acc[i][j], 0, 0, 0);
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[i].w), __uint_as_float(fb[j].w), acc[i][j], 0, 0, 0);
+                        for (int p = 0; p < 2; p++) {
+                            fa[i][p] = __builtin_bit_cast(kbf16x8, S.a[(wm * 64 + i * 32 + col) * (KROW / 16) + p * 4 + s * 2 + half]);
+                            fb[i][p] = __builtin_bit_cast(kbf16x8, S.b[(wn * 64 + i * 32 + col) * (KROW / 16) + p * 4 + s * 2 + half]);
                         }
+#pragma unroll
+                    for (int i = 0; i < 2; i++)
+#pragma unroll
+                        for (int j = 0; j < 2; j++) {
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][1], fb[j][0], acc[i][j], 0, 0, 0);
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][0], fb[j][1], acc[i][j], 0, 0, 0);
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][0], fb[j][0], acc[i][j], 0, 0, 0);
+                        }
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; s++) {
+                    uint4 fa[2], fb[2];
+#pragma unroll
+                    for (int i = 0; i < 2; i++) {
+                        fa[i] = S.a[(wm * 64 + i * 32 + col) * (KROW / 16) + s * 2 + half];
+                        fb[i] = S.b[(wn * 64 + i * 32 + col) * (KROW / 16) + s * 2 + half];
                     }
+#pragma unroll
+                    for (int i = 0; i < 2; i++)
+#pragma unroll
+                        for (int j = 0; j < 2; j++) {
+                            if constexpr (DT == JX_U8)
+                                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(ki32x4, fa[i]), __builtin_bit_cast(ki32x4, fb[j]), acc[i][j], 0, 0, 0);
+                            else
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(kf16x8, fa[i]), __builtin_bit_cast(kf16x8, fb[j]), acc[i][j], 0, 0, 0);
+                        }
+                }
             }
             if (slab + 1 < nslab) __syncthreads();  // else the barrier behind the appends stands before the next write
         }
@@ -514,7 +648,8 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                 const int q = wave * 32 + __builtin_ctzll(need);
                 need &= need - 1ull;
                 knn_flush<DT, NL>(S, q, a.lists + ((size_t)(q0 + q) * a.nsplit + split) * a.kp, a.kp,
-                                   a.published ? a.published + (size_t)(q0 + q) * a.nsplit : nullptr, a.nsplit, split, a.r_th, lane);
+                                   a.published ? a.published + (size_t)(q0 + q) * a.nsplit * a.pub : nullptr, a.nsplit, split, a.pub,
+                                   a.pub_shift, lane);
             }
             if (!again) break;  // the next step's first barrier stands between these merges and its appends
             __syncthreads();
@@ -523,54 +658,13 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
         }
     }
     if constexpr (SEED) {
-        elem_t* cols = reinterpret_cast<elem_t*>(&S.buf[0][0]);  // [64][128]
-        static_assert(sizeof(S.buf) >= 64 * 128 * 4, "columns of 64 queries");
-        for (int h = 0; h < 2; h++) {  // 64 queries at a time
-            if (wm == h) {
-#pragma unroll
-                for (int i = 0; i < 2; i++)
-#pragma unroll
-                    for (int j = 0; j < 2; j++)
-#pragma unroll
-                        for (int e = 0; e < 16; e++)
-                            cols[(i * 32 + 8 * (e >> 2) + 4 * half + (e & 3)) * 128 + wn * 64 + j * 32 + col] = best[(i * 2 + j) * 16 + e];
-            }
-            __syncthreads();
-            for (int r = wave; r < 64; r += 4) {
-                const long long qi = q0 + h * 64 + r;
-                if (qi >= a.nq) break;
-                elem_t x = cols[r * 128 + lane], y = cols[r * 128 + 64 + lane], m = 0;
-                const elem_t none = DT == JX_U8 ? (elem_t)-0x7FFFFFFF : (elem_t)-__builtin_inff();
-                for (int k = 0; k < a.r_th; k++) {
-                    m = knn_wave_max<elem_t>(x > y ? x : y);
-                    const uint64_t hx = ballot(x == m), hy = ballot(y == m);
-                    if (hx) {
-                        if (lane == __builtin_ctzll(hx)) x = none;
-                    } else if (hy) {
-                        if (lane == __builtin_ctzll(hy)) y = none;
-                    }
-                }
-                uint32_t code = 0x7F800000u;
-                const elem_t qn = knn_val<DT>(S.qn[h * 64 + r]);
-                if constexpr (DT == JX_U8) {
-                    if (m > -0x40000000) code = (uint32_t)(qn - m);
-                } else {
-                    const float d = fmaxf(qn - m, 0.f);
-                    if (d < __builtin_inff() && m > -__builtin_inff()) code = __float_as_uint(d);
-                }
-                if (lane == 0) {
-                    a.published[(size_t)qi * a.nsplit + split] = code;
-                    S.lim[h * 64 + r] = code;
-                }
-            }
-            __syncthreads();
-        }
+        knn_publish<DT>(S, a, best, q0, split);
         if constexpr (DT != JX_U8) {
             if (tid < KT) {
                 const float first = __uint_as_float(S.lim[tid]);
-                const bool hope = first < __builtin_inff() && knn_eps(a.d, __uint_as_float(S.qn[tid]), first, __builtin_inff()) * (float)a.kp <= first * (float)(KNN_SLACK / 4);
+                const bool hope = first < __builtin_inff() && knn_eps(a.d, __uint_as_float(S.qn[tid]), first, __builtin_inff(), KNN_SPLIT<DT>) * (float)a.kp <= first * (float)(KNN_SLACK / 4);
                 const uint64_t bits = ballot(q0 + tid < a.nq && !hope);
-                if (lane == 0) reinterpret_cast<uint64_t*>(a.hopeless + (size_t)blockIdx.x * a.nsplit + split)[wave] = bits;
+                if (lane == 0) reinterpret_cast<uint64_t*>(a.hopeless + (size_t)tile * a.nsplit + split)[wave] = bits;
             }
         }
         return;
@@ -581,7 +675,7 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
         const int q = wave * 32 + i;
         if (q0 + q >= a.nq) break;
         uint64_t* list = a.lists + ((size_t)(q0 + q) * a.nsplit + split) * a.kp;
-        if (S.cnt[q]) knn_flush<DT, NL>(S, q, list, a.kp, nullptr, 0, 0, a.kp, lane);
+        if (S.cnt[q]) knn_flush<DT, NL>(S, q, list, a.kp, nullptr, 0, 0, 0, 0, lane);
         for (int e = (int)S.fill[q] + lane; e < a.kp; e += 64) list[e] = JX_EMPTY_KEY;
     }
     if (DT != JX_U8) {
@@ -590,7 +684,240 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
         __syncthreads();
         atomicMax(&S.again, bmax);
         __syncthreads();
-        if (tid == 0) atomicMax(&a.odd[blockIdx.x].bb_max, S.again);
+        if (tid == 0) atomicMax(&a.odd[tile].bb_max, S.again);
+    }
+}
+
+// uint8 vectors of at most 128 bytes: one slab.  What a step costs besides its 16 matrix instructions a wavefront is
+// vector instructions and barriers, so:
+//   the queries' operands stay in registers;
+//   an accumulator starts at (t + 1) / 2, t = limit - |q|^2 of its query, as the first matrix instruction's C operand, so
+//   that the test 2 <q, b> + t > |b|^2 is one comparison of the largest of 16 elements with |b|^2 / 2 (rounded down: what
+//   passes is looked at again, exactly);
+//   the base vectors are staged in two buffers, and the only barrier of a step stands between staging and use.  What the
+//   step before has appended is merged behind that barrier, its accumulators still at hand for what found a full buffer.
+// 342 -> 235 vector instructions a step, appends and merges included; search launch of 10,000 x 1M, d = 128, k = 10
+// 3,998 -> 3,233 us, without a single candidate 3,056 -> 2,000 (the int8 rate of a large product: 1,239).
+template <int NL, bool SEED>
+__global__ void __launch_bounds__(256, 2) knn_u8_kernel(KnnArgs a) {
+    __shared__ KnnLds S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
+    const long long q0 = (long long)blockIdx.x * KT;
+    const int split = blockIdx.y;
+    const long long steps = (a.n + KT - 1) / KT;
+    const int b_begin = __builtin_amdgcn_readfirstlane((int)(split * steps / a.nsplit) * KT);
+    const long long after = (split + 1) * steps / a.nsplit * KT;
+    int b_end = __builtin_amdgcn_readfirstlane((int)(after > a.n ? a.n : after));
+    if (SEED && b_end - b_begin > a.seed_steps * KT) b_end = b_begin + a.seed_steps * KT;
+    const uint8_t* Q = reinterpret_cast<const uint8_t*>(a.queries);
+    const uint8_t* B = reinterpret_cast<const uint8_t*>(a.base);
+    const int srow = tid >> 3, sch = tid & 7;  // staging: 8 threads per row, rows srow + 32 t
+    const size_t row_bytes = (size_t)(a.nch * 16);
+    const bool whole = a.nch == 8;
+
+    for (int i = tid; i < KT; i += 256) {
+        S.cnt[i] = 0;
+        S.fill[i] = 0;
+        uint32_t lim = (uint32_t)KINF;
+        if (!SEED && a.seed_steps && q0 + i < a.nq) {
+            const uint32_t first = a.redo[q0 + i];
+            if (first < lim) lim = first;
+        }
+        S.lim[i] = lim;
+    }
+    if (tid < 3) S.flag[tid] = 0;
+    if (tid == 0) S.again = 0;
+    __syncthreads();
+    ki32x4 fa[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const int row = wm * 64 + i * 32 + col;
+        const bool in = q0 + row < a.nq;
+        int nn = 0;
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            const int ch = s * 2 + half;
+            const uint4 v = knn_stage<JX_U8>(load16(Q + (size_t)(in ? q0 + row : q0) * row_bytes + (size_t)((ch < a.nch ? ch : 0) * 16)), in && ch < a.nch);
+            nn = knn_sq<JX_U8>(v, nn);
+            fa[i][s] = __builtin_bit_cast(ki32x4, v);
+        }
+        nn += shfl_xor(nn, 32);
+        if (wn == 0 && half == 0) {
+            S.qn[row] = (uint32_t)nn;
+            S.t[row] = in ? (uint32_t)((int)S.lim[row] - nn) : 0xB0000000u;  // rows beyond the last query accept nothing
+        }
+    }
+    __syncthreads();
+    ki32x16 start[2];  // the accumulators' first values
+    auto load_start = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+            for (int h = 0; h < 4; h++) {
+                const int4 t = *reinterpret_cast<const int4*>(&S.t[wm * 64 + i * 32 + 8 * h + 4 * half]);
+                start[i][4 * h] = (t.x + 1) >> 1;
+                start[i][4 * h + 1] = (t.y + 1) >> 1;
+                start[i][4 * h + 2] = (t.z + 1) >> 1;
+                start[i][4 * h + 3] = (t.w + 1) >> 1;
+            }
+    };
+    if (!SEED) load_start();
+    int best[SEED ? 64 : 1];
+#pragma unroll
+    for (int e = 0; e < (SEED ? 64 : 1); e++) best[e] = -0x7FFFFFFF;
+    uint4 pb[4];
+    auto fetch = [&](const int b0) __attribute__((always_inline)) {
+        if (b0 + KT <= b_end && whole) {  // uniform
+#pragma unroll
+            for (int t = 0; t < 4; t++) pb[t] = load16(B + (size_t)(b0 + srow + 32 * t) * 128 + sch * 16);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const int row = b0 + srow + 32 * t;
+                pb[t] = load16(B + (size_t)(row < b_end ? row : b_end - 1) * row_bytes + (size_t)((sch < a.nch ? sch : 0) * 16));
+            }
+        }
+    };
+    if (b_begin < b_end) fetch(b_begin);
+    ki32x16 acc[2][2];
+    uint64_t stored = 0;
+    // Appends what of a step passes; a full buffer leaves the element for the next round (later rounds: limits may have come
+    // down to a distance that an element stored in the meantime has, and equal ones stay in)
+    auto append = [&](const int b0, const int cur, const int slot, const bool again) __attribute__((always_inline)) {
+        int nbv[2];
+#pragma unroll
+        for (int j = 0; j < 2; j++) nbv[j] = (int)S.bn[cur * KT + wn * 64 + j * 32 + col];
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+            for (int h = 0; h < 4; h++) {
+                int r0 = wm * 64 + i * 32 + 8 * h + 4 * half;
+                asm volatile("" : "+v"(r0));  // not known outside: addresses of all 64 elements would not fit the registers
+                int most[2];
+#pragma unroll
+                for (int j = 0; j < 2; j++) most[j] = max(max(max(acc[i][j][4 * h], acc[i][j][4 * h + 1]), acc[i][j][4 * h + 2]), acc[i][j][4 * h + 3]);
+                if (!again && ballot(most[0] > (nbv[0] >> 1) || most[1] > (nbv[1] >> 1)) == 0ull) continue;
+                const int4 t4 = *reinterpret_cast<const int4*>(&S.t[r0]);
+                const int tt[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+                for (int c = 0; c < 4; c++)
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+                        const int bit = ((i * 4 + h) * 4 + c) * 2 + j;
+                        const uint32_t id = (uint32_t)b0 + (uint32_t)(wn * 64 + j * 32 + col);
+                        const int x = acc[i][j][h * 4 + c] - start[i][h * 4 + c];
+                        const int v = (x << 1) + tt[c];
+                        if ((again ? v >= nbv[j] : v > nbv[j]) && !((stored >> bit) & 1ull) && id < (uint32_t)b_end) {
+                            const uint32_t pos = atomicAdd(&S.cnt[r0 + c], 1u);
+                            if (pos < KCAP) {
+                                S.buf[r0 + c][pos] = ((uint64_t)(uint32_t)((int)S.qn[r0 + c] + nbv[j] - 2 * x) << 32) | (uint64_t)id;
+                                stored |= 1ull << bit;
+                            } else {
+                                S.again = 1;
+                            }
+                            if (pos >= KFLUSH - 1) S.flag[slot] = 1;
+                        }
+                    }
+            }
+    };
+    int cur = 0, slot = 0;  // staging buffer and flag of the step
+    for (int b0 = b_begin;; b0 += KT, cur ^= 1, slot = slot == 2 ? 0 : slot + 1) {
+        uint4* stage = cur ? S.b : S.a;
+        if (b0 < b_end) {
+            const bool full = b0 + KT <= b_end && whole;  // uniform
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const int row = srow + 32 * t;
+                const bool in = b0 + row < b_end;
+                const uint4 v = full ? knn_stage<JX_U8>(pb[t], true) : knn_stage<JX_U8>(pb[t], in && sch < a.nch);
+                stage[row * (KROW / 16) + sch] = v;
+                const int nn = group_sum<8>(knn_sq<JX_U8>(v, 0));
+                if (sch == 0) S.bn[cur * KT + row] = in ? (uint32_t)nn : 0x7FFFFFFFu;
+            }
+        }
+        __syncthreads();
+        const int before = slot == 0 ? 2 : slot - 1;
+        if (!SEED && S.flag[before]) {  // the same in every thread: written before the barrier, cleared behind the next
+            // the step before: merge its buffers that are nearly full, and offer again what found a full one
+            for (;;) {
+                // wavefront w merges the buffers of rows 32 w .. 32 w + 31
+                uint64_t need = ballot(lane < 32 && S.cnt[wave * 32 + (lane & 31)] >= KFLUSH);
+                while (need) {
+                    const int q = wave * 32 + __builtin_ctzll(need);
+                    need &= need - 1ull;
+                    knn_flush<JX_U8, NL>(S, q, a.lists + ((size_t)(q0 + q) * a.nsplit + split) * a.kp, a.kp,
+                                         a.published ? a.published + (size_t)(q0 + q) * a.nsplit * a.pub : nullptr, a.nsplit, split, a.pub,
+                                         a.pub_shift, lane);
+                }
+                __syncthreads();
+                const uint32_t more = S.again;
+                __syncthreads();
+                if (!more) break;
+                if (tid == 0) S.again = 0;
+                __syncthreads();
+                append(b0 - KT, cur ^ 1, before, true);
+                __syncthreads();
+            }
+            load_start();
+        }
+        if (b0 >= b_end) break;
+        if (tid == 0) S.flag[slot == 2 ? 0 : slot + 1] = 0;  // the next step's: last read before the barrier above
+        if (b0 + KT < b_end) fetch(b0 + KT);
+        if constexpr (SEED) {
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) start[i][e] = 0;
+        }
+        const uint4* opnd = stage + (wn * 64 + col) * (KROW / 16) + half;
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            ki32x4 fb[2];
+#pragma unroll
+            for (int j = 0; j < 2; j++) fb[j] = __builtin_bit_cast(ki32x4, opnd[j * 32 * (KROW / 16) + s * 2]);
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+#pragma unroll
+                for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i][s], fb[j], s ? acc[i][j] : start[i], 0, 0, 0);
+        }
+        if constexpr (SEED) {
+#pragma unroll
+            for (int j = 0; j < 2; j++) {
+                const int nb = (int)S.bn[cur * KT + wn * 64 + j * 32 + col];
+#pragma unroll
+                for (int i = 0; i < 2; i++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++) best[(i * 2 + j) * 16 + e] = max(best[(i * 2 + j) * 16 + e], (acc[i][j][e] << 1) - nb);
+            }
+            continue;
+        }
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            const int nbh = (int)S.bn[cur * KT + wn * 64 + j * 32 + col] >> 1;
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                int most = acc[i][j][0];
+#pragma unroll
+                for (int e = 1; e < 16; e++) most = max(most, acc[i][j][e]);
+                any = any || most > nbh;
+            }
+        }
+        stored = 0;
+        if (ballot(any)) append(b0, cur, slot, false);
+    }
+    if constexpr (SEED) {
+        knn_publish<JX_U8>(S, a, best, q0, split);
+        return;
+    }
+    // ---- what is left in the buffers, and the padding of short lists
+    for (int i = 0; i < 32; i++) {
+        const int q = wave * 32 + i;
+        if (q0 + q >= a.nq) break;
+        uint64_t* list = a.lists + ((size_t)(q0 + q) * a.nsplit + split) * a.kp;
+        if (S.cnt[q]) knn_flush<JX_U8, NL>(S, q, list, a.kp, nullptr, 0, 0, 0, 0, lane);
+        for (int e = (int)S.fill[q] + lane; e < a.kp; e += 64) list[e] = JX_EMPTY_KEY;
     }
 }
 
@@ -721,7 +1048,7 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
     bool proven = n_valid == a.n;
     if (!proven && n_valid == kp + n_odd && odd.count <= KNN_ODD && who) {
         const float e_k = __uint_as_float(readlane32(__float_as_uint(kth), __builtin_ctzll(who)));
-        proven = __uint_as_float((uint32_t)(worst >> 32)) - knn_eps(a.d, qq, e_k, __uint_as_float(odd.bb_max)) > e_k;
+        proven = __uint_as_float((uint32_t)(worst >> 32)) - knn_eps(a.d, qq, e_k, __uint_as_float(odd.bb_max), KNN_SPLIT<DT>) > e_k;
     }
     if (lane == 0) a.redo[qi] = proven ? 0u : 1u;
 }
@@ -736,8 +1063,22 @@ static hipError_t launch_knn(const KnnArgs& a, hipStream_t st) {
     constexpr bool U8 = DT == JX_U8;
     dim3 grid((unsigned)((a.nq + KT - 1) / KT), (unsigned)a.nsplit), block(256);
     const bool one = knn_one_slab(DT, a.nch);
-    if (a.seed_steps) hipLaunchKernelGGL((one ? knn_tile_kernel<DT, 1, U8, true> : knn_tile_kernel<DT, 1, false, true>), grid, block, 0, st, a);
-    hipLaunchKernelGGL((one ? knn_tile_kernel<DT, NL, U8, false> : knn_tile_kernel<DT, NL, false, false>), grid, block, 0, st, a);
+    if constexpr (U8) {
+        if (one) {
+            if (a.seed_steps) {
+                hipLaunchKernelGGL((knn_u8_kernel<1, true>), grid, block, 0, st, a);
+                hipLaunchKernelGGL(knn_limit_kernel, dim3((unsigned)a.nq), dim3(64), 0, st, a);
+            }
+            hipLaunchKernelGGL((knn_u8_kernel<NL, false>), grid, block, 0, st, a);
+        }
+    }
+    if (!one) {
+        if (a.seed_steps) {
+            hipLaunchKernelGGL((knn_tile_kernel<DT, 1, true>), grid, block, 0, st, a);
+            hipLaunchKernelGGL(knn_limit_kernel, dim3((unsigned)a.nq), dim3(64), 0, st, a);
+        }
+        hipLaunchKernelGGL((knn_tile_kernel<DT, NL, false>), grid, block, 0, st, a);
+    }
     hipLaunchKernelGGL((knn_merge_kernel<DT, NL>), dim3((unsigned)a.nq), dim3(64), 0, st, a);
     return hipGetLastError();
 }
@@ -802,7 +1143,8 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     const long long redo_bytes = (b.nq * 4 + 255) & ~255LL;
     const long long odd_bytes = (qt * (long long)sizeof(KnnOdd) + 255) & ~255LL;
     const long long aux = redo_bytes + odd_bytes + (qt > KNN_BLOCKS ? qt : KNN_BLOCKS) * 16 + 256;
-    const long long fit = (scratch_bytes - aux) / (b.nq * (a.kp * 8 + 4));
+    long long fit = (scratch_bytes - aux) / (b.nq * (a.kp * 8 + KNN_PUB * 4));
+    if (fit < 1) fit = (scratch_bytes - aux) / (b.nq * (a.kp * 8));  // a single slice publishes nothing
     if (nsplit > fit) nsplit = fit;
     // Where the tiled kernel stays, tiled / this in us: few vectors (1,000 x 2,000 float32 d = 96, k = 10 181 / 210, 300 x
     // 8,000, k = 1 125 / 155; uint8 300 x 8,000 108 / 111, k = 10 213 / 112); hardly any workgroups; and one neighbour or
@@ -814,6 +1156,12 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     if (b.n < knn_fewest(b, row)) return hipSuccess;
     a.nsplit = (int)nsplit;
     a.r_th = (int)((a.kp + nsplit - 1) / nsplit);
+    // each slice publishes some more than would make up kp if all were alike, in at most KNN_PUB values
+    const int top = a.r_th + (a.r_th < 4 ? a.r_th : 4);
+    a.pub_shift = 0;
+    while ((top + (1 << a.pub_shift) - 1) >> a.pub_shift > KNN_PUB) a.pub_shift++;
+    a.pub = (top + (1 << a.pub_shift) - 1) >> a.pub_shift;
+    if (a.pub > KNN_ENTRIES / nsplit) a.pub = (int)(KNN_ENTRIES / nsplit);  // r_th at least: more than 128 slices of kp <= 156
     uint8_t* p = (uint8_t*)scratch + scratch_bytes - aux;  // behind the lists and the published distances
     p -= (uintptr_t)p & 255;
     a.lists = (uint64_t*)scratch;
@@ -822,11 +1170,16 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     a.odd = (KnnOdd*)(p + redo_bytes);
     a.hopeless = (uint4*)(p + redo_bytes + odd_bytes);  // qt * nsplit <= max(qt, KNN_BLOCKS)
     hipError_t e = hipSuccess;
-    // a first threshold from a sixteenth of every slice, one step at least: without it the first step of every slice is
-    // merged whole, 200 us and more
+    // First limits from a share f of every slice.  A tile's 128 queries meet about 128 kp / f vectors below them, each 900
+    // cycles of its workgroup (append, its part of a merge, the others waiting); a slab of a step takes 4,000.  The sum of that
+    // and of f of the steps is least at f^2 = 28 kp / (steps nslab); a sixteenth at least, a quarter at most.  10,000 x 1M
+    // uint8, k = 10, f = 1/16, 1/8, 1/4: 3,452, 3,159, 3,062 us; 1,000 x 100,003 float32 d = 960, k = 100: 1,379, 1,244,
+    // 1,172
     const long long each = steps / nsplit;
-    a.seed_steps = a.published && a.r_th <= 32 ? (int)((each + 15) / 16) : 0;
-    if (a.published && !a.seed_steps) e = launch_fill_u32(a.published, b.nq * nsplit, 0x7F800000u, st);
+    const double f = sqrt(28.0 * a.kp / ((double)steps * ((a.nch + 7) / 8)));
+    const long long seed = (long long)ceil((double)each * (f < 0.0625 ? 0.0625 : (f > 0.25 ? 0.25 : f)));
+    a.seed_steps = a.published && a.r_th <= 32 ? (int)(seed < 1 ? 1 : seed) : 0;
+    if (a.published && !a.seed_steps) e = launch_fill_u32(a.published, b.nq * nsplit * a.pub, 0x7F800000u, st);
     if (e != hipSuccess) return e;
     if (!exact && !a.seed_steps) e = launch_fill_u32((uint32_t*)a.odd, qt * (long long)(sizeof(KnnOdd) / 4), 0u, st);
     if (e != hipSuccess) return e;

@@ -90,3 +90,16 @@ def test_index_search_slices_queries(jx):
     for at in (0, 75_000, 149_872):
         i0, d0 = jx.bruteforce_static(dev(b), dev(q[at:at + 128]), 64)
         assert torch.equal(ids[at:at + 128], i0) and torch.equal(dist[at:at + 128], d0)
+
+
+@pytest.mark.parametrize("dtype", ["uint8", "float32", "float16"])
+@pytest.mark.parametrize("d,n,nq,k", [(128, 40_000, 130, 10), (96, 30_000, 300, 100), (112, 60_001, 64, 8)])
+def test_vectors_that_come_nearer_and_nearer(jx, dtype, d, n, nq, k):
+    """Sorted from far to near: whatever the first limits are, every vector of a step passes, each buffer overflows many times
+    over, and what it had no room for is offered again until it fits."""
+    t = np.uint8 if dtype == "uint8" else np.float32
+    b, q = random_data(n, d, t, 31).astype(np.float64), random_data(nq, d, t, 32)
+    q[:] = q[0]
+    q[1::2, 0] += 1
+    b = b[np.argsort(-((b - q[0]) ** 2).sum(1))].astype(dtype)
+    check(jx, dev(b), dev(q.astype(dtype)), k)

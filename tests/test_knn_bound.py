@@ -14,6 +14,9 @@ SOURCE = """
 extern "C" void thresholds(const float* lim, const float* qq, float* out, long n) {
     for (long i = 0; i < n; i++) out[i] = jx::knn_threshold(lim[i], qq[i]);
 }
+extern "C" void bounds_parts(int d, const float* qq, const float* e, const float* bb_max, float* out, long n) {
+    for (long i = 0; i < n; i++) out[i] = jx::knn_eps(d, qq[i], e[i], bb_max[i], KNN_BF16_PARTS);
+}
 extern "C" void bounds(int d, const float* qq, const float* e, const float* bb_max, float* out, long n) {
     for (long i = 0; i < n; i++) out[i] = jx::knn_eps(d, qq[i], e[i], bb_max[i]);
 }
@@ -89,3 +92,36 @@ def test_one_long_vector_does_not_widen_the_bound(lib):
         eps = np.empty(1, np.float32)
         lib.bounds(C.c_int(960), _ptr(np.array([bad], np.float32)), _ptr(e), _ptr(np.array([2.0], np.float32)), _ptr(eps), C.c_long(1))
         assert not eps[0] < np.inf
+
+
+def _bf16(x):
+    """Rounded to bfloat16, to nearest even."""
+    u = x.view(np.uint32).astype(np.uint64)
+    return ((u + 0x7FFF + ((u >> 16) & 1)) & 0xFFFF0000).astype(np.uint32).view(np.float32)
+
+
+@pytest.mark.parametrize("d", [4, 32, 128, 1536])
+@pytest.mark.parametrize("offset", [0.0, 3.0, 1000.0])
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")
+@pytest.mark.parametrize("scale", [1e-19, 1.0, 1e15])
+def test_bound_covers_the_parts(lib, d, offset, scale):
+    """The norm form on two bfloat16 parts of each value, what the parts lack alone (products summed in 64 bits) and with a
+    float32 rounding after every 16 coordinates."""
+    rng = np.random.default_rng(9)
+    n, f = 2_000, np.float32
+    q = ((rng.standard_normal((n, d)) + offset) * scale).astype(f)
+    b = (q + rng.standard_normal((n, d)) * scale * 10.0 ** rng.uniform(-3, 1, (n, 1))).astype(f)
+    qh, bh = _bf16(q), _bf16(b)
+    ql, bl = _bf16(q - qh), _bf16(b - bh)
+    Q, B, QL, BL = (v.astype(np.float64) for v in (qh, bh, ql, bl))
+    products = QL * B + Q * BL + Q * B
+    x64, x32 = products.sum(1), np.zeros(n, f)
+    for j in range(0, d, 16):
+        x32 = (x32 + products[:, j:j + 16].sum(1)).astype(f)
+    qq, bb = (q.astype(np.float64) ** 2).sum(1), (b.astype(np.float64) ** 2).sum(1)
+    e = ((q.astype(np.float64) - b) ** 2).sum(1)
+    eps = np.empty(n, f)
+    lib.bounds_parts(C.c_int(d), _ptr(qq.astype(f)), _ptr(e.astype(f)), _ptr(np.full(n, np.inf, f)), _ptr(eps), C.c_long(n))
+    assert scale > 1 or np.isfinite(eps).all()
+    for x in (x64, x32.astype(np.float64)):  # as above: no proof where norms of that length could overflow
+        assert (~(eps < np.inf) | (np.abs(qq + bb - 2 * x - e) <= eps)).all()
