@@ -6,11 +6,13 @@
 //                candidate set is (live neighbours of v) U (live neighbours of
 //                each deleted neighbour), v excluded.  The work is arranged as
 //                flat, regular passes instead of one irregular task per vertex:
-//                count -> prefix sum -> emit (v, candidate) pairs -> sort by
+//                count -> the sets, without repeats, sorted by (distance, id): in LDS,
+//                a workgroup per vertex; where a slice has a set of more than 4,096
+//                pairs by prefix sum -> emit (v, candidate) pairs -> sort by
 //                (v, candidate) -> drop repeated pairs and compute d(v, c) ->
 //                stable sort by (v, distance), which keeps equal distances in
 //                candidate-id order -> robustPrune per segment (the reverse-merge
-//                kernel with the existing row ignored) -> empty the deleted rows.
+//                kernels with the existing row ignored) -> empty the deleted rows.
 //                New rows only depend on the rows of v itself and of deleted
 //                vertices, which are not rewritten until the end, so slices of
 //                vertices can be processed one after the other.
@@ -123,8 +125,38 @@ hipError_t launch_consol_emit(const ConsolArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// sorted (v, candidate) pairs -> (v << 32 | distance bits, candidate); a repeated pair gets the empty key.
-// 8 lanes per pair, chunks strided over the lanes.
+// d(v, c) by 8 lanes, chunks strided over them
+template <int KIND>
+__device__ __forceinline__ float consol_dist(const ConsolArgs& a, const uint8_t* pv, const uint8_t* pc, const int lig) {
+    uint32_t acc_u = 0;
+    float acc_f = 0.f;
+    for (int ch = lig; ch < a.ds.nch; ch += 8) {
+        const uint4 x = load16(pv + (size_t)ch * 16), y = load16(pc + (size_t)ch * 16);
+        const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            if constexpr (KIND == K_U8) {
+                acc_u = __builtin_amdgcn_udot4(xs[t], xs[t], acc_u, false);
+                acc_u = __builtin_amdgcn_udot4(ys[t], ys[t], acc_u, false);
+                acc_u -= 2u * __builtin_amdgcn_udot4(xs[t], ys[t], 0u, false);
+            } else if constexpr (KIND == K_F16) {
+                const half2_t hx = __builtin_bit_cast(half2_t, xs[t]), hy = __builtin_bit_cast(half2_t, ys[t]);
+                const float d0 = (float)hx.x - (float)hy.x, d1 = (float)hx.y - (float)hy.y;
+                acc_f = fmaf(d0, d0, acc_f);
+                acc_f = fmaf(d1, d1, acc_f);
+            } else {
+                const float df = __uint_as_float(xs[t]) - __uint_as_float(ys[t]);
+                acc_f = fmaf(df, df, acc_f);
+            }
+        }
+    }
+    if constexpr (KIND == K_U8)
+        return (float)group_sum<8>(acc_u);
+    else
+        return fmaxf(group_sum<8>(acc_f), 0.f);
+}
+
+// sorted (v, candidate) pairs -> (v << 32 | distance bits, candidate); a repeated pair gets the empty key.  8 lanes per pair
 template <int KIND>
 __global__ void __launch_bounds__(256) consol_dist_kernel(ConsolArgs a, uint64_t* keys_out, uint32_t* vals_out) {
     const int lane = lane_id();
@@ -134,38 +166,9 @@ __global__ void __launch_bounds__(256) consol_dist_kernel(ConsolArgs a, uint64_t
     const uint64_t k = in ? a.keys[i] : JX_EMPTY_KEY;
     const bool dup = in && i > 0 && a.keys[i - 1] == k;
     const uint32_t v = (uint32_t)(k >> 32), c = (uint32_t)k;
-    uint32_t acc_u = 0;
-    float acc_f = 0.f;
-    if (in && !dup) {
-        const uint8_t* pv = a.ds.recs + (size_t)v * (size_t)a.ds.rec_stride;
-        const uint8_t* pc = a.ds.recs + (size_t)c * (size_t)a.ds.rec_stride;
-        for (int ch = lig; ch < a.ds.nch; ch += 8) {
-            const uint4 x = load16(pv + (size_t)ch * 16), y = load16(pc + (size_t)ch * 16);
-            const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-            for (int t = 0; t < 4; t++) {
-                if constexpr (KIND == K_U8) {
-                    acc_u = __builtin_amdgcn_udot4(xs[t], xs[t], acc_u, false);
-                    acc_u = __builtin_amdgcn_udot4(ys[t], ys[t], acc_u, false);
-                    acc_u -= 2u * __builtin_amdgcn_udot4(xs[t], ys[t], 0u, false);
-                } else if constexpr (KIND == K_F16) {
-                    const half2_t hx = __builtin_bit_cast(half2_t, xs[t]), hy = __builtin_bit_cast(half2_t, ys[t]);
-                    const float d0 = (float)hx.x - (float)hy.x, d1 = (float)hx.y - (float)hy.y;
-                    acc_f = fmaf(d0, d0, acc_f);
-                    acc_f = fmaf(d1, d1, acc_f);
-                } else {
-                    const float df = __uint_as_float(xs[t]) - __uint_as_float(ys[t]);
-                    acc_f = fmaf(df, df, acc_f);
-                }
-            }
-        }
-    }
-    float dist;
-    if constexpr (KIND == K_U8) {
-        dist = (float)group_sum<8>(acc_u);
-    } else {
-        dist = fmaxf(group_sum<8>(acc_f), 0.f);
-    }
+    float dist = 0.f;
+    if (in && !dup)
+        dist = consol_dist<KIND>(a, a.ds.recs + (size_t)v * (size_t)a.ds.rec_stride, a.ds.recs + (size_t)c * (size_t)a.ds.rec_stride, lig);
     if (in && lig == 0) {
         keys_out[i] = dup ? JX_EMPTY_KEY : (((uint64_t)v << 32) | __float_as_uint(dist));
         vals_out[i] = dup ? JX_NONE_ID : c;
@@ -182,6 +185,190 @@ hipError_t launch_consol_dist(int dtype, const ConsolArgs& a, uint64_t* keys_out
     else
         hipLaunchKernelGGL(consol_dist_kernel<K_F32>, grid, block, 0, st, a, keys_out, vals_out);
     return hipGetLastError();
+}
+
+// ---- candidate sets of at most CONSOL_LDS pairs, repeats included (any row of at most 64 neighbours): put together in LDS, a
+// workgroup per vertex.  The passes above sort all pairs of a slice twice, 14 radix passes over 3.2 M pairs; a set of some 280
+// is sorted where it is.  A hash table finds the repeats, a distance is taken per candidate that is left, and the keys
+// are sorted by (distance, id) and written as one segment: 20,000 of 200,000 uint8 vertices deleted, lists of all slices
+// 8.6 -> 1.8 ms.  Bound: the gathers, and the LDS round trips of the sort.
+
+// affected vertices of the slice and where their segments begin (in no particular order, one atomic per workgroup):
+// list[i] = vertex, heads[i] = start; slot[0] counts them, sum counts pairs
+__global__ void __launch_bounds__(1024) consol_select_kernel(ConsolArgs a, uint32_t* list, uint32_t* heads, uint32_t* slot, uint32_t* sum) {
+    __shared__ uint32_t ws[16], wn[16], base[2];
+    const long long v = a.v0 + (long long)blockIdx.x * 1024 + threadIdx.x;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t c = v < a.v1 ? a.cnt[v] : 0u;
+    const uint64_t on = ballot(c != 0u);
+    uint32_t x = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = __shfl_up(x, d, 64);
+        if (lane >= d) x += o;
+    }
+    if (lane == 63) {
+        ws[wave] = x;
+        wn[wave] = (uint32_t)__builtin_popcountll(on);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t ts = 0, tn = 0;
+        for (int w = 0; w < 16; w++) {
+            const uint32_t s = ws[w], n = wn[w];
+            ws[w] = ts;
+            wn[w] = tn;
+            ts += s;
+            tn += n;
+        }
+        base[0] = ts ? atomicAdd(sum, ts) : 0u;
+        base[1] = tn ? atomicAdd(slot, tn) : 0u;
+    }
+    __syncthreads();
+    if (c) {
+        const uint32_t i = base[1] + wn[wave] + (uint32_t)prefix_count(on);
+        list[i] = (uint32_t)v;
+        heads[i] = base[0] + ws[wave] + x - c;
+    }
+}
+
+// sets of (min_cnt, CAP] pairs, W wavefronts each
+template <int KIND, int W, int CAP>
+__global__ void __launch_bounds__(W * 64) consol_list_kernel(ConsolArgs a, const uint32_t* list, const uint32_t* heads, const uint32_t* nlist,
+                                                            uint32_t min_cnt, uint64_t* keys_out, uint32_t* vals_out) {
+    __shared__ uint32_t table[2 * CAP];
+    __shared__ uint64_t key[CAP];
+    __shared__ uint32_t count;
+    auto sync = []() {
+        if constexpr (W == 1) wave_sync();
+        else __syncthreads();
+    };
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const uint32_t n = *nlist;
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        const uint32_t v = list[i], cnt = a.cnt[v];
+        if (cnt <= min_cnt || cnt > CAP) continue;
+        const uint32_t head = heads[i];
+        int mask = 127;  // the table: at least twice the pairs
+        while (mask + 1 < 2 * (int)cnt) mask = 2 * mask + 1;
+        sync();  // the previous set's reads are done
+        for (int t = tid; t <= mask; t += W * 64) table[t] = JX_NONE_ID;
+        if (tid == 0) count = 0;
+        sync();
+        // ids that are not in the table yet go to the low words of key
+        auto add = [&](const bool ok, const uint32_t id) {
+            bool fresh = false;
+            if (ok) {
+                uint32_t h = (id * 2654435761u) >> 7;
+                for (;;) {  // ends: half of the table stays empty
+                    h &= (uint32_t)mask;
+                    const uint32_t was = atomicCAS(&table[h], JX_NONE_ID, id);
+                    fresh = was == JX_NONE_ID;
+                    if (fresh || was == id) break;
+                    h++;
+                }
+            }
+            const uint64_t m = ballot(fresh);
+            if (!m) return;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&count, (uint32_t)__builtin_popcountll(m));
+            at = readlane32(at, 0);
+            if (fresh) key[at + (uint32_t)prefix_count(m)] = id;
+        };
+        const uint32_t* row = a.adj + (size_t)v * a.R;
+        int turn = 0;  // deleted neighbours are dealt to the wavefronts
+        for (int rb = 0; rb < a.R; rb += 64) {
+            const uint32_t u = rb + lane < a.R ? row[rb + lane] : JX_NONE_ID;
+            const bool valid = u != JX_NONE_ID;
+            const bool dead = valid && a.deleted[u] != 0;
+            if (wave == 0) add(valid && !dead, u);
+            uint64_t dm = ballot(dead);
+            while (dm) {
+                // four rows at a time: a row is a chain of two loads
+                uint32_t w[4][(JX_MAX_R + 63) / 64];
+                int took = 0;
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    if (!dm) break;
+                    const int j = __builtin_ctzll(dm);
+                    dm &= dm - 1;
+                    took = k + 1;
+                    const bool own = W == 1 || turn % W == wave;
+                    turn++;
+                    const uint32_t* ru = a.adj + (size_t)readlane32(u, j) * a.R;
+#pragma unroll
+                    for (int c = 0; c < (JX_MAX_R + 63) / 64; c++) w[k][c] = own && c * 64 + lane < a.R ? ru[c * 64 + lane] : JX_NONE_ID;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    if (k >= took) break;
+#pragma unroll
+                    for (int c = 0; c < (JX_MAX_R + 63) / 64; c++) {
+                        if (c * 64 >= a.R) break;  // uniform
+                        const uint32_t x = w[k][c];
+                        add(x != JX_NONE_ID && x != v && a.deleted[x != JX_NONE_ID ? x : v] == 0, x);
+                    }
+                }
+            }
+        }
+        sync();
+        const int m = (int)count;
+        // distances: 8 lanes per candidate, as in the flat pass
+        {
+            const int g = lane >> 3, lig = lane & 7;
+            const uint8_t* pv = a.ds.recs + (size_t)v * (size_t)a.ds.rec_stride;
+            for (int c0 = wave * 8; c0 < m; c0 += W * 8) {
+                const int c = c0 + g;
+                const uint32_t id = (uint32_t)key[c < m ? c : m - 1];
+                const float dist = consol_dist<KIND>(a, pv, a.ds.recs + (size_t)id * (size_t)a.ds.rec_stride, lig);
+                if (lig == 0 && c < m) key[c] = ((uint64_t)__float_as_uint(dist) << 32) | id;
+            }
+        }
+        int P = 64;
+        while (P < m) P *= 2;
+        for (int t = m + tid; t < P; t += W * 64) key[t] = JX_EMPTY_KEY;
+        sync();
+        for (int k = 2; k <= P; k <<= 1)
+            for (int j = k >> 1; j >= 1; j >>= 1) {
+                for (int t = tid; t < P / 2; t += W * 64) {
+                    const int lo = ((t & ~(j - 1)) << 1) | (t & (j - 1)), hi = lo | j;
+                    const uint64_t x = key[lo], y = key[hi];
+                    if ((x > y) == ((lo & k) == 0)) {
+                        key[lo] = y;
+                        key[hi] = x;
+                    }
+                }
+                sync();
+            }
+        for (int t = tid; t < (int)cnt; t += W * 64) {
+            const uint64_t k = t < m ? key[t] : JX_EMPTY_KEY;
+            keys_out[(size_t)head + t] = t < m ? (((uint64_t)v << 32) | (k >> 32)) : JX_EMPTY_KEY;
+            vals_out[(size_t)head + t] = t < m ? (uint32_t)k : JX_NONE_ID;
+        }
+    }
+}
+
+template <int KIND>
+static hipError_t launch_consol_lists_kind(const ConsolArgs& a, uint32_t max_cnt, uint32_t* list, uint32_t* heads, uint32_t* counters,
+                                           uint64_t* keys_out, uint32_t* vals_out, hipStream_t st) {
+    const long long nv = a.v1 - a.v0;
+    const unsigned most = (unsigned)(nv < 16384 ? nv : 16384);  // persistent
+    hipLaunchKernelGGL((consol_list_kernel<KIND, 1, 512>), dim3(most), dim3(64), 0, st, a, list, heads, counters, 0u, keys_out, vals_out);
+    if (max_cnt > 512)
+        hipLaunchKernelGGL((consol_list_kernel<KIND, 4, CONSOL_LDS>), dim3(most < 2048 ? most : 2048), dim3(256), 0, st, a, list, heads, counters,
+                           512u, keys_out, vals_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_consol_lists(int dtype, const ConsolArgs& a, uint32_t max_cnt, uint32_t* list, uint32_t* heads, uint32_t* counters,
+                               uint64_t* keys_out, uint32_t* vals_out, hipStream_t st) {
+    hipError_t e = launch_fill_u32(counters, 16, 0u, st);
+    if (e != hipSuccess) return e;
+    const long long nv = a.v1 - a.v0;
+    hipLaunchKernelGGL(consol_select_kernel, dim3((unsigned)((nv + 1023) / 1024)), dim3(1024), 0, st, a, list, heads, counters, counters + 3);
+    if (dtype == JX_U8) return launch_consol_lists_kind<K_U8>(a, max_cnt, list, heads, counters, keys_out, vals_out, st);
+    if (dtype == JX_F16) return launch_consol_lists_kind<K_F16>(a, max_cnt, list, heads, counters, keys_out, vals_out, st);
+    return launch_consol_lists_kind<K_F32>(a, max_cnt, list, heads, counters, keys_out, vals_out, st);
 }
 
 __global__ void clear_deleted_rows_kernel(uint32_t* adj, int R, long long n, const uint8_t* deleted) {

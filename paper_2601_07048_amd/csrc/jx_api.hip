@@ -987,25 +987,35 @@ int jx_consolidate(jx_index* idx, void* stream) {
     int64_t v0 = 0;
     while (v0 < n) {
         int64_t v1 = v0, E = 0;
-        while (v1 < n && E + cnt[(size_t)v1] <= Ecap) E += cnt[(size_t)v1++];
+        uint32_t most = 0;
+        while (v1 < n && E + cnt[(size_t)v1] <= Ecap) {
+            const uint32_t here = cnt[(size_t)v1++];
+            E += here;
+            if (here > most) most = here;
+        }
         if (E > 0) {
-            const int64_t nv = v1 - v0;
-            JX_HIP(hipMemcpyAsync(d_offs, c.cnt + v0, (size_t)nv * 4, hipMemcpyDeviceToDevice, st));
-            JX_HIP(jx::launch_scan_u32(d_offs, nv, st));
             c.v0 = v0;
             c.v1 = v1;
             c.E = E;
-            c.keys = (uint64_t*)(W + w.keys0);
-            c.vals = (uint32_t*)(W + w.vals0);
-            JX_HIP(jx::launch_consol_emit(c, st));
-            // (v, candidate) order brings repeated candidates together
-            JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys0), (uint32_t*)(W + w.vals0), (uint64_t*)(W + w.keys1),
-                                         (uint32_t*)(W + w.vals1), E, 32 + tbits, tbits, (uint32_t*)(W + w.table), nullptr, nullptr, st));
-            JX_HIP(jx::launch_consol_dist(p.dtype, c, (uint64_t*)(W + w.keys1), (uint32_t*)(W + w.vals1), st));
-            // (v, distance) order; the sort is stable, so equal distances stay in id order
-            JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys1), (uint32_t*)(W + w.vals1), (uint64_t*)(W + w.keys0),
-                                         (uint32_t*)(W + w.vals0), E, 32 + tbits, 32, (uint32_t*)(W + w.table), (uint32_t*)(W + w.heads),
-                                         (uint32_t*)(W + w.counters), st));
+            if (most <= CONSOL_LDS) {
+                JX_HIP(jx::launch_consol_lists(p.dtype, c, most, (uint32_t*)(W + w.vals0), (uint32_t*)(W + w.heads), (uint32_t*)(W + w.counters),
+                                               (uint64_t*)(W + w.keys1), (uint32_t*)(W + w.vals1), st));
+            } else {
+                const int64_t nv = v1 - v0;
+                JX_HIP(hipMemcpyAsync(d_offs, c.cnt + v0, (size_t)nv * 4, hipMemcpyDeviceToDevice, st));
+                JX_HIP(jx::launch_scan_u32(d_offs, nv, st));
+                c.keys = (uint64_t*)(W + w.keys0);
+                c.vals = (uint32_t*)(W + w.vals0);
+                JX_HIP(jx::launch_consol_emit(c, st));
+                // (v, candidate) order brings repeated candidates together
+                JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys0), (uint32_t*)(W + w.vals0), (uint64_t*)(W + w.keys1),
+                                             (uint32_t*)(W + w.vals1), E, 32 + tbits, tbits, (uint32_t*)(W + w.table), nullptr, nullptr, st));
+                JX_HIP(jx::launch_consol_dist(p.dtype, c, (uint64_t*)(W + w.keys1), (uint32_t*)(W + w.vals1), st));
+                // (v, distance) order; the sort is stable, so equal distances stay in id order
+                JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys1), (uint32_t*)(W + w.vals1), (uint64_t*)(W + w.keys0),
+                                             (uint32_t*)(W + w.vals0), E, 32 + tbits, 32, (uint32_t*)(W + w.table), (uint32_t*)(W + w.heads),
+                                             (uint32_t*)(W + w.counters), st));
+            }
             a.E = E;
             a.B = (E + p.R - 1) / p.R;
             JX_HIP(jx::launch_reverse_merge(p.dtype, a, st));

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import oracle
+from paper_2601_07048_amd import datagen
 from gpu_common import dev, u32, random_data
 
 pytestmark = pytest.mark.gpu
@@ -351,3 +352,22 @@ def test_compact_rabitq_records_move(jx):
         assert np.array_equal(ad.cpu().numpy(), bd.cpu().numpy())
     codes, meta, _ = g.export_codes()
     assert codes.shape[0] == n - 600
+
+
+@pytest.mark.parametrize("dtype", [np.uint8, np.float32])
+@pytest.mark.parametrize("R,L,drop", [(8, 40, 0.3), (24, 60, 0.5), (64, 100, 0.1), (64, 100, 0.6), (130, 160, 0.25), (256, 300, 0.4)])
+def test_consolidate_sets_of_every_size(jx, dtype, R, L, drop):
+    """Candidate sets of a few pairs, around 512, of thousands, and beyond the 4,096 that are put together in LDS (rows of 256,
+    two fifths of them deleted), in one slice and in many."""
+    n, d = 1500, 64
+    x = random_data(n, d, dtype, seed=R) if dtype == np.uint8 else datagen.dyadic_grid(n, d, seed=R)
+    ref = oracle.Index(d, dtype, R, L, 1.2, n)
+    ref.insert(x)
+    gone = np.random.default_rng(R).choice(n, int(n * drop), replace=False).astype(np.uint32)
+    adj, entry = ref.graph()[0].copy(), ref.entry
+    ref.delete(gone); ref.consolidate()
+    for batch in (n, 96):  # max_batch * R pairs fit a slice
+        g = jx.Index(d, jx.U8 if dtype == np.uint8 else jx.F32, R, L, 1.2, capacity=n, max_batch=batch)
+        g.import_graph(dev(x), dev(adj), entry)
+        g.delete(dev(gone)); g.consolidate()
+        assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), batch
