@@ -1,9 +1,9 @@
 // RaBitQ pipeline (Sec. 5.1): rotation GEMM on the matrix cores, encoder,
 // integer query records, exact re-rank.
 //
-//   rotate      out = (in - c) P^T   float32 MFMA (32x32x2), 128x128 tile per
-//               workgroup, 64x64 per wavefront, K staged through LDS in slabs
-//               of 32; the centroid is subtracted while staging.
+//   rotate      out = (in - c) P^T   bfloat16 MFMA on three parts of each float32
+//               value, 128x128 tile per workgroup, 64x64 per wavefront, K staged
+//               through LDS in slabs of 32; the centroid is subtracted while staging.
 //   encode      one wavefront per vector: 1-bit codes via ballot, 4-bit codes
 //               with the max-abs grid scale; data_add, data_rescale in double.
 //   query prep  one wavefront per query: min/max, B_q-bit integer query,
@@ -16,14 +16,162 @@
 namespace jx {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float rq_f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 rq_bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 rq_bf16x2 __attribute__((ext_vector_type(2)));
 
 #define GT 128
 #define GK 32
-#define GLD 36  // padded LDS row (floats)
+#define GLD 36               // floats of a staged row of the float32 form, padded
+#define GPIECE 576            // 32 rows x 16 operand bytes, padded: 64 bytes further on in the banks from piece to piece
+#define GBLOCK (12 * GPIECE)  // operand pieces of 32 rows and a slab: [step][part][half]
 
-// IN: storage type of the input rows (JX_F32, JX_F16, JX_U8); all three convert to float32 exactly
+// Four float32 values as three bfloat16 parts each, whose sum they are exactly (8 bits of the significand in each)
+__device__ __forceinline__ void rotate_stage(uint8_t* at, float v0, float v1, float v2, float v3) {
+#pragma unroll
+    for (int part = 0; part < 3; part++) {
+        const rq_f32x2 x = {v0, v1}, y = {v2, v3};
+        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, rq_bf16x2));
+        const uint32_t k = __builtin_bit_cast(uint32_t, __builtin_convertvector(y, rq_bf16x2));
+        v0 -= __uint_as_float(h << 16);
+        v1 -= __uint_as_float(h & 0xFFFF0000u);
+        v2 -= __uint_as_float(k << 16);
+        v3 -= __uint_as_float(k & 0xFFFF0000u);
+        *reinterpret_cast<uint2*>(at + part * 2 * GPIECE) = make_uint2(h, k);
+    }
+}
+
 template <int IN>
-__global__ void __launch_bounds__(256) rotate_gemm_kernel(const void* __restrict__ in_v, long long n, int d,
+__device__ __forceinline__ float4 rotate_load(const void* in_v, const size_t at) {
+    if (IN == JX_F16) {
+        const _Float16* hp = reinterpret_cast<const _Float16*>(in_v) + at;
+        return make_float4((float)hp[0], (float)hp[1], (float)hp[2], (float)hp[3]);
+    } else if (IN == JX_U8) {
+        const uint8_t* bp = reinterpret_cast<const uint8_t*>(in_v) + at;
+        return make_float4((float)bp[0], (float)bp[1], (float)bp[2], (float)bp[3]);
+    } else {
+        return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(in_v) + at);
+    }
+}
+
+// IN: storage type of the input rows (JX_F32, JX_F16, JX_U8); all three convert to float32 exactly.
+// Six products of the parts (those of weight 2^-16 and above) take 192 cycles for 16 coordinates where
+// v_mfma_f32_32x32x2_f32 takes 512; every 32 coordinates have a sum of their own, so the result is nearer to 64 bits than that
+// instruction's: error relative to the root mean square of a row, root mean
+// square / largest, d = 128 8.1e-8 / 7.1e-7 (2.0e-7 / 2.3e-6 before), d = 960 1.3e-7 / 2.1e-6 (5.6e-7 / 9.4e-6).  Values of 3.39e38 and more round to an
+// infinite part: elements that do not come out finite are summed again in plain float32.
+// Bound: matrix instructions (1,536 cycles a slab and wavefront) and the vector instructions of the split (1,200), which
+// overlap in part.  10,000 x 960 226 -> 149 us, 5,000 x 1536 235 -> 145, 50,000 x 960 1,089 -> 717.
+template <int IN>
+__global__ void __launch_bounds__(256, 2) rotate_gemm_kernel(const void* __restrict__ in_v, long long n, int d,
+                                                             const float* __restrict__ P, const float* __restrict__ c,
+                                                             float* __restrict__ out) {
+    __shared__ __align__(16) uint8_t As[4 * GBLOCK];
+    __shared__ __align__(16) uint8_t Bs[4 * GBLOCK];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const long long m0 = (long long)blockIdx.y * GT;
+    const int n0 = blockIdx.x * GT;
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+
+    // a slab on its way in registers while the one before it is multiplied; rows beyond the last are read again, and what
+    // comes of them is not stored.  d is a multiple of 32: every slab is whole
+    const int srow = tid >> 3, piece = tid & 7, c4 = piece * 4;
+    float4 pa[4], pb[4], pc;
+    auto fetch = [&](const int k0) __attribute__((always_inline)) {
+        pc = *reinterpret_cast<const float4*>(c + k0 + c4);
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            const long long ra = m0 + srow + 32 * t < n ? m0 + srow + 32 * t : n - 1;
+            const int rb = n0 + srow + 32 * t < d ? n0 + srow + 32 * t : d - 1;
+            pa[t] = rotate_load<IN>(in_v, (size_t)ra * d + k0 + c4);
+            pb[t] = *reinterpret_cast<const float4*>(P + (size_t)rb * d + k0 + c4);
+        }
+    };
+    fetch(0);
+    const int to = ((piece >> 2) * 6 + ((piece >> 1) & 1)) * GPIECE + (piece & 1) * 8 + srow * 16;
+    const int from = (lane >> 5) * GPIECE + (lane & 31) * 16;
+    for (int k0 = 0; k0 < d; k0 += GK) {
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            rotate_stage(As + t * GBLOCK + to, pa[t].x - pc.x, pa[t].y - pc.y, pa[t].z - pc.z, pa[t].w - pc.w);
+            rotate_stage(Bs + t * GBLOCK + to, pb[t].x, pb[t].y, pb[t].z, pb[t].w);
+        }
+        __syncthreads();
+        if (k0 + GK < d) fetch(k0 + GK);
+#pragma unroll
+        for (int mi = 0; mi < 2; mi++) {
+            rq_bf16x8 a[2][3];
+#pragma unroll
+            for (int q = 0; q < 6; q++) a[q / 3][q % 3] = *reinterpret_cast<const rq_bf16x8*>(As + (wm * 2 + mi) * GBLOCK + from + q * 2 * GPIECE);
+#pragma unroll
+            for (int ni = 0; ni < 2; ni++) {
+                f32x16 part;
+#pragma unroll
+                for (int e = 0; e < 16; e++) part[e] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < 2; ks++) {
+                    rq_bf16x8 b[3];
+#pragma unroll
+                    for (int q = 0; q < 3; q++) b[q] = *reinterpret_cast<const rq_bf16x8*>(Bs + (wn * 2 + ni) * GBLOCK + from + (ks * 3 + q) * 2 * GPIECE);
+                    // the smallest products first
+                    part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][2], b[0], part, 0, 0, 0);
+                    part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[2], part, 0, 0, 0);
+                    part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[1], part, 0, 0, 0);
+                    part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[0], part, 0, 0, 0);
+                    part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[1], part, 0, 0, 0);
+                    part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[0], part, 0, 0, 0);
+                }
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[mi][ni][e] += part[e];
+            }
+        }
+        __syncthreads();
+    }
+    bool odd = false;
+#pragma unroll
+    for (int mi = 0; mi < 2; mi++)
+#pragma unroll
+        for (int ni = 0; ni < 2; ni++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const long long row = m0 + wm * 64 + mi * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+                const int col = n0 + wn * 64 + ni * 32 + (lane & 31);
+                if (row < n && col < d) {
+                    const float v = acc[mi][ni][e];
+                    out[(size_t)row * d + col] = v;
+                    odd = odd || !(fabsf(v) < __builtin_inff());
+                }
+            }
+    if (!__syncthreads_or(odd)) return;
+    __threadfence_block();
+    for (int i = tid; i < GT * GT; i += 256) {
+        const long long row = m0 + i / GT;
+        const int col = n0 + i % GT;
+        if (row >= n || col >= d || fabsf(out[(size_t)row * d + col]) < __builtin_inff()) continue;
+        float s = 0.f;
+        for (int k = 0; k < d; k += 4) {
+            const float4 x = rotate_load<IN>(in_v, (size_t)row * d + k), p = *reinterpret_cast<const float4*>(P + (size_t)col * d + k);
+            s = fmaf(x.x - c[k], p.x, s);
+            s = fmaf(x.y - c[k + 1], p.y, s);
+            s = fmaf(x.z - c[k + 2], p.z, s);
+            s = fmaf(x.w - c[k + 3], p.w, s);
+        }
+        out[(size_t)row * d + col] = s;
+    }
+}
+
+// The same by v_mfma_f32_32x32x2_f32, for 8-bit codes: a level is a hundredth of the largest coordinate wide, and between the
+// two forms 2.1e-5 of the codes of a set differ (4 bits 3e-6, 1 bit 6e-7), more than a change of rounding may move in an
+// index that is filled by more than one version of this library.  50,000 x 960 1,089 us, the kernel above 717.
+template <int IN>
+__global__ void __launch_bounds__(256) rotate_f32_kernel(const void* __restrict__ in_v, long long n, int d,
                                                           const float* __restrict__ P, const float* __restrict__ c,
                                                           float* __restrict__ out) {
     __shared__ __align__(16) float As[GT][GLD];
@@ -51,15 +199,7 @@ __global__ void __launch_bounds__(256) rotate_gemm_kernel(const void* __restrict
             const long long ra = m0 + srow + 32 * t < n ? m0 + srow + 32 * t : n - 1;
             const int rb = n0 + srow + 32 * t < d ? n0 + srow + 32 * t : d - 1;
             const size_t at = (size_t)ra * d + k0 + c4;
-            if (IN == JX_F16) {
-                const _Float16* hp = reinterpret_cast<const _Float16*>(in_v) + at;
-                pa[t] = make_float4((float)hp[0], (float)hp[1], (float)hp[2], (float)hp[3]);
-            } else if (IN == JX_U8) {
-                const uint8_t* bp = reinterpret_cast<const uint8_t*>(in_v) + at;
-                pa[t] = make_float4((float)bp[0], (float)bp[1], (float)bp[2], (float)bp[3]);
-            } else {
-                pa[t] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(in_v) + at);
-            }
+            pa[t] = rotate_load<IN>(in_v, at);
             pb[t] = *reinterpret_cast<const float4*>(P + (size_t)rb * d + k0 + c4);
         }
     };
@@ -107,10 +247,19 @@ __global__ void __launch_bounds__(256) rotate_gemm_kernel(const void* __restrict
             }
 }
 
-hipError_t launch_rotate(const void* in, int in_dtype, long long n, int d, const float* P, const float* c, float* out,
+hipError_t launch_rotate(const void* in, int in_dtype, long long n, int d, const float* P, const float* c, float* out, bool f32,
                          hipStream_t st) {
     if (n <= 0) return hipSuccess;
     dim3 grid((unsigned)((d + GT - 1) / GT), (unsigned)((n + GT - 1) / GT));
+    if (f32) {
+        if (in_dtype == JX_F16)
+            hipLaunchKernelGGL(rotate_f32_kernel<JX_F16>, grid, dim3(256), 0, st, in, n, d, P, c, out);
+        else if (in_dtype == JX_U8)
+            hipLaunchKernelGGL(rotate_f32_kernel<JX_U8>, grid, dim3(256), 0, st, in, n, d, P, c, out);
+        else
+            hipLaunchKernelGGL(rotate_f32_kernel<JX_F32>, grid, dim3(256), 0, st, in, n, d, P, c, out);
+        return hipGetLastError();
+    }
     if (in_dtype == JX_F16)
         hipLaunchKernelGGL(rotate_gemm_kernel<JX_F16>, grid, dim3(256), 0, st, in, n, d, P, c, out);
     else if (in_dtype == JX_U8)

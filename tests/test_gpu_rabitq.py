@@ -372,3 +372,37 @@ def test_quantize_end_to_end_other_widths(jx, bits, d, n):
     # a code that differs by one (coarse) level moves that vector's estimate; everything else agrees to rounding
     err = np.abs(dist[m] - ref["F_dist"][m]) / np.abs(ref["F_dist"]).mean()
     assert np.quantile(err, 0.98) < 1e-3 and err.max() < 0.05, (np.quantile(err, 0.98), err.max())
+
+
+@pytest.mark.parametrize("d,n", [(32, 1), (96, 127), (128, 128), (160, 129), (960, 300)])
+def test_rotation_of_every_tile_edge(jx, d, n):
+    """One row to just over a tile of them, dimensions that end inside one: products of three bfloat16 parts against double
+    sums, 1e-6 of a row's norm (sums of 32 coordinates leave 2e-7)."""
+    x = random_data(n, d, np.float32, seed=d + n)
+    P = datagen.random_orthogonal(d, d).astype(np.float32)
+    g = jx.Index(d, jx.F32, 8, 16, 1.2, capacity=max(n, 16), max_batch=1024, quant_bits=1)
+    g.insert(dev(x))
+    g.quantize(1, dev(P), query_bits=4)
+    c = g.export_codes()[2].cpu().numpy().astype(np.float64)
+    got = g.rotate(dev(x)).cpu().numpy().astype(np.float64)
+    want = (x.astype(np.float64) - c) @ P.astype(np.float64).T
+    norm = np.linalg.norm(want, axis=1, keepdims=True)
+    assert (np.abs(got - want) <= 1e-6 * norm + 1e-7 * np.abs(x).max()).all()
+
+
+def test_rotation_of_values_that_are_hardly_finite(jx):
+    """The largest float32 values round to an infinite bfloat16 part, infinities and NaN have no parts: such elements come out
+    as plain float32 sums give them."""
+    d = 64
+    P = np.eye(d, dtype=np.float32)[::-1].copy()
+    x = random_data(40, d, np.float32, seed=2)
+    g = jx.Index(d, jx.F32, 8, 16, 1.2, capacity=64, max_batch=1024, quant_bits=1)
+    g.insert(dev(x))
+    g.quantize(1, dev(P), dev(np.zeros(d, np.float32)), query_bits=4)
+    top = np.finfo(np.float32).max
+    q = x[:6].copy()
+    q[0, 3], q[1, 60], q[2, 5], q[3, 7], q[4, 9] = top, -top, 3.395e38, np.inf, np.nan
+    got = g.rotate(dev(q)).cpu().numpy()
+    assert np.array_equal(got[[0, 1, 2, 5]], q[[0, 1, 2, 5], ::-1])
+    for r, at in ((3, 7), (4, 9)):  # infinity and NaN times zero: the whole row, as the float32 sums have it
+        assert not np.isfinite(got[r]).any()
