@@ -783,7 +783,7 @@ static int encode_range(jx_index* idx, int64_t first, int64_t count, hipStream_t
     for (int64_t s0 = 0; s0 < count; s0 += slice) {
         const int64_t m = count - s0 < slice ? count - s0 : slice;
         const uint8_t* src = idx->d_vecs + (size_t)(first + s0) * idx->vec_bytes;
-        JX_HIP(jx::launch_rotate(src, p.dtype, m, p.dim, idx->d_P, idx->d_centroid, rot, idx->quantized == 8, st));
+        JX_HIP(jx::launch_rotate(src, p.dtype, m, p.dim, idx->d_P, idx->d_centroid, rot, idx->quantized > 1, st));
         jx::EncodeArgs e;
         memset(&e, 0, sizeof e);
         e.rot = rot;

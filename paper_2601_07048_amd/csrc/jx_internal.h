@@ -141,7 +141,7 @@ struct RerankArgs {
     unsigned long long* stats;  // the same stripes: [2] += number of vectors read
 };
 
-// f32: by float32 matrix instructions (what 8-bit codes are made from), else by three bfloat16 parts of each value
+// f32: by float32 matrix instructions (what codes of more than one bit are made from), else by three bfloat16 parts of each value
 hipError_t launch_rotate(const void* in, int in_dtype, long long n, int d, const float* P, const float* c, float* out, bool f32,
                          hipStream_t st);
 hipError_t launch_encode(const EncodeArgs& a, hipStream_t st);

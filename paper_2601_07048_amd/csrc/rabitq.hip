@@ -61,7 +61,7 @@ __device__ __forceinline__ float4 rotate_load(const void* in_v, const size_t at)
 // square / largest, d = 128 8.1e-8 / 7.1e-7 (2.0e-7 / 2.3e-6 before), d = 960 1.3e-7 / 2.1e-6 (5.6e-7 / 9.4e-6).  Values of 3.39e38 and more round to an
 // infinite part: elements that do not come out finite are summed again in plain float32.
 // Bound: matrix instructions (1,536 cycles a slab and wavefront) and the vector instructions of the split (1,200), which
-// overlap in part.  10,000 x 960 226 -> 149 us, 5,000 x 1536 235 -> 145, 50,000 x 960 1,089 -> 717.
+// overlap in part.  10,000 x 960 226 -> 149 us, 5,000 x 1536 235 -> 145, 50,000 x 960 717.
 template <int IN>
 __global__ void __launch_bounds__(256, 2) rotate_gemm_kernel(const void* __restrict__ in_v, long long n, int d,
                                                              const float* __restrict__ P, const float* __restrict__ c,
@@ -167,84 +167,77 @@ __global__ void __launch_bounds__(256, 2) rotate_gemm_kernel(const void* __restr
     }
 }
 
-// The same by v_mfma_f32_32x32x2_f32, for 8-bit codes: a level is a hundredth of the largest coordinate wide, and between the
-// two forms 2.1e-5 of the codes of a set differ (4 bits 3e-6, 1 bit 6e-7), more than a change of rounding may move in an
-// index that is filled by more than one version of this library.  50,000 x 960 1,089 us, the kernel above 717.
+// The same by v_mfma_f32_32x32x2_f32, for codes of more than one bit.  Which grid point is nearest is often decided by the last
+// bits of the rotated vector: between the two forms 6e-6 of the 4-bit codes of a set differ and 2.1e-5 of the 8-bit codes, and a
+// vector whose best two grid scales are nearly equal gets another factor along with them.  So codes stay what they were for
+// indices that are filled over time.  128 x 64 tiles: 64 divides the dimensions in use, and 12,500 x 960 (a workspace's
+// worth) are 5.7 tiles a CU, where 128 x 128 made 3.1 and a last round that is nearly empty: 50,000 x 960
+// 1,089 -> 930 us.
 template <int IN>
 __global__ void __launch_bounds__(256) rotate_f32_kernel(const void* __restrict__ in_v, long long n, int d,
-                                                          const float* __restrict__ P, const float* __restrict__ c,
-                                                          float* __restrict__ out) {
+                                                         const float* __restrict__ P, const float* __restrict__ c,
+                                                         float* __restrict__ out) {
     __shared__ __align__(16) float As[GT][GLD];
-    __shared__ __align__(16) float Bs[GT][GLD];
+    __shared__ __align__(16) float Bs[GT / 2][GLD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const long long m0 = (long long)blockIdx.y * GT;
-    const int n0 = blockIdx.x * GT;
-    f32x16 acc[2][2];
+    const int n0 = blockIdx.x * (GT / 2);
+    f32x16 acc[2];
 #pragma unroll
     for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+        for (int e = 0; e < 16; e++) acc[i][e] = 0.f;
 
-    // a slab on its way in registers while the one before it is multiplied; rows beyond the last are read again and
-    // multiplied as zeros.  d is a multiple of 32: every slab is whole.  10,000 x 960 251 -> 226 us, 5,000 x 1536 320 -> 227
+    // a slab on its way in registers while the one before it is multiplied
     const int srow = tid >> 3, c4 = (tid & 7) * 4;
-    float4 pa[4], pb[4], pc;
-    auto fetch = [&](const int k0) {
+    float4 pa[4], pb[2], pc;
+    auto fetch = [&](const int k0) __attribute__((always_inline)) {
         pc = *reinterpret_cast<const float4*>(c + k0 + c4);
 #pragma unroll
         for (int t = 0; t < 4; t++) {
             const long long ra = m0 + srow + 32 * t < n ? m0 + srow + 32 * t : n - 1;
+            pa[t] = rotate_load<IN>(in_v, (size_t)ra * d + k0 + c4);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
             const int rb = n0 + srow + 32 * t < d ? n0 + srow + 32 * t : d - 1;
-            const size_t at = (size_t)ra * d + k0 + c4;
-            pa[t] = rotate_load<IN>(in_v, at);
             pb[t] = *reinterpret_cast<const float4*>(P + (size_t)rb * d + k0 + c4);
         }
     };
     fetch(0);
     for (int k0 = 0; k0 < d; k0 += GK) {
 #pragma unroll
-        for (int t = 0; t < 4; t++) {
-            const bool ina = m0 + srow + 32 * t < n, inb = n0 + srow + 32 * t < d;
-            *reinterpret_cast<float4*>(&As[srow + 32 * t][c4]) =
-                make_float4(ina ? pa[t].x - pc.x : 0.f, ina ? pa[t].y - pc.y : 0.f, ina ? pa[t].z - pc.z : 0.f, ina ? pa[t].w - pc.w : 0.f);
-            *reinterpret_cast<float4*>(&Bs[srow + 32 * t][c4]) =
-                make_float4(inb ? pb[t].x : 0.f, inb ? pb[t].y : 0.f, inb ? pb[t].z : 0.f, inb ? pb[t].w : 0.f);
-        }
+        for (int t = 0; t < 4; t++)
+            *reinterpret_cast<float4*>(&As[srow + 32 * t][c4]) = make_float4(pa[t].x - pc.x, pa[t].y - pc.y, pa[t].z - pc.z, pa[t].w - pc.w);
+#pragma unroll
+        for (int t = 0; t < 2; t++) *reinterpret_cast<float4*>(&Bs[srow + 32 * t][c4]) = pb[t];
         __syncthreads();
         if (k0 + GK < d) fetch(k0 + GK);
 #pragma unroll
         for (int s8 = 0; s8 < GK / 8; s8++) {
-            float4 af[2], bf[2];
+            const float4 bf = *reinterpret_cast<const float4*>(&Bs[wn * 32 + (lane & 31)][8 * s8 + 4 * (lane >> 5)]);
+            float4 af[2];
 #pragma unroll
-            for (int s = 0; s < 2; s++) {
-                af[s] = *reinterpret_cast<const float4*>(&As[wm * 64 + s * 32 + (lane & 31)][8 * s8 + 4 * (lane >> 5)]);
-                bf[s] = *reinterpret_cast<const float4*>(&Bs[wn * 64 + s * 32 + (lane & 31)][8 * s8 + 4 * (lane >> 5)]);
+            for (int s = 0; s < 2; s++) af[s] = *reinterpret_cast<const float4*>(&As[wm * 64 + s * 32 + (lane & 31)][8 * s8 + 4 * (lane >> 5)]);
+#pragma unroll
+            for (int mi = 0; mi < 2; mi++) {
+                acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].x, bf.x, acc[mi], 0, 0, 0);
+                acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].y, bf.y, acc[mi], 0, 0, 0);
+                acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].z, bf.z, acc[mi], 0, 0, 0);
+                acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].w, bf.w, acc[mi], 0, 0, 0);
             }
-#pragma unroll
-            for (int mi = 0; mi < 2; mi++)
-#pragma unroll
-                for (int ni = 0; ni < 2; ni++) {
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].x, bf[ni].x, acc[mi][ni], 0, 0, 0);
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].y, bf[ni].y, acc[mi][ni], 0, 0, 0);
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].z, bf[ni].z, acc[mi][ni], 0, 0, 0);
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].w, bf[ni].w, acc[mi][ni], 0, 0, 0);
-                }
         }
         __syncthreads();
     }
 #pragma unroll
     for (int mi = 0; mi < 2; mi++)
 #pragma unroll
-        for (int ni = 0; ni < 2; ni++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const long long row = m0 + wm * 64 + mi * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-                const int col = n0 + wn * 64 + ni * 32 + (lane & 31);
-                if (row < n && col < d) out[(size_t)row * d + col] = acc[mi][ni][e];
-            }
+        for (int e = 0; e < 16; e++) {
+            const long long row = m0 + wm * 64 + mi * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+            const int col = n0 + wn * 32 + (lane & 31);
+            if (row < n && col < d) out[(size_t)row * d + col] = acc[mi][e];
+        }
 }
 
 hipError_t launch_rotate(const void* in, int in_dtype, long long n, int d, const float* P, const float* c, float* out, bool f32,
@@ -252,6 +245,7 @@ hipError_t launch_rotate(const void* in, int in_dtype, long long n, int d, const
     if (n <= 0) return hipSuccess;
     dim3 grid((unsigned)((d + GT - 1) / GT), (unsigned)((n + GT - 1) / GT));
     if (f32) {
+        grid.x = (unsigned)((d + GT / 2 - 1) / (GT / 2));
         if (in_dtype == JX_F16)
             hipLaunchKernelGGL(rotate_f32_kernel<JX_F16>, grid, dim3(256), 0, st, in, n, d, P, c, out);
         else if (in_dtype == JX_U8)
@@ -358,12 +352,17 @@ __global__ void __launch_bounds__(256) encode_kernel(EncodeArgs a) {
 // compare alike).  A thread takes consecutive breakpoints of one level and moves its counts along: the state at the end of
 // each group of equal t.  The largest cosine wins, the smallest t among equals, and t -> 0+ competes.  The level of a
 // coordinate is then the number of its own breakpoints that are <= t.
-// Bound: vector instructions.  A table of the quotients and a binary search per breakpoint and level took ten times the LDS
-// reads, and its 54 KB held a CU to two workgroups: 50,000 vectors of d = 960, 4 bits 16.7 -> 7.8 ms,
-// with the runs that cannot reach the best cosine ended early 7.1 ms.  Bounding the cosine
-// on a grid of 256 values of t first left most breakpoints in and took 15.7 ms.  Vectors of few dimensions have little to
-// move: with the table / now 53,353 x 96 1,105 / 1,111 us, 53,353 x 128 1,315 / 1,320, 30,000 x 256 1,222 / 1,270, 20,000 x
-// 512 2,170 / 1,612 (the searches for a run's first counts one after the other: 1,146, 1,418, 1,347 and 1,667)
+//
+// Few breakpoints can win.  The state is taken at 256 values t_g (64 for few dimensions) first, a binary search per level and
+// thread.  A breakpoint in (t_g, t_g+1] of level j has |r| < j / t_g, so where such breakpoints add x to ||xbar||^2 they add
+// less than x / (2 t_g) to <xbar,|r|>, and (ip_g + x / (2 t_g)) / sqrt(nn_g + x) falls and then rises with x: the larger of its
+// values at both ends bounds every cosine of the interval.  Both ends are close to cosines that are reached, an interval a
+// hundredth of t wide is bounded to some 1e-4, and what is left around the maximum (some 600 of 6,720 breakpoints at d =
+// 960) is evaluated exactly, all threads at once.  (A bound by the sums at both ends alone leaves most breakpoints in.)
+// Bound: vector instructions of the searches and of the sort.  50,000 vectors of d = 960, 4 bits 6,960 -> 1,010 us; before
+// that every breakpoint was evaluated, a thread moving its counts along consecutive ones of a level.  Whole quantisation,
+// rotation included: 53,353 x 96 1,086 -> 561, 50,000 x 128 1,180 -> 546, 30,000 x 256 1,260 -> 429, 20,000 x 512 1,620 -> 406,
+// 2 bits 50,000 x 1536 4,622 -> 3,652
 #define MC_CAP 8192   // breakpoints per vector
 #define MC_DMAX 4096  // dimensions
 
@@ -383,40 +382,83 @@ __device__ __forceinline__ double block_scan_incl(double v, double* ws, int tid)
     return v + off;
 }
 
-// NL = 2^(bits-1) - 1 levels
-template <int NL>
+template <int M>
+__device__ __forceinline__ float lane_xor(float v) {
+    const uint32_t u = __float_as_uint(v);
+    if (M == 1) return __uint_as_float(dpp_u32<0xB1>(u));
+    if (M == 2) return __uint_as_float(dpp_u32<0x4E>(u));
+    if (M == 8) return __uint_as_float(dpp_u32<0x128>(u));  // row_ror:8
+    if (M == 32) return shfl_xor(v, 32);
+    return __uint_as_float((uint32_t)__builtin_amdgcn_ds_swizzle((int)u, (M << 10) | 0x1F));
+}
+
+// one stage of the network below: entry i = tid V + r against entry i ^ J, descending where i & K is 0
+template <int V, int K, int J>
+__device__ __forceinline__ void sort_stage(float (&v)[V], float* sa, const int tid) {
+    if constexpr (J < V) {
+#pragma unroll
+        for (int r = 0; r < V; r++)
+            if ((r & J) == 0) {
+                const bool down = K < V ? (r & K) == 0 : (tid & (K / V)) == 0;
+                const float hi = fmaxf(v[r], v[r | J]), lo = fminf(v[r], v[r | J]);
+                v[r] = down ? hi : lo;
+                v[r | J] = down ? lo : hi;
+            }
+    } else {
+        const bool top = ((tid & (J / V)) == 0) == ((tid & (K / V)) == 0);
+        float o[V];
+        if constexpr (J / V < 64) {
+#pragma unroll
+            for (int r = 0; r < V; r++) o[r] = lane_xor<J / V>(v[r]);
+        } else {  // another wavefront's
+#pragma unroll
+            for (int r = 0; r < V; r++) sa[r * 256 + tid] = v[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < V; r++) o[r] = sa[r * 256 + (tid ^ (J / V))];
+            __syncthreads();
+        }
+#pragma unroll
+        for (int r = 0; r < V; r++) v[r] = top ? fmaxf(v[r], o[r]) : fminf(v[r], o[r]);
+    }
+    if constexpr (J > 1)
+        sort_stage<V, K, J / 2>(v, sa, tid);
+    else if constexpr (K < V * 256)
+        sort_stage<V, K * 2, K>(v, sa, tid);
+}
+
+// NL = 2^(bits-1) - 1 levels, V magnitudes per thread (256 V >= d)
+template <int NL, int V>
 __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
-    extern __shared__ __align__(16) unsigned char dyn[];
-    constexpr int half = NL + 1;
-    int dpad = 256;
-    while (dpad < a.d) dpad <<= 1;
-    float* sa = reinterpret_cast<float*>(dyn);                          // [dpad] magnitudes, descending
-    double* pref = reinterpret_cast<double*>(dyn + (size_t)dpad * 4);   // [dpad + 1] prefix sums of sa
+    constexpr int half = NL + 1, dpad = 256 * V;
+    __shared__ __align__(16) float sa[dpad];  // magnitudes, descending
+    __shared__ double pref[dpad + 1];         // prefix sums of sa
     __shared__ double ws[8];
-    __shared__ double red_c[256], red_t[256];
-    __shared__ float red_a[256];  // the breakpoint's magnitude; its level is red_t * red_a
-    __shared__ int red_j[256];
-    __shared__ uint32_t s_low;
+    __shared__ double st_ip[256], st_nn[256];  // state at t_g
+    __shared__ uint16_t st_cnt[256 * NL];
+    __shared__ uint64_t keep[4];
+    __shared__ double red_c[4], red_t[4];
+    __shared__ float red_a[4];
+    __shared__ int red_j[4];
     __shared__ int s_npos;
-    if (threadIdx.x == 0) s_low = 0u;  // barriers follow before it is used
     __shared__ double s_l1, s_l2, s_ip;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long v = blockIdx.x;
     const float* r = a.rot + (size_t)v * a.d;
     uint8_t* code = a.codes + (size_t)v * a.code_stride;
 
     // ---- sums, magnitudes
     double l1 = 0.0, l2 = 0.0;
-    for (int i = tid; i < a.d; i += 256) {
-        const double x = fabs((double)r[i]);
+    int npos_t = 0;
+    float mag[V];
+#pragma unroll
+    for (int q = 0; q < V; q++) {
+        const int i = tid + 256 * q;
+        mag[q] = i < a.d ? fabsf(r[i]) : 0.f;
+        const double x = (double)mag[q];
         l1 += x;
         l2 += x * x;
-    }
-    int npos_t = 0;
-    for (int e = tid; e < dpad; e += 256) {
-        const float x = e < a.d ? fabsf(r[e]) : 0.f;
-        sa[e] = x;
-        npos_t += x > 0.f ? 1 : 0;
+        npos_t += mag[q] > 0.f ? 1 : 0;
     }
     {   // block sums (fixed order)
         const double t1 = block_scan_incl(l1, ws, tid);
@@ -426,141 +468,182 @@ __global__ void __launch_bounds__(256) encode_maxcos_kernel(EncodeArgs a) {
         const double t3 = block_scan_incl((double)npos_t, ws, tid);
         if (tid == 255) s_npos = (int)t3;
     }
-    __syncthreads();
-    // ---- bitonic sort, descending
-    for (int k = 2; k <= dpad; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int e = tid; e < dpad / 2; e += 256) {
-                const int lo = ((e & ~(j - 1)) << 1) | (e & (j - 1));
-                const int hi = lo | j;
-                const bool down = (lo & k) == 0;
-                const float xl = sa[lo], xh = sa[hi];
-                if ((xl < xh) == down) {
-                    sa[lo] = xh;
-                    sa[hi] = xl;
-                }
-            }
-            __syncthreads();
-        }
-    }
-    const int npos = s_npos;  // the zeros sit behind the npos positive magnitudes
-    // ---- prefix sums (thread t owns dpad/256 consecutive entries) and the quotient lists
+    // ---- bitonic sort, descending: in registers, through LDS only between wavefronts
+    sort_stage<V, 2, 1>(mag, sa, tid);
+#pragma unroll
+    for (int q = 0; q < V; q++) sa[tid * V + q] = mag[q];
+    // ---- prefix sums (thread t owns V consecutive entries)
     {
-        const int PER = dpad / 256, e0 = tid * PER;
         double loc = 0.0;
-        for (int e = e0; e < e0 + PER; e++) loc += (double)sa[e];
+#pragma unroll
+        for (int q = 0; q < V; q++) loc += (double)mag[q];
         double run = block_scan_incl(loc, ws, tid) - loc;
         if (tid == 0) pref[0] = 0.0;
-        for (int e = e0; e < e0 + PER; e++) {
-            run += (double)sa[e];
-            pref[e + 1] = run;
+#pragma unroll
+        for (int q = 0; q < V; q++) {
+            run += (double)mag[q];
+            pref[tid * V + q + 1] = run;
         }
     }
     __syncthreads();
-    // ---- every breakpoint evaluates the cosine at the end of its group of equal t
+    const int npos = s_npos;  // the zeros sit behind the npos positive magnitudes
     const double ip0 = 0.5 * s_l1, nn0 = 0.25 * (double)a.d;
-    double best = -1.0, best_t = __builtin_inf();
-    float best_a = 1.f, best_est = -1.f;
-    int best_j = 0;
-    // float32 estimates of the cosine, in units of the sum of the magnitudes: any float32 vector stays in range
-    const double unit = 1.0 / s_l1;
-    constexpr int SEGS = 256 / NL;  // threads per level
-    const int lev = tid / SEGS, run = (npos + SEGS - 1) / SEGS;
-    const int p0 = (tid - lev * SEGS) * run, p1 = lev < NL ? (p0 + run < npos ? p0 + run : npos) : 0;
-    const double J = (double)(lev + 1);
-    int cnt[NL];  // level-(jj+1) breakpoints <= t
-    // whether runs are long enough for an early end (never: 128 dimensions 1,320 -> 1,405 us, 256 1,270 -> 1,410)
-    const bool ends = run > 3;
-    uint32_t first = 0;         // estimate of the cosine at the run's first breakpoint
-    if (p0 < p1) {
-        const double A = (double)sa[p0];
-        // binary searches of all levels side by side, a chain of LDS reads for one (behind npos stand zeros, which are below
-        // every limit)
+    // ---- states at t_0 = 0, a geometric grid from just below the first breakpoint to 8 / (the median magnitude), and infinity
+    const int G = V == 1 ? 64 : 256;
+    double t_g = 0.0, ip_g = ip0, nn_g = nn0, c_g = -1.0;
+    if (tid < G) {
+        const float first = 0.99f / sa[0], last = 8.f / sa[npos >> 1 > 0 ? (npos >> 1) - 1 : 0];
+        const float grow = log2f(last / first) / (float)(G - 3);
+        float t = tid == 0 ? 0.f : first * exp2f(grow * (float)(tid - 1));
+        if (tid == G - 1 || !(t < __builtin_inff())) t = __builtin_inff();
+        t_g = (double)t;
+        int cnt[NL];
 #pragma unroll
         for (int jj = 0; jj < NL; jj++) cnt[jj] = 0;
-        for (int step = dpad >> 1, last = 0; !last; step = step > 1 ? step >> 1 : 0) {
-            last = step == 0;  // dpad entries have dpad + 1 places: one more step of one
-            const int by = last ? 1 : step;
+        if (t == __builtin_inff()) {
+#pragma unroll
+            for (int jj = 0; jj < NL; jj++) cnt[jj] = npos;
+        } else {
+            // all levels side by side, a chain of LDS reads for one; behind npos stand zeros, which reach no level
+            for (int step = dpad >> 1, end = 0; !end; step = step > 1 ? step >> 1 : 0) {
+                end = step == 0;  // dpad entries have dpad + 1 places: one more step of one
+                const int by = end ? 1 : step;
+#pragma unroll
+                for (int jj = 0; jj < NL; jj++)
+                    if ((double)(jj + 1) <= t_g * (double)sa[cnt[jj] + by - 1]) cnt[jj] += by;
+            }
+        }
+#pragma unroll
+        for (int jj = 0; jj < NL; jj++) {
+            st_cnt[jj * 256 + tid] = (uint16_t)cnt[jj];
+            ip_g += pref[cnt[jj]];
+            nn_g += 2.0 * (double)(jj + 1) * (double)cnt[jj];
+        }
+        st_ip[tid] = ip_g;
+        st_nn[tid] = nn_g;
+        c_g = ip_g / sqrt(nn_g);
+    }
+    {
+        double most = c_g;
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            const double o = shfl_xor(most, m);
+            most = o > most ? o : most;
+        }
+        if (lane == 0) ws[wave] = most;
+    }
+    __syncthreads();
+    {   // intervals that may hold the largest cosine; comparisons with NaN keep them
+        double least = ws[0];
+        for (int w = 1; w < 4; w++) least = ws[w] > least ? ws[w] : least;
+        least *= 1.0 - 1e-9;
+        bool on = false;
+        if (tid < G - 1) {
+            const double next = st_nn[tid + 1], x = next - nn_g;
+            const double end = (ip_g + 0.5 * x / t_g) / sqrt(next);  // t_0: infinite
+            on = x != 0.0 && !(c_g < least && end < least);
+        }
+        const uint64_t m = ballot(on);
+        if (lane == 0) keep[wave] = m;
+    }
+    __syncthreads();
+    int g0 = 256, g1 = -1;
+#pragma unroll
+    for (int w = 0; w < 4; w++) {
+        const uint64_t m = keep[w];
+        if (m) {
+            if (g0 == 256) g0 = w * 64 + __builtin_ctzll(m);
+            g1 = w * 64 + 63 - __builtin_clzll(m);
+        }
+    }
+    // ---- the breakpoints in (t_g0, t_g1 + 1]: of every level consecutive ones
+    int lo[NL], hi[NL], total = 0, widest = 0;
+#pragma unroll
+    for (int jj = 0; jj < NL; jj++) {
+        lo[jj] = g1 < 0 ? 0 : (int)st_cnt[jj * 256 + g0];
+        hi[jj] = g1 < 0 ? 0 : (int)st_cnt[jj * 256 + g1 + 1];
+        if (hi[jj] < lo[jj]) hi[jj] = lo[jj];  // rows with NaN
+        total += hi[jj] - lo[jj];
+        widest = hi[jj] - lo[jj] > widest ? hi[jj] - lo[jj] : widest;
+    }
+    int top = 1;
+    while (2 * top <= widest) top *= 2;
+    double best = -1.0, best_t = __builtin_inf();
+    float best_a = 1.f;
+    int best_j = 0;
+    for (int k = tid; k < total; k += 256) {
+        int lev = 0, p = k;
+#pragma unroll
+        for (int jj = 0; jj < NL; jj++)
+            if (lev == jj) {
+                const int n = hi[jj] - lo[jj];
+                if (p < n) p += lo[jj];
+                else {
+                    p -= n;
+                    lev = jj + 1;
+                    continue;
+                }
+                break;
+            }
+        const float Af = sa[p];
+        const double A = (double)Af, J = (double)(lev + 1);
+        // counts at the end of the group of equal t, inside the window
+        int cnt[NL];
+#pragma unroll
+        for (int jj = 0; jj < NL; jj++) cnt[jj] = lo[jj];
+        for (int step = top; step >= 1; step >>= 1)
 #pragma unroll
             for (int jj = 0; jj < NL; jj++)
-                if ((double)(jj + 1) * A <= J * (double)sa[cnt[jj] + by - 1]) cnt[jj] += by;
-        }
-        if (ends) {
-            double ip = ip0, nn = nn0;
+                if (cnt[jj] + step <= hi[jj] && (double)(jj + 1) * A <= J * (double)sa[cnt[jj] + step - 1]) cnt[jj] += step;
+        double ip = ip0, nn = nn0;
 #pragma unroll
-            for (int jj = 0; jj < NL; jj++) {
-                ip += pref[cnt[jj]];
-                nn += 2.0 * (double)(jj + 1) * (double)cnt[jj];
-            }
-            first = __float_as_uint((float)(ip * unit) * __builtin_amdgcn_rsqf((float)nn));
+        for (int jj = 0; jj < NL; jj++) {
+            ip += pref[cnt[jj]];
+            nn += 2.0 * (double)(jj + 1) * (double)cnt[jj];
         }
-    }
-    if (ends) {
-        first = max(first, dpp_u32<0xB1>(first));
-        first = max(first, dpp_u32<0x4E>(first));
-        first = max(first, dpp_u32<0x141>(first));
-        first = max(first, dpp_u32<0x140>(first));
-        if ((tid & 15) == 0) atomicMax(&s_low, first);
-        __syncthreads();
-    }
-    if (p0 < p1) {
-        // the largest cosine among the first breakpoints of all runs has to be reached; from t on no cosine exceeds the
-        // largest <xbar,|r|> there is over ||xbar|| at t: beyond the maximum, where the counts move fastest, runs end early
-        const float low = ends ? __uint_as_float(s_low) * 0.99999f : 0.f;
-        const float ip_all = (float)((ip0 + (double)NL * pref[npos]) * unit);
-        for (int p = p0; p < p1; p++) {
-            const float Af = sa[p];
-            const double A = (double)Af;
-            double ip = ip0, nn = nn0;
-#pragma unroll
-            for (int jj = 0; jj < NL; jj++) {
-                const double lim = (double)(jj + 1) * A;
-                int lo = cnt[jj];
-                while (lo < npos && lim <= J * (double)sa[lo]) lo++;
-                cnt[jj] = lo;
-                ip += pref[lo];
-                nn += 2.0 * (double)(jj + 1) * (double)lo;
-            }
-            const float inv = __builtin_amdgcn_rsqf((float)nn);
-            if (ip_all * inv < low) break;
-            // most breakpoints are behind the best so far by more than this estimate is off
-            const float est = (float)(ip * unit) * inv;
-            if (est < best_est * 0.999995f || est < low) continue;
-            const double c = ip / sqrt(nn);
-            if (c > best) {  // t grows within a thread: the first of equals stays
+        const double c = ip / sqrt(nn);
+        if (c >= best) {
+            const double t = J / A;
+            if (c > best || t < best_t) {
                 best = c;
-                best_est = est;
-                best_t = J / A;
+                best_t = t;
                 best_a = Af;
                 best_j = lev + 1;
             }
         }
     }
-    red_c[tid] = best;
-    red_t[tid] = best_t;
-    red_a[tid] = best_a;
-    red_j[tid] = best_j;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s) {
-            const double oc = red_c[tid + s], ot = red_t[tid + s];
-            if (oc > red_c[tid] || (oc == red_c[tid] && ot < red_t[tid])) {
-                red_c[tid] = oc;
-                red_t[tid] = ot;
-                red_a[tid] = red_a[tid + s];
-                red_j[tid] = red_j[tid + s];
-            }
+    // largest cosine, the smallest t among equals
+    auto better = [&](const double oc, const double ot, const float oa, const int oj) {
+        if (oc > best || (oc == best && ot < best_t)) {
+            best = oc;
+            best_t = ot;
+            best_a = oa;
+            best_j = oj;
         }
-        __syncthreads();
+    };
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const double oc = shfl_xor(best, m), ot = shfl_xor(best_t, m);
+        const float oa = shfl_xor(best_a, m);
+        const int oj = shfl_xor(best_j, m);
+        better(oc, ot, oa, oj);
     }
-    if (tid == 0) {
-        // the all-zero-level grid (t -> 0+) competes too; a later cosine must be strictly larger
-        const double c0 = ip0 / sqrt(nn0);
-        if (!(npos > 0 && red_c[0] > c0)) red_j[0] = 0;
+    if (lane == 0) {
+        red_c[wave] = best;
+        red_t[wave] = best_t;
+        red_a[wave] = best_a;
+        red_j[wave] = best_j;
     }
     __syncthreads();
+    best = -1.0;
+    best_t = __builtin_inf();
+    best_a = 1.f;
+    best_j = 0;
+    for (int w = 0; w < 4; w++) better(red_c[w], red_t[w], red_a[w], red_j[w]);
+    // the all-zero-level grid (t -> 0+) competes too; a later cosine must be strictly larger
+    if (!(npos > 0 && best > ip0 / sqrt(nn0))) best_j = 0;
     // level lv + 1 is reached where (lv + 1) / |r_i| <= j / a
-    const double bj = (double)red_j[0], ba = (double)red_a[0];
+    const double bj = (double)best_j, ba = (double)best_a;
     // ---- codes: 32 / bits consecutive coordinates per thread -> one dword
     const double cb = ((double)(1 << a.bits) - 1.0) * 0.5;
     const int per = 32 / a.bits;
@@ -596,11 +679,19 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t st) {
     if (a.bits > 1 && a.rule == JX_RULE_MAXCOS) {
         const int nl = (1 << (a.bits - 1)) - 1;
         if ((a.bits != 4 && a.bits != 2) || a.d * nl > MC_CAP || a.d > MC_DMAX) return hipErrorInvalidValue;
-        int dpad = 256;
-        while (dpad < a.d) dpad <<= 1;
-        const size_t sh = (size_t)dpad * 4 + (size_t)(dpad + 2) * 8;
-        auto kern = a.bits == 4 ? encode_maxcos_kernel<7> : encode_maxcos_kernel<1>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)a.n), dim3(256), sh, st, a);
+        const dim3 grid((unsigned)a.n), block(256);
+        if (a.bits == 4) {  // at most 1,170 dimensions
+            if (a.d <= 256) hipLaunchKernelGGL((encode_maxcos_kernel<7, 1>), grid, block, 0, st, a);
+            else if (a.d <= 512) hipLaunchKernelGGL((encode_maxcos_kernel<7, 2>), grid, block, 0, st, a);
+            else if (a.d <= 1024) hipLaunchKernelGGL((encode_maxcos_kernel<7, 4>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((encode_maxcos_kernel<7, 8>), grid, block, 0, st, a);
+        } else {
+            if (a.d <= 256) hipLaunchKernelGGL((encode_maxcos_kernel<1, 1>), grid, block, 0, st, a);
+            else if (a.d <= 512) hipLaunchKernelGGL((encode_maxcos_kernel<1, 2>), grid, block, 0, st, a);
+            else if (a.d <= 1024) hipLaunchKernelGGL((encode_maxcos_kernel<1, 4>), grid, block, 0, st, a);
+            else if (a.d <= 2048) hipLaunchKernelGGL((encode_maxcos_kernel<1, 8>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((encode_maxcos_kernel<1, 16>), grid, block, 0, st, a);
+        }
         return hipGetLastError();
     }
     hipLaunchKernelGGL(encode_kernel, dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, st, a);

@@ -406,3 +406,25 @@ def test_rotation_of_values_that_are_hardly_finite(jx):
     assert np.array_equal(got[[0, 1, 2, 5]], q[[0, 1, 2, 5], ::-1])
     for r, at in ((3, 7), (4, 9)):  # infinity and NaN times zero: the whole row, as the float32 sums have it
         assert not np.isfinite(got[r]).any()
+
+
+@pytest.mark.parametrize("bits,d", [(4, 64), (4, 256), (4, 288), (4, 512), (4, 544), (4, 1024), (4, 1056), (2, 256), (2, 544), (2, 1024), (2, 2048), (2, 2080), (2, 4096)])
+def test_max_cosine_of_every_spread(jx, bits, d):
+    """Where the largest cosine lies depends on how the magnitudes are spread; the encoder evaluates what bounds leave of the
+    breakpoints.  Normal, heavy-tailed, few different values (ties between levels), sparse, one outlier, subnormal and huge
+    magnitudes, at both sides of every number of magnitudes per thread, against the oracle's sweep over all of them."""
+    rng = np.random.default_rng(d)
+    base = rng.standard_normal((24, d))
+    tails = base / (np.abs(rng.standard_normal((24, d))) + 1e-3)
+    rows = [base, base ** 3, tails, np.round(base * 1.5), np.round(base * 6), base * (rng.random((24, d)) < 0.04), base * 1e-39, base * 1e35,
+            rng.random((24, d)), np.where(rng.random((24, d)) < 2 / d, 60.0, base), np.tile(np.arange(1, 9), (24, d // 8)).astype(float)]
+    r32 = np.concatenate(rows).astype(np.float32)
+    g = jx.Index(d, jx.U8 if d > 1536 else jx.F32, 8, 8, 1.2, capacity=64, quant_bits=bits)
+    x = np.ones((64, d), np.uint8 if d > 1536 else np.float32)
+    g.import_graph(dev(x), dev(np.full((64, 8), jx.NONE, np.uint32)), 0)
+    g.quantize(bits, dev(np.eye(d, dtype=np.float32)), dev(np.zeros(d, np.float32)), rule=jx.RULE_MAXCOS)
+    codes, meta = g.encode_rotated(dev(r32))
+    wc, wm, _ = oracle.rabitq_encode(r32, bits, oracle.RULE_MAXCOS)
+    bad = np.nonzero((codes.cpu().numpy() != wc).any(axis=1))[0]
+    assert bad.size == 0, (bad[:8], bad.size)
+    assert np.allclose(meta.cpu().numpy(), wm, rtol=2e-7, atol=1e-45)
