@@ -277,7 +277,16 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
             }
         if (half == hcol) {
             L->nrm[wave * 32 + col] = dv;
-            if (DT == JX_F32 && wave * 32 + col < n_fixed) L->dp[wave * 32 + col] = dv;
+            if (DT == JX_F32 && wave * 32 + col < n_fixed) {
+                if (dv != dv) {  // a square overflowed, or a value is not finite: products of the parts have both signs
+                    dv = 0.f;
+                    const float* xr = reinterpret_cast<const float*>(recs + (size_t)L->id[wave * 32 + col] * stride);
+                    const float* pr = reinterpret_cast<const float*>(recs + (size_t)p * stride);
+#pragma unroll 1
+                    for (int e = 0; e < vec_bytes / 4; e++) dv = fmaf(xr[e] - pr[e], xr[e] - pr[e], dv);
+                }
+                L->dp[wave * 32 + col] = dv;
+            }
         }
         if (want_dp) {
             if constexpr (DT == JX_F16) fpp = group_sum<8>(fpp);

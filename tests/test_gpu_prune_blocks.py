@@ -64,6 +64,23 @@ def test_rows_that_are_not_finite(jx):
     assert np.all((adj < n) | (adj == 0xFFFFFFFF))
 
 
+def test_distances_that_overflow(jx):
+    """Rows whose squared distance to every other one is infinite: products of the parts of such a value are infinite with
+    both signs, and the distance of a present neighbour has to stay infinite, as the list-based kernels have it."""
+    n, d = 600, 100
+    x = datagen.dyadic_grid(n, d, seed=5).astype(np.float32)
+    rng = np.random.default_rng(6)
+    far = rng.choice(n, 40, replace=False)
+    x[far] = (rng.uniform(1, 2, (40, d)) * 1e22).astype(np.float32)
+    for R, L in ((16, 60), (32, 140)):
+        gs = [jx.Index(d, jx.F32, R, L, 1.2, capacity=n, max_batch=n, batch_growth=1.0, flags=f) for f in (0, jx.FLAG_NO_GRAM)]
+        for lo, hi in ((0, 200), (200, 350), (350, n)):
+            for g in gs:
+                g.insert(dev(x[lo:hi]))
+            a, b = (u32(g.export_graph()[0]) for g in gs)
+            assert np.array_equal(a, b), (R, lo, np.flatnonzero((a != b).any(1))[:5])
+
+
 @pytest.mark.parametrize("d", [16, 96, 128, 144, 256, 272])
 @pytest.mark.parametrize("R,L", [(8, 31), (12, 33), (31, 64), (33, 65), (64, 96), (63, 128), (100, 200), (256, 300)])
 def test_pivot_rounds_u8(jx, d, R, L):
