@@ -597,63 +597,109 @@ __global__ void __launch_bounds__(256) radix_scatter8_kernel(const uint64_t* key
     }
 }
 
-// ---- small edge buffers: bitonic chunks in LDS, then merge passes
+// ---- small edge buffers: chunks sorted by a workgroup each, then merge passes
 //
 // A pass of the radix sort is three launches of 4 to 14 us however few the keys are, and a sort is six or eight passes:
-// most of an insertion of a few points.  Up to SORT_ONE pairs are sorted by one workgroup in LDS, which lists the segments
-// as well; up to SORT_MERGE pairs by a workgroup per SORT_CHUNK pairs and a launch per doubling of the runs, every pair
-// finding its place by binary search in the neighbouring run.  The order is (key, value): what the stable radix sort
+// most of an insertion of a few points.  Up to SORT_ONE pairs are sorted by one workgroup, which lists the segments as well;
+// up to SORT_MERGE pairs by a workgroup per SORT_CHUNK pairs and a launch per eightfold of the runs, every pair
+// finding its place by binary searches in up to seven neighbouring runs.  The order is (key, value): what the stable radix sort
 // gives, because equal keys are emitted in ascending order of their values.
-// 16 insert calls of 32 points (2,048 pairs each) 6.65 -> 5.12 ms, a build of 200,000 points 43.4 -> 36.9 ms.
-#define SORT_ONE 8192
-#define SORT_CHUNK 4096
+// A chunk is a bitonic network over V pairs per thread in registers: strides below V are moves inside a thread, those below
+// 64 V go from lane to lane, and only the few that are wider through LDS with a barrier.  With every stride through LDS
+// 4,096 pairs took 53 us, now 28; 2,048 27.8 and 17, 20,000 80 and 43, 600,000 188 and 163.  Chunks of 2,048: two of them and a
+// merge are done before one workgroup has sorted 8,192 (55 us).  Beyond 2^20 the radix sort takes over: 2.4 M pairs 478 us,
+// 626 by merges.
+#define SORT_ONE 4096
+#define SORT_CHUNK 2048  // 4,096 beyond 2^18 pairs, where the last pass merges four runs instead of eight: 2^20 pairs 252 us -> 220
 #define SORT_MERGE (1 << 20)
 
-// one workgroup per `cap` pairs (a power of two); heads / counters: NULL, or the segment list of a single chunk
-__global__ void __launch_bounds__(1024) sort_chunk_kernel(const uint64_t* keys, const uint32_t* vals, uint64_t* keys_out, uint32_t* vals_out,
-                                                         long long n, int cap, uint32_t* heads, uint32_t* counters) {
+__device__ __forceinline__ bool pair_after(uint64_t a, uint32_t x, uint64_t b, uint32_t y) { return a > b || (a == b && x > y); }
+
+// one stage of the network: pair i = tid V + r against pair i ^ J, ascending where i & K is 0, and the stages that follow
+template <int T, int V, int K, int J>
+__device__ __forceinline__ void sort_pairs(uint64_t (&k)[V], uint32_t (&v)[V], uint64_t* sk, uint32_t* sv, const int tid) {
+    if constexpr (J < V) {
+#pragma unroll
+        for (int r = 0; r < V; r++)
+            if ((r & J) == 0) {
+                const bool up = K < V ? (r & K) == 0 : (tid & (K / V)) == 0;
+                const uint64_t a = k[r], b = k[r | J];
+                const uint32_t x = v[r], y = v[r | J];
+                const bool swap = pair_after(a, x, b, y) == up;
+                k[r] = swap ? b : a;
+                k[r | J] = swap ? a : b;
+                v[r] = swap ? y : x;
+                v[r | J] = swap ? x : y;
+            }
+    } else {
+        const bool low = ((tid & (J / V)) == 0) == ((tid & (K / V)) == 0);  // keeps the smaller one
+        if constexpr (J / V >= 64) {  // another wavefront's
+            __syncthreads();  // what was read last is no longer needed
+#pragma unroll
+            for (int r = 0; r < V; r++) {
+                sk[r * T + tid] = k[r];
+                sv[r * T + tid] = v[r];
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int r = 0; r < V; r++) {
+            uint64_t b;
+            uint32_t y;
+            if constexpr (J / V < 64) {
+                b = (uint64_t)lane_xor_u32<J / V>((uint32_t)(k[r] >> 32)) << 32 | lane_xor_u32<J / V>((uint32_t)k[r]);
+                y = lane_xor_u32<J / V>(v[r]);
+            } else {
+                b = sk[r * T + (tid ^ (J / V))];
+                y = sv[r * T + (tid ^ (J / V))];
+            }
+            const bool take = pair_after(k[r], v[r], b, y) == low;
+            k[r] = take ? b : k[r];
+            v[r] = take ? y : v[r];
+        }
+    }
+    if constexpr (J > 1)
+        sort_pairs<T, V, K, J / 2>(k, v, sk, sv, tid);
+    else if constexpr (K < T * V)
+        sort_pairs<T, V, K * 2, K>(k, v, sk, sv, tid);
+}
+
+// one workgroup per T V pairs; heads / counters: NULL, or the segment list of a single chunk
+template <int T, int V>
+__global__ void __launch_bounds__(T) sort_chunk_kernel(const uint64_t* keys, const uint32_t* vals, uint64_t* keys_out, uint32_t* vals_out,
+                                                      long long n, uint32_t* heads, uint32_t* counters) {
     extern __shared__ __align__(16) unsigned char dyn[];
-    uint64_t* sk = reinterpret_cast<uint64_t*>(dyn);        // [cap]
-    uint32_t* sv = reinterpret_cast<uint32_t*>(sk + cap);   // [cap]
+    uint64_t* sk = reinterpret_cast<uint64_t*>(dyn);          // [T V]
+    uint32_t* sv = reinterpret_cast<uint32_t*>(sk + T * V);   // [T V]
     __shared__ uint32_t wsum[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long base = (long long)blockIdx.x * cap;
-    const int m = (int)(n - base < cap ? n - base : cap);
-    for (int i = tid; i < cap; i += 1024) {
-        sk[i] = i < m ? keys[base + i] : JX_EMPTY_KEY;
-        sv[i] = i < m ? vals[base + i] : JX_NONE_ID;
-    }
-    __syncthreads();
-    for (int k = 2; k <= cap; k <<= 1) {
-        for (int j = k >> 1; j >= 1; j >>= 1) {
-            for (int p = tid; p < cap / 2; p += 1024) {
-                const int lo = ((p & ~(j - 1)) << 1) | (p & (j - 1)), hi = lo | j;
-                const uint64_t a = sk[lo], b = sk[hi];
-                const uint32_t x = sv[lo], y = sv[hi];
-                const bool after = a > b || (a == b && x > y);
-                if (after == ((lo & k) == 0)) {
-                    sk[lo] = b;
-                    sk[hi] = a;
-                    sv[lo] = y;
-                    sv[hi] = x;
-                }
-            }
-            // the 64 pairs of a wavefront lie in 128 neighbouring places while j <= 64: only before and after wider
-            // strides do the wavefronts wait for each other
-            if (j > 64 || (j == 1 && k > 64))
-                __syncthreads();
-            else
-                wave_sync();
+    const long long base = (long long)blockIdx.x * (T * V);
+    const int m = (int)(n - base < T * V ? n - base : T * V);
+    {
+        uint64_t k[V];
+        uint32_t v[V];
+#pragma unroll
+        for (int r = 0; r < V; r++) {
+            const int i = r * T + tid;
+            k[r] = i < m ? keys[base + i] : JX_EMPTY_KEY;
+            v[r] = i < m ? vals[base + i] : JX_NONE_ID;
+        }
+        sort_pairs<T, V, 2, 1>(k, v, sk, sv, tid);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < V; r++) {
+            sk[tid * V + r] = k[r];
+            sv[tid * V + r] = v[r];
         }
     }
     __syncthreads();
-    for (int i = tid; i < m; i += 1024) {
+    for (int i = tid; i < m; i += T) {
         keys_out[base + i] = sk[i];
         vals_out[base + i] = sv[i];
     }
     if (!heads) return;
     uint32_t done = 0;  // heads of the pairs before this round's
-    for (int i0 = 0; i0 < m; i0 += 1024) {
+    for (int i0 = 0; i0 < m; i0 += T) {
         const int i = i0 + tid;
         const uint32_t t = i < m ? (uint32_t)(sk[i] >> 32) : JX_NONE_ID;
         const bool head = t != JX_NONE_ID && (i == 0 || (uint32_t)(sk[i - 1] >> 32) != t);
@@ -661,7 +707,7 @@ __global__ void __launch_bounds__(1024) sort_chunk_kernel(const uint64_t* keys, 
         if (lane == 0) wsum[wave] = (uint32_t)__builtin_popcountll(hm);
         __syncthreads();
         uint32_t before = done, all = 0;
-        for (int w = 0; w < 16; w++) {
+        for (int w = 0; w < T / 64; w++) {
             before += w < wave ? wsum[w] : 0u;
             all += wsum[w];
         }
@@ -672,30 +718,52 @@ __global__ void __launch_bounds__(1024) sort_chunk_kernel(const uint64_t* keys, 
     if (tid < 16) counters[tid] = tid == 0 ? done : 0u;
 }
 
-// sorted runs of `run` pairs -> runs of twice as many
+template <int T, int V>
+static hipError_t launch_sort_chunk(const uint64_t* keys, const uint32_t* vals, uint64_t* keys_out, uint32_t* vals_out, long long n,
+                                    uint32_t* heads, uint32_t* counters, hipStream_t st) {
+    const size_t sh = (size_t)T * V * 12;  // at most 48 KB
+    hipLaunchKernelGGL((sort_chunk_kernel<T, V>), dim3((unsigned)((n + T * V - 1) / (T * V))), dim3(T), sh, st, keys, vals, keys_out, vals_out, n,
+                       heads, counters);
+    return hipGetLastError();
+}
+
+// sorted runs of `run` pairs (a power of two, at least 256) -> runs of WAYS times as many
+template <int WAYS>
 __global__ void __launch_bounds__(256) merge_runs_kernel(const uint64_t* keys, const uint32_t* vals, uint64_t* keys_out, uint32_t* vals_out,
-                                                        long long n, long long run) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+                                                        int n, int run) {
+    const int b0 = (int)blockIdx.x * 256, i = b0 + (int)threadIdx.x;
     if (i >= n) return;
+    const int group = b0 / (run * WAYS) * (run * WAYS), own = (b0 - group) / run;  // the same for the whole workgroup
     const uint64_t k = keys[i];
     const uint32_t v = vals[i];
-    const long long r = i / run, pair = (r >> 1) * 2 * run;
-    const bool right = r & 1;
-    const long long o0 = right ? pair : pair + run;  // the neighbouring run
-    const long long o1 = o0 + run < n ? o0 + run : n;
-    long long lo = o0 < n ? o0 : n, hi = o1;
-    if (hi < lo) hi = lo;
-    const long long first = lo;
-    while (lo < hi) {  // its pairs that come before this one; of equal pairs (padding) the left run's come first
-        const long long mid = (lo + hi) >> 1;
-        const uint64_t ko = keys[mid];
-        const bool before = ko < k || (ko == k && (vals[mid] < v || (right && vals[mid] == v)));
-        if (before)
-            lo = mid + 1;
-        else
-            hi = mid;
+    const bool padding = k == JX_EMPTY_KEY;  // all alike: those of earlier runs come first
+    int cnt[WAYS], len[WAYS];
+#pragma unroll
+    for (int o = 0; o < WAYS; o++) {
+        const long long left = (long long)n - group - (long long)o * run;
+        len[o] = o == own || left <= 0 ? 0 : left < run ? (int)left : run;
+        cnt[o] = 0;
     }
-    const long long at = pair + (i - r * run) + (lo - first);
+    // in each run the pairs that come before this one; the loads of a step are under way together
+    for (int step = run; step >= 1; step >>= 1) {
+        int at[WAYS];
+        uint64_t ko[WAYS];
+#pragma unroll
+        for (int o = 0; o < WAYS; o++) {
+            at[o] = cnt[o] + step <= len[o] ? group + o * run + cnt[o] + step - 1 : 0;
+            ko[o] = keys[at[o]];
+        }
+#pragma unroll
+        for (int o = 0; o < WAYS; o++) {
+            uint32_t vo = v;
+            if (ko[o] == k && !padding) vo = vals[at[o]];
+            const bool before = ko[o] < k || (ko[o] == k && (vo < v || (vo == v && o < own)));
+            cnt[o] += (before && cnt[o] + step <= len[o]) ? step : 0;
+        }
+    }
+    int at = i - own * run;
+#pragma unroll
+    for (int o = 0; o < WAYS; o++) at += cnt[o];
     keys_out[at] = k;
     vals_out[at] = v;
 }
@@ -878,31 +946,34 @@ hipError_t launch_sort_edges(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_
         hipError_t e = launch_radix_sort(keys_a, vals_a, keys_b, vals_b, n, nbits, low_bits, table, st);
         if (e != hipSuccess) return e;
     } else {
-        int cap = SORT_CHUNK, passes = 0;
-        if (n <= SORT_ONE) {
-            cap = 64;
-            while (cap < n) cap *= 2;
-        } else {
-            for (long long run = SORT_CHUNK; run < n; run *= 2) passes++;
-        }
+        int passes = 0;
+        const int chunk = n > (1 << 18) ? 2 * SORT_CHUNK : SORT_CHUNK;
+        if (n > SORT_ONE)
+            for (long long run = chunk; run < n; run *= 8) passes++;
         // the last pass writes to keys_a
         uint64_t *ki = keys_a, *ko = passes & 1 ? keys_b : keys_a;
         uint32_t *vi = vals_a, *vo = passes & 1 ? vals_b : vals_a;
-        const size_t sh = (size_t)cap * 12;
-        if (sh > 48 * 1024) {
-            hipError_t e = hipFuncSetAttribute((const void*)sort_chunk_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-            if (e != hipSuccess) return e;
-        }
         const bool list = passes == 0 && heads;
-        hipLaunchKernelGGL(sort_chunk_kernel, dim3((unsigned)((n + cap - 1) / cap)), dim3(1024), sh, st, ki, vi, ko, vo, n, cap,
-                           list ? heads : nullptr, list ? counters : nullptr);
-        if (list) return hipGetLastError();
-        for (long long run = SORT_CHUNK; passes > 0; passes--, run *= 2) {
+        uint32_t *lh = list ? heads : nullptr, *lc = list ? counters : nullptr;
+        hipError_t ec;
+        if (passes > 0 ? chunk == SORT_CHUNK : n > 1024 && n <= 2048) ec = launch_sort_chunk<512, SORT_CHUNK / 512>(ki, vi, ko, vo, n, lh, lc, st);
+        else if (n <= 64) ec = launch_sort_chunk<64, 1>(ki, vi, ko, vo, n, lh, lc, st);
+        else if (n <= 256) ec = launch_sort_chunk<64, 4>(ki, vi, ko, vo, n, lh, lc, st);
+        else if (n <= 1024) ec = launch_sort_chunk<256, 4>(ki, vi, ko, vo, n, lh, lc, st);
+        else ec = launch_sort_chunk<1024, 4>(ki, vi, ko, vo, n, lh, lc, st);
+        if (ec != hipSuccess || list) return ec;
+        for (long long run = chunk; passes > 0; passes--, run *= 8) {
             ki = ko;
             vi = vo;
             ko = ki == keys_a ? keys_b : keys_a;
             vo = vi == vals_a ? vals_b : vals_a;
-            hipLaunchKernelGGL(merge_runs_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, ki, vi, ko, vo, n, run);
+            const dim3 grid((unsigned)((n + 255) / 256));
+            if (n <= 2 * run)
+                hipLaunchKernelGGL(merge_runs_kernel<2>, grid, dim3(256), 0, st, ki, vi, ko, vo, (int)n, (int)run);
+            else if (n <= 4 * run)
+                hipLaunchKernelGGL(merge_runs_kernel<4>, grid, dim3(256), 0, st, ki, vi, ko, vo, (int)n, (int)run);
+            else
+                hipLaunchKernelGGL(merge_runs_kernel<8>, grid, dim3(256), 0, st, ki, vi, ko, vo, (int)n, (int)run);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

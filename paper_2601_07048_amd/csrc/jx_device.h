@@ -49,6 +49,16 @@ __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
 
+// The value of lane ^ M
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor_u32(uint32_t v) {
+    if (M == 1) return dpp_u32<0xB1>(v);
+    if (M == 2) return dpp_u32<0x4E>(v);
+    if (M == 8) return dpp_u32<0x128>(v);  // row_ror:8
+    if (M == 32) return shfl_xor(v, 32);
+    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, ((M & 31) << 10) | 0x1F);
+}
+
 // Every lane's value moves one lane up; lane 0 receives `in` (DPP 0x138 = wave_shr:1)
 __device__ __forceinline__ uint64_t wave_shift_up(uint64_t v, uint64_t in) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)in, (int)(uint32_t)v, 0x138, 0xF, 0xF, false);

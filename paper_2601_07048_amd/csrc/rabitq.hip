@@ -382,16 +382,6 @@ __device__ __forceinline__ double block_scan_incl(double v, double* ws, int tid)
     return v + off;
 }
 
-template <int M>
-__device__ __forceinline__ float lane_xor(float v) {
-    const uint32_t u = __float_as_uint(v);
-    if (M == 1) return __uint_as_float(dpp_u32<0xB1>(u));
-    if (M == 2) return __uint_as_float(dpp_u32<0x4E>(u));
-    if (M == 8) return __uint_as_float(dpp_u32<0x128>(u));  // row_ror:8
-    if (M == 32) return shfl_xor(v, 32);
-    return __uint_as_float((uint32_t)__builtin_amdgcn_ds_swizzle((int)u, (M << 10) | 0x1F));
-}
-
 // one stage of the network below: entry i = tid V + r against entry i ^ J, descending where i & K is 0
 template <int V, int K, int J>
 __device__ __forceinline__ void sort_stage(float (&v)[V], float* sa, const int tid) {
@@ -409,7 +399,7 @@ __device__ __forceinline__ void sort_stage(float (&v)[V], float* sa, const int t
         float o[V];
         if constexpr (J / V < 64) {
 #pragma unroll
-            for (int r = 0; r < V; r++) o[r] = lane_xor<J / V>(v[r]);
+            for (int r = 0; r < V; r++) o[r] = __uint_as_float(lane_xor_u32<J / V>(__float_as_uint(v[r])));
         } else {  // another wavefront's
 #pragma unroll
             for (int r = 0; r < V; r++) sa[r * 256 + tid] = v[r];

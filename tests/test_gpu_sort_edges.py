@@ -32,6 +32,15 @@ def test_insert_batches_equal_the_oracle(jx, n0, batch, R):
     assert np.array_equal(u32(g.export_graph()[0]), full.graph()[0])
 
 
+# the widths of the one-workgroup network (64, 256, 1,024, 2,048, 4,096 edges), then chunks of 2,048 and a merge of two, of eight,
+# a second pass of eight, a third, and chunks of 4,096: each size exactly, and one point more
+@pytest.mark.parametrize("n0,batch,R", [(300, 4, 16), (300, 5, 16), (300, 16, 16), (300, 17, 16), (300, 64, 16), (300, 65, 16), (1100, 128, 16),
+                                        (1100, 129, 16), (1100, 256, 16), (1100, 257, 16), (4200, 1024, 16), (4200, 1025, 16), (8300, 2048, 64),
+                                        (8300, 2049, 64), (16_400, 4096, 64), (16_400, 4097, 64)])
+def test_widths_of_the_sorts_equal_the_oracle(jx, n0, batch, R):
+    test_insert_batches_equal_the_oracle(jx, n0, batch, R)
+
+
 @pytest.mark.parametrize("drop", [3, 40, 700])
 def test_consolidation_equals_the_oracle(jx, drop):
     n, R = 4000, 24
