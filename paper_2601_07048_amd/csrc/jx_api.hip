@@ -699,7 +699,6 @@ static int run_subbatch(jx_index* idx, const InsertWork& w, int64_t pos0, int64_
     a.vals = (uint32_t*)(W + w.vals0);
     a.heads = (const uint32_t*)(W + w.heads);
     a.nseg = (const uint32_t*)(W + w.counters);
-    a.lists = (uint64_t*)(W + w.keys1);  // free once the edges are sorted
     a.vec_cache_bytes = 0;
     a.gram = gram_mode(idx);
     JX_HIP(jx::launch_forward_prune(p.dtype, a, st));
@@ -707,9 +706,13 @@ static int run_subbatch(jx_index* idx, const InsertWork& w, int64_t pos0, int64_
     int tbits = 1;
     while (((int64_t)1 << tbits) <= n_after) tbits++;
     const int64_t E = B * p.R;
+    bool other = false;  // the sorted edges are in the second pair of buffers
     JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys0), (uint32_t*)(W + w.vals0), (uint64_t*)(W + w.keys1),
                                  (uint32_t*)(W + w.vals1), E, 32 + tbits, 32, (uint32_t*)(W + w.table), (uint32_t*)(W + w.heads),
-                                 (uint32_t*)(W + w.counters), st));
+                                 (uint32_t*)(W + w.counters), &other, st));
+    a.keys = (uint64_t*)(W + (other ? w.keys1 : w.keys0));
+    a.vals = (uint32_t*)(W + (other ? w.vals1 : w.vals0));
+    a.lists = (uint64_t*)(W + (other ? w.keys0 : w.keys1));  // the one that is free now
     // 4. per target: append or robustPrune
     // LDS room per wavefront for the vectors of a full row plus up to 32 new edges (96 x 128 bytes);
     // larger merges take the path that reads from global memory
@@ -1009,12 +1012,12 @@ int jx_consolidate(jx_index* idx, void* stream) {
                 JX_HIP(jx::launch_consol_emit(c, st));
                 // (v, candidate) order brings repeated candidates together
                 JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys0), (uint32_t*)(W + w.vals0), (uint64_t*)(W + w.keys1),
-                                             (uint32_t*)(W + w.vals1), E, 32 + tbits, tbits, (uint32_t*)(W + w.table), nullptr, nullptr, st));
+                                             (uint32_t*)(W + w.vals1), E, 32 + tbits, tbits, (uint32_t*)(W + w.table), nullptr, nullptr, nullptr, st));
                 JX_HIP(jx::launch_consol_dist(p.dtype, c, (uint64_t*)(W + w.keys1), (uint32_t*)(W + w.vals1), st));
                 // (v, distance) order; the sort is stable, so equal distances stay in id order
                 JX_HIP(jx::launch_sort_edges((uint64_t*)(W + w.keys1), (uint32_t*)(W + w.vals1), (uint64_t*)(W + w.keys0),
                                              (uint32_t*)(W + w.vals0), E, 32 + tbits, 32, (uint32_t*)(W + w.table), (uint32_t*)(W + w.heads),
-                                             (uint32_t*)(W + w.counters), st));
+                                             (uint32_t*)(W + w.counters), nullptr, st));
             }
             a.E = E;
             a.B = (E + p.R - 1) / p.R;

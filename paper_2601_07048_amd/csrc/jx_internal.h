@@ -100,11 +100,12 @@ hipError_t launch_forward_prune_u8(const InsertArgs& a, hipStream_t st);  // pru
 hipError_t launch_reverse_merge_u8(const InsertArgs& a, hipStream_t st);
 hipError_t launch_forward_prune_gram(int dtype, const InsertArgs& a, hipStream_t st);
 hipError_t launch_reverse_merge_gram(int dtype, const InsertArgs& a, hipStream_t st);
-// Sorts n (key, value) pairs by key, then value (equal keys come in ascending order of their values) into keys_a / vals_a;
+// Sorts n (key, value) pairs by key, then value (equal keys come in ascending order of their values) into keys_a / vals_a,
+// or keys_b / vals_b where *in_b says so afterwards (NULL: never);
 // heads (may be NULL) receives the starts of the segments of equal key >> 32, counters[0] their number (counters[1..15]
 // are cleared).  Keys are below 2^nbits or empty; the low word of each is below 2^low_bits (32: anything, empty keys too)
 hipError_t launch_sort_edges(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b, long long n, int nbits,
-                             int low_bits, uint32_t* table, uint32_t* heads, uint32_t* counters, hipStream_t st);
+                             int low_bits, uint32_t* table, uint32_t* heads, uint32_t* counters, bool* in_b, hipStream_t st);
 hipError_t launch_argmin(const double* dist, long long n, uint32_t* out_id, hipStream_t st);
 hipError_t launch_segment_heads(const uint64_t* keys, long long n, uint32_t* heads, uint32_t* nseg, hipStream_t st);
 

@@ -17,7 +17,7 @@ def jx():
 
 
 # edges of the last internal batch = points x R: one workgroup (full and not), one merge, several, runs that end
-# early; 2^20 edges exactly (merge passes) and just more (radix sort, six passes, and seven and an idle one where ids have 17 bits)
+# early; 2^20 edges exactly (merge passes) and just more (radix sort, six passes, and seven where ids have 17 bits)
 @pytest.mark.parametrize("n0,batch,R", [(1500, 1, 16), (1500, 33, 31), (2100, 512, 16), (2100, 513, 16), (3000, 700, 24), (6000, 1400, 48),
                                         (16_400, 4096, 256), (16_400, 4097, 256), (66_000, 4097, 256)])
 def test_insert_batches_equal_the_oracle(jx, n0, batch, R):
