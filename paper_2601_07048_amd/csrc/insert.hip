@@ -912,7 +912,7 @@ hipError_t launch_reverse_merge(int dtype, const InsertArgs& a, hipStream_t st) 
 }
 
 // Sorts n (key, value) pairs on key bits [0, nbits), stable.  The result is in keys_a / vals_a again, or where in_b is
-// given, after an odd number of passes, in keys_b / vals_b (insertions into 2^17 to 2^24 points have seven: an eighth that
+// given, after an odd number of passes, in keys_b / vals_b (insertions into 2^16 to 2^24 points have seven: an eighth that
 // moved nothing cost a build of 200,000 points 0.2 of 22.4 ms).
 static hipError_t launch_radix_sort(uint64_t* keys_a, uint32_t* vals_a, uint64_t* keys_b, uint32_t* vals_b, long long n, int nbits,
                                     int low_bits, uint32_t* table, bool* in_b, hipStream_t st) {
