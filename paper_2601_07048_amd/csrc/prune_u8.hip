@@ -256,14 +256,17 @@ __global__ void __launch_bounds__(64) forward_prune_u8_kernel(InsertArgs a) {
 // ---- reverse-edge merge (Alg. 4 step 3) and consolidation: the listed segments, a wavefront each.  Beyond MAXC candidates
 // the pool is the row and the closest new edges (they arrive sorted by distance): what happens to a candidate depends on
 // earlier ones only, so the result is exact if the R-th selection comes no later than the last new edge of the pool.
-// MAXC = 512 takes both lists, MAXC = 2,048 what it has left of the second (hubs: the entry point, vertices near it), and
-// the list-based kernel the rest.
+// lists: bit 0 / 1 = the first / second.  MAXC = 512 takes both, or the second alone, MAXC = 2,048 what it has left of the second
+// (hubs: the entry point, vertices near it), and the list-based kernel the rest.  MAXC = 128 takes the first, of at most 128
+// candidates, where a batch has PIVOT_MANY edges: 7 KB of LDS let 16 wavefronts into a CU for 12, below that the launch costs
+// more than it gives (5 us).  100,000 points into 8 M 26.4 -> 23.5 ms.
+#define PIVOT_MANY (1 << 20)
 template <int S, int MAXC>
-__global__ void __launch_bounds__(64, S == 1 && MAXC == 512 ? 4 : 1) reverse_merge_u8_kernel(InsertArgs a) {
+__global__ void __launch_bounds__(64, S == 1 && MAXC <= 512 ? 4 : 1) reverse_merge_u8_kernel(InsertArgs a, int lists) {
     __shared__ PivotLds<MAXC> lds;
     PivotLds<MAXC>* L = &lds;
     const int lane = lane_id(), col = lane & 31, half = lane >> 5;
-    const uint32_t n1 = MAXC == 512 ? a.nseg[1] : 0, n = n1 + a.nseg[2];
+    const uint32_t n1 = lists & 1 ? a.nseg[1] : 0, n = n1 + (lists & 2 ? a.nseg[2] : 0);
     const long long total = a.E ? a.E : a.B * a.R;
     for (uint32_t at = blockIdx.x; at < n; at += gridDim.x) {
         const uint64_t entry = a.lists[at < n1 ? (long long)at : total - 1 - (at - n1)];
@@ -368,16 +371,20 @@ hipError_t launch_forward_prune_u8(const InsertArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_reverse_merge_u8(const InsertArgs& a, hipStream_t st) {
-    hipError_t e = launch_reverse_class(a, 512, JX_MAX_R, st);
-    if (e != hipSuccess) return e;
     const long long most = a.E ? a.E : a.B * a.R;  // segments there can be; persistent wavefronts
+    const bool many = most >= PIVOT_MANY;
+    const int rest = many ? 2 : 3;
+    hipError_t e = launch_reverse_class(a, many ? 128 : 512, JX_MAX_R, st);
+    if (e != hipSuccess) return e;
     const dim3 block(64), grid((unsigned)(most < 8192 ? most : 8192)), few((unsigned)(most < 1024 ? most : 1024));
     if (a.ds.nch <= 8) {
-        hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 512>), grid, block, 0, st, a);
-        hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 2048>), few, block, 0, st, a);
+        if (many) hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 128>), grid, block, 0, st, a, 1);
+        hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 512>), grid, block, 0, st, a, rest);
+        hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 2048>), few, block, 0, st, a, 2);
     } else {
-        hipLaunchKernelGGL((reverse_merge_u8_kernel<2, 512>), grid, block, 0, st, a);
-        hipLaunchKernelGGL((reverse_merge_u8_kernel<2, 2048>), few, block, 0, st, a);
+        if (many) hipLaunchKernelGGL((reverse_merge_u8_kernel<2, 128>), grid, block, 0, st, a, 1);
+        hipLaunchKernelGGL((reverse_merge_u8_kernel<2, 512>), grid, block, 0, st, a, rest);
+        hipLaunchKernelGGL((reverse_merge_u8_kernel<2, 2048>), few, block, 0, st, a, 2);
     }
     return hipGetLastError();
 }

@@ -130,3 +130,15 @@ def test_hub_u8(jx, copies):
     for lo in range(1, n, 2700):  # the first of these batches is as large as max_batch lets it be
         ref.insert(x[lo:lo + 2700]); g.insert(dev(x[lo:lo + 2700]))
         assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), lo
+
+
+def test_many_edges_u8(jx):
+    """A batch of more than 2^20 edges into full rows: merges of at most 128 candidates in a form of their own."""
+    n0, batch, R = 263_000, 65_700, 16
+    x = random_data(n0 + batch, 32, np.uint8, seed=9)
+    gs = [jx.Index(32, jx.U8, R, 24, 1.2, capacity=n0 + batch, max_batch=70_000, flags=f) for f in (0, jx.FLAG_NO_GRAM)]
+    for g in gs:
+        g.insert(dev(x[:n0]))
+        g.insert(dev(x[n0:]))
+    a, b = (u32(g.export_graph()[0]) for g in gs)
+    assert np.array_equal(a, b)
