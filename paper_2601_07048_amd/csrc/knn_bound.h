@@ -25,11 +25,15 @@ JX_HD float knn_threshold(float lim, float qq) { return (lim - qq) + (lim + qq) 
 // by the triangle inequality, the rounding of e included by the last factor.  Holds up to KNN_FLOAT_D dimensions
 #define KNN_FLOAT_D 65536
 // parts: what the values of the norm form lack, as a share of (|q| + |b|)^2.  float32 values go to the matrix cores as two
-// bfloat16 parts, x = h + l + r with |l| <= 2^-9 |x| and |r| <= 2^-18 |x|, and h h' + h l' + l h' leaves out l l', h r' and r h':
-// at most 3.02 2^-18 |q| |b|, twice that in 2 <q, b>, and |q| |b| is at most a quarter of (|q| + |b|)^2.  An instruction takes
-// 16 coordinates and is off by at most 8 2^-24 of its largest term, subnormals are kept (measured): 3 d / 16 of them in a row
-// by 1.5 d 2^-24 |q| |b|, which the first bound covers
-#define KNN_BF16_PARTS 6e-6f
+// bfloat16 parts, x = h + l + r.  A bfloat16 has 8 significant bits, so rounding to nearest leaves |l| <= 2^-8 |x| and
+// |r| <= 2^-17 |x|, and h h' + h l' + l h' leaves out l l', h r' and r h': at most 2^-15 (1 + 2^-9) |q| |b|, twice that in
+// 2 <q, b>, and |q| |b| is at most a quarter of (|q| + |b|)^2: 2^-16 (1 + 2^-9) = 1.53e-5.  A duplicate of a query of
+// coordinates 1.0039 comes within 2 % of it.  Where 8 bits leave only 2^-9 and 2^-18 (6e-6, the value here before) the bound
+// holds from about 64 dimensions on, by what the first term has to spare.
+// An instruction takes 16 coordinates and is off by at most 8 2^-24 of its largest term, subnormals are kept (both measured):
+// 3 ceil(d / 16) of them in a row by 24 ceil(d / 16) 2^-24 |q| |b|, in 2 <q, b> at most (0.75 d + 12) 2^-24 (|q| + |b|)^2.  With
+// the norms (d / 8 + 7), the sum (4) and the form of the result (d + 2) that is 1.9 d + 25; the first term has 2 d + 32
+#define KNN_BF16_PARTS 1.6e-5f
 JX_HD float knn_eps(int d, float qq, float e, float bb_max, float parts = 0.f) {
     const float c = (float)(d + 16) * 1.2e-7f + parts;
     float len = (2.f * sqrtf(qq) + sqrtf(e)) * (1.f + sqrtf(c));

@@ -1,6 +1,7 @@
 """The exhaustive search on the matrix cores at the ends of what it takes: rows so long that uint8 distances leave its
 integer range, floats so small that squares are subnormal, rows that no threshold can decide on, sets far from the
 origin.  Every result is compared with the tiled kernel's, which rows on 4-byte boundaries take."""
+import numpy as np
 import pytest
 import torch
 
@@ -138,3 +139,53 @@ def test_few_neighbours_of_short_vectors(jx, dtype, d, nq, k, fewest):
     check(jx, x, q, k)
     jx.bruteforce_static(x[:fewest - 1], q, k)
     assert jx.bruteforce_kernel().startswith("bruteforce_tile_kernel<")
+
+
+@pytest.mark.parametrize("d,k", [(4, 1), (8, 1), (16, 1), (16, 10), (32, 1), (48, 1), (64, 1)])
+def test_significands_that_two_parts_hold_worst(jx, d, k):
+    """Coordinates of 1.0039139 (0x3F808040): both roundings to bfloat16 leave the most they can, and the norm form of a duplicate of
+    such a query is 2^-14 |q|^2 too far.  Vectors that differ from it in two coordinates, which hold on their own, come before it in
+    that form, more of them than the lists keep; the duplicates have to be found all the same."""
+    worst = float(np.array([0x3F808040], np.uint32).view(np.float32)[0])
+    g = torch.Generator(device="cuda").manual_seed(12)
+    b = torch.randn((20_000, d), device="cuda", generator=g) * 3
+    q = torch.full((8, d), worst, device="cuda")
+    near = torch.randperm(20_000, device="cuda", generator=g)[:120]
+    b[near] = worst
+    i = torch.arange(120, device="cuda")
+    b[near[:100], (i % d)[:100]] = 1.0078125
+    b[near[:100], ((i + 1 + i // d) % d)[:100]] = 1.0
+    ids, dist = check(jx, b, q, k)
+    assert not dist.any()
+    assert ids[0].tolist() == sorted(near[100:].tolist())[:k]
+
+
+def test_one_matrix_instruction(jx):
+    """What knn_bound.h takes for granted of v_mfma_f32_32x32x16_bf16: off by at most 8 2^-24 of its largest term (of 16 products
+    and the sum before them), subnormal values kept.  The rotation of bfloat16 values by a matrix of bfloat16 values that is zero
+    outside sixteen columns is one such instruction; its sum before them is zero, or, with a second half, of the same order."""
+    d, n, f = 32, 512, np.float64
+    rng = np.random.default_rng(13)
+
+    def bf16(x):
+        return torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16).float()
+
+    index_ = jx.Index(d, jx.F32, 8, 8, 1.2, capacity=64, max_batch=1024, quant_bits=1)
+    index_.import_graph(torch.ones((64, d), device="cuda"), torch.full((64, 8), -1, dtype=torch.int32, device="cuda"), 0)
+    for spread, scale in ((0, 1.0), (4, 1.0), (12, 1.0), (30, 1.0), (4, 1e-37), (2, 1e-39)):
+        for columns in (16, 32):
+            x = bf16(rng.standard_normal((n, d)) * 2.0 ** rng.uniform(-spread, 0, (n, d)) * scale)
+            p = bf16(rng.standard_normal((d, d)) * 2.0 ** rng.uniform(-spread, 0, (d, d)))
+            x[:, columns:] = 0
+            x[::7, 1] = -x[::7, 0]  # cancellation of the two largest
+            p[::5, 1] = p[::5, 0]
+            index_.quantize(1, p.cuda(), torch.zeros(d, device="cuda"), query_bits=4)
+            got = index_.rotate(x.cuda()).cpu().numpy().astype(f)
+            products = x.numpy().astype(f)[:, None, :] * p.numpy().astype(f)[None, :, :]
+            first, both = products[:, :, :16], products[:, :, :columns]
+            bound = 8 * 2.0 ** -24 * np.abs(first).max(2)
+            if columns == 32:
+                bound += 8 * 2.0 ** -24 * np.maximum(np.abs(first.sum(2)) + bound, np.abs(products[:, :, 16:]).max(2))
+            off = np.abs(got - both.sum(2))
+            print(spread, scale, columns, (off / np.maximum(bound, 1e-300)).max())
+            assert (off <= bound + 2.0 ** -149).all()

@@ -125,3 +125,50 @@ def test_bound_covers_the_parts(lib, d, offset, scale):
     assert scale > 1 or np.isfinite(eps).all()
     for x in (x64, x32.astype(np.float64)):  # as above: no proof where norms of that length could overflow
         assert (~(eps < np.inf) | (np.abs(qq + bb - 2 * x - e) <= eps)).all()
+
+
+def _parts(x):
+    """Two bfloat16 parts of float32 values and what they leave, in 64 bits."""
+    h = _bf16(x)
+    l = _bf16(x - h)
+    return h.astype(np.float64), l.astype(np.float64), x.astype(np.float64) - h - l
+
+
+def test_what_two_parts_leave_of_any_value():
+    """All significands: roundings to 8 bits leave up to 2^-8 and 2^-17 of a value, and the three products that are taken of a
+    value's own square lack up to 2^-15 of it."""
+    x = (np.arange(1 << 23, dtype=np.uint32) | 0x3F800000).view(np.float32)
+    h, l, r = _parts(x)
+    assert (np.abs(l) <= 2.0 ** -8 * x).all() and np.abs(l / x).max() > 0.99 * 2.0 ** -8
+    assert (np.abs(r) <= 2.0 ** -17 * x).all() and np.abs(r / x).max() > 0.99 * 2.0 ** -17
+    lacks = (l * l + 2 * h * r) / x.astype(np.float64) ** 2
+    assert 0.98 * 2.0 ** -15 < np.abs(lacks).max() <= 2.0 ** -15 * (1 + 2.0 ** -7)
+
+
+# significands whose parts lack most, of either sign: 1.0039139 (the search above finds it) and neighbours in other binades
+WORST = np.array([0x3F808040], np.uint32).view(np.float32)[0]
+
+
+@pytest.mark.parametrize("d", [4, 8, 16, 20, 32, 48, 52, 64, 128, 960])
+@pytest.mark.parametrize("scale", [2.0 ** -40, 1.0, 2.0 ** 40])
+def test_bound_covers_the_worst_significands(lib, d, scale):
+    """A duplicate of a query whose every coordinate lacks the most there is: nothing cancels.  With every rounding of the norm
+    form against it as well: each matrix instruction off by 8 2^-24 of its largest term (16 products and the sum before them),
+    three of them per 16 coordinates, and the sums behind by half a unit in the last place each."""
+    u = 2.0 ** -24
+    x = np.full(d, WORST * np.float32(scale), np.float32)
+    h, l, r = _parts(x)
+    total = 0.0
+    for j in range(0, d, 16):
+        for products in (l * h, h * l, h * h):
+            group = products[j:j + 16]
+            largest = max(total, group.max())
+            total = total + group.sum() - 8 * u * largest
+    norm = (x.astype(np.float64) ** 2).sum()
+    longest_chain = 4 * ((d + 31) // 32) + 3  # squares of a norm that one thread adds, and the eight threads of a row
+    apart = 2 * norm * (1 + longest_chain * u) * (1 + u) - 2 * total + 2 * u * norm
+    eps = np.empty(1, np.float32)
+    for e in (0.0, norm * 1e-3):
+        lib.bounds_parts(C.c_int(d), _ptr(np.array([norm], np.float32)), _ptr(np.array([e], np.float32)), _ptr(np.array([norm], np.float32)),
+                         _ptr(eps), C.c_long(1))
+        assert apart <= eps[0], (apart, eps[0])
