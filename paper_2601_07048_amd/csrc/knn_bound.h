@@ -1,7 +1,8 @@
-// Rounding rules of the exhaustive search on the matrix cores (knn_tile.hip): plain float arithmetic, so that the test of
-// these rules can compile them for the CPU.
+// Rounding rules of the exhaustive search on the matrix cores (knn_tile.hip), and how it counts: plain arithmetic, so that the
+// test of these rules can compile them for the CPU.
 #pragma once
 #include <math.h>
+#include <stdint.h>
 
 #ifdef __HIPCC__
 #define JX_HD __host__ __device__ __forceinline__
@@ -10,6 +11,20 @@
 #endif
 
 namespace jx {
+
+#define KT 128  // queries per workgroup, base vectors per step
+
+// What counts base vectors in 32 bits: a set has up to 2^31 - 2 of them, and the step behind the last one begins up to KT - 1
+// further on
+typedef uint32_t knn_row;
+// slice `split` of nsplit; every slice has as many steps, or one more
+JX_HD void knn_slice(long long n, int nsplit, int split, knn_row* begin, knn_row* end) {
+    const long long steps = (n + KT - 1) / KT, after = (split + 1) * steps / nsplit * KT;
+    *begin = (knn_row)(split * steps / nsplit * KT);
+    *end = (knn_row)(after > n ? n : after);
+}
+JX_HD bool knn_whole_step(knn_row b0, knn_row end) { return b0 + KT <= end; }
+JX_HD bool knn_last_step(knn_row b0, knn_row end) { return b0 + KT >= end; }
 
 // What 2 <q, b> is compared with |b|^2 behind, so that every vector whose distance, by either formula of the kernel, is
 // below lim passes 2 <q, b> + threshold > |b|^2.  A first threshold counts vectors by |q|^2 - (2 <q, b> - |b|^2) and they

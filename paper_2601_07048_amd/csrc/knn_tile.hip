@@ -38,7 +38,6 @@ typedef __bf16 kbf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 kbf16x2 __attribute__((ext_vector_type(2)));
 typedef float kf32x2 __attribute__((ext_vector_type(2)));
 
-#define KT 128        // queries per workgroup, base vectors per step
 #define KROW 144      // bytes of a staged row: 128 and 16 of padding
 #define KCAP 32       // buffer entries per query
 #define KFLUSH 28     // a buffer with this many entries is merged: with 16, 24, 28 1,000 x 300,000 uint8 d = 96, k = 100 1,153, 966, 852 us
@@ -705,11 +704,11 @@ __global__ void __launch_bounds__(256, 2) knn_u8_kernel(KnnArgs a) {
     const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
     const long long q0 = (long long)blockIdx.x * KT;
     const int split = blockIdx.y;
-    const long long steps = (a.n + KT - 1) / KT;
-    const int b_begin = __builtin_amdgcn_readfirstlane((int)(split * steps / a.nsplit) * KT);
-    const long long after = (split + 1) * steps / a.nsplit * KT;
-    int b_end = __builtin_amdgcn_readfirstlane((int)(after > a.n ? a.n : after));
-    if (SEED && b_end - b_begin > a.seed_steps * KT) b_end = b_begin + a.seed_steps * KT;
+    knn_row b_begin, b_end;
+    knn_slice(a.n, a.nsplit, split, &b_begin, &b_end);
+    b_begin = (knn_row)__builtin_amdgcn_readfirstlane((int)b_begin);
+    b_end = (knn_row)__builtin_amdgcn_readfirstlane((int)b_end);
+    if (SEED && b_end - b_begin > (knn_row)a.seed_steps * KT) b_end = b_begin + (knn_row)a.seed_steps * KT;
     const uint8_t* Q = reinterpret_cast<const uint8_t*>(a.queries);
     const uint8_t* B = reinterpret_cast<const uint8_t*>(a.base);
     const int srow = tid >> 3, sch = tid & 7;  // staging: 8 threads per row, rows srow + 32 t
@@ -767,14 +766,14 @@ __global__ void __launch_bounds__(256, 2) knn_u8_kernel(KnnArgs a) {
 #pragma unroll
     for (int e = 0; e < (SEED ? 64 : 1); e++) best[e] = -0x7FFFFFFF;
     uint4 pb[4];
-    auto fetch = [&](const int b0) __attribute__((always_inline)) {
-        if (b0 + KT <= b_end && whole) {  // uniform
+    auto fetch = [&](const knn_row b0) __attribute__((always_inline)) {
+        if (knn_whole_step(b0, b_end) && whole) {  // uniform
 #pragma unroll
             for (int t = 0; t < 4; t++) pb[t] = load16(B + (size_t)(b0 + srow + 32 * t) * 128 + sch * 16);
         } else {
 #pragma unroll
             for (int t = 0; t < 4; t++) {
-                const int row = b0 + srow + 32 * t;
+                const knn_row row = b0 + srow + 32 * t;
                 pb[t] = load16(B + (size_t)(row < b_end ? row : b_end - 1) * row_bytes + (size_t)((sch < a.nch ? sch : 0) * 16));
             }
         }
@@ -784,7 +783,7 @@ __global__ void __launch_bounds__(256, 2) knn_u8_kernel(KnnArgs a) {
     uint64_t stored = 0;
     // Appends what of a step passes; a full buffer leaves the element for the next round (later rounds: limits may have come
     // down to a distance that an element stored in the meantime has, and equal ones stay in)
-    auto append = [&](const int b0, const int cur, const int slot, const bool again) __attribute__((always_inline)) {
+    auto append = [&](const knn_row b0, const int cur, const int slot, const bool again) __attribute__((always_inline)) {
         int nbv[2];
 #pragma unroll
         for (int j = 0; j < 2; j++) nbv[j] = (int)S.bn[cur * KT + wn * 64 + j * 32 + col];
@@ -805,10 +804,10 @@ __global__ void __launch_bounds__(256, 2) knn_u8_kernel(KnnArgs a) {
 #pragma unroll
                     for (int j = 0; j < 2; j++) {
                         const int bit = ((i * 4 + h) * 4 + c) * 2 + j;
-                        const uint32_t id = (uint32_t)b0 + (uint32_t)(wn * 64 + j * 32 + col);
+                        const knn_row id = b0 + (knn_row)(wn * 64 + j * 32 + col);
                         const int x = acc[i][j][h * 4 + c] - start[i][h * 4 + c];
                         const int v = (x << 1) + tt[c];
-                        if ((again ? v >= nbv[j] : v > nbv[j]) && !((stored >> bit) & 1ull) && id < (uint32_t)b_end) {
+                        if ((again ? v >= nbv[j] : v > nbv[j]) && !((stored >> bit) & 1ull) && id < b_end) {
                             const uint32_t pos = atomicAdd(&S.cnt[r0 + c], 1u);
                             if (pos < KCAP) {
                                 S.buf[r0 + c][pos] = ((uint64_t)(uint32_t)((int)S.qn[r0 + c] + nbv[j] - 2 * x) << 32) | (uint64_t)id;
@@ -822,10 +821,10 @@ __global__ void __launch_bounds__(256, 2) knn_u8_kernel(KnnArgs a) {
             }
     };
     int cur = 0, slot = 0;  // staging buffer and flag of the step
-    for (int b0 = b_begin;; b0 += KT, cur ^= 1, slot = slot == 2 ? 0 : slot + 1) {
+    for (knn_row b0 = b_begin;; b0 += KT, cur ^= 1, slot = slot == 2 ? 0 : slot + 1) {
         uint4* stage = cur ? S.b : S.a;
         if (b0 < b_end) {
-            const bool full = b0 + KT <= b_end && whole;  // uniform
+            const bool full = knn_whole_step(b0, b_end) && whole;  // uniform
 #pragma unroll
             for (int t = 0; t < 4; t++) {
                 const int row = srow + 32 * t;
@@ -863,7 +862,7 @@ __global__ void __launch_bounds__(256, 2) knn_u8_kernel(KnnArgs a) {
         }
         if (b0 >= b_end) break;
         if (tid == 0) S.flag[slot == 2 ? 0 : slot + 1] = 0;  // the next step's: last read before the barrier above
-        if (b0 + KT < b_end) fetch(b0 + KT);
+        if (!knn_last_step(b0, b_end)) fetch(b0 + KT);
         if constexpr (SEED) {
 #pragma unroll
             for (int i = 0; i < 2; i++)

@@ -1,5 +1,6 @@
 """The rounding rules of the float form of the exhaustive search (knn_bound.h), compiled for the CPU: what its first
-thresholds count is admitted, and the two forms of a distance are no further apart than its bound says."""
+thresholds count is admitted, and the two forms of a distance are no further apart than its bound says.  Counting of base
+vectors and scratch as well."""
 import ctypes as C
 import os
 import subprocess
@@ -20,6 +21,22 @@ extern "C" void bounds_parts(int d, const float* qq, const float* e, const float
 extern "C" void bounds(int d, const float* qq, const float* e, const float* bb_max, float* out, long n) {
     for (long i = 0; i < n; i++) out[i] = jx::knn_eps(d, qq[i], e[i], bb_max[i]);
 }
+// the loop of knn_u8_kernel over a slice: steps, rows that are staged as if they were of the set, the row that is fetched last
+extern "C" void walk(long long n, int nsplit, int split, long long out[4]) {
+    jx::knn_row begin, end;
+    jx::knn_slice(n, nsplit, split, &begin, &end);
+    long long steps = 0, outside = 0, last = -1;
+    for (jx::knn_row b0 = begin;; b0 += KT) {
+        if (b0 >= end || steps > (1LL << 31) / KT) break;  // the second: it does not end by itself
+        steps++;
+        if (jx::knn_whole_step(b0, end)) outside += (long long)b0 + KT > n;
+        if (!jx::knn_last_step(b0, end)) last = (long long)b0 + KT;
+    }
+    out[0] = (long long)end - (long long)begin;
+    out[1] = steps;
+    out[2] = outside;
+    out[3] = last;
+}
 """
 
 
@@ -27,7 +44,7 @@ extern "C" void bounds(int d, const float* qq, const float* e, const float* bb_m
 def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("knn_bound")
     (d / "b.cpp").write_text(SOURCE)
-    subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-shared", "-fPIC", "-I", CSRC, str(d / "b.cpp"), "-o", str(d / "b.so")], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-fwrapv", "-ffp-contract=off", "-shared", "-fPIC", "-I", CSRC, str(d / "b.cpp"), "-o", str(d / "b.so")], check=True)
     return C.CDLL(str(d / "b.so"))
 
 
@@ -172,3 +189,16 @@ def test_bound_covers_the_worst_significands(lib, d, scale):
         lib.bounds_parts(C.c_int(d), _ptr(np.array([norm], np.float32)), _ptr(np.array([e], np.float32)), _ptr(np.array([norm], np.float32)),
                          _ptr(eps), C.c_long(1))
         assert apart <= eps[0], (apart, eps[0])
+
+
+@pytest.mark.parametrize("n", [6_000, 16_383, 1_000_000, 2 ** 31 - 257, 2 ** 31 - 129, 2 ** 31 - 128, 2 ** 31 - 127, 2 ** 31 - 100, 2 ** 31 - 2])
+@pytest.mark.parametrize("nsplit", [1, 2, 5])
+def test_steps_of_a_slice_end_with_the_set(lib, n, nsplit):
+    """Up to the largest set there can be: a step is whole only where the set has all its rows, nothing is fetched beyond it, and
+    the steps end."""
+    total, out = 0, (C.c_longlong * 4)()
+    for split in range(nsplit):
+        lib.walk(C.c_longlong(n), C.c_int(nsplit), C.c_int(split), out)
+        total += out[0]
+        assert out[1] == -(-out[0] // 128) and out[2] == 0 and out[3] < n
+    assert total == n
