@@ -26,6 +26,13 @@ JX_HD void knn_slice(long long n, int nsplit, int split, knn_row* begin, knn_row
 JX_HD bool knn_whole_step(knn_row b0, knn_row end) { return b0 + KT <= end; }
 JX_HD bool knn_last_step(knn_row b0, knn_row end) { return b0 + KT >= end; }
 
+#define KNN_PUB 8  // published distances of one slice and query, at most
+// Slices whose lists (kp keys of a query) and published distances have room in so many bytes; a single slice publishes nothing
+JX_HD long long knn_slices_that_fit(long long bytes, long long nq, int kp) {
+    const long long fit = bytes / (nq * (kp * 8 + KNN_PUB * 4));
+    return fit > 0 ? fit : (bytes >= nq * kp * 8 ? 1 : 0);
+}
+
 // What 2 <q, b> is compared with |b|^2 behind, so that every vector whose distance, by either formula of the kernel, is
 // below lim passes 2 <q, b> + threshold > |b|^2.  A first threshold counts vectors by |q|^2 - (2 <q, b> - |b|^2) and they
 // have to be admitted when the search meets them again.  With u = 2^-24: the two subtractions of the count are off by

@@ -48,8 +48,7 @@ typedef float kf32x2 __attribute__((ext_vector_type(2)));
 
 #define KNN_SLACK 28  // float types: candidates kept beyond k
 #define KNN_BLOCKS 512   // and so the largest number of slices
-#define KNN_ENTRIES 512  // published distances of a query, all slices
-#define KNN_PUB 8        // ... of one slice
+#define KNN_ENTRIES 512  // published distances of a query, all slices (KNN_PUB of one)
 #define KNN_ODD 30  // rows that are listed for the merge of a query tile, see KnnOdd
 
 // Rows of the base set that no threshold can decide on: float32 with a NaN, binary16 with a NaN or an infinity.  They are kept
@@ -1142,8 +1141,7 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     const long long redo_bytes = (b.nq * 4 + 255) & ~255LL;
     const long long odd_bytes = (qt * (long long)sizeof(KnnOdd) + 255) & ~255LL;
     const long long aux = redo_bytes + odd_bytes + (qt > KNN_BLOCKS ? qt : KNN_BLOCKS) * 16 + 256;
-    long long fit = (scratch_bytes - aux) / (b.nq * (a.kp * 8 + KNN_PUB * 4));
-    if (fit < 1) fit = (scratch_bytes - aux) / (b.nq * (a.kp * 8));  // a single slice publishes nothing
+    const long long fit = knn_slices_that_fit(scratch_bytes - aux, b.nq, a.kp);
     if (nsplit > fit) nsplit = fit;
     // Where the tiled kernel stays, tiled / this in us: few vectors (1,000 x 2,000 float32 d = 96, k = 10 181 / 210, 300 x
     // 8,000, k = 1 125 / 155; uint8 300 x 8,000 108 / 111, k = 10 213 / 112); hardly any workgroups; and one neighbour or

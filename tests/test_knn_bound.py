@@ -21,6 +21,8 @@ extern "C" void bounds_parts(int d, const float* qq, const float* e, const float
 extern "C" void bounds(int d, const float* qq, const float* e, const float* bb_max, float* out, long n) {
     for (long i = 0; i < n; i++) out[i] = jx::knn_eps(d, qq[i], e[i], bb_max[i]);
 }
+extern "C" long long fits(long long bytes, long long nq, int kp) { return jx::knn_slices_that_fit(bytes, nq, kp); }
+extern "C" int published_bytes() { return KNN_PUB * 4; }
 // the loop of knn_u8_kernel over a slice: steps, rows that are staged as if they were of the set, the row that is fetched last
 extern "C" void walk(long long n, int nsplit, int split, long long out[4]) {
     jx::knn_row begin, end;
@@ -202,3 +204,17 @@ def test_steps_of_a_slice_end_with_the_set(lib, n, nsplit):
         total += out[0]
         assert out[1] == -(-out[0] // 128) and out[2] == 0 and out[3] < n
     assert total == n
+
+
+@pytest.mark.parametrize("kp", [1, 2, 3, 4, 10, 29, 128, 156])
+def test_lists_and_published_distances_fit_the_scratch(lib, kp):
+    """At every size around which a slice more or less fits, one-slice scratch (which publishes nothing) included."""
+    lib.fits.restype = C.c_longlong
+    for nq in (1, 7, 128, 16_384, 100_000):
+        for slices in (0, 1, 2, 3, 4, 5, 64):
+            for publish in (0, 1):
+                for off in (-1, 0, 1):
+                    size = nq * slices * (kp * 8 + publish * lib.published_bytes()) + off
+                    n = lib.fits(C.c_longlong(size), C.c_longlong(nq), C.c_int(kp))
+                    assert n >= (1 if size >= nq * kp * 8 else 0)
+                    assert n == 0 or nq * n * (kp * 8 + (lib.published_bytes() if n > 1 else 0)) <= size
