@@ -72,6 +72,7 @@ struct InsertArgs {
     int R, L;
     float alpha;
     long long B;           // points in this batch
+    long long first;       // forward prune: the launch begins at this point of the batch
     long long id_base;     // id of batch element i = id_base + i (+1 if >= id_skip)
     long long id_skip;
     const uint32_t* cand_ids;   // [B][L]

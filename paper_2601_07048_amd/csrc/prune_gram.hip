@@ -455,7 +455,7 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) forward_prune_gram_
     __shared__ TeamLds<DT, NB> lds;
     TeamLds<DT, NB>* L = &lds;
     const int tid = threadIdx.x, lane = lane_id();
-    const long long i = blockIdx.x;
+    const long long i = a.first + blockIdx.x;
     long long xid = a.id_base + i;
     if (xid >= a.id_skip) xid++;
     const uint32_t* ids = a.cand_ids + (size_t)i * a.L;
@@ -588,8 +588,12 @@ hipError_t launch_reverse_class(const InsertArgs& a, int small_max, int deg_max,
 
 template <int DT>
 static hipError_t launch_forward_gram_dt(const InsertArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 4>), dim3((unsigned)a.B), dim3(256), 0, st, a);
-    if (a.L > GT_SMALL) hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 8>), dim3((unsigned)a.B), dim3(512), 0, st, a);
+    constexpr long long MOST = 1 << 22;  // workgroups of a launch, which has fewer than 2^32 threads
+    for (InsertArgs s = a; s.first < a.B; s.first += MOST) {
+        const dim3 grid((unsigned)(a.B - s.first < MOST ? a.B - s.first : MOST));
+        hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 4>), grid, dim3(256), 0, st, s);
+        if (a.L > GT_SMALL) hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 8>), grid, dim3(512), 0, st, s);
+    }
     return hipGetLastError();
 }
 

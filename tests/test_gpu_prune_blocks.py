@@ -4,6 +4,7 @@ exact in float32 (and in the three bfloat16 parts of a value), so the adjacency 
 In rounds of 32 pivots (uint8): the same edges, rows of one and of two 128-byte pieces, and hubs."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2601_07048_amd import datagen
@@ -142,3 +143,19 @@ def test_many_edges_u8(jx):
         g.insert(dev(x[n0:]))
     a, b = (u32(g.export_graph()[0]) for g in gs)
     assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("L,logB", [(8, 24), (129, 23)])
+def test_batches_of_more_workgroups_than_one_launch_takes(jx, L, logB):
+    """A launch has fewer than 2^32 threads: 2^24 workgroups of 256 (lists of at most 128) and 2^23 of 512 (longer ones) are more.
+    Whole numbers below 1,024 in four dimensions are exact in every form, so the table is that of the list-based kernels."""
+    n = 2 << logB
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    x = torch.randint(0, 1024, (n, 4), device="cuda", generator=gen).float()
+    tables = []
+    for flags in (0, jx.FLAG_NO_GRAM):
+        g = jx.Index(4, jx.F32, 4, L, 1.2, capacity=n, max_batch=1 << logB, batch_growth=1.0, flags=flags)
+        g.insert(x)
+        tables.append(g.export_graph()[0])
+        g.close()
+    assert torch.equal(*tables)
