@@ -357,10 +357,17 @@ int jx_import_codes(jx_index* idx, int32_t bits, const float* d_rotation, const 
 /* Stage entry points of the RaBitQ pipeline (Sec. 5.1), used to test each
  * stage against injected inputs.
  *   jx_rotate: d_out[n][dim] = (d_in[n][dim] - c) P^T with the index's frozen
- *   P and c (the GEMM used for queries and for encoding).
+ *   P and c, as queries are rotated.
+ *   jx_rotate_points: the same for n vectors of the index's dtype, as jx_quantize
+ *   and jx_insert rotate what they encode.  For codes of 2, 4 and 8 bits that is
+ *   another kernel (float32 matrix instructions, jx_rotate: three bfloat16 parts
+ *   of each value): the two agree to 1e-6 of a vector's norm, and a few codes in
+ *   a million depend on which it was.
  *   jx_encode_rotated: encode n already-rotated vectors into unpadded codes
- *   and meta, with the index's bits and rule. */
+ *   and meta, with the index's bits and rule; of what jx_rotate_points returns it
+ *   makes the codes and floats of jx_quantize, bit for bit. */
 int jx_rotate(jx_index* idx, const float* d_in, int64_t n, float* d_out, void* stream);
+int jx_rotate_points(jx_index* idx, const void* d_in, int64_t n, float* d_out, void* stream);
 int jx_encode_rotated(jx_index* idx, const float* d_rot, int64_t n, uint8_t* d_codes, float* d_meta, void* stream);
 
 const char* jx_strerror(int code);

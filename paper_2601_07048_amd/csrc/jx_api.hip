@@ -775,6 +775,11 @@ int jx_insert(jx_index* idx, const void* d_vecs, int64_t n, void* stream) {
     return JX_OK;
 }
 
+// as vectors that are to be encoded are rotated: codes of more than one bit stay those of the float32 form (rabitq.hip)
+static hipError_t rotate_points(const jx_index* idx, const void* d_in, int64_t n, float* d_out, hipStream_t st) {
+    return jx::launch_rotate(d_in, idx->p.dtype, n, idx->p.dim, idx->d_P, idx->d_centroid, d_out, idx->quantized > 1, st);
+}
+
 // rotate + encode vectors [first, first+count) of the store into their records
 static int encode_range(jx_index* idx, int64_t first, int64_t count, hipStream_t st) {
     const jx_params& p = idx->p;
@@ -786,7 +791,7 @@ static int encode_range(jx_index* idx, int64_t first, int64_t count, hipStream_t
     for (int64_t s0 = 0; s0 < count; s0 += slice) {
         const int64_t m = count - s0 < slice ? count - s0 : slice;
         const uint8_t* src = idx->d_vecs + (size_t)(first + s0) * idx->vec_bytes;
-        JX_HIP(jx::launch_rotate(src, p.dtype, m, p.dim, idx->d_P, idx->d_centroid, rot, idx->quantized > 1, st));
+        JX_HIP(rotate_points(idx, src, m, rot, st));
         jx::EncodeArgs e;
         memset(&e, 0, sizeof e);
         e.rot = rot;
@@ -876,6 +881,16 @@ int jx_rotate(jx_index* idx, const float* d_in, int64_t n, float* d_out, void* s
     if (n == 0) return JX_OK;
     if (!d_in || !d_out) return fail(JX_EINVAL, "NULL argument");
     JX_HIP(jx::launch_rotate(d_in, JX_F32, n, idx->p.dim, idx->d_P, idx->d_centroid, d_out, false, as_stream(stream)));
+    return JX_OK;
+}
+
+int jx_rotate_points(jx_index* idx, const void* d_in, int64_t n, float* d_out, void* stream) {
+    if (!idx) return fail(JX_EINVAL, "index is NULL");
+    if (!idx->quantized) return fail(JX_ESTATE, "index is not quantised");
+    if (n < 0) return fail(JX_EINVAL, "n < 0");
+    if (n == 0) return JX_OK;
+    if (!d_in || !d_out) return fail(JX_EINVAL, "NULL argument");
+    JX_HIP(rotate_points(idx, d_in, n, d_out, as_stream(stream)));
     return JX_OK;
 }
 

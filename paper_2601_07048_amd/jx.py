@@ -31,7 +31,7 @@ MAX_L, MAX_R, MAX_BF_K = 512, 256, 128
 EXPORTS = [
     "jx_arena_bytes", "jx_create", "jx_destroy", "jx_insert", "jx_quantize", "jx_search", "jx_beam_frontier",
     "jx_bruteforce", "jx_size", "jx_export_graph", "jx_import_graph", "jx_export_codes", "jx_import_codes", "jx_rotate",
-    "jx_encode_rotated", "jx_delete", "jx_consolidate", "jx_compact", "jx_deleted_count", "jx_probe_gather", "jx_mips_augment", "jx_strerror", "jx_last_error",
+    "jx_rotate_points", "jx_encode_rotated", "jx_delete", "jx_consolidate", "jx_compact", "jx_deleted_count", "jx_probe_gather", "jx_mips_augment", "jx_strerror", "jx_last_error",
     "jx_bruteforce_static", "jx_bruteforce_kernel", "jx_set_flags",
 ]
 
@@ -192,6 +192,13 @@ class Index:
         out = torch.empty_like(x)
         with torch.cuda.device(self.device):
             _check(_lib.jx_rotate(self._h, _ptr(x), C.c_int64(x.shape[0]), _ptr(out), _stream()))
+        return out
+
+    def rotate_points(self, x):
+        assert x.dtype == _torch_dtype(self.dtype) and x.shape[1] == self.dim
+        out = torch.empty(x.shape, dtype=torch.float32, device=self.device)
+        with torch.cuda.device(self.device):
+            _check(_lib.jx_rotate_points(self._h, _ptr(x), C.c_int64(x.shape[0]), _ptr(out), _stream()))
         return out
 
     def encode_rotated(self, r):

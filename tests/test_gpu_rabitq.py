@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2601_07048_amd import datagen
-from gpu_common import dev, u32, oracle_index, gpu_index_from_oracle, random_data
+from gpu_common import dev, u32, oracle_index, gpu_index_from_oracle, jx_dtype, random_data
 
 pytestmark = pytest.mark.gpu
 
@@ -374,20 +374,38 @@ def test_quantize_end_to_end_other_widths(jx, bits, d, n):
     assert np.quantile(err, 0.98) < 1e-3 and err.max() < 0.05, (np.quantile(err, 0.98), err.max())
 
 
+@pytest.mark.parametrize("dtype,bits", [(np.float32, 1), (np.float32, 4), (np.float16, 8), (np.uint8, 2)])
 @pytest.mark.parametrize("d,n", [(32, 1), (96, 127), (128, 128), (160, 129), (960, 300)])
-def test_rotation_of_every_tile_edge(jx, d, n):
-    """One row to just over a tile of them, dimensions that end inside one: products of three bfloat16 parts against double
-    sums, 1e-6 of a row's norm (sums of 32 coordinates leave 2e-7)."""
-    x = random_data(n, d, np.float32, seed=d + n)
+def test_rotation_of_every_tile_edge(jx, d, n, dtype, bits):
+    """One row to just over a tile of them, dimensions that end inside one: products of three bfloat16 parts (queries, 1-bit codes)
+    and the float32 form (codes of more bits) against double sums, 1e-6 of a row's norm (sums of 32 coordinates leave 2e-7)."""
+    x = random_data(n, d, np.uint8 if dtype == np.uint8 else np.float32, seed=d + n).astype(dtype)
     P = datagen.random_orthogonal(d, d).astype(np.float32)
-    g = jx.Index(d, jx.F32, 8, 16, 1.2, capacity=max(n, 16), max_batch=1024, quant_bits=1)
+    g = jx.Index(d, jx_dtype(jx, x), 8, 16, 1.2, capacity=max(n, 16), max_batch=1024, quant_bits=bits)
     g.insert(dev(x))
-    g.quantize(1, dev(P), query_bits=4)
+    g.quantize(bits, dev(P), query_bits=4)
+    x = x.astype(np.float32)
     c = g.export_codes()[2].cpu().numpy().astype(np.float64)
-    got = g.rotate(dev(x)).cpu().numpy().astype(np.float64)
     want = (x.astype(np.float64) - c) @ P.astype(np.float64).T
     norm = np.linalg.norm(want, axis=1, keepdims=True)
-    assert (np.abs(got - want) <= 1e-6 * norm + 1e-7 * np.abs(x).max()).all()
+    for got in (g.rotate(dev(x)), g.rotate_points(dev(x.astype(dtype)))):
+        assert (np.abs(got.cpu().numpy().astype(np.float64) - want) <= 1e-6 * norm + 1e-7 * np.abs(x).max()).all()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16, np.uint8])
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+def test_stages_make_the_codes_of_an_index(jx, bits, dtype):
+    """jx_rotate_points and jx_encode_rotated are what jx_quantize does, bit for bit.  Of two forms of the rotation that differ in the
+    last bits only, some ten of these 2.9 M codes and most of the floats beside them would not agree."""
+    n, d = 3_000, 960
+    x = random_data(n, d, np.uint8, bits) if dtype == np.uint8 else _clustered(n, d, bits).astype(dtype)
+    g = jx.Index(d, jx_dtype(jx, x), 8, 8, 1.2, capacity=n, max_batch=1024, quant_bits=bits)
+    g.import_graph(dev(x), dev(np.full((n, 8), jx.NONE, np.uint32)), 0)
+    g.quantize(bits, dev(datagen.random_orthogonal(d, 5).astype(np.float32)))
+    codes, meta = g.encode_rotated(g.rotate_points(dev(x)))
+    want_codes, want_meta, _ = g.export_codes()
+    assert torch.equal(codes, want_codes)
+    assert torch.equal(meta.view(torch.int32), want_meta.view(torch.int32))
 
 
 def test_rotation_of_values_that_are_hardly_finite(jx):
