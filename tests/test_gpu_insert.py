@@ -183,9 +183,9 @@ def test_insert_errors(jx):
 
 
 def test_matrix_core_prune_on_uint8_variant(jx):
-    """The matrix-core robustPrune also has a uint8 instantiation (int8 MFMA, exact integers).  It is slower than
-    the LDS-cached form for 128-byte vectors and therefore off by default (JX_FLAG_GRAM_U8 switches it on): the
-    oracle's graph bit for bit, build and consolidation."""
+    """robustPrune as a Gram matrix has a uint8 instantiation (int8 MFMA, exact integers), the default for vectors of more
+    than 256 bytes; JX_FLAG_GRAM_U8 takes it for shorter ones as well, which rounds of pivots prune faster.  The oracle's
+    graph bit for bit, build and consolidation."""
     for (n, d, R, L, growth) in ((3000, 128, 32, 64, 0.25), (2500, 64, 100, 128, 0.25), (5000, 32, 12, 24, 1.0)):
         x = random_data(n, d, np.uint8, seed=n + R)
         ref = oracle.Index(d, np.uint8, R, L, 1.2, n, batch_growth=growth)
@@ -199,10 +199,9 @@ def test_matrix_core_prune_on_uint8_variant(jx):
         assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), "consolidate"
 
 
-def test_incremental_prune_of_full_rows(jx):
-    """uint8 rows remember which leading entries one robustPrune call selected together; the next prune of such a
-    row evaluates only the pairs that involve an appended or new entry.  Small R makes nearly every reverse edge
-    overflow its row; several insert calls, the oracle's graph bit for bit after each."""
+def test_rows_that_overflow_again_and_again(jx):
+    """Small R makes nearly every reverse edge overflow its row, which is pruned as a whole each time; several insert
+    calls, the oracle's graph bit for bit after each."""
     n, d, R, L = 6000, 128, 16, 32
     x = random_data(n, d, np.uint8, seed=77)
     ref = oracle.Index(d, np.uint8, R, L, 1.2, n)
@@ -217,14 +216,16 @@ def test_incremental_prune_of_full_rows(jx):
     assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0])
 
 
-def test_incremental_prune_switched_off_gives_the_same_graph(jx):
-    """Streaming inserts with the incremental prune switched off (JX_FLAG_NO_INCR_PRUNE) and on: both graphs equal
-    the oracle's after every call at N = 40,000, and each other at N = 200,000 (where the oracle is not run)."""
+def test_streaming_inserts_of_every_prune_kernel(jx):
+    """Streaming inserts with the pivot kernels, the Gram-matrix kernels and the list-based ones: each graph equals the
+    oracle's after every call at N = 40,000, and they equal each other at N = 200,000 (where the oracle is not run).
+    JX_FLAG_NO_INCR_PRUNE is accepted and changes nothing."""
     import torch
+    kernels = (0, jx.FLAG_NO_GRAM, jx.FLAG_GRAM_U8)
     n = 40_000
     x = datagen.base(2, n)
     ref = oracle.Index(128, np.uint8, 64, 128, 1.2, n)
-    gs = [jx.Index(128, jx.U8, 64, 128, 1.2, capacity=n, max_batch=n // 4 + 1, flags=fl) for fl in (0, jx.FLAG_NO_INCR_PRUNE)]
+    gs = [jx.Index(128, jx.U8, 64, 128, 1.2, capacity=n, max_batch=n // 4 + 1, flags=fl) for fl in (*kernels, jx.FLAG_NO_INCR_PRUNE)]
     for lo in range(0, n, 10_000):
         ref.insert(x[lo:lo + 10_000])
         want = ref.graph()[0]
@@ -235,13 +236,13 @@ def test_incremental_prune_switched_off_gives_the_same_graph(jx):
     n = 200_000
     dx = torch.from_numpy(datagen.base(2, n)).cuda()
     tables = []
-    for fl in (0, jx.FLAG_NO_INCR_PRUNE):
+    for fl in kernels:
         g = jx.Index(128, jx.U8, 64, 128, 1.2, capacity=n, max_batch=n // 4 + 1, flags=fl)
         for lo in range(0, n, 50_000):
             g.insert(dx[lo:lo + 50_000])
         tables.append(g.export_graph()[0])
         del g
-    assert torch.equal(tables[0], tables[1])
+    assert torch.equal(tables[0], tables[1]) and torch.equal(tables[0], tables[2])
 
 
 @pytest.mark.parametrize("n,d,R,L,calls,growth", [
