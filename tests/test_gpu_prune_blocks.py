@@ -115,12 +115,13 @@ def test_discard_limit_u8(jx, alpha):
     assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0])
 
 
+@pytest.mark.parametrize("d", [128, 256])
 @pytest.mark.parametrize("copies", [0, 900, 4000])
-def test_hub_u8(jx, copies):
+def test_hub_u8(jx, copies, d):
     """A centre that every point links to: more reverse edges than the first pool (512) and the second (2,048) hold.  With
     copies of three points next to it the closest 512 or 2,048 yield fewer than R neighbours, and the next kernel goes on."""
     rng = np.random.default_rng(8)
-    d, R = 128, 16
+    R = 16
     shell = np.clip(np.rint(128 + rng.normal(0, 25, (1500, d))), 0, 255).astype(np.uint8)
     near = 128 + 4 * np.eye(d, dtype=np.int64)[rng.integers(0, 3, copies)]
     x = np.concatenate([np.full((1, d), 128, np.uint8), near.astype(np.uint8), shell])
@@ -133,11 +134,12 @@ def test_hub_u8(jx, copies):
         assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), lo
 
 
-def test_many_edges_u8(jx):
+@pytest.mark.parametrize("d", [32, 144, 256])
+def test_many_edges_u8(jx, d):
     """A batch of more than 2^20 edges into full rows: merges of at most 128 candidates in a form of their own."""
     n0, batch, R = 263_000, 65_700, 16
-    x = random_data(n0 + batch, 32, np.uint8, seed=9)
-    gs = [jx.Index(32, jx.U8, R, 24, 1.2, capacity=n0 + batch, max_batch=70_000, flags=f) for f in (0, jx.FLAG_NO_GRAM)]
+    x = random_data(n0 + batch, d, np.uint8, seed=9)
+    gs = [jx.Index(d, jx.U8, R, 24, 1.2, capacity=n0 + batch, max_batch=70_000, flags=f) for f in (0, jx.FLAG_NO_GRAM)]
     for g in gs:
         g.insert(dev(x[:n0]))
         g.insert(dev(x[n0:]))
