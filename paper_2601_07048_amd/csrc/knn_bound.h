@@ -56,6 +56,12 @@ JX_HD float knn_threshold(float lim, float qq) { return (lim - qq) + (lim + qq) 
 // 3 ceil(d / 16) of them in a row by 24 ceil(d / 16) 2^-24 |q| |b|, in 2 <q, b> at most (0.75 d + 12) 2^-24 (|q| + |b|)^2.  With
 // the norms (d / 8 + 7), the sum (4) and the form of the result (d + 2) that is 1.9 d + 25; the first term has 2 d + 32
 #define KNN_BF16_PARTS 1.6e-5f
+// Up to KNN_FEW_D dimensions a value has three parts (what they leave is nothing) and six products: l r', r l' and r r' are left
+// out, 2^-24 (1 + 2^-10) |q| |b|, 2^-25 of the share.  Six instructions are off by 24 where 0.75 d + 12 is spared above: 41.5 of
+// 40 at d = 4
+#define KNN_FEW_D 16
+#define KNN_BF16_THREE 1.5e-7f
+JX_HD float knn_parts(int d) { return d <= KNN_FEW_D ? KNN_BF16_THREE : KNN_BF16_PARTS; }  // float32
 JX_HD float knn_eps(int d, float qq, float e, float bb_max, float parts = 0.f) {
     const float c = (float)(d + 16) * 1.2e-7f + parts;
     float len = (2.f * sqrtf(qq) + sqrtf(e)) * (1.f + sqrtf(c));

@@ -11,8 +11,8 @@
 //   uint8            v_mfma_i32_32x32x32_i8 on the values shifted by -128 (distances do not change): exact integers, so
 //                    the lists hold the result.
 //   float32/binary16 v_mfma_f32_32x32x16_bf16 on two bfloat16 parts of each value (three products: 96 cycles for 16
-//                    coordinates, 512 by 32x32x2_f32) / 32x32x16_f16: these distances only choose KNN_SLACK more candidates
-//                    than asked for.  The merge kernel evaluates them with the arithmetic of bruteforce_tile_kernel,
+//                    coordinates, 512 by 32x32x2_f32; three parts up to 16 dimensions) / 32x32x16_f16: these distances only
+//                    choose KNN_SLACK more candidates than asked for.  The merge kernel evaluates them with the arithmetic of bruteforce_tile_kernel,
 //                    operation by operation, orders them, and proves that nothing left out can be among the first
 //                    k: the first distance left out, less the error bound of both forms (knn_bound.h), has to exceed
 //                    the k-th one.
@@ -62,15 +62,13 @@ struct KnnOdd {
 template <int DT>
 constexpr uint32_t KNN_DECIDABLE = DT == JX_F16 ? 0x7F800000u : 0x7F800001u;  // bits of |b|^2 from which a row is one of those
 
-template <int DT>
-constexpr float KNN_SPLIT = DT == JX_F32 ? KNN_BF16_PARTS : 0.f;
-
 struct KnnArgs {
     const void* base;
     const void* queries;
     long long n, nq;
     int d, nch;         // dimensions, 16-byte chunks per vector
     int k, kp;          // neighbours asked for, kept per list
+    float parts;        // knn_parts of float32, else 0
     int nsplit;
     uint64_t* lists;    // [nq][nsplit][kp] keys (distance, id)
     uint32_t* published;  // [nq][nsplit][pub] distances of each slice's entries 2^pub_shift - 1, 2 2^pub_shift - 1, .., or NULL
@@ -112,12 +110,14 @@ __device__ __forceinline__ uint4 knn_stage(uint4 v, const bool in) {
     return make_uint4(in ? v.x : 0u, in ? v.y : 0u, in ? v.z : 0u, in ? v.w : 0u);
 }
 
-// Four float32 values on their way to LDS as bfloat16: rounded, and what that leaves, rounded again
+// Four float32 values on their way to LDS as bfloat16: rounded, and what that leaves, rounded again.  Three parts: of the first
+// sixteen coordinates
+template <int PARTS>
 __device__ __forceinline__ void knn_split(uint4* row, const int sch, const uint4 v) {
     float x[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
-    uint2 part[2];
+    uint2 part[PARTS];
 #pragma unroll
-    for (int p = 0; p < 2; p++) {
+    for (int p = 0; p < PARTS; p++) {
         uint32_t h[2];
 #pragma unroll
         for (int i = 0; i < 2; i++) {
@@ -128,8 +128,8 @@ __device__ __forceinline__ void knn_split(uint4* row, const int sch, const uint4
         }
         part[p] = make_uint2(h[0], h[1]);
     }
-    reinterpret_cast<uint2*>(row)[sch] = part[0];
-    reinterpret_cast<uint2*>(row)[8 + sch] = part[1];
+#pragma unroll
+    for (int p = 0; p < PARTS; p++) reinterpret_cast<uint2*>(row)[p * (PARTS == 3 ? 4 : 8) + sch] = part[p];
 }
 
 template <int DT>
@@ -388,8 +388,16 @@ __device__ __forceinline__ void knn_publish(KnnLds& S, const KnnArgs& a, const t
 // 1,000 from the origin, k = 10, with the stop / without / the tiled kernel alone: 256 x 100,003 float32 d = 960 4,330 / 5,190
 // / 4,216 us, 1,000 x 200,000 float32 d = 128 1,893 / 3,270 / 1,822, 256 x 100,000 binary16 d = 960 1,891 / 2,298 / 1,817.
 // What only the finished lists show is paid twice: 29 or more copies of every vector 5,103 / 4,216 and 2,971 / 1,860
-template <int DT, int NL, bool SEED>
+//
+// FEW: float32 of at most KNN_FEW_D dimensions, one slab of sixteen coordinates in three parts: the six matrix instructions that
+// two parts of 32 coordinates take, half the rows to stage and the queries' staged once.  With two parts vectors of few dimensions
+// that lie far from the origin cannot be proven.  k = 10, two parts / three / float32 instruction (which could prove them): d = 4
+// ten standard deviations away 1,000 x 100,000 722 / 200 / 561 us, 1,000 x 1M 2,240 / 685 / 1,876, 32 x 200,000 612 / 90 / 318;
+// d = 16 around the origin 217 / 205 / 569, 800 / 690 / 1,880 and 97 / 89 / 320
+template <int DT, int NL, bool SEED, bool FEW = false>
 __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
+    constexpr int PARTS = FEW ? 3 : 2;
+    constexpr int TPR = FEW ? 4 : 8, NT = KT * TPR / 256, STEP = 256 / TPR;  // staging: threads per row, rows per thread and how far apart
     typedef typename KAcc<DT>::type acc_t;
     typedef typename KAcc<DT>::elem elem_t;
     __shared__ KnnLds S;
@@ -405,7 +413,7 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
     const uint8_t* Q = reinterpret_cast<const uint8_t*>(a.queries);
     const uint8_t* B = reinterpret_cast<const uint8_t*>(a.base);
     const int nslab = (a.nch + 7) / 8;
-    const int srow = tid >> 3, sch = tid & 7;  // staging: 8 threads per row, rows srow + 32 t
+    const int srow = tid / TPR, sch = tid % TPR;
 
     for (int i = tid; i < KT; i += 256) {
         S.cnt[i] = 0;
@@ -433,16 +441,17 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
     }
     uint32_t bmax = 0;
 
-    uint4 pa[4], pb[4];
+    uint4 pa[NT], pb[NT];
     const size_t row_bytes = (size_t)(a.nch * 16);
     auto at = [&](const uint8_t* base, const long long row, const long long rows, const int ch) {
         return load16(base + (size_t)(row < rows ? row : rows - 1) * row_bytes + (size_t)((ch < a.nch ? ch : a.nch - 1) * 16));
     };
     auto fetch = [&](const long long b0, const int slab) {
 #pragma unroll
-        for (int t = 0; t < 4; t++) pb[t] = at(B, b0 + srow + 32 * t, b_end, slab * 8 + sch);
+        for (int t = 0; t < NT; t++) pb[t] = at(B, b0 + srow + STEP * t, b_end, slab * 8 + sch);
 #pragma unroll
-        for (int t = 0; t < 4; t++) pa[t] = at(Q, q0 + srow + 32 * t, a.nq, slab * 8 + sch);
+        for (int t = 0; t < NT; t++)
+            if (!FEW || b0 == b_begin) pa[t] = at(Q, q0 + srow + STEP * t, a.nq, slab * 8 + sch);
     };
     if (b_begin < b_end) fetch(b_begin, 0);
 
@@ -455,38 +464,38 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
             for (int j = 0; j < 2; j++)
 #pragma unroll
                 for (int e = 0; e < 16; e++) acc[i][j][e] = 0;
-        elem_t nb[4] = {0, 0, 0, 0}, nq[4] = {0, 0, 0, 0};
+        elem_t nb[NT] = {}, nq[NT] = {};
         for (int slab = 0; slab < nslab; slab++) {
 #pragma unroll
-            for (int t = 0; t < 4; t++) {
+            for (int t = 0; t < NT; t++) {
                 const bool chunk = slab * 8 + sch < a.nch;
-                {
-                    const uint4 v = knn_stage<DT>(pa[t], chunk && q0 + srow + 32 * t < a.nq);
+                if (!FEW || first) {
+                    const uint4 v = knn_stage<DT>(pa[t], chunk && q0 + srow + STEP * t < a.nq);
                     if constexpr (DT == JX_F32)
-                        knn_split(S.a + (srow + 32 * t) * (KROW / 16), sch, v);
+                        knn_split<PARTS>(S.a + (srow + STEP * t) * (KROW / 16), sch, v);
                     else
-                        S.a[(srow + 32 * t) * (KROW / 16) + sch] = v;
+                        S.a[(srow + STEP * t) * (KROW / 16) + sch] = v;
                     if (first) nq[t] = knn_sq<DT>(v, nq[t]);
                 }
-                const uint4 v = knn_stage<DT>(pb[t], chunk && b0 + srow + 32 * t < b_end);
+                const uint4 v = knn_stage<DT>(pb[t], chunk && b0 + srow + STEP * t < b_end);
                 if constexpr (DT == JX_F32)
-                    knn_split(S.b + (srow + 32 * t) * (KROW / 16), sch, v);
+                    knn_split<PARTS>(S.b + (srow + STEP * t) * (KROW / 16), sch, v);
                 else
-                    S.b[(srow + 32 * t) * (KROW / 16) + sch] = v;
+                    S.b[(srow + STEP * t) * (KROW / 16) + sch] = v;
                 nb[t] = knn_sq<DT>(v, nb[t]);
             }
-            if (slab == nslab - 1) {  // norms: the 8 threads of a row
-                uint32_t norm[4];
+            if (slab == nslab - 1) {  // norms: the threads of a row
+                uint32_t norm[NT];
 #pragma unroll
-                for (int t = 0; t < 4; t++) {
-                    const int row = srow + 32 * t;
-                    const elem_t x = group_sum<8>(nb[t]);
+                for (int t = 0; t < NT; t++) {
+                    const int row = srow + STEP * t;
+                    const elem_t x = group_sum<TPR>(nb[t]);
                     const bool in = b0 + row < b_end;
                     norm[t] = in ? knn_bits<DT>(x) : 0u;
                     // binary16: what is listed as odd takes no other way into the result
                     if (sch == 0) S.bn[row] = DT == JX_F16 && norm[t] == 0x7F800000u ? 0x7FC00000u : (in ? norm[t] : (DT == JX_U8 ? 0x7FFFFFFFu : 0x7F800000u));
                     if (first) {
-                        const elem_t y = group_sum<8>(nq[t]);
+                        const elem_t y = group_sum<TPR>(nq[t]);
                         if (sch == 0) {
                             S.qn[row] = knn_bits<DT>(y);
                             // rows beyond the last query accept nothing
@@ -500,17 +509,17 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                     }
                 }
                 if constexpr (DT != JX_U8 && !SEED) {
-                    const uint32_t lo = max(norm[0], norm[1]), hi = max(norm[2], norm[3]), most = max(lo, hi);
+                    const uint32_t most = NT == 2 ? max(norm[0], norm[1]) : max(max(norm[0], norm[1]), max(norm[NT - 2], norm[NT - 1]));
                     if (most < KNN_DECIDABLE<DT>) {
                         bmax = max(bmax, most);
                     } else if (sch == 0) {
 #pragma unroll
-                        for (int t = 0; t < 4; t++) {
+                        for (int t = 0; t < NT; t++) {
                             if (norm[t] < KNN_DECIDABLE<DT>) {
                                 bmax = max(bmax, norm[t]);
                             } else {
                                 const uint32_t to = atomicAdd(&a.odd[tile].count, 1u);
-                                if (to < KNN_ODD) a.odd[tile].id[to] = (uint32_t)(b0 + srow + 32 * t);
+                                if (to < KNN_ODD) a.odd[tile].id[to] = (uint32_t)(b0 + srow + STEP * t);
                             }
                         }
                     }
@@ -521,7 +530,28 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
                 fetch(b0, slab + 1);
             else if (b0 + KT < b_end)
                 fetch(b0 + KT, 0);
-            if constexpr (DT == JX_F32) {
+            if constexpr (FEW) {
+                kbf16x8 fb[2][3];  // [tile][part]
+#pragma unroll
+                for (int j = 0; j < 2; j++)
+#pragma unroll
+                    for (int p = 0; p < 3; p++) fb[j][p] = __builtin_bit_cast(kbf16x8, S.b[(wn * 64 + j * 32 + col) * (KROW / 16) + p * 2 + half]);
+#pragma unroll
+                for (int i = 0; i < 2; i++) {
+                    kbf16x8 fa[3];
+#pragma unroll
+                    for (int p = 0; p < 3; p++) fa[p] = __builtin_bit_cast(kbf16x8, S.a[(wm * 64 + i * 32 + col) * (KROW / 16) + p * 2 + half]);
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[2], fb[j][0], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0], fb[j][2], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1], fb[j][1], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1], fb[j][0], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0], fb[j][1], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0], fb[j][0], acc[i][j], 0, 0, 0);
+                    }
+                }
+            } else if constexpr (DT == JX_F32) {
 #pragma unroll
                 for (int s = 0; s < 2; s++) {
                     kbf16x8 fa[2][2], fb[2][2];  // [tile][part]
@@ -660,7 +690,7 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
         if constexpr (DT != JX_U8) {
             if (tid < KT) {
                 const float first = __uint_as_float(S.lim[tid]);
-                const bool hope = first < __builtin_inff() && knn_eps(a.d, __uint_as_float(S.qn[tid]), first, __builtin_inff(), KNN_SPLIT<DT>) * (float)a.kp <= first * (float)(KNN_SLACK / 4);
+                const bool hope = first < __builtin_inff() && knn_eps(a.d, __uint_as_float(S.qn[tid]), first, __builtin_inff(), a.parts) * (float)a.kp <= first * (float)(KNN_SLACK / 4);
                 const uint64_t bits = ballot(q0 + tid < a.nq && !hope);
                 if (lane == 0) reinterpret_cast<uint64_t*>(a.hopeless + (size_t)tile * a.nsplit + split)[wave] = bits;
             }
@@ -1046,7 +1076,7 @@ __global__ void __launch_bounds__(64) knn_merge_kernel(KnnArgs a) {
     bool proven = n_valid == a.n;
     if (!proven && n_valid == kp + n_odd && odd.count <= KNN_ODD && who) {
         const float e_k = __uint_as_float(readlane32(__float_as_uint(kth), __builtin_ctzll(who)));
-        proven = __uint_as_float((uint32_t)(worst >> 32)) - knn_eps(a.d, qq, e_k, __uint_as_float(odd.bb_max), KNN_SPLIT<DT>) > e_k;
+        proven = __uint_as_float((uint32_t)(worst >> 32)) - knn_eps(a.d, qq, e_k, __uint_as_float(odd.bb_max), a.parts) > e_k;
     }
     if (lane == 0) a.redo[qi] = proven ? 0u : 1u;
 }
@@ -1071,11 +1101,15 @@ static hipError_t launch_knn(const KnnArgs& a, hipStream_t st) {
         }
     }
     if (!one) {
+        const bool few = DT == JX_F32 && a.d <= KNN_FEW_D;
+        constexpr bool F32 = DT == JX_F32;
         if (a.seed_steps) {
-            hipLaunchKernelGGL((knn_tile_kernel<DT, 1, true>), grid, block, 0, st, a);
+            if (few) hipLaunchKernelGGL((knn_tile_kernel<DT, 1, true, F32>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((knn_tile_kernel<DT, 1, true>), grid, block, 0, st, a);
             hipLaunchKernelGGL(knn_limit_kernel, dim3((unsigned)a.nq), dim3(64), 0, st, a);
         }
-        hipLaunchKernelGGL((knn_tile_kernel<DT, NL, false>), grid, block, 0, st, a);
+        if (few) hipLaunchKernelGGL((knn_tile_kernel<DT, NL, false, F32>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((knn_tile_kernel<DT, NL, false>), grid, block, 0, st, a);
     }
     hipLaunchKernelGGL((knn_merge_kernel<DT, NL>), dim3((unsigned)a.nq), dim3(64), 0, st, a);
     return hipGetLastError();
@@ -1132,6 +1166,7 @@ hipError_t launch_knn_tile(const BfArgs& b, void* scratch, long long scratch_byt
     a.nch = (int)(row / 16);
     a.k = b.k;
     a.kp = exact ? b.k : b.k + KNN_SLACK;
+    a.parts = b.dtype == JX_F32 ? knn_parts(b.d) : 0.f;
     a.out_ids = b.out_ids;
     a.out_dist = b.out_dist;
     const long long qt = (b.nq + KT - 1) / KT, steps = (b.n + KT - 1) / KT;

@@ -80,6 +80,18 @@ def test_sets_far_from_the_origin(jx, dtype, far):
         check(jx, b.to(dtype), q.to(dtype), k)
 
 
+@pytest.mark.parametrize("d", [4, 8, 12, 16, 20])
+@pytest.mark.parametrize("offset", [0, 10, 40])
+def test_few_dimensions(jx, d, offset):
+    """Up to 16 dimensions values are taken whole: what two parts could not prove far from the origin is proven there."""
+    g = torch.Generator(device="cuda").manual_seed(14)
+    b, q = (torch.randn((n, d), device="cuda", generator=g) + offset for n in (40_000, 300))
+    b[7_000, 1], b[8_000, 2] = float("nan"), float("inf")
+    for k in (8, 10, 60):
+        check(jx, b, q, k)
+    check(jx, b, q[:7], 1)
+
+
 def rows(dtype, n, d, seed):
     g = torch.Generator(device="cuda").manual_seed(seed)
     x = torch.randn((n, d), device="cuda", generator=g)

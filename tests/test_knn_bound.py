@@ -16,7 +16,7 @@ extern "C" void thresholds(const float* lim, const float* qq, float* out, long n
     for (long i = 0; i < n; i++) out[i] = jx::knn_threshold(lim[i], qq[i]);
 }
 extern "C" void bounds_parts(int d, const float* qq, const float* e, const float* bb_max, float* out, long n) {
-    for (long i = 0; i < n; i++) out[i] = jx::knn_eps(d, qq[i], e[i], bb_max[i], KNN_BF16_PARTS);
+    for (long i = 0; i < n; i++) out[i] = jx::knn_eps(d, qq[i], e[i], bb_max[i], jx::knn_parts(d));
 }
 extern "C" void bounds(int d, const float* qq, const float* e, const float* bb_max, float* out, long n) {
     for (long i = 0; i < n; i++) out[i] = jx::knn_eps(d, qq[i], e[i], bb_max[i]);
@@ -119,52 +119,67 @@ def _bf16(x):
     return ((u + 0x7FFF + ((u >> 16) & 1)) & 0xFFFF0000).astype(np.uint32).view(np.float32)
 
 
-@pytest.mark.parametrize("d", [4, 32, 128, 1536])
+def _parts(x):
+    """Three bfloat16 parts of float32 values, in 64 bits."""
+    h = _bf16(x)
+    l = _bf16(x - h)
+    return h.astype(np.float64), l.astype(np.float64), (x - h - l).astype(np.float64)
+
+
+def _products(q, b):
+    """What the matrix cores add of each coordinate, smallest first: of two parts, and of three up to 16 dimensions."""
+    (h, l, r), (hb, lb, rb) = _parts(q), _parts(b)
+    three = [l * hb, h * lb, h * hb]
+    return [r * hb, h * rb, l * lb, *three] if q.shape[-1] <= 16 else three
+
+
+def _sums(products, sign):
+    """Sums of rows as matrix instructions take them: 16 products and the sum before them, each time off by 8 2^-24 of the largest
+    of these, towards the given side."""
+    d, total = products[0].shape[1], np.zeros(products[0].shape[0])
+    for j in range(0, d, 16):
+        for p in products:
+            group = p[:, j:j + 16]
+            total = total + group.sum(1) + sign * 8 * 2.0 ** -24 * np.maximum(np.abs(total), np.abs(group).max(1))
+    return total
+
+
+@pytest.mark.parametrize("d", [4, 16, 32, 128, 1536])
 @pytest.mark.parametrize("offset", [0.0, 3.0, 1000.0])
 @pytest.mark.filterwarnings("ignore::RuntimeWarning")
 @pytest.mark.parametrize("scale", [1e-19, 1.0, 1e15])
 def test_bound_covers_the_parts(lib, d, offset, scale):
-    """The norm form on two bfloat16 parts of each value, what the parts lack alone (products summed in 64 bits) and with a
-    float32 rounding after every 16 coordinates."""
+    """The norm form on bfloat16 parts of each value, what the parts lack alone (products summed in 64 bits) and with every
+    matrix instruction off by the most there is, to either side."""
     rng = np.random.default_rng(9)
     n, f = 2_000, np.float32
     q = ((rng.standard_normal((n, d)) + offset) * scale).astype(f)
     b = (q + rng.standard_normal((n, d)) * scale * 10.0 ** rng.uniform(-3, 1, (n, 1))).astype(f)
-    qh, bh = _bf16(q), _bf16(b)
-    ql, bl = _bf16(q - qh), _bf16(b - bh)
-    Q, B, QL, BL = (v.astype(np.float64) for v in (qh, bh, ql, bl))
-    products = QL * B + Q * BL + Q * B
-    x64, x32 = products.sum(1), np.zeros(n, f)
-    for j in range(0, d, 16):
-        x32 = (x32 + products[:, j:j + 16].sum(1)).astype(f)
+    products = _products(q, b)
     qq, bb = (q.astype(np.float64) ** 2).sum(1), (b.astype(np.float64) ** 2).sum(1)
     e = ((q.astype(np.float64) - b) ** 2).sum(1)
     eps = np.empty(n, f)
     lib.bounds_parts(C.c_int(d), _ptr(qq.astype(f)), _ptr(e.astype(f)), _ptr(np.full(n, np.inf, f)), _ptr(eps), C.c_long(n))
     assert scale > 1 or np.isfinite(eps).all()
-    for x in (x64, x32.astype(np.float64)):  # as above: no proof where norms of that length could overflow
-        assert (~(eps < np.inf) | (np.abs(qq + bb - 2 * x - e) <= eps)).all()
+    for sign in (-1, 0, 1):  # as above: no proof where norms of that length could overflow
+        assert (~(eps < np.inf) | (np.abs(qq + bb - 2 * _sums(products, sign) - e) <= eps)).all()
 
 
-def _parts(x):
-    """Two bfloat16 parts of float32 values and what they leave, in 64 bits."""
-    h = _bf16(x)
-    l = _bf16(x - h)
-    return h.astype(np.float64), l.astype(np.float64), x.astype(np.float64) - h - l
-
-
-def test_what_two_parts_leave_of_any_value():
-    """All significands: roundings to 8 bits leave up to 2^-8 and 2^-17 of a value, and the three products that are taken of a
-    value's own square lack up to 2^-15 of it."""
+def test_what_parts_leave_of_any_value():
+    """All significands: roundings to 8 bits leave up to 2^-8 and 2^-17 of a value, a third part leaves nothing, and the three products
+    of two parts that are taken of a value's own square lack up to 2^-15 of it, the six of three parts up to 2^-24."""
     x = (np.arange(1 << 23, dtype=np.uint32) | 0x3F800000).view(np.float32)
     h, l, r = _parts(x)
     assert (np.abs(l) <= 2.0 ** -8 * x).all() and np.abs(l / x).max() > 0.99 * 2.0 ** -8
     assert (np.abs(r) <= 2.0 ** -17 * x).all() and np.abs(r / x).max() > 0.99 * 2.0 ** -17
+    assert np.array_equal(_bf16(r.astype(np.float32)), r) and np.array_equal(h + l + r, x)
     lacks = (l * l + 2 * h * r) / x.astype(np.float64) ** 2
-    assert 0.98 * 2.0 ** -15 < np.abs(lacks).max() <= 2.0 ** -15 * (1 + 2.0 ** -7)
+    assert 0.98 * 2.0 ** -15 < np.abs(lacks).max() <= 2.0 ** -15 * (1 + 2.0 ** -9)
+    lacks = (r * r + 2 * l * r) / x.astype(np.float64) ** 2
+    assert 0.98 * 2.0 ** -24 < np.abs(lacks).max() <= 2.0 ** -24 * (1 + 2.0 ** -10)
 
 
-# significands whose parts lack most, of either sign: 1.0039139 (the search above finds it) and neighbours in other binades
+# the significand whose parts lack most (the search above finds it): 1.0039139
 WORST = np.array([0x3F808040], np.uint32).view(np.float32)[0]
 
 
@@ -172,17 +187,10 @@ WORST = np.array([0x3F808040], np.uint32).view(np.float32)[0]
 @pytest.mark.parametrize("scale", [2.0 ** -40, 1.0, 2.0 ** 40])
 def test_bound_covers_the_worst_significands(lib, d, scale):
     """A duplicate of a query whose every coordinate lacks the most there is: nothing cancels.  With every rounding of the norm
-    form against it as well: each matrix instruction off by 8 2^-24 of its largest term (16 products and the sum before them),
-    three of them per 16 coordinates, and the sums behind by half a unit in the last place each."""
+    form against it as well: matrix instructions as above, and the sums behind by half a unit in the last place each."""
     u = 2.0 ** -24
-    x = np.full(d, WORST * np.float32(scale), np.float32)
-    h, l, r = _parts(x)
-    total = 0.0
-    for j in range(0, d, 16):
-        for products in (l * h, h * l, h * h):
-            group = products[j:j + 16]
-            largest = max(total, group.max())
-            total = total + group.sum() - 8 * u * largest
+    x = np.full((1, d), WORST * np.float32(scale), np.float32)
+    total = _sums(_products(x, x), -1)[0]
     norm = (x.astype(np.float64) ** 2).sum()
     longest_chain = 4 * ((d + 31) // 32) + 3  # squares of a norm that one thread adds, and the eight threads of a row
     apart = 2 * norm * (1 + longest_chain * u) * (1 + u) - 2 * total + 2 * u * norm
