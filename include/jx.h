@@ -74,7 +74,8 @@ extern "C" {
  * variable.
  */
 #define JX_FLAG_NO_PAIR (1u << 0)       /* beamSearch: never take two expansions per round */
-#define JX_FLAG_NO_INCR_PRUNE (1u << 1) /* no effect: every overflowing row is pruned as a whole */
+#define JX_FLAG_NO_INCR_PRUNE (1u << 1) /* uint8 reverse merge: every overflowing row is pruned as a
+                                             whole, whatever it remembers of its last prune */
 #define JX_FLAG_NO_GRAM (1u << 2)       /* robustPrune by the list-based kernels, not the matrix-core (MFMA) ones */
 #define JX_FLAG_GRAM_U8 (1u << 3)       /* uint8 data: robustPrune by the Gram-matrix kernels, as for floats */
 #define JX_FLAG_VISITED_IDS (1u << 4)   /* beamSearch visited filter: direct-mapped table of full 32-bit ids (ParlayANN's

@@ -447,14 +447,16 @@ __global__ void __launch_bounds__(256) compact_flags_kernel(const uint32_t* adj,
 }
 
 // adj[i] = map[adj[i]] in place; the public renaming gets NONE for removed vertices
+// clean (NULL: none): what rows remember of their last prune does not move along
 __global__ void compact_rename_kernel(uint32_t* adj, long long n_entries, const uint32_t* map, const uint8_t* deleted, long long n,
-                                      uint32_t* public_map) {
+                                      uint32_t* public_map, uint8_t* clean) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n_entries) {
         const uint32_t u = adj[i];
         if (u != JX_NONE_ID) adj[i] = map[u];
     }
     if (public_map && i < n) public_map[i] = deleted[i] ? JX_NONE_ID : map[i];
+    if (clean && i < n) clean[i] = 0;
 }
 
 // live records of vertices [c0, c1) -> staging, packed in order; UNIT = uint4 or uint32_t
@@ -487,10 +489,10 @@ hipError_t launch_compact_flags(const uint32_t* adj, int R, long long n, const u
 }
 
 hipError_t launch_compact_rename(uint32_t* adj, int R, long long n, const uint32_t* map, const uint8_t* deleted,
-                                 uint32_t* public_map, hipStream_t st) {
+                                 uint32_t* public_map, uint8_t* clean, hipStream_t st) {
     const long long ne = n * R;
     hipLaunchKernelGGL(compact_rename_kernel, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, st, adj, ne, map, deleted, n,
-                       public_map);
+                       public_map, clean);
     return hipGetLastError();
 }
 

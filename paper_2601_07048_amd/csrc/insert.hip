@@ -265,6 +265,7 @@ __global__ void __launch_bounds__(INS_WPB * 64) forward_prune_kernel(InsertArgs 
     __threadfence_block();
     wave_sync();
     const int nsel = robust_prune_wave<KIND, T, CPL>(a.ds, L, 0, B, a.R, a.alpha);
+    if (KIND == K_U8 && lane == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
     uint32_t* row = a.adj + (size_t)xid * a.R;
     for (int j = lane; j < a.R; j += 64) {
         const bool on = j < nsel;
@@ -398,6 +399,7 @@ __global__ void __launch_bounds__(INS_WPB * 64) reverse_merge_kernel(InsertArgs 
             }
         }
         for (int j = lane; j < a.R; j += 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
+        if (KIND == K_U8 && lane == 0) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
         wave_sync();
     }
 }

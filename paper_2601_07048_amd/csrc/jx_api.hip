@@ -38,7 +38,7 @@ int fail(int code, const char* fmt, ...) {
 inline int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
 struct Layout {
-    int64_t vecs, adj, codes, P, centroid, stats, stripes, deleted, work, work_bytes, total;
+    int64_t vecs, adj, codes, P, centroid, stats, stripes, deleted, clean, work, work_bytes, total;
     int vec_bytes, code_bytes, meta_chunk, code_stride, plane_chunks, plane_shift;
 };
 
@@ -157,6 +157,8 @@ void layout(const jx_params* p, Layout* L) {
     off += 64 * 16 * 8;
     L->deleted = off;
     off += align256((int64_t)p->capacity + 4);
+    L->clean = off;
+    off += p->dtype == JX_U8 ? align256((int64_t)p->capacity + 4) : 0;
     // workspace: the larger of the insert phase and the query phase, at least 64 MiB
     const int64_t B = p->max_batch;
     InsertWork iw;
@@ -189,6 +191,15 @@ int gram_mode(const jx_index* idx) {
     if (idx->flags & JX_FLAG_NO_GRAM) return 0;
     if (idx->p.dtype == JX_U8) return (idx->flags & JX_FLAG_GRAM_U8) || idx->vec_bytes > 256 ? 3 : 4;
     return idx->p.dtype == JX_F16 ? 2 : 1;
+}
+
+// Whether merges of a batch of B points into `linked` ones use what rows remember of their last prune: a launch of its own
+// (5 us), for rows that are full and get an edge or two.  R = 64, whole prunes / with the memory, us a call: 256 points into
+// 2M x 128 478 / 484, 512 544 / 529, 2,048 828 / 703, 8,192 2,121 / 1,608.  Batches that are large against the index meet rows
+// that are not full, or bring them many edges: 1/4 of 400,000 x 128 7,552 / 7,543, 1/16 2,307 / 2,320, 1/32 1,384 / 1,372,
+// 1/16 of 400,000 x 256 3,234 / 3,059, 1/4 9,765 / 9,743
+bool merges_by_memory(const jx_index* idx, int64_t linked, int64_t B) {
+    return !(idx->flags & JX_FLAG_NO_INCR_PRUNE) && B * idx->p.R >= 1 << 15 && B * 16 <= linked;
 }
 
 hipError_t launch_tiled(const jx::BfArgs& a, hipStream_t st) {
@@ -315,6 +326,7 @@ int jx_create(const jx_params* p, void* d_arena, int64_t arena_bytes, void* stre
     x->d_stats = (unsigned long long*)(x->d_arena + L.stats);
     x->d_stripes = (unsigned long long*)(x->d_arena + L.stripes);
     x->d_deleted = x->d_arena + L.deleted;
+    x->d_clean = p->dtype == JX_U8 ? x->d_arena + L.clean : nullptr;
     x->d_work = x->d_arena + L.work;
     x->work_bytes = L.work_bytes;
     x->code_bytes = L.code_bytes;
@@ -326,6 +338,7 @@ int jx_create(const jx_params* p, void* d_arena, int64_t arena_bytes, void* stre
     hipError_t e = jx::launch_fill_u32(x->d_adj, (long long)p->capacity * p->R, JX_NONE, as_stream(stream));
     if (e == hipSuccess) e = jx::launch_fill_u32((uint32_t*)x->d_stats, 64, 0u, as_stream(stream));
     if (e == hipSuccess) e = jx::launch_fill_u32((uint32_t*)x->d_deleted, (p->capacity + 3) / 4, 0u, as_stream(stream));
+    if (e == hipSuccess && x->d_clean) e = jx::launch_fill_u32((uint32_t*)x->d_clean, (p->capacity + 3) / 4, 0u, as_stream(stream));
     if (e != hipSuccess) {
         delete x;
         return fail(JX_EHIP, "arena initialisation: %s", hipGetErrorString(e));
@@ -371,6 +384,8 @@ int jx_import_graph(jx_index* idx, const void* d_vecs, int64_t n, const uint32_t
     }
     JX_HIP(hipMemcpyAsync(idx->d_vecs, d_vecs, (size_t)n * idx->vec_bytes, hipMemcpyDeviceToDevice, st));
     JX_HIP(hipMemcpyAsync(idx->d_adj, d_adj, (size_t)n * idx->p.R * 4, hipMemcpyDeviceToDevice, st));
+    if (idx->d_clean && idx->any_clean) JX_HIP(jx::launch_fill_u32((uint32_t*)idx->d_clean, (idx->p.capacity + 3) / 4, 0u, st));  // nothing is known about foreign rows
+    idx->any_clean = 0;
     if (n < idx->n) JX_HIP(jx::launch_fill_u32(idx->d_adj + (size_t)n * idx->p.R, (idx->n - n) * idx->p.R, JX_NONE, st));
     if (idx->any_delete) {
         JX_HIP(jx::launch_fill_u32((uint32_t*)idx->d_deleted, (idx->p.capacity + 3) / 4, 0u, st));
@@ -701,6 +716,8 @@ static int run_subbatch(jx_index* idx, const InsertWork& w, int64_t pos0, int64_
     a.nseg = (const uint32_t*)(W + w.counters);
     a.vec_cache_bytes = 0;
     a.gram = gram_mode(idx);
+    a.clean = idx->d_clean;
+    idx->any_clean = 1;
     JX_HIP(jx::launch_forward_prune(p.dtype, a, st));
     // 3. one global sort by (target, distance, source)
     int tbits = 1;
@@ -713,6 +730,7 @@ static int run_subbatch(jx_index* idx, const InsertWork& w, int64_t pos0, int64_
     a.keys = (uint64_t*)(W + (other ? w.keys1 : w.keys0));
     a.vals = (uint32_t*)(W + (other ? w.vals1 : w.vals0));
     a.lists = (uint64_t*)(W + (other ? w.keys0 : w.keys1));  // the one that is free now
+    if (a.gram == 4 && merges_by_memory(idx, id_base, B)) a.fresh = (uint32_t*)(W + (other ? w.vals0 : w.vals1));
     // 4. per target: append or robustPrune
     // LDS room per wavefront for the vectors of a full row plus up to 32 new edges (96 x 128 bytes);
     // larger merges take the path that reads from global memory
@@ -999,6 +1017,8 @@ int jx_consolidate(jx_index* idx, void* stream) {
     a.lists = (uint64_t*)(W + w.keys0);
     a.force_prune = 1;
     a.gram = gram_mode(idx);
+    a.clean = idx->d_clean;
+    idx->any_clean = 1;
     a.vec_cache_bytes = 12288;
     // 2. slices of consecutive vertices whose candidate lists fit the edge buffers; every new row is
     //    computed from its own old row and from rows of deleted vertices, none of which is rewritten here
@@ -1085,7 +1105,7 @@ int jx_compact(jx_index* idx, uint32_t* d_old_to_new, void* stream) {
     JX_HIP(hipStreamSynchronize(st));
     if (herr) return fail(JX_ESTATE, "a live vertex still points to a deleted one: call jx_consolidate first");
     JX_HIP(jx::launch_scan_u32(map, n + 1, st));
-    JX_HIP(jx::launch_compact_rename(idx->d_adj, p.R, n, map, idx->d_deleted, d_old_to_new, st));
+    JX_HIP(jx::launch_compact_rename(idx->d_adj, p.R, n, map, idx->d_deleted, d_old_to_new, idx->d_clean, st));
     JX_HIP(jx::launch_compact_records(idx->d_vecs, idx->vec_bytes, n, map, idx->d_deleted, staging, staging_bytes, st));
     JX_HIP(jx::launch_compact_records((uint8_t*)idx->d_adj, p.R * 4, n, map, idx->d_deleted, staging, staging_bytes, st));
     if (idx->quantized)
@@ -1097,6 +1117,7 @@ int jx_compact(jx_index* idx, uint32_t* d_old_to_new, void* stream) {
     if (live > (uint64_t)n) return fail(JX_EHIP, "compaction counted %u live vertices of %lld", live, (long long)n);
     if (live < (uint64_t)n) JX_HIP(jx::launch_fill_u32(idx->d_adj + (size_t)live * p.R, (n - live) * p.R, JX_NONE, st));
     JX_HIP(jx::launch_fill_u32((uint32_t*)idx->d_deleted, (n + 3) / 4, 0u, st));
+    idx->any_clean = 0;
     JX_HIP(jx::launch_fill_u32((uint32_t*)(idx->d_stats + 8), 2, 0u, st));
     idx->n = live;
     idx->entry = live ? new_entry : JX_NONE;

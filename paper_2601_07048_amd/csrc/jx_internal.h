@@ -81,9 +81,12 @@ struct InsertArgs {
     uint64_t* keys;             // [B*R] edge keys
     uint32_t* vals;             // [B*R] edge sources
     const uint32_t* heads;      // segment starts (reverse merge); bit 31 is set by a kernel that has merged the segment
-    const uint32_t* nseg;       // number of segments (device); [1], [2]: lengths of the lists below, cleared by the sort
+    const uint32_t* nseg;       // number of segments (device); [1], [2], [3]: lengths of the lists below, cleared by the sort
     uint64_t* lists;            // Gram-matrix kernels: room for an entry per edge, segments by size
     long long E;                // reverse merge: number of sorted edges (0 = B * R)
+    uint8_t* clean;             // uint8: [N] so many leading entries of a row are what one robustPrune selected together (255: or more),
+                                // kept up by every kernel that writes rows; NULL for floats
+    uint32_t* fresh;            // room for an entry per edge: segments that rely on it, see reverse_class_kernel; NULL = none may
     int force_prune;            // consolidation: ignore the existing row, always prune the candidate segment
     int gram;                   // 0 = list-based kernels only, 1 / 2 / 3 = Gram-matrix kernels (float32 / binary16 / uint8), 4 = pivot kernels (uint8)
     int vec_cache_bytes;        // reverse merge: LDS bytes per wavefront for candidate vectors (0 = never cache)
@@ -93,6 +96,7 @@ hipError_t launch_entry_point(const void* vecs, int dtype, long long n, int d, d
                               uint32_t* out_id, hipStream_t st);
 hipError_t launch_forward_prune(int dtype, const InsertArgs& a, hipStream_t st);
 hipError_t launch_reverse_merge(int dtype, const InsertArgs& a, hipStream_t st);
+#define FRESH_MAX 15
 // splits the segments into lists[] by size and appends where the row still fits (prune_gram.hip); an entry of lists
 hipError_t launch_reverse_class(const InsertArgs& a, int small_max, int deg_max, hipStream_t st);
 __host__ __device__ inline int seg_deg(uint64_t entry) { return (int)(entry >> 44); }
@@ -189,7 +193,7 @@ hipError_t launch_nearest_live(const void* vecs, int dtype, long long n, int d, 
 hipError_t launch_compact_flags(const uint32_t* adj, int R, long long n, const uint8_t* deleted, uint32_t* flag, uint32_t* err,
                                 hipStream_t st);
 hipError_t launch_compact_rename(uint32_t* adj, int R, long long n, const uint32_t* map, const uint8_t* deleted,
-                                 uint32_t* public_map, hipStream_t st);
+                                 uint32_t* public_map, uint8_t* clean, hipStream_t st);
 hipError_t launch_compact_records(uint8_t* base, int rec_bytes, long long n, const uint32_t* map, const uint8_t* deleted,
                                   uint8_t* staging, long long staging_bytes, hipStream_t st);
 
@@ -241,6 +245,8 @@ struct jx_index {
     unsigned long long* d_stats;  // [8] = vertices marked deleted so far, [10] scratch of jx_import_graph
     unsigned long long* d_stripes;  // [64][16] search counters (BeamArgs::stats)
     uint8_t* d_deleted;  // [capacity] 1 = logically deleted
+    uint8_t* d_clean;    // [capacity] see InsertArgs::clean
+    int any_clean;       // rows have been pruned since it was cleared
     int any_delete;      // a delete call has been made since the graph was created / imported
     uint32_t flags;      // JX_FLAG_* switches (jx_params.flags, jx_set_flags)
     // RaBitQ state

@@ -477,6 +477,7 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) forward_prune_gram_
     const int nsel = team_prune<DT, NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, m, 0, (uint32_t)xid, a.R, a.alpha, m < nB);
     if (NB == 8 && tid == 0) a.dead[(size_t)i * a.L] = nsel < 0 ? 0 : 0xFF;
     if (nsel < 0) return;
+    if (DT == JX_U8 && tid == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
     uint32_t* row = a.adj + (size_t)xid * a.R;
     for (int j = tid; j < a.R; j += NB * 64) {
         const bool on = j < nsel;
@@ -492,7 +493,8 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) forward_prune_gram_
 // kernels below spends a chain of dependent loads on a segment that is not its own.  An entry holds the segment, the
 // degree of its row and the number of new edges (at most 4,095 are told apart); lists[0..) is the list of the small
 // ones (at most small_max candidates), lists[.. E - 1] downwards that of the large ones; rows of more than deg_max
-// neighbours leave a large one too little room for new edges.
+// neighbours leave a large one too little room for new edges.  fresh[0..) (or NULL) is the list of the rows whose first
+// entries one prune selected, with at most FRESH_MAX others (prune_u8.hip).
 __global__ void __launch_bounds__(256) reverse_class_kernel(InsertArgs a, int small_max, int deg_max) {
     const int lane = lane_id();
     const long long nseg = *a.nseg;
@@ -532,17 +534,22 @@ __global__ void __launch_bounds__(256) reverse_class_kernel(InsertArgs a, int sm
                 const_cast<uint32_t*>(a.heads)[s] = (uint32_t)lo | 0x80000000u;
             } else {
                 cls = deg + m <= small_max ? 1 : (deg <= deg_max ? 2 : 0);
+                if (a.fresh) {
+                    const int c = a.clean[v];
+                    if (c > 0 && c <= 64 && c <= deg && deg - c + m <= FRESH_MAX && deg + m > 32) cls = 3;
+                }
                 entry = (uint64_t)s | ((uint64_t)((uint32_t)deg << 12 | (uint32_t)(m < 4095 ? m : 4095)) << 32);
             }
         }
 #pragma unroll
-        for (int k = 1; k <= 2; k++) {
+        for (int k = 1; k <= 3; k++) {
             const uint64_t on = ballot(cls == k);
             if (!on) continue;
             uint32_t at = 0;
             if (lane == 0) at = atomicAdd(const_cast<uint32_t*>(a.nseg) + k, (uint32_t)__builtin_popcountll(on));
             at = readlane32(at, 0) + (uint32_t)prefix_count(on);
-            if (cls == k) a.lists[k == 1 ? (long long)at : total - 1 - at] = entry;
+            if (cls == k && k == 3) a.fresh[at] = (uint32_t)s;
+            else if (cls == k) a.lists[k == 1 ? (long long)at : total - 1 - at] = entry;
         }
     }
 }
@@ -574,6 +581,7 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) reverse_merge_gram_
         const int nsel = team_prune<DT, NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, deg + mp, deg, v, a.R, a.alpha, mp < m);
         if (nsel >= 0) {
             for (int j = tid; j < a.R; j += NB * 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
+            if (DT == JX_U8 && tid == 0) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
             if (tid == 0) const_cast<uint32_t*>(a.heads)[s] = (uint32_t)lo | 0x80000000u;
         }
         __syncthreads();

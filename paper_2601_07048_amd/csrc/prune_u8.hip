@@ -243,6 +243,7 @@ __global__ void __launch_bounds__(64) forward_prune_u8_kernel(InsertArgs a) {
     wave_sync();
     const int nsel = pivot_prune<S, MAXC>(L, a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch, m, (uint32_t)xid, a.R, a.alpha);
     wave_sync();
+    if (lane == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
     uint32_t* row = a.adj + (size_t)xid * a.R;
     for (int j = lane; j < a.R; j += 64) {
         const bool on = j < nsel;
@@ -253,13 +254,141 @@ __global__ void __launch_bounds__(64) forward_prune_u8_kernel(InsertArgs a) {
     }
 }
 
+// ---- reverse-edge merge of a row whose first c entries one robustPrune selected together (they stand in (distance, id) order and
+// none discards another), with k - 1 <= 15 appended entries and new edges behind them: the fresh ones.  Only pairs with a fresh
+// one have to be tested.  In order of distance a fresh entry is dead if one that is alive and comes before it discards it; else it
+// stays, and what it discards is dead from then on.  p and the fresh vectors are the rows of a tile, the clean ones the
+// columns of one or two, so every vector is read once and the chain has one memory latency, where rounds of pivots have
+// one for the distances and one for each round.  Full rows that get an edge now and then, which is what a stream into a large
+// index consists of, take this way: 100,000 points into 8M 20.8 -> 17.3 ms, into 20M 29.4 -> 23.1 (26.7 by the list-based kernel
+// of few fresh entries that stood here before the rounds of pivots).
+template <int S>
+__device__ __forceinline__ int merge_fresh(const InsertArgs& a, const uint32_t v, uint32_t* row, const int c, const int deg, const int k,
+                                           const long long lo) {
+    const int lane = lane_id(), col = lane & 31, half = lane >> 5;
+    const size_t stride = (size_t)a.ds.rec_stride;
+    uint32_t iid = v;  // items: 0 = v, 1 .. k = the fresh ones
+    if (col >= 1 && col <= k) {
+        const int f = col - 1;
+        iid = f < deg - c ? row[c + f] : a.vals[lo + f - (deg - c)];
+    }
+    uint32_t cid[2];
+#pragma unroll
+    for (int b = 0; b < 2; b++) cid[b] = row[b * 32 + col < c ? b * 32 + col : 0];
+    const int nb = c > 32 ? 2 : 1;  // uniform
+    Frag<S> it, x[2];
+    it.load(a.ds.recs + (size_t)iid * stride, half, a.ds.nch);
+    x[0].load(a.ds.recs + (size_t)cid[0] * stride, half, a.ds.nch);
+    if (nb == 2) x[1].load(a.ds.recs + (size_t)cid[1] * stride, half, a.ds.nch);
+    it.shift();
+    const int ni = frag_dot(it, it), np = (int)readlane32((uint32_t)ni, 0);
+    uint32_t dis[3] = {}, vic[3] = {};  // lane r, item r: what discards it and what it discards among the clean ones 0 .. 31, 32 .. 63, the items
+    uint64_t kx[3];                     // (distance, id) of the lane's column
+    // the tile of one set of columns
+    auto tile = [&](const Frag<S>& y, const int ny, const uint32_t id, const bool on, const int b) __attribute__((always_inline)) {
+        gi32x16_t acc;
+#pragma unroll
+        for (int e = 0; e < 16; e++) acc[e] = 0;
+#pragma unroll
+        for (int s = 0; s < 4 * S; s++)
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(gi32x4_t, it.x[s]), __builtin_bit_cast(gi32x4_t, y.x[s]), acc, 0, 0, 0);
+        const int other = shfl_xor(acc[0], 32), dp = half ? other : acc[0];  // row 0 is with the first half
+        const float dx = (float)(uint32_t)(np + ny - 2 * dp);
+        kx[b] = ((uint64_t)__float_as_uint(dx) << 32) | id;
+#pragma unroll
+        for (int e = 0; e < 8; e++) {  // rows r0 and r0 + 4: accumulator register e of half h is row 8 (e / 4) + 4 h + e % 4
+            const int r0 = 8 * (e >> 2) + (e & 3), r = r0 + 4 * half;
+            if (r0 > k) continue;  // uniform
+            const uint64_t kf0 = readlane64(kx[2], r0), kf1 = readlane64(kx[2], r0 + 4), kf = half ? kf1 : kf0;
+            const int nf0 = (int)readlane32((uint32_t)ni, r0), nf1 = (int)readlane32((uint32_t)ni, r0 + 4);
+            const float ad = __fmul_rn(a.alpha, (float)(uint32_t)(ny + (half ? nf1 : nf0) - 2 * acc[e]));
+            const bool pair = on && r >= 1 && r <= k;
+            const uint64_t out = ballot(pair && kf < kx[b] && ad <= dx);
+            const uint64_t in = ballot(pair && kx[b] < kf && ad <= __uint_as_float((uint32_t)(kf >> 32)));
+            if (lane == r0) {
+                vic[b] = (uint32_t)out;
+                dis[b] = (uint32_t)in;
+            }
+            if (lane == r0 + 4) {
+                vic[b] = (uint32_t)(out >> 32);
+                dis[b] = (uint32_t)(in >> 32);
+            }
+        }
+    };
+    tile(it, ni, iid, col >= 1 && col <= k, 2);  // first: the fresh ones' own distances
+    kx[1] = JX_EMPTY_KEY;
+    x[0].shift();
+    tile(x[0], frag_dot(x[0], x[0]), cid[0], col < c, 0);
+    if (nb == 2) {
+        x[1].shift();
+        tile(x[1], frag_dot(x[1], x[1]), cid[1], 32 + col < c, 1);
+    }
+    // ---- Alg. 3
+    uint32_t alive0 = c >= 32 ? 0xFFFFFFFFu : (1u << c) - 1u, alive1 = c >= 64 ? 0xFFFFFFFFu : (c > 32 ? (1u << (c - 32)) - 1u : 0u), alivef = 0;
+    int place = 0;
+    for (int t = 1; t <= k; t++) place += readlane64(kx[2], t) < kx[2] ? 1 : 0;
+    for (int s = 0; s < k; s++) {
+        uint32_t next = (uint32_t)ballot(lane >= 1 && lane <= k && place == s);
+        for (; next; next &= next - 1u) {
+            const int r = __builtin_ctz(next);
+            if ((readlane32(dis[0], r) & alive0) | (readlane32(dis[1], r) & alive1) | (readlane32(dis[2], r) & alivef)) continue;
+            alive0 &= ~readlane32(vic[0], r);
+            alive1 &= ~readlane32(vic[1], r);
+            alivef |= 1u << r;
+        }
+    }
+    int nsel = c;
+    if (alivef) {  // else the clean ones stay where they are
+        const uint32_t before = (1u << col) - 1u;
+        int at0 = __builtin_popcount(alive0 & before), at1 = __builtin_popcount(alive0) + __builtin_popcount(alive1 & before), atf = 0;
+        for (uint32_t w = alivef; w; w &= w - 1u) {
+            const int f = __builtin_ctz(w);
+            const uint64_t kf = readlane64(kx[2], f);
+            const int ahead = __builtin_popcount(alive0 & ~(uint32_t)ballot(kf < kx[0])) + __builtin_popcount(alive1 & ~(uint32_t)ballot(kf < kx[1]));
+            at0 += kf < kx[0] ? 1 : 0;
+            at1 += kf < kx[1] ? 1 : 0;
+            atf += (kf < kx[2] ? 1 : 0) + (lane == f ? ahead : 0);
+        }
+        if (half == 0 && ((alive0 >> col) & 1u) && at0 != col && at0 < a.R) row[at0] = cid[0];
+        if (half == 1 && ((alive1 >> col) & 1u) && at1 != 32 + col && at1 < a.R) row[at1] = cid[1];
+        if (half == 0 && ((alivef >> col) & 1u) && atf < a.R) row[atf] = iid;
+        nsel = __builtin_popcount(alive0) + __builtin_popcount(alive1) + __builtin_popcount(alivef);
+        if (nsel > a.R) nsel = a.R;
+    }
+    for (int j = nsel + lane; j < deg; j += 64) row[j] = JX_NONE_ID;
+    return nsel;
+}
+
+// The segments that reverse_class_kernel has listed for it
+template <int S>
+__global__ void __launch_bounds__(64, S == 1 ? 4 : 1) reverse_merge_fresh_u8_kernel(InsertArgs a) {
+    const int lane = lane_id();
+    const uint32_t n = a.nseg[3];
+    const long long total = a.B * a.R;
+    for (uint32_t at = blockIdx.x; at < n; at += gridDim.x) {
+        const uint32_t s = a.fresh[at], lo = a.heads[s];
+        const uint32_t v = (uint32_t)(a.keys[lo] >> 32);
+        const uint32_t* keys_hi = reinterpret_cast<const uint32_t*>(a.keys) + 1;
+        const int m = __builtin_popcountll(ballot(lane < 16 && lo + lane < total && keys_hi[2 * (size_t)(lo + (lane < 16 ? lane : 0))] == v));
+        uint32_t* row = a.adj + (size_t)v * a.R;
+        const int c = a.clean[v];
+        int deg = 0;
+        for (int r = 0; r < a.R; r += 64) deg += __builtin_popcountll(ballot(r + lane < a.R && row[r + lane] != JX_NONE_ID));
+        const int nsel = merge_fresh<S>(a, v, row, c, deg, deg - c + m, lo);
+        if (lane == 0) {
+            a.clean[v] = (uint8_t)nsel;
+            const_cast<uint32_t*>(a.heads)[s] = lo | 0x80000000u;
+        }
+    }
+}
+
 // ---- reverse-edge merge (Alg. 4 step 3) and consolidation: the listed segments, a wavefront each.  Beyond MAXC candidates
 // the pool is the row and the closest new edges (they arrive sorted by distance): what happens to a candidate depends on
 // earlier ones only, so the result is exact if the R-th selection comes no later than the last new edge of the pool.
 // lists: bit 0 / 1 = the first / second.  MAXC = 512 takes both, or the second alone, MAXC = 2,048 what it has left of the second
 // (hubs: the entry point, vertices near it), and the list-based kernel the rest.  MAXC = 128 takes the first, of at most 128
 // candidates, where a batch has PIVOT_MANY edges: 7 KB of LDS let 16 wavefronts into a CU for 12, below that the launch costs
-// more than it gives (5 us).  100,000 points into 8 M 26.4 -> 23.5 ms.
+// more than it gives (5 us).  100,000 points into 2 M 10.0 -> 9.8 ms; beyond, where full rows go by their memory, even.
 #define PIVOT_MANY (1 << 20)
 template <int S, int MAXC>
 __global__ void __launch_bounds__(64, S == 1 && MAXC <= 512 ? 4 : 1) reverse_merge_u8_kernel(InsertArgs a, int lists) {
@@ -350,7 +479,10 @@ __global__ void __launch_bounds__(64, S == 1 && MAXC <= 512 ? 4 : 1) reverse_mer
             if (nsel < a.R || (((uint64_t)L->sel_dist[nsel - 1] << 32) | L->sel_id[nsel - 1]) > tau) continue;
         }
         for (int j = lane; j < a.R; j += 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
-        if (lane == 0) const_cast<uint32_t*>(a.heads)[s] = (uint32_t)lo | 0x80000000u;
+        if (lane == 0) {
+            a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
+            const_cast<uint32_t*>(a.heads)[s] = (uint32_t)lo | 0x80000000u;
+        }
     }
 }
 
@@ -376,6 +508,11 @@ hipError_t launch_reverse_merge_u8(const InsertArgs& a, hipStream_t st) {
     const int rest = many ? 2 : 3;
     hipError_t e = launch_reverse_class(a, many ? 128 : 512, JX_MAX_R, st);
     if (e != hipSuccess) return e;
+    if (a.fresh) {
+        const dim3 grid((unsigned)(most < 16384 ? most : 16384));
+        if (a.ds.nch <= 8) hipLaunchKernelGGL(reverse_merge_fresh_u8_kernel<1>, grid, dim3(64), 0, st, a);
+        else hipLaunchKernelGGL(reverse_merge_fresh_u8_kernel<2>, grid, dim3(64), 0, st, a);
+    }
     const dim3 block(64), grid((unsigned)(most < 8192 ? most : 8192)), few((unsigned)(most < 1024 ? most : 1024));
     if (a.ds.nch <= 8) {
         if (many) hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 128>), grid, block, 0, st, a, 1);

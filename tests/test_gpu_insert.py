@@ -217,15 +217,15 @@ def test_rows_that_overflow_again_and_again(jx):
 
 
 def test_streaming_inserts_of_every_prune_kernel(jx):
-    """Streaming inserts with the pivot kernels, the Gram-matrix kernels and the list-based ones: each graph equals the
-    oracle's after every call at N = 40,000, and they equal each other at N = 200,000 (where the oracle is not run).
-    JX_FLAG_NO_INCR_PRUNE is accepted and changes nothing."""
+    """Streaming inserts with the pivot kernels (with and without what rows remember of their last prune), the Gram-matrix
+    kernels and the list-based ones: each graph equals the oracle's after every call at N = 40,000, and they equal each other
+    at N = 200,000 (where the oracle is not run)."""
     import torch
-    kernels = (0, jx.FLAG_NO_GRAM, jx.FLAG_GRAM_U8)
+    kernels = (0, jx.FLAG_NO_INCR_PRUNE, jx.FLAG_NO_GRAM, jx.FLAG_GRAM_U8)
     n = 40_000
     x = datagen.base(2, n)
     ref = oracle.Index(128, np.uint8, 64, 128, 1.2, n)
-    gs = [jx.Index(128, jx.U8, 64, 128, 1.2, capacity=n, max_batch=n // 4 + 1, flags=fl) for fl in (*kernels, jx.FLAG_NO_INCR_PRUNE)]
+    gs = [jx.Index(128, jx.U8, 64, 128, 1.2, capacity=n, max_batch=n // 4 + 1, flags=fl) for fl in kernels]
     for lo in range(0, n, 10_000):
         ref.insert(x[lo:lo + 10_000])
         want = ref.graph()[0]
@@ -242,7 +242,7 @@ def test_streaming_inserts_of_every_prune_kernel(jx):
             g.insert(dx[lo:lo + 50_000])
         tables.append(g.export_graph()[0])
         del g
-    assert torch.equal(tables[0], tables[1]) and torch.equal(tables[0], tables[2])
+    assert all(torch.equal(tables[0], t) for t in tables[1:])
 
 
 @pytest.mark.parametrize("n,d,R,L,calls,growth", [

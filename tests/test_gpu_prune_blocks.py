@@ -147,6 +147,38 @@ def test_many_edges_u8(jx, d):
     assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("d", [32, 128, 144, 256])
+@pytest.mark.parametrize("R,alpha", [(16, 1.2), (31, 1.0), (32, 1.2), (33, 1.2), (48, 1.05), (64, 1.2), (64, 2.0), (65, 1.2), (96, 1.2)])
+def test_rows_that_remember_their_last_prune(jx, d, R, alpha):
+    """Streams of batches from one that gives a row an edge now and then to one that gives it more than it takes, with what one
+    prune selected at the head of a row: 1 to 15 others behind 1 to 64 of them, and more of either.  The memory has to survive
+    other prune kernels, deletion and compaction; the table is that of whole prunes after every call."""
+    n0, calls = 50_000, [2_048, 2_600, 3_100, 2_100, 2_300, 3_000]
+    x = torch.from_numpy(random_data(n0 + sum(calls), d, np.uint8, seed=R + d)).cuda()
+    gs = [jx.Index(d, jx.U8, R, 48, alpha, capacity=len(x), max_batch=len(x), batch_growth=1.0, flags=f) for f in (0, jx.FLAG_NO_INCR_PRUNE)]
+    at = 0
+    for step, m in enumerate([n0, *calls]):
+        if step == 2:  # rows are rewritten by the list-based kernels, then by the Gram-matrix ones
+            gs[0].set_flags(jx.FLAG_NO_GRAM)
+        if step == 3:
+            gs[0].set_flags(jx.FLAG_GRAM_U8)
+        if step == 4:
+            gs[0].set_flags(0)
+        if step == 5:
+            gone = torch.randperm(at, generator=torch.Generator().manual_seed(R))[:at // 40].int().cuda()
+            for g in gs:
+                g.delete(gone)
+                g.consolidate()
+        if step == 6:
+            for g in gs:
+                g.compact()
+        for g in gs:
+            g.insert(x[at:at + m])
+        at += m
+        a, b = (g.export_graph()[0] for g in gs)
+        assert torch.equal(a, b), (step, int((a != b).any(1).sum()))
+
+
 @pytest.mark.parametrize("L,logB", [(8, 24), (129, 23)])
 def test_batches_of_more_workgroups_than_one_launch_takes(jx, L, logB):
     """A launch has fewer than 2^32 threads: 2^24 workgroups of 256 (lists of at most 128) and 2^23 of 512 (longer ones) are more.
