@@ -5,10 +5,12 @@
 //     d(i,j) = G_ii + G_jj - 2 G_ij,   G = X X^T,
 // on the matrix cores, and every candidate vector is read exactly once.
 //   float32 : rows centred at the pruned vertex p (x_j - x_p: distances are translation invariant and the cancellation
-//             in G_ii + G_jj - 2 G_ij then involves local magnitudes only); G_jj is d(p,j) itself.  A centred value is
-//             the exact sum of three bfloat16 values (8 + 8 + 8 bits of its significand), and the six products of weight
-//             2^-16 and above go through v_mfma_f32_32x32x16_bf16: 192 cycles for 16 coordinates where
-//             v_mfma_f32_32x32x2f32 takes 512.  What is left out is below 2^-25 of a product.  Every 32 coordinates have a
+//             in G_ii + G_jj - 2 G_ij then involves local magnitudes only); G_jj is d(p,j) itself.  A centred value of
+//             2^-110 and more is the exact sum of three bfloat16 values (8 + 8 + 8 bits of its significand; of smaller ones what
+//             lies below 2^-134 is lost, and their squares are zero), and the six products of weight 2^-17 and above go
+//             through v_mfma_f32_32x32x16_bf16: 192 cycles for 16 coordinates where v_mfma_f32_32x32x2f32 takes 512.  The
+//             second part is at most 2^-8 of a value and the third 2^-17, so the two products of weight 2^-25 and the one
+//             behind them are left out, at most 2^-24 (1 + 2^-10) of a product.  Every 32 coordinates have a
 //             sum of their own, added to the total by the vector unit, so the result is nearer to the exact one than that
 //             of the float32 instruction: relative error of d(i,j) against 64 bits, root mean square / largest,
 //             d = 128 1.1e-7 / 4.7e-7 (float32 instruction 2.9e-7 / 1.5e-6), d = 960 1.4e-7 / 5.5e-7 (7.1e-7 / 2.9e-6).

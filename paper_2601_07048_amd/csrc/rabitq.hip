@@ -1,11 +1,13 @@
 // RaBitQ pipeline (Sec. 5.1): rotation GEMM on the matrix cores, encoder,
 // integer query records, exact re-rank.
 //
-//   rotate      out = (in - c) P^T   bfloat16 MFMA on three parts of each float32
-//               value, 128x128 tile per workgroup, 64x64 per wavefront, K staged
-//               through LDS in slabs of 32; the centroid is subtracted while staging.
-//   encode      one wavefront per vector: 1-bit codes via ballot, 4-bit codes
-//               with the max-abs grid scale; data_add, data_rescale in double.
+//   rotate      out = (in - c) P^T   queries and 1-bit codes: bfloat16 MFMA on three parts of
+//               each float32 value, 128x128 tile per workgroup; codes of more
+//               bits: float32 MFMA, 128x64.  K staged through LDS in slabs of
+//               32; the centroid is subtracted while staging.
+//   encode      one wavefront per vector: 1-bit codes via ballot, more bits with
+//               the max-abs grid scale, or a workgroup with the max-cosine one;
+//               data_add, data_rescale in double.
 //   query prep  one wavefront per query: min/max, B_q-bit integer query,
 //               nibble planes (4-bit codes) or bit planes (1-bit codes).
 //   rerank      one wavefront per query: exact float32 squared L2 of the first
@@ -26,7 +28,8 @@ typedef __bf16 rq_bf16x2 __attribute__((ext_vector_type(2)));
 #define GPIECE 576            // 32 rows x 16 operand bytes, padded: 64 bytes further on in the banks from piece to piece
 #define GBLOCK (12 * GPIECE)  // operand pieces of 32 rows and a slab: [step][part][half]
 
-// Four float32 values as three bfloat16 parts each, whose sum they are exactly (8 bits of the significand in each)
+// Four float32 values as three bfloat16 parts each, whose sum they are exactly (8 bits of the significand in each; values below
+// 2^-110 lose what lies below 2^-134)
 __device__ __forceinline__ void rotate_stage(uint8_t* at, float v0, float v1, float v2, float v3) {
 #pragma unroll
     for (int part = 0; part < 3; part++) {
@@ -55,11 +58,11 @@ __device__ __forceinline__ float4 rotate_load(const void* in_v, const size_t at)
 }
 
 // IN: storage type of the input rows (JX_F32, JX_F16, JX_U8); all three convert to float32 exactly.
-// Six products of the parts (those of weight 2^-16 and above) take 192 cycles for 16 coordinates where
-// v_mfma_f32_32x32x2_f32 takes 512; every 32 coordinates have a sum of their own, so the result is nearer to 64 bits than that
-// instruction's: error relative to the root mean square of a row, root mean
-// square / largest, d = 128 8.1e-8 / 7.1e-7 (2.0e-7 / 2.3e-6 before), d = 960 1.3e-7 / 2.1e-6 (5.6e-7 / 9.4e-6).  Values of 3.39e38 and more round to an
-// infinite part: elements that do not come out finite are summed again in plain float32.
+// Six products of the parts (those of weight 2^-17 and above; what is left out is at most 2^-24 of a product) take 192 cycles
+// for 16 coordinates where v_mfma_f32_32x32x2_f32 takes 512; every 32 coordinates have a sum of their own, so the result is
+// nearer to 64 bits than that instruction's: error relative to the root mean square of a row, root mean square / largest,
+// d = 128 8.1e-8 / 7.1e-7 (2.0e-7 / 2.3e-6 before), d = 960 1.3e-7 / 2.1e-6 (5.6e-7 / 9.4e-6).  Values of 3.39e38 and more
+// round to an infinite part: elements that do not come out finite are summed again in plain float32.
 // Bound: matrix instructions (1,536 cycles a slab and wavefront) and the vector instructions of the split (1,200), which
 // overlap in part.  10,000 x 960 226 -> 149 us, 5,000 x 1536 235 -> 145, 50,000 x 960 717.
 template <int IN>
