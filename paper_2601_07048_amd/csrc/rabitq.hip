@@ -173,28 +173,32 @@ __global__ void __launch_bounds__(256, 2) rotate_gemm_kernel(const void* __restr
 // The same by v_mfma_f32_32x32x2_f32, for codes of more than one bit.  Which grid point is nearest is often decided by the last
 // bits of the rotated vector: between the two forms 6e-6 of the 4-bit codes of a set differ and 2.1e-5 of the 8-bit codes, and a
 // vector whose best two grid scales are nearly equal gets another factor along with them.  So codes stay what they were for
-// indices that are filled over time.  128 x 64 tiles: 64 divides the dimensions in use, and 12,500 x 960 (a workspace's
-// worth) are 5.7 tiles a CU, where 128 x 128 made 3.1 and a last round that is nearly empty: 50,000 x 960
-// 1,089 -> 930 us.
-template <int IN>
+// indices that are filled over time.  Tiles of 128 rows and TN columns, each wavefront 64 x TN / 2 of them.
+// Bound: the float32 matrix instructions (512 cycles for 32 x 32 x 16).  A float4 of pb goes to LDS by its components: stored as a
+// whole the array stays in scratch memory, every slab waits for it, and 8,000 x 1536 take 369 us (328 with 64 columns, 311
+// with 128).
+template <int IN, int TN>
 __global__ void __launch_bounds__(256) rotate_f32_kernel(const void* __restrict__ in_v, long long n, int d,
                                                          const float* __restrict__ P, const float* __restrict__ c,
                                                          float* __restrict__ out) {
     __shared__ __align__(16) float As[GT][GLD];
-    __shared__ __align__(16) float Bs[GT / 2][GLD];
+    constexpr int NJ = TN / 64;  // tiles of 32 columns of a wavefront
+    __shared__ __align__(16) float Bs[TN][GLD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const long long m0 = (long long)blockIdx.y * GT;
-    const int n0 = blockIdx.x * (GT / 2);
-    f32x16 acc[2];
+    const int n0 = blockIdx.x * TN;
+    f32x16 acc[2][NJ];
 #pragma unroll
     for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int e = 0; e < 16; e++) acc[i][e] = 0.f;
+        for (int j = 0; j < NJ; j++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
 
     // a slab on its way in registers while the one before it is multiplied
     const int srow = tid >> 3, c4 = (tid & 7) * 4;
-    float4 pa[4], pb[2], pc;
+    float4 pa[4], pb[TN / 32], pc;
     auto fetch = [&](const int k0) __attribute__((always_inline)) {
         pc = *reinterpret_cast<const float4*>(c + k0 + c4);
 #pragma unroll
@@ -203,7 +207,7 @@ __global__ void __launch_bounds__(256) rotate_f32_kernel(const void* __restrict_
             pa[t] = rotate_load<IN>(in_v, (size_t)ra * d + k0 + c4);
         }
 #pragma unroll
-        for (int t = 0; t < 2; t++) {
+        for (int t = 0; t < TN / 32; t++) {
             const int rb = n0 + srow + 32 * t < d ? n0 + srow + 32 * t : d - 1;
             pb[t] = *reinterpret_cast<const float4*>(P + (size_t)rb * d + k0 + c4);
         }
@@ -214,33 +218,58 @@ __global__ void __launch_bounds__(256) rotate_f32_kernel(const void* __restrict_
         for (int t = 0; t < 4; t++)
             *reinterpret_cast<float4*>(&As[srow + 32 * t][c4]) = make_float4(pa[t].x - pc.x, pa[t].y - pc.y, pa[t].z - pc.z, pa[t].w - pc.w);
 #pragma unroll
-        for (int t = 0; t < 2; t++) *reinterpret_cast<float4*>(&Bs[srow + 32 * t][c4]) = pb[t];
+        for (int t = 0; t < TN / 32; t++) *reinterpret_cast<float4*>(&Bs[srow + 32 * t][c4]) = make_float4(pb[t].x, pb[t].y, pb[t].z, pb[t].w);
         __syncthreads();
         if (k0 + GK < d) fetch(k0 + GK);
 #pragma unroll
         for (int s8 = 0; s8 < GK / 8; s8++) {
-            const float4 bf = *reinterpret_cast<const float4*>(&Bs[wn * 32 + (lane & 31)][8 * s8 + 4 * (lane >> 5)]);
-            float4 af[2];
+            float4 af[2], bf[NJ];
+#pragma unroll
+            for (int s = 0; s < NJ; s++) bf[s] = *reinterpret_cast<const float4*>(&Bs[wn * (TN / 2) + s * 32 + (lane & 31)][8 * s8 + 4 * (lane >> 5)]);
 #pragma unroll
             for (int s = 0; s < 2; s++) af[s] = *reinterpret_cast<const float4*>(&As[wm * 64 + s * 32 + (lane & 31)][8 * s8 + 4 * (lane >> 5)]);
 #pragma unroll
-            for (int mi = 0; mi < 2; mi++) {
-                acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].x, bf.x, acc[mi], 0, 0, 0);
-                acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].y, bf.y, acc[mi], 0, 0, 0);
-                acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].z, bf.z, acc[mi], 0, 0, 0);
-                acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].w, bf.w, acc[mi], 0, 0, 0);
-            }
+            for (int mi = 0; mi < 2; mi++)
+#pragma unroll
+                for (int ni = 0; ni < NJ; ni++) {
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].x, bf[ni].x, acc[mi][ni], 0, 0, 0);
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].y, bf[ni].y, acc[mi][ni], 0, 0, 0);
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].z, bf[ni].z, acc[mi][ni], 0, 0, 0);
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi].w, bf[ni].w, acc[mi][ni], 0, 0, 0);
+                }
         }
         __syncthreads();
     }
 #pragma unroll
     for (int mi = 0; mi < 2; mi++)
 #pragma unroll
-        for (int e = 0; e < 16; e++) {
-            const long long row = m0 + wm * 64 + mi * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-            const int col = n0 + wn * 32 + (lane & 31);
-            if (row < n && col < d) out[(size_t)row * d + col] = acc[mi][e];
-        }
+        for (int ni = 0; ni < NJ; ni++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const long long row = m0 + wm * 64 + mi * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+                const int col = n0 + wn * (TN / 2) + ni * 32 + (lane & 31);
+                if (row < n && col < d) out[(size_t)row * d + col] = acc[mi][ni][e];
+            }
+}
+
+// Tiles of 64 columns or of 128: rounds of 256 workgroups, a round of wide tiles takes 1.9 times as long.  64 / 128 columns in us:
+// 12,500 x 960 207 / 261 (6 rounds / 4), 50,000 x 960 763 / 812 (23 / 13), 5,000 x 1536 220 / 215 (4 / 2), 8,000 x 1536 328 / 311
+// (6 / 3), 20,000 x 1536 790 / 797 (15 / 8), 50,000 x 1536 1,933 / 1,878 (37 / 19), 1,000 x 128 13 / 14 (1 / 1)
+static bool rotate_narrow(long long n, int d) {
+    const long long rows = (n + GT - 1) / GT;
+    const long long narrow = (rows * ((d + 63) / 64) + 255) / 256, wide = (rows * ((d + 127) / 128) + 255) / 256;
+    return narrow * 21 < wide * 40;
+}
+
+template <int TN>
+static void launch_rotate_f32(const void* in, int in_dtype, long long n, int d, const float* P, const float* c, float* out, hipStream_t st) {
+    const dim3 grid((unsigned)((d + TN - 1) / TN), (unsigned)((n + GT - 1) / GT));
+    if (in_dtype == JX_F16)
+        hipLaunchKernelGGL((rotate_f32_kernel<JX_F16, TN>), grid, dim3(256), 0, st, in, n, d, P, c, out);
+    else if (in_dtype == JX_U8)
+        hipLaunchKernelGGL((rotate_f32_kernel<JX_U8, TN>), grid, dim3(256), 0, st, in, n, d, P, c, out);
+    else
+        hipLaunchKernelGGL((rotate_f32_kernel<JX_F32, TN>), grid, dim3(256), 0, st, in, n, d, P, c, out);
 }
 
 hipError_t launch_rotate(const void* in, int in_dtype, long long n, int d, const float* P, const float* c, float* out, bool f32,
@@ -248,13 +277,8 @@ hipError_t launch_rotate(const void* in, int in_dtype, long long n, int d, const
     if (n <= 0) return hipSuccess;
     dim3 grid((unsigned)((d + GT - 1) / GT), (unsigned)((n + GT - 1) / GT));
     if (f32) {
-        grid.x = (unsigned)((d + GT / 2 - 1) / (GT / 2));
-        if (in_dtype == JX_F16)
-            hipLaunchKernelGGL(rotate_f32_kernel<JX_F16>, grid, dim3(256), 0, st, in, n, d, P, c, out);
-        else if (in_dtype == JX_U8)
-            hipLaunchKernelGGL(rotate_f32_kernel<JX_U8>, grid, dim3(256), 0, st, in, n, d, P, c, out);
-        else
-            hipLaunchKernelGGL(rotate_f32_kernel<JX_F32>, grid, dim3(256), 0, st, in, n, d, P, c, out);
+        if (rotate_narrow(n, d)) launch_rotate_f32<64>(in, in_dtype, n, d, P, c, out, st);
+        else launch_rotate_f32<128>(in, in_dtype, n, d, P, c, out, st);
         return hipGetLastError();
     }
     if (in_dtype == JX_F16)

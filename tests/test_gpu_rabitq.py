@@ -375,13 +375,13 @@ def test_quantize_end_to_end_other_widths(jx, bits, d, n):
 
 
 @pytest.mark.parametrize("dtype,bits", [(np.float32, 1), (np.float32, 4), (np.float16, 8), (np.uint8, 2)])
-@pytest.mark.parametrize("d,n", [(32, 1), (96, 127), (128, 128), (160, 129), (960, 300)])
+@pytest.mark.parametrize("d,n", [(32, 1), (96, 127), (128, 128), (160, 129), (960, 300), (960, 2945), (160, 16001)])
 def test_rotation_of_every_tile_edge(jx, d, n, dtype, bits):
-    """One row to just over a tile of them, dimensions that end inside one: products of three bfloat16 parts (queries, 1-bit codes)
+    """One row to just over a tile of them, dimensions that end inside one, tiles of 64 and (the last two) of 128 columns: products of three bfloat16 parts (queries, 1-bit codes)
     and the float32 form (codes of more bits) against double sums, 1e-6 of a row's norm (sums of 32 coordinates leave 2e-7)."""
     x = random_data(n, d, np.uint8 if dtype == np.uint8 else np.float32, seed=d + n).astype(dtype)
     P = datagen.random_orthogonal(d, d).astype(np.float32)
-    g = jx.Index(d, jx_dtype(jx, x), 8, 16, 1.2, capacity=max(n, 16), max_batch=1024, quant_bits=bits)
+    g = jx.Index(d, jx_dtype(jx, x), 8, 16, 1.2, capacity=max(n, 16), max_batch=max(n, 1024), quant_bits=bits)
     g.insert(dev(x))
     g.quantize(bits, dev(P), query_bits=4)
     x = x.astype(np.float32)
