@@ -199,5 +199,4 @@ def test_one_matrix_instruction(jx):
             if columns == 32:
                 bound += 8 * 2.0 ** -24 * np.maximum(np.abs(first.sum(2)) + bound, np.abs(products[:, :, 16:]).max(2))
             off = np.abs(got - both.sum(2))
-            print(spread, scale, columns, (off / np.maximum(bound, 1e-300)).max())
             assert (off <= bound + 2.0 ** -149).all()
