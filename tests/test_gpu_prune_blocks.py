@@ -152,7 +152,7 @@ def test_many_edges_u8(jx, d):
 def test_rows_that_remember_their_last_prune(jx, d, R, alpha):
     """Streams of batches from one that gives a row an edge now and then to one that gives it more than it takes, with what one
     prune selected at the head of a row: 1 to 15 others behind 1 to 64 of them, and more of either.  The memory has to survive
-    other prune kernels, deletion and compaction; the table is that of whole prunes after every call."""
+    other prune kernels, import, deletion and compaction; the table is that of whole prunes after every call."""
     n0, calls = 50_000, [2_048, 2_600, 3_100, 2_100, 2_300, 3_000]
     x = torch.from_numpy(random_data(n0 + sum(calls), d, np.uint8, seed=R + d)).cuda()
     gs = [jx.Index(d, jx.U8, R, 48, alpha, capacity=len(x), max_batch=len(x), batch_growth=1.0, flags=f) for f in (0, jx.FLAG_NO_INCR_PRUNE)]
@@ -162,8 +162,14 @@ def test_rows_that_remember_their_last_prune(jx, d, R, alpha):
             gs[0].set_flags(jx.FLAG_NO_GRAM)
         if step == 3:
             gs[0].set_flags(jx.FLAG_GRAM_U8)
-        if step == 4:
+        if step == 4:  # the same graph from outside, its rows in another order: nothing is known about them
             gs[0].set_flags(0)
+            adj, deg = gs[1].export_graph()
+            place = torch.arange(R, device="cuda")
+            turned = adj.gather(1, (deg.long()[:, None] - 1 - place).clamp(min=0))
+            turned[place >= deg.long()[:, None]] = -1
+            for g in gs:
+                g.import_graph(x[:at], turned, g.size()[1])
         if step == 5:
             gone = torch.randperm(at, generator=torch.Generator().manual_seed(R))[:at // 40].int().cuda()
             for g in gs:
