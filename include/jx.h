@@ -132,7 +132,7 @@ typedef struct {
     uint64_t hops;         /* expansions (adjacency rows read) */
     uint64_t dist_evals;   /* distance evaluations in beamSearch */
     uint64_t adj_bytes;    /* hops * 4R */
-    uint64_t vec_bytes;    /* dist_evals * bytes fetched per evaluation */
+    uint64_t vec_bytes;    /* dist_evals * bytes of a record (beam_search_sketch_kernel fetches less) */
     uint64_t rerank_bytes; /* exact re-rank reads */
     /* elapsed time of each stage of the call, from HIP events recorded on the
      * caller's stream around the stage's launches (summed over query slices) */
@@ -142,7 +142,8 @@ typedef struct {
      * codes, 4 binary16), lanes per record, 16-byte chunks per lane, frontier registers per lane (64 entries
      * each), query bits, form (0 general, 1 tag table and R <= 64, 2 the same with more records in flight for small
      * batches); "beam_search_pair_kernel<...>" = two expansions per round; "beam_search_ahead_kernel<...>" = a team of
-     * wavefronts per query (small batches, long records) */
+     * wavefronts per query (small batches, long records); "beam_search_sketch_kernel<T,CPL,NREG,...>" = float32 vectors
+     * of more than 128 dimensions, byte copies read first (larger batches and indices) */
     char beam_kernel[96];
 } jx_stats;
 

@@ -29,6 +29,8 @@ hipError_t launch_beam_search(int kind, int qbits, const BeamArgs& a, hipStream_
     bool done = false;
     const hipError_t e = launch_beam_ahead(kind, qbits, a, st, kernel_name, &done);  // small batches
     if (e != hipSuccess || done) return e;
+    const hipError_t es = launch_beam_sketch(kind, a, st, kernel_name, &done);
+    if (es != hipSuccess || done) return es;
     if (a.vis_cap) return launch_beam_visited(kind, a, st, kernel_name);
     if (a.flags & (JX_FLAG_TILED_LOADS | JX_FLAG_QPW_2 | JX_FLAG_QPW_4 | JX_FLAG_WAVES_2 | JX_FLAG_WAVES_4))
         return launch_beam_variant(kind, a, st, kernel_name);

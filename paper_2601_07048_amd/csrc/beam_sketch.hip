@@ -1,0 +1,408 @@
+// beamSearch of float32 vectors through byte copies ("sketches") of them.
+//
+// A search evaluates some thirty neighbours per expansion, and late in it three or four of them enter the frontier: of 3,967
+// evaluations of a d = 960 search at L = 128 on 20,000 points 293 do, and 158 more come before the frontier is full.  The
+// others have to be shown to be farther than the worst entry, for which a quarter of the bytes will do: next to each vector
+// x stands a record x' = m + s c with 8-bit codes c and e >= |x - x'|.  From |q - x| >= |q' - x'| - e - eq a neighbour whose
+// bound lies above the worst entry's distance cannot enter (a frontier changes by keys below the worst one only), and is
+// left out; the rest, 503 of 3,967 above, is evaluated on the vectors by eval_batch as in beam_search_kernel.  Frontier
+// sequence, results, expansion lists and counters are that kernel's, bit for bit, whatever the codes are worth: a loose
+// bound costs evaluations, never an entry.
+//
+// Bound: the gather.  Why matrix instructions: the query stands as 16-bit integers v = 256 h + l in rows of operand A (h
+// and l in turn, so that every lane group receives both sums), 16 neighbours' codes are operand B as they are loaded, and
+// <c, h>, <c, l> are exact integers: no conversion, no reduction, one instruction per 1 KB of codes, where the float form
+// takes eight vector instructions per chunk and six reduction steps per neighbour.
+// Measured: search of a 20,000 x 960 build 31.3 -> 15.7 ms; 30,000 x 960, 2,500 queries, L = 16 / 64 / 128 / 200 852 / 1,658 /
+// 2,984 / 5,000 -> 336 / 727 / 1,105 / 2,185 us; 15,000 x 1536 1,567 / 4,331 / 7,133 / 9,539 -> 580 / 1,379 / 2,458 / 4,076.
+#include <stdio.h>
+#include "beam_kernels.h"
+
+namespace jx {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// Roundings of the bound.  With X = |x'| + 2 |m| sqrt(d) and Y = |q'|, every sum below errs by less than 4e-6 (X^2 + Y^2)
+// (36 float32 roundings of the largest sums, 2^-24 each, and a few of their products); the record carries |x'|^2 - 8e-6 X^2
+// and the query |q'|^2 - 8e-6 Y^2.  SKETCH_REL covers the roundings of the float32 distance itself (24 + 6 + 3 of them, all
+// terms positive) and of the bound's last steps, SKETCH_ABS subnormal squares.
+#define SKETCH_SLACK 8e-6f
+#define SKETCH_REL 2e-5f
+#define SKETCH_ABS 1e-30f
+// coordinates beyond this have no sketch: squares of 1,536 of them stay finite
+#define SKETCH_MAX 1e17f
+
+// record: codes (d bytes, zeros up to a multiple of 16), then {|x'|^2 - slack, m, s, e}
+// One wavefront per vector; e = inf where the vector has no sketch (then the bound never holds).
+__global__ void __launch_bounds__(256) sketch_kernel(const float* x, long long n, int d, uint8_t* sk, int stride) {
+    const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= n) return;
+    const int lane = lane_id();
+    const float* v = x + (size_t)i * d;
+    const int nch = (d + 15) / 16;
+    uint8_t* rec = sk + (size_t)i * stride;
+    float lo = __builtin_inff(), hi = -__builtin_inff();
+    bool ok = true;
+    for (int c = lane; c < d / 4; c += 64) {
+        const float4 w = reinterpret_cast<const float4*>(v)[c];
+        const float mx = fmaxf(fmaxf(w.x, w.y), fmaxf(w.z, w.w)), mn = fminf(fminf(w.x, w.y), fminf(w.z, w.w));
+        // fmaxf drops a NaN; the sum of absolute values does not
+        ok = ok && fabsf(w.x) + fabsf(w.y) + fabsf(w.z) + fabsf(w.w) < 4.f * SKETCH_MAX;
+        hi = fmaxf(hi, mx);
+        lo = fminf(lo, mn);
+    }
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) {
+        hi = fmaxf(hi, shfl_xor(hi, k));
+        lo = fminf(lo, shfl_xor(lo, k));
+    }
+    ok = ballot(!ok) == 0ull && hi <= SKETCH_MAX && lo >= -SKETCH_MAX;
+    const float m = ok ? 0.5f * (lo + hi) : 0.f;
+    const float s = ok ? (hi - lo) * (1.f / 255.f) : 0.f;
+    const float inv = s > 1e-30f ? 1.f / s : 0.f;  // (a range of no width, or one that no bound will reach: all codes 0)
+    float err = 0.f, nn = 0.f;
+    for (int c = lane; c < nch * 4; c += 64) {
+        uint32_t word = 0;
+        if (c < d / 4 && ok) {
+            const float4 w = reinterpret_cast<const float4*>(v)[c];
+            const float f[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const float code = fminf(fmaxf(rintf((f[k] - m) * inv), -128.f), 127.f);
+                const float r = fmaf(-s, code, f[k] - m), y = fmaf(s, code, m);
+                err = fmaf(r, r, err);
+                nn = fmaf(y, y, nn);
+                word |= ((uint32_t)(int)code & 255u) << (8 * k);
+            }
+        }
+        reinterpret_cast<uint32_t*>(rec)[c] = word;
+    }
+    err = group_sum<64>(err);
+    nn = group_sum<64>(nn);
+    if (lane == 0) {
+        const float X = sqrtf(nn) + 2.f * fabsf(m) * sqrtf((float)d);
+        // the residuals carry a rounding of f - m (2^-24 of 128 s at most) each, their sum some thirty
+        const float e = sqrtf(err) * 1.001f + s * 2e-5f * sqrtf((float)d) + 1e-20f;
+        float4 meta = make_float4(nn - SKETCH_SLACK * X * X, m, s, ok ? e : __builtin_inff());
+        *reinterpret_cast<float4*>(rec + (size_t)nch * 16) = meta;
+    }
+}
+
+hipError_t launch_sketch(const float* x, long long n, int d, uint8_t* sk, int stride, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(sketch_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, x, n, d, sk, stride);
+    return hipGetLastError();
+}
+
+// <c, l> and <c, h> of neighbours first + 16 p .. (p < NP) in the lanes of their numbers; KU loads of each in flight.
+// lq: this lane's part of operand A (rows l, h, l, h, ...; columns 16 (lane / 16) .. of each 64).  A lane group reads up to 48
+// bytes behind the codes of a record where d is no multiple of 64 (its own meta chunk or the next record, the arena's next
+// buffer behind the last one): the query is zero there.
+template <int NP, int KU>
+__device__ __forceinline__ void sketch_dots(const uint8_t* sk, const uint32_t stride, const int kb, const uint8_t* lq,
+                                            const uint32_t* cand_id, const int first, const int n, const int lane, int& il, int& ih) {
+    const uint8_t* rec[NP];
+    v4i acc[NP];
+#pragma unroll
+    for (int p = 0; p < NP; p++) {
+        const int c = first + p * 16 + (lane & 15);
+        rec[p] = sk + (size_t)cand_id[c < n ? c : n - 1] * stride + (lane >> 4) * 16;
+        acc[p] = v4i{0, 0, 0, 0};
+    }
+    for (int k0 = 0; k0 < kb; k0 += KU) {
+        v4i b[NP][KU];
+#pragma unroll
+        for (int p = 0; p < NP; p++)
+            if (first + p * 16 < n) {
+#pragma unroll
+                for (int u = 0; u < KU; u++)
+                    if (k0 + u < kb) b[p][u] = *reinterpret_cast<const v4i*>(rec[p] + (size_t)(k0 + u) * 64);
+            }
+#pragma unroll
+        for (int u = 0; u < KU; u++)
+            if (k0 + u < kb) {
+                const v4i aq = *reinterpret_cast<const v4i*>(lq + (size_t)(k0 + u) * 64);
+#pragma unroll
+                for (int p = 0; p < NP; p++)
+                    if (first + p * 16 < n) acc[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aq, b[p][u], acc[p], 0, 0, 0);
+            }
+    }
+#pragma unroll
+    for (int p = 0; p < NP; p++)
+        if ((lane >> 4) * 16 == first + p * 16) {
+            il = acc[p][0];
+            ih = acc[p][1];
+        }
+}
+
+// bytes of one query plane in LDS (a bank group apart from the other)
+__host__ __device__ inline int sketch_plane(int nch_codes) { return (nch_codes + 3) / 4 * 64 + 16; }
+
+// Tag table and rows of at most 64 entries only (the launcher checks).  KU: 64-byte pieces of two tiles of 16 neighbours in
+// flight, as the registers allow for four wavefronts per SIMD (codes of at most 256 bytes: KU = 4; 40,000 x 200 built with
+// KU = 4 / five wavefronts, spilled / four tiles 16.2 / 18.5 / 16.6 ms), three (8) or two (16: batches that fill no more).
+template <int T, int CPL, int NREG, bool VIS, int KU>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4 ? 4 : (KU == 8 ? 3 : 2), 8))) beam_search_sketch_kernel(BeamArgs a) {
+    constexpr int G = 64 / T;
+    constexpr int U0 = CPL == 4 ? 4 : 8 / CPL;
+    constexpr int U = U0 < (64 / G) ? U0 : (64 / G);
+    constexpr int FCAP = mirror_entries<NREG>();
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = lane_id();
+    const int g = lane / T, lig = lane % T;
+    const int64_t qi = blockIdx.x;
+    if (qi >= a.nq) return;
+
+    const int tag_bits = a.tag_bits;
+    const uint32_t id_mask = (1u << (tag_bits + 30 - __builtin_clz((uint32_t)a.hash_slots))) - 1u;  // hash_slots / 2 sets
+    const int plane = sketch_plane(a.sk_nch), kb = (a.sk_nch + 3) / 4;
+    uint8_t* const qpl = smem;
+    uint64_t* fr = reinterpret_cast<uint64_t*>(smem + 2 * plane);
+    uint64_t* cand_key = fr + FCAP;
+    uint32_t* cand_id = reinterpret_cast<uint32_t*>(cand_key + 64);
+    uint32_t* tab = cand_id + 64;
+    uint64_t* vis = reinterpret_cast<uint64_t*>(tab + a.hash_slots / 2);
+
+    for (int i = lane; i < a.hash_slots / 2; i += 64) tab[i] = JX_NONE_ID;
+    for (int i = lane; i < FCAP; i += 64) fr[i] = JX_EMPTY_KEY;
+
+    const int64_t qrec = qi + (qi >= a.q_skip ? 1 : 0);
+    QueryRegs<K_F32, CPL, 0> q;
+    load_query<K_F32, T, CPL, 0>(q, a.ds, qrec, lig);
+
+    // ---- the query in 16 bits: q' = qs v, |q - q'| <= qe
+    float qs, qe, qn;
+    int vsum = 0;
+    bool use;
+    {
+        const float4* qv = reinterpret_cast<const float4*>(a.ds.qrecs + qrec * a.ds.qrec_stride);
+        float mx = 0.f;
+        bool ok = true;
+        for (int c = lane; c < a.ds.nch; c += 64) {
+            const float4 w = qv[c];
+            ok = ok && fabsf(w.x) + fabsf(w.y) + fabsf(w.z) + fabsf(w.w) < 4.f * SKETCH_MAX;  // false for a NaN
+            mx = fmaxf(mx, fmaxf(fmaxf(fabsf(w.x), fabsf(w.y)), fmaxf(fabsf(w.z), fabsf(w.w))));
+        }
+#pragma unroll
+        for (int k = 1; k < 64; k <<= 1) mx = fmaxf(mx, shfl_xor(mx, k));
+        use = ballot(!ok) == 0ull && mx <= SKETCH_MAX;
+        qs = mx * (1.f / 32639.f);
+        const float inv = qs > 1e-30f ? 1.f / qs : 0.f;
+        float err = 0.f, nn = 0.f;
+        for (int c = lane; c < kb * 16; c += 64) {
+            uint32_t wl = 0, wh = 0;
+            if (c < a.ds.nch && use) {
+                const float4 w = qv[c];
+                const float f[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const float code = fminf(fmaxf(rintf(f[k] * inv), -32639.f), 32639.f);
+                    const float r = fmaf(-qs, code, f[k]), y = qs * code;
+                    err = fmaf(r, r, err);
+                    nn = fmaf(y, y, nn);
+                    const int v = (int)code, h = (v + 128) >> 8;  // v = 256 h + l, both in [-128, 127]
+                    vsum += v;
+                    wh |= ((uint32_t)h & 255u) << (8 * k);
+                    wl |= ((uint32_t)(v - 256 * h) & 255u) << (8 * k);
+                }
+            }
+            reinterpret_cast<uint32_t*>(qpl)[c] = wl;
+            reinterpret_cast<uint32_t*>(qpl + plane)[c] = wh;
+        }
+        err = group_sum<64>(err);
+        nn = group_sum<64>(nn);
+        vsum = group_sum<64>(vsum);
+        qe = sqrtf(err) * 1.001f + 1e-20f;
+        qn = nn - SKETCH_SLACK * nn;
+    }
+    const float qsum = qs * (float)vsum;
+    const uint8_t* lq = qpl + (lane & 1) * plane + (lane >> 4) * 16;
+
+    uint64_t fk[NREG];
+#pragma unroll
+    for (int r = 0; r < NREG; r++) fk[r] = JX_EMPTY_KEY;
+    int count = 0;
+    uint64_t worst = JX_EMPTY_KEY;  // see frontier_merge
+    const int L = a.L;
+    const bool full = a.ds.nch == T * CPL;
+    uint32_t hops = 0, evals = 0;
+    int tried = 0, kept = 0;  // by sketches
+
+    if (lane == 0) {  // seed: the entry vertex
+        cand_id[0] = a.entry;
+        const uint32_t h = (a.entry * 0x9E3779B1u) & id_mask;
+        tab[h >> tag_bits] = 0xFFFF0000u | (h & ((1u << tag_bits) - 1u));
+    }
+    wave_sync();
+    eval_batch<K_F32, T, CPL, 0, 1>(q, a.ds, 0, 1, cand_id, cand_key, g, lig);
+    wave_sync();
+    if (lane == 0) {
+        fk[0] = cand_key[0];
+        fr[0] = cand_key[0];
+    }
+    wave_sync();
+    count = 1;
+    evals = 1;
+
+    // the loop of beam_search_body's MODE 1, with step 4a
+    const uint32_t* my_adj = a.adj + (lane < a.R ? lane : 0);
+    uint32_t row_u = a.entry, row_v = my_adj[(size_t)a.entry * (uint32_t)a.R];
+    for (;;) {
+        // ---- 1. the two closest unexpanded entries
+        uint64_t ukey = 0;
+        uint32_t u2 = 0;
+        int sel_r = -1, sel_lane = 0;
+        bool have2 = false;
+#pragma unroll
+        for (int r = 0; r < NREG; r++) {
+            uint64_t m = ballot((fk[r] & 1ull) == 0ull);
+            if (sel_r < 0 && m != 0ull) {
+                sel_r = r;
+                sel_lane = __builtin_ctzll(m);
+                ukey = readlane64(fk[r], sel_lane);
+                m &= m - 1ull;
+            }
+            if (!have2 && m != 0ull) {
+                have2 = true;
+                u2 = readlane32((uint32_t)fk[r], __builtin_ctzll(m)) >> 1;
+            }
+        }
+        if (sel_r < 0) break;
+        const uint32_t u = key_id(ukey);
+#pragma unroll
+        for (int r = 0; r < NREG; r++) fk[r] |= (r == sel_r && lane == sel_lane) ? 1ull : 0ull;
+        if constexpr (VIS) {
+            if (lane == 0 && hops < (uint32_t)a.vis_cap) vis[hops] = ukey | 1ull;
+        }
+        hops++;
+        // ---- 2. adjacency row
+        if (row_u != u) row_v = my_adj[(size_t)u * (uint32_t)a.R];
+        const uint32_t v = lane < a.R ? row_v : JX_NONE_ID;
+        // ---- 3. visited filter
+        const uint32_t h = (v * 0x9E3779B1u) & id_mask;
+        const uint32_t tag = h & ((1u << tag_bits) - 1u);
+        const uint32_t w = tab[h >> tag_bits];
+        row_u = have2 ? u2 : u;
+        row_v = my_adj[(size_t)row_u * (uint32_t)a.R];
+        const bool is_new = v != JX_NONE_ID && (w & 0xFFFFu) != tag && (w >> 16) != tag;
+        const uint64_t nm = ballot(is_new);
+        if (nm == 0ull) continue;
+        int n_new = __builtin_popcountll(nm);
+        if (is_new) {
+            tab[h >> tag_bits] = (w << 16) | tag;
+            cand_id[prefix_count(nm)] = v;
+        }
+        wave_sync();
+        evals += n_new;
+        // ---- 4a. which of them may enter a full frontier
+        if (use && worst != JX_EMPTY_KEY) {
+            const uint32_t id = cand_id[lane < n_new ? lane : n_new - 1];
+            const float4 meta = *reinterpret_cast<const float4*>(a.sk + (size_t)id * (uint32_t)a.sk_stride + (size_t)a.sk_nch * 16);
+            int il = 0, ih = 0;
+            for (int f = 0; f < n_new; f += 32) sketch_dots<2, KU>(a.sk, (uint32_t)a.sk_stride, kb, lq, cand_id, f, n_new, lane, il, ih);
+            const float dot = fmaf(256.f, (float)ih, (float)il);
+            const float t = fmaf(meta.z * dot, qs, meta.y * qsum);  // <x', q'>
+            const float d2 = fmaf(-2.f, t, meta.x + qn);
+            const float far = sqrtf(ordered_to_f32(key_dist(worst))) + meta.w + qe;
+            const bool keep = lane < n_new && !(d2 > fmaf(far * far, 1.f + SKETCH_REL, SKETCH_ABS));
+            const uint64_t km = ballot(keep);
+            const int nk = __builtin_popcountll(km);
+            tried += n_new;
+            kept += nk;
+            // vectors that their codes say little about (far from the origin, say): this query goes on without
+            use = kept * 4 <= tried * 3 + 256;
+            if (nk == 0) continue;
+            if (nk < n_new) {
+                wave_sync();
+                if (keep) cand_id[prefix_count(km)] = id;
+                n_new = nk;
+                wave_sync();
+            }
+        }
+        // ---- 4./5. gather + distances
+        if (full) {
+            for (int s0 = 0; s0 < n_new; s0 += G * U)
+                eval_batch<K_F32, T, CPL, 0, U, true>(q, a.ds, s0, n_new, cand_id, cand_key, g, lig);
+        } else {
+            for (int s0 = 0; s0 < n_new; s0 += G * U)
+                eval_batch<K_F32, T, CPL, 0, U, false>(q, a.ds, s0, n_new, cand_id, cand_key, g, lig);
+        }
+        wave_sync();
+        const uint64_t ck = lane < n_new ? cand_key[lane] : JX_EMPTY_KEY;
+        wave_sync();
+        // ---- 6. merge into the sorted frontier
+        frontier_merge<NREG>(fk, fr, count, worst, L, ck, n_new, lane);
+    }
+
+    if constexpr (VIS) {
+        write_visited<K_F32>(a, qi, vis, (int)(hops < (uint32_t)a.vis_cap ? hops : (uint32_t)a.vis_cap), lane);
+        if (a.stats && lane == 0) {
+            unsigned long long* sp = a.stats + (size_t)(qi & 63) * 16;
+            atomicAdd(&sp[0], (unsigned long long)hops);
+            atomicAdd(&sp[1], (unsigned long long)evals);
+        }
+    } else {
+        write_results<K_F32, NREG>(a, qi, fk, count, lane, hops, evals);
+    }
+}
+
+// ------------------------------------------------------------------ launch
+
+template <int T, int CPL>
+static hipError_t launch_sketch_shape(BeamArgs a, hipStream_t st, char* name) {
+    const int nreg = a.L <= 64 ? 1 : (a.L <= 128 ? 2 : 4);
+    // what the visited table forgets costs a quarter of the bytes here, so a smaller one than the vectors ask for, and more
+    // wavefronts by LDS (build of 20,000 x 960, L = 128: 16 / 8 / 4 KB 33.2 / 32.3 / 33.9 ms; 1,500 queries at L = 200 2.19 /
+    // 1.99 / 2.19 ms, but 5,000 3.52 / 3.68 / 4.00)
+    while (a.hash_slots > (a.L <= 128 ? 4096 : 8192) && a.tag_bits < 15) {
+        a.hash_slots /= 2;
+        a.tag_bits++;
+    }
+    const size_t sh0 = 2 * (size_t)sketch_plane(a.sk_nch) + 64 * 8 + 64 * 4 + (size_t)a.hash_slots * 2 + (size_t)a.vis_cap * 8;
+    constexpr bool SHORT = T * CPL <= 64;
+    // two wavefronts per SIMD are 2,048 queries: 15,000 x 1536 at L = 200, 700 / 1,500 / 2,000 queries 1,681 / 2,152 / 3,741 ->
+    // 1,505 / 2,046 / 3,478 us, 30,000 x 960 at L = 64 447 / 561 / 649 -> 422 / 541 / 632
+    const bool wide = !SHORT && a.sk_nch > 32 && a.nq <= 2048;
+    if (name) snprintf(name, 96, "beam_search_sketch_kernel<%d,%d,%d,%d,%d>", T, CPL, nreg, a.vis_cap ? 1 : 0, SHORT ? 4 : (wide ? 16 : 8));
+#define JX_LAUNCH(NR, VISIBLE)                                                                                          \
+    {                                                                                                                   \
+        const size_t sh = sh0 + mirror_entries<NR>() * 8;                                                               \
+        auto kern = SHORT ? beam_search_sketch_kernel<T, CPL, NR, VISIBLE, SHORT ? 4 : 8>                               \
+                          : (wide ? beam_search_sketch_kernel<T, CPL, NR, VISIBLE, SHORT ? 4 : 16>                      \
+                                  : beam_search_sketch_kernel<T, CPL, NR, VISIBLE, SHORT ? 4 : 8>);                     \
+        hipLaunchKernelGGL(kern, dim3((unsigned)a.nq), dim3(64), sh, st, a);                                            \
+        return hipGetLastError();                                                                                       \
+    }
+    if (a.vis_cap) {
+        if constexpr (SHORT || CPL == 2) {
+            return hipErrorInvalidValue;  // no expansion lists of such vectors (visited_list_offered)
+        } else {
+            if (nreg == 1) JX_LAUNCH(1, true)
+            JX_LAUNCH(2, true)
+        }
+    }
+    if (nreg == 1) JX_LAUNCH(1, false)
+    if (nreg == 2) JX_LAUNCH(2, false)
+    if constexpr (!SHORT) JX_LAUNCH(4, false)
+    return hipErrorInvalidValue;
+#undef JX_LAUNCH
+}
+
+hipError_t launch_beam_sketch(int kind, const BeamArgs& a, hipStream_t st, char* name, bool* done) {
+    *done = false;
+    const uint32_t prune_flags = JX_FLAG_NO_INCR_PRUNE | JX_FLAG_NO_GRAM | JX_FLAG_GRAM_U8;
+    if (kind != K_F32 || !a.sk || a.tag_bits == 0 || a.R > 64 || a.L > 256 || (a.flags & ~prune_flags)) return hipSuccess;
+    const int nch = a.ds.nch;
+    if (a.vis_cap && (a.L > 128 || nch <= 128)) return hipSuccess;
+    // short vectors and wide frontiers: 60,000 x 200 at L = 128 / 200, 1,000 queries 439 / 596 -> 405 / 588 us, 3,500 473 / 701 ->
+    // 429 / 863
+    *done = true;
+    if (nch <= 64 && a.L <= 128) return launch_sketch_shape<32, 2>(a, st, name);
+    if (nch > 64 && nch <= 128) return launch_sketch_shape<64, 2>(a, st, name);
+    if (nch > 128 && nch <= 256) return launch_sketch_shape<64, 4>(a, st, name);
+    if (nch > 256 && nch <= 384) return launch_sketch_shape<64, 6>(a, st, name);
+    *done = false;
+    return hipSuccess;
+}
+
+}  // namespace jx

@@ -38,8 +38,8 @@ int fail(int code, const char* fmt, ...) {
 inline int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
 struct Layout {
-    int64_t vecs, adj, codes, P, centroid, stats, stripes, deleted, clean, work, work_bytes, total;
-    int vec_bytes, code_bytes, meta_chunk, code_stride, plane_chunks, plane_shift;
+    int64_t vecs, adj, codes, sketch, P, centroid, stats, stripes, deleted, clean, work, work_bytes, total;
+    int vec_bytes, code_bytes, meta_chunk, code_stride, sk_stride, plane_chunks, plane_shift;
 };
 
 int elem_bytes(int dtype) { return dtype == JX_U8 ? 1 : (dtype == JX_F16 ? 2 : 4); }
@@ -128,6 +128,14 @@ int64_t query_work(const jx_params* p, int64_t B, int plane_chunks, QueryWork* w
     return off;
 }
 
+// Bytes between the byte copies of float32 vectors (beam_sketch.hip), 0 = none: not of vectors of at most 512 bytes (300,000 x
+// 128, L = 16: 10,000 queries 324 -> 272 us, but L = 128 1,033 -> 1,064 and 1,000 queries 99 -> 109), nor of stores that leave
+// little of the card's memory
+int sketch_stride(const jx_params* p) {
+    if (p->dtype != JX_F32 || p->dim <= 128 || (int64_t)p->capacity * p->dim * 4 > (128ll << 30)) return 0;
+    return ((p->dim + 15) / 16 * 16 + 16 + 63) / 64 * 64;
+}
+
 void layout(const jx_params* p, Layout* L) {
     L->vec_bytes = p->dim * elem_bytes(p->dtype);
     // 1- and 4-bit codes are one plane; 2- and 8-bit codes are stored as a low and a high plane of the 1-bit /
@@ -147,6 +155,9 @@ void layout(const jx_params* p, Layout* L) {
     off += align256((int64_t)p->capacity * p->R * 4);
     L->codes = off;
     off += align256((int64_t)p->capacity * L->code_stride);
+    L->sk_stride = sketch_stride(p);
+    L->sketch = off;
+    off += align256((int64_t)p->capacity * L->sk_stride);
     L->P = off;
     off += align256(p->quant_bits ? (int64_t)p->dim * p->dim * 4 : 0);
     L->centroid = off;
@@ -205,6 +216,13 @@ bool merges_by_memory(const jx_index* idx, int64_t linked, int64_t B) {
 hipError_t launch_tiled(const jx::BfArgs& a, hipStream_t st) {
     snprintf(g_bf_kernel, sizeof g_bf_kernel, "bruteforce_tile_kernel<%d> nsplit=%d", a.dtype, a.nsplit);
     return jx::launch_bruteforce(a, st);
+}
+
+// byte copies of vectors [first, first + count) of the store
+hipError_t sketch_range(const jx_index* idx, int64_t first, int64_t count, hipStream_t st) {
+    if (!idx->d_sketch) return hipSuccess;
+    return jx::launch_sketch((const float*)(idx->d_vecs + (size_t)first * idx->vec_bytes), count, idx->p.dim,
+                             idx->d_sketch + (size_t)first * idx->sk_stride, idx->sk_stride, st);
 }
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
@@ -321,6 +339,8 @@ int jx_create(const jx_params* p, void* d_arena, int64_t arena_bytes, void* stre
     x->d_vecs = x->d_arena + L.vecs;
     x->d_adj = (uint32_t*)(x->d_arena + L.adj);
     x->d_codes = x->d_arena + L.codes;
+    x->d_sketch = L.sk_stride ? x->d_arena + L.sketch : nullptr;
+    x->sk_stride = L.sk_stride;
     x->d_P = (float*)(x->d_arena + L.P);
     x->d_centroid = (float*)(x->d_arena + L.centroid);
     x->d_stats = (unsigned long long*)(x->d_arena + L.stats);
@@ -383,6 +403,7 @@ int jx_import_graph(jx_index* idx, const void* d_vecs, int64_t n, const uint32_t
         if (bad) return fail(JX_EINVAL, "%u adjacency entries are out of range, follow a padding entry or repeat an id of their row", bad);
     }
     JX_HIP(hipMemcpyAsync(idx->d_vecs, d_vecs, (size_t)n * idx->vec_bytes, hipMemcpyDeviceToDevice, st));
+    JX_HIP(sketch_range(idx, 0, n, st));
     JX_HIP(hipMemcpyAsync(idx->d_adj, d_adj, (size_t)n * idx->p.R * 4, hipMemcpyDeviceToDevice, st));
     if (idx->d_clean && idx->any_clean) JX_HIP(jx::launch_fill_u32((uint32_t*)idx->d_clean, (idx->p.capacity + 3) / 4, 0u, st));  // nothing is known about foreign rows
     idx->any_clean = 0;
@@ -446,6 +467,19 @@ static void fill_exact_src(const jx_index* idx, jx::DistSrc* ds, const void* que
     ds->qrec_stride = idx->vec_bytes;
 }
 
+// Byte copies are read where the n vectors a search may meet take this much.  Below, the caches hold what is gathered, and the
+// copies only make an expansion's chain longer.  Insertion, whole builds with the line at none / 16 / 4 / 2 MiB: 20,000 x 960
+// 47.6 / 33.0 / 31.9 / 31.9 ms, 5,000 x 960 14.4 / 14.4 / 13.2 / 13.2, 40,000 x 200 21.2 / 19.1 / 16.8 / 16.5; vectors of six
+// chunks per lane, whose own chain keeps more in flight, later: 5,000 x 1536 17.3 / 16.9 / 17.7 / 18.1.  Searches of 1,000 /
+// 2,500 queries, L = 128: 3,000 x 512 (6 MB) 516 -> 344, 1,033 -> 404 us; 1,000 x 960 376 -> 390, 743 -> 454; 2,000 x 1536
+// (12 MB) 664 -> 749, 2,117 -> 957
+static void fill_sketch(const jx_index* idx, int64_t n, bool insertion, jx::BeamArgs* a) {
+    const int64_t least = idx->vec_bytes <= 2048 || (insertion && idx->vec_bytes <= 4096) ? 4 << 20 : 16 << 20;
+    a->sk = n * idx->vec_bytes >= least ? idx->d_sketch : nullptr;
+    a->sk_stride = idx->sk_stride;
+    a->sk_nch = (idx->p.dim + 15) / 16;
+}
+
 static int search_common(jx_index* idx, const void* d_queries, int64_t nq, int32_t out_k, int32_t L, int32_t mode,
                          int32_t rerank, uint32_t* d_out_ids, float* d_out_dist, jx_stats* h_stats, hipStream_t st) {
     if (!idx) return fail(JX_EINVAL, "index is NULL");
@@ -477,6 +511,7 @@ static int search_common(jx_index* idx, const void* d_queries, int64_t nq, int32
     if (mode == JX_EXACT) {
         // distances are already exact: a re-rank would change nothing
         fill_exact_src(idx, &a.ds, d_queries);
+        fill_sketch(idx, idx->n, false, &a);
         a.nq = nq;
         a.out_ids = d_out_ids;
         a.out_dist = d_out_dist;
@@ -688,6 +723,7 @@ static int run_subbatch(jx_index* idx, const InsertWork& w, int64_t pos0, int64_
     b.entry = idx->entry;
     visited_table_for(idx->flags, p.L_build, n_after, idx->vec_bytes, &b.hash_slots, &b.tag_bits);
     b.flags = idx->flags;
+    fill_sketch(idx, id_base, true, &b);
     const int Lc = cand_len(&p);
     b.out_ids = (uint32_t*)(W + w.cand_ids);
     b.out_dist = (float*)(W + w.cand_dist);
@@ -765,6 +801,7 @@ int jx_insert(jx_index* idx, const void* d_vecs, int64_t n, void* stream) {
     if (w.total > idx->work_bytes) return fail(JX_ECAPACITY, "workspace too small");
     uint8_t* W = idx->d_work;
     JX_HIP(hipMemcpyAsync(idx->d_vecs + (size_t)first * idx->vec_bytes, d_vecs, (size_t)n * idx->vec_bytes, hipMemcpyDeviceToDevice, st));
+    JX_HIP(sketch_range(idx, first, n, st));
     int64_t id_skip = 0x7FFFFFFFFFFFFFFFLL;
     int64_t m = n, linked = first;
     if (first == 0) {
@@ -1108,6 +1145,8 @@ int jx_compact(jx_index* idx, uint32_t* d_old_to_new, void* stream) {
     JX_HIP(jx::launch_compact_rename(idx->d_adj, p.R, n, map, idx->d_deleted, d_old_to_new, idx->d_clean, st));
     JX_HIP(jx::launch_compact_records(idx->d_vecs, idx->vec_bytes, n, map, idx->d_deleted, staging, staging_bytes, st));
     JX_HIP(jx::launch_compact_records((uint8_t*)idx->d_adj, p.R * 4, n, map, idx->d_deleted, staging, staging_bytes, st));
+    if (idx->d_sketch)
+        JX_HIP(jx::launch_compact_records(idx->d_sketch, idx->sk_stride, n, map, idx->d_deleted, staging, staging_bytes, st));
     if (idx->quantized)
         JX_HIP(jx::launch_compact_records(idx->d_codes, idx->code_stride, n, map, idx->d_deleted, staging, staging_bytes, st));
     uint32_t live = 0, new_entry = JX_NONE;

@@ -46,12 +46,17 @@ struct BeamArgs {
     int vis_cap;                // > 0 (a power of two <= 512): instead of the frontier, out_ids / out_dist [nq][vis_cap]
                                 // receive the expanded vertices (Alg. 1's set V), the first vis_cap of them in
                                 // expansion order, sorted by (distance, id)
+    const uint8_t* sk;          // NULL, or the byte copies of float32 vectors (beam_sketch.hip), sk_stride bytes apart, sk_nch chunks
+    int sk_stride, sk_nch;      // of codes each
 };
 // kernel_name (may be NULL): receives the name of the instance that was launched, at most 96 bytes
 hipError_t launch_beam_search(int kind, int qbits, const BeamArgs& a, hipStream_t st, char* kernel_name = nullptr);
 // batches that leave the machine mostly idle: a team of wavefronts per query; *done = whether the batch is one and
 // has been launched
 hipError_t launch_beam_ahead(int kind, int qbits, const BeamArgs& a, hipStream_t st, char* kernel_name, bool* done);
+// float32 vectors with byte copies; *done as above
+hipError_t launch_beam_sketch(int kind, const BeamArgs& a, hipStream_t st, char* kernel_name, bool* done);
+hipError_t launch_sketch(const float* x, long long n, int d, uint8_t* sk, int stride, hipStream_t st);
 hipError_t launch_beam_codes(int kind, int qbits, const BeamArgs& a, hipStream_t st, char* kernel_name);
 // ablation instances (JX_FLAG_TILED_LOADS, JX_FLAG_QPW_*, JX_FLAG_WAVES_*); hipErrorInvalidValue where none exists
 hipError_t launch_beam_variant(int kind, const BeamArgs& a, hipStream_t st, char* kernel_name);
@@ -238,6 +243,8 @@ struct jx_index {
     uint8_t* d_vecs;     // [capacity][vec_bytes]
     uint32_t* d_adj;     // [capacity][R]
     uint8_t* d_codes;    // [capacity][code_stride] RaBitQ records
+    uint8_t* d_sketch;   // [capacity][sk_stride] byte copies of float32 vectors, or NULL
+    int sk_stride;
     float* d_P;          // [dim][dim]
     float* d_centroid;   // [dim]
     uint8_t* d_work;     // workspace shared by the phases

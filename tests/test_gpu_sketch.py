@@ -1,0 +1,98 @@
+"""float32 searches that read byte copies of the vectors first leave out what cannot enter a frontier: ids, distances (to the
+last bit), expansion lists and expansion counts are those of the general kernel, which a full-id visited table selects."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import dev, random_data
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def jx():
+    from paper_2601_07048_amd import jx as m
+    return m
+
+
+def _same(jx, g, q, L, want_sketch=True):
+    g.set_flags(0)
+    ids, dist, st = g.search(q, min(10, L), L, stats=True)
+    g.set_flags(jx.FLAG_VISITED_IDS)
+    ids0, dist0, st0 = g.search(q, min(10, L), L, stats=True)
+    g.set_flags(0)
+    assert st["beam_kernel"].startswith("beam_search_sketch_kernel<") == want_sketch, st["beam_kernel"]
+    assert st0["beam_kernel"].startswith("beam_search_kernel<"), st0["beam_kernel"]
+    assert torch.equal(ids, ids0), (L, st["beam_kernel"])
+    assert torch.equal(dist.view(torch.int32), dist0.view(torch.int32)), (L, st["beam_kernel"])
+    assert st["hops"] == st0["hops"], (L, st["beam_kernel"])
+
+
+def _mixed(n, d, seed, extremes=True):
+    """Clusters near and far from the origin, long and short vectors, copies, one-sided rows, constant and single-spike rows,
+    rows without a byte copy (beyond 1e17, infinities, NaN) and rows whose squares are subnormal."""
+    x = random_data(n, d, np.float32, seed)
+    rng = np.random.default_rng(seed + 1)
+    part = np.array_split(rng.permutation(n)[:n // 2], 10)
+    x[part[0]] += np.float32(300)
+    x[part[1]] *= np.float32(1e-3)
+    x[part[2]] = x[part[2][0]]
+    x[part[3]] = np.abs(x[part[3]])
+    x[part[4]] = rng.standard_normal((len(part[4]), 1)).astype(np.float32)
+    x[part[5]] = 0
+    x[part[5], rng.integers(0, d, len(part[5]))] = 50
+    x[part[6]] *= np.float32(1e-25)
+    x[part[7]] += rng.integers(0, 2, (len(part[7]), d)).astype(np.float32) * np.float32(1e4)
+    if not extremes:
+        return x
+    odd = part[8][:12]
+    x[odd[:4], 3] = [np.inf, -np.inf, np.nan, 3e38]
+    x[odd[4:8]] *= np.float32(1e18)
+    x[odd[8:12]] *= np.float32(5e16)
+    return x
+
+
+@pytest.mark.parametrize("d,R,n", [(132, 64, 9000), (200, 33, 6000), (256, 64, 5000), (260, 64, 5000), (516, 64, 9000), (960, 64, 5000),
+                                   (1024, 17, 5000), (1028, 64, 5000), (1536, 64, 3000)])
+def test_searches_equal_the_general_kernel(jx, d, R, n):
+    q = np.concatenate([random_data(1500, d, np.float32, 32), _mixed(1200, d, 33)])
+    x = random_data(n, d, np.float32, 31)
+    g = jx.Index(d, jx.F32, R, 48, 1.2, capacity=n, max_batch=n)
+    g.insert(dev(x))
+    adj, entry = g.export_graph()[0], g.size()[1]
+    for y in (x, _mixed(n, d, 31)):
+        g.import_graph(dev(y), adj, entry)
+        for L in (1, 10, 64, 65, 128, 129, 256):
+            for nq in (513, 2700):
+                _same(jx, g, dev(q[:nq]), L, want_sketch=d > 256 or L <= 128)
+
+
+@pytest.mark.parametrize("d,R,L_build,visited", [(200, 64, 128, False), (300, 40, 64, False), (960, 64, 128, True), (960, 64, 64, True),
+                                                 (1536, 64, 100, True)])
+def test_builds_equal_the_general_kernel(jx, d, R, L_build, visited):
+    n = 8000
+    for x in (random_data(n, d, np.float32, 41), _mixed(n, d, 42, extremes=False)):
+        adj = []
+        for flags in (0, jx.FLAG_VISITED_IDS):
+            g = jx.Index(d, jx.F32, R, L_build, 1.2, capacity=n, max_batch=n, flags=flags,
+                         cand_mode=jx.CAND_VISITED if visited else jx.CAND_FRONTIER)
+            g.insert(dev(x))
+            adj.append(g.export_graph()[0])
+        assert torch.equal(adj[0], adj[1])
+
+
+def test_copies_follow_imports_inserts_and_compaction(jx):
+    d, n = 300, 9000
+    x, q = random_data(n, d, np.float32, 51), dev(random_data(700, d, np.float32, 52))
+    g = jx.Index(d, jx.F32, 48, 64, 1.2, capacity=n, max_batch=n)
+    g.insert(dev(x[:6000]))
+    h = jx.Index(d, jx.F32, 48, 64, 1.2, capacity=n, max_batch=n)
+    h.import_graph(dev(x[:6000]), g.export_graph()[0], g.size()[1])
+    _same(jx, h, q, 64)
+    h.insert(dev(x[6000:]))
+    _same(jx, h, q, 64)
+    h.delete(dev(np.random.default_rng(5).permutation(n)[:3000].astype(np.int32)))
+    _same(jx, h, q, 64)
+    h.consolidate()
+    h.compact()
+    _same(jx, h, q, 64)
