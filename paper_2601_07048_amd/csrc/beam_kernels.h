@@ -184,35 +184,64 @@ __device__ __forceinline__ void frontier_merge(uint64_t (&fk)[NREG], uint64_t* f
         if (r == (L - 1) >> 6) worst = readlane64(fk[r], (L - 1) & 63) | 1ull;
 }
 
-// The expansion list of one query (Alg. 1's set V; what Alg. 4 hands to robustPrune), kept in LDS in expansion order:
-// sort its first n entries by key = (distance, id) -- a bitonic network over cap (a power of two) slots, padded with
-// the largest key, four compare-exchanges per lane and stage at cap = 512 -- then write the ids and distances of the
-// entries that are not logically deleted to out_ids / out_dist [qi][out_k], padded with JX_NONE / +inf.
-template <int KIND>
-__device__ __forceinline__ void write_visited(const BeamArgs& a, const int64_t qi, uint64_t* vis, const int n, const int lane) {
-    const int cap = a.vis_cap;
-    for (int i = n + lane; i < cap; i += 64) vis[i] = JX_EMPTY_KEY;
+// The expansion list of one query (Alg. 1's set V; what Alg. 4 hands to robustPrune): its first vis_cap entries in expansion
+// order, sorted by (distance, id), those not logically deleted, written to out_ids / out_dist [qi][out_k] and padded with
+// JX_NONE / +inf.  While the search runs, 64 expansions at a time stand in a register (visited_add) and then in the query's own
+// part of the two output arrays, vis_cap / 2 keys each (visited_slot).  In LDS the list took 4 of 10 KB at L = 128 and with that
+// a third of the wavefronts a CU can hold (200,000 x 128 uint8 built in 22.3 -> 18.8 ms, 60,000 x 128 float32 20.8 -> 19.2, 32
+// points into 50,000 uint8 249 -> 231 us); a store at every expansion is waited for by the next gather (249 -> 299).
+__device__ __forceinline__ uint64_t* visited_slot(const BeamArgs& a, const int64_t qi, const uint32_t i) {
+    const uint32_t half = (uint32_t)a.vis_cap / 2;
+    return i < half ? reinterpret_cast<uint64_t*>(a.out_ids + qi * a.out_k) + i : reinterpret_cast<uint64_t*>(a.out_dist + qi * a.out_k) + (i - half);
+}
+
+__device__ __forceinline__ void visited_add(const BeamArgs& a, const int64_t qi, uint64_t& vk, const uint32_t hops, const uint64_t key, const int lane) {
+    vk = lane == (int)(hops & 63u) ? key : vk;
+    if ((hops & 63u) == 63u && hops < (uint32_t)a.vis_cap) *visited_slot(a, qi, hops - 63u + (uint32_t)lane) = vk;
+}
+
+// Every entry of the final frontier has been expanded, and an expanded vertex that is not in it was pushed out by closer
+// ones: it lies behind all of them.  So the list is the frontier, which is sorted, and then those pushed out, which are few
+// (hops - L, a handful at L = 128) and are sorted in LDS (list: room for vis_cap keys, where the visited table was).  Only a
+// search of more than vis_cap expansions has to sort them all.
+template <int KIND, int NREG>
+__device__ __forceinline__ void write_visited(const BeamArgs& a, const int64_t qi, const uint64_t (&fk)[NREG], const int count,
+                                              const uint64_t worst, const uint64_t vk, uint64_t* list, const uint32_t hops, const int lane) {
+    const bool whole = hops <= (uint32_t)a.vis_cap;
+    const int n = whole ? (int)hops : a.vis_cap;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the keys stored below are read back by other lanes
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     wave_sync();
-    for (int k = 2; k <= cap; k <<= 1) {
+    int m = 0;
+    for (int i0 = 0; i0 < n; i0 += 64) {
+        const uint64_t k = i0 + 64 <= n ? *visited_slot(a, qi, (uint32_t)(i0 + lane)) : vk;
+        const bool out = i0 + lane < n && (!whole || k > worst);
+        const uint64_t om = ballot(out);
+        if (out) list[m + prefix_count(om)] = k;
+        m += __builtin_popcountll(om);
+    }
+    int cap = 1;
+    while (cap < m) cap <<= 1;
+    for (int i = m + lane; i < cap; i += 64) list[i] = JX_EMPTY_KEY;
+    wave_sync();
+    for (int k = 2; k <= cap; k <<= 1) {  // a bitonic network
         for (int j = k >> 1; j >= 1; j >>= 1) {
             for (int p = lane; p < cap / 2; p += 64) {
                 const int i = ((p & ~(j - 1)) << 1) | (p & (j - 1));  // p with a zero bit inserted at bit log2(j)
-                const int m = i | j;
-                const uint64_t x = vis[i], y = vis[m];
+                const int o = i | j;
+                const uint64_t x = list[i], y = list[o];
                 const bool up = (i & k) == 0;
                 if ((x > y) == up) {
-                    vis[i] = y;
-                    vis[m] = x;
+                    list[i] = y;
+                    list[o] = x;
                 }
             }
             wave_sync();
         }
     }
     int base_pos = 0;
-    for (int p0 = 0; p0 < cap; p0 += 64) {
-        const uint64_t k = vis[p0 + lane];
+    auto put = [&](const uint64_t k, bool keep) {
         const uint32_t id = key_id(k);
-        bool keep = p0 + lane < n;
         if (keep && a.deleted) keep = a.deleted[id] == 0;
         const uint64_t km = ballot(keep);
         const int pos = base_pos + prefix_count(km);
@@ -227,11 +256,22 @@ __device__ __forceinline__ void write_visited(const BeamArgs& a, const int64_t q
             a.out_dist[qi * a.out_k + pos] = d;
         }
         base_pos += __builtin_popcountll(km);
+    };
+    if (whole) {
+#pragma unroll
+        for (int r = 0; r < NREG; r++) put(fk[r], r * 64 + lane < count);
     }
+    for (int p0 = 0; p0 < m; p0 += 64) put(list[p0 + lane < m ? p0 + lane : 0], p0 + lane < m);
     for (int p = base_pos + lane; p < a.out_k; p += 64) {
         a.out_ids[qi * a.out_k + p] = JX_NONE_ID;
         a.out_dist[qi * a.out_k + p] = __builtin_inff();
     }
+}
+
+// LDS behind the candidate buffers: the visited table, and after the search what the expansion list has to sort
+inline size_t table_bytes(const BeamArgs& a) {
+    const size_t t = (size_t)a.hash_slots * (a.tag_bits ? 2 : 4), v = (size_t)a.vis_cap * 8;
+    return t > v ? t : v;
 }
 
 // Records in flight per lane group of the wide instances, for batches of at most two wavefronts per SIMD: 48 records at
@@ -305,7 +345,7 @@ inline int beam_mode(const BeamArgs& a) {
 template <int KIND, int T, int CPL, int NREG, int QB, int WPB, bool TILED, bool VIS = false, int MODE = 0>
 __device__ __forceinline__ void beam_search_body(const BeamArgs& a) {
     constexpr int G = 64 / T;
-    constexpr int UMAX = (KIND == K_RQ1) ? JX_UMAX_RQ1 : ((KIND == K_U8) ? JX_UMAX_EXACT : ((KIND == K_RQ4) ? JX_UMAX_RQ4 : 8));  // 16-byte loads in flight per lane (the 1-bit path keeps its bit planes in registers)
+    constexpr int UMAX = MODE == 3 ? 4 : (KIND == K_RQ1) ? JX_UMAX_RQ1 : ((KIND == K_U8) ? JX_UMAX_EXACT : ((KIND == K_RQ4) ? JX_UMAX_RQ4 : 8));  // 16-byte loads in flight per lane (the 1-bit path keeps its bit planes in registers)
     constexpr int U0 = (UMAX / CPL) > 0 ? (UMAX / CPL) : 1;
     constexpr bool FAST = MODE != 0;
     constexpr int U = MODE == 2 ? wide_u<T, CPL>() : (U0 < (64 / G) ? U0 : (64 / G));  // records in flight per lane group
@@ -321,13 +361,12 @@ __device__ __forceinline__ void beam_search_body(const BeamArgs& a) {
     const int tag_bits = a.tag_bits;  // > 0: 16-bit entries (slot and tag together name the id exactly)
     const uint32_t id_mask = tag_bits ? ((1u << (tag_bits + 30 - __builtin_clz((uint32_t)H))) - 1u) : 0u;  // H / 2 sets
     constexpr int QL = query_lds_bytes<KIND, T, CPL, QB>();  // query bit planes kept in LDS (jx_distance.h)
-    const size_t per_wave = (size_t)QL + (size_t)FCAP * 8 + 64 * 8 + 64 * 4 + (size_t)H * (tag_bits ? 2 : 4) + (VIS ? (size_t)a.vis_cap * 8 : 0);
+    const size_t per_wave = (size_t)QL + (size_t)FCAP * 8 + 64 * 8 + 64 * 4 + (size_t)H * (tag_bits ? 2 : 4);  // (VIS: one wavefront per workgroup)
     unsigned char* my = smem + per_wave * wave;
     uint64_t* fr = reinterpret_cast<uint64_t*>(my + QL);
     uint64_t* cand_key = fr + FCAP;
     uint32_t* cand_id = reinterpret_cast<uint32_t*>(cand_key + 64);
     uint32_t* tab = cand_id + 64;
-    uint64_t* vis = reinterpret_cast<uint64_t*>(my + per_wave) - (VIS ? a.vis_cap : 0);  // behind the table (8-byte aligned)
 
     for (int i = lane; i < (tag_bits ? H / 2 : H); i += 64) tab[i] = JX_NONE_ID;
     for (int i = lane; i < FCAP; i += 64) fr[i] = JX_EMPTY_KEY;
@@ -343,6 +382,7 @@ __device__ __forceinline__ void beam_search_body(const BeamArgs& a) {
     const int L = a.L;
     const bool full = (sep_meta<KIND, CPL>() ? a.ds.meta_chunk : a.ds.nch) == T * CPL;  // wave-uniform: no chunk slot is idle
     uint32_t hops = 0, evals = 0;
+    uint64_t vk = 0;  // VIS: see visited_add
 
     // seed: the entry vertex
     if (lane == 0) {
@@ -399,7 +439,7 @@ __device__ __forceinline__ void beam_search_body(const BeamArgs& a) {
 #pragma unroll
             for (int r = 0; r < NREG; r++) fk[r] |= (r == sel_r && lane == sel_lane) ? 1ull : 0ull;
             if constexpr (VIS) {
-                if (lane == 0 && hops < (uint32_t)a.vis_cap) vis[hops] = ukey | 1ull;
+                visited_add(a, qi, vk, hops, ukey | 1ull, lane);
             }
             hops++;
             // ---- 2. adjacency row
@@ -456,7 +496,7 @@ __device__ __forceinline__ void beam_search_body(const BeamArgs& a) {
                 u = key_id(ukey);
                 if (lane == sel_lane) fk[r] |= 1ull;
                 if constexpr (VIS) {
-                    if (lane == 0 && hops < (uint32_t)a.vis_cap) vis[hops] = ukey | 1ull;
+                    visited_add(a, qi, vk, hops, ukey | 1ull, lane);
                 }
             }
         }
@@ -512,7 +552,7 @@ __device__ __forceinline__ void beam_search_body(const BeamArgs& a) {
     }
 
     if constexpr (VIS) {
-        write_visited<KIND>(a, qi, vis, (int)(hops < (uint32_t)a.vis_cap ? hops : (uint32_t)a.vis_cap), lane);
+        write_visited<KIND, NREG>(a, qi, fk, count, worst, vk, reinterpret_cast<uint64_t*>(tab), hops, lane);
         if (a.stats && lane == 0) {
             unsigned long long* sp = a.stats + (size_t)(qi & 63) * 16;
             atomicAdd(&sp[0], (unsigned long long)hops);
@@ -537,9 +577,11 @@ beam_search_variant_kernel(BeamArgs a) {
     beam_search_body<KIND, T, CPL, NREG, 0, WPB, TILED>(a);
 }
 
-// Insertion with the expansion list as candidate set (exact distances; see BeamArgs::vis_cap)
+// Insertion with the expansion list as candidate set (exact distances; see BeamArgs::vis_cap).  Five wavefronts per SIMD by
+// registers (six spill: 22.3 -> 23.8 ms for 200,000 x 128 uint8).  MODE 3: half as many records in flight and six, for batches
+// that fill the card more than once
 template <int KIND, int T, int CPL, int NREG, int MODE>
-__global__ void __launch_bounds__(64) beam_search_visited_kernel(BeamArgs a) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == 3 ? 6 : (MODE != 2 && CPL <= 2 ? 5 : 1), 8))) beam_search_visited_kernel(BeamArgs a) {
     beam_search_body<KIND, T, CPL, NREG, 0, 1, false, true, MODE>(a);
 }
 

@@ -161,7 +161,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
     uint64_t* cand_key = fr + FCAP;
     uint32_t* cand_id = reinterpret_cast<uint32_t*>(cand_key + 64);
     uint32_t* tab = cand_id + 64;
-    uint64_t* vis = reinterpret_cast<uint64_t*>(tab + a.hash_slots / 2);
 
     for (int i = lane; i < a.hash_slots / 2; i += 64) tab[i] = JX_NONE_ID;
     for (int i = lane; i < FCAP; i += 64) fr[i] = JX_EMPTY_KEY;
@@ -226,6 +225,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
     const int L = a.L;
     const bool full = a.ds.nch == T * CPL;
     uint32_t hops = 0, evals = 0;
+    uint64_t vk = 0;  // VIS: see visited_add
     int tried = 0, kept = 0;  // by sketches
 
     if (lane == 0) {  // seed: the entry vertex
@@ -272,7 +272,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
 #pragma unroll
         for (int r = 0; r < NREG; r++) fk[r] |= (r == sel_r && lane == sel_lane) ? 1ull : 0ull;
         if constexpr (VIS) {
-            if (lane == 0 && hops < (uint32_t)a.vis_cap) vis[hops] = ukey | 1ull;
+            visited_add(a, qi, vk, hops, ukey | 1ull, lane);
         }
         hops++;
         // ---- 2. adjacency row
@@ -335,7 +335,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
     }
 
     if constexpr (VIS) {
-        write_visited<K_F32>(a, qi, vis, (int)(hops < (uint32_t)a.vis_cap ? hops : (uint32_t)a.vis_cap), lane);
+        write_visited<K_F32, NREG>(a, qi, fk, count, worst, vk, reinterpret_cast<uint64_t*>(tab), hops, lane);
         if (a.stats && lane == 0) {
             unsigned long long* sp = a.stats + (size_t)(qi & 63) * 16;
             atomicAdd(&sp[0], (unsigned long long)hops);
@@ -358,7 +358,7 @@ static hipError_t launch_sketch_shape(BeamArgs a, hipStream_t st, char* name) {
         a.hash_slots /= 2;
         a.tag_bits++;
     }
-    const size_t sh0 = 2 * (size_t)sketch_plane(a.sk_nch) + 64 * 8 + 64 * 4 + (size_t)a.hash_slots * 2 + (size_t)a.vis_cap * 8;
+    const size_t sh0 = 2 * (size_t)sketch_plane(a.sk_nch) + 64 * 8 + 64 * 4 + table_bytes(a);
     constexpr bool SHORT = T * CPL <= 64;
     // two wavefronts per SIMD are 2,048 queries: 15,000 x 1536 at L = 200, 700 / 1,500 / 2,000 queries 1,681 / 2,152 / 3,741 ->
     // 1,505 / 2,046 / 3,478 us, 30,000 x 960 at L = 64 447 / 561 / 649 -> 422 / 541 / 632

@@ -183,12 +183,16 @@ static hipError_t launch_team(const BeamArgs& a, hipStream_t st, char* name) {
 template <int KIND, int T, int CPL>
 static hipError_t launch_visited_shape(const BeamArgs& a, hipStream_t st, char* name) {
     const int nreg = (a.L + 63) / 64;
-    const size_t tail = 64 * 8 + 64 * 4 + (size_t)a.hash_slots * (a.tag_bits ? 2 : 4) + (size_t)a.vis_cap * 8;
-    const int mode = beam_mode<KIND, T, CPL, 2, 0>(a);
+    const size_t tail = 64 * 8 + 64 * 4 + table_bytes(a);
+    int mode = beam_mode<KIND, T, CPL, 2, 0>(a);
+    // uint8: an expansion of a full graph has some eleven new neighbours, one pass of 16 (200,000 x 128 19.4 -> 18.9 ms with the
+    // line at 10,000, 18.9 at 5,120; 32 points into 50,000 231 -> 242 us); float32 passes hold four: 19.17 -> 19.18
+    if (KIND == K_U8 && mode == 1 && a.nq > 8192) mode = 3;
     if (name) snprintf(name, 96, "beam_search_visited_kernel<%d,%d,%d,%d,%d>", KIND, T, CPL, nreg <= 1 ? 1 : 2, mode);
 #define JX_LAUNCH(NR)                                                                                                         \
     {                                                                                                                         \
         auto kern = mode == 2 ? beam_search_visited_kernel<KIND, T, CPL, NR, has_wide<T, CPL>() ? 2 : 1>                      \
+                    : mode == 3 ? beam_search_visited_kernel<KIND, T, CPL, NR, KIND == K_U8 ? 3 : 1>                              \
                               : (mode ? beam_search_visited_kernel<KIND, T, CPL, NR, 1> : beam_search_visited_kernel<KIND, T, CPL, NR, 0>); \
         hipLaunchKernelGGL(kern, dim3((unsigned)a.nq), dim3(64), mirror_entries<NR>() * 8 + tail, st, a);                     \
     }

@@ -317,3 +317,31 @@ def test_workload1_frontier_vs_visited_candidates(jx):
             out[(name, L)] = (round(r_g, 4), round(r_o, 4), round(float(u32(g.export_graph()[1]).mean()), 1))
     print("workload 1, recall@10 (GPU, oracle, mean degree):", out, flush=True)
     assert out[("visited", 64)][0] >= 0.95 and out[("frontier", 64)][0] >= 0.95
+
+
+@pytest.mark.parametrize("dtype,d", [("uint8", 128), ("float32", 128), ("float32", 960)])
+@pytest.mark.parametrize("L", [1, 16, 40, 64, 128])
+def test_insert_visited_candidates_of_long_walks(jx, dtype, d, L):
+    """Searches along a chain expand hundreds of vertices: more than the expansion list holds (the first 64 .. 512 of them, in
+    order of expansion) at small L, and all but L of them pushed out of the frontier at large L.  The rows of the new points
+    are the oracle's (all distances are integers below 2^24)."""
+    n, m, R = 1500, 90, 4
+    step = 20 * np.arange(n)[:, None] - 255 * np.arange(128)[None, :]
+    x = np.zeros((n, d), dtype)
+    x[:, :128] = np.clip(step, 0, 255)
+    rng = np.random.default_rng(7)
+    new = x[rng.integers(5, n, m)].copy()
+    new[:, 0] = rng.integers(0, 256, m)
+    new[:, 127] = rng.integers(0, 256, m)
+    i = np.arange(n)[:, None] + np.array([1, 2, -1, -2])[None, :]
+    adj = np.full((n, R), 0xFFFFFFFF, np.uint32)
+    for v in range(n):
+        row = [w for w in i[v] if 0 <= w < n]
+        adj[v, :len(row)] = row
+    ref = oracle.Index(d, x.dtype, R, L, 1.2, n + m, cand_mode=oracle.CAND_VISITED)
+    ref.set_graph(x, adj, 0)
+    ref.insert(new)
+    g = jx.Index(d, jx.U8 if dtype == "uint8" else jx.F32, R, L, 1.2, capacity=n + m, max_batch=1024, cand_mode=jx.CAND_VISITED)
+    g.import_graph(dev(x), dev(adj), 0)
+    g.insert(dev(new))
+    assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0])
