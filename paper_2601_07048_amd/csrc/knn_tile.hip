@@ -85,6 +85,17 @@ struct KnnArgs {
 template <int DT> struct KAcc { typedef kf32x16 type; typedef float elem; };
 template <> struct KAcc<JX_U8> { typedef ki32x16 type; typedef int elem; };
 
+// The query tile (.x) and slice (.y) of a workgroup.  Workgroups go round the eight XCDs by their number; consecutive tiles of
+// one slice are given to one XCD, whose workgroups then stream the same vectors through its L2.  In order of their numbers /
+// like this, k = 10: 1,000 x 200,000 float32 d = 128 416 / 372 us, 1,000 x 100,000 d = 960 1,022 / 986, 300 x 50,000 d = 1536 455 /
+// 441, binary16 1,000 x 100,000 d = 960 531 / 520.  Not knn_u8_kernel: 5,000 x 300,000 d = 96, k = 100 1,774 / 1,808.
+__device__ __forceinline__ int2 knn_work(const KnnArgs& a) {
+    const uint32_t g = gridDim.x, xcd = blockIdx.x & 7u, each = g >> 3, more = g & 7u;
+    const uint32_t w = xcd * each + (xcd < more ? xcd : more) + (blockIdx.x >> 3);
+    const uint32_t tiles = (uint32_t)((a.nq + KT - 1) / KT);
+    return make_int2((int)(w % tiles), (int)(w / tiles));
+}
+
 struct KnnLds {
     uint4 a[KT * KROW / 16], b[KT * KROW / 16];
     uint64_t buf[KT][KCAP];
@@ -403,7 +414,8 @@ __global__ void __launch_bounds__(256, 2) knn_tile_kernel(KnnArgs a) {
     __shared__ KnnLds S;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
-    const int tile = blockIdx.x, split = blockIdx.y;
+    const int2 work = knn_work(a);
+    const int tile = work.x, split = work.y;
     const long long q0 = (long long)tile * KT;
     const long long steps = (a.n + KT - 1) / KT;  // every slice has as many, or one more
     const long long b_begin = split * steps / a.nsplit * KT;
@@ -731,8 +743,9 @@ __global__ void __launch_bounds__(256, 2) knn_u8_kernel(KnnArgs a) {
     __shared__ KnnLds S;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
-    const long long q0 = (long long)blockIdx.x * KT;
-    const int split = blockIdx.y;
+    const uint32_t tiles = (uint32_t)((a.nq + KT - 1) / KT);
+    const long long q0 = (long long)(blockIdx.x % tiles) * KT;
+    const int split = (int)(blockIdx.x / tiles);
     knn_row b_begin, b_end;
     knn_slice(a.n, a.nsplit, split, &b_begin, &b_end);
     b_begin = (knn_row)__builtin_amdgcn_readfirstlane((int)b_begin);
@@ -1089,7 +1102,7 @@ static bool knn_one_slab(int dtype, int nch) { return dtype == JX_U8 && nch <= 8
 template <int DT, int NL>
 static hipError_t launch_knn(const KnnArgs& a, hipStream_t st) {
     constexpr bool U8 = DT == JX_U8;
-    dim3 grid((unsigned)((a.nq + KT - 1) / KT), (unsigned)a.nsplit), block(256);
+    dim3 grid((unsigned)((a.nq + KT - 1) / KT * a.nsplit)), block(256);
     const bool one = knn_one_slab(DT, a.nch);
     if constexpr (U8) {
         if (one) {
