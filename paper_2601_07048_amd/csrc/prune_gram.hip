@@ -14,6 +14,11 @@
 //             sum of their own, added to the total by the vector unit, so the result is nearer to the exact one than that
 //             of the float32 instruction: relative error of d(i,j) against 64 bits, root mean square / largest,
 //             d = 128 1.1e-7 / 4.7e-7 (float32 instruction 2.9e-7 / 1.5e-6), d = 960 1.4e-7 / 5.5e-7 (7.1e-7 / 2.9e-6).
+//             Long vectors (LONG) take two parts and the three products of them first.  They leave d(i,j) uncertain by 6e-5 of
+//             |x_i|^2 + |x_j|^2, which settles all but a few of the 32,000 comparisons of a prune; for those the float32 distance
+//             of the two vectors is taken.  Where hundreds are undecided (ties), or squares are subnormal, the three parts are.
+//             G_jj is then a float32 sum of the centred values' squares.  Relative error against 64 bits, root mean square /
+//             largest, d = 960: those distances 3.7e-8 / 1.1e-7, these sums 4.0e-8 / 1.9e-7.
 //   binary16: v_mfma_f32_32x32x16_f16 on the stored values (products exact, float32 accumulation).
 //   uint8   : v_mfma_i32_32x32x32_i8 on the values shifted by -128, exact.
 //
@@ -24,7 +29,7 @@
 //
 // What bounds it: the matrix cores where vectors are long (d = 960, float32), the relation and the fixpoint where they are
 // short.  One wavefront per prune took 450 us for 256 candidates of d = 960, the length of a launch however small its
-// batch; a workgroup takes 60.  Build of 20,000 x 960 float32: prunes 62 -> 15 ms of 96 -> 49; 60,000 x 128 float32
+// batch; a workgroup takes 60.  Build of 20,000 x 960 float32: prunes 62 -> 15 ms, with two parts 11; 60,000 x 128 float32
 // 40.6 -> 21.6 ms, binary16 23.9 -> 12.5.
 //
 // The relation is kept as bit masks by victim, and only with discarders that come before it in (distance, id) order:
@@ -33,6 +38,7 @@
 // selected.  The first undecided candidate in order is always decided, so a round makes progress, and a handful of rounds
 // of 40 to 130 instructions replace a walk of up to 256 dependent LDS reads.  Candidates beyond the R-th selected one are
 // cut off afterwards: they cannot influence earlier ones.
+#include <type_traits>
 #include "jx_distance.h"
 
 namespace jx {
@@ -77,6 +83,15 @@ __device__ __forceinline__ uint32_t take_bf16(float& a, float& b) {
 #define GT_WAVES(DT, NB) ((DT) != JX_F32 ? 4 : (NB) == 4 ? 3 : 2)
 #define GT_SMALL 128
 #define GT_BIG 256
+#define GT_PAIRS 1024  // float32: a prune with more undecided pairs takes the three parts
+// two parts: error of G_ij in |x_i| |x_j|.  Roundings to 8 bits leave up to 2^-8 and 2^-16 of a value: 2^-16 for the product of the
+// second parts, 2 x 2^-16 (1 + 2^-8) for what is behind them; sums of 32 coordinates and of the slabs, less than (6 + d / 32) 2^-24
+#define GT_TWO 6e-5f
+#define GT_TINY 1e-28f  // squares below this: products of the parts may be subnormal, and the bound above means nothing
+// float32 vectors of so many bytes take two parts first (LONG).  Builds, three parts / two: 20,000 x 960 31.0 / 27.5 ms, 20,000 x
+// 512 17.2 / 16.0, 40,000 x 200 17.1 / 16.8, 60,000 x 128 18.9 / 19.1: of short ones the relation is the longer part, and the
+// search for undecided pairs comes on top
+#define GT_LONG 640
 #define GT_PIECE 576  // bytes of 32 rows x 16 operand bytes, padded: 64 bytes further on in the banks from piece to piece
 
 template <int DT, int NB>
@@ -91,12 +106,14 @@ struct TeamLds {
             uint32_t by_rank[M];   // slot of the selected candidate of this rank, or JX_NONE_ID
             uint32_t sel_id[M];
             uint32_t sel_dist[M];  // float bits of d(p, selected), selection order
+            uint32_t pair[GT_PAIRS];  // float32: pairs that two parts do not decide, discarder << 16 | victim
         };
     };
     uint32_t id[M];
     float dp[M];        // d(p, j); -1 beyond the last candidate: nothing discards it
     float nrm[M];       // G_jj
     uint32_t rank[M];   // place in (distance, id) order
+    int pairs;          // entries of pair[], more than GT_PAIRS: all three parts are needed
     int nsel;
 };
 
@@ -104,7 +121,7 @@ struct TeamLds {
 // distances in L->dp.  truncated: further candidates, none before the last one here, exist beyond the pool.  All threads
 // of the workgroup call; the arrays are visible (a barrier after they were filled).  Returns the number selected
 // (L->sel_id / L->sel_dist, visible to all), or -1 if the pool did not suffice.
-template <int DT, int NB>
+template <int DT, int NB, bool LONG>
 __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, int vec_bytes, TeamLds<DT, NB>* L, int m, int n_fixed,
                                           uint32_t p, int R, float alpha, bool truncated) {
     using Lds = TeamLds<DT, NB>;
@@ -163,17 +180,20 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
             }
         }
     };
+    auto gram = [&](auto parts) __attribute__((always_inline)) {
+    constexpr int PARTS = decltype(parts)::value;
     if (mine) fetch(0);
     for (int p0 = 0; p0 < vec_bytes; p0 += 128) {
         if (mine) {
             if constexpr (DT == JX_F32) {
-                uint8_t* at = own + (((piece >> 2) * 6 + ((piece >> 1) & 1)) * GT_PIECE) + (piece & 1) * 8 + r8 * 16;
+                uint8_t* at = own + (((piece >> 2) * (2 * PARTS) + ((piece >> 1) & 1)) * GT_PIECE) + (piece & 1) * 8 + r8 * 16;
 #pragma unroll
                 for (int s = 0; s < 4; s++) {
                     float v0 = __uint_as_float(x[s].x) - __uint_as_float(c.x), v1 = __uint_as_float(x[s].y) - __uint_as_float(c.y);
                     float v2 = __uint_as_float(x[s].z) - __uint_as_float(c.z), v3 = __uint_as_float(x[s].w) - __uint_as_float(c.w);
+                    if (PARTS == 2) fnn[s] += fmaf(v3, v3, fmaf(v2, v2, fmaf(v1, v1, v0 * v0)));
 #pragma unroll
-                    for (int part = 0; part < 3; part++) {
+                    for (int part = 0; part < PARTS; part++) {
                         uint2 h;
                         h.x = take_bf16(v0, v1);
                         h.y = take_bf16(v2, v3);
@@ -213,10 +233,10 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
         if (mine) {
             const uint8_t* opnd = L->slab + half * GT_PIECE + col * 16;
             if constexpr (DT == JX_F32) {
-                bf16x8_t a[2][3];
+                bf16x8_t a[2][PARTS];
 #pragma unroll
-                for (int q = 0; q < 6; q++)
-                    a[q / 3][q % 3] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)wave * BLOCK + q * 2 * GT_PIECE);
+                for (int q = 0; q < 2 * PARTS; q++)
+                    a[q / PARTS][q % PARTS] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)wave * BLOCK + q * 2 * GT_PIECE);
 #pragma unroll
                 for (int t = 0; t < TILES; t++) {
                     if (2 * t < nb || t == 0 || (2 * t == nb && wave < t)) {  // uniform
@@ -227,13 +247,15 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
                         for (int e = 0; e < 16; e++) part[e] = 0.f;
 #pragma unroll
                         for (int ks = 0; ks < 2; ks++) {
-                            bf16x8_t b[3];
+                            bf16x8_t b[PARTS];
 #pragma unroll
-                            for (int q = 0; q < 3; q++)
-                                b[q] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)bj * BLOCK + (ks * 3 + q) * 2 * GT_PIECE);
-                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][2], b[0], part, 0, 0, 0);
-                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[2], part, 0, 0, 0);
-                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[1], part, 0, 0, 0);
+                            for (int q = 0; q < PARTS; q++)
+                                b[q] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)bj * BLOCK + (ks * PARTS + q) * 2 * GT_PIECE);
+                            if constexpr (PARTS == 3) {
+                                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][2], b[0], part, 0, 0, 0);
+                                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[2], part, 0, 0, 0);
+                                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[1], part, 0, 0, 0);
+                            }
                             part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[0], part, 0, 0, 0);
                             part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[1], part, 0, 0, 0);
                             part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[0], part, 0, 0, 0);
@@ -264,9 +286,23 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
         }
         __syncthreads();
     }
+    };
+    gram(std::integral_constant<int, LONG ? 2 : 3>());
     // Accumulator layout of the 32x32 tiles: register e of lane (col, half) holds row 8*(e/4) + 4*half + e%4, column col.
-    // ---- G_jj from the diagonal tiles, d(p, j) of the candidates that came without
-    if (mine) {
+    // ---- G_jj from the diagonal tiles (float32: the sums of the centred values' squares), d(p, j) of the candidates that came without
+    if (LONG && tid == 0) L->pairs = 0;
+    if (LONG && mine) {
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            const float n = group_sum<8>(fnn[s]);
+            const int slot = wave * 32 + s * 8 + r8;
+            if (piece == 0) {
+                L->nrm[slot] = n;
+                if (slot < n_fixed) L->dp[slot] = n;
+            }
+        }
+    }
+    if (!LONG && mine) {
         const int hcol = (col >> 2) & 1, ecol = ((col >> 3) << 2) | (col & 3);
         float dv = 0.f;
 #pragma unroll
@@ -334,6 +370,23 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
     // ---- the discard relation, tile by tile.  Candidates that came in order (n_fixed = 0) are discarded by those of their own
     // block and of blocks before it only: half of it
     const bool sorted = n_fixed == 0;
+    if (LONG && tid < m && L->nrm[tid] > 0.f && L->nrm[tid] < GT_TINY) L->pairs = GT_PAIRS + 1;
+    const float two = GT_TWO * 1.01f * alpha;
+    // undecided: |alpha d(i,j) - d(p,j)| within alpha times the error of d(i,j), 2 GT_TWO |x_i| |x_j| at most.  An infinite d(p,j)
+    // is decided
+    auto list = [&](const typename GAcc<DT>::type& g, const float nj, const int j, const float dpj, const uint32_t rj, const bool j_first) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int i = wave * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+            const float ni = L->nrm[i], dv = j_first ? L->dp[i] : dpj;
+            const uint32_t ri = L->rank[i];
+            if ((j_first ? rj < ri : ri < rj) && fmaf(-two, ni + nj, fabsf(__fmul_rn(alpha, gram_dist<DT>(ni, nj, g[e])) - dv)) < 0.f) {
+                const int at = atomicAdd(&L->pairs, 1);
+                if (at < GT_PAIRS) L->pair[at] = j_first ? (uint32_t)(j << 16 | i) : (uint32_t)(i << 16 | j);
+            }
+        }
+    };
+    auto relate = [&](const bool mark) __attribute__((always_inline)) {
     if (mine) {
 #pragma unroll
         for (int t = 0; t < TILES; t++) {
@@ -345,6 +398,7 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
                 const bool fwd = !sorted || wave <= bj, back = t > 0 && (!sorted || bj < wave);
                 uint32_t victim_j = 0, victim_i = 0;
                 if (fwd) {
+                    float near = 0.f;
 #pragma unroll
                     for (int g = 0; g < 4; g++) {
                         const int i0 = wave * 32 + 8 * g + 4 * half;
@@ -356,13 +410,16 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
                         for (int f = 0; f < 4; f++) {
                             const float ad = __fmul_rn(alpha, gram_dist<DT>(ni[f], nj, acc[t][4 * g + f]));
                             if (ri[f] < rj && ad <= dpj) victim_j |= 1u << (8 * g + f);
+                            if (LONG && mark) near = fminf(near, fmaf(-two, ni[f] + nj, fabsf(ad - dpj)));
                         }
                     }
+                    if (LONG && mark) if (ballot(near < 0.f)) list(acc[t], nj, j, dpj, rj, false);
                     victim_j <<= 4 * half;
                     victim_j |= shfl_xor(victim_j, 32);
                     if (half == 0) L->kb[wave * Lds::M + j] = victim_j;
                 }
                 if (back) {
+                    float near = 0.f;
 #pragma unroll
                     for (int g = 0; g < 4; g++) {
                         const int i0 = wave * 32 + 8 * g + 4 * half;
@@ -375,11 +432,46 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
                         for (int f = 0; f < 4; f++) {
                             const float ad = __fmul_rn(alpha, gram_dist<DT>(ni[f], nj, acc[t][4 * g + f]));
                             const uint64_t mi = ballot(rj < ri[f] && ad <= di[f]);
+                            if (LONG && mark) near = fminf(near, fmaf(-two, ni[f] + nj, fabsf(ad - di[f])));
                             const uint32_t row = (col & 4) ? (uint32_t)(mi >> 32) : (uint32_t)mi;  // of the lane's own row, if it is among these two
                             if (4 * g + f == (((col >> 3) << 2) | (col & 3))) victim_i = row;
                         }
                     }
+                    if (LONG && mark) if (ballot(near < 0.f)) list(acc[t], nj, j, dpj, rj, true);
                     if (half == 0) L->kb[bj * Lds::M + wave * 32 + col] = victim_i;
+                }
+            }
+        }
+    }
+    };
+    relate(LONG);
+    if constexpr (LONG) {
+        __syncthreads();
+        const int pairs = L->pairs;
+        if (pairs > GT_PAIRS) {  // ties by the hundred, or squares too small: the products of three parts
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < TILES; t++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[t][e] = 0;
+            gram(std::integral_constant<int, 3>());
+            relate(false);
+        } else {
+            for (int k = wave; k < pairs; k += NB) {  // a wavefront per pair: the float32 distance of the vectors
+                const uint32_t ij = L->pair[k];
+                const int i = (int)(ij >> 16), j = (int)(ij & 0xFFFFu);
+                const float* xi = reinterpret_cast<const float*>(recs + (size_t)L->id[i] * stride);
+                const float* xj = reinterpret_cast<const float*>(recs + (size_t)L->id[j] * stride);
+                float d = 0.f;
+                for (int e = lane * 4; e < vec_bytes / 4; e += 256) {
+                    const float4 u = *reinterpret_cast<const float4*>(xi + e), w = *reinterpret_cast<const float4*>(xj + e);
+                    d += fmaf(u.w - w.w, u.w - w.w, fmaf(u.z - w.z, u.z - w.z, fmaf(u.y - w.y, u.y - w.y, (u.x - w.x) * (u.x - w.x))));
+                }
+                d = group_sum<64>(d);
+                uint32_t* word = &L->kb[(i >> 5) * Lds::M + j];
+                if (lane == 0) {
+                    if (__fmul_rn(alpha, d) <= L->dp[j]) atomicOr(word, 1u << (i & 31));
+                    else atomicAnd(word, ~(1u << (i & 31)));
                 }
             }
         }
@@ -452,7 +544,7 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
 // 256 and the closest 256 of a longer one (NB = 8; exact if Alg. 3 finds R neighbours in them).  NB = 8 marks every point
 // of the batch in a.dead[i * a.L]: 0xFF = row and reverse edges written here, 0 = left to the list-based kernel (which
 // leaves lists of at most 128 alone).
-template <int DT, int NB>
+template <int DT, int NB, bool LONG>
 __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) forward_prune_gram_kernel(InsertArgs a) {
     __shared__ TeamLds<DT, NB> lds;
     TeamLds<DT, NB>* L = &lds;
@@ -476,7 +568,7 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) forward_prune_gram_
         L->dp[j] = __uint_as_float(dbits[j]);
     }
     __syncthreads();
-    const int nsel = team_prune<DT, NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, m, 0, (uint32_t)xid, a.R, a.alpha, m < nB);
+    const int nsel = team_prune<DT, NB, LONG>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, m, 0, (uint32_t)xid, a.R, a.alpha, m < nB);
     if (NB == 8 && tid == 0) a.dead[(size_t)i * a.L] = nsel < 0 ? 0 : 0xFF;
     if (nsel < 0) return;
     if (DT == JX_U8 && tid == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
@@ -559,7 +651,7 @@ __global__ void __launch_bounds__(256) reverse_class_kernel(InsertArgs a, int sm
 // NB = 4: at most 128 candidates.  NB = 8: up to 256, or the existing neighbours and the closest new edges up to 256 (the
 // new edges arrive sorted); a pool that does not yield R neighbours no farther than its last new edge is left to the
 // list-based kernel.  A segment that is done is marked (bit 31 of its head): its rewritten row no longer tells.
-template <int DT, int NB>
+template <int DT, int NB, bool LONG>
 __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) reverse_merge_gram_kernel(InsertArgs a) {
     __shared__ TeamLds<DT, NB> lds;
     TeamLds<DT, NB>* L = &lds;
@@ -580,7 +672,7 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) reverse_merge_gram_
             L->dp[deg + j] = __uint_as_float((uint32_t)a.keys[lo + j]);
         }
         __syncthreads();
-        const int nsel = team_prune<DT, NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, deg + mp, deg, v, a.R, a.alpha, mp < m);
+        const int nsel = team_prune<DT, NB, LONG>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, deg + mp, deg, v, a.R, a.alpha, mp < m);
         if (nsel >= 0) {
             for (int j = tid; j < a.R; j += NB * 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
             if (DT == JX_U8 && tid == 0) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
@@ -596,38 +688,40 @@ hipError_t launch_reverse_class(const InsertArgs& a, int small_max, int deg_max,
     return hipGetLastError();
 }
 
-template <int DT>
+template <int DT, bool LONG = false>
 static hipError_t launch_forward_gram_dt(const InsertArgs& a, hipStream_t st) {
     constexpr long long MOST = 1 << 22;  // workgroups of a launch, which has fewer than 2^32 threads
     for (InsertArgs s = a; s.first < a.B; s.first += MOST) {
         const dim3 grid((unsigned)(a.B - s.first < MOST ? a.B - s.first : MOST));
-        hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 4>), grid, dim3(256), 0, st, s);
-        if (a.L > GT_SMALL) hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 8>), grid, dim3(512), 0, st, s);
+        hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 4, LONG>), grid, dim3(256), 0, st, s);
+        if (a.L > GT_SMALL) hipLaunchKernelGGL((forward_prune_gram_kernel<DT, 8, LONG>), grid, dim3(512), 0, st, s);
     }
     return hipGetLastError();
 }
 
-template <int DT>
+template <int DT, bool LONG = false>
 static hipError_t launch_reverse_gram_dt(const InsertArgs& a, hipStream_t st) {
     const long long most = a.E ? a.E : a.B * a.R;  // segments there can be
     auto grid = [&](long long cap) { return dim3((unsigned)(most < cap ? (most < 1 ? 1 : most) : cap)); };
     hipError_t e = launch_reverse_class(a, GT_SMALL, GT_BIG - 64, st);
     if (e != hipSuccess) return e;
     // persistent workgroups: as many as the card holds, twice over
-    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 4>), grid(2048), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 8>), grid(1024), dim3(512), 0, st, a);
+    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 4, LONG>), grid(2048), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 8, LONG>), grid(1024), dim3(512), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_forward_prune_gram(int dtype, const InsertArgs& a, hipStream_t st) {
     if (a.B <= 0) return hipSuccess;
     if (dtype == JX_U8) return launch_forward_gram_dt<JX_U8>(a, st);
-    return dtype == JX_F16 ? launch_forward_gram_dt<JX_F16>(a, st) : launch_forward_gram_dt<JX_F32>(a, st);
+    if (dtype == JX_F16) return launch_forward_gram_dt<JX_F16>(a, st);
+    return a.ds.nch * 16 >= GT_LONG ? launch_forward_gram_dt<JX_F32, true>(a, st) : launch_forward_gram_dt<JX_F32>(a, st);
 }
 
 hipError_t launch_reverse_merge_gram(int dtype, const InsertArgs& a, hipStream_t st) {
     if (dtype == JX_U8) return launch_reverse_gram_dt<JX_U8>(a, st);
-    return dtype == JX_F16 ? launch_reverse_gram_dt<JX_F16>(a, st) : launch_reverse_gram_dt<JX_F32>(a, st);
+    if (dtype == JX_F16) return launch_reverse_gram_dt<JX_F16>(a, st);
+    return a.ds.nch * 16 >= GT_LONG ? launch_reverse_gram_dt<JX_F32, true>(a, st) : launch_reverse_gram_dt<JX_F32>(a, st);
 }
 
 }  // namespace jx

@@ -199,3 +199,29 @@ def test_batches_of_more_workgroups_than_one_launch_takes(jx, L, logB):
         tables.append(g.export_graph()[0])
         g.close()
     assert torch.equal(*tables)
+
+
+@pytest.mark.parametrize("d,R,L", [(160, 8, 31), (164, 63, 64), (260, 64, 129), (160, 40, 161), (516, 64, 256), (960, 30, 128), (1536, 48, 300)])
+@pytest.mark.parametrize("kind,alpha", [("wide", 1.2), ("wide", 1.0), ("bits", 1.0), ("bits", 1.25), ("tiny", 1.2), ("copies", 1.2)])
+def test_long_rows_take_two_parts_first(jx, d, R, L, kind, alpha):
+    """Rows of 640 bytes and more: comparisons that two bfloat16 parts leave open are settled by float32 distances, and by three
+    parts where there are hundreds of them (equal distances) or squares are subnormal.  Integers whose squared distances stay
+    below 2^24: of as many bits as that allows (up to 9, so the second part is needed), of one bit (ties), scaled by 2^-55, and
+    with many copies.  Every float32 sum is exact, so the table is the oracle's."""
+    n = 600
+    rng = np.random.default_rng(d + L)
+    lim = 1 if kind == "bits" else int(np.sqrt(2.0 ** 24 / d) / 2 * 0.99)
+    x = rng.integers(0 if kind == "bits" else -lim, lim + 1, (n, d)).astype(np.float32)
+    if kind == "tiny":
+        x *= np.float32(2.0 ** -55)
+    if kind == "copies":
+        x[rng.permutation(n)[:n // 2]] = x[0]
+    ref = oracle.Index(d, np.float32, R, L, alpha, n, batch_growth=1.0)
+    g = jx.Index(d, jx.F32, R, L, alpha, capacity=n, max_batch=n, batch_growth=1.0)
+    for lo, hi in ((0, 250), (250, n)):
+        ref.insert(x[lo:hi])
+        g.insert(dev(x[lo:hi]))
+        assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), (lo, hi)
+    gone = rng.choice(n, n // 5, replace=False).astype(np.uint32)
+    ref.delete(gone); g.delete(dev(gone)); ref.consolidate(); g.consolidate()
+    assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), "consolidated"
