@@ -138,6 +138,66 @@ __device__ __forceinline__ void sketch_dots(const uint8_t* sk, const uint32_t st
 // bytes of one query plane in LDS (a bank group apart from the other)
 __host__ __device__ inline int sketch_plane(int nch_codes) { return (nch_codes + 3) / 4 * 64 + 16; }
 
+// The query in 16 bits, q' = scale v with |q - q'| <= err, its planes l and h in LDS; none: it has no such form.
+struct SketchQuery {
+    float scale, err, norm, sum;  // norm: |q'|^2 less the slack; sum: of the coordinates of q'
+    bool none;
+};
+
+// By a whole wavefront; rec: nch chunks of four floats
+__device__ __forceinline__ SketchQuery sketch_query(const uint8_t* rec, const int nch, const int kb, uint8_t* qpl, const int plane, const int lane) {
+    SketchQuery o;
+    const float4* qv = reinterpret_cast<const float4*>(rec);
+    float mx = 0.f;
+    bool ok = true;
+    for (int c = lane; c < nch; c += 64) {
+        const float4 w = qv[c];
+        ok = ok && fabsf(w.x) + fabsf(w.y) + fabsf(w.z) + fabsf(w.w) < 4.f * SKETCH_MAX;  // false for a NaN
+        mx = fmaxf(mx, fmaxf(fmaxf(fabsf(w.x), fabsf(w.y)), fmaxf(fabsf(w.z), fabsf(w.w))));
+    }
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) mx = fmaxf(mx, shfl_xor(mx, k));
+    o.none = ballot(!ok) != 0ull || !(mx <= SKETCH_MAX);
+    o.scale = mx * (1.f / 32639.f);
+    const float inv = o.scale > 1e-30f ? 1.f / o.scale : 0.f;
+    float err = 0.f, nn = 0.f;
+    int vsum = 0;
+    for (int c = lane; c < kb * 16; c += 64) {
+        uint32_t wl = 0, wh = 0;
+        if (c < nch && !o.none) {
+            const float4 w = qv[c];
+            const float f[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const float code = fminf(fmaxf(rintf(f[k] * inv), -32639.f), 32639.f);
+                const float r = fmaf(-o.scale, code, f[k]), y = o.scale * code;
+                err = fmaf(r, r, err);
+                nn = fmaf(y, y, nn);
+                const int v = (int)code, h = (v + 128) >> 8;  // v = 256 h + l, both in [-128, 127]
+                vsum += v;
+                wh |= ((uint32_t)h & 255u) << (8 * k);
+                wl |= ((uint32_t)(v - 256 * h) & 255u) << (8 * k);
+            }
+        }
+        reinterpret_cast<uint32_t*>(qpl)[c] = wl;
+        reinterpret_cast<uint32_t*>(qpl + plane)[c] = wh;
+    }
+    err = group_sum<64>(err);
+    nn = group_sum<64>(nn);
+    vsum = group_sum<64>(vsum);
+    o.err = sqrtf(err) * 1.001f + 1e-20f;
+    o.norm = nn - SKETCH_SLACK * nn;
+    o.sum = o.scale * (float)vsum;
+    return o;
+}
+
+// |q' - x'|^2 less the slack of both, from the two sums of sketch_dots and the record's meta chunk
+__device__ __forceinline__ float sketch_dist(const SketchQuery& q, const float4 meta, const int il, const int ih) {
+    const float dot = fmaf(256.f, (float)ih, (float)il);
+    const float t = fmaf(meta.z * dot, q.scale, meta.y * q.sum);  // <x', q'>
+    return fmaf(-2.f, t, meta.x + q.norm);
+}
+
 // Tag table and rows of at most 64 entries only (the launcher checks).  KU: 64-byte pieces of two tiles of 16 neighbours in
 // flight, as the registers allow for four wavefronts per SIMD (codes of at most 256 bytes: KU = 4; 40,000 x 200 built with
 // KU = 4 / five wavefronts, spilled / four tiles 16.2 / 18.5 / 16.6 ms), three (8) or two (16: batches that fill no more).
@@ -169,52 +229,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
     QueryRegs<K_F32, CPL, 0> q;
     load_query<K_F32, T, CPL, 0>(q, a.ds, qrec, lig);
 
-    // ---- the query in 16 bits: q' = qs v, |q - q'| <= qe
-    float qs, qe, qn;
-    int vsum = 0;
-    bool use;
-    {
-        const float4* qv = reinterpret_cast<const float4*>(a.ds.qrecs + qrec * a.ds.qrec_stride);
-        float mx = 0.f;
-        bool ok = true;
-        for (int c = lane; c < a.ds.nch; c += 64) {
-            const float4 w = qv[c];
-            ok = ok && fabsf(w.x) + fabsf(w.y) + fabsf(w.z) + fabsf(w.w) < 4.f * SKETCH_MAX;  // false for a NaN
-            mx = fmaxf(mx, fmaxf(fmaxf(fabsf(w.x), fabsf(w.y)), fmaxf(fabsf(w.z), fabsf(w.w))));
-        }
-#pragma unroll
-        for (int k = 1; k < 64; k <<= 1) mx = fmaxf(mx, shfl_xor(mx, k));
-        use = ballot(!ok) == 0ull && mx <= SKETCH_MAX;
-        qs = mx * (1.f / 32639.f);
-        const float inv = qs > 1e-30f ? 1.f / qs : 0.f;
-        float err = 0.f, nn = 0.f;
-        for (int c = lane; c < kb * 16; c += 64) {
-            uint32_t wl = 0, wh = 0;
-            if (c < a.ds.nch && use) {
-                const float4 w = qv[c];
-                const float f[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const float code = fminf(fmaxf(rintf(f[k] * inv), -32639.f), 32639.f);
-                    const float r = fmaf(-qs, code, f[k]), y = qs * code;
-                    err = fmaf(r, r, err);
-                    nn = fmaf(y, y, nn);
-                    const int v = (int)code, h = (v + 128) >> 8;  // v = 256 h + l, both in [-128, 127]
-                    vsum += v;
-                    wh |= ((uint32_t)h & 255u) << (8 * k);
-                    wl |= ((uint32_t)(v - 256 * h) & 255u) << (8 * k);
-                }
-            }
-            reinterpret_cast<uint32_t*>(qpl)[c] = wl;
-            reinterpret_cast<uint32_t*>(qpl + plane)[c] = wh;
-        }
-        err = group_sum<64>(err);
-        nn = group_sum<64>(nn);
-        vsum = group_sum<64>(vsum);
-        qe = sqrtf(err) * 1.001f + 1e-20f;
-        qn = nn - SKETCH_SLACK * nn;
-    }
-    const float qsum = qs * (float)vsum;
+    const SketchQuery sq = sketch_query(a.ds.qrecs + qrec * a.ds.qrec_stride, a.ds.nch, kb, qpl, plane, lane);
+    bool use = !sq.none;
     const uint8_t* lq = qpl + (lane & 1) * plane + (lane >> 4) * 16;
 
     uint64_t fk[NREG];
@@ -300,10 +316,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
             const float4 meta = *reinterpret_cast<const float4*>(a.sk + (size_t)id * (uint32_t)a.sk_stride + (size_t)a.sk_nch * 16);
             int il = 0, ih = 0;
             for (int f = 0; f < n_new; f += 32) sketch_dots<2, KU>(a.sk, (uint32_t)a.sk_stride, kb, lq, cand_id, f, n_new, lane, il, ih);
-            const float dot = fmaf(256.f, (float)ih, (float)il);
-            const float t = fmaf(meta.z * dot, qs, meta.y * qsum);  // <x', q'>
-            const float d2 = fmaf(-2.f, t, meta.x + qn);
-            const float far = sqrtf(ordered_to_f32(key_dist(worst))) + meta.w + qe;
+            const float d2 = sketch_dist(sq, meta, il, ih);
+            const float far = sqrtf(ordered_to_f32(key_dist(worst))) + meta.w + sq.err;
             const bool keep = lane < n_new && !(d2 > fmaf(far * far, 1.f + SKETCH_REL, SKETCH_ABS));
             const uint64_t km = ballot(keep);
             const int nk = __builtin_popcountll(km);
@@ -344,6 +358,106 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
     } else {
         write_results<K_F32, NREG>(a, qi, fk, count, lane, hops, evals);
     }
+}
+
+// ------------------------------------------------------------------ exact re-rank
+//
+// The first k of at most 64 candidates, by exact distance: as rerank_kernel does it, but what its byte copy shows to be farther
+// than k others is not read.  The k-th smallest of the upper bounds (|q' - x'| + e + eq)^2 is no smaller than the k-th distance,
+// so a candidate whose lower bound exceeds it is none of the first k.  Bound: the gathers, 40 copies and some twelve vectors of a
+// query for 40 vectors (10,000 queries, d = 960 223 -> 171 us; 64 candidates 345 -> 196, 5,000 queries of d = 1536 284 -> 157).
+struct SketchRerankLds {
+    uint64_t cand_key[64];
+    uint32_t cand_id[64];
+    float bound[64];
+};
+
+template <int T, int CPL>
+__global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
+    constexpr int G = 64 / T;
+    constexpr int U0 = CPL == 4 ? 4 : 8 / CPL;
+    constexpr int U = U0 < (64 / G) ? U0 : (64 / G);
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int wave = threadIdx.x >> 6, lane = lane_id();
+    const int g = lane / T, lig = lane % T;
+    const long long qi = (long long)blockIdx.x * 4 + wave;
+    if (qi >= a.nq) return;
+    const int plane = sketch_plane(a.sk_nch), kb = (a.sk_nch + 3) / 4;
+    unsigned char* my = smem + (size_t)wave * (sizeof(SketchRerankLds) + 2 * (size_t)plane);
+    SketchRerankLds* L = reinterpret_cast<SketchRerankLds*>(my);
+    uint8_t* qpl = my + sizeof(SketchRerankLds);
+    QueryRegs<K_F32, CPL, 0> q;
+    load_query<K_F32, T, CPL, 0>(q, a.ds, qi, lig);
+    const SketchQuery sq = sketch_query(a.ds.qrecs + qi * a.ds.qrec_stride, a.ds.nch, kb, qpl, plane, lane);
+    const uint32_t* cand = a.cand + (size_t)qi * a.cand_stride;
+    const uint32_t id = lane < a.rr ? cand[lane] : JX_NONE_ID;
+    const int m = __builtin_popcountll(ballot(id != JX_NONE_ID));  // the frontier is filled from the left
+    if (lane < m) L->cand_id[lane] = id;
+    wave_sync();
+    int n = m;
+    if (m > a.k && !sq.none) {
+        const float4 meta = *reinterpret_cast<const float4*>(a.sk + (size_t)L->cand_id[lane < m ? lane : 0] * (uint32_t)a.sk_stride + (size_t)a.sk_nch * 16);
+        int il = 0, ih = 0;
+        const uint8_t* lq = qpl + (lane & 1) * plane + (lane >> 4) * 16;
+        if (m <= 48) {
+            sketch_dots<3, 5>(a.sk, (uint32_t)a.sk_stride, kb, lq, L->cand_id, 0, m, lane, il, ih);
+        } else {
+            for (int f = 0; f < m; f += 32) sketch_dots<2, 8>(a.sk, (uint32_t)a.sk_stride, kb, lq, L->cand_id, f, m, lane, il, ih);
+        }
+        const float d2 = sketch_dist(sq, meta, il, ih), off = meta.w + sq.err;
+        // upward: the slack twice (it stands below |x'|^2 and |q'|^2, whose sum it is 8e-6 of, X <= |x'| + 2 |m| sqrt(d))
+        const float X = sqrtf(fmaxf(meta.x, 0.f)) * 1.001f + 2.f * fabsf(meta.y) * sqrtf((float)(a.sk_nch * 16));
+        const float up = sqrtf(fmaxf(d2, 0.f) + 2.02f * SKETCH_SLACK * (X * X + sq.norm * 1.001f)) + off;
+        const float most = fmaf(up * up, 1.f + SKETCH_REL, SKETCH_ABS);  // no smaller than the float32 distance
+        L->bound[lane] = lane < m && most == most ? most : __builtin_inff();
+        wave_sync();
+        int rank = 0;
+        const float mine = L->bound[lane];
+        for (int t = 0; t < m; t++) {
+            const float o = L->bound[t];
+            rank += o < mine || (o == mine && t < lane) ? 1 : 0;
+        }
+        const uint64_t kth = ballot(lane < m && rank == a.k - 1);
+        const float bar = sqrtf(L->bound[kth ? __builtin_ctzll(kth) : 0]) + off;  // (ranks are distinct: there is one)
+        const bool keep = lane < m && !(d2 > fmaf(bar * bar, 1.f + SKETCH_REL, SKETCH_ABS));
+        const uint64_t km = ballot(keep);
+        n = __builtin_popcountll(km);
+        wave_sync();
+        if (keep) L->cand_id[prefix_count(km)] = id;
+        wave_sync();
+    }
+    for (int s0 = 0; s0 < n; s0 += G * U) eval_batch<K_F32, T, CPL, 0, U>(q, a.ds, s0, n, L->cand_id, L->cand_key, g, lig);
+    wave_sync();
+    // rank sort by (distance, id); write the first k, pad what is left
+    for (int j = n + lane; j < a.k; j += 64) {
+        a.out_ids[qi * a.k + j] = JX_NONE_ID;
+        a.out_dist[qi * a.k + j] = __builtin_inff();
+    }
+    if (lane < n) {
+        const uint64_t kj = L->cand_key[lane];
+        int rank = 0;
+        for (int t = 0; t < n; t++) rank += (L->cand_key[t] < kj) ? 1 : 0;
+        if (rank < a.k) {
+            a.out_ids[qi * a.k + rank] = key_id(kj);
+            a.out_dist[qi * a.k + rank] = ordered_to_f32(key_dist(kj));
+        }
+    }
+    if (a.stats && lane == 0) atomicAdd(&a.stats[(size_t)(qi & 63) * 16 + 2], (unsigned long long)m);
+}
+
+hipError_t launch_rerank_sketch(const RerankArgs& a, hipStream_t st, bool* done) {
+    *done = false;
+    const int nch = a.ds.nch;
+    // Whole vectors / this, us: 41 candidates for 40 neighbours, 10,000 queries 227 / 292; 50,000 x 256, 5,000 queries 33 / 35; of
+    // d = 960 and 40 candidates 1 query 18 / 19, 1,000 31 / 34, 5,000 119 / 97, and 64 candidates 26 / 18, 45 / 38, 177 / 107
+    if (!a.sk || a.rr > 64 || a.rr < 3 * a.k || nch <= 64 || nch > 384 || (a.nq < 2048 && a.rr <= 48)) return hipSuccess;
+    *done = true;
+    const size_t sh = 4 * (sizeof(SketchRerankLds) + 2 * (size_t)sketch_plane(a.sk_nch));
+    const dim3 grid((unsigned)((a.nq + 3) / 4));
+    if (nch <= 128) hipLaunchKernelGGL((rerank_sketch_kernel<64, 2>), grid, dim3(256), sh, st, a);
+    else if (nch <= 256) hipLaunchKernelGGL((rerank_sketch_kernel<64, 4>), grid, dim3(256), sh, st, a);
+    else hipLaunchKernelGGL((rerank_sketch_kernel<64, 6>), grid, dim3(256), sh, st, a);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ launch

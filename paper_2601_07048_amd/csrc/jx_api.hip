@@ -571,6 +571,9 @@ static int search_common(jx_index* idx, const void* d_queries, int64_t nq, int32
                 jx::RerankArgs r;
                 memset(&r, 0, sizeof r);
                 fill_exact_src(idx, &r.ds, qs);
+                r.sk = idx->d_sketch;
+                r.sk_stride = idx->sk_stride;
+                r.sk_nch = (p.dim + 15) / 16;
                 r.nq = m;
                 r.cand = (const uint32_t*)(W + qw.fr_ids);
                 r.cand_stride = rerank;

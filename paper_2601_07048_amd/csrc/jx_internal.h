@@ -149,7 +149,9 @@ struct RerankArgs {
     int cand_stride, rr, k;
     uint32_t* out_ids;       // [nq][k]
     float* out_dist;
-    unsigned long long* stats;  // the same stripes: [2] += number of vectors read
+    unsigned long long* stats;  // the same stripes: [2] += number of candidates
+    const uint8_t* sk;          // as in BeamArgs
+    int sk_stride, sk_nch;
 };
 
 // f32: by float32 matrix instructions (what codes of more than one bit are made from), else by three bfloat16 parts of each value
@@ -163,6 +165,7 @@ hipError_t launch_pack_records(uint8_t* recs, long long n, int code_stride, int 
                                const uint8_t* codes, const float* meta, hipStream_t st);
 hipError_t launch_code_sums(uint8_t* recs, long long n, int code_stride, int code_bytes, int meta_off, int bits, hipStream_t st);
 hipError_t launch_query_prep(const QueryPrepArgs& a, hipStream_t st);
+hipError_t launch_rerank_sketch(const RerankArgs& a, hipStream_t st, bool* done);  // beam_sketch.hip; *done: whether it was launched
 hipError_t launch_rerank(int dtype, const RerankArgs& a, hipStream_t st);
 hipError_t launch_column_mean(const void* vecs, int dtype, long long n, int d, double* partial, float* mean, hipStream_t st);
 

@@ -1040,7 +1040,9 @@ hipError_t launch_rerank(int dtype, const RerankArgs& a, hipStream_t st) {
     if (a.nq <= 0) return hipSuccess;
     if (dtype == JX_U8) return launch_rerank_shape<K_U8>(a, st);
     if (dtype == JX_F16) return launch_rerank_shape<K_F16>(a, st);
-    return launch_rerank_shape<K_F32>(a, st);
+    bool done = false;
+    const hipError_t e = launch_rerank_sketch(a, st, &done);
+    return e != hipSuccess || done ? e : launch_rerank_shape<K_F32>(a, st);
 }
 
 }  // namespace jx

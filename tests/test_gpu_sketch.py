@@ -96,3 +96,34 @@ def test_copies_follow_imports_inserts_and_compaction(jx):
     h.consolidate()
     h.compact()
     _same(jx, h, q, 64)
+
+
+@pytest.mark.parametrize("d,n", [(288, 9000), (512, 9000), (960, 5000), (1536, 3000)])
+def test_rerank_reads_what_may_be_among_the_first(jx, d, n):
+    """The re-rank that reads byte copies first returns, bit for bit, what the one on whole vectors returns, which keeps batches
+    of fewer than 2,048 queries with at most 48 candidates; with more candidates its ids are those of 64-bit distances.  Copies
+    of one row and rows without a byte copy are among the candidates."""
+    x = random_data(n, d, np.float32, 61)
+    y = _mixed(n, d, 61, extremes=False)
+    y[np.random.default_rng(64).permutation(n)[:9]] *= np.float32(1e17)
+    q = dev(np.concatenate([random_data(1400, d, np.float32, 62), _mixed(700, d, 63)]))
+    g = jx.Index(d, jx.F32, 48, 64, 1.2, capacity=n, max_batch=n, quant_bits=1)
+    g.insert(dev(x))
+    adj, entry = g.export_graph()[0], g.size()[1]
+    rot = np.linalg.qr(np.random.default_rng(9).standard_normal((d, d)))[0].astype(np.float32)
+    for z in (x, y):
+        g.import_graph(dev(z), adj, entry)
+        g.quantize(1, dev(rot), dev(x.mean(0, dtype=np.float64).astype(np.float32)), query_bits=4)
+        for k, L, rr in ((1, 8, 3), (3, 40, 16), (10, 64, 32), (13, 64, 40), (16, 64, 48)):
+            ids, dist = g.search(q, k, L, mode=jx.RABITQ, rerank=rr)
+            few = [g.search(part.contiguous(), k, L, mode=jx.RABITQ, rerank=rr) for part in q.split(700)]
+            assert torch.equal(ids, torch.cat([f[0] for f in few])), (k, rr)
+            assert torch.equal(dist.view(torch.int32), torch.cat([f[1] for f in few]).view(torch.int32)), (k, rr)
+    g.import_graph(dev(x), adj, entry)
+    g.quantize(1, dev(rot), query_bits=4)
+    x64, q = dev(x).double(), q[:300].contiguous()
+    for k, rr in ((10, 49), (21, 64)):
+        cand = g.search(q, rr, 70, mode=jx.RABITQ)[0].long()
+        far = torch.stack([(x64[c] - v.double()).square().sum(1) for c, v in zip(cand, q)])
+        want = cand.gather(1, far.sort(dim=1)[1][:, :k]).to(torch.int32)
+        assert torch.equal(g.search(q, k, 70, mode=jx.RABITQ, rerank=rr)[0], want), (k, rr)
