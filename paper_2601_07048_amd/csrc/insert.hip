@@ -896,7 +896,7 @@ hipError_t launch_forward_prune(int dtype, const InsertArgs& a, hipStream_t st) 
     if (a.gram == 4) return launch_forward_prune_u8(a, st);
     if (a.gram) {
         hipError_t e = launch_forward_prune_gram(dtype, a, st);
-        if (e != hipSuccess || a.L <= 128) return e;  // wider frontiers: the list-based kernel takes the rest
+        if (e != hipSuccess || a.L <= 256) return e;  // longer lists: the list-based kernel takes the rest
     }
     if (dtype == JX_U8) return launch_prune_shape<K_U8>(true, a, st);
     if (dtype == JX_F16) return launch_prune_shape<K_F16>(true, a, st);
@@ -907,6 +907,8 @@ hipError_t launch_reverse_merge(int dtype, const InsertArgs& a, hipStream_t st) 
     if (a.gram) {  // then the list-based kernel: what these leave
         hipError_t e = a.gram == 4 ? launch_reverse_merge_u8(a, st) : launch_reverse_merge_gram(dtype, a, st);
         if (e != hipSuccess) return e;
+        // pools of 512 (uint8) and of 256 (beside rows of at most 192) have merged every smaller segment
+        if (segment_most(a) <= (a.gram == 4 ? 512 : (a.R <= 192 ? 256 : 128))) return hipSuccess;
     }
     if (dtype == JX_U8) return launch_prune_shape<K_U8>(false, a, st);
     if (dtype == JX_F16) return launch_prune_shape<K_F16>(false, a, st);

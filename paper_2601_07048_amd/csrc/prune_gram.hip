@@ -707,7 +707,7 @@ static hipError_t launch_reverse_gram_dt(const InsertArgs& a, hipStream_t st) {
     if (e != hipSuccess) return e;
     // persistent workgroups: as many as the card holds, twice over
     hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 4, LONG>), grid(2048), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 8, LONG>), grid(1024), dim3(512), 0, st, a);
+    if (segment_most(a) > GT_SMALL) hipLaunchKernelGGL((reverse_merge_gram_kernel<DT, 8, LONG>), grid(1024), dim3(512), 0, st, a);
     return hipGetLastError();
 }
 

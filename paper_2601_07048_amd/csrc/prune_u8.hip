@@ -517,11 +517,11 @@ hipError_t launch_reverse_merge_u8(const InsertArgs& a, hipStream_t st) {
     if (a.ds.nch <= 8) {
         if (many) hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 128>), grid, block, 0, st, a, 1);
         hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 512>), grid, block, 0, st, a, rest);
-        hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 2048>), few, block, 0, st, a, 2);
+        if (segment_most(a) > 512) hipLaunchKernelGGL((reverse_merge_u8_kernel<1, 2048>), few, block, 0, st, a, 2);
     } else {
         if (many) hipLaunchKernelGGL((reverse_merge_u8_kernel<2, 128>), grid, block, 0, st, a, 1);
         hipLaunchKernelGGL((reverse_merge_u8_kernel<2, 512>), grid, block, 0, st, a, rest);
-        hipLaunchKernelGGL((reverse_merge_u8_kernel<2, 2048>), few, block, 0, st, a, 2);
+        if (segment_most(a) > 512) hipLaunchKernelGGL((reverse_merge_u8_kernel<2, 2048>), few, block, 0, st, a, 2);
     }
     return hipGetLastError();
 }

@@ -225,3 +225,26 @@ def test_long_rows_take_two_parts_first(jx, d, R, L, kind, alpha):
     gone = rng.choice(n, n // 5, replace=False).astype(np.uint32)
     ref.delete(gone); g.delete(dev(gone)); ref.consolidate(); g.consolidate()
     assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), "consolidated"
+
+
+@pytest.mark.parametrize("dtype,d", [(np.uint8, 128), (np.uint8, 256), (np.float32, 36), (np.float32, 164), (np.float16, 40)])
+@pytest.mark.parametrize("R,most", [(16, 512), (40, 512), (60, 256), (24, 128), (200, 256)])
+@pytest.mark.parametrize("over", [0, 1])
+def test_segments_as_large_as_a_batch_allows(jx, dtype, d, R, most, over):
+    """A hub that every point of a batch links to: its segment holds a full row and the whole batch, as many candidates as the
+    kernels that such a batch launches take, and one more.  The table is the oracle's."""
+    B = most - R + over
+    rng = np.random.default_rng(most + R)
+    near = rng.integers(0, 3, (520, d))
+    near[0] = 1
+    x = np.concatenate([near + 40, rng.integers(0, 90, (300, d))]).astype(dtype) if dtype == np.uint8 else \
+        np.concatenate([near, rng.integers(-30, 30, (300, d))]).astype(dtype)
+    hub = x[:1].repeat(B, axis=0).astype(np.int64)
+    hub[np.arange(B), rng.integers(0, d, B)] += rng.integers(1, 6, B)  # each nearest to the hub
+    n = len(x) + B
+    ref = oracle.Index(d, dtype, R, 64, 1.2, n, batch_growth=1.0)
+    g = jx.Index(d, jx_dtype(jx, x), R, 64, 1.2, capacity=n, max_batch=n, batch_growth=1.0)
+    for part in (x, hub.astype(dtype)):
+        ref.insert(part)
+        g.insert(dev(part))
+        assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0])
