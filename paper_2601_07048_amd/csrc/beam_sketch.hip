@@ -89,8 +89,11 @@ __global__ void __launch_bounds__(256) sketch_kernel(const float* x, long long n
 }
 
 hipError_t launch_sketch(const float* x, long long n, int d, uint8_t* sk, int stride, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(sketch_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, x, n, d, sk, stride);
+    const long long most = 1 << 24;  // a launch has fewer than 2^32 threads
+    for (long long i = 0; i < n; i += most) {
+        const long long m = n - i < most ? n - i : most;
+        hipLaunchKernelGGL(sketch_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, x + (size_t)i * d, m, d, sk + (size_t)i * stride, stride);
+    }
     return hipGetLastError();
 }
 
