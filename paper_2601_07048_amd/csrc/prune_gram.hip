@@ -121,7 +121,7 @@ struct TeamLds {
 // distances in L->dp.  truncated: further candidates, none before the last one here, exist beyond the pool.  All threads
 // of the workgroup call; the arrays are visible (a barrier after they were filled).  Returns the number selected
 // (L->sel_id / L->sel_dist, visible to all), or -1 if the pool did not suffice.
-template <int DT, int NB, bool LONG>
+template <int DT, int NB>
 __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, int vec_bytes, TeamLds<DT, NB>* L, int m, int n_fixed,
                                           uint32_t p, int R, float alpha, bool truncated) {
     using Lds = TeamLds<DT, NB>;
@@ -180,20 +180,17 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
             }
         }
     };
-    auto gram = [&](auto parts) __attribute__((always_inline)) {
-    constexpr int PARTS = decltype(parts)::value;
     if (mine) fetch(0);
     for (int p0 = 0; p0 < vec_bytes; p0 += 128) {
         if (mine) {
             if constexpr (DT == JX_F32) {
-                uint8_t* at = own + (((piece >> 2) * (2 * PARTS) + ((piece >> 1) & 1)) * GT_PIECE) + (piece & 1) * 8 + r8 * 16;
+                uint8_t* at = own + (((piece >> 2) * 6 + ((piece >> 1) & 1)) * GT_PIECE) + (piece & 1) * 8 + r8 * 16;
 #pragma unroll
                 for (int s = 0; s < 4; s++) {
                     float v0 = __uint_as_float(x[s].x) - __uint_as_float(c.x), v1 = __uint_as_float(x[s].y) - __uint_as_float(c.y);
                     float v2 = __uint_as_float(x[s].z) - __uint_as_float(c.z), v3 = __uint_as_float(x[s].w) - __uint_as_float(c.w);
-                    if (PARTS == 2) fnn[s] += fmaf(v3, v3, fmaf(v2, v2, fmaf(v1, v1, v0 * v0)));
 #pragma unroll
-                    for (int part = 0; part < PARTS; part++) {
+                    for (int part = 0; part < 3; part++) {
                         uint2 h;
                         h.x = take_bf16(v0, v1);
                         h.y = take_bf16(v2, v3);
@@ -233,10 +230,10 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
         if (mine) {
             const uint8_t* opnd = L->slab + half * GT_PIECE + col * 16;
             if constexpr (DT == JX_F32) {
-                bf16x8_t a[2][PARTS];
+                bf16x8_t a[2][3];
 #pragma unroll
-                for (int q = 0; q < 2 * PARTS; q++)
-                    a[q / PARTS][q % PARTS] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)wave * BLOCK + q * 2 * GT_PIECE);
+                for (int q = 0; q < 6; q++)
+                    a[q / 3][q % 3] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)wave * BLOCK + q * 2 * GT_PIECE);
 #pragma unroll
                 for (int t = 0; t < TILES; t++) {
                     if (2 * t < nb || t == 0 || (2 * t == nb && wave < t)) {  // uniform
@@ -247,15 +244,13 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
                         for (int e = 0; e < 16; e++) part[e] = 0.f;
 #pragma unroll
                         for (int ks = 0; ks < 2; ks++) {
-                            bf16x8_t b[PARTS];
+                            bf16x8_t b[3];
 #pragma unroll
-                            for (int q = 0; q < PARTS; q++)
-                                b[q] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)bj * BLOCK + (ks * PARTS + q) * 2 * GT_PIECE);
-                            if constexpr (PARTS == 3) {
-                                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][2], b[0], part, 0, 0, 0);
-                                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[2], part, 0, 0, 0);
-                                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[1], part, 0, 0, 0);
-                            }
+                            for (int q = 0; q < 3; q++)
+                                b[q] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)bj * BLOCK + (ks * 3 + q) * 2 * GT_PIECE);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][2], b[0], part, 0, 0, 0);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[2], part, 0, 0, 0);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[1], part, 0, 0, 0);
                             part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[0], part, 0, 0, 0);
                             part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[1], part, 0, 0, 0);
                             part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[0], part, 0, 0, 0);
@@ -286,23 +281,9 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
         }
         __syncthreads();
     }
-    };
-    gram(std::integral_constant<int, LONG ? 2 : 3>());
     // Accumulator layout of the 32x32 tiles: register e of lane (col, half) holds row 8*(e/4) + 4*half + e%4, column col.
-    // ---- G_jj from the diagonal tiles (float32: the sums of the centred values' squares), d(p, j) of the candidates that came without
-    if (LONG && tid == 0) L->pairs = 0;
-    if (LONG && mine) {
-#pragma unroll
-        for (int s = 0; s < 4; s++) {
-            const float n = group_sum<8>(fnn[s]);
-            const int slot = wave * 32 + s * 8 + r8;
-            if (piece == 0) {
-                L->nrm[slot] = n;
-                if (slot < n_fixed) L->dp[slot] = n;
-            }
-        }
-    }
-    if (!LONG && mine) {
+    // ---- G_jj from the diagonal tiles, d(p, j) of the candidates that came without
+    if (mine) {
         const int hcol = (col >> 2) & 1, ecol = ((col >> 3) << 2) | (col & 3);
         float dv = 0.f;
 #pragma unroll
@@ -370,23 +351,6 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
     // ---- the discard relation, tile by tile.  Candidates that came in order (n_fixed = 0) are discarded by those of their own
     // block and of blocks before it only: half of it
     const bool sorted = n_fixed == 0;
-    if (LONG && tid < m && L->nrm[tid] > 0.f && L->nrm[tid] < GT_TINY) L->pairs = GT_PAIRS + 1;
-    const float two = GT_TWO * 1.01f * alpha;
-    // undecided: |alpha d(i,j) - d(p,j)| within alpha times the error of d(i,j), 2 GT_TWO |x_i| |x_j| at most.  An infinite d(p,j)
-    // is decided
-    auto list = [&](const typename GAcc<DT>::type& g, const float nj, const int j, const float dpj, const uint32_t rj, const bool j_first) __attribute__((always_inline)) {
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-            const int i = wave * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-            const float ni = L->nrm[i], dv = j_first ? L->dp[i] : dpj;
-            const uint32_t ri = L->rank[i];
-            if ((j_first ? rj < ri : ri < rj) && fmaf(-two, ni + nj, fabsf(__fmul_rn(alpha, gram_dist<DT>(ni, nj, g[e])) - dv)) < 0.f) {
-                const int at = atomicAdd(&L->pairs, 1);
-                if (at < GT_PAIRS) L->pair[at] = j_first ? (uint32_t)(j << 16 | i) : (uint32_t)(i << 16 | j);
-            }
-        }
-    };
-    auto relate = [&](const bool mark) __attribute__((always_inline)) {
     if (mine) {
 #pragma unroll
         for (int t = 0; t < TILES; t++) {
@@ -398,7 +362,6 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
                 const bool fwd = !sorted || wave <= bj, back = t > 0 && (!sorted || bj < wave);
                 uint32_t victim_j = 0, victim_i = 0;
                 if (fwd) {
-                    float near = 0.f;
 #pragma unroll
                     for (int g = 0; g < 4; g++) {
                         const int i0 = wave * 32 + 8 * g + 4 * half;
@@ -410,16 +373,13 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
                         for (int f = 0; f < 4; f++) {
                             const float ad = __fmul_rn(alpha, gram_dist<DT>(ni[f], nj, acc[t][4 * g + f]));
                             if (ri[f] < rj && ad <= dpj) victim_j |= 1u << (8 * g + f);
-                            if (LONG && mark) near = fminf(near, fmaf(-two, ni[f] + nj, fabsf(ad - dpj)));
                         }
                     }
-                    if (LONG && mark) if (ballot(near < 0.f)) list(acc[t], nj, j, dpj, rj, false);
                     victim_j <<= 4 * half;
                     victim_j |= shfl_xor(victim_j, 32);
                     if (half == 0) L->kb[wave * Lds::M + j] = victim_j;
                 }
                 if (back) {
-                    float near = 0.f;
 #pragma unroll
                     for (int g = 0; g < 4; g++) {
                         const int i0 = wave * 32 + 8 * g + 4 * half;
@@ -432,46 +392,11 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
                         for (int f = 0; f < 4; f++) {
                             const float ad = __fmul_rn(alpha, gram_dist<DT>(ni[f], nj, acc[t][4 * g + f]));
                             const uint64_t mi = ballot(rj < ri[f] && ad <= di[f]);
-                            if (LONG && mark) near = fminf(near, fmaf(-two, ni[f] + nj, fabsf(ad - di[f])));
                             const uint32_t row = (col & 4) ? (uint32_t)(mi >> 32) : (uint32_t)mi;  // of the lane's own row, if it is among these two
                             if (4 * g + f == (((col >> 3) << 2) | (col & 3))) victim_i = row;
                         }
                     }
-                    if (LONG && mark) if (ballot(near < 0.f)) list(acc[t], nj, j, dpj, rj, true);
                     if (half == 0) L->kb[bj * Lds::M + wave * 32 + col] = victim_i;
-                }
-            }
-        }
-    }
-    };
-    relate(LONG);
-    if constexpr (LONG) {
-        __syncthreads();
-        const int pairs = L->pairs;
-        if (pairs > GT_PAIRS) {  // ties by the hundred, or squares too small: the products of three parts
-            __syncthreads();
-#pragma unroll
-            for (int t = 0; t < TILES; t++)
-#pragma unroll
-                for (int e = 0; e < 16; e++) acc[t][e] = 0;
-            gram(std::integral_constant<int, 3>());
-            relate(false);
-        } else {
-            for (int k = wave; k < pairs; k += NB) {  // a wavefront per pair: the float32 distance of the vectors
-                const uint32_t ij = L->pair[k];
-                const int i = (int)(ij >> 16), j = (int)(ij & 0xFFFFu);
-                const float* xi = reinterpret_cast<const float*>(recs + (size_t)L->id[i] * stride);
-                const float* xj = reinterpret_cast<const float*>(recs + (size_t)L->id[j] * stride);
-                float d = 0.f;
-                for (int e = lane * 4; e < vec_bytes / 4; e += 256) {
-                    const float4 u = *reinterpret_cast<const float4*>(xi + e), w = *reinterpret_cast<const float4*>(xj + e);
-                    d += fmaf(u.w - w.w, u.w - w.w, fmaf(u.z - w.z, u.z - w.z, fmaf(u.y - w.y, u.y - w.y, (u.x - w.x) * (u.x - w.x))));
-                }
-                d = group_sum<64>(d);
-                uint32_t* word = &L->kb[(i >> 5) * Lds::M + j];
-                if (lane == 0) {
-                    if (__fmul_rn(alpha, d) <= L->dp[j]) atomicOr(word, 1u << (i & 31));
-                    else atomicAnd(word, ~(1u << (i & 31)));
                 }
             }
         }
@@ -540,6 +465,347 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
     return L->nsel;
 }
 
+// The last two parts of team_prune, for team_prune_long.  The two functions share no code on purpose: as one template the binary16
+// kernels, whose registers spill, came out slower (a deletion from 6,292 x 128 1,295 -> 1,400 us, from 6,736 x 128 1,508 -> 1,570).
+// Ranks of all candidates where some came without their distance.  All threads of the workgroup
+template <int DT, int NB>
+__device__ __forceinline__ void team_ranks(TeamLds<DT, NB>* L, const int m, const int n_fixed, const int tid) {
+    if (n_fixed > 0) {
+        // ranks: the candidates of known distance are in order already
+        uint64_t k = 0;
+        if (tid < m) {
+            k = ((uint64_t)__float_as_uint(L->dp[tid]) << 32) | L->id[tid];
+            L->key[tid] = k;
+        }
+        __syncthreads();
+        if (tid < m) {
+            int rank = tid < n_fixed ? 0 : tid - n_fixed;
+            for (int t = 0; t < n_fixed; t++) {
+                const uint64_t o = L->key[t];
+                rank += (o < k || (o == k && t < tid)) ? 1 : 0;
+            }
+            if (tid < n_fixed) {
+                int lo = n_fixed, hi = m;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (L->key[mid] < k) lo = mid + 1;
+                    else hi = mid;
+                }
+                rank += lo - n_fixed;
+            }
+            L->rank[tid] = (uint32_t)rank;
+        }
+        __syncthreads();
+    }
+}
+
+// Alg. 3 on the masks of L->kb, by the first wavefront; the number selected, as team_prune returns it
+template <int DT, int NB>
+__device__ __forceinline__ int team_select(TeamLds<DT, NB>* L, const int m, const int nb, const bool sorted, const uint32_t p, const int R,
+                                           const bool truncated, const int wave, const int lane) {
+    using Lds = TeamLds<DT, NB>;
+    if (wave == 0) {
+        constexpr int H = NB / 2;
+        uint32_t kw[H][NB];
+        uint64_t U[H], S[H];
+#pragma unroll
+        for (int h = 0; h < H; h++) {
+            const int slot = h * 64 + lane;
+            const bool on = slot < m;
+#pragma unroll
+            for (int w = 0; w < NB; w++) kw[h][w] = on && w < nb && (!sorted || w <= slot >> 5) ? L->kb[w * Lds::M + slot] : 0u;
+            U[h] = ballot(on && L->id[on ? slot : 0] != p);
+            S[h] = 0;
+            L->by_rank[slot] = JX_NONE_ID;
+        }
+        for (;;) {
+            uint64_t any = 0, ns[H], nd[H];
+#pragma unroll
+            for (int h = 0; h < H; h++) any |= U[h];
+            if (!any) break;
+#pragma unroll
+            for (int h = 0; h < H; h++) {
+                uint32_t dead = 0, wait = 0;
+#pragma unroll
+                for (int w = 0; w < NB; w++) {
+                    dead |= kw[h][w] & (uint32_t)(S[w >> 1] >> (32 * (w & 1)));
+                    wait |= kw[h][w] & (uint32_t)(U[w >> 1] >> (32 * (w & 1)));
+                }
+                ns[h] = ballot(dead == 0 && wait == 0) & U[h];
+                nd[h] = ballot(dead != 0) & U[h];
+            }
+#pragma unroll
+            for (int h = 0; h < H; h++) {
+                U[h] &= ~(ns[h] | nd[h]);
+                S[h] |= ns[h];
+            }
+        }
+        wave_sync();
+#pragma unroll
+        for (int h = 0; h < H; h++)
+            if ((S[h] >> lane) & 1ull) L->by_rank[L->rank[h * 64 + lane]] = (uint32_t)(h * 64 + lane);
+        wave_sync();
+        const int tau = (int)L->rank[m > 0 ? m - 1 : 0];
+        int nsel = 0, inside = 0;
+#pragma unroll
+        for (int h = 0; h < H; h++) {
+            const uint32_t slot = L->by_rank[h * 64 + lane];
+            const uint64_t on = ballot(slot != JX_NONE_ID);
+            const int pos = nsel + prefix_count(on);
+            if (slot != JX_NONE_ID && pos < R) {
+                L->sel_id[pos] = L->id[slot];
+                L->sel_dist[pos] = __float_as_uint(L->dp[slot]);
+            }
+            nsel += __builtin_popcountll(on);
+            inside += __builtin_popcountll(ballot(slot != JX_NONE_ID && h * 64 + lane <= tau));
+        }
+        // beyond the last candidate of known distance an excluded one could come first
+        if (lane == 0) L->nsel = truncated && inside < R ? -1 : (nsel < R ? nsel : R);
+    }
+    __syncthreads();
+    return L->nsel;
+}
+
+// The same for long float32 vectors: two parts first (see above).
+template <int NB>
+__device__ __forceinline__ int team_prune_long(const uint8_t* recs, size_t stride, int vec_bytes, TeamLds<JX_F32, NB>* L, int m, int n_fixed,
+                                          uint32_t p, int R, float alpha, bool truncated) {
+    constexpr int DT = JX_F32;
+    using Lds = TeamLds<DT, NB>;
+    constexpr int TILES = NB / 2 + 1;
+    constexpr int BLOCK = Lds::PIECES * GT_PIECE;
+    const int tid = threadIdx.x;
+    int lane = lane_id();
+    asm volatile("" : "+v"(lane));  // what follows from it is worked out here and not kept across a caller's loop: no registers for that
+    const int col = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nb = (m + 31) >> 5;
+    const bool mine = wave < nb;
+    if (tid < 32 * nb) {
+        L->rank[tid] = tid < m ? (uint32_t)tid : 0xFFFFu;
+        if (tid >= m) L->dp[tid] = -1.f;
+    }
+    typename GAcc<DT>::type acc[TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; t++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) acc[t][e] = 0;
+    // staging: a load covers 8 rows x 128 bytes
+    const int piece = lane & 7, r8 = lane >> 3;
+    const uint8_t* rp[4];
+    const uint8_t* pp = recs + (size_t)p * stride + piece * 16;
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+        const int slot = wave * 32 + s * 8 + r8;
+        rp[s] = recs + (size_t)(slot < m ? L->id[slot] : p) * stride + piece * 16;
+    }
+    float fnn[4] = {0.f, 0.f, 0.f, 0.f};
+    uint8_t* own = L->slab + (size_t)wave * BLOCK;
+    uint4 x[4], c;
+    auto fetch = [&](int p0) {
+        if (p0 + 128 <= vec_bytes) {  // uniform: no lane's load waits for a branch
+            c = load16(pp + p0);
+#pragma unroll
+            for (int s = 0; s < 4; s++) x[s] = load16(rp[s] + p0);
+        } else {  // the last piece of a row: zeros (after the shift) beyond the data
+            const bool in = p0 + piece * 16 < vec_bytes;
+            const uint4 zero = make_uint4(0, 0, 0, 0);
+            c = in ? load16(pp + p0) : zero;
+#pragma unroll
+            for (int s = 0; s < 4; s++) x[s] = in ? load16(rp[s] + p0) : zero;
+        }
+    };
+    auto gram = [&](auto parts) __attribute__((always_inline)) {
+    constexpr int PARTS = decltype(parts)::value;
+    if (mine) fetch(0);
+    for (int p0 = 0; p0 < vec_bytes; p0 += 128) {
+        if (mine) {
+            {
+                uint8_t* at = own + (((piece >> 2) * (2 * PARTS) + ((piece >> 1) & 1)) * GT_PIECE) + (piece & 1) * 8 + r8 * 16;
+#pragma unroll
+                for (int s = 0; s < 4; s++) {
+                    float v0 = __uint_as_float(x[s].x) - __uint_as_float(c.x), v1 = __uint_as_float(x[s].y) - __uint_as_float(c.y);
+                    float v2 = __uint_as_float(x[s].z) - __uint_as_float(c.z), v3 = __uint_as_float(x[s].w) - __uint_as_float(c.w);
+                    if (PARTS == 2) fnn[s] += fmaf(v3, v3, fmaf(v2, v2, fmaf(v1, v1, v0 * v0)));
+#pragma unroll
+                    for (int part = 0; part < PARTS; part++) {
+                        uint2 h;
+                        h.x = take_bf16(v0, v1);
+                        h.y = take_bf16(v2, v3);
+                        *reinterpret_cast<uint2*>(at + part * 2 * GT_PIECE + s * 128) = h;
+                    }
+                }
+            }
+            if (p0 + 128 < vec_bytes) fetch(p0 + 128);
+        }
+        __syncthreads();
+        if (mine) {
+            const uint8_t* opnd = L->slab + half * GT_PIECE + col * 16;
+            {
+                bf16x8_t a[2][PARTS];
+#pragma unroll
+                for (int q = 0; q < 2 * PARTS; q++)
+                    a[q / PARTS][q % PARTS] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)wave * BLOCK + q * 2 * GT_PIECE);
+#pragma unroll
+                for (int t = 0; t < TILES; t++) {
+                    if (2 * t < nb || t == 0 || (2 * t == nb && wave < t)) {  // uniform
+                        const int bj = wave + t < nb ? wave + t : wave + t - nb;
+                        // a sum of its own for the 32 coordinates of the slab, the smallest products first
+                        f32x16_t part;
+#pragma unroll
+                        for (int e = 0; e < 16; e++) part[e] = 0.f;
+#pragma unroll
+                        for (int ks = 0; ks < 2; ks++) {
+                            bf16x8_t b[PARTS];
+#pragma unroll
+                            for (int q = 0; q < PARTS; q++)
+                                b[q] = *reinterpret_cast<const bf16x8_t*>(opnd + (size_t)bj * BLOCK + (ks * PARTS + q) * 2 * GT_PIECE);
+                            if constexpr (PARTS == 3) {
+                                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][2], b[0], part, 0, 0, 0);
+                                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[2], part, 0, 0, 0);
+                                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[1], part, 0, 0, 0);
+                            }
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][1], b[0], part, 0, 0, 0);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[1], part, 0, 0, 0);
+                            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][0], b[0], part, 0, 0, 0);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 16; e++) acc[t][e] += part[e];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    };
+    gram(std::integral_constant<int, 2>());
+    // Accumulator layout of the 32x32 tiles: register e of lane (col, half) holds row 8*(e/4) + 4*half + e%4, column col.
+    // ---- G_jj from the diagonal tiles (float32: the sums of the centred values' squares), d(p, j) of the candidates that came without
+    if (tid == 0) L->pairs = 0;
+    if (mine) {
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            const float n = group_sum<8>(fnn[s]);
+            const int slot = wave * 32 + s * 8 + r8;
+            if (piece == 0) {
+                L->nrm[slot] = n;
+                if (slot < n_fixed) L->dp[slot] = n;
+            }
+        }
+    }
+    __syncthreads();
+    team_ranks<DT, NB>(L, m, n_fixed, tid);
+    // ---- the discard relation, tile by tile.  Candidates that came in order (n_fixed = 0) are discarded by those of their own
+    // block and of blocks before it only: half of it
+    const bool sorted = n_fixed == 0;
+    if (tid < m && L->nrm[tid] > 0.f && L->nrm[tid] < GT_TINY) L->pairs = GT_PAIRS + 1;
+    const float two = GT_TWO * 1.01f * alpha;
+    // undecided: |alpha d(i,j) - d(p,j)| within alpha times the error of d(i,j), 2 GT_TWO |x_i| |x_j| at most.  An infinite d(p,j)
+    // is decided
+    auto list = [&](const typename GAcc<DT>::type& g, const float nj, const int j, const float dpj, const uint32_t rj, const bool j_first) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int i = wave * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+            const float ni = L->nrm[i], dv = j_first ? L->dp[i] : dpj;
+            const uint32_t ri = L->rank[i];
+            if ((j_first ? rj < ri : ri < rj) && fmaf(-two, ni + nj, fabsf(__fmul_rn(alpha, gram_dist<DT>(ni, nj, g[e])) - dv)) < 0.f) {
+                const int at = atomicAdd(&L->pairs, 1);
+                if (at < GT_PAIRS) L->pair[at] = j_first ? (uint32_t)(j << 16 | i) : (uint32_t)(i << 16 | j);
+            }
+        }
+    };
+    auto relate = [&](const bool mark) __attribute__((always_inline)) {
+    if (mine) {
+#pragma unroll
+        for (int t = 0; t < TILES; t++) {
+            if (2 * t < nb || t == 0 || (2 * t == nb && wave < t)) {  // uniform
+                const int bj = wave + t < nb ? wave + t : wave + t - nb;
+                const int j = bj * 32 + col;
+                const float nj = L->nrm[j], dpj = L->dp[j];
+                const uint32_t rj = L->rank[j];
+                const bool fwd = !sorted || wave <= bj, back = t > 0 && (!sorted || bj < wave);
+                uint32_t victim_j = 0, victim_i = 0;
+                if (fwd) {
+                    float near = 0.f;
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        const int i0 = wave * 32 + 8 * g + 4 * half;
+                        const float4 n4 = *reinterpret_cast<const float4*>(&L->nrm[i0]);
+                        const uint4 r4 = *reinterpret_cast<const uint4*>(&L->rank[i0]);
+                        const float ni[4] = {n4.x, n4.y, n4.z, n4.w};
+                        const uint32_t ri[4] = {r4.x, r4.y, r4.z, r4.w};
+#pragma unroll
+                        for (int f = 0; f < 4; f++) {
+                            const float ad = __fmul_rn(alpha, gram_dist<DT>(ni[f], nj, acc[t][4 * g + f]));
+                            if (ri[f] < rj && ad <= dpj) victim_j |= 1u << (8 * g + f);
+                            if (mark) near = fminf(near, fmaf(-two, ni[f] + nj, fabsf(ad - dpj)));
+                        }
+                    }
+                    if (mark && ballot(near < 0.f)) list(acc[t], nj, j, dpj, rj, false);
+                    victim_j <<= 4 * half;
+                    victim_j |= shfl_xor(victim_j, 32);
+                    if (half == 0) L->kb[wave * Lds::M + j] = victim_j;
+                }
+                if (back) {
+                    float near = 0.f;
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        const int i0 = wave * 32 + 8 * g + 4 * half;
+                        const float4 n4 = *reinterpret_cast<const float4*>(&L->nrm[i0]);
+                        const float4 d4 = *reinterpret_cast<const float4*>(&L->dp[i0]);
+                        const uint4 r4 = *reinterpret_cast<const uint4*>(&L->rank[i0]);
+                        const float ni[4] = {n4.x, n4.y, n4.z, n4.w}, di[4] = {d4.x, d4.y, d4.z, d4.w};
+                        const uint32_t ri[4] = {r4.x, r4.y, r4.z, r4.w};
+#pragma unroll
+                        for (int f = 0; f < 4; f++) {
+                            const float ad = __fmul_rn(alpha, gram_dist<DT>(ni[f], nj, acc[t][4 * g + f]));
+                            const uint64_t mi = ballot(rj < ri[f] && ad <= di[f]);
+                            if (mark) near = fminf(near, fmaf(-two, ni[f] + nj, fabsf(ad - di[f])));
+                            const uint32_t row = (col & 4) ? (uint32_t)(mi >> 32) : (uint32_t)mi;  // of the lane's own row, if it is among these two
+                            if (4 * g + f == (((col >> 3) << 2) | (col & 3))) victim_i = row;
+                        }
+                    }
+                    if (mark && ballot(near < 0.f)) list(acc[t], nj, j, dpj, rj, true);
+                    if (half == 0) L->kb[bj * Lds::M + wave * 32 + col] = victim_i;
+                }
+            }
+        }
+    }
+    };
+    relate(true);
+    __syncthreads();
+    const int pairs = L->pairs;
+    if (pairs > GT_PAIRS) {  // ties by the hundred, or squares too small: the products of three parts
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < TILES; t++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[t][e] = 0;
+        gram(std::integral_constant<int, 3>());
+        relate(false);
+    } else {
+        for (int k = wave; k < pairs; k += NB) {  // a wavefront per pair: the float32 distance of the vectors
+            const uint32_t ij = L->pair[k];
+            const int i = (int)(ij >> 16), j = (int)(ij & 0xFFFFu);
+            const float* xi = reinterpret_cast<const float*>(recs + (size_t)L->id[i] * stride);
+            const float* xj = reinterpret_cast<const float*>(recs + (size_t)L->id[j] * stride);
+            float d = 0.f;
+            for (int e = lane * 4; e < vec_bytes / 4; e += 256) {
+                const float4 u = *reinterpret_cast<const float4*>(xi + e), w = *reinterpret_cast<const float4*>(xj + e);
+                d += fmaf(u.w - w.w, u.w - w.w, fmaf(u.z - w.z, u.z - w.z, fmaf(u.y - w.y, u.y - w.y, (u.x - w.x) * (u.x - w.x))));
+            }
+            d = group_sum<64>(d);
+            uint32_t* word = &L->kb[(i >> 5) * Lds::M + j];
+            if (lane == 0) {
+                if (__fmul_rn(alpha, d) <= L->dp[j]) atomicOr(word, 1u << (i & 31));
+                else atomicAnd(word, ~(1u << (i & 31)));
+            }
+        }
+    }
+    __syncthreads();
+    return team_select<DT, NB>(L, m, nb, sorted, p, R, truncated, wave, lane);
+}
+
 // ---- forward prune of the candidate list of each new point (Alg. 4 step 2): lists of at most 128 (NB = 4), or of 129 to
 // 256 and the closest 256 of a longer one (NB = 8; exact if Alg. 3 finds R neighbours in them).  NB = 8 marks every point
 // of the batch in a.dead[i * a.L]: 0xFF = row and reverse edges written here, 0 = left to the list-based kernel (which
@@ -568,7 +834,9 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) forward_prune_gram_
         L->dp[j] = __uint_as_float(dbits[j]);
     }
     __syncthreads();
-    const int nsel = team_prune<DT, NB, LONG>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, m, 0, (uint32_t)xid, a.R, a.alpha, m < nB);
+    int nsel;
+    if constexpr (LONG) nsel = team_prune_long<NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, m, 0, (uint32_t)xid, a.R, a.alpha, m < nB);
+    else nsel = team_prune<DT, NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, m, 0, (uint32_t)xid, a.R, a.alpha, m < nB);
     if (NB == 8 && tid == 0) a.dead[(size_t)i * a.L] = nsel < 0 ? 0 : 0xFF;
     if (nsel < 0) return;
     if (DT == JX_U8 && tid == 0) a.clean[xid] = (uint8_t)(nsel < 255 ? nsel : 255);
@@ -672,7 +940,9 @@ __global__ void __launch_bounds__(NB * 64, GT_WAVES(DT, NB)) reverse_merge_gram_
             L->dp[deg + j] = __uint_as_float((uint32_t)a.keys[lo + j]);
         }
         __syncthreads();
-        const int nsel = team_prune<DT, NB, LONG>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, deg + mp, deg, v, a.R, a.alpha, mp < m);
+        int nsel;
+        if constexpr (LONG) nsel = team_prune_long<NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, deg + mp, deg, v, a.R, a.alpha, mp < m);
+        else nsel = team_prune<DT, NB>(a.ds.recs, (size_t)a.ds.rec_stride, a.ds.nch * 16, L, deg + mp, deg, v, a.R, a.alpha, mp < m);
         if (nsel >= 0) {
             for (int j = tid; j < a.R; j += NB * 64) row[j] = j < nsel ? L->sel_id[j] : JX_NONE_ID;
             if (DT == JX_U8 && tid == 0) a.clean[v] = (uint8_t)(nsel < 255 ? nsel : 255);
