@@ -130,10 +130,11 @@ typedef struct {
 /* Counters of one jx_search call, summed over its queries. */
 typedef struct {
     uint64_t hops;         /* expansions (adjacency rows read) */
-    uint64_t dist_evals;   /* distance evaluations in beamSearch */
+    uint64_t dist_evals;   /* distance evaluations in beamSearch, those that a byte copy decided among them */
     uint64_t adj_bytes;    /* hops * 4R */
-    uint64_t vec_bytes;    /* dist_evals * bytes of a record (beam_search_sketch_kernel fetches less) */
-    uint64_t rerank_bytes; /* exact re-rank reads */
+    uint64_t vec_bytes;    /* dist_evals * bytes of a record; where byte copies are read first, the vectors that were
+                              still read and the copies (a byte per dimension, padded to 16, and 16 more) */
+    uint64_t rerank_bytes; /* exact re-rank reads, counted alike */
     /* elapsed time of each stage of the call, from HIP events recorded on the
      * caller's stream around the stage's launches (summed over query slices) */
     float rotate_ms, prep_ms, beam_ms, rerank_ms;

@@ -6,8 +6,9 @@
 // x stands a record x' = m + s c with 8-bit codes c and e >= |x - x'|.  From |q - x| >= |q' - x'| - e - eq a neighbour whose
 // bound lies above the worst entry's distance cannot enter (a frontier changes by keys below the worst one only), and is
 // left out; the rest, 503 of 3,967 above, is evaluated on the vectors by eval_batch as in beam_search_kernel.  Frontier
-// sequence, results, expansion lists and counters are that kernel's, bit for bit, whatever the codes are worth: a loose
-// bound costs evaluations, never an entry.
+// sequence, results, expansion lists and number of expansions are that kernel's, bit for bit, whatever the codes are worth: a
+// loose bound costs evaluations, never an entry.  The number of neighbours looked at is not: the visited table is smaller here
+// (launch_sketch_shape) and forgets more of them.
 //
 // Bound: the gather.  Why matrix instructions: the query stands as 16-bit integers v = 256 h + l in rows of operand A (h
 // and l in turn, so that every lane group receives both sums), 16 neighbours' codes are operand B as they are loaded, and
@@ -297,7 +298,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
     const bool full = a.ds.nch == T * CPL;
     uint32_t hops = 0, evals = 0;
     uint64_t vk = 0;  // VIS: see visited_add
-    int tried = 0, kept = 0;  // by sketches
+    int tried = 0, kept = 0;  // by sketches: copies read, vectors read after them
 
     if (lane == 0) {  // seed: the entry vertex
         cand_id[0] = a.entry;
@@ -417,6 +418,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
         }
     } else {
         write_results<K_F32, NREG>(a, qi, fk, count, lane, hops, evals);
+        if (a.stats && lane == 0) {
+            unsigned long long* sp = a.stats + (size_t)(qi & 63) * 16;
+            atomicAdd(&sp[3], (unsigned long long)tried);
+            atomicAdd(&sp[4], (unsigned long long)(tried - kept));
+        }
     }
 }
 
@@ -455,7 +461,8 @@ __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
     if (lane < m) L->cand_id[lane] = id;
     wave_sync();
     int n = m;
-    if (m > a.k && !sq.none) {
+    const bool use = m > a.k && !sq.none;
+    if (use) {
         const float4 meta = *reinterpret_cast<const float4*>(a.sk + (size_t)L->cand_id[lane < m ? lane : 0] * (uint32_t)a.sk_stride + (size_t)a.sk_nch * 16);
         int il = 0, ih = 0;
         const uint8_t* lq = qpl + (lane & 1) * plane + (lane >> 4) * 16;
@@ -502,7 +509,11 @@ __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
             a.out_dist[qi * a.k + rank] = ordered_to_f32(key_dist(kj));
         }
     }
-    if (a.stats && lane == 0) atomicAdd(&a.stats[(size_t)(qi & 63) * 16 + 2], (unsigned long long)m);
+    if (a.stats && lane == 0) {
+        unsigned long long* sp = a.stats + (size_t)(qi & 63) * 16;
+        atomicAdd(&sp[2], (unsigned long long)n);
+        if (use) atomicAdd(&sp[5], (unsigned long long)m);
+    }
 }
 
 hipError_t launch_rerank_sketch(const RerankArgs& a, hipStream_t st, bool* done) {

@@ -589,17 +589,18 @@ static int search_common(jx_index* idx, const void* d_queries, int64_t nq, int32
         }
     }
     if (h_stats) {
-        unsigned long long stripes[64 * 16], hs[3] = {0, 0, 0};
+        unsigned long long stripes[64 * 16], hs[6] = {0, 0, 0, 0, 0, 0};
         JX_HIP(hipMemcpyAsync(stripes, idx->d_stripes, sizeof stripes, hipMemcpyDeviceToHost, st));
         JX_HIP(hipStreamSynchronize(st));
         for (int i = 0; i < 64; i++)
-            for (int c = 0; c < 3; c++) hs[c] += stripes[i * 16 + c];
+            for (int c = 0; c < 6; c++) hs[c] += stripes[i * 16 + c];
         memset(h_stats, 0, sizeof *h_stats);
         h_stats->hops = hs[0];
         h_stats->dist_evals = hs[1];
         h_stats->adj_bytes = hs[0] * 4ull * p.R;
-        h_stats->vec_bytes = hs[1] * (unsigned long long)(mode == JX_EXACT ? idx->vec_bytes : (idx->meta_chunk + 1) * 16);
-        h_stats->rerank_bytes = hs[2] * (unsigned long long)idx->vec_bytes;
+        const unsigned long long copy_bytes = ((p.dim + 15) / 16 + 1) * 16;  // codes and the meta chunk
+        h_stats->vec_bytes = (hs[1] - hs[4]) * (unsigned long long)(mode == JX_EXACT ? idx->vec_bytes : (idx->meta_chunk + 1) * 16) + hs[3] * copy_bytes;
+        h_stats->rerank_bytes = hs[2] * (unsigned long long)idx->vec_bytes + hs[5] * copy_bytes;
         h_stats->rotate_ms = tm.acc[0];
         h_stats->prep_ms = tm.acc[1];
         h_stats->beam_ms = tm.acc[2];

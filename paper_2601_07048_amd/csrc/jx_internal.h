@@ -40,7 +40,8 @@ struct BeamArgs {
     uint32_t* out_ids;     // [nq][out_k]
     float* out_dist;       // [nq][out_k]
     int out_k;
-    unsigned long long* stats;  // NULL, or 64 stripes of 16 counters (query i adds to stripe i % 64): [0] hops, [1] dist_evals
+    unsigned long long* stats;  // NULL, or 64 stripes of 16 counters (query i adds to stripe i % 64): [0] hops, [1] dist_evals,
+                                // [3] byte copies read, [4] vectors left out after that
     const uint8_t* deleted;     // [N] 1 = logically deleted (never returned), or NULL
     uint32_t flags;             // JX_FLAG_* switches that select a kernel variant
     int vis_cap;                // > 0 (a power of two <= 512): instead of the frontier, out_ids / out_dist [nq][vis_cap]
@@ -152,7 +153,7 @@ struct RerankArgs {
     int cand_stride, rr, k;
     uint32_t* out_ids;       // [nq][k]
     float* out_dist;
-    unsigned long long* stats;  // the same stripes: [2] += number of candidates
+    unsigned long long* stats;  // the same stripes: [2] vectors read, [5] byte copies read
     const uint8_t* sk;          // as in BeamArgs
     int sk_stride, sk_nch;
 };

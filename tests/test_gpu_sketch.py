@@ -4,7 +4,8 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_common import dev, random_data
+import oracle
+from gpu_common import dev, random_data, u32
 
 pytestmark = pytest.mark.gpu
 
@@ -127,3 +128,30 @@ def test_rerank_reads_what_may_be_among_the_first(jx, d, n):
         far = torch.stack([(x64[c] - v.double()).square().sum(1) for c, v in zip(cand, q)])
         want = cand.gather(1, far.sort(dim=1)[1][:, :k]).to(torch.int32)
         assert torch.equal(g.search(q, k, 70, mode=jx.RABITQ, rerank=rr)[0], want), (k, rr)
+
+
+def test_counters_count_what_is_read(jx):
+    """dist_evals lies between an exact visited set's count and that of no filter; vec_bytes and rerank_bytes are those of the
+    vectors that were read and of the byte copies, not of every neighbour and candidate.  Integer data: the oracle's walk."""
+    d, n, L, nq = 960, 5000, 64, 2100
+    rng = np.random.default_rng(71)
+    c = rng.integers(-20, 21, (8, d))
+    x, q = ((c[rng.integers(0, 8, m)] + rng.integers(-12, 13, (m, d))).astype(np.float32) for m in (n, nq))
+    g = jx.Index(d, jx.F32, 48, L, 1.2, capacity=n, max_batch=n, quant_bits=1)
+    g.insert(dev(x))
+    ref = oracle.Index(d, np.float32, 48, L, 1.2, n)
+    ref.set_graph(x, u32(g.export_graph()[0]), g.size()[1])
+    few = q[:600]
+    st = g.search(dev(few), 10, L, stats=True)[2]
+    assert st["beam_kernel"].startswith("beam_search_sketch_kernel<")
+    exact, none = ref.search(few, 10, L), ref.search(few, 10, L, filter=oracle.FILTER_NONE)
+    assert st["hops"] == exact["hops"]
+    assert exact["evals"] <= st["dist_evals"] <= none["evals"]
+    copy = d + 16  # bytes
+    # all were looked at through their copies but those before the frontier was full, which are read whole
+    assert 600 * L * 4 * d + (st["dist_evals"] - 600 * (L + 48)) * copy <= st["vec_bytes"] <= 0.75 * st["dist_evals"] * 4 * d
+    g.quantize(1, dev(np.linalg.qr(rng.standard_normal((d, d)))[0].astype(np.float32)), query_bits=4)
+    st = g.search(dev(q), 10, L, mode=jx.RABITQ, rerank=40, stats=True)[2]
+    assert nq * (10 * 4 * d + 40 * copy) <= st["rerank_bytes"] <= nq * (30 * 4 * d + 40 * copy)
+    st = g.search(dev(few), 10, L, mode=jx.RABITQ, rerank=40, stats=True)[2]
+    assert st["rerank_bytes"] == 600 * 40 * 4 * d
