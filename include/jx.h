@@ -71,7 +71,9 @@ extern "C" {
  * variant does the work, and exist for the kernel-variant ablation (Sec. 6.5
  * "Ablation study"; App. Block-Size, Tile Size and Load microbenchmarks) and
  * for comparisons in the tests.  Nothing in the library reads an environment
- * variable.
+ * variable.  A search that would read byte copies first (beam_search_sketch_kernel)
+ * reads whole vectors under a JX_FLAG_VISITED_*, TILED_LOADS, WAVES_* or QPW_*
+ * switch, and under LANES_WIDE up to 256 dimensions; it takes two to four times as long.
  */
 #define JX_FLAG_NO_PAIR (1u << 0)       /* beamSearch: never take two expansions per round */
 #define JX_FLAG_NO_INCR_PRUNE (1u << 1) /* uint8 reverse merge: every overflowing row is pruned as a

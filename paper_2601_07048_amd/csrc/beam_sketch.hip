@@ -575,9 +575,15 @@ static hipError_t launch_sketch_shape(BeamArgs a, hipStream_t st, char* name) {
 
 hipError_t launch_beam_sketch(int kind, const BeamArgs& a, hipStream_t st, char* name, bool* done) {
     *done = false;
-    const uint32_t prune_flags = JX_FLAG_NO_INCR_PRUNE | JX_FLAG_NO_GRAM | JX_FLAG_GRAM_U8;
-    if (kind != K_F32 || !a.sk || a.tag_bits == 0 || a.R > 64 || a.L > 256 || (a.flags & ~prune_flags)) return hipSuccess;
     const int nch = a.ds.nch;
+    // Switches that change nothing about these searches; with any other one whole vectors are read.  Batches that a team of
+    // wavefronts per query serves without a switch (launch_beam_ahead): with one they run on the one-wavefront kernel, whose
+    // visited table and counters are the team's.  A search for expansion lists has no other forms; a table of another kind has
+    // no tag_bits
+    uint32_t indifferent = JX_FLAG_NO_INCR_PRUNE | JX_FLAG_NO_GRAM | JX_FLAG_GRAM_U8;
+    if (a.nq > 512) indifferent |= JX_FLAG_NO_PAIR | JX_FLAG_LANES_NARROW | (nch > 64 ? JX_FLAG_LANES_WIDE : 0u);
+    if (a.vis_cap) indifferent = JX_FLAG_ALL;
+    if (kind != K_F32 || !a.sk || a.tag_bits == 0 || a.R > 64 || a.L > 256 || (a.flags & ~indifferent)) return hipSuccess;
     if (a.vis_cap && (a.L > 128 || nch <= 128)) return hipSuccess;
     // short vectors and wide frontiers: 60,000 x 200 at L = 128 / 200, 1,000 queries 439 / 596 -> 405 / 588 us, 3,500 473 / 701 ->
     // 429 / 863

@@ -155,3 +155,41 @@ def test_counters_count_what_is_read(jx):
     assert nq * (10 * 4 * d + 40 * copy) <= st["rerank_bytes"] <= nq * (30 * 4 * d + 40 * copy)
     st = g.search(dev(few), 10, L, mode=jx.RABITQ, rerank=40, stats=True)[2]
     assert st["rerank_bytes"] == 600 * 40 * 4 * d
+
+
+@pytest.mark.parametrize("d", [200, 960])
+def test_switches_of_other_kernels_leave_the_copies_in_use(jx, d):
+    """Two expansions per round and half the lanes per record are no forms of these searches, twice the lanes none of vectors of
+    more than 256 dimensions: such a switch changes nothing.  Those that ask for another kernel get it, as do all of them in
+    the batches of teams, and the results are the same."""
+    n = 20_000 if d == 200 else 5000
+    x, q = (dev(np.rint(4 * random_data(m, d, np.float32, s))) for m, s in ((n, 81), (600, 82)))  # exact in every order of sums
+    g = jx.Index(d, jx.F32, 64, 64, 1.2, capacity=n, max_batch=n)
+    g.insert(x)
+    ids0, dist0, st0 = g.search(q, 10, 64, stats=True)
+    assert st0["beam_kernel"].startswith("beam_search_sketch_kernel<")
+    none = (jx.FLAG_NO_PAIR, jx.FLAG_LANES_NARROW, jx.FLAG_NO_GRAM | jx.FLAG_NO_PAIR, jx.FLAG_NO_INCR_PRUNE)
+    other = (jx.FLAG_VISITED_IDS, jx.FLAG_VISITED_NONE | jx.FLAG_NO_PAIR) + ((jx.FLAG_WAVES_2,) if d == 960 else ())
+    for fl in none + other + (jx.FLAG_LANES_WIDE,):
+        g.set_flags(fl)
+        ids, dist, st = g.search(q, 10, 64, stats=True)
+        kept = fl in none or (fl == jx.FLAG_LANES_WIDE and d == 960)
+        assert st["beam_kernel"].startswith("beam_search_sketch_kernel<") == kept, (fl, st["beam_kernel"])
+        assert torch.equal(ids, ids0) and torch.equal(dist, dist0) and st["hops"] == st0["hops"], fl
+        if fl in none:
+            assert st["dist_evals"] == st0["dist_evals"], fl
+            st = g.search(q[:64], 10, 64, stats=True)[2]
+            assert st["beam_kernel"].startswith("beam_search_ahead_kernel<" if not fl & (jx.FLAG_NO_PAIR | jx.FLAG_LANES_NARROW) else "beam_search_kernel<"), fl
+
+
+@pytest.mark.parametrize("d", [960, 1536])
+def test_insertion_of_expansion_lists_reads_copies_under_switches(jx, d):
+    """Expansion lists have one kernel per visited table: graphs built under the other switches are the same."""
+    n = 6000
+    x = dev(random_data(n, d, np.float32, 91))
+    adj = []
+    for flags in (0, jx.FLAG_NO_PAIR, jx.FLAG_TILED_LOADS, jx.FLAG_WAVES_2, jx.FLAG_VISITED_IDS):
+        g = jx.Index(d, jx.F32, 64, 64, 1.2, capacity=n, max_batch=n, flags=flags, cand_mode=jx.CAND_VISITED)
+        g.insert(x)
+        adj.append(g.export_graph()[0])
+    assert all(torch.equal(a, adj[0]) for a in adj)
