@@ -204,10 +204,10 @@ def test_batches_of_more_workgroups_than_one_launch_takes(jx, L, logB):
 @pytest.mark.parametrize("d,R,L", [(160, 8, 31), (164, 63, 64), (260, 64, 129), (160, 40, 161), (516, 64, 256), (960, 30, 128), (1536, 48, 300)])
 @pytest.mark.parametrize("kind,alpha", [("wide", 1.2), ("wide", 1.0), ("bits", 1.0), ("bits", 1.25), ("tiny", 1.2), ("copies", 1.2)])
 def test_long_rows_take_two_parts_first(jx, d, R, L, kind, alpha):
-    """Rows of 640 bytes and more: comparisons that two bfloat16 parts leave open are settled by float32 distances, and by three
-    parts where there are hundreds of them (equal distances) or squares are subnormal.  Integers whose squared distances stay
-    below 2^24: of as many bits as that allows (up to 9, so the second part is needed), of one bit (ties), scaled by 2^-55, and
-    with many copies.  Every float32 sum is exact, so the table is the oracle's."""
+    """Rows of integers that take two bfloat16 parts first, and shorter ones: squared distances below 2^24, of coordinates of as many
+    bits as that allows (nine up to 164 dimensions, seven at 1536), of one bit (ties), scaled by 2^-55 (subnormal squares), and
+    with many copies.  Every float32 sum is exact, so the table is the oracle's.  The products of two parts are exact as well but
+    for the nine bits: test_two_parts_decide_nothing_within_their_error has rows where they are not."""
     n = 600
     rng = np.random.default_rng(d + L)
     lim = 1 if kind == "bits" else int(np.sqrt(2.0 ** 24 / d) / 2 * 0.99)
@@ -248,3 +248,62 @@ def test_segments_as_large_as_a_batch_allows(jx, dtype, d, R, most, over):
         ref.insert(part)
         g.insert(dev(part))
         assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0])
+
+
+@pytest.mark.parametrize("d,R,L", [(316, 30, 100), (320, 8, 31), (320, 63, 64), (516, 64, 129), (960, 64, 256), (1536, 48, 300)])
+@pytest.mark.parametrize("kind", ["near", "ties"])
+@pytest.mark.parametrize("alpha", [1.04, 1.5, 2.0])
+def test_two_parts_decide_nothing_within_their_error(jx, d, R, L, kind, alpha):
+    """Rows with one or two coordinates of +-1005, or of +-1004 .. 1006: ten bits, so a product of two second parts is missing
+    from what two parts give.  Squared distances are multiples of 1005^2, or a few units off: at alpha = 1.5 / 2 two parts alone
+    decide 16 / 6 comparisons of the 128 closest candidates wrongly where some 160 / 20 are undecided (near), and 2,100 / 77 of as
+    many (ties), on either side of what a prune settles pair by pair.  |x_i - p|^2 + |x_j - p|^2 stays below 2^24, where every sum is
+    exact, so the table is the oracle's."""
+    n = 600
+    rng = np.random.default_rng(d + L)
+    at = rng.choice(d, 24, replace=False)
+    x = np.zeros((n, d), np.float32)
+    for row in x[1:]:  # the first one stays at the origin: it is nearest to the mean of the others, which are at equal distances
+        m = rng.integers(1, 3)
+        row[rng.choice(at, m, replace=False)] = 1005 * rng.choice([-1, 1], m) + (rng.integers(-1, 2, m) if kind == "near" else 0)
+    ref = oracle.Index(d, np.float32, R, L, alpha, n, batch_growth=1.0)
+    g = jx.Index(d, jx.F32, R, L, alpha, capacity=n, max_batch=n, batch_growth=1.0)
+    for lo, hi in ((0, 250), (250, n)):
+        ref.insert(x[lo:hi])
+        g.insert(dev(x[lo:hi]))
+        assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), (lo, hi)
+    gone = rng.choice(n, n // 5, replace=False).astype(np.uint32)
+    ref.delete(gone); g.delete(dev(gone)); ref.consolidate(); g.consolidate()
+    assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), "consolidated"
+
+
+@pytest.mark.parametrize("d", [320, 960])
+def test_long_rows_that_are_not_finite(jx, d):
+    """As test_rows_that_are_not_finite, on rows that take two parts first."""
+    n = 600
+    x = random_data(n, d, np.float32, seed=4)
+    x[317, 3] = np.nan
+    x[400, :] = np.inf
+    x[401, 5] = -3.0e38
+    g = jx.Index(d, jx.F32, 16, 140, 1.2, capacity=n, max_batch=n)
+    g.insert(dev(x[:300]))
+    g.insert(dev(x[300:]))
+    adj = u32(g.export_graph()[0])
+    assert np.all((adj < n) | (adj == 0xFFFFFFFF))
+
+
+@pytest.mark.parametrize("d", [320, 960])
+def test_distances_of_long_rows_that_overflow(jx, d):
+    """As test_distances_that_overflow, on rows that take two parts first: their squares are summed apart from the products."""
+    n = 600
+    x = datagen.dyadic_grid(n, d, seed=5).astype(np.float32)
+    rng = np.random.default_rng(6)
+    far = rng.choice(n, 40, replace=False)
+    x[far] = (rng.uniform(1, 2, (40, d)) * 1e22).astype(np.float32)
+    for R, L in ((16, 60), (32, 140)):
+        gs = [jx.Index(d, jx.F32, R, L, 1.2, capacity=n, max_batch=n, batch_growth=1.0, flags=f) for f in (0, jx.FLAG_NO_GRAM)]
+        for lo, hi in ((0, 200), (200, 350), (350, n)):
+            for g in gs:
+                g.insert(dev(x[lo:hi]))
+            a, b = (u32(g.export_graph()[0]) for g in gs)
+            assert np.array_equal(a, b), (R, lo, np.flatnonzero((a != b).any(1))[:5])
