@@ -14,7 +14,7 @@
 //             sum of their own, added to the total by the vector unit, so the result is nearer to the exact one than that
 //             of the float32 instruction: relative error of d(i,j) against 64 bits, root mean square / largest,
 //             d = 128 1.1e-7 / 4.7e-7 (float32 instruction 2.9e-7 / 1.5e-6), d = 960 1.4e-7 / 5.5e-7 (7.1e-7 / 2.9e-6).
-//             Long vectors (LONG) take two parts and the three products of them first.  They leave d(i,j) uncertain by 6e-5 of
+//             Long vectors with alpha above 1 (LONG) take two parts and the three products of them first.  They leave d(i,j) uncertain by 6e-5 of
 //             |x_i|^2 + |x_j|^2, which settles all but a few of the 32,000 comparisons of a prune; for those the float32 distance
 //             of the two vectors is taken.  Where hundreds are undecided (ties), or squares are subnormal, the three parts are.
 //             G_jj is then a float32 sum of the centred values' squares.  Relative error against 64 bits, root mean square /
@@ -83,15 +83,23 @@ __device__ __forceinline__ uint32_t take_bf16(float& a, float& b) {
 #define GT_WAVES(DT, NB) ((DT) != JX_F32 ? 4 : (NB) == 4 ? 3 : 2)
 #define GT_SMALL 128
 #define GT_BIG 256
-#define GT_PAIRS 1024  // float32: a prune with more undecided pairs takes the three parts
+// float32: a prune with more undecided pairs takes the three parts on top.  Builds of 12,000 x 960 / 512 with 128 / 256 / 512 /
+// 1,024: coordinates of one bit, alpha = 1, 20.5 / 19.4 / 19.4 / 19.4 and 10.8 / 11.0 / 11.4 / 11.5 ms; twelve ones each, alpha = 1,
+// 27.7 / 27.9 / 28.7 / 30.5 and 12.8 / 13.0 / 13.6 / 15.7; of normal data, and of all of them with alpha = 1.2, the same
+#define GT_PAIRS 256
 // two parts: error of G_ij in |x_i| |x_j|.  Roundings to 8 bits leave up to 2^-8 and 2^-16 of a value: 2^-16 for the product of the
 // second parts, 2 x 2^-16 (1 + 2^-8) for what is behind them; sums of 32 coordinates and of the slabs, less than (6 + d / 32) 2^-24
 #define GT_TWO 6e-5f
 #define GT_TINY 1e-28f  // squares below this: products of the parts may be subnormal, and the bound above means nothing
-// float32 vectors of so many bytes take two parts first (LONG).  Builds, three parts / two: 20,000 x 960 31.0 / 27.5 ms, 20,000 x
-// 512 17.2 / 16.0, 40,000 x 200 17.1 / 16.8, 60,000 x 128 18.9 / 19.1: of short ones the relation is the longer part, and the
-// search for undecided pairs comes on top
-#define GT_LONG 640
+// float32 vectors of so many bytes take two parts first (LONG) where alpha is GT_ALPHA at least.  Builds, three parts / two:
+// 20,000 x 960 31.0 / 27.5 ms, 20,000 x 512 17.2 / 16.0, 16,000 x 320 13.25 / 12.8; at 200 dimensions and less 2 % and nothing: the
+// relation is the longer part there, and the search for undecided pairs comes on top.  Where distances tie the two parts are made
+// in vain.  Coordinates of one bit in clusters, alpha = 1.2: d = 164 9.7 / 10.2 ms, 256 9.7 / 10.0, 320 11.4 / 11.7, 512 11.1 /
+// 10.8, 960 19.9 / 17.7.  With alpha = 1 any two candidates as far from each other as from the vertex tie, so copies and
+// coordinates of few values do: d = 960 17.3 / 19.4, 512 9.9 / 10.9, copies of every vector 16.1 / 18.3 and 10.3 / 11.1, against
+// 18.6 / 17.6 and 11.2 / 11.2 of normal data; with alpha = 1.05 49.3 / 47.9, 10.0 / 9.9, 17.1 / 15.7, 10.9 / 10.6
+#define GT_LONG 1280
+#define GT_ALPHA 1.05f
 #define GT_PIECE 576  // bytes of 32 rows x 16 operand bytes, padded: 64 bytes further on in the banks from piece to piece
 
 template <int DT, int NB>
@@ -981,17 +989,19 @@ static hipError_t launch_reverse_gram_dt(const InsertArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+static bool two_parts_first(const InsertArgs& a) { return a.ds.nch * 16 >= GT_LONG && a.alpha >= GT_ALPHA; }
+
 hipError_t launch_forward_prune_gram(int dtype, const InsertArgs& a, hipStream_t st) {
     if (a.B <= 0) return hipSuccess;
     if (dtype == JX_U8) return launch_forward_gram_dt<JX_U8>(a, st);
     if (dtype == JX_F16) return launch_forward_gram_dt<JX_F16>(a, st);
-    return a.ds.nch * 16 >= GT_LONG ? launch_forward_gram_dt<JX_F32, true>(a, st) : launch_forward_gram_dt<JX_F32>(a, st);
+    return two_parts_first(a) ? launch_forward_gram_dt<JX_F32, true>(a, st) : launch_forward_gram_dt<JX_F32>(a, st);
 }
 
 hipError_t launch_reverse_merge_gram(int dtype, const InsertArgs& a, hipStream_t st) {
     if (dtype == JX_U8) return launch_reverse_gram_dt<JX_U8>(a, st);
     if (dtype == JX_F16) return launch_reverse_gram_dt<JX_F16>(a, st);
-    return a.ds.nch * 16 >= GT_LONG ? launch_reverse_gram_dt<JX_F32, true>(a, st) : launch_reverse_gram_dt<JX_F32>(a, st);
+    return two_parts_first(a) ? launch_reverse_gram_dt<JX_F32, true>(a, st) : launch_reverse_gram_dt<JX_F32>(a, st);
 }
 
 }  // namespace jx
