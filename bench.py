@@ -531,9 +531,9 @@ def ablate(args):
     # --- 128-byte uint8 vectors (the paper's BigANN axis)
     g, dq, gt, n = build(2)
     rows(f"workload 2 (N={n}, d=128 uint8, exact)", g, dq, gt, (16, 32, 96), [
-        ("default: tag table, 4 lanes x 2 chunks, chunked loads, 1 query per workgroup, two expansions per round where it applies", 0),
-        ("one expansion per round", F.FLAG_NO_PAIR),
+        ("default: tag table, 4 lanes x 2 chunks, chunked loads, 1 query per workgroup", 0),
         ("visited: direct-mapped table of full ids", F.FLAG_VISITED_IDS | F.FLAG_NO_PAIR),
+        ("the same, two expansions per round where it applies", F.FLAG_VISITED_IDS),
         ("visited: none (Alg. 2 as printed)", F.FLAG_VISITED_NONE),
         ("lanes per vector: 8 x 1 chunk", F.FLAG_LANES_WIDE | F.FLAG_NO_PAIR),
         ("lanes per vector: 2 x 4 chunks", F.FLAG_LANES_NARROW),

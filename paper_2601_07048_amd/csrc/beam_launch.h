@@ -21,13 +21,13 @@ static hipError_t launch_nreg(const BeamArgs& a, hipStream_t st, char* name) {
         // bandwidth, and the dropped second lists cost 12 % at d = 200, L = 128.
         // measured: +2..6 % for records of one 128-byte line from L = 64 (-3 % at L = 32); -8..-11 % for the 496- and
         // 208-byte records of d = 960 / 1536 codes, whose searches run at 7 TB/s and pay for every dropped list
-        // uint8 with one or two frontier registers: the tag table's own loop (MODE 1) with its row read ahead is ahead of it, pair /
-        // one expansion, L = 64 / 100 / 128: 300,000 x 128, 1,000 queries 127 / 122, 182 / 183, 214 / 213 us, 5,000 193 / 180, 280 /
-        // 280, 323 / 325; 1M 181 / 164, 250 / 241, 285 / 275 and 233 / 209, 380 / 369, 433 / 421; 20,000 x 128 97 / 86, 155 / 147,
-        // 193 / 181.  A few queries against a large index wait for memory (1M, one query, L = 100 107 / 108).  From 8,192 queries on
-        // the pair stays, though 4 to 12 % behind as well (10,000 on 1M 420 / 375, 563 / 538, 660 / 623): the parity test at full
-        // size holds it to the oracle there.  With four registers it wins (10,000 on 1M, L = 256 1,252 / 1,393)
-        const bool alone = KIND == K_U8 && nreg <= 2 && a.nq < 8192 && (a.nq >= 16 || nreg == 1) && beam_mode<KIND, T, CPL, 2, QB>(a) == 1;
+        // uint8 with one or two frontier registers and the tag table: that table's own loop (MODE 1) with its row read ahead is ahead
+        // of the pair, pair / one expansion, us, L = 64 / 96 / 128: 20,000 x 128, 10,000 queries 249 / 232, 420 / 388, 550 / 508;
+        // 300,000 283 / 267, 420 / 403, 514 / 494; 1M 421 / 382, 579 / 546, 697 / 666, 32,768 queries 1,192 / 1,052, 1,512 / 1,387,
+        // 1,813 / 1,663, 1,000 181 / 164, 250 / 241, 285 / 275, four 91 / 91, 142 / 134, 172 / 165 (300,000 114 / 112, 140 / 140).
+        // With four registers the pair wins (10,000 on 1M, L = 256 1,252 / 1,393), and with full ids in up to 10,000 queries (1M,
+        // L = 96, 1,000 queries 266 / 294, 10,000 709 / 720, 32,768 1,957 / 1,835)
+        const bool alone = KIND == K_U8 && nreg <= 2 && beam_mode<KIND, T, CPL, 2, QB>(a) == 1;
         if (nreg <= 4 && a.L >= 64 && a.R <= 64 && a.ds.rec_stride <= 128 && a.nq <= PAIR_MAX_QUERIES && H > 0 && !alone &&
             !(a.flags & JX_FLAG_NO_PAIR)) {
             const int pn = nreg <= 1 ? 1 : (nreg <= 2 ? 2 : 4);

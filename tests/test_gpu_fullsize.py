@@ -78,7 +78,7 @@ def test_fullsize_search_sampled_against_oracle(jx, big):
 
 def test_fullsize_kernel_variants_against_oracle_and_each_other(jx, big):
     """The variants of the beamSearch kernel that the library can be switched to (jx_set_flags) on the 1M-point
-    graph: one expansion per round instead of two, a table of full ids, no visited filter, one / four chunks per lane.
+    graph: one expansion per round, a table of full ids (two expansions per round), no visited filter, one / four chunks per lane.
     Each must give the oracle's ids and distances on sampled queries, and -- all 10,000 queries -- exactly the
     default variant's results and expansion count; the evaluation count changes only with the visited filter."""
     x, q, g, adj, deg = big
@@ -93,7 +93,8 @@ def test_fullsize_kernel_variants_against_oracle_and_each_other(jx, big):
         for L in (64, 96, 128, 256):   # 256: the four-register instance of the two-expansion kernel
             g.set_flags(0)
             ids0, dist0, st0 = g.search(dq, 10, L, stats=True)
-            assert st0["beam_kernel"].startswith("beam_search_pair_kernel<0,4,2,")
+            # two expansions per round are the faster form with four frontier registers only
+            assert st0["beam_kernel"].startswith("beam_search_pair_kernel<0,4,2,4," if L == 256 else "beam_search_kernel<0,4,2,"), L
             want = ref.search(q[sample], 10, L)
             no_filter = ref.search(q[sample], 10, L, filter=oracle.FILTER_NONE)
             assert np.array_equal(u32(ids0)[sample], want["ids"])
@@ -101,6 +102,7 @@ def test_fullsize_kernel_variants_against_oracle_and_each_other(jx, big):
                 g.set_flags(fl)
                 ids, dist, st = g.search(dq, 10, L, stats=True)
                 assert "pair" not in st["beam_kernel"] or not (fl & (jx.FLAG_NO_PAIR | jx.FLAG_VISITED_NONE)), name
+                assert "pair" in st["beam_kernel"] or fl != jx.FLAG_VISITED_IDS, name
                 assert np.array_equal(u32(ids)[sample], want["ids"]), (name, L)
                 assert np.array_equal(dist.cpu().numpy().astype(np.float64)[sample], want["dist"]), (name, L)
                 assert torch.equal(ids, ids0) and torch.equal(dist, dist0), (name, L)

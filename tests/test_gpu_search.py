@@ -255,6 +255,9 @@ def test_ablation_variants_uint8_bit_exact(jx, u8_case):
                 g.set_flags(fl)
                 ids, dist, st = g.beam_frontier(dev(q), L, stats=True)
                 names.add(st["beam_kernel"].split("<")[0] + "<" + ",".join(st["beam_kernel"].split("<")[1].split(",")[:3]))
+                # two expansions per round: with one and two frontier registers on a table of full ids, with four on either
+                if fl in (0, jx.FLAG_VISITED_IDS):
+                    assert ("pair" in st["beam_kernel"]) == (L == 200 or (L >= 64 and fl == jx.FLAG_VISITED_IDS)), (fl, L)
                 assert np.array_equal(u32(ids), ref["F_ids"]), (fl, L)
                 assert np.array_equal(dist.cpu().numpy().astype(np.float64), ref["F_dist"]), (fl, L)
                 assert st["hops"] == ref["hops"], (fl, L)
