@@ -150,12 +150,21 @@ typedef struct {
     char beam_kernel[96];
 } jx_stats;
 
-/* Bytes of device memory jx_create needs for these parameters (256-aligned
- * sub-buffers: vectors, adjacency, codes, rotation, workspaces). <0: JX_EINVAL. */
+/* Bytes of device memory jx_create takes for these parameters (256-aligned
+ * sub-buffers: vectors, adjacency, codes, rotation, workspaces, byte copies).
+ * <0: JX_EINVAL.  Byte copies belong to float32 indices of more than 128
+ * dimensions and at most 128 GiB of vectors where something reads them: R <= 64
+ * and a capacity of 4 MiB of vectors (16 MiB above 1,024 dimensions), or
+ * quant_bits != 0 and more than 256 dimensions.  They are the last
+ * capacity * s bytes (rounded up to 256), s = the next multiple of 64 of
+ * 16 + dim rounded up to 16, a quarter to a third of the vectors. */
 int64_t jx_arena_bytes(const jx_params* p);
 
 /* Create an empty index inside the caller's arena (device memory, at least
- * jx_arena_bytes(p) bytes, 256-byte aligned).  Enqueues a fill of the
+ * jx_arena_bytes(p) bytes, 256-byte aligned).  An arena that lacks the bytes of
+ * the byte copies is accepted: the index then has none, reads whole vectors,
+ * and returns the same results (searches of long vectors take two to four times
+ * as long).  Enqueues a fill of the
  * adjacency table with JX_NONE on `stream`.  *out is a host object freed by
  * jx_destroy. */
 int jx_create(const jx_params* p, void* d_arena, int64_t arena_bytes, void* stream, jx_index** out);

@@ -38,7 +38,7 @@ int fail(int code, const char* fmt, ...) {
 inline int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
 struct Layout {
-    int64_t vecs, adj, codes, sketch, P, centroid, stats, stripes, deleted, clean, work, work_bytes, total;
+    int64_t vecs, adj, codes, P, centroid, stats, stripes, deleted, clean, work, work_bytes, sketch, total;  // sketch: the least an arena needs
     int vec_bytes, code_bytes, meta_chunk, code_stride, sk_stride, plane_chunks, plane_shift;
 };
 
@@ -128,11 +128,18 @@ int64_t query_work(const jx_params* p, int64_t B, int plane_chunks, QueryWork* w
     return off;
 }
 
+// Byte copies are read where the vectors a search may meet take this much (figures at fill_sketch)
+int64_t sketch_least(int vec_bytes, bool insertion) { return vec_bytes <= 2048 || (insertion && vec_bytes <= 4096) ? 4 << 20 : 16 << 20; }
+
 // Bytes between the byte copies of float32 vectors (beam_sketch.hip), 0 = none: not of vectors of at most 512 bytes (300,000 x
 // 128, L = 16: 10,000 queries 324 -> 272 us, but L = 128 1,033 -> 1,064 and 1,000 queries 99 -> 109), nor of stores that leave
-// little of the card's memory
+// little of the card's memory, nor where nothing reads them: searches of rows of more than 64 neighbours or of fewer vectors than
+// fill_sketch asks for, and re-ranks of at most 256 dimensions (launch_beam_sketch, launch_rerank_sketch)
 int sketch_stride(const jx_params* p) {
-    if (p->dtype != JX_F32 || p->dim <= 128 || (int64_t)p->capacity * p->dim * 4 > (128ll << 30)) return 0;
+    const int64_t bytes = (int64_t)p->capacity * p->dim * 4;
+    if (p->dtype != JX_F32 || p->dim <= 128 || bytes > (128ll << 30)) return 0;
+    const bool searches = p->R <= 64 && bytes >= sketch_least(p->dim * 4, true), reranks = p->quant_bits && p->dim > 256;
+    if (!searches && !reranks) return 0;
     return ((p->dim + 15) / 16 * 16 + 16 + 63) / 64 * 64;
 }
 
@@ -155,9 +162,6 @@ void layout(const jx_params* p, Layout* L) {
     off += align256((int64_t)p->capacity * p->R * 4);
     L->codes = off;
     off += align256((int64_t)p->capacity * L->code_stride);
-    L->sk_stride = sketch_stride(p);
-    L->sketch = off;
-    off += align256((int64_t)p->capacity * L->sk_stride);
     L->P = off;
     off += align256(p->quant_bits ? (int64_t)p->dim * p->dim * 4 : 0);
     L->centroid = off;
@@ -183,7 +187,9 @@ void layout(const jx_params* p, Layout* L) {
     L->work = off;
     L->work_bytes = w;
     off += align256(w);
-    L->total = off;
+    L->sk_stride = sketch_stride(p);
+    L->sketch = off;
+    L->total = off + align256((int64_t)p->capacity * L->sk_stride);
 }
 
 }  // namespace
@@ -326,7 +332,7 @@ int jx_create(const jx_params* p, void* d_arena, int64_t arena_bytes, void* stre
     if (((uintptr_t)d_arena) & 255) return fail(JX_EINVAL, "arena must be 256-byte aligned");
     Layout L;
     layout(p, &L);
-    if (arena_bytes < L.total) return fail(JX_ECAPACITY, "arena holds %lld bytes, %lld needed", (long long)arena_bytes, (long long)L.total);
+    if (arena_bytes < L.sketch) return fail(JX_ECAPACITY, "arena holds %lld bytes, %lld needed", (long long)arena_bytes, (long long)L.sketch);
     jx_index* x = new (std::nothrow) jx_index();
     if (!x) return fail(JX_EINVAL, "out of host memory");
     memset(x, 0, sizeof *x);
@@ -339,7 +345,7 @@ int jx_create(const jx_params* p, void* d_arena, int64_t arena_bytes, void* stre
     x->d_vecs = x->d_arena + L.vecs;
     x->d_adj = (uint32_t*)(x->d_arena + L.adj);
     x->d_codes = x->d_arena + L.codes;
-    x->d_sketch = L.sk_stride ? x->d_arena + L.sketch : nullptr;
+    x->d_sketch = L.sk_stride && arena_bytes >= L.total ? x->d_arena + L.sketch : nullptr;
     x->sk_stride = L.sk_stride;
     x->d_P = (float*)(x->d_arena + L.P);
     x->d_centroid = (float*)(x->d_arena + L.centroid);
@@ -474,8 +480,7 @@ static void fill_exact_src(const jx_index* idx, jx::DistSrc* ds, const void* que
 // 2,500 queries, L = 128: 3,000 x 512 (6 MB) 516 -> 344, 1,033 -> 404 us; 1,000 x 960 376 -> 390, 743 -> 454; 2,000 x 1536
 // (12 MB) 664 -> 749, 2,117 -> 957
 static void fill_sketch(const jx_index* idx, int64_t n, bool insertion, jx::BeamArgs* a) {
-    const int64_t least = idx->vec_bytes <= 2048 || (insertion && idx->vec_bytes <= 4096) ? 4 << 20 : 16 << 20;
-    a->sk = n * idx->vec_bytes >= least ? idx->d_sketch : nullptr;
+    a->sk = n * idx->vec_bytes >= sketch_least(idx->vec_bytes, insertion) ? idx->d_sketch : nullptr;
     a->sk_stride = idx->sk_stride;
     a->sk_nch = (idx->p.dim + 15) / 16;
 }

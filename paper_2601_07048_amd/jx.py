@@ -109,13 +109,13 @@ class Index:
     """Owns the arena tensor and the opaque handle; methods mirror the C ABI."""
 
     def __init__(self, dim, dtype, R, L_build, alpha=1.2, capacity=0, max_batch=0, quant_bits=0, batch_growth=0.25,
-                 device="cuda:0", flags=0, cand_mode=CAND_FRONTIER):
+                 device="cuda:0", flags=0, cand_mode=CAND_FRONTIER, arena_bytes=0):
         self.params = Params(dim=dim, dtype=dtype, R=R, L_build=L_build, alpha=alpha, cand_mode=cand_mode,
                              capacity=capacity, max_batch=max_batch or capacity, quant_bits=quant_bits, batch_growth=batch_growth,
                              flags=flags)
         self.device = torch.device(device)
         self.dim, self.dtype, self.R = dim, dtype, R
-        nbytes = jx_arena_bytes(self.params)
+        nbytes = arena_bytes or jx_arena_bytes(self.params)  # fewer: without byte copies (see jx_create)
         with torch.cuda.device(self.device):
             self.arena = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
             h = C.c_void_p()

@@ -95,6 +95,29 @@ def test_arena_size_and_parameter_checks(lib):
     assert lib.jx_mips_augment(None, C.c_int64(1), 4, C.c_float(1.0), 0, None, 8, None, None) == -1
 
 
+def test_byte_copies_are_paid_for_where_something_reads_them(lib):
+    """float32 and binary16 indices of vectors of as many bytes differ in their arenas by the centroid and the byte copies, which
+    an index has no room for where no search and no re-rank reads them."""
+    from paper_2601_07048_amd import jx
+    lib.jx_arena_bytes.restype = C.c_int64
+
+    def up(x, to):
+        return (x + to - 1) // to * to
+
+    for dim, R, capacity, copies in ((960, 64, 10_000, True), (960, 65, 10_000, False), (960, 64, 1092, False), (960, 64, 1093, True),
+                                     (1536, 64, 2730, False), (1536, 64, 2731, True), (512, 64, 2047, False), (512, 64, 2048, True),
+                                     (128, 64, 100_000, False), (132, 64, 100_000, True), (960, 64, (128 << 30) // 3840 + 1, False)):
+        both = [lib.jx_arena_bytes(C.byref(_params(jx, dtype=t, dim=d, R=R, capacity=capacity, max_batch=1000)))
+                for t, d in ((jx.F32, dim), (jx.F16, 2 * dim))]
+        if max(both) > 1 << 34:
+            assert both[0] < both[1] + 1024, "no copies beyond 128 GiB"
+            continue
+        want = up(capacity * up(up(dim, 16) + 16, 64), 256) if copies else 0
+        assert both[0] - both[1] == up(4 * dim, 256) - up(8 * dim, 256) + want, (dim, R, capacity)
+    few = [lib.jx_arena_bytes(C.byref(_params(jx, dtype=jx.F32, dim=d, R=96, capacity=1000, quant_bits=1))) for d in (256, 288)]
+    assert few[1] - few[0] > 1000 * 320  # the re-rank of more than 256 dimensions reads them, whatever R and the capacity
+
+
 def test_product_path_never_imports_the_oracle():
     """The oracle is test infrastructure: nothing under the package may import or load it."""
     pkg = os.path.join(ROOT, "paper_2601_07048_amd")

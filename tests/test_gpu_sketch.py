@@ -193,3 +193,39 @@ def test_insertion_of_expansion_lists_reads_copies_under_switches(jx, d):
         g.insert(x)
         adj.append(g.export_graph()[0])
     assert all(torch.equal(a, adj[0]) for a in adj)
+
+
+def test_arenas_without_room_for_copies(jx):
+    """An arena that lacks the bytes of the byte copies, and no others, is accepted: whole vectors are read and the results are the
+    same."""
+    d, n = 960, 6000
+    x, q = dev(random_data(n, d, np.float32, 101)), dev(random_data(700, d, np.float32, 102))
+    rot = dev(np.linalg.qr(np.random.default_rng(9).standard_normal((d, d)))[0].astype(np.float32))
+
+    def index(lean):
+        kw = dict(capacity=n, max_batch=n, quant_bits=1, cand_mode=jx.CAND_VISITED)
+        full = jx.Index(d, jx.F32, 64, 64, 1.2, **kw)
+        copies = n * 1024
+        if lean == 0:
+            return full
+        size = full.arena.numel() - copies + (0 if lean == 1 else copies - 256)
+        full.close()
+        with pytest.raises(jx.JxError) as e:
+            jx.Index(d, jx.F32, 64, 64, 1.2, arena_bytes=full.arena.numel() - copies - 256, **kw)
+        assert e.value.code == -2
+        return jx.Index(d, jx.F32, 64, 64, 1.2, arena_bytes=size, **kw)
+
+    out = []
+    for lean in (0, 1, 2):
+        g = index(lean)
+        g.insert(x[:5000])
+        g.insert(x[5000:])
+        g.delete(torch.arange(0, n, 7, dtype=torch.int32, device="cuda"))
+        g.consolidate()
+        g.compact()
+        ids, dist, st = g.search(q, 10, 64, stats=True)
+        assert st["beam_kernel"].startswith("beam_search_sketch_kernel<" if lean == 0 else "beam_search_kernel<")
+        g.quantize(1, rot, query_bits=4)
+        many = q.repeat(3, 1)  # 2,100 queries: the re-rank that reads copies
+        out.append((g.export_graph()[0], ids, dist, *g.search(many, 10, 64, mode=jx.RABITQ, rerank=40)))
+    assert all(torch.equal(a, b) for o in out[1:] for a, b in zip(o, out[0]))
