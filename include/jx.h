@@ -157,7 +157,10 @@ typedef struct {
  * and a capacity of 4 MiB of vectors (16 MiB above 1,024 dimensions), or
  * quant_bits != 0 and more than 256 dimensions.  They are the last
  * capacity * s bytes (rounded up to 256), s = the next multiple of 64 of
- * 16 + dim rounded up to 16, a quarter to a third of the vectors. */
+ * 16 + dim rounded up to 16, a quarter to a third of the vectors.  Whether they
+ * are read is decided by the vectors of the first jx_insert or of
+ * jx_import_graph (a sample of 256; far from the origin they say too little);
+ * results do not depend on it. */
 int64_t jx_arena_bytes(const jx_params* p);
 
 /* Create an empty index inside the caller's arena (device memory, at least

@@ -224,9 +224,15 @@ hipError_t launch_tiled(const jx::BfArgs& a, hipStream_t st) {
     return jx::launch_bruteforce(a, st);
 }
 
+// the byte copies, where the index has them and reads them
+uint8_t* sketches(const jx_index* idx) { return idx->use_copies ? idx->d_sketch : nullptr; }
+
+// from the two counters of launch_sketch_probe
+int copies_useful(const uint32_t* counts) { return counts[0] * 2 <= counts[1]; }
+
 // byte copies of vectors [first, first + count) of the store
 hipError_t sketch_range(const jx_index* idx, int64_t first, int64_t count, hipStream_t st) {
-    if (!idx->d_sketch) return hipSuccess;
+    if (!sketches(idx)) return hipSuccess;
     return jx::launch_sketch((const float*)(idx->d_vecs + (size_t)first * idx->vec_bytes), count, idx->p.dim,
                              idx->d_sketch + (size_t)first * idx->sk_stride, idx->sk_stride, st);
 }
@@ -347,6 +353,7 @@ int jx_create(const jx_params* p, void* d_arena, int64_t arena_bytes, void* stre
     x->d_codes = x->d_arena + L.codes;
     x->d_sketch = L.sk_stride && arena_bytes >= L.total ? x->d_arena + L.sketch : nullptr;
     x->sk_stride = L.sk_stride;
+    x->use_copies = 1;
     x->d_P = (float*)(x->d_arena + L.P);
     x->d_centroid = (float*)(x->d_arena + L.centroid);
     x->d_stats = (unsigned long long*)(x->d_arena + L.stats);
@@ -400,13 +407,15 @@ int jx_import_graph(jx_index* idx, const void* d_vecs, int64_t n, const uint32_t
     hipStream_t st = as_stream(stream);
     {   // a table with ids out of range or with a repeated id in a row would send the search kernels out of bounds:
         // check it before it is installed
-        uint32_t* d_bad = (uint32_t*)(idx->d_stats + 10);
-        uint32_t bad = 0;
-        JX_HIP(jx::launch_fill_u32(d_bad, 1, 0u, st));
-        JX_HIP(jx::launch_validate_adj(d_adj, n, idx->p.R, d_bad, st));
-        JX_HIP(hipMemcpyAsync(&bad, d_bad, 4, hipMemcpyDeviceToHost, st));
+        uint32_t* d_seen = (uint32_t*)(idx->d_stats + 10);  // [0] bad entries, [2], [3] of launch_sketch_probe
+        uint32_t seen[4] = {0, 0, 0, 0};
+        JX_HIP(jx::launch_fill_u32(d_seen, 4, 0u, st));
+        JX_HIP(jx::launch_validate_adj(d_adj, n, idx->p.R, d_seen, st));
+        if (idx->d_sketch) JX_HIP(jx::launch_sketch_probe((const float*)d_vecs, n, idx->p.dim, d_seen + 2, st));
+        JX_HIP(hipMemcpyAsync(seen, d_seen, sizeof seen, hipMemcpyDeviceToHost, st));
         JX_HIP(hipStreamSynchronize(st));
-        if (bad) return fail(JX_EINVAL, "%u adjacency entries are out of range, follow a padding entry or repeat an id of their row", bad);
+        if (seen[0]) return fail(JX_EINVAL, "%u adjacency entries are out of range, follow a padding entry or repeat an id of their row", seen[0]);
+        idx->use_copies = copies_useful(seen + 2);
     }
     JX_HIP(hipMemcpyAsync(idx->d_vecs, d_vecs, (size_t)n * idx->vec_bytes, hipMemcpyDeviceToDevice, st));
     JX_HIP(sketch_range(idx, 0, n, st));
@@ -480,7 +489,7 @@ static void fill_exact_src(const jx_index* idx, jx::DistSrc* ds, const void* que
 // 2,500 queries, L = 128: 3,000 x 512 (6 MB) 516 -> 344, 1,033 -> 404 us; 1,000 x 960 376 -> 390, 743 -> 454; 2,000 x 1536
 // (12 MB) 664 -> 749, 2,117 -> 957
 static void fill_sketch(const jx_index* idx, int64_t n, bool insertion, jx::BeamArgs* a) {
-    a->sk = n * idx->vec_bytes >= sketch_least(idx->vec_bytes, insertion) ? idx->d_sketch : nullptr;
+    a->sk = n * idx->vec_bytes >= sketch_least(idx->vec_bytes, insertion) ? sketches(idx) : nullptr;
     a->sk_stride = idx->sk_stride;
     a->sk_nch = (idx->p.dim + 15) / 16;
 }
@@ -576,7 +585,7 @@ static int search_common(jx_index* idx, const void* d_queries, int64_t nq, int32
                 jx::RerankArgs r;
                 memset(&r, 0, sizeof r);
                 fill_exact_src(idx, &r.ds, qs);
-                r.sk = idx->d_sketch;
+                r.sk = sketches(idx);
                 r.sk_stride = idx->sk_stride;
                 r.sk_nch = (p.dim + 15) / 16;
                 r.nq = m;
@@ -810,16 +819,21 @@ int jx_insert(jx_index* idx, const void* d_vecs, int64_t n, void* stream) {
     if (w.total > idx->work_bytes) return fail(JX_ECAPACITY, "workspace too small");
     uint8_t* W = idx->d_work;
     JX_HIP(hipMemcpyAsync(idx->d_vecs + (size_t)first * idx->vec_bytes, d_vecs, (size_t)n * idx->vec_bytes, hipMemcpyDeviceToDevice, st));
-    JX_HIP(sketch_range(idx, first, n, st));
+    if (first > 0) JX_HIP(sketch_range(idx, first, n, st));
     int64_t id_skip = 0x7FFFFFFFFFFFFFFFLL;
     int64_t m = n, linked = first;
     if (first == 0) {
         // entry point: the point nearest to the mean of this first call; it joins alone
         JX_HIP(jx::launch_entry_point(idx->d_vecs, p.dtype, n, p.dim, (double*)(W + w.partial), (float*)(W + w.mean),
                                       (double*)(W + w.dist), (uint32_t*)(W + w.counters) + 32, st));
-        uint32_t e = 0;
-        JX_HIP(hipMemcpyAsync(&e, (uint32_t*)(W + w.counters) + 32, 4, hipMemcpyDeviceToHost, st));
+        uint32_t seen[3] = {0, 0, 0}, *d_seen = (uint32_t*)(W + w.counters) + 32;  // entry id, then the counts of launch_sketch_probe
+        JX_HIP(jx::launch_fill_u32(d_seen + 1, 2, 0u, st));
+        if (idx->d_sketch) JX_HIP(jx::launch_sketch_probe((const float*)idx->d_vecs, n, p.dim, d_seen + 1, st));
+        JX_HIP(hipMemcpyAsync(seen, d_seen, sizeof seen, hipMemcpyDeviceToHost, st));
         JX_HIP(hipStreamSynchronize(st));
+        const uint32_t e = seen[0];
+        idx->use_copies = copies_useful(seen + 1);
+        JX_HIP(sketch_range(idx, 0, n, st));
         if (e >= (uint64_t)n) return fail(JX_EHIP, "entry point selection returned %u", e);
         idx->entry = e;
         id_skip = e;
@@ -1154,7 +1168,7 @@ int jx_compact(jx_index* idx, uint32_t* d_old_to_new, void* stream) {
     JX_HIP(jx::launch_compact_rename(idx->d_adj, p.R, n, map, idx->d_deleted, d_old_to_new, idx->d_clean, st));
     JX_HIP(jx::launch_compact_records(idx->d_vecs, idx->vec_bytes, n, map, idx->d_deleted, staging, staging_bytes, st));
     JX_HIP(jx::launch_compact_records((uint8_t*)idx->d_adj, p.R * 4, n, map, idx->d_deleted, staging, staging_bytes, st));
-    if (idx->d_sketch)
+    if (sketches(idx))
         JX_HIP(jx::launch_compact_records(idx->d_sketch, idx->sk_stride, n, map, idx->d_deleted, staging, staging_bytes, st));
     if (idx->quantized)
         JX_HIP(jx::launch_compact_records(idx->d_codes, idx->code_stride, n, map, idx->d_deleted, staging, staging_bytes, st));

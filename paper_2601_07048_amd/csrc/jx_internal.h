@@ -58,6 +58,7 @@ hipError_t launch_beam_ahead(int kind, int qbits, const BeamArgs& a, hipStream_t
 // float32 vectors with byte copies; *done as above
 hipError_t launch_beam_sketch(int kind, const BeamArgs& a, hipStream_t st, char* kernel_name, bool* done);
 hipError_t launch_sketch(const float* x, long long n, int d, uint8_t* sk, int stride, hipStream_t st);
+hipError_t launch_sketch_probe(const float* x, long long n, int d, uint32_t* counts, hipStream_t st);
 hipError_t launch_beam_codes(int kind, int qbits, const BeamArgs& a, hipStream_t st, char* kernel_name);
 // ablation instances (JX_FLAG_TILED_LOADS, JX_FLAG_QPW_*, JX_FLAG_WAVES_*); hipErrorInvalidValue where none exists
 hipError_t launch_beam_variant(int kind, const BeamArgs& a, hipStream_t st, char* kernel_name);
@@ -252,11 +253,12 @@ struct jx_index {
     uint8_t* d_codes;    // [capacity][code_stride] RaBitQ records
     uint8_t* d_sketch;   // [capacity][sk_stride] byte copies of float32 vectors, or NULL
     int sk_stride;
+    int use_copies;      // whether they say something about the vectors of the first insert or the import (sketch_probe_kernel)
     float* d_P;          // [dim][dim]
     float* d_centroid;   // [dim]
     uint8_t* d_work;     // workspace shared by the phases
     int64_t work_bytes;
-    unsigned long long* d_stats;  // [8] = vertices marked deleted so far, [10] scratch of jx_import_graph
+    unsigned long long* d_stats;  // [8] = vertices marked deleted so far, [10], [11] scratch of jx_import_graph
     unsigned long long* d_stripes;  // [64][16] search counters (BeamArgs::stats)
     uint8_t* d_deleted;  // [capacity] 1 = logically deleted
     uint8_t* d_clean;    // [capacity] see InsertArgs::clean
