@@ -316,13 +316,21 @@ __device__ __forceinline__ float sketch_dist(const SketchQuery& q, const float4 
     return fmaf(-2.f, t, meta.x + q.norm);
 }
 
+// Copies take a round trip of their own before the vectors'.  Where an expansion has few new neighbours, whose vectors come in one
+// round trip, they only make it longer: norms over three decades (some five new neighbours per expansion), without copies /
+// copies of all / of more than these, 60,000 x 132, L = 64, 2,000 queries 253 / 300 / 255 us, 20,000 x 512, L = 256 803 / 938 /
+// 805, 20,000 x 960, 16 calls of 32 points 10,297 / 10,573 / 9,414; 5,000 x 1536, L = 128, 4,000 queries of fifth powers of normal
+// values 712 / 901 / 603.  With 8 instead of 4 a build of 20,000 x 960 took 27.9 for 27.7 ms
+template <int T, int CPL, int KU>
+constexpr int sketch_few() { return T * CPL <= 64 || (CPL == 6 && KU == 16) ? 8 : 4; }
+
 // Tag table and rows of at most 64 entries only (the launcher checks).  KU: 64-byte pieces of two tiles of 16 neighbours in
 // flight, as the registers allow for four wavefronts per SIMD (codes of at most 256 bytes: KU = 4; 40,000 x 200 built with
 // KU = 4 / five wavefronts, spilled / four tiles 16.2 / 18.5 / 16.6 ms), three (8) or two (16: batches that fill no more).
 template <int T, int CPL, int NREG, bool VIS, int KU>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4 ? 4 : (KU == 8 ? 3 : 2), 8))) beam_search_sketch_kernel(BeamArgs a) {
     constexpr int G = 64 / T;
-    constexpr int U0 = CPL == 4 ? 4 : 8 / CPL;
+    constexpr int U0 = CPL == 4 ? 4 : (CPL == 6 ? 2 : 8 / CPL);  // (one of six chunks: 30,000 x 1536, L = 10, 600 queries 251 -> 188 us)
     constexpr int U = U0 < (64 / G) ? U0 : (64 / G);
     constexpr int FCAP = mirror_entries<NREG>();
     extern __shared__ __align__(16) unsigned char smem[];
@@ -429,7 +437,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
         wave_sync();
         evals += n_new;
         // ---- 4a. which of them may enter a full frontier
-        if (use && worst != JX_EMPTY_KEY) {
+        if (use && worst != JX_EMPTY_KEY && n_new > sketch_few<T, CPL, KU>()) {
             const uint32_t id = cand_id[lane < n_new ? lane : n_new - 1];
             const float4 meta = *reinterpret_cast<const float4*>(a.sk + (size_t)id * (uint32_t)a.sk_stride + (size_t)a.sk_nch * 16);
             int il = 0, ih = 0;
