@@ -606,18 +606,23 @@ hipError_t launch_rerank_sketch(const RerankArgs& a, hipStream_t st, bool* done)
 template <int T, int CPL>
 static hipError_t launch_sketch_shape(BeamArgs a, hipStream_t st, char* name) {
     const int nreg = a.L <= 64 ? 1 : (a.L <= 128 ? 2 : 4);
-    // what the visited table forgets costs a quarter of the bytes here, so a smaller one than the vectors ask for, and more
-    // wavefronts by LDS (build of 20,000 x 960, L = 128: 16 / 8 / 4 KB 33.2 / 32.3 / 33.9 ms; 1,500 queries at L = 200 2.19 /
-    // 1.99 / 2.19 ms, but 5,000 3.52 / 3.68 / 4.00)
-    while (a.hash_slots > (a.L <= 128 ? 4096 : 8192) && a.tag_bits < 15) {
-        a.hash_slots /= 2;
-        a.tag_bits++;
-    }
-    const size_t sh0 = 2 * (size_t)sketch_plane(a.sk_nch) + 64 * 8 + 64 * 4 + table_bytes(a);
     constexpr bool SHORT = T * CPL <= 64;
     // two wavefronts per SIMD are 2,048 queries: 15,000 x 1536 at L = 200, 700 / 1,500 / 2,000 queries 1,681 / 2,152 / 3,741 ->
     // 1,505 / 2,046 / 3,478 us, 30,000 x 960 at L = 64 447 / 561 / 649 -> 422 / 541 / 632
     const bool wide = !SHORT && a.sk_nch > 32 && a.nq <= 2048;
+    // what the visited table forgets costs a quarter of the bytes here, so a smaller one than the vectors ask for, and more
+    // wavefronts by LDS (build of 20,000 x 960, L = 128: 16 / 8 / 4 KB 33.2 / 32.3 / 33.9 ms; 1,500 queries at L = 200 2.19 /
+    // 1.99 / 2.19 ms, but 5,000 3.52 / 3.68 / 4.00).  With 16 KB 1,792 queries of more than 128 entries are resident, and the
+    // rest of a wide batch waited for them: 2,000 queries on 6,000 x 960, L = 256 1,506 -> 805 us
+    // 8 KB let 3,584 queries of vectors of at most 256 dimensions and of more than 64 entries be resident, 4 KB 4,096 (the
+    // kernel on whole vectors as many): 60,000 x 132, L = 128, 4,000 queries without copies / 8 / 4 KB 412 / 479 / 361 us, norms over
+    // three decades 491 / 606 / 501, 8,000 763 / 838 / 763, 10,000 985 / 1,048 / 995, normal data 3,214 / 1,615 / 1,683
+    const bool tight = SHORT && a.L > 64 && a.nq > 3584;
+    while (a.hash_slots > (tight ? 2048 : (a.L <= 128 || wide ? 4096 : 8192)) && a.tag_bits < 15) {
+        a.hash_slots /= 2;
+        a.tag_bits++;
+    }
+    const size_t sh0 = 2 * (size_t)sketch_plane(a.sk_nch) + 64 * 8 + 64 * 4 + table_bytes(a);
     if (name) snprintf(name, 96, "beam_search_sketch_kernel<%d,%d,%d,%d,%d>", T, CPL, nreg, a.vis_cap ? 1 : 0, SHORT ? 4 : (wide ? 16 : 8));
 #define JX_LAUNCH(NR, VISIBLE)                                                                                          \
     {                                                                                                                   \
