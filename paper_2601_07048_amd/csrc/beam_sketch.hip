@@ -501,7 +501,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
 // The first k of at most 64 candidates, by exact distance: as rerank_kernel does it, but what its byte copy shows to be farther
 // than k others is not read.  The k-th smallest of the upper bounds (|q' - x'| + e + eq)^2 is no smaller than the k-th distance,
 // so a candidate whose lower bound exceeds it is none of the first k.  Bound: the gathers, 40 copies and some twelve vectors of a
-// query for 40 vectors (10,000 queries, d = 960 223 -> 171 us; 64 candidates 345 -> 196, 5,000 queries of d = 1536 284 -> 157).
+// query for 40 vectors.
 struct SketchRerankLds {
     uint64_t cand_key[64];
     uint32_t cand_id[64];
@@ -511,7 +511,7 @@ struct SketchRerankLds {
 template <int T, int CPL>
 __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
     constexpr int G = 64 / T;
-    constexpr int U0 = CPL == 4 ? 4 : 8 / CPL;
+    constexpr int U0 = CPL == 2 ? 8 : (CPL == 4 ? 6 : 4);  // (few wavefronts per SIMD: the byte products take 180 registers)
     constexpr int U = U0 < (64 / G) ? U0 : (64 / G);
     extern __shared__ __align__(16) unsigned char smem[];
     const int wave = threadIdx.x >> 6, lane = lane_id();
@@ -524,16 +524,31 @@ __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
     uint8_t* qpl = my + sizeof(SketchRerankLds);
     QueryRegs<K_F32, CPL, 0> q;
     load_query<K_F32, T, CPL, 0>(q, a.ds, qi, lig);
-    const SketchQuery sq = sketch_query(a.ds.qrecs + qi * a.ds.qrec_stride, a.ds.nch, kb, qpl, plane, lane);
     const uint32_t* cand = a.cand + (size_t)qi * a.cand_stride;
     const uint32_t id = lane < a.rr ? cand[lane] : JX_NONE_ID;
     const int m = __builtin_popcountll(ballot(id != JX_NONE_ID));  // the frontier is filled from the left
     if (lane < m) L->cand_id[lane] = id;
     wave_sync();
     int n = m;
-    const bool use = m > a.k && !sq.none;
+    bool use = m > a.k;
+    float4 meta = make_float4(0.f, 0.f, 0.f, 0.f);
     if (use) {
-        const float4 meta = *reinterpret_cast<const float4*>(a.sk + (size_t)L->cand_id[lane < m ? lane : 0] * (uint32_t)a.sk_stride + (size_t)a.sk_nch * 16);
+        meta = *reinterpret_cast<const float4*>(a.sk + (size_t)L->cand_id[lane < m ? lane : 0] * (uint32_t)a.sk_stride + (size_t)a.sk_nch * 16);
+        // Worth it where the estimates put half of the candidates farther beyond the k-th than both bounds are wide: else most
+        // vectors are read after all (fifth powers of normal values, 5,000 queries of d = 1536, 64 candidates: 76 us without copies,
+        // 157 with, 105 so; normal ones 176, 161, 180; a Gaussian mixture 253, 116, 117)
+        const float est = lane < m ? a.cand_dist[(size_t)qi * a.cand_stride + lane] : 0.f;
+        const float wide = 2.f * sqrtf(fmaxf(est, 0.f)) * meta.w;
+        const float bar = __uint_as_float(readlane32(__float_as_uint(est + wide), a.k - 1));
+        use = __builtin_popcountll(ballot(lane < m && est - wide > bar)) * 2 >= m;
+    }
+    SketchQuery sq;
+    if (use) {
+        sq = sketch_query(a.ds.qrecs + qi * a.ds.qrec_stride, a.ds.nch, kb, qpl, plane, lane);
+        use = !sq.none;
+        wave_sync();
+    }
+    if (use) {
         int il = 0, ih = 0;
         const uint8_t* lq = qpl + (lane & 1) * plane + (lane >> 4) * 16;
         if (m <= 48) {
@@ -589,9 +604,11 @@ __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
 hipError_t launch_rerank_sketch(const RerankArgs& a, hipStream_t st, bool* done) {
     *done = false;
     const int nch = a.ds.nch;
-    // Whole vectors / this, us: 41 candidates for 40 neighbours, 10,000 queries 227 / 292; 50,000 x 256, 5,000 queries 33 / 35; of
-    // d = 960 and 40 candidates 1 query 18 / 19, 1,000 31 / 34, 5,000 119 / 97, and 64 candidates 26 / 18, 45 / 38, 177 / 107
-    if (!a.sk || a.rr > 64 || a.rr < 3 * a.k || nch <= 64 || nch > 384 || (a.nq < 2048 && a.rr <= 48)) return hipSuccess;
+    // Whole vectors / this, us: 41 candidates for 40 neighbours, 10,000 queries 227 / 292; 50,000 x 256, 5,000 queries 33 / 35; Gaussian
+    // mixtures of d = 960 / 1536, 40 candidates, 2,100 queries 53 / 55 and 76 / 64, 4,500 99 / 80 and 148 / 100, 10,000 209 / 140 and
+    // 316 / 189, 64 candidates, 200 queries 42 / 27 and 60 / 38, 5,000 165 / 88 and 253 / 117; of d = 384, 40, 2,100 and 10,000 24 / 24
+    // and 79 / 68.  2,100 queries lose where copies say little (normal values, d = 960, 40 candidates 33 / 47)
+    if (!a.sk || a.rr > 64 || a.rr < 3 * a.k || nch <= 64 || nch > 384 || (a.nq < 4096 && a.rr <= 48)) return hipSuccess;
     *done = true;
     const size_t sh = 4 * (sizeof(SketchRerankLds) + 2 * (size_t)sketch_plane(a.sk_nch));
     const dim3 grid((unsigned)((a.nq + 3) / 4));

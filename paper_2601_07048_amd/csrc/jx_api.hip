@@ -590,6 +590,7 @@ static int search_common(jx_index* idx, const void* d_queries, int64_t nq, int32
                 r.sk_nch = (p.dim + 15) / 16;
                 r.nq = m;
                 r.cand = (const uint32_t*)(W + qw.fr_ids);
+                r.cand_dist = (const float*)(W + qw.fr_dist);
                 r.cand_stride = rerank;
                 r.rr = rerank;
                 r.k = out_k;

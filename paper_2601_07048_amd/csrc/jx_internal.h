@@ -151,6 +151,7 @@ struct RerankArgs {
     DistSrc ds;              // recs = the float32 store, qrecs = the original queries
     long long nq;
     const uint32_t* cand;    // [nq][cand_stride] frontier ids (JX_NONE padded)
+    const float* cand_dist;  // and their estimated distances, ascending
     int cand_stride, rr, k;
     uint32_t* out_ids;       // [nq][k]
     float* out_dist;

@@ -102,12 +102,12 @@ def test_copies_follow_imports_inserts_and_compaction(jx):
 @pytest.mark.parametrize("d,n", [(288, 9000), (512, 9000), (960, 5000), (1536, 3000)])
 def test_rerank_reads_what_may_be_among_the_first(jx, d, n):
     """The re-rank that reads byte copies first returns, bit for bit, what the one on whole vectors returns, which keeps batches
-    of fewer than 2,048 queries with at most 48 candidates; with more candidates its ids are those of 64-bit distances.  Copies
+    of fewer than 4,096 queries with at most 48 candidates; with more candidates its ids are those of 64-bit distances.  Copies
     of one row and rows without a byte copy are among the candidates."""
     x = random_data(n, d, np.float32, 61)
     y = _mixed(n, d, 61, extremes=False)
     y[np.random.default_rng(64).permutation(n)[:9]] *= np.float32(1e17)
-    q = dev(np.concatenate([random_data(1400, d, np.float32, 62), _mixed(700, d, 63)]))
+    q = dev(np.concatenate([random_data(2800, d, np.float32, 62), _mixed(1400, d, 63)]))
     g = jx.Index(d, jx.F32, 48, 64, 1.2, capacity=n, max_batch=n, quant_bits=1)
     g.insert(dev(x))
     adj, entry = g.export_graph()[0], g.size()[1]
@@ -133,7 +133,7 @@ def test_rerank_reads_what_may_be_among_the_first(jx, d, n):
 def test_counters_count_what_is_read(jx):
     """dist_evals lies between an exact visited set's count and that of no filter; vec_bytes and rerank_bytes are those of the
     vectors that were read and of the byte copies, not of every neighbour and candidate.  Integer data: the oracle's walk."""
-    d, n, L, nq = 960, 5000, 64, 2100
+    d, n, L, nq = 960, 5000, 64, 4200
     rng = np.random.default_rng(71)
     c = rng.integers(-20, 21, (8, d))
     x, q = ((c[rng.integers(0, 8, m)] + rng.integers(-12, 13, (m, d))).astype(np.float32) for m in (n, nq))
@@ -226,7 +226,7 @@ def test_arenas_without_room_for_copies(jx):
         ids, dist, st = g.search(q, 10, 64, stats=True)
         assert st["beam_kernel"].startswith("beam_search_sketch_kernel<" if lean == 0 else "beam_search_kernel<")
         g.quantize(1, rot, query_bits=4)
-        many = q.repeat(3, 1)  # 2,100 queries: the re-rank that reads copies
+        many = q.repeat(6, 1)  # 4,200 queries: the re-rank that reads copies
         out.append((g.export_graph()[0], ids, dist, *g.search(many, 10, 64, mode=jx.RABITQ, rerank=40)))
     assert all(torch.equal(a, b) for o in out[1:] for a, b in zip(o, out[0]))
 
@@ -267,3 +267,36 @@ def test_sets_of_which_copies_say_nothing_do_without(jx, d, kind, useful):
             ix.import_graph(moved, adj, entry)
         a, b = searched(g), searched(lean)
         assert a[0] == use and all(torch.equal(a[i], b[i]) for i in (1, 2))
+
+
+@pytest.mark.parametrize("d,bits", [(288, 4), (512, 2), (960, 4), (1536, 1)])
+@pytest.mark.parametrize("kind,spread", [("clusters", True), ("powers", False)])
+def test_rerank_reads_copies_where_the_estimates_are_spread(jx, d, bits, kind, spread):
+    """Candidates whose estimates lie farther apart than the bounds are wide are left out by their copies; of others the vectors are
+    read at once.  Either way the result is that of an index without copies, bit for bit."""
+    n, nq = 6000, 4500
+    rng = np.random.default_rng(d)
+    if kind == "clusters":  # a decaying spectrum around many centres: neighbours at very different distances
+        c = rng.standard_normal((400, d)) * 1.3
+        mix = rng.standard_normal((d, d)) * np.arange(1, d + 1)[:, None] ** -1.0
+        make = lambda m: (c[rng.integers(0, 400, m)] + rng.standard_normal((m, d)) @ mix * 0.7).astype(np.float32)
+    else:
+        make = lambda m: (rng.standard_normal((m, d)) ** 5).astype(np.float32)
+    x, q = dev(make(n)), dev(make(nq))
+    rot = dev(np.linalg.qr(rng.standard_normal((d, d)))[0].astype(np.float32))
+    kw = dict(capacity=n, max_batch=n, quant_bits=bits)
+    g = jx.Index(d, jx.F32, 48, 64, 1.2, **kw)
+    g.insert(x)
+    stride = (d + 15) // 16 * 16 + 16 + 63 >> 6 << 6
+    lean = jx.Index(d, jx.F32, 48, 64, 1.2, arena_bytes=g.arena.numel() - (n * stride + 255 >> 8 << 8), **kw)
+    lean.import_graph(x, g.export_graph()[0], g.size()[1])
+    read = []
+    for ix in (g, lean):
+        ix.quantize(bits, rot, query_bits=4)
+    for k, rr in ((10, 40), (1, 3), (13, 40), (16, 48), (10, 64), (21, 64)):
+        out = [ix.search(q, k, 64, mode=jx.RABITQ, rerank=rr, stats=True) for ix in (g, lean)]
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32)), (k, rr)
+        assert out[1][2]["rerank_bytes"] == rr * nq * 4 * d
+        read.append(out[0][2]["rerank_bytes"] / out[1][2]["rerank_bytes"])
+    # a third of the candidates asked for: copies are left alone where the estimates are close
+    assert (min(read[0], read[4]) < 0.8) if spread else (0.85 < read[2] <= 1 and 0.9 < read[5] <= 1), read
