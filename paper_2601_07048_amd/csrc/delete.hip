@@ -371,15 +371,27 @@ hipError_t launch_consol_lists(int dtype, const ConsolArgs& a, uint32_t max_cnt,
     return launch_consol_lists_kind<K_F32>(a, max_cnt, list, heads, counters, keys_out, vals_out, st);
 }
 
-__global__ void clear_deleted_rows_kernel(uint32_t* adj, int R, long long n, const uint8_t* deleted) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * R) return;
-    if (deleted[i / R]) adj[i] = JX_NONE_ID;
+// Empties the rows of deleted vertices, and those of live ones whose candidate set was empty: all their neighbours are deleted and
+// point to deleted vertices or back only.  Every other live row with a deleted neighbour has been rewritten, so the first entry
+// tells.  Each lane looks at one row; the wavefront then empties those that were found.
+__global__ void __launch_bounds__(256) clear_deleted_rows_kernel(uint32_t* adj, int R, long long n, const uint8_t* deleted, uint8_t* clean) {
+    const int lane = lane_id();
+    const long long base = ((long long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64, i = base + lane;
+    bool found = false;
+    if (i < n) {
+        const uint32_t first = adj[(size_t)i * R];
+        found = deleted[i] || (first != JX_NONE_ID && deleted[first]);
+        if (found && clean) clean[i] = 0;
+    }
+    for (unsigned long long rows = __ballot(found); rows; rows &= rows - 1) {
+        uint32_t* row = adj + (size_t)(base + __ffsll(rows) - 1) * R;
+        for (int c = lane; c < R; c += 64) row[c] = JX_NONE_ID;
+    }
 }
 
-hipError_t launch_clear_deleted_rows(uint32_t* adj, int R, long long n, const uint8_t* deleted, hipStream_t st) {
+hipError_t launch_clear_deleted_rows(uint32_t* adj, int R, long long n, const uint8_t* deleted, uint8_t* clean, hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(clear_deleted_rows_kernel, dim3((unsigned)((n * R + 255) / 256)), dim3(256), 0, st, adj, R, n, deleted);
+    hipLaunchKernelGGL(clear_deleted_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, adj, R, n, deleted, clean);
     return hipGetLastError();
 }
 

@@ -1121,8 +1121,8 @@ int jx_consolidate(jx_index* idx, void* stream) {
         }
         v0 = v1;
     }
-    // 3. nothing points to a deleted vertex any more: empty their rows
-    JX_HIP(jx::launch_clear_deleted_rows(idx->d_adj, p.R, n, idx->d_deleted, st));
+    // 3. the rows of deleted vertices, and of live ones that are left without a candidate
+    JX_HIP(jx::launch_clear_deleted_rows(idx->d_adj, p.R, n, idx->d_deleted, idx->d_clean, st));
     // 4. a deleted entry point hands over to the nearest live vertex
     uint8_t entry_dead = 0;
     if (idx->entry == JX_NONE) return JX_OK;

@@ -200,7 +200,7 @@ hipError_t launch_consol_dist(int dtype, const ConsolArgs& a, uint64_t* keys_out
 #define CONSOL_LDS 4096
 hipError_t launch_consol_lists(int dtype, const ConsolArgs& a, uint32_t max_cnt, uint32_t* list, uint32_t* heads, uint32_t* counters,
                                uint64_t* keys_out, uint32_t* vals_out, hipStream_t st);
-hipError_t launch_clear_deleted_rows(uint32_t* adj, int R, long long n, const uint8_t* deleted, hipStream_t st);
+hipError_t launch_clear_deleted_rows(uint32_t* adj, int R, long long n, const uint8_t* deleted, uint8_t* clean, hipStream_t st);
 hipError_t launch_nearest_live(const void* vecs, int dtype, long long n, int d, uint32_t target, const uint8_t* deleted,
                                double* dist, uint32_t* out_id, hipStream_t st);
 

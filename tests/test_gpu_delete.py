@@ -371,3 +371,41 @@ def test_consolidate_sets_of_every_size(jx, dtype, R, L, drop):
         g.import_graph(dev(x), dev(adj), entry)
         g.delete(dev(gone)); g.consolidate()
         assert np.array_equal(u32(g.export_graph()[0]), ref.graph()[0]), batch
+
+
+@pytest.mark.parametrize("dtype", [np.uint8, np.float32, np.float16])
+@pytest.mark.parametrize("R", [4, 64, 70])
+def test_a_live_vertex_left_without_candidates(jx, dtype, R):
+    """All neighbours of some live vertices are deleted and point to deleted vertices, back to them, or nowhere: their candidate
+    sets are empty, and so are their rows afterwards.  Nothing live points to a deleted vertex, the index can be compacted, and
+    what is inserted next may link them again."""
+    n, d, L = 400, 32, 24
+    x = random_data(n + 60, d, np.uint8, seed=11).astype(dtype)
+    ref = oracle.Index(d, dtype, R, L, 1.2, 2 * n)
+    ref.insert(x[:n])
+    adj = ref.graph()[0].copy()
+    lone, gone = np.arange(40, 52), np.arange(100, 130)
+    keep = ~np.isin(np.arange(n), np.concatenate([lone, gone, [ref.entry]]))
+    for v in np.flatnonzero(keep):  # nobody else points to either
+        row = [w for w in adj[v] if w != 0xFFFFFFFF and keep[w]] or [int(ref.entry)]
+        adj[v] = 0xFFFFFFFF
+        adj[v, :len(row)] = row
+    adj[lone] = adj[gone] = 0xFFFFFFFF
+    adj[lone[:4], 0] = gone[:4]                                       # one neighbour, which points nowhere
+    adj[lone[4:8], :2] = np.stack([gone[4:8], gone[8:12]], 1)         # two, which point to each other and back
+    adj[gone[4:8], :2], adj[gone[8:12], :2] = np.stack([gone[8:12], lone[4:8]], 1), np.stack([lone[4:8], gone[4:8]], 1)
+    adj[lone[8:], 0] = gone[12:16]                                    # one, which points to a deleted one and to a live one
+    adj[gone[12:16], :2] = np.stack([gone[16:20], np.flatnonzero(keep)[:4]], 1)
+    ref.set_graph(x[:n], adj, ref.entry)
+    g = jx.Index(d, {np.uint8: jx.U8, np.float32: jx.F32, np.float16: jx.F16}[dtype], R, L, 1.2, capacity=2 * n, max_batch=n)
+    g.import_graph(dev(x[:n]), dev(adj), ref.entry)
+    ref.delete(gone.astype(np.uint32)); g.delete(dev(gone.astype(np.uint32)))
+    ref.consolidate(); g.consolidate()
+    _same_graph(ref, g)
+    after = u32(g.export_graph()[0])
+    assert np.all(after[lone[:8]] == 0xFFFFFFFF) and np.all(after[lone[8:], 0] != 0xFFFFFFFF)
+    assert not np.isin(after[~np.isin(np.arange(n), gone)], gone).any()
+    ref.compact(); g.compact()
+    _same_graph(ref, g)
+    ref.insert(x[n:]); g.insert(dev(x[n:]))
+    _same_graph(ref, g)
