@@ -125,6 +125,107 @@ struct TeamLds {
     int nsel;
 };
 
+// Ranks of all candidates where some came without their distance.  All threads of the workgroup.  Ranks and selection are those of
+// team_prune and of team_prune_long: as functions of their own the 8-block uint8 merge spills 207 registers for 33, and no deletion
+// or insertion of uint8, binary16 or float32 rows takes 1 % longer for it (d = 96 to 960, 72 to 256 candidates).
+template <int DT, int NB>
+__device__ __forceinline__ void team_ranks(TeamLds<DT, NB>* L, const int m, const int n_fixed, const int tid) {
+    if (n_fixed > 0) {
+        // ranks: the candidates of known distance are in order already
+        uint64_t k = 0;
+        if (tid < m) {
+            k = ((uint64_t)__float_as_uint(L->dp[tid]) << 32) | L->id[tid];
+            L->key[tid] = k;
+        }
+        __syncthreads();
+        if (tid < m) {
+            int rank = tid < n_fixed ? 0 : tid - n_fixed;
+            for (int t = 0; t < n_fixed; t++) {
+                const uint64_t o = L->key[t];
+                rank += (o < k || (o == k && t < tid)) ? 1 : 0;
+            }
+            if (tid < n_fixed) {
+                int lo = n_fixed, hi = m;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (L->key[mid] < k) lo = mid + 1;
+                    else hi = mid;
+                }
+                rank += lo - n_fixed;
+            }
+            L->rank[tid] = (uint32_t)rank;
+        }
+        __syncthreads();
+    }
+}
+
+// Alg. 3 on the masks of L->kb, by the first wavefront; the number selected, as team_prune returns it
+template <int DT, int NB>
+__device__ __forceinline__ int team_select(TeamLds<DT, NB>* L, const int m, const int nb, const bool sorted, const uint32_t p, const int R,
+                                           const bool truncated, const int wave, const int lane) {
+    using Lds = TeamLds<DT, NB>;
+    if (wave == 0) {
+        constexpr int H = NB / 2;
+        uint32_t kw[H][NB];
+        uint64_t U[H], S[H];
+#pragma unroll
+        for (int h = 0; h < H; h++) {
+            const int slot = h * 64 + lane;
+            const bool on = slot < m;
+#pragma unroll
+            for (int w = 0; w < NB; w++) kw[h][w] = on && w < nb && (!sorted || w <= slot >> 5) ? L->kb[w * Lds::M + slot] : 0u;
+            U[h] = ballot(on && L->id[on ? slot : 0] != p);
+            S[h] = 0;
+            L->by_rank[slot] = JX_NONE_ID;
+        }
+        for (;;) {
+            uint64_t any = 0, ns[H], nd[H];
+#pragma unroll
+            for (int h = 0; h < H; h++) any |= U[h];
+            if (!any) break;
+#pragma unroll
+            for (int h = 0; h < H; h++) {
+                uint32_t dead = 0, wait = 0;
+#pragma unroll
+                for (int w = 0; w < NB; w++) {
+                    dead |= kw[h][w] & (uint32_t)(S[w >> 1] >> (32 * (w & 1)));
+                    wait |= kw[h][w] & (uint32_t)(U[w >> 1] >> (32 * (w & 1)));
+                }
+                ns[h] = ballot(dead == 0 && wait == 0) & U[h];
+                nd[h] = ballot(dead != 0) & U[h];
+            }
+#pragma unroll
+            for (int h = 0; h < H; h++) {
+                U[h] &= ~(ns[h] | nd[h]);
+                S[h] |= ns[h];
+            }
+        }
+        wave_sync();
+#pragma unroll
+        for (int h = 0; h < H; h++)
+            if ((S[h] >> lane) & 1ull) L->by_rank[L->rank[h * 64 + lane]] = (uint32_t)(h * 64 + lane);
+        wave_sync();
+        const int tau = (int)L->rank[m > 0 ? m - 1 : 0];
+        int nsel = 0, inside = 0;
+#pragma unroll
+        for (int h = 0; h < H; h++) {
+            const uint32_t slot = L->by_rank[h * 64 + lane];
+            const uint64_t on = ballot(slot != JX_NONE_ID);
+            const int pos = nsel + prefix_count(on);
+            if (slot != JX_NONE_ID && pos < R) {
+                L->sel_id[pos] = L->id[slot];
+                L->sel_dist[pos] = __float_as_uint(L->dp[slot]);
+            }
+            nsel += __builtin_popcountll(on);
+            inside += __builtin_popcountll(ballot(slot != JX_NONE_ID && h * 64 + lane <= tau));
+        }
+        // beyond the last candidate of known distance an excluded one could come first
+        if (lane == 0) L->nsel = truncated && inside < R ? -1 : (nsel < R ? nsel : R);
+    }
+    __syncthreads();
+    return L->nsel;
+}
+
 // L->id[0..m): n_fixed candidates of unknown distance to p, then candidates in ascending (distance, id) order with their
 // distances in L->dp.  truncated: further candidates, none before the last one here, exist beyond the pool.  All threads
 // of the workgroup call; the arrays are visible (a barrier after they were filled).  Returns the number selected
@@ -329,33 +430,7 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
         }
     }
     __syncthreads();
-    if (n_fixed > 0) {
-        // ranks: the candidates of known distance are in order already
-        uint64_t k = 0;
-        if (tid < m) {
-            k = ((uint64_t)__float_as_uint(L->dp[tid]) << 32) | L->id[tid];
-            L->key[tid] = k;
-        }
-        __syncthreads();
-        if (tid < m) {
-            int rank = tid < n_fixed ? 0 : tid - n_fixed;
-            for (int t = 0; t < n_fixed; t++) {
-                const uint64_t o = L->key[t];
-                rank += (o < k || (o == k && t < tid)) ? 1 : 0;
-            }
-            if (tid < n_fixed) {
-                int lo = n_fixed, hi = m;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (L->key[mid] < k) lo = mid + 1;
-                    else hi = mid;
-                }
-                rank += lo - n_fixed;
-            }
-            L->rank[tid] = (uint32_t)rank;
-        }
-        __syncthreads();
-    }
+    team_ranks<DT, NB>(L, m, n_fixed, tid);
     // ---- the discard relation, tile by tile.  Candidates that came in order (n_fixed = 0) are discarded by those of their own
     // block and of blocks before it only: half of it
     const bool sorted = n_fixed == 0;
@@ -410,171 +485,10 @@ __device__ __forceinline__ int team_prune(const uint8_t* recs, size_t stride, in
         }
     }
     __syncthreads();
-    // ---- Alg. 3
-    if (wave == 0) {
-        constexpr int H = NB / 2;
-        uint32_t kw[H][NB];
-        uint64_t U[H], S[H];
-#pragma unroll
-        for (int h = 0; h < H; h++) {
-            const int slot = h * 64 + lane;
-            const bool on = slot < m;
-#pragma unroll
-            for (int w = 0; w < NB; w++) kw[h][w] = on && w < nb && (!sorted || w <= slot >> 5) ? L->kb[w * Lds::M + slot] : 0u;
-            U[h] = ballot(on && L->id[on ? slot : 0] != p);
-            S[h] = 0;
-            L->by_rank[slot] = JX_NONE_ID;
-        }
-        for (;;) {
-            uint64_t any = 0, ns[H], nd[H];
-#pragma unroll
-            for (int h = 0; h < H; h++) any |= U[h];
-            if (!any) break;
-#pragma unroll
-            for (int h = 0; h < H; h++) {
-                uint32_t dead = 0, wait = 0;
-#pragma unroll
-                for (int w = 0; w < NB; w++) {
-                    dead |= kw[h][w] & (uint32_t)(S[w >> 1] >> (32 * (w & 1)));
-                    wait |= kw[h][w] & (uint32_t)(U[w >> 1] >> (32 * (w & 1)));
-                }
-                ns[h] = ballot(dead == 0 && wait == 0) & U[h];
-                nd[h] = ballot(dead != 0) & U[h];
-            }
-#pragma unroll
-            for (int h = 0; h < H; h++) {
-                U[h] &= ~(ns[h] | nd[h]);
-                S[h] |= ns[h];
-            }
-        }
-        wave_sync();
-#pragma unroll
-        for (int h = 0; h < H; h++)
-            if ((S[h] >> lane) & 1ull) L->by_rank[L->rank[h * 64 + lane]] = (uint32_t)(h * 64 + lane);
-        wave_sync();
-        const int tau = (int)L->rank[m > 0 ? m - 1 : 0];
-        int nsel = 0, inside = 0;
-#pragma unroll
-        for (int h = 0; h < H; h++) {
-            const uint32_t slot = L->by_rank[h * 64 + lane];
-            const uint64_t on = ballot(slot != JX_NONE_ID);
-            const int pos = nsel + prefix_count(on);
-            if (slot != JX_NONE_ID && pos < R) {
-                L->sel_id[pos] = L->id[slot];
-                L->sel_dist[pos] = __float_as_uint(L->dp[slot]);
-            }
-            nsel += __builtin_popcountll(on);
-            inside += __builtin_popcountll(ballot(slot != JX_NONE_ID && h * 64 + lane <= tau));
-        }
-        // beyond the last candidate of known distance an excluded one could come first
-        if (lane == 0) L->nsel = truncated && inside < R ? -1 : (nsel < R ? nsel : R);
-    }
-    __syncthreads();
-    return L->nsel;
+    return team_select<DT, NB>(L, m, nb, sorted, p, R, truncated, wave, lane);
 }
 
-// The last two parts of team_prune, for team_prune_long.  The two functions share no code on purpose: as one template the binary16
-// kernels, whose registers spill, came out slower (a deletion from 6,292 x 128 1,295 -> 1,400 us, from 6,736 x 128 1,508 -> 1,570).
-// Ranks of all candidates where some came without their distance.  All threads of the workgroup
-template <int DT, int NB>
-__device__ __forceinline__ void team_ranks(TeamLds<DT, NB>* L, const int m, const int n_fixed, const int tid) {
-    if (n_fixed > 0) {
-        // ranks: the candidates of known distance are in order already
-        uint64_t k = 0;
-        if (tid < m) {
-            k = ((uint64_t)__float_as_uint(L->dp[tid]) << 32) | L->id[tid];
-            L->key[tid] = k;
-        }
-        __syncthreads();
-        if (tid < m) {
-            int rank = tid < n_fixed ? 0 : tid - n_fixed;
-            for (int t = 0; t < n_fixed; t++) {
-                const uint64_t o = L->key[t];
-                rank += (o < k || (o == k && t < tid)) ? 1 : 0;
-            }
-            if (tid < n_fixed) {
-                int lo = n_fixed, hi = m;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (L->key[mid] < k) lo = mid + 1;
-                    else hi = mid;
-                }
-                rank += lo - n_fixed;
-            }
-            L->rank[tid] = (uint32_t)rank;
-        }
-        __syncthreads();
-    }
-}
-
-// Alg. 3 on the masks of L->kb, by the first wavefront; the number selected, as team_prune returns it
-template <int DT, int NB>
-__device__ __forceinline__ int team_select(TeamLds<DT, NB>* L, const int m, const int nb, const bool sorted, const uint32_t p, const int R,
-                                           const bool truncated, const int wave, const int lane) {
-    using Lds = TeamLds<DT, NB>;
-    if (wave == 0) {
-        constexpr int H = NB / 2;
-        uint32_t kw[H][NB];
-        uint64_t U[H], S[H];
-#pragma unroll
-        for (int h = 0; h < H; h++) {
-            const int slot = h * 64 + lane;
-            const bool on = slot < m;
-#pragma unroll
-            for (int w = 0; w < NB; w++) kw[h][w] = on && w < nb && (!sorted || w <= slot >> 5) ? L->kb[w * Lds::M + slot] : 0u;
-            U[h] = ballot(on && L->id[on ? slot : 0] != p);
-            S[h] = 0;
-            L->by_rank[slot] = JX_NONE_ID;
-        }
-        for (;;) {
-            uint64_t any = 0, ns[H], nd[H];
-#pragma unroll
-            for (int h = 0; h < H; h++) any |= U[h];
-            if (!any) break;
-#pragma unroll
-            for (int h = 0; h < H; h++) {
-                uint32_t dead = 0, wait = 0;
-#pragma unroll
-                for (int w = 0; w < NB; w++) {
-                    dead |= kw[h][w] & (uint32_t)(S[w >> 1] >> (32 * (w & 1)));
-                    wait |= kw[h][w] & (uint32_t)(U[w >> 1] >> (32 * (w & 1)));
-                }
-                ns[h] = ballot(dead == 0 && wait == 0) & U[h];
-                nd[h] = ballot(dead != 0) & U[h];
-            }
-#pragma unroll
-            for (int h = 0; h < H; h++) {
-                U[h] &= ~(ns[h] | nd[h]);
-                S[h] |= ns[h];
-            }
-        }
-        wave_sync();
-#pragma unroll
-        for (int h = 0; h < H; h++)
-            if ((S[h] >> lane) & 1ull) L->by_rank[L->rank[h * 64 + lane]] = (uint32_t)(h * 64 + lane);
-        wave_sync();
-        const int tau = (int)L->rank[m > 0 ? m - 1 : 0];
-        int nsel = 0, inside = 0;
-#pragma unroll
-        for (int h = 0; h < H; h++) {
-            const uint32_t slot = L->by_rank[h * 64 + lane];
-            const uint64_t on = ballot(slot != JX_NONE_ID);
-            const int pos = nsel + prefix_count(on);
-            if (slot != JX_NONE_ID && pos < R) {
-                L->sel_id[pos] = L->id[slot];
-                L->sel_dist[pos] = __float_as_uint(L->dp[slot]);
-            }
-            nsel += __builtin_popcountll(on);
-            inside += __builtin_popcountll(ballot(slot != JX_NONE_ID && h * 64 + lane <= tau));
-        }
-        // beyond the last candidate of known distance an excluded one could come first
-        if (lane == 0) L->nsel = truncated && inside < R ? -1 : (nsel < R ? nsel : R);
-    }
-    __syncthreads();
-    return L->nsel;
-}
-
-// The same for long float32 vectors: two parts first (see above).
+// team_prune for long float32 vectors: two parts first (see above).
 template <int NB>
 __device__ __forceinline__ int team_prune_long(const uint8_t* recs, size_t stride, int vec_bytes, TeamLds<JX_F32, NB>* L, int m, int n_fixed,
                                           uint32_t p, int R, float alpha, bool truncated) {
