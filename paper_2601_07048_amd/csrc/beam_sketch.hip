@@ -161,9 +161,9 @@ hipError_t launch_sketch_probe(const float* x, long long n, int d, uint32_t* cou
 }
 
 // <c, l> and <c, h> of neighbours first + 16 p .. (p < NP) in the lanes of their numbers; KU loads of each in flight.
-// lq: this lane's part of operand A (rows l, h, l, h, ...; columns 16 (lane / 16) .. of each 64).  A lane group reads up to 48
-// bytes behind the codes of a record where d is no multiple of 64 (its own meta chunk or the next record, the arena's next
-// buffer behind the last one): the query is zero there.
+// lq: this lane's part of operand A (rows l, h, l, h, ...; columns 16 (lane / 16) .. of each 64).  Where d is no multiple of 64 a lane
+// group reads up to 48 bytes behind the codes: the rest of the record, whose stride is a multiple of 64 that holds the codes and the
+// 16 bytes of their scale.  The query is zero there.
 template <int NP, int KU>
 __device__ __forceinline__ void sketch_dots(const uint8_t* sk, const uint32_t stride, const int kb, const uint8_t* lq,
                                             const uint32_t* cand_id, const int first, const int n, const int lane, int& il, int& ih) {

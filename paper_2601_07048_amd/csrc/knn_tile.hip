@@ -88,7 +88,9 @@ template <> struct KAcc<JX_U8> { typedef ki32x16 type; typedef int elem; };
 // The query tile (.x) and slice (.y) of a workgroup.  Workgroups go round the eight XCDs by their number; consecutive tiles of
 // one slice are given to one XCD, whose workgroups then stream the same vectors through its L2.  In order of their numbers /
 // like this, k = 10: 1,000 x 200,000 float32 d = 128 416 / 372 us, 1,000 x 100,000 d = 960 1,022 / 986, 300 x 50,000 d = 1536 455 /
-// 441, binary16 1,000 x 100,000 d = 960 531 / 520.  Not knn_u8_kernel: 5,000 x 300,000 d = 96, k = 100 1,774 / 1,808.
+// 441, binary16 1,000 x 100,000 d = 960 531 / 520.  uint8 above 128 bytes: 1,000 x 100,000 d = 144 134.6 / 132.6, d = 256 136.7 /
+// 138.5, 300 x 300,000 d = 256 133.3 / 131.7, d = 960 271 / 259, 10,000 x 200,000 d = 256 1,588 / 1,581, d = 960 4,240 / 4,147.
+// Not knn_u8_kernel: 5,000 x 300,000 d = 96, k = 100 1,774 / 1,808.
 __device__ __forceinline__ int2 knn_work(const KnnArgs& a) {
     const uint32_t g = gridDim.x, xcd = blockIdx.x & 7u, each = g >> 3, more = g & 7u;
     const uint32_t w = xcd * each + (xcd < more ? xcd : more) + (blockIdx.x >> 3);
