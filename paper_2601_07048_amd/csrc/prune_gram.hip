@@ -623,14 +623,15 @@ __device__ __forceinline__ int team_prune_long(const uint8_t* recs, size_t strid
     if (tid < m && L->nrm[tid] > 0.f && L->nrm[tid] < GT_TINY) L->pairs = GT_PAIRS + 1;
     const float two = GT_TWO * 1.01f * alpha;
     // undecided: |alpha d(i,j) - d(p,j)| within alpha times the error of d(i,j), 2 GT_TWO |x_i| |x_j| at most.  An infinite d(p,j)
-    // is decided
+    // is decided.  The slots behind the last candidate have no vector to read: a vector with an infinite coordinate is undecided
+    // against each of them (its norm is infinite, its product with a row of zeros is NaN and its distance 0 for it)
     auto list = [&](const typename GAcc<DT>::type& g, const float nj, const int j, const float dpj, const uint32_t rj, const bool j_first) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             const int i = wave * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
             const float ni = L->nrm[i], dv = j_first ? L->dp[i] : dpj;
             const uint32_t ri = L->rank[i];
-            if ((j_first ? rj < ri : ri < rj) && fmaf(-two, ni + nj, fabsf(__fmul_rn(alpha, gram_dist<DT>(ni, nj, g[e])) - dv)) < 0.f) {
+            if ((j_first ? rj < ri : ri < rj) && (j_first ? i : j) < m && fmaf(-two, ni + nj, fabsf(__fmul_rn(alpha, gram_dist<DT>(ni, nj, g[e])) - dv)) < 0.f) {
                 const int at = atomicAdd(&L->pairs, 1);
                 if (at < GT_PAIRS) L->pair[at] = j_first ? (uint32_t)(j << 16 | i) : (uint32_t)(i << 16 | j);
             }
