@@ -161,11 +161,11 @@ hipError_t launch_sketch_probe(const float* x, long long n, int d, uint32_t* cou
 }
 
 // <c, l> and <c, h> of neighbours first + 16 p .. (p < NP) in the lanes of their numbers; KU loads of each in flight.
-// lq: this lane's part of operand A (rows l, h, l, h, ...; columns 16 (lane / 16) .. of each 64).  Where d is no multiple of 64 a lane
+// lq(k): this lane's part of operand A (rows l, h, l, h, ...; columns 64 k + 16 (lane / 16) ..).  Where d is no multiple of 64 a lane
 // group reads up to 48 bytes behind the codes: the rest of the record, whose stride is a multiple of 64 that holds the codes and the
 // 16 bytes of their scale.  The query is zero there.
-template <int NP, int KU>
-__device__ __forceinline__ void sketch_dots(const uint8_t* sk, const uint32_t stride, const int kb, const uint8_t* lq,
+template <int NP, int KU, typename Operand>
+__device__ __forceinline__ void sketch_dots(const uint8_t* sk, const uint32_t stride, const int kb, const Operand& lq,
                                             const uint32_t* cand_id, const int first, const int n, const int lane, int& il, int& ih) {
     const uint8_t* rec[NP];
     v4i acc[NP];
@@ -175,7 +175,7 @@ __device__ __forceinline__ void sketch_dots(const uint8_t* sk, const uint32_t st
         rec[p] = sk + (size_t)cand_id[c < n ? c : n - 1] * stride + (lane >> 4) * 16;
         acc[p] = v4i{0, 0, 0, 0};
     }
-    for (int k0 = 0; k0 < kb; k0 += KU) {
+    for (int k0 = 0; k0 < (KU == 4 ? 4 : kb); k0 += KU) {  // (KU = 4: kb <= 4)
         v4i b[NP][KU];
 #pragma unroll
         for (int p = 0; p < NP; p++)
@@ -187,7 +187,7 @@ __device__ __forceinline__ void sketch_dots(const uint8_t* sk, const uint32_t st
 #pragma unroll
         for (int u = 0; u < KU; u++)
             if (k0 + u < kb) {
-                const v4i aq = *reinterpret_cast<const v4i*>(lq + (size_t)(k0 + u) * 64);
+                const v4i aq = lq(k0 + u);
 #pragma unroll
                 for (int p = 0; p < NP; p++)
                     if (first + p * 16 < n) acc[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aq, b[p][u], acc[p], 0, 0, 0);
@@ -342,14 +342,17 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
     const int tag_bits = a.tag_bits;
     const uint32_t id_mask = (1u << (tag_bits + 30 - __builtin_clz((uint32_t)a.hash_slots))) - 1u;  // hash_slots / 2 sets
     const int plane = sketch_plane(a.sk_nch), kb = (a.sk_nch + 3) / 4;
-    uint8_t* const qpl = smem;
-    uint64_t* fr = reinterpret_cast<uint64_t*>(smem + 2 * plane);
+    constexpr bool HELD = KU == 4;  // the query's planes in 16 registers; they stand in the table's room until they are read
+    uint64_t* fr = reinterpret_cast<uint64_t*>(smem + (HELD ? 0 : 2 * plane));
     uint64_t* cand_key = fr + FCAP;
     uint32_t* cand_id = reinterpret_cast<uint32_t*>(cand_key + 64);
     uint32_t* tab = cand_id + 64;
-
-    for (int i = lane; i < a.hash_slots / 2; i += 64) tab[i] = JX_NONE_ID;
-    for (int i = lane; i < FCAP; i += 64) fr[i] = JX_EMPTY_KEY;
+    uint8_t* const qpl = HELD ? reinterpret_cast<uint8_t*>(tab) : smem;
+    const auto clear = [=]() __attribute__((always_inline)) {
+        for (int i = lane; i < a.hash_slots / 2; i += 64) tab[i] = JX_NONE_ID;
+        for (int i = lane; i < FCAP; i += 64) fr[i] = JX_EMPTY_KEY;
+    };
+    if constexpr (!HELD) clear();
 
     const int64_t qrec = qi + (qi >= a.q_skip ? 1 : 0);
     QueryRegs<K_F32, CPL, 0> q;
@@ -357,7 +360,20 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KU == 4
 
     const SketchQuery sq = sketch_query(a.ds.qrecs + qrec * a.ds.qrec_stride, a.ds.nch, kb, qpl, plane, lane);
     bool use = !sq.none;
-    const uint8_t* lq = qpl + (lane & 1) * plane + (lane >> 4) * 16;
+    const uint8_t* my_q = qpl + (lane & 1) * plane + (lane >> 4) * 16;
+    v4i held[4];
+    if constexpr (HELD) {
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < 4; k++) held[k] = k < kb ? *reinterpret_cast<const v4i*>(my_q + k * 64) : v4i{0, 0, 0, 0};
+        wave_sync();
+        clear();
+        wave_sync();
+    }
+    const auto lq = [&](const int k) __attribute__((always_inline)) {
+        if constexpr (HELD) return held[k];
+        else return *reinterpret_cast<const v4i*>(my_q + (size_t)k * 64);
+    };
 
     uint64_t fk[NREG];
 #pragma unroll
@@ -550,7 +566,8 @@ __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
     }
     if (use) {
         int il = 0, ih = 0;
-        const uint8_t* lq = qpl + (lane & 1) * plane + (lane >> 4) * 16;
+        const uint8_t* my_q = qpl + (lane & 1) * plane + (lane >> 4) * 16;
+        const auto lq = [=](const int k) __attribute__((always_inline)) { return *reinterpret_cast<const v4i*>(my_q + (size_t)k * 64); };
         if (m <= 48) {
             sketch_dots<3, 5>(a.sk, (uint32_t)a.sk_stride, kb, lq, L->cand_id, 0, m, lane, il, ih);
         } else {
@@ -631,15 +648,16 @@ static hipError_t launch_sketch_shape(BeamArgs a, hipStream_t st, char* name) {
     // wavefronts by LDS (build of 20,000 x 960, L = 128: 16 / 8 / 4 KB 33.2 / 32.3 / 33.9 ms; 1,500 queries at L = 200 2.19 /
     // 1.99 / 2.19 ms, but 5,000 3.52 / 3.68 / 4.00).  With 16 KB 1,792 queries of more than 128 entries are resident, and the
     // rest of a wide batch waited for them: 2,000 queries on 6,000 x 960, L = 256 1,506 -> 805 us
-    // 8 KB let 3,584 queries of vectors of at most 256 dimensions and of more than 64 entries be resident, 4 KB 4,096 (the
-    // kernel on whole vectors as many): 60,000 x 132, L = 128, 4,000 queries without copies / 8 / 4 KB 412 / 479 / 361 us, norms over
-    // three decades 491 / 606 / 501, 8,000 763 / 838 / 763, 10,000 985 / 1,048 / 995, normal data 3,214 / 1,615 / 1,683
-    const bool tight = SHORT && a.L > 64 && a.nq > 3584;
-    while (a.hash_slots > (tight ? 2048 : (a.L <= 128 || wide ? 4096 : 8192)) && a.tag_bits < 15) {
+    // Vectors of at most 256 dimensions: 8 KB as without copies; as the planes of the query take no room (HELD), 4,096 queries of 65 to
+    // 128 entries are resident, as without copies.  With the planes beside them 3,584 were, or 4 KB for the table: 60,000 x 132, L =
+    // 128, 10,000 queries without copies / 4 KB / this 880 / 779 / 746 us, normal data 3,288 / 1,686 / 1,544, 300,000 x 200 1,866 /
+    // 1,637 / 1,542 and 6,190 / 2,516 / 2,354; inner products by an extra dimension, where copies say nothing, 1M x 204 3,847 / 4,266 /
+    // 3,881
+    while (a.hash_slots > (a.L <= 128 || wide ? 4096 : 8192) && a.tag_bits < 15) {
         a.hash_slots /= 2;
         a.tag_bits++;
     }
-    const size_t sh0 = 2 * (size_t)sketch_plane(a.sk_nch) + 64 * 8 + 64 * 4 + table_bytes(a);
+    const size_t sh0 = (SHORT ? 0 : 2 * (size_t)sketch_plane(a.sk_nch)) + 64 * 8 + 64 * 4 + table_bytes(a);
     if (name) snprintf(name, 96, "beam_search_sketch_kernel<%d,%d,%d,%d,%d>", T, CPL, nreg, a.vis_cap ? 1 : 0, SHORT ? 4 : (wide ? 16 : 8));
 #define JX_LAUNCH(NR, VISIBLE)                                                                                          \
     {                                                                                                                   \

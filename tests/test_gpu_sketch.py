@@ -157,6 +157,21 @@ def test_counters_count_what_is_read(jx):
     assert st["rerank_bytes"] == 600 * 40 * 4 * d
 
 
+@pytest.mark.parametrize("d,L", [(132, 128), (200, 65), (256, 100)])
+def test_short_vectors_forget_no_more_than_without_copies(jx, d, L):
+    """The visited table of a full batch is the one that searches of whole vectors have (another lane mapping asks for these)."""
+    n = 10_000
+    x, q = (dev(np.rint(4 * random_data(m, d, np.float32, s))) for m, s in ((n, 83), (4200, 84)))  # exact in every order of sums
+    g = jx.Index(d, jx.F32, 64, 64, 1.2, capacity=n, max_batch=n)
+    g.insert(x)
+    ids0, dist0, st0 = g.search(q, 10, L, stats=True)
+    g.set_flags(jx.FLAG_LANES_WIDE)
+    ids, dist, st = g.search(q, 10, L, stats=True)
+    assert st0["beam_kernel"].startswith("beam_search_sketch_kernel<") and st["beam_kernel"].startswith("beam_search_kernel<")
+    assert torch.equal(ids, ids0) and torch.equal(dist, dist0)
+    assert (st["hops"], st["dist_evals"]) == (st0["hops"], st0["dist_evals"])
+
+
 @pytest.mark.parametrize("d", [200, 960])
 def test_switches_of_other_kernels_leave_the_copies_in_use(jx, d):
     """Two expansions per round and half the lanes per record are no forms of these searches, twice the lanes none of vectors of
