@@ -550,13 +550,14 @@ __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
     float4 meta = make_float4(0.f, 0.f, 0.f, 0.f);
     if (use) {
         meta = *reinterpret_cast<const float4*>(a.sk + (size_t)L->cand_id[lane < m ? lane : 0] * (uint32_t)a.sk_stride + (size_t)a.sk_nch * 16);
-        // Worth it where the estimates put half of the candidates farther beyond the k-th than both bounds are wide: else most
-        // vectors are read after all (fifth powers of normal values, 5,000 queries of d = 1536, 64 candidates: 76 us without copies,
-        // 157 with, 105 so; normal ones 176, 161, 180; a Gaussian mixture 253, 116, 117)
+        // Worth it where the estimates put a third of the candidates farther beyond the k-th than both bounds are wide: else most
+        // vectors are read after all.  10,000 queries, without copies / always / a half / a third / a quarter, us: 1M x 1536, 1-bit
+        // codes, 40 candidates 400 / 371 / 408 / 390 / 374, 1M x 960, 4 bits 237 / 226 / 228 / 218 / 220; 10,000 x 1536, 64, fifth
+        // powers of normal values 141 / 262 / 181 / 193 / 205, a Gaussian mixture 531 / 223 / 224 / 229 / 223
         const float est = lane < m ? a.cand_dist[(size_t)qi * a.cand_stride + lane] : 0.f;
         const float wide = 2.f * sqrtf(fmaxf(est, 0.f)) * meta.w;
         const float bar = __uint_as_float(readlane32(__float_as_uint(est + wide), a.k - 1));
-        use = __builtin_popcountll(ballot(lane < m && est - wide > bar)) * 2 >= m;
+        use = __builtin_popcountll(ballot(lane < m && est - wide > bar)) * 3 >= m;
     }
     SketchQuery sq;
     if (use) {

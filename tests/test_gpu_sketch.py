@@ -313,5 +313,7 @@ def test_rerank_reads_copies_where_the_estimates_are_spread(jx, d, bits, kind, s
         assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32)), (k, rr)
         assert out[1][2]["rerank_bytes"] == rr * nq * 4 * d
         read.append(out[0][2]["rerank_bytes"] / out[1][2]["rerank_bytes"])
-    # a third of the candidates asked for: copies are left alone where the estimates are close
-    assert (min(read[0], read[4]) < 0.8) if spread else (0.85 < read[2] <= 1 and 0.9 < read[5] <= 1), read
+    # A query that takes copies reads all m of them and k vectors at least.  Where the estimates are close fewer than half of the
+    # queries do, with a third of the candidates asked for
+    least = lambda k, m: 1 - 0.5 * (1 - k / m - stride / (4 * d))
+    assert (min(read[0], read[4]) < 0.8) if spread else (least(13, 40) < read[2] <= 1 and least(21, 64) < read[5] <= 1), read
