@@ -7,8 +7,8 @@
 // bound lies above the worst entry's distance cannot enter (a frontier changes by keys below the worst one only), and is
 // left out; the rest, 503 of 3,967 above, is evaluated on the vectors by eval_batch as in beam_search_kernel.  Frontier
 // sequence, results, expansion lists and number of expansions are that kernel's, bit for bit, whatever the codes are worth: a
-// loose bound costs evaluations, never an entry.  The number of neighbours looked at is not: the visited table is smaller here
-// (launch_sketch_shape) and forgets more of them.
+// loose bound costs evaluations, never an entry.  The number of neighbours looked at is not above 256 dimensions: the visited
+// table is smaller there (launch_sketch_shape) and forgets more of them.
 //
 // Bound: the gather.  Why matrix instructions: the query stands as 16-bit integers v = 256 h + l in rows of operand A (h
 // and l in turn, so that every lane group receives both sums), 16 neighbours' codes are operand B as they are loaded, and
