@@ -524,10 +524,16 @@ struct SketchRerankLds {
     float bound[64];
 };
 
-template <int T, int CPL>
-__global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
+// MANY: few loads in flight and four to six wavefronts per SIMD (76 to 103 registers), which hold a batch of 4,096 queries; else two
+// or three with many (149 to 169).  Whole searches at L = 64 of 4,000 queries on 20,000 vectors, 40 candidates, times as fast as
+// with whole vectors in the re-rank, two / four: d = 960 Gaussian mixtures 1.02 / 1.06, normal values 0.91 / 0.99, fifth powers of
+// them 0.89 / 0.96, d = 1536 1.07 / 1.09, 0.92 / 0.99, 0.90 / 0.96; 10,000 queries, d = 384 523 / 502, 588 / 551 and 380 / 344 us, d =
+// 960 1,195 / 1,185, 1,183 / 1,181 and 652 / 617.  A batch that leaves the card idle waits for its own loads: 64 candidates, 200
+// queries of d = 960, normal values 264 / 269 us
+template <int T, int CPL, bool MANY>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MANY ? 4 : 2, 8))) rerank_sketch_kernel(RerankArgs a) {
     constexpr int G = 64 / T;
-    constexpr int U0 = CPL == 2 ? 8 : (CPL == 4 ? 6 : 4);  // (few wavefronts per SIMD: the byte products take 180 registers)
+    constexpr int U0 = MANY ? (CPL == 6 ? 2 : 8 / CPL) : (CPL == 2 ? 8 : (CPL == 4 ? 6 : 4));
     constexpr int U = U0 < (64 / G) ? U0 : (64 / G);
     extern __shared__ __align__(16) unsigned char smem[];
     const int wave = threadIdx.x >> 6, lane = lane_id();
@@ -551,7 +557,7 @@ __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
     if (use) {
         meta = *reinterpret_cast<const float4*>(a.sk + (size_t)L->cand_id[lane < m ? lane : 0] * (uint32_t)a.sk_stride + (size_t)a.sk_nch * 16);
         // Worth it where the estimates put a third of the candidates farther beyond the k-th than both bounds are wide: else most
-        // vectors are read after all.  10,000 queries, without copies / always / a half / a third / a quarter, us: 1M x 1536, 1-bit
+        // vectors are read after all (a quarter: the same within 0.5 %).  Before MANY, 10,000 queries, without copies / always / a half / a third / a quarter, us: 1M x 1536, 1-bit
         // codes, 40 candidates 400 / 371 / 408 / 390 / 374, 1M x 960, 4 bits 237 / 226 / 228 / 218 / 220; 10,000 x 1536, 64, fifth
         // powers of normal values 141 / 262 / 181 / 193 / 205, a Gaussian mixture 531 / 223 / 224 / 229 / 223
         const float est = lane < m ? a.cand_dist[(size_t)qi * a.cand_stride + lane] : 0.f;
@@ -570,9 +576,9 @@ __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
         const uint8_t* my_q = qpl + (lane & 1) * plane + (lane >> 4) * 16;
         const auto lq = [=](const int k) __attribute__((always_inline)) { return *reinterpret_cast<const v4i*>(my_q + (size_t)k * 64); };
         if (m <= 48) {
-            sketch_dots<3, 5>(a.sk, (uint32_t)a.sk_stride, kb, lq, L->cand_id, 0, m, lane, il, ih);
+            sketch_dots<3, MANY ? 2 : 5>(a.sk, (uint32_t)a.sk_stride, kb, lq, L->cand_id, 0, m, lane, il, ih);
         } else {
-            for (int f = 0; f < m; f += 32) sketch_dots<2, 8>(a.sk, (uint32_t)a.sk_stride, kb, lq, L->cand_id, f, m, lane, il, ih);
+            for (int f = 0; f < m; f += 32) sketch_dots<2, MANY ? 3 : 8>(a.sk, (uint32_t)a.sk_stride, kb, lq, L->cand_id, f, m, lane, il, ih);
         }
         const float d2 = sketch_dist(sq, meta, il, ih), off = meta.w + sq.err;
         // upward: the slack twice (it stands below |x'|^2 and |q'|^2, whose sum it is 8e-6 of, X <= |x'| + 2 |m| sqrt(d))
@@ -622,17 +628,21 @@ __global__ void __launch_bounds__(256) rerank_sketch_kernel(RerankArgs a) {
 hipError_t launch_rerank_sketch(const RerankArgs& a, hipStream_t st, bool* done) {
     *done = false;
     const int nch = a.ds.nch;
-    // Whole vectors / this, us: 41 candidates for 40 neighbours, 10,000 queries 227 / 292; 50,000 x 256, 5,000 queries 33 / 35; Gaussian
-    // mixtures of d = 960 / 1536, 40 candidates, 2,100 queries 53 / 55 and 76 / 64, 4,500 99 / 80 and 148 / 100, 10,000 209 / 140 and
-    // 316 / 189, 64 candidates, 200 queries 42 / 27 and 60 / 38, 5,000 165 / 88 and 253 / 117; of d = 384, 40, 2,100 and 10,000 24 / 24
-    // and 79 / 68.  2,100 queries lose where copies say little (normal values, d = 960, 40 candidates 33 / 47)
-    if (!a.sk || a.rr > 64 || a.rr < 3 * a.k || nch <= 64 || nch > 384 || (a.nq < 4096 && a.rr <= 48)) return hipSuccess;
+    // Whole vectors / this before MANY, us: 41 candidates for 40 neighbours, 10,000 queries 227 / 292; 50,000 x 256, 5,000 queries 33 /
+    // 35; Gaussian mixtures of d = 960 / 1536, 64 candidates, 200 queries 42 / 27 and 60 / 38.  Fewer than 2,048 queries with 40
+    // candidates lose: 2,100, whole searches with MANY, Gaussian mixtures of d = 384 / 960 / 1536 227 / 225, 459 / 446, 455 / 432, normal
+    // values 241 / 245, 394 / 401, 404 / 413, fifth powers 164 / 166, 229 / 237, 264 / 274
+    if (!a.sk || a.rr > 64 || a.rr < 3 * a.k || nch <= 64 || nch > 384 || (a.nq < 2048 && a.rr <= 48)) return hipSuccess;
     *done = true;
     const size_t sh = 4 * (sizeof(SketchRerankLds) + 2 * (size_t)sketch_plane(a.sk_nch));
     const dim3 grid((unsigned)((a.nq + 3) / 4));
-    if (nch <= 128) hipLaunchKernelGGL((rerank_sketch_kernel<64, 2>), grid, dim3(256), sh, st, a);
-    else if (nch <= 256) hipLaunchKernelGGL((rerank_sketch_kernel<64, 4>), grid, dim3(256), sh, st, a);
-    else hipLaunchKernelGGL((rerank_sketch_kernel<64, 6>), grid, dim3(256), sh, st, a);
+#define JX_RR(C)                                                                                               \
+    if (nch <= 64 * C) {                                                                                       \
+        auto kern = a.nq >= 2048 ? rerank_sketch_kernel<64, C, true> : rerank_sketch_kernel<64, C, false>;     \
+        hipLaunchKernelGGL(kern, grid, dim3(256), sh, st, a);                                                  \
+    }
+    JX_RR(2) else JX_RR(4) else JX_RR(6)
+#undef JX_RR
     return hipGetLastError();
 }
 

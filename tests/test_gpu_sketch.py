@@ -102,12 +102,12 @@ def test_copies_follow_imports_inserts_and_compaction(jx):
 @pytest.mark.parametrize("d,n", [(288, 9000), (512, 9000), (960, 5000), (1536, 3000)])
 def test_rerank_reads_what_may_be_among_the_first(jx, d, n):
     """The re-rank that reads byte copies first returns, bit for bit, what the one on whole vectors returns, which keeps batches
-    of fewer than 4,096 queries with at most 48 candidates; with more candidates its ids are those of 64-bit distances.  Copies
+    of fewer than 2,048 queries with at most 48 candidates; with more candidates its ids are those of 64-bit distances.  Copies
     of one row and rows without a byte copy are among the candidates."""
     x = random_data(n, d, np.float32, 61)
     y = _mixed(n, d, 61, extremes=False)
     y[np.random.default_rng(64).permutation(n)[:9]] *= np.float32(1e17)
-    q = dev(np.concatenate([random_data(2800, d, np.float32, 62), _mixed(1400, d, 63)]))
+    q = dev(np.concatenate([random_data(1400, d, np.float32, 62), _mixed(700, d, 63)]))
     g = jx.Index(d, jx.F32, 48, 64, 1.2, capacity=n, max_batch=n, quant_bits=1)
     g.insert(dev(x))
     adj, entry = g.export_graph()[0], g.size()[1]
