@@ -658,13 +658,14 @@ static hipError_t launch_sketch_shape(BeamArgs a, hipStream_t st, char* name) {
     // what the visited table forgets costs a quarter of the bytes here, so a smaller one than the vectors ask for, and more
     // wavefronts by LDS (build of 20,000 x 960, L = 128: 16 / 8 / 4 KB 33.2 / 32.3 / 33.9 ms; 1,500 queries at L = 200 2.19 /
     // 1.99 / 2.19 ms, but 5,000 3.52 / 3.68 / 4.00).  With 16 KB 1,792 queries of more than 128 entries are resident, and the
-    // rest of a wide batch waited for them: 2,000 queries on 6,000 x 960, L = 256 1,506 -> 805 us
+    // rest of a wide batch waited for them: 2,000 queries on 6,000 x 960, L = 256 1,506 -> 805 us; of fewer none waits, and what the
+    // smaller table forgets makes the chain longer (300 queries on 30,000 x 960, L = 256 1,297 / 1,455)
     // Vectors of at most 256 dimensions: 8 KB as without copies; as the planes of the query take no room (HELD), 4,096 queries of 65 to
     // 128 entries are resident, as without copies.  With the planes beside them 3,584 were, or 4 KB for the table: 60,000 x 132, L =
     // 128, 10,000 queries without copies / 4 KB / this 880 / 779 / 746 us, normal data 3,288 / 1,686 / 1,544, 300,000 x 200 1,866 /
     // 1,637 / 1,542 and 6,190 / 2,516 / 2,354; inner products by an extra dimension, where copies say nothing, 1M x 204 3,847 / 4,266 /
     // 3,881
-    while (a.hash_slots > (a.L <= 128 || wide ? 4096 : 8192) && a.tag_bits < 15) {
+    while (a.hash_slots > (a.L <= 128 || (wide && a.nq > 1792) ? 4096 : 8192) && a.tag_bits < 15) {
         a.hash_slots /= 2;
         a.tag_bits++;
     }

@@ -172,6 +172,24 @@ def test_short_vectors_forget_no_more_than_without_copies(jx, d, L):
     assert (st["hops"], st["dist_evals"]) == (st0["hops"], st0["dist_evals"])
 
 
+@pytest.mark.parametrize("d,L", [(960, 256), (1536, 129)])
+def test_batches_that_are_all_resident_forget_no_more(jx, d, L):
+    """Wide frontiers: the visited table is halved for batches of 1,793 to 2,048 queries only, which all fit beside each other then."""
+    n = 6000
+    x, q = (dev(np.rint(4 * random_data(m, d, np.float32, s))) for m, s in ((n, 85), (2100, 86)))  # exact in every order of sums
+    g = jx.Index(d, jx.F32, 64, 64, 1.2, capacity=n, max_batch=n)
+    g.insert(x)
+    ids, dist, st = g.search(q, 10, L, stats=True)
+    assert st["beam_kernel"].startswith("beam_search_sketch_kernel<")
+    for at in (1050, 1792, 1793, 2048):
+        parts = [g.search(part.contiguous(), 10, L, stats=True) for part in (q[:at], q[at:])]
+        assert all(torch.equal(torch.cat([p[i] for p in parts]), (ids, dist)[i]) for i in (0, 1)), at
+        assert sum(p[2]["hops"] for p in parts) == st["hops"], at
+        if at == 1050:
+            assert all(p[2]["beam_kernel"].startswith("beam_search_sketch_kernel<") for p in parts)
+            assert sum(p[2]["dist_evals"] for p in parts) == st["dist_evals"]
+
+
 @pytest.mark.parametrize("d", [200, 960])
 def test_switches_of_other_kernels_leave_the_copies_in_use(jx, d):
     """Two expansions per round and half the lanes per record are no forms of these searches, twice the lanes none of vectors of
